@@ -127,7 +127,6 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
     node_bwd = ("mfma", N * (3 * row + 4) + T * w2, 4.0 * N * d * d)
     out_dst = row if layer == "hgt" else r32                                  # HGT's Z / dQ are intermediates
     agg_dst = ("hbm", E * (row + 4 + 4 * H) + N * (out_dst + 8), 2.0 * E * d)  # row + in_pair + coefficient(s); out row + item
-    agg_pair = ("hbm", E * (row + 8 + 4 * H) + P * (row + 8), 2.0 * E * d)    # row + out_epos + out_dst + coefficient(s)
     table = {
         # RGAT: + s_src per pair and head; backward also reads ds_src
         "typed_linear_fwd": ("mfma", pair_fwd[1] + (P * 4 * H if layer == "rgat" and not fused else 0), pair_fwd[2]),
@@ -169,12 +168,13 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
         "node_linear_out_bwd": node_bwd,
         "pair_linear_att": pair_fwd, "pair_linear_msg": pair_fwd,
         "pair_linear_att_bwd": pair_bwd, "pair_linear_msg_bwd": pair_bwd,
-        # with the softmax in the same walk: + (max, sum) kept in registers; the weights overwrite the logits
-        # (one more 4-byte store per edge and head for the destinations of more than four edges, counted for all)
-        "hgt_edge_logit": ("hbm", E * (row + 4 + 8 * H) + N * (row + 8), 2.0 * E * d + 10.0 * E * H),
-        "hgt_edge_dot_bwd": ("hbm", E * (row + 4 + 8 * H) + N * (2 * row + 8), 2.0 * E * d),
-        "hgt_softmax": ("hbm", E * H * 8 + N * 8, 10.0 * E * H),
-        "aggregate_bwd_msg": agg_pair, "aggregate_bwd_key": agg_pair, "aggregate_bwd_query": agg_dst,
+        # the walks gather the key and the message row of a pair together (2 rows per edge).  Forward: + pair id; per node the
+        # query row, the result row, (max, sum) per head and the item.  Backward: + pair id and the (att, dl) pair per head;
+        # per node the query, gradient and result rows in, dQ out.  Pair-major: the query and gradient rows of the edge's
+        # destination, position, destination and the (att, dl) pair per head; per pair the two gradient rows
+        "hgt_attend_fwd": ("hbm", E * (2 * row + 4) + N * (2 * row + 8 + 8 * H), 4.0 * E * d + 10.0 * E * H),
+        "hgt_attend_bwd": ("hbm", E * (2 * row + 4 + 8 * H) + N * (4 * row + 8 + 8 * H), 6.0 * E * d),
+        "hgt_pair_bwd": ("hbm", E * (2 * row + 8 + 8 * H) + P * (2 * row + 8), 4.0 * E * d),
     }
     return table.get(name)
 

@@ -70,10 +70,6 @@ __device__ __forceinline__ Tv group_lane(Tv v, int lane) {
     }
     return __shfl(v, lane, W);
 }
-__device__ __forceinline__ float group_sum_dyn(float v, int w) {
-    for (int o = w / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));

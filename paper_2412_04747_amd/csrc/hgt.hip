@@ -1,9 +1,7 @@
-// Kernels of the HGT layer: block-diagonal expansion of the per-(relation, head) matrices, the
-// per-head edge logits, the per-head edge softmax and the per-head backward edge dot.
-// (Caption of the thesis figure "HGT and RGAT layer": attention of HGT is an edgewise dot
-// product between the relation-transformed key of the source and the query of the
-// destination; the message depends only on (source node, edge type), so both are stored
-// once per pair.)
+// Weight kernels of the HGT layer: block-diagonal expansion of the per-(relation, head) matrices, folding of the node
+// linears into them, and their backward.  (Caption of the thesis figure "HGT and RGAT layer": attention of HGT is an
+// edgewise dot product between the relation-transformed key of the source and the query of the destination; the message
+// depends only on (source node, edge type), so both are stored once per pair.  The edge walks are in hgt_walk.hip.)
 //
 // The d_head x d_head matrices W[r][h] are expanded to one block-diagonal d x d matrix per
 // relation so that the relation-segmented typed-linear kernel serves them unchanged; with
@@ -137,227 +135,6 @@ __global__ void hgt_fold_bwd_node_kernel(int T, int R, int d, int H, const int32
     dWnode[i] = s;
 }
 
-// logit[e][h] = Ka[pair_e][h] . Q[v][h]   (Ka already carries mu / sqrt(dh)); TI = storage type of the rows.
-// SM (heads of at least four lanes): the per-head softmax over the destination's edges rides along.  The lanes of a
-// head keep a running maximum and the sum of exp(logit - maximum) over the batches; a whole destination then
-// turns the logits it has just written into weights (each lane re-reads the entries it stored itself), a piece of a
-// cut destination stores its (maximum, sum) per head for the finish kernel, which normalises the pieces' entries.
-template <int D, typename TI, bool SM>
-__global__ __launch_bounds__(256) void hgt_edge_logit_kernel(Items it, int H, const int32_t* __restrict__ in_pair,
-                                                             const TI* __restrict__ Ka, const TI* __restrict__ Q,
-                                                             float* logit, float* __restrict__ part_m,
-                                                             float* __restrict__ part_s) {
-    constexpr int V = RowT<TI>::V, LPR = D / V, IPB = 256 / LPR;
-    const int i = blockIdx.x * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
-    if (i >= it.n) return;
-    const int b = it.beg[i], e = it.end[i];
-    if (e == b) return;
-    const int lph = LPR / H, head = cv / lph;
-    float q[V];
-    load_cols(Q + (size_t)it.row[i] * D + cv * V, q);
-    // pair ids run one batch of four ahead of the rows (positions past the end repeat the last edge)
-    int pr[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) pr[u] = in_pair[min(b + u, e - 1)];
-    float mx = -INFINITY, sum = 0.f;
-    const int sl = SM ? it.slot[i] : -1;
-    const bool one = SM && e - b <= 4 && sl < 0;
-    for (int j = b; j < e; j += 4) {
-        float k[4][V];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) load_cols(Ka + (size_t)pr[u] * D + cv * V, k[u]);
-        if (j + 4 < e) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) pr[u] = in_pair[min(j + 4 + u, e - 1)];
-        }
-        // lane t < 4 of a head's lanes stores edge j + t (every lane of the head holds all four sums), so the
-        // 4 x H results of a batch leave in one store instruction; heads of fewer than 4 lanes store one by one
-        float mine = 0.f, sv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float s = group_sum_dyn(dot_cols(q, k[u]), lph);
-            sv[u] = j + u < e ? s : -INFINITY;
-            if (lph >= 4) { if (cv % lph == u) mine = s; }
-            else if (cv % lph == 0 && j + u < e) logit[(size_t)(j + u) * H + head] = s;
-        }
-        if (SM) {
-            const float mn = fmaxf(fmaxf(mx, fmaxf(sv[0], sv[1])), fmaxf(sv[2], sv[3]));     // sv[0] is finite: j < e
-            sum = sum * __expf(mx - mn) + ((__expf(sv[0] - mn) + __expf(sv[1] - mn)) + (__expf(sv[2] - mn) + __expf(sv[3] - mn)));
-            mx = mn;
-            if (one) mine = __expf(mine - mx) / sum;      // a whole destination of up to four edges: the weights at once
-        }
-        if (lph >= 4 && cv % lph < 4 && j + cv % lph < e) logit[(size_t)(j + cv % lph) * H + head] = mine;
-    }
-    if (SM) {
-        if (one) return;
-        const int t = cv % lph;
-        if (sl >= 0) {
-            if (t == 0) {
-                part_m[(size_t)sl * H + head] = mx;
-                part_s[(size_t)sl * H + head] = sum;
-            }
-            return;
-        }
-        if (t >= 4) return;
-        const float inv = 1.f / sum;
-        for (int j = b + t; j < e; j += 4) {
-            float* x = logit + (size_t)j * H + head;
-            *x = __expf(*x - mx) * inv;
-        }
-    }
-}
-
-// Per-head softmax of att[e][h] (holding logits on entry) over each destination's edges, as a pass of its own: for
-// the shapes whose heads span fewer than four lanes (bf16 rows with 16 columns per head); the others take the
-// softmax in the logit walk.
-// Short nodes: one lane per (node, head).  Long items and pieces of cut nodes: one wavefront
-// per item, heads in turn; pieces store (max, sum) per head for the finish kernel.
-__device__ __forceinline__ float soft_out(float l, float m, float inv) { return expf(l - m) * inv; }
-__global__ __launch_bounds__(256) void hgt_softmax_kernel(int N, int H, const int32_t* __restrict__ in_ptr,
-                                                          float* __restrict__ att) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)N * H) return;
-    const int lh = 31 - __clz(H);                 // the head count is a power of two
-    const int v = (int)(t >> lh), h = (int)(t & (H - 1));
-    const int b = in_ptr[v], len = in_ptr[v + 1] - b;
-    if (len == 0 || len > kSerialMax) return;
-    float l[kSerialMax];               // the logits stay in registers: one read and one write of att
-#pragma unroll
-    for (int c = 0; c < kSerialMax; c += 8) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) l[c + u] = -INFINITY;
-        if (c < len) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (c + u < len) l[c + u] = att[(size_t)(b + c + u) * H + h];
-        }
-    }
-    float m = -INFINITY, s = 0.f;
-#pragma unroll
-    for (int k = 0; k < kSerialMax; ++k) m = fmaxf(m, l[k]);
-#pragma unroll
-    for (int k = 0; k < kSerialMax; ++k) s += expf(l[k] - m);
-    const float inv = 1.f / s;
-#pragma unroll
-    for (int k = 0; k < kSerialMax; ++k)
-        if (k < len) att[(size_t)(b + k) * H + h] = soft_out(l[k], m, inv);
-}
-__global__ __launch_bounds__(256) void hgt_softmax_long_kernel(Items it, int n_long, const int32_t* __restrict__ long_item,
-                                                               int H, float* __restrict__ att, float* __restrict__ part_m,
-                                                               float* __restrict__ part_s) {
-    constexpr int PER = kItemMax / 64;     // an item has at most kItemMax entries
-    const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (w >= n_long) return;
-    const int i = long_item[w];
-    const int bb = it.beg[i], ee = it.end[i], sl = it.slot[i];
-    for (int h = 0; h < H; ++h) {
-        float l[PER];
-        float m = -INFINITY, s = 0.f;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int j = bb + lane + 64 * u;
-            l[u] = j < ee ? att[(size_t)j * H + h] : -INFINITY;
-            m = fmaxf(m, l[u]);
-        }
-        m = wave_max(m);
-#pragma unroll
-        for (int u = 0; u < PER; ++u) s += expf(l[u] - m);
-        s = group_sum<64>(s);
-        if (sl < 0) {
-            const float inv = 1.f / s;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int j = bb + lane + 64 * u;
-                if (j < ee) att[(size_t)j * H + h] = soft_out(l[u], m, inv);
-            }
-        } else if (lane == 0) {
-            part_m[(size_t)sl * H + h] = m;
-            part_s[(size_t)sl * H + h] = s;
-        }
-    }
-}
-// Cut nodes: one wavefront per piece.  The head count is a power of two, so lane l always meets head
-// l & (H - 1): it combines that head's (m, sum) over the node's pieces (the lanes of a head take the
-// pieces in turn and are then reduced across the wavefront), and the piece's att entries, H per edge
-// and contiguous, are normalised with consecutive lanes on consecutive addresses.
-__global__ void hgt_softmax_finish_kernel(int num_partials, const int32_t* __restrict__ part_item,
-                                          const int32_t* __restrict__ part_split,
-                                          const int32_t* __restrict__ split_ptr, Items it, int H,
-                                          const float* __restrict__ part_m, const float* __restrict__ part_s,
-                                          float* __restrict__ att) {
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (t >= num_partials) return;
-    const int sp = part_split[t];
-    const int p0 = split_ptr[sp], p1 = split_ptr[sp + 1];
-    const int item = part_item[t];
-    const int lh = 31 - __clz(H), h = lane & (H - 1), step = 64 >> lh;
-    float m = -INFINITY;
-    for (int p = p0 + (lane >> lh); p < p1; p += step) m = fmaxf(m, part_m[(size_t)p * H + h]);
-    for (int o = 32; o >= H; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    float s = 0.f;
-    for (int p = p0 + (lane >> lh); p < p1; p += step) s += part_s[(size_t)p * H + h] * expf(part_m[(size_t)p * H + h] - m);
-    for (int o = 32; o >= H; o >>= 1) s += __shfl_xor(s, o);
-    const float inv = 1.f / s;
-    const size_t a0 = (size_t)it.beg[item] * H, a1 = (size_t)it.end[item] * H;
-    for (size_t x = a0 + lane; x < a1; x += 64) att[x] = soft_out(att[x], m, inv);   // a0 and 64 are multiples of H: entry x is head h
-}
-
-// dl[e][h] = att[e][h] * (dZ[v][h] . M[pair_e][h] - dZ[v][h] . Z[v][h])
-// (the second term is sum_e att_e g_e because Z[v][h] = sum_e att_e M[pair_e][h]).
-template <int D, typename TI>
-__global__ __launch_bounds__(256) void hgt_edge_dot_bwd_kernel(Items it, int H, const int32_t* __restrict__ in_pair,
-                                                               const float* __restrict__ att,
-                                                               const TI* __restrict__ M, const TI* __restrict__ dZ,
-                                                               const TI* __restrict__ Z, float* __restrict__ dl) {
-    constexpr int V = RowT<TI>::V, LPR = D / V, IPB = 256 / LPR;
-    const int i = blockIdx.x * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
-    if (i >= it.n) return;
-    const int b = it.beg[i], e = it.end[i];
-    if (e == b) return;
-    const int lph = LPR / H, head = cv / lph;
-    const size_t v = (size_t)it.row[i];
-    float gz[V], zz[V];
-    load_cols(dZ + v * D + cv * V, gz);
-    load_cols(Z + v * D + cv * V, zz);
-    // pair ids and attention weights run one batch of four ahead of the rows
-    int pr[4];
-    float an[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int jj = min(b + u, e - 1);
-        pr[u] = in_pair[jj];
-        an[u] = att[(size_t)jj * H + head];
-    }
-    const float gbar = group_sum_dyn(dot_cols(gz, zz), lph);
-    for (int j = b; j < e; j += 4) {
-        float mm[4][V];
-        float a[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            load_cols(M + (size_t)pr[u] * D + cv * V, mm[u]);
-            a[u] = an[u];
-        }
-        if (j + 4 < e) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int jj = min(j + 4 + u, e - 1);
-                pr[u] = in_pair[jj];
-                an[u] = att[(size_t)jj * H + head];
-            }
-        }
-        float mine = 0.f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float g = group_sum_dyn(dot_cols(gz, mm[u]), lph);
-            const float w = a[u];
-            if (lph >= 4) { if (cv % lph == u) mine = w * (g - gbar); }
-            else if (cv % lph == 0 && j + u < e) dl[(size_t)(j + u) * H + head] = w * (g - gbar);
-        }
-        // one store instruction for the 4 x H results of the batch (see hgt_edge_logit_kernel)
-        if (lph >= 4 && cv % lph < 4 && j + cv % lph < e) dl[(size_t)(j + cv % lph) * H + head] = mine;
-    }
-}
-
 __global__ void add3_kernel(size_t n, const float* __restrict__ a, const float* __restrict__ b,
                             const float* __restrict__ c, float* __restrict__ out) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -377,85 +154,6 @@ rgnn_status_t hgt_extract(int R, int d, int H, const float* dWbd, const float* W
                           float* dmu, hipStream_t st) {
     KernelTimer kt(st, "hgt_extract");
     hipLaunchKernelGGL(hgt_extract_kernel, dim3(R * H), dim3(256), 0, st, d, H, dWbd, W, mu, scaled, dW, dmu);
-    RGNN_CHECK_LAUNCH();
-    return RGNN_OK;
-}
-// part_m / part_s given: the softmax is taken in the same walk (logit then holds the attention weights) where a head
-// spans at least four lanes; otherwise, and without them, logit holds the logits and hgt_softmax follows.
-static bool hgt_softmax_rides(int D, int H, int rows_bf16) { return (D / (rows_bf16 ? 8 : 4)) / H >= 4; }
-rgnn_status_t hgt_edge_logit(const rgnn_graph* g, int D, int H, const void* Ka, const void* Q, float* logit,
-                             hipStream_t st, int rows_bf16, float* part_m, float* part_s) {
-    const ItemList& L = g->dst_items;
-    if (L.num_items == 0 || g->E == 0) return RGNN_OK;
-    const bool sm = part_m && part_s && hgt_softmax_rides(D, H, rows_bf16);
-    {
-        KernelTimer kt(st, "hgt_edge_logit");
-        if (rows_bf16) {
-            if (D != 128) RGNN_FAIL(RGNN_EUNSUPPORTED, "bf16 rows need width 128, got %d", D);
-            const dim3 grid(blocks_for(L.num_items, 256 / (128 / 8)));
-            if (sm)
-                hipLaunchKernelGGL((hgt_edge_logit_kernel<128, bf16_t, true>), grid, dim3(256), 0, st, dev_items(L), H, g->idx[RGNN_IDX_IN_PAIR],
-                                   static_cast<const bf16_t*>(Ka), static_cast<const bf16_t*>(Q), logit, part_m, part_s);
-            else
-                hipLaunchKernelGGL((hgt_edge_logit_kernel<128, bf16_t, false>), grid, dim3(256), 0, st, dev_items(L), H, g->idx[RGNN_IDX_IN_PAIR],
-                                   static_cast<const bf16_t*>(Ka), static_cast<const bf16_t*>(Q), logit, part_m, part_s);
-        } else if (sm) {
-            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((hgt_edge_logit_kernel<DD, float, true>), dim3(blocks_for(L.num_items, 256 / (DD / 4))),
-                                                  dim3(256), 0, st, dev_items(L), H, g->idx[RGNN_IDX_IN_PAIR],
-                                                  static_cast<const float*>(Ka), static_cast<const float*>(Q), logit, part_m, part_s));
-        } else {
-            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((hgt_edge_logit_kernel<DD, float, false>), dim3(blocks_for(L.num_items, 256 / (DD / 4))),
-                                                  dim3(256), 0, st, dev_items(L), H, g->idx[RGNN_IDX_IN_PAIR],
-                                                  static_cast<const float*>(Ka), static_cast<const float*>(Q), logit, part_m, part_s));
-        }
-        RGNN_CHECK_LAUNCH();
-    }
-    if (sm) return hgt_softmax_finish(g, H, logit, part_m, part_s, st);
-    if (part_m && part_s) return hgt_softmax(g, H, logit, part_m, part_s, st);
-    return RGNN_OK;
-}
-rgnn_status_t hgt_softmax(const rgnn_graph* g, int H, float* att, float* part_m, float* part_s, hipStream_t st) {
-    const ItemList& L = g->dst_items;
-    if (g->E == 0) return RGNN_OK;
-    {
-        KernelTimer kt(st, "hgt_softmax");
-        hipLaunchKernelGGL(hgt_softmax_kernel, dim3(blocks_for((size_t)g->N * H, 256)), dim3(256), 0, st, (int)g->N, H,
-                           g->idx[RGNN_IDX_IN_PTR], att);
-        RGNN_CHECK_LAUNCH();
-        if (L.num_long > 0) {
-            hipLaunchKernelGGL(hgt_softmax_long_kernel, dim3(blocks_for((size_t)L.num_long * 64, 256)), dim3(256), 0, st,
-                               dev_items(L), L.num_long, L.long_item, H, att, part_m, part_s);
-            RGNN_CHECK_LAUNCH();
-        }
-    }
-    return hgt_softmax_finish(g, H, att, part_m, part_s, st);
-}
-rgnn_status_t hgt_softmax_finish(const rgnn_graph* g, int H, float* att, const float* part_m, const float* part_s, hipStream_t st) {
-    const ItemList& L = g->dst_items;
-    if (L.num_partials == 0) return RGNN_OK;
-    KernelTimer kt(st, "hgt_softmax.finish");
-    hipLaunchKernelGGL(hgt_softmax_finish_kernel, dim3(blocks_for((size_t)L.num_partials * 64, 256)), dim3(256), 0,
-                       st, L.num_partials, L.part_item, L.part_split, L.split_ptr, dev_items(L), H, part_m, part_s,
-                       att);
-    RGNN_CHECK_LAUNCH();
-    return RGNN_OK;
-}
-rgnn_status_t hgt_edge_dot_bwd(const rgnn_graph* g, int D, int H, const float* att, const void* M, const void* dZ,
-                               const void* Z, float* dl, hipStream_t st, int rows_bf16) {
-    const ItemList& L = g->dst_items;
-    if (L.num_items == 0 || g->E == 0) return RGNN_OK;
-    KernelTimer kt(st, "hgt_edge_dot_bwd");
-    if (rows_bf16) {
-        if (D != 128) RGNN_FAIL(RGNN_EUNSUPPORTED, "bf16 rows need width 128, got %d", D);
-        hipLaunchKernelGGL((hgt_edge_dot_bwd_kernel<128, bf16_t>), dim3(blocks_for(L.num_items, 256 / (128 / 8))), dim3(256), 0,
-                           st, dev_items(L), H, g->idx[RGNN_IDX_IN_PAIR], att, static_cast<const bf16_t*>(M),
-                           static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(Z), dl);
-    } else {
-        RGNN_DISPATCH_D(D, hipLaunchKernelGGL((hgt_edge_dot_bwd_kernel<DD, float>), dim3(blocks_for(L.num_items, 256 / (DD / 4))),
-                                              dim3(256), 0, st, dev_items(L), H, g->idx[RGNN_IDX_IN_PAIR], att,
-                                              static_cast<const float*>(M), static_cast<const float*>(dZ),
-                                              static_cast<const float*>(Z), dl));
-    }
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }

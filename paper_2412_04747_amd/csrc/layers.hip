@@ -214,11 +214,12 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // of the nodes are folded into the per-relation weights (Wf = Wk[type] Watt[r], Wv[type] Wmsg[r]), so
 // K, V and their gradients do not exist and the per-pair rows come straight from X.
 inline bool hgt_folded(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_hgt_folded(g->rel_src_tied, d->flags); }
-struct HgtSaved { void* K; void* Q; void* V; void* Z; void* Ka; void* M; float* att; };
-struct HgtFwdWs { float* Wbd_att; float* Wbd_msg; float* Wf_att; float* Wf_msg; float* part_m; float* part_s; float* partial; };
+// KM holds the key row and the message row of a pair side by side; ms the (max, sum) of every (destination, head) softmax.
+struct HgtSaved { void* K; void* Q; void* V; void* Z; void* KM; float* ms; };
+struct HgtFwdWs { float* Wbd_att; float* Wbd_msg; float* Wf_att; float* Wf_msg; float* part_ms; float* partial; };
 struct HgtBwdWs {
     float* Wbd_att; float* Wbd_msg; float* dWbd_att; float* dWbd_msg; float* Wf_att; float* Wf_msg; float* dWf_att;
-    float* dWf_msg; void* dZ; float* dl; void* dM; void* dKa;
+    float* dWf_msg; void* dZ; float* adl; void* dKM;
     void* dQ; void* dKp; void* dVp; void* dK; void* dV; float* dXk; float* dXq; float* dXv; float* tl_part;
     float* partial;
     float* acc_node[4]; float* acc_rel[2]; float* acc_mu;     // RGNN_FLAG_ACCUMULATE: dWk, dWq, dWv, dWo; dWatt, dWmsg; dmu
@@ -229,8 +230,8 @@ size_t carve_hgt_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* 
     const bool h = rows_bf16(d);
     const size_t nd = (size_t)g->N * d->d_out, pd = (size_t)g->P * d->d_out, kv = hgt_folded(g, d) ? 0 : nd;
     s->K = c.rows(kv, h); s->Q = c.rows(nd, h); s->V = c.rows(kv, h); s->Z = c.rows(nd, h);
-    s->Ka = c.rows(pd, h); s->M = c.rows(pd, h);
-    s->att = c.take<float>((size_t)g->E * d->heads);
+    s->KM = c.rows(2 * pd, h);
+    s->ms = c.take<float>(2 * (size_t)g->N * d->heads);
     return c.off;
 }
 size_t carve_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, HgtFwdWs* w) {
@@ -238,8 +239,7 @@ size_t carve_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     const size_t rdd = (size_t)g->R * d->d_out * d->d_out, fdd = hgt_folded(g, d) ? rdd : 0;
     w->Wbd_att = c.take<float>(rdd); w->Wbd_msg = c.take<float>(rdd);
     w->Wf_att = c.take<float>(fdd); w->Wf_msg = c.take<float>(fdd);
-    w->part_m = c.take<float>((size_t)g->dst_items.num_partials * d->heads);
-    w->part_s = c.take<float>((size_t)g->dst_items.num_partials * d->heads);
+    w->part_ms = c.take<float>(2 * (size_t)g->dst_items.num_partials * d->heads);
     w->partial = c.take<float>((size_t)g->dst_items.num_partials * d->d_out);
     return c.off;
 }
@@ -252,14 +252,14 @@ size_t carve_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     w->dWbd_att = c.take<float>(rdd); w->dWbd_msg = c.take<float>(rdd);
     w->Wf_att = c.take<float>(fold ? rdd : 0); w->Wf_msg = c.take<float>(fold ? rdd : 0);
     w->dWf_att = c.take<float>(fold ? rdd : 0); w->dWf_msg = c.take<float>(fold ? rdd : 0);
-    w->dZ = c.rows(nd, h); w->dl = c.take<float>((size_t)g->E * d->heads);
-    w->dM = c.rows(pd, h); w->dKa = c.rows(pd, h); w->dQ = c.rows(nd, h);
+    w->dZ = c.rows(nd, h); w->adl = c.take<float>(2 * (size_t)g->E * d->heads);
+    w->dKM = c.rows(2 * pd, h); w->dQ = c.rows(nd, h);
     w->dKp = c.rows(pd, h); w->dVp = c.rows(pd, h);
     w->dK = c.rows(fold ? 0 : nd, h); w->dV = c.rows(fold ? 0 : nd, h);
     w->dXk = c.take<float>(h || fold ? 0 : nd); w->dXq = c.take<float>(h && !fold ? 0 : nd); w->dXv = c.take<float>(h || fold ? 0 : nd);
     w->tl_part = c.take<float>(std::max(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles),
                                         typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->node_tiles)));
-    w->partial = c.take<float>((size_t)std::max(g->pair_items.num_partials, g->dst_items.num_partials) * D);
+    w->partial = c.take<float>(std::max(2 * (size_t)g->pair_items.num_partials, (size_t)g->dst_items.num_partials) * D);
     const bool acc = grads_accumulate(d);
     const size_t dh = D / d->heads;
     for (int i = 0; i < 4; ++i) w->acc_node[i] = acc ? c.take<float>((size_t)g->T * D * D) : nullptr;
@@ -300,20 +300,22 @@ void* saved_or_scratch(const rgnn_graph_t* g, int layer, const rgnn_layer_desc_t
 // the weight has to be split, and in the fp32 kernels, loading a segment's weight costs more and one
 // resident round of long chunks (`wide`) wins.
 // d_in (fp32 kernels only): width of the input rows when it differs from the output width d.
+// y_stride: the output rows are y_stride * d elements apart.
 rgnn_status_t tl_fwd(bool bf16, const rgnn::TileList* tiles, const rgnn::TileList* wide, int d, const float* A32,
                      const void* A16, const int32_t* gather, int scatter, const float* W32, const void* W16, void* Y,
-                     bool y16, const char* label, hipStream_t st, int d_in = 0) {
+                     bool y16, const char* label, hipStream_t st, int d_in = 0, int y_stride = 1) {
     if (d_in == 0) d_in = d;
     if (bf16) {
         if (d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear on the bf16 matrix cores: equal widths only");
         TypedLinearBf16Args a{};
         a.tiles = W16 ? tiles : wide; a.A = A16 ? A16 : A32; a.a_bf16 = A16 != nullptr; a.gather = gather; a.scatter_out = scatter;
         a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.Y = Y; a.y_bf16 = y16; a.label = label;
+        a.y_stride = y_stride;
         return typed_linear_bf16(d, a, st);
     }
     TypedLinearArgs a{};
     a.tiles = wide; a.X = A32; a.gather = gather; a.W = W32; a.Y = static_cast<float*>(Y); a.scatter_out = scatter;
-    a.label = label;
+    a.label = label; a.y_stride = y_stride;
     return typed_linear_fwd(d_in, d, a, st);
 }
 
@@ -324,13 +326,14 @@ rgnn_status_t tl_fwd(bool bf16, const rgnn::TileList* tiles, const rgnn::TileLis
 //     the slot reduction.  dXrow is stored as bf16 (dx16) or fp32.
 //   otherwise: the fused fp32 kernel on fp32 X, W, dY.
 //   wide: the same tiles in fewer chunks, for the weight-gradient kernel;  dx_acc: dXrow += (fp32 dXrow, rows16)
+//   dy_stride: the rows of dY are dy_stride * d elements apart (dY not gathered)
 //   ysel / y_alt (rows16, dY not gathered): row i of dY is dY[ysel[i]], or y_alt[ysel[i] & 0x7FFFFFFF] when the
 //     top bit of ysel[i] is set; with yscale it is also multiplied by yscale[i]
 rgnn_status_t tl_bwd(bool rows16, const rgnn::TileList* tiles, const rgnn::TileList* wide, int d, const void* X,
                      const int32_t* gather, int both_gathered, const float* W32, const void* W16, const void* dY,
                      void* dXrow, bool dx16, float* dW, float* part, const char* label, hipStream_t st,
                      bool dx_acc = false, const int32_t* ysel = nullptr, const void* y_alt = nullptr,
-                     const float* yscale = nullptr, int d_in = 0) {
+                     const float* yscale = nullptr, int d_in = 0, int dy_stride = 1) {
     if (d_in == 0) d_in = d;
     if (rows16 && d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward on the bf16 matrix cores: equal widths only");
     if (ysel && (!rows16 || both_gathered)) RGNN_FAIL(RGNN_EUNSUPPORTED, "row selector: bf16 rows and ungathered dY only");
@@ -339,10 +342,11 @@ rgnn_status_t tl_bwd(bool rows16, const rgnn::TileList* tiles, const rgnn::TileL
         a.tiles = W16 ? tiles : wide; a.A = dY; a.a_bf16 = 1; a.gather = both_gathered ? gather : ysel; a.scatter_out = both_gathered;
         a.A_alt = y_alt; a.rowscale = ysel ? yscale : nullptr;
         a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.transpose_w = 1; a.Y = dXrow; a.y_bf16 = dx16; a.accumulate = dx_acc; a.label = label;
+        a.a_stride = dy_stride;
         RGNN_TRY(typed_linear_bf16(d, a, st));
         TypedLinearWgradBf16Args w{};
         w.tiles = wide; w.X = X; w.gather = gather; w.dy_gathered = both_gathered; w.dY = dY; w.part = part;
-        w.label = wgrad_label(label); w.ysel = ysel; w.dY_alt = y_alt; w.yscale = yscale;
+        w.label = wgrad_label(label); w.ysel = ysel; w.dY_alt = y_alt; w.yscale = yscale; w.dy_stride = dy_stride;
         RGNN_TRY(typed_linear_wgrad_bf16(d, w, st));
         return typed_linear_slot_reduce(d, d, *wide, part, dW, nullptr, st);
     }
@@ -350,7 +354,7 @@ rgnn_status_t tl_bwd(bool rows16, const rgnn::TileList* tiles, const rgnn::TileL
     TypedLinearBwdArgs b{};
     b.tiles = wide; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
     b.dy_gathered = both_gathered; b.dXrow = static_cast<float*>(dXrow); b.scatter_dx = both_gathered; b.dW = dW;
-    b.part = part; b.label = label;
+    b.part = part; b.label = label; b.dy_stride = dy_stride;
     return typed_linear_bwd(d_in, d, b, st);
 }
 
@@ -774,7 +778,8 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
     // 2. per (relation, head) matrices as block-diagonal d x d weights; mu / sqrt(dh) folded into the attention one
     RGNN_TRY(hgt_expand(g->R, D, H, Watt32, mu32, 1, w.Wbd_att, st));
     RGNN_TRY(hgt_expand(g->R, D, H, Wmsg32, nullptr, 0, w.Wbd_msg, st));
-    // 3. compact per pair: Ka[p] = K[src_p] Watt[r], M[p] = V[src_p] Wmsg[r]
+    // 3. compact per pair, side by side in KM[p]: Ka[p] = K[src_p] Watt[r], M[p] = V[src_p] Wmsg[r]
+    void* const Mrow = h ? static_cast<void*>(static_cast<uint16_t*>(sv.KM) + D) : static_cast<void*>(static_cast<float*>(sv.KM) + D);
     if (fold) {
         //    = X[src_p] (Wk[type of r's sources] Watt[r]) and X[src_p] (Wv[type] Wmsg[r])
         //    With bf16 rows the products are rounded to bf16 once (as K and V would have been) and feed the
@@ -782,18 +787,15 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
         //    128, its fp32 copy otherwise.
         RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, st));
         RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, st));
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_att), R16(w.Wf_att), sv.Ka, h, "pair_linear_att", st));
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_msg), R16(w.Wf_msg), sv.M, h, "pair_linear_msg", st));
+        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_att), R16(w.Wf_att), sv.KM, h, "pair_linear_att", st, 0, 2));
+        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_msg), R16(w.Wf_msg), Mrow, h, "pair_linear_msg", st, 0, 2));
     } else {
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.K), R16(sv.K), psrc, 0, w.Wbd_att, nullptr, sv.Ka, h, "pair_linear_att", st));
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.V), R16(sv.V), psrc, 0, w.Wbd_msg, nullptr, sv.M, h, "pair_linear_msg", st));
+        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.K), R16(sv.K), psrc, 0, w.Wbd_att, nullptr, sv.KM, h, "pair_linear_att", st, 0, 2));
+        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.V), R16(sv.V), psrc, 0, w.Wbd_msg, nullptr, Mrow, h, "pair_linear_msg", st, 0, 2));
     }
-    // 4. per edge and head: logit, softmax over the destination's edges
-    RGNN_TRY(hgt_edge_logit(g, D, H, sv.Ka, sv.Q, sv.att, st, h, w.part_m, w.part_s));     // logits, then softmax per head
-    // 5. Z[v][h] = sum_e att[e][h] M[pair_e][h]
-    RGNN_TRY(gather_sum(g->dst_items, D, nullptr, g->idx[RGNN_IDX_IN_PAIR], 0, sv.att, H, 0, sv.M, sv.Z, w.partial, st, 0,
-                        "aggregate_fwd", "aggregate_fwd.combine", H, h, h));
-    // 6. out = Z Wo[type]
+    // 4. one walk per destination: logit per edge and head, softmax over the destination's edges, Z[v][h] = sum_e att[e][h] M[pair_e][h]
+    RGNN_TRY(hgt_attend_fwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.partial, w.part_ms, st, h));
+    // 5. out = Z Wo[type]
     RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, R32(sv.Z), R16(sv.Z), perm, 1, Wo32, Wo16, out, false, "node_linear_out", st));
     return RGNN_OK;
 }
@@ -844,17 +846,13 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     // 1. output linear: dZ = dOut Wo^T, dWo = Z^T dOut
     RGNN_TRY(tl_bwd(h, &g->node_tiles, &g->node_tiles_wide, D, sv.Z, perm, 1, Wo32, Wo16, dOr, w.dZ, h, static_cast<float*>(dWo), w.tl_part,
                     "node_linear_out_bwd", st));
-    // 2. per edge and head: d logit
-    RGNN_TRY(hgt_edge_dot_bwd(g, D, H, sv.att, sv.M, w.dZ, sv.Z, w.dl, st, h));
-    // 3. pair-major: dM[p][h] = sum att dZ[dst][h];  dKa[p][h] = sum dl Q[dst][h]
-    RGNN_TRY(gather_sum(g->pair_items, D, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_DST], 0, sv.att, H, 0, w.dZ, w.dM,
-                        w.partial, st, 1, "aggregate_bwd_msg", "aggregate_bwd_msg.combine", H, h, h));
-    RGNN_TRY(gather_sum(g->pair_items, D, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_DST], 0, w.dl, H, 0, sv.Q, w.dKa,
-                        w.partial, st, 1, "aggregate_bwd_key", "aggregate_bwd_key.combine", H, h, h));
-    // 4. destination-major: dQ[v][h] = sum dl Ka[pair][h]
-    RGNN_TRY(gather_sum(g->dst_items, D, nullptr, g->idx[RGNN_IDX_IN_PAIR], 0, w.dl, H, 0, sv.Ka, w.dQ, w.partial, st, 0,
-                        "aggregate_bwd_query", "aggregate_bwd_query.combine", H, h, h));
-    // 5. per-pair linears backward
+    // 2. per destination: att (recomputed) and d logit per edge and head, dQ[v][h] = sum dl Ka[pair][h]
+    RGNN_TRY(hgt_attend_bwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.dZ, w.dQ, w.adl, w.partial, st, h));
+    // 3. per pair: dKa[p][h] = sum dl Q[dst][h], dM[p][h] = sum att dZ[dst][h]
+    RGNN_TRY(hgt_pair_bwd(g, D, H, sv.Q, w.dZ, w.adl, w.dKM, w.partial, st, h));
+    const void* dKa = w.dKM;
+    const void* dM = h ? static_cast<const void*>(static_cast<const uint16_t*>(w.dKM) + D) : static_cast<const void*>(static_cast<const float*>(w.dKM) + D);
+    // 4. per-pair linears backward
     RGNN_TRY(hgt_expand(g->R, D, H, Watt32, mu32, 1, w.Wbd_att, st));
     RGNN_TRY(hgt_expand(g->R, D, H, Wmsg32, nullptr, 0, w.Wbd_msg, st));
     if (fold) {
@@ -862,10 +860,10 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
         // unfolded into those of the node-type and of the per-relation matrices
         RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, st));
         RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, st));
-        RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, Xr, psrc, 0, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, w.dKa, w.dKp,
-                        h, w.dWf_att, w.tl_part, "pair_linear_att_bwd", st));
-        RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, Xr, psrc, 0, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, w.dM, w.dVp,
-                        h, w.dWf_msg, w.tl_part, "pair_linear_msg_bwd", st));
+        RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, Xr, psrc, 0, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, dKa, w.dKp,
+                        h, w.dWf_att, w.tl_part, "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
+        RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, Xr, psrc, 0, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, dM, w.dVp,
+                        h, w.dWf_msg, w.tl_part, "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
         RGNN_TRY(hgt_fold_bwd(g->T, g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, w.dWf_att, w.dWbd_att, static_cast<float*>(dWk), st));
         RGNN_TRY(hgt_fold_bwd(g->T, g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, w.dWf_msg, w.dWbd_msg, static_cast<float*>(dWv), st));
         RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_att, Watt32, mu32, 1, static_cast<float*>(dWatt), static_cast<float*>(dmu), st));
@@ -877,16 +875,16 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
         RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, w.dXq, dX, st, h, 0, 1, w.dVp));
         return ga.flush(st);
     }
-    RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, sv.K, psrc, 0, w.Wbd_att, nullptr, w.dKa, w.dKp, h, w.dWbd_att, w.tl_part,
-                    "pair_linear_att_bwd", st));
-    RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, sv.V, psrc, 0, w.Wbd_msg, nullptr, w.dM, w.dVp, h, w.dWbd_msg, w.tl_part,
-                    "pair_linear_msg_bwd", st));
+    RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.tl_part,
+                    "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
+    RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.tl_part,
+                    "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
     RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_att, Watt32, mu32, 1, static_cast<float*>(dWatt), static_cast<float*>(dmu), st));
     RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_msg, Wmsg32, nullptr, 0, static_cast<float*>(dWmsg), nullptr, st));
-    // 6. dK[u], dV[u] = sums over u's pairs
+    // 5. dK[u], dV[u] = sums over u's pairs
     RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, nullptr, w.dK, st, h, h));
     RGNN_TRY(node_grad_sum(g, D, w.dVp, nullptr, nullptr, nullptr, w.dV, st, h, h));
-    // 7. node linears backward and dX
+    // 6. node linears backward and dX
     //    (bf16 rows: the three input gradients are accumulated into dX by the kernels themselves)
     RGNN_TRY(tl_bwd(h, &g->node_tiles, &g->node_tiles_wide, D, Xr, perm, 1, Wk32, Wk16, w.dK, h ? dX : static_cast<void*>(w.dXk),
                     false, static_cast<float*>(dWk), w.tl_part, "node_linear_k_bwd", st, h && acc));

@@ -84,6 +84,7 @@ struct ItemList {
     int32_t num_single = 0;        // with exactly one entry
     int32_t first_short = 0;       // items [first_short, first_short + num_short) are the whole segments with
     int32_t num_short = 0;         // 2..kShortLen entries; the single-entry ones follow directly
+    int32_t num_wide = 0;          // items [0, num_wide) have kWideMin entries or more
 };
 
 }  // namespace rgnn
@@ -154,6 +155,7 @@ struct TypedLinearArgs {
     float* s_out;            // [rows][s_heads]
     int s_heads = 1;         // a power of two with ND / s_heads >= 16
     const char* label;       // name in the timing report (nullptr: default)
+    int y_stride = 1;        // rows of Y are y_stride * d_out floats apart (1 or 2)
 };
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st);
 
@@ -184,6 +186,7 @@ struct TypedLinearBwdArgs {
     const float* hcoef = nullptr;    // [rows][2][sel_heads]
     const float* wvec = nullptr;     // [segs][ND]
     int sel_heads = 0;
+    int dy_stride = 1;               // rows of dY are dy_stride * d_out floats apart (1 or 2)
 };
 // bf16 matrix-core variant (typed_linear_bf16.hip): Y[i] = A[g(i)] W[seg]  (or W[seg]^T)
 struct TypedLinearBf16Args {
@@ -202,6 +205,7 @@ struct TypedLinearBf16Args {
     const void* A_alt = nullptr;   // gathered rows only: a gather entry with the top bit set reads row
                                    // (entry & 0x7FFFFFFF) of this tensor instead of A
     const float* rowscale = nullptr;   // bf16 rows only: row i of the tiles is multiplied by rowscale[i]
+    int a_stride = 1, y_stride = 1;    // rows of A / Y are that many widths apart
 };
 rgnn_status_t typed_linear_bf16(int d, const TypedLinearBf16Args& a, hipStream_t st);
 
@@ -220,6 +224,7 @@ struct TypedLinearWgradBf16Args {
     const int32_t* ysel = nullptr;
     const void* dY_alt = nullptr;
     const float* yscale = nullptr;   // with ysel: row i is also multiplied by yscale[i]
+    int dy_stride = 1;               // rows of dY are that many widths apart (not with ysel)
 };
 rgnn_status_t typed_linear_wgrad_bf16(int d, const TypedLinearWgradBf16Args& a, hipStream_t st);
 rgnn_status_t typed_linear_slot_reduce(int d_in, int d_out, const TileList& tiles, const float* part, float* dW,

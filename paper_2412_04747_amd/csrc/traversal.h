@@ -43,6 +43,12 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
                          hipStream_t st, int role, const char* label, const char* combine_label, int heads = 1,
                          int src_bf16 = 0, int out_bf16 = 0, const Rank1* r1 = nullptr, float* sum2 = nullptr,
                          int sum2_stride = 1);
+// rows of the cut segments of a list from their pieces: plain sums (widths 32 .. 256), and sums whose pieces carry their
+// own softmax statistics (max, sum) per head
+rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, void* out, int out_bf16, const char* label,
+                               hipStream_t st, const Rank1* r1 = nullptr, int heads = 1);
+rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
+                              int out_bf16, float* ms, const char* label, hipStream_t st);
 // H weighted sums of the same gathered rows in one walk (coef [entries][H]); out [H][out_rows][D]
 rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, const int32_t* via, const int32_t* rowidx,
                                 int row_by_k, const float* coef, const float* src, float* out, float* partial,
@@ -64,15 +70,16 @@ rgnn_status_t rgat_param_finish(int R, int kd, int nd, const float* W, const flo
 rgnn_status_t hgt_expand(int R, int d, int H, const float* W, const float* mu, int scaled, float* Wbd, hipStream_t st);
 rgnn_status_t hgt_extract(int R, int d, int H, const float* dWbd, const float* W, const float* mu, int scaled, float* dW,
                           float* dmu, hipStream_t st);
-// with part_m / part_s: followed by the per-head softmax over each destination's edges (in the same walk where the
-// lane layout allows), so that logit holds the attention weights afterwards
-rgnn_status_t hgt_edge_logit(const rgnn_graph* g, int D, int H, const void* Ka, const void* Q, float* logit,
-                             hipStream_t st, int rows_bf16 = 0, float* part_m = nullptr, float* part_s = nullptr);
-rgnn_status_t hgt_softmax_finish(const rgnn_graph* g, int H, float* att, const float* part_m, const float* part_s, hipStream_t st);
-rgnn_status_t hgt_softmax(const rgnn_graph* g, int H, float* att, float* part_m, float* part_s, hipStream_t st);
-// dl = att (g - gbar)
-rgnn_status_t hgt_edge_dot_bwd(const rgnn_graph* g, int D, int H, const float* att, const void* M, const void* dZ,
-                               const void* Z, float* dl, hipStream_t st, int rows_bf16 = 0);
+// hgt_walk.hip: the edge walks of HGT over the key / message rows KM[p][2][D] of the pairs (rows fp32 or bf16)
+//   forward: Z[v] = sum_e att_e M[pair_e], att = softmax per head of Ka[pair_e] . Q[v]; ms[v][h] = (max, sum of exp)
+rgnn_status_t hgt_attend_fwd(const rgnn_graph* g, int D, int H, const void* KM, const void* Q, void* Z, float* ms,
+                             float* partial, float* part_ms, hipStream_t st, int rows_bf16);
+//   backward, destination-major: adl[e][h] = (att, dl), dl = att (dZ . M - dZ . Z); dQ[v] = sum_e dl Ka[pair_e]
+rgnn_status_t hgt_attend_bwd(const rgnn_graph* g, int D, int H, const void* KM, const void* Q, const void* Z, const float* ms,
+                             const void* dZ, void* dQ, float* adl, float* partial, hipStream_t st, int rows_bf16);
+//   backward, pair-major: dKM[p] = (sum dl Q[dst], sum att dZ[dst]); partial rows are 2 D wide
+rgnn_status_t hgt_pair_bwd(const rgnn_graph* g, int D, int H, const void* Q, const void* dZ, const float* adl, void* dKM,
+                           float* partial, hipStream_t st, int rows_bf16);
 // rgat_heads.hip: pieces of multi-head RGAT
 rgnn_status_t fold_weight_heads(int R, int kd, int nd, int H, const float* W, const float* w, float* wv, hipStream_t st);
 rgnn_status_t run_logit_heads(const rgnn_graph* g, int D, int H, const float* X, const float* wtp, float* s_dst,

@@ -634,6 +634,71 @@ __global__ __launch_bounds__(1024) void combine_partials_kernel(const int32_t* _
     }
 }
 
+// Cut destinations of a softmax-weighted sum: the pieces carry (max m_i, sum s_i of exp(l - m_i)) per head and the
+// unnormalised row; out[v] = sum_i exp(m_i - M) partial_i / S with M = max_i m_i, S = sum_i s_i exp(m_i - M).  One workgroup
+// per cut destination: group g of D/4 lanes takes the pieces g, g + G, ... four at a time (their loads independent) in the
+// running-maximum form, and the G group results are merged in group order through LDS.  H heads are equal column slices.
+template <int D, int H, typename TO>
+__global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __restrict__ split_row,
+                                                              const int32_t* __restrict__ split_ptr,
+                                                              const float* __restrict__ partial,
+                                                              const float2* __restrict__ part_ms, TO* __restrict__ out,
+                                                              float2* __restrict__ ms) {
+    constexpr int LPR = D / 4, G = 256 / LPR, LPH = LPR / H;
+    __shared__ float4 red[256];
+    __shared__ float2 redms[G][H];
+    const int s = blockIdx.x, g = threadIdx.x / LPR, c = threadIdx.x % LPR, head = c / LPH;
+    const int p0 = split_ptr[s], p1 = split_ptr[s + 1];
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float M = -INFINITY, S = 0.f;
+    for (int p = p0 + g; p < p1; p += 4 * G) {
+        float2 t[4];
+        float4 r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int pp = min(p + u * G, p1 - 1);
+            t[u] = part_ms[(size_t)pp * H + head];
+            r[u] = *reinterpret_cast<const float4*>(partial + (size_t)pp * D + c * 4);
+        }
+        float mn = M;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (p + u * G < p1) mn = fmaxf(mn, t[u].x);
+        const float sc = __expf(M - mn);          // 0 for the first four pieces
+        S *= sc;
+        acc.x *= sc; acc.y *= sc; acc.z *= sc; acc.w *= sc;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float w = p + u * G < p1 ? __expf(t[u].x - mn) : 0.f;
+            S += w * t[u].y;
+            fma4(acc, w, r[u]);
+        }
+        M = mn;
+    }
+    red[threadIdx.x] = acc;
+    if (c % LPH == 0) redms[g][head] = make_float2(M, S);
+    __syncthreads();
+    if (g == 0) {
+        const int n = min(G, p1 - p0);            // groups that had a piece
+        for (int k = 1; k < n; ++k) M = fmaxf(M, redms[k][head].x);
+        S = 0.f;
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < n; ++k) {
+            const float2 q = redms[k][head];
+            const float w = __expf(q.x - M);
+            const float4 r = red[k * LPR + c];
+            S += w * q.y;
+            t[0] += w * r.x; t[1] += w * r.y; t[2] += w * r.z; t[3] += w * r.w;
+        }
+        const float inv = 1.f / S;
+        const size_t v = (size_t)split_row[s];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t[q] *= inv;
+        store_cols(out + v * D + c * 4, t);
+        if (c % LPH == 0) ms[v * H + head] = make_float2(M, S);
+    }
+}
+
 // ------------------------------------------------------------------ edge-parallel aggregation (comparison schedule)
 
 // out[dst_e] += |att_e| * Hs[pair_e] over equal shares of the CSR edge list: a lane group takes
@@ -980,6 +1045,53 @@ rgnn_status_t edge_softmax(const rgnn_graph* g, const float* s_src, const float*
         else { using TI = float; using TO = bf16_t; constexpr int DD = 128; __VA_ARGS__; }                      \
     } while (0)
 
+rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
+                              int out_bf16, float* ms, const char* label, hipStream_t st) {
+    if (L.num_split == 0) return RGNN_OK;
+    KernelTimer kt(st, label);
+#define RGNN_COMBINE_H(HH)                                                                                            \
+    do {                                                                                                              \
+        if (out_bf16)                                                                                                 \
+            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_softmax_kernel<DD, (DD / (HH) >= 16 ? (HH) : 1), bf16_t>), dim3(L.num_split), dim3(256), 0, st, \
+                                                  L.split_row, L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), \
+                                                  static_cast<bf16_t*>(out), reinterpret_cast<float2*>(ms)));          \
+        else                                                                                                          \
+            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_softmax_kernel<DD, (DD / (HH) >= 16 ? (HH) : 1), float>), dim3(L.num_split), dim3(256), 0, st, \
+                                                  L.split_row, L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), \
+                                                  static_cast<float*>(out), reinterpret_cast<float2*>(ms)));           \
+    } while (0)
+    if (H < 1 || D / H < 16) { if (H != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "combine_softmax: %d heads at width %d not built", H, D); }
+    if (H == 1) RGNN_COMBINE_H(1);
+    else if (H == 2) RGNN_COMBINE_H(2);
+    else if (H == 4) RGNN_COMBINE_H(4);
+    else if (H == 8) RGNN_COMBINE_H(8);
+    else RGNN_FAIL(RGNN_EUNSUPPORTED, "combine_softmax: %d heads not built (1, 2, 4, 8)", H);
+#undef RGNN_COMBINE_H
+    RGNN_CHECK_LAUNCH();
+    return RGNN_OK;
+}
+
+rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, void* out, int out_bf16, const char* label,
+                               hipStream_t st, const Rank1* r1, int heads) {
+    if (L.num_split == 0) return RGNN_OK;
+    const Rank1 r1v = r1 ? *r1 : Rank1{nullptr, 0, nullptr, nullptr};
+    KernelTimer kt(st, label);
+#define RGNN_LAUNCH_COMBINE(DD_, TO_)                                                                                  \
+    hipLaunchKernelGGL((combine_partials_kernel<DD_, TO_>), dim3(L.num_split), dim3(1024), 0, st, L.split_row, L.split_ptr, \
+                       partial, static_cast<TO_*>(out), r1v, (DD_ / 4) / heads)
+    if (D == 256) {
+        if (out_bf16) RGNN_LAUNCH_COMBINE(256, bf16_t);
+        else RGNN_LAUNCH_COMBINE(256, float);
+    } else if (out_bf16) {
+        RGNN_DISPATCH_D(D, RGNN_LAUNCH_COMBINE(DD, bf16_t));
+    } else {
+        RGNN_DISPATCH_D(D, RGNN_LAUNCH_COMBINE(DD, float));
+    }
+#undef RGNN_LAUNCH_COMBINE
+    RGNN_CHECK_LAUNCH();
+    return RGNN_OK;
+}
+
 rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int32_t* rowidx, int row_by_k,
                          const float* coef, int cstride, int cabs, const void* src, void* out, float* partial,
                          hipStream_t st, int role, const char* label, const char* combine_label, int heads,
@@ -1029,17 +1141,7 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
         }
 #undef RGNN_LAUNCH_GATHER
     }
-    if (L.num_split > 0) {
-        KernelTimer kt(st, combine_label);
-        if (out_bf16)
-            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_partials_kernel<DD, bf16_t>), dim3(L.num_split), dim3(1024), 0, st,
-                                                  L.split_row, L.split_ptr, partial, static_cast<bf16_t*>(out), r1v, (DD / 4) / heads));
-        else
-            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_partials_kernel<DD, float>), dim3(L.num_split), dim3(1024), 0, st,
-                                                  L.split_row, L.split_ptr, partial, static_cast<float*>(out), r1v, (DD / 4) / heads));
-        RGNN_CHECK_LAUNCH();
-    }
-    return RGNN_OK;
+    return combine_partials(L, D, partial, out, out_bf16, combine_label, st, &r1v, heads);
 }
 
 rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, const int32_t* via, const int32_t* rowidx,

@@ -74,7 +74,8 @@ __device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int
 //   DYG      backward: dY rows are read through the list  RS       backward: rowscale / Avec / xvec in use
 //   WT       multiply by W[seg]^T (W stored [ND][KD]): the input-gradient product dY W^T
 //   ADDV     Y_row += rowscale[row] * vec[seg]  (the rank-1 part of single-head RGAT's input gradient)
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool WT = false, bool ADDV = false>
+//   IS, OS   the rows of X / Y are IS * KD / OS * ND floats apart (2: the key or message half of HGT's pair rows)
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool WT = false, bool ADDV = false, int IS = 1, int OS = 1>
 __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X,
                                                                     const int32_t* __restrict__ gather,
                                                                     const float* __restrict__ W, float* __restrict__ Y,
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
     }
 #define RGNN_FETCH_ROWS()                                                           \
     _Pragma("unroll") for (int it = 0; it < NX; ++it) {                             \
-        xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gi[it] * KD + ci * 4); \
+        xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gi[it] * (IS * KD) + ci * 4); \
         gcur[it] = gi[it];                                                          \
     }
         RGNN_FETCH_IDX(wave)
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
                 const bool ok = row < rbnd;
                 float4 y = *reinterpret_cast<const float4*>(Xw + r * XS + co * 4);
                 const size_t d = SCATTER ? (size_t)gout[it] : (size_t)min(row, rbnd - 1);
-                float4* yp = reinterpret_cast<float4*>(Y + d * ND + co * 4);
+                float4* yp = reinterpret_cast<float4*>(Y + d * (OS * ND) + co * 4);
                 if (ACCUM) {
                     const float4 o = *yp;
                     y.x += o.x; y.y += o.y; y.z += o.z; y.w += o.w;
@@ -235,7 +236,8 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
 // selected come from dY as they are.)  The slot's vector part then holds HS vectors, sum over the rows of
 // b[h] * X[g(i)] for h < HS (selected or not: b is the row's rowscale per head).
 struct RowSelect { const int32_t* sel; const float* alt; const float2* ds_scale; const float* hcoef; const float* wvec; };
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0>
+// DS: the rows of dY are DS * ND floats apart (not with SEL).
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1>
 __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, const float* __restrict__ X,
                                                                     const int32_t* __restrict__ gather,
                                                                     const float* __restrict__ W,
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
                                                                     const float* __restrict__ rowscale,
                                                                     const float* __restrict__ vec,
                                                                     float* __restrict__ part, RowSelect ys) {
-    static_assert(!SEL || !DYG, "the row selector replaces the dY gather");
+    static_assert(!SEL || (!DYG && DS == 1), "the row selector replaces the dY gather");
     static_assert(HS == 0 || (SEL && !RS && (HS == 2 || HS == 4)), "per-head row selector: two or four heads, no rowscale");
     constexpr int NW = 8;
     constexpr int XS = KD + 4, YS = (ND > KD ? ND : KD) + 4, WS = ND + 1;
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
                     yr[it] = *reinterpret_cast<const v4f*>(base + (size_t)(sl & 0x7FFFFFFF) * ND + cy * 4);
                 } else {
                     const size_t s2 = DYG ? (size_t)gi[it] : (size_t)min(ra + u * 32 + ry + it * RPY, rbnd - 1);
-                    yr[it] = *reinterpret_cast<const v4f*>(dY + s2 * ND + cy * 4);
+                    yr[it] = *reinterpret_cast<const v4f*>(dY + s2 * (DS * ND) + cy * 4);
                 }
             }
             if (HS) {
@@ -372,7 +374,7 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
                 v4f v = yr[it];
                 if (HS) {
                     // coefficients of this lane's head from the lane that keeps them for the row
-                    const int hd = cy / (LPRY / HS);
+                    const int hd = cy / (LPRY / (HS ? HS : 1));
                     const int from = ry + it * RPY + (HS == 4 ? 32 * (hd >> 1) : 0);
                     const float b0 = __shfl(hon ? hcf[0] : 0.f, from), b1 = __shfl(hon ? hcf[1] : 0.f, from);
                     const float a0 = __shfl(hcf[2], from), a1 = __shfl(hcf[3], from);
@@ -577,7 +579,8 @@ __global__ void slot_reduce_kernel(const float* __restrict__ part, const int32_t
 // X[row 2s + kh][band + m] and its B operand dY[row 2s + kh][block + m], both conflict-free 4-byte
 // reads.  The next tile's rows are in flight in registers while the current one is multiplied.
 // RS: the slot's vector part gets sum over the rows of rowscale[i] * X[g(i)] (otherwise zeros).
-template <int D, bool GATHER, bool DYG, bool RS>
+// DS: the rows of dY are DS * D floats apart.
+template <int D, bool GATHER, bool DYG, bool RS, int DS = 1>
 __global__ __launch_bounds__(256) void typed_linear_wgrad_f32_kernel(TileArgs t, const float* __restrict__ X,
                                                                      const int32_t* __restrict__ gather,
                                                                      const float* __restrict__ dY,
@@ -618,7 +621,7 @@ __global__ __launch_bounds__(256) void typed_linear_wgrad_f32_kernel(TileArgs t,
             xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gi[it] * D + cx * 4); \
             const int row_ = min(row0_ + rx + it * RPP, row1_ - 1);                 \
             const size_t s_ = (DYG && GATHER) ? (size_t)gi[it] : (size_t)row_;      \
-            yr[it] = *reinterpret_cast<const v4f*>(dY + s_ * D + cx * 4);           \
+            yr[it] = *reinterpret_cast<const v4f*>(dY + s_ * (DS * D) + cx * 4);           \
             if (RS) rs[it] = rowscale[row_];                                        \
         }                                                                           \
     }
@@ -692,10 +695,10 @@ static TileArgs tile_args(const TileList& t) {
     return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot};
 }
 
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool WT = false, bool ADDV = false>
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool WT = false, bool ADDV = false, int IS = 1, int OS = 1>
 static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st, const float* rowscale = nullptr) {
     const size_t lds = sizeof(float) * (KD * ND + 4 * 32 * ((KD > ND ? KD : ND) + 4));
-    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, WT, ADDV>;
+    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, WT, ADDV, IS, OS>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
@@ -710,6 +713,12 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
     const bool g = a.gather != nullptr, sc = g && a.scatter_out, ac = a.accumulate != 0, v = a.vec != nullptr;
     if (v && (a.s_heads < 1 || (a.s_heads & (a.s_heads - 1)) || a.s_heads > ND / 4))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, ND);
+    if (a.y_stride == 2) {
+        if constexpr (KD == ND) {
+            if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false, false, false, 1, 2>(a, st);
+        }
+        RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built for gathered rows of equal widths only");
+    }
     if (g && !sc && !ac && v) return launch_fwd_wave<KD, ND, true, false, false, true>(a, st);
     if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false>(a, st);
     if constexpr (KD == ND) {
@@ -743,12 +752,12 @@ static rgnn_status_t launch_slot_reduce(int kd, int nd, const TypedLinearBwdArgs
     return RGNN_OK;
 }
 
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0>
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1>
 static rgnn_status_t launch_bwd_wave(const TypedLinearBwdArgs& a, hipStream_t st) {
     constexpr int WREG = 32 * (KD + 4) + 32 * ((ND > KD ? ND : KD) + 4) + 32;
     static_assert(WREG >= KD * ND + (HS ? HS : 1) * KD, "per-wavefront LDS region must hold a weight-gradient copy");
     const size_t lds = sizeof(float) * (KD * (ND + 1) + 8 * WREG);
-    auto kern = typed_linear_bwd_wave_kernel<KD, ND, GATHER, DYG, SCATTER, RS, SEL, HS>;
+    auto kern = typed_linear_bwd_wave_kernel<KD, ND, GATHER, DYG, SCATTER, RS, SEL, HS, DS>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(512), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W,
@@ -767,22 +776,26 @@ static rgnn_status_t launch_bwd_split(const TypedLinearBwdArgs& a, hipStream_t s
     f.scatter_out = sc; f.vec = a.vec; f.label = a.label ? a.label : "typed_linear_bwd";
     if (dg != sc) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY gathered and dXrow scattered must go together");
     if (rs && (dg || !a.vec)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: rowscale needs vec and ungathered dY");
-    if (rs) RGNN_TRY((launch_fwd_wave<D, D, false, false, false, false, true, true>(f, st, a.rowscale)));
+    const bool two = a.dy_stride == 2;
+    if (two && (rs || dg || !g)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY rows two widths apart are built for gathered X, ungathered dY and no rowscale only");
+    if (two) RGNN_TRY((launch_fwd_wave<D, D, false, false, false, false, true, false, 2, 1>(f, st)));
+    else if (rs) RGNN_TRY((launch_fwd_wave<D, D, false, false, false, false, true, true>(f, st, a.rowscale)));
     else if (dg) RGNN_TRY((launch_fwd_wave<D, D, true, true, false, false, true>(f, st)));
     else RGNN_TRY((launch_fwd_wave<D, D, false, false, false, false, true>(f, st)));
     const size_t lds = sizeof(float) * 2 * 64 * (D + 4);
     KernelTimer kt(st, wgrad_label(f.label));
-#define RGNN_LAUNCH_WGRAD(G_, DG_, RS_)                                                                              \
+#define RGNN_LAUNCH_WGRAD(G_, DG_, RS_, DS_)                                                                              \
     {                                                                                                                \
-        auto kern = typed_linear_wgrad_f32_kernel<D, G_, DG_, RS_>;                                                  \
+        auto kern = typed_linear_wgrad_f32_kernel<D, G_, DG_, RS_, DS_>;                                               \
         RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));                                       \
         hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, tile_args(*a.tiles), a.X, a.gather, \
                            a.dY, a.rowscale, a.part);                                                                \
     }
-    if (g && dg) RGNN_LAUNCH_WGRAD(true, true, false)
-    else if (g && rs) RGNN_LAUNCH_WGRAD(true, false, true)
-    else if (g) RGNN_LAUNCH_WGRAD(true, false, false)
-    else if (!rs) RGNN_LAUNCH_WGRAD(false, false, false)
+    if (two) RGNN_LAUNCH_WGRAD(true, false, false, 2)
+    else if (g && dg) RGNN_LAUNCH_WGRAD(true, true, false, 1)
+    else if (g && rs) RGNN_LAUNCH_WGRAD(true, false, true, 1)
+    else if (g) RGNN_LAUNCH_WGRAD(true, false, false, 1)
+    else if (!rs) RGNN_LAUNCH_WGRAD(false, false, false, 1)
     else RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: rowscale needs gathered X");
 #undef RGNN_LAUNCH_WGRAD
     RGNN_HIP(hipGetLastError());
@@ -801,7 +814,11 @@ static rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
         if constexpr (KD <= 64 && ND <= 64) {
             const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
             done = true;
-            if (a.ysel && a.hcoef) {
+            if (a.dy_stride == 2) {
+                if (!(g && !dg && !sc && !rs && !a.ysel && KD == ND))
+                    RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY rows two widths apart are built for gathered X, ungathered dY, no rowscale and no selector only");
+                if constexpr (KD == ND) RGNN_TRY((launch_bwd_wave<KD, ND, true, false, false, false, false, 0, 2>(a, st)));
+            } else if (a.ysel && a.hcoef) {
                 if (!(g && !dg && !sc && !rs && a.dY_alt && a.wvec) || (a.sel_heads != 2 && a.sel_heads != 4) || ND % (4 * a.sel_heads))
                     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: the per-head row selector needs gathered X, ungathered dY, no rowscale, 2 or 4 heads of a multiple of 4 columns");
                 if (a.sel_heads == 2) RGNN_TRY((launch_bwd_wave<KD, ND, true, false, false, false, true, 2>(a, st)));

@@ -79,6 +79,7 @@ __device__ __forceinline__ int run_end_b(const int32_t* __restrict__ tile_seg, i
 //   WT     false: Y = A W  (W stored [CD][OD])          true: Y = A W^T  (W stored [OD][CD])
 //   GATHER rows are read through the gather list        SCATTER outputs are written through it as well
 //   Y_BF16 output rows are stored as bf16 / fp32        ACC    (fp32 output only) Y += result
+// lda, ldy: elements from one row of A (and Alt) / of Y to the next.
 // A gather entry with the top bit set reads row (entry & 0x7FFFFFFF) of Alt instead of A (not with SCATTER).
 // rowscale (optional, bf16 A only): row i of the tiles is multiplied by rowscale[i] (and rounded to bf16
 // again) on its way into LDS; the lane that holds a row's factor hands it to the lanes that store the row.
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(256) void typed_linear_bf16_kernel(TileArgsB t, con
                                                                 const int32_t* __restrict__ gather,
                                                                 const void* __restrict__ Wv, void* __restrict__ Yv,
                                                                 const void* __restrict__ Alt,
-                                                                const float* __restrict__ rowscale) {
+                                                                const float* __restrict__ rowscale, int lda, int ldy) {
     constexpr int NW = 4;
     constexpr int LS = CD + 8;                                // LDS row stride in bf16 elements (16-byte aligned rows)
     constexpr int OB = OD / 32;
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(256) void typed_linear_bf16_kernel(TileArgsB t, con
 #define RGNN_FETCH_ROWS()                                                       \
     _Pragma("unroll") for (int it = 0; it < NX; ++it) {                         \
         const char* b_ = static_cast<const char*>(GATHER && !SCATTER && gi[it] < 0 ? Alt : Av); \
-        const char* p_ = b_ + (size_t)(GATHER && !SCATTER ? gi[it] & 0x7FFFFFFF : gi[it]) * CD * (A_BF16 ? 2 : 4) + ci * 16; \
+        const char* p_ = b_ + (size_t)(GATHER && !SCATTER ? gi[it] & 0x7FFFFFFF : gi[it]) * lda * (A_BF16 ? 2 : 4) + ci * 16; \
         xr[it] = *reinterpret_cast<const v4u*>(p_);                             \
         gcur[it] = gi[it];                                                      \
     }                                                                           \
@@ -198,8 +199,8 @@ __global__ __launch_bounds__(256) void typed_linear_bf16_kernel(TileArgsB t, con
                         const size_t d = SCATTER ? (size_t)gidx[r] : (size_t)(ra + u * 32 + r);
 #pragma unroll
                             for (int b = 0; b < OB; ++b) {
-                            if (ACC) Y[d * OD + b * 32 + m] += acc[b][v];
-                            else Y[d * OD + b * 32 + m] = acc[b][v];
+                            if (ACC) Y[d * ldy + b * 32 + m] += acc[b][v];
+                            else Y[d * ldy + b * 32 + m] = acc[b][v];
                         }
                     }
                 }
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(256) void typed_linear_bf16_kernel(TileArgsB t, con
                     const int r = orow + pass * RPP;
                     if (r < rows_left) {
                         const size_t d = SCATTER ? (size_t)gidx[r] : (size_t)(ra + u * 32 + r);
-                        __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(Aw + r * LS + oc * 8), reinterpret_cast<v4u*>(Y + d * OD + oc * 8));
+                        __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(Aw + r * LS + oc * 8), reinterpret_cast<v4u*>(Y + d * ldy + oc * 8));
                     }
                 }
             }
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
                                                                       float* __restrict__ part,
                                                                       const int32_t* __restrict__ ysel,
                                                                       const unsigned short* __restrict__ dYalt,
-                                                                      const float* __restrict__ yscale) {
+                                                                      const float* __restrict__ yscale, int ldd) {
     static_assert(D == 128, "four wavefronts x four 32-column blocks");
     static_assert(!(SEL && DYG), "the row selector replaces the dY gather");
     constexpr int TMW = 64;
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
                 yr[k] = *reinterpret_cast<const v4u*>((y_ < 0 ? dYalt : dY) + (size_t)(y_ & 0x7FFFFFFF) * D + cx * 8); \
             } else {                                                                \
                 const size_t s_ = (DYG && GATHER) ? (size_t)gi[k] : (size_t)row_;   \
-                yr[k] = *reinterpret_cast<const v4u*>(dY + s_ * D + cx * 8);        \
+                yr[k] = *reinterpret_cast<const v4u*>(dY + s_ * ldd + cx * 8);        \
             }                                                                       \
         }                                                                           \
         ysc = ysn;                                                                  \
@@ -410,7 +411,7 @@ static rgnn_status_t launch_wgrad(const TypedLinearWgradBf16Args& a, hipStream_t
     TileArgsB t{a.tiles->tile_seg, a.tiles->tile_row0, a.tiles->tile_row1, a.tiles->chunk_tile};
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, t, a.tiles->chunk_slot,
                        static_cast<const unsigned short*>(a.X), a.gather, static_cast<const unsigned short*>(a.dY), a.part,
-                       a.ysel, static_cast<const unsigned short*>(a.dY_alt), a.yscale);
+                       a.ysel, static_cast<const unsigned short*>(a.dY_alt), a.yscale, a.dy_stride * D);
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -437,7 +438,8 @@ static rgnn_status_t launch(const TypedLinearBf16Args& a, hipStream_t st) {
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bf16");
     TileArgsB t{a.tiles->tile_seg, a.tiles->tile_row0, a.tiles->tile_row1, a.tiles->chunk_tile};
-    hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, t, a.A, a.gather, a.W, a.Y, a.A_alt, a.rowscale);
+    hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, t, a.A, a.gather, a.W, a.Y, a.A_alt, a.rowscale,
+                       a.a_stride * CD, a.y_stride * OD);
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -446,6 +448,7 @@ template <int D, bool A_BF16, bool W_BF16, bool WT, bool Y_BF16, bool ACC = fals
 static rgnn_status_t launch_gs(const TypedLinearBf16Args& a, hipStream_t st) {
     const bool g = a.gather != nullptr, sc = g && a.scatter_out;
     if (a.A_alt && !(g && !sc)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bf16: a second row tensor needs gathered, unscattered rows");
+    if (a.A_alt && a.a_stride != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bf16: a second row tensor needs rows that follow each other");
     if (a.rowscale && !A_BF16) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bf16: the row scale is built for bf16 rows");
     if (g && sc) return launch<D, D, A_BF16, W_BF16, WT, true, true, Y_BF16, ACC>(a, st);
     if constexpr (ACC) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bf16: accumulation is built for gathered + scattered rows only");

@@ -19,6 +19,8 @@ constexpr int kMinChunks = 512;     // fewer chunks than this only when there ar
 constexpr int kChunkTiles = 8;      // tiles a chunk spans before the chunk count grows beyond kMinChunks
 constexpr int kItemMax = 256;       // longest traversal item (entries)
 constexpr int kItemTarget = 65536;  // lists are cut finer while they yield fewer items than this
+constexpr int kWideMin = 29;        // items with at least this many entries: a wavefront per item where a kernel has that walk (up to
+                                    // eight lane groups share it in batches of four entries, and each has to get some)
 constexpr int kSerialMax = 32;      // longest segment a single lane walks; longer ones get a wavefront
 
 // Tiles of at most `tile_rows` rows that never straddle a segment, in row order, grouped into
@@ -85,6 +87,7 @@ constexpr int kShortLen = 4;
 
 struct ItemPlan {
     int32_t num_partials = 0, num_split = 0, first_single = 0, num_single = 0, first_short = 0, num_short = 0;
+    int32_t num_wide = 0;                          // items with at least kWideMin entries: a prefix of the list
     std::vector<int32_t> beg, end, row, slot;      // [num_items]
     std::vector<int32_t> split_row, split_ptr;     // [num_split], [num_split + 1] range of partial rows
     std::vector<int32_t> part_item, part_split;    // [num_partials] item writing the partial row; index into split_*
@@ -137,6 +140,7 @@ inline ItemPlan plan_items(const std::vector<int32_t>& ptr, int max_len, int min
     L.first_short = n;
     for (int i = 0; i < n; ++i) {
         const int len = L.end[i] - L.beg[i];
+        if (len >= kWideMin) ++L.num_wide;
         if (len == 1 && L.slot[i] < 0) {
             if (L.num_single == 0) L.first_single = i;
             ++L.num_single;

@@ -107,6 +107,28 @@ def test_relations_tied_to_one_source_type(dtype, d, H):
     _run(N, T, R, src, dst, rel, ntype, p, d, H, f"tied-{dtype}-d{d}", dtype=dtype)
 
 
+@pytest.mark.parametrize("dtype,d,H", [("f32", 32, 1), ("f32", 32, 2), ("f32", 64, 1), ("f32", 64, 4), ("f32", 128, 2),
+                                       ("f32", 128, 8), ("bf16", 128, 2), ("bf16", 128, 4), ("bf16", 128, 8)])
+def test_walk_lengths(dtype, d, H):
+    """Destinations and pairs at the lengths where the edge walks change: none, one batch of four and its remainders, the
+    shortest item that a whole wavefront takes (29 entries), the longest uncut item (32) and cut ones with a remainder."""
+    rng = np.random.default_rng(400 + d + H)
+    lengths = [0, 1, 2, 3, 4, 5, 7, 8, 9, 27, 28, 29, 30, 31, 32, 33, 61, 64, 65, 97, 130] * 3
+    dst = np.repeat(np.arange(len(lengths)), lengths)
+    E, N, T, R = len(dst), 150, 2, 3
+    src = np.concatenate([np.repeat(np.arange(len(lengths)), rng.permutation(lengths)), rng.integers(0, N, 40)])[:E]
+    src = np.concatenate([src, rng.integers(0, N, E - len(src))])
+    rel = rng.integers(0, R, E)
+    rel[:E // 2] = 1                                  # pairs of many edges too
+    perm = rng.permutation(E)
+    ntype = rng.integers(0, T, N).astype(np.int32)
+    p = synth.hgt_params(rng, N, T, R, d, H, with_mu=True)
+    if dtype == "bf16":
+        p = {k: (None if v is None else synth.round_to_bf16(v)) for k, v in p.items()}
+    _run(N, T, R, src.astype(np.int32)[perm], dst.astype(np.int32), rel.astype(np.int32), ntype, p, d, H, f"lengths-{dtype}-d{d}-H{H}",
+         dtype=dtype)
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None
