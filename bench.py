@@ -96,8 +96,8 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
     r32 = d * 4                       # an fp32 row
     row = d * 2 if half else r32      # an input / intermediate row
     wb = 2 if half else 4             # element size of a given weight
-    # width 128: the backward typed linear is two kernels, "<label>" = dY W^T and "<label>.wgrad"
-    # (bf16 rows: always; fp32 rows: wherever the rank-1 extras of single-head RGAT are not needed)
+    # width 128, fp32 rows, wherever the rank-1 extras of single-head RGAT are not needed: the backward typed linear is
+    # two kernels, "<label>" = dY W^T and "<label>.wgrad".  bf16 rows: one kernel reads both rows and forms both products.
     split = d == 128 and (half or layer != "rgat" or H > 1)
     if split:
         rows = {"typed_linear": P, "pair_linear": P, "node_linear": N, "self_loop": N}
@@ -108,11 +108,15 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
             # one row in, one row out (or two rows in for the weight gradient), + the gather index
             segs = T if key.startswith("node_linear") else (1 if key.startswith("self_loop") else R)
             w2 = d * d * (4 if key.startswith("pair_linear") else wb)       # block-diagonal weights are fp32
+            if name == "pair_linear_bwd":      # key and message halves together: X row, two gradient rows in, one row out
+                return (bound, n * (4 * row + 4) + 2 * segs * d * d * (wb + 4), 8.0 * n * d * d)
             if name.endswith(".wgrad"):
                 return (bound, n * (2 * row + 4) + segs * d * d * 4, 2.0 * n * d * d)
             out_row = r32 if key in ("node_linear_out", "node_linear_k_bwd", "node_linear_q_bwd", "node_linear_v_bwd") else row
             # unfolded, bf16 rows: the second and third node linear accumulate into dX (read + write of the fp32 row)
             extra = r32 if half and not sched.get("hgt_folded") and key in ("node_linear_q_bwd", "node_linear_v_bwd") else 0
+            if half and key.endswith("_bwd"):
+                return (bound, n * (2 * row + out_row + extra + 4) + segs * (w2 + d * d * 4), 4.0 * n * d * d)
             return (bound, n * (row + out_row + extra + 4) + segs * w2, 2.0 * n * d * d)
     w2 = d * d * 4
     # RGAT up to width 64: the gradient row of a single-edge pair is not stored per pair; the

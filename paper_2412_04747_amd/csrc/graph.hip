@@ -151,6 +151,9 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     const int wide = kWideChunksPerCU * std::max(cus, 1);
     build_tiles(U, g->pair_tiles_wide, pair_ptr, kTileRows, wide);
     build_tiles(U, g->node_tiles_wide, ntype_ptr, kTileRows, wide);
+    build_tiles(U, g->pair_tiles_cu2, pair_ptr, kTileRows, 2 * g->num_cus);
+    build_tiles(U, g->pair_tiles_cu1, pair_ptr, kTileRows, g->num_cus);
+    build_tiles(U, g->node_tiles_cu2, ntype_ptr, kTileRows, 2 * g->num_cus);
     build_items(U, g->dst_items, in_ptr, item_cut(g->E));
     build_items(U, g->pair_items, out_ptr, item_cut(g->E));
     build_items(U, g->relrun_items, relrun_ptr, item_cut(g->E));

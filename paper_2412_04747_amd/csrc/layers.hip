@@ -170,7 +170,7 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->dXp = c.take<float>((size_t)g->P * d->d_in);
     w->A = c.take<float>(H * g->R * d->d_in);
     w->U = c.take<float>(H * g->R * d->d_in);
-    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles, (int)H));
+    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles_wide, (int)H));
     const size_t parts = std::max<size_t>({(size_t)g->pair_items.num_partials, (size_t)g->relrun_items.num_partials,
                                            (size_t)g->relpair_items.num_partials});
     w->partial = c.take<float>(parts * std::max(d->d_in, d->d_out) * H);   // the run walk keeps one partial row per head
@@ -179,6 +179,16 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->acc_dws = acc ? c.take<float>((size_t)g->R * d->d_out) : nullptr;
     w->acc_dwt = acc ? c.take<float>((size_t)g->R * d->d_out) : nullptr;
     return c.off;
+}
+
+// the chunkings of one list of row tiles that a backward typed linear picks from, and the scratch it needs on them
+struct BwdTiles { const rgnn::TileList* f32; const rgnn::TileList* cu2; const rgnn::TileList* cu1; };
+inline BwdTiles pair_bwd_tiles(const rgnn_graph_t* g) { return {&g->pair_tiles_wide, &g->pair_tiles_cu2, &g->pair_tiles_cu1}; }
+inline BwdTiles node_bwd_tiles(const rgnn_graph_t* g) { return {&g->node_tiles_wide, &g->node_tiles_cu2, nullptr}; }
+size_t tl_bwd_scratch(bool rows16, const BwdTiles& t, int d_in, int d_out) {
+    if (!rows16) return typed_linear_bwd_scratch_floats(d_in, d_out, *t.f32);
+    // two weights, or a split one, use the one-chunk-per-compute-unit list
+    return (size_t)d_in * d_out * std::max((size_t)t.cu2->num_slots, t.cu1 ? 2 * (size_t)t.cu1->num_slots : 0);
 }
 
 // ---- RGCN buffers -----------------------------------------------------------------------
@@ -199,7 +209,7 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->G = c.rows((size_t)g->P * d->d_out, h);
     w->dXp = c.rows((size_t)g->P * d->d_in, h);
     w->dX0 = c.take<float>((size_t)g->N * d->d_in);
-    w->tl_part = c.take<float>(std::max(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles),
+    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_bwd_tiles(g), d->d_in, d->d_out),
                                         typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles)));
     w->partial = c.take<float>((size_t)g->pair_items.num_partials * d->d_out);
     const bool acc = grads_accumulate(d);
@@ -254,11 +264,11 @@ size_t carve_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     w->dWf_att = c.take<float>(fold ? rdd : 0); w->dWf_msg = c.take<float>(fold ? rdd : 0);
     w->dZ = c.rows(nd, h); w->adl = c.take<float>(2 * (size_t)g->E * d->heads);
     w->dKM = c.rows(2 * pd, h); w->dQ = c.rows(nd, h);
-    w->dKp = c.rows(pd, h); w->dVp = c.rows(pd, h);
+    w->dKp = c.rows(pd, h); w->dVp = c.rows(h && fold ? 0 : pd, h);     // folded, bf16 rows: dKp holds the sum of both
     w->dK = c.rows(fold ? 0 : nd, h); w->dV = c.rows(fold ? 0 : nd, h);
     w->dXk = c.take<float>(h || fold ? 0 : nd); w->dXq = c.take<float>(h && !fold ? 0 : nd); w->dXv = c.take<float>(h || fold ? 0 : nd);
-    w->tl_part = c.take<float>(std::max(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles),
-                                        typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->node_tiles)));
+    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_bwd_tiles(g), d->d_in, d->d_out),
+                                        tl_bwd_scratch(h, node_bwd_tiles(g), d->d_in, d->d_out)));
     w->partial = c.take<float>(std::max(2 * (size_t)g->pair_items.num_partials, (size_t)g->dst_items.num_partials) * D);
     const bool acc = grads_accumulate(d);
     const size_t dh = D / d->heads;
@@ -321,15 +331,14 @@ rgnn_status_t tl_fwd(bool bf16, const rgnn::TileList* tiles, const rgnn::TileLis
 
 // Backward typed linear: dXrow = dY W^T (rows through `gather` on both sides when `both_gathered`),
 // dW = sum X^T dY.
-//   rows16 (bf16 rows, width 128): X and dY are bf16; two kernels on the bf16 matrix cores (dY W^T with
-//     the weight as is when its bf16 form W16 exists, split otherwise; X^T dY into per-chunk slots) and
-//     the slot reduction.  dXrow is stored as bf16 (dx16) or fp32.
+//   rows16 (bf16 rows, width 128): X and dY are bf16; one kernel on the bf16 matrix cores (the weight as is when its
+//     bf16 form W16 exists, split into two planes otherwise) and the slot reduction.  dXrow is stored as bf16 (dx16) or fp32.
 //   otherwise: the fused fp32 kernel on fp32 X, W, dY.
-//   wide: the same tiles in fewer chunks, for the weight-gradient kernel;  dx_acc: dXrow += (fp32 dXrow, rows16)
+//   dx_acc: dXrow += (fp32 dXrow, rows16)
 //   dy_stride: the rows of dY are dy_stride * d elements apart (dY not gathered)
 //   ysel / y_alt (rows16, dY not gathered): row i of dY is dY[ysel[i]], or y_alt[ysel[i] & 0x7FFFFFFF] when the
 //     top bit of ysel[i] is set; with yscale it is also multiplied by yscale[i]
-rgnn_status_t tl_bwd(bool rows16, const rgnn::TileList* tiles, const rgnn::TileList* wide, int d, const void* X,
+rgnn_status_t tl_bwd(bool rows16, const BwdTiles& tiles, int d, const void* X,
                      const int32_t* gather, int both_gathered, const float* W32, const void* W16, const void* dY,
                      void* dXrow, bool dx16, float* dW, float* part, const char* label, hipStream_t st,
                      bool dx_acc = false, const int32_t* ysel = nullptr, const void* y_alt = nullptr,
@@ -338,26 +347,20 @@ rgnn_status_t tl_bwd(bool rows16, const rgnn::TileList* tiles, const rgnn::TileL
     if (rows16 && d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward on the bf16 matrix cores: equal widths only");
     if (ysel && (!rows16 || both_gathered)) RGNN_FAIL(RGNN_EUNSUPPORTED, "row selector: bf16 rows and ungathered dY only");
     if (rows16) {
-        TypedLinearBf16Args a{};
-        a.tiles = W16 ? tiles : wide; a.A = dY; a.a_bf16 = 1; a.gather = both_gathered ? gather : ysel; a.scatter_out = both_gathered;
-        a.A_alt = y_alt; a.rowscale = ysel ? yscale : nullptr;
-        a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.transpose_w = 1; a.Y = dXrow; a.y_bf16 = dx16; a.accumulate = dx_acc; a.label = label;
-        a.a_stride = dy_stride;
-        RGNN_TRY(typed_linear_bf16(d, a, st));
-        TypedLinearWgradBf16Args w{};
-        w.tiles = wide; w.X = X; w.gather = gather; w.dy_gathered = both_gathered; w.dY = dY; w.part = part;
-        w.label = wgrad_label(label); w.ysel = ysel; w.dY_alt = y_alt; w.yscale = yscale; w.dy_stride = dy_stride;
-        RGNN_TRY(typed_linear_wgrad_bf16(d, w, st));
-        return typed_linear_slot_reduce(d, d, *wide, part, dW, nullptr, st);
+        TypedLinearBwdBf16Args a{};
+        a.tiles = W16 ? tiles.cu2 : tiles.cu1; a.X = X; a.gather = gather; a.both_gathered = both_gathered;
+        a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.dY = dY; a.dy_stride = dy_stride; a.dXrow = dXrow; a.dx_f32 = !dx16;
+        a.accumulate = dx_acc; a.dW = dW; a.part = part; a.label = label; a.ysel = ysel; a.dY_alt = y_alt; a.yscale = yscale;
+        if (!a.tiles) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: no chunking of this list for an fp32 weight");
+        return typed_linear_bwd_bf16(d, a, st);
     }
     if (dx_acc) RGNN_FAIL(RGNN_EUNSUPPORTED, "accumulating input gradient needs bf16 rows");
     TypedLinearBwdArgs b{};
-    b.tiles = wide; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
+    b.tiles = tiles.f32; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
     b.dy_gathered = both_gathered; b.dXrow = static_cast<float*>(dXrow); b.scatter_dx = both_gathered; b.dW = dW;
     b.part = part; b.label = label; b.dy_stride = dy_stride;
     return typed_linear_bwd(d_in, d, b, st);
 }
-
 }  // namespace
 
 extern "C" rgnn_status_t rgnn_workspace_bytes(const rgnn_graph_t* g, int32_t layer, const rgnn_layer_desc_t* desc,
@@ -499,7 +502,7 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     RGNN_TRY(gather_sum(sel ? g->pair_items_multi : g->pair_items, D, nullptr, g->idx[RGNN_IDX_OUT_DST], 0, ocoef, 1, 0, dPre, w.G,
                         w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", 1, h, h));
     // 2. per pair dXp = dHs W^T; dW[r] = sum X^T dHs
-    RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
+    RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
                     w.dXp, h, static_cast<float*>(dW), w.tl_part, "typed_linear_bwd", st, false, ysel, y_alt, yscale, K));
     // 3. self-loop: dX0 = dPre W0^T, dW0 = X^T dPre
     if (W0) {
@@ -844,7 +847,7 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     dWatt = ga.route(w.acc_rel[0], dWatt, rh * dh * dh); dWmsg = ga.route(w.acc_rel[1], dWmsg, rh * dh * dh);
     dmu = ga.route(w.acc_mu, dmu, rh);
     // 1. output linear: dZ = dOut Wo^T, dWo = Z^T dOut
-    RGNN_TRY(tl_bwd(h, &g->node_tiles, &g->node_tiles_wide, D, sv.Z, perm, 1, Wo32, Wo16, dOr, w.dZ, h, static_cast<float*>(dWo), w.tl_part,
+    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, sv.Z, perm, 1, Wo32, Wo16, dOr, w.dZ, h, static_cast<float*>(dWo), w.tl_part,
                     "node_linear_out_bwd", st));
     // 2. per destination: att (recomputed) and d logit per edge and head, dQ[v][h] = sum dl Ka[pair][h]
     RGNN_TRY(hgt_attend_bwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.dZ, w.dQ, w.adl, w.partial, st, h));
@@ -860,24 +863,32 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
         // unfolded into those of the node-type and of the per-relation matrices
         RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, st));
         RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, st));
-        RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, Xr, psrc, 0, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, dKa, w.dKp,
-                        h, w.dWf_att, w.tl_part, "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
-        RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, Xr, psrc, 0, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, dM, w.dVp,
-                        h, w.dWf_msg, w.tl_part, "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
+        if (h) {
+            //   dKp[p] = dKa Wf_att^T + dM Wf_msg^T in one kernel, with both weight gradients
+            TypedLinearBwdBf16Args b{};
+            b.tiles = &g->pair_tiles_cu1; b.X = X; b.gather = psrc; b.W = w.Wf_att; b.W2 = w.Wf_msg; b.w_bf16 = 1; b.dY = w.dKM;
+            b.dy_stride = 2; b.dXrow = w.dKp; b.dW = w.dWf_att; b.dW2 = w.dWf_msg; b.part = w.tl_part; b.label = "pair_linear_bwd";
+            RGNN_TRY(typed_linear_bwd_bf16(D, b, st));
+        } else {
+            RGNN_TRY(tl_bwd(false, pair_bwd_tiles(g), D, Xr, psrc, 0, w.Wf_att, nullptr, dKa, w.dKp, false, w.dWf_att, w.tl_part,
+                            "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
+            RGNN_TRY(tl_bwd(false, pair_bwd_tiles(g), D, Xr, psrc, 0, w.Wf_msg, nullptr, dM, w.dVp, false, w.dWf_msg, w.tl_part,
+                            "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
+        }
         RGNN_TRY(hgt_fold_bwd(g->T, g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, w.dWf_att, w.dWbd_att, static_cast<float*>(dWk), st));
         RGNN_TRY(hgt_fold_bwd(g->T, g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, w.dWf_msg, w.dWbd_msg, static_cast<float*>(dWv), st));
         RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_att, Watt32, mu32, 1, static_cast<float*>(dWatt), static_cast<float*>(dmu), st));
         RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_msg, Wmsg32, nullptr, 0, static_cast<float*>(dWmsg), nullptr, st));
         // dX = dQ Wq^T + sums over each node's pairs of the two per-pair gradients
-        RGNN_TRY(tl_bwd(h, &g->node_tiles, &g->node_tiles_wide, D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
+        RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
                         w.tl_part, "node_linear_q_bwd", st));
         if (acc) RGNN_TRY(add_into((size_t)g->N * D, static_cast<const float*>(dX), w.dXq, st));
-        RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, w.dXq, dX, st, h, 0, 1, w.dVp));
+        RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, w.dXq, dX, st, h, 0, 1, h ? nullptr : w.dVp));
         return ga.flush(st);
     }
-    RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.tl_part,
+    RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.tl_part,
                     "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
-    RGNN_TRY(tl_bwd(h, &g->pair_tiles, &g->pair_tiles_wide, D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.tl_part,
+    RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.tl_part,
                     "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
     RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_att, Watt32, mu32, 1, static_cast<float*>(dWatt), static_cast<float*>(dmu), st));
     RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_msg, Wmsg32, nullptr, 0, static_cast<float*>(dWmsg), nullptr, st));
@@ -886,11 +897,11 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     RGNN_TRY(node_grad_sum(g, D, w.dVp, nullptr, nullptr, nullptr, w.dV, st, h, h));
     // 6. node linears backward and dX
     //    (bf16 rows: the three input gradients are accumulated into dX by the kernels themselves)
-    RGNN_TRY(tl_bwd(h, &g->node_tiles, &g->node_tiles_wide, D, Xr, perm, 1, Wk32, Wk16, w.dK, h ? dX : static_cast<void*>(w.dXk),
+    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wk32, Wk16, w.dK, h ? dX : static_cast<void*>(w.dXk),
                     false, static_cast<float*>(dWk), w.tl_part, "node_linear_k_bwd", st, h && acc));
-    RGNN_TRY(tl_bwd(h, &g->node_tiles, &g->node_tiles_wide, D, Xr, perm, 1, Wq32, Wq16, w.dQ, h ? dX : static_cast<void*>(w.dXq),
+    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wq32, Wq16, w.dQ, h ? dX : static_cast<void*>(w.dXq),
                     false, static_cast<float*>(dWq), w.tl_part, "node_linear_q_bwd", st, h));
-    RGNN_TRY(tl_bwd(h, &g->node_tiles, &g->node_tiles_wide, D, Xr, perm, 1, Wv32, Wv16, w.dV, h ? dX : static_cast<void*>(w.dXv),
+    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wv32, Wv16, w.dV, h ? dX : static_cast<void*>(w.dXv),
                     false, static_cast<float*>(dWv), w.tl_part, "node_linear_v_bwd", st, h));
     if (!h) {
         if (acc) RGNN_TRY(add_into((size_t)g->N * D, static_cast<const float*>(dX), w.dXk, st));

@@ -112,6 +112,9 @@ struct rgnn_graph {
     rgnn::TileList all_tiles;              // all nodes as one segment (RGCN self-loop)
     rgnn::TileList pair_tiles_wide;        // same tiles as pair_tiles / node_tiles in fewer, longer chunks: for the
     rgnn::TileList node_tiles_wide;        // weight-gradient kernels, whose chunks each flush a d x d partial
+    rgnn::TileList pair_tiles_cu2;         // the same in one chunk per workgroup of a kernel that keeps two (one)
+    rgnn::TileList pair_tiles_cu1;         // workgroups per compute unit
+    rgnn::TileList node_tiles_cu2;
     rgnn::ItemList dst_items;              // CSR edges by destination
     rgnn::ItemList pair_items;             // transposed edges by pair
     rgnn::ItemList pair_items_multi;       // the same, pairs with two or more edges only
@@ -188,7 +191,7 @@ struct TypedLinearBwdArgs {
     int sel_heads = 0;
     int dy_stride = 1;               // rows of dY are dy_stride * d_out floats apart (1 or 2)
 };
-// bf16 matrix-core variant (typed_linear_bf16.hip): Y[i] = A[g(i)] W[seg]  (or W[seg]^T)
+// bf16 matrix-core variant (typed_linear_bf16.hip): Y[i] = A[g(i)] W[seg]
 struct TypedLinearBf16Args {
     const TileList* tiles;
     const void* A;           // rows: bf16 (a_bf16) or fp32
@@ -197,38 +200,40 @@ struct TypedLinearBf16Args {
     int scatter_out;         // 1: row i writes Y[gather[i]]
     const void* W;           // [segs][d][d]: bf16 (w_bf16) or fp32
     int w_bf16;
-    int transpose_w;         // 1: multiply by W[seg]^T
     void* Y;                 // output rows: bf16 (y_bf16) or fp32
     int y_bf16;
-    int accumulate;          // 1: Y += result (fp32 Y)
     const char* label;
-    const void* A_alt = nullptr;   // gathered rows only: a gather entry with the top bit set reads row
-                                   // (entry & 0x7FFFFFFF) of this tensor instead of A
-    const float* rowscale = nullptr;   // bf16 rows only: row i of the tiles is multiplied by rowscale[i]
-    int a_stride = 1, y_stride = 1;    // rows of A / Y are that many widths apart
+    int y_stride = 1;        // rows of Y are that many widths apart
 };
 rgnn_status_t typed_linear_bf16(int d, const TypedLinearBf16Args& a, hipStream_t st);
 
-// bf16 matrix-core weight gradient: part[slot] = sum over the chunk's rows of X[g(i)]^T dY[i];
-// typed_linear_slot_reduce then adds a segment's slots into dW.
-struct TypedLinearWgradBf16Args {
+// Backward on the bf16 matrix cores (typed_linear_bwd_bf16.hip): X, dY and (unless dx_f32) dXrow rows in bf16.
+struct TypedLinearBwdBf16Args {
     const TileList* tiles;
-    const void* X;           // bf16 rows
-    const int32_t* gather;
-    int dy_gathered;         // 1: dY rows are read through the gather list as well
-    const void* dY;          // bf16 rows
-    float* part;
+    const void* X;
+    const int32_t* gather;   // row i reads X[gather[i]]
+    int both_gathered;       // 1: dY rows are read and dXrow rows written through the gather list as well
+    const void* W;           // [segs][d][d]: bf16 (w_bf16) or fp32
+    int w_bf16;
+    const void* W2 = nullptr;   // optional second weight (bf16) for the second half of dY rows two widths wide
+    const void* dY;
+    int dy_stride = 1;       // rows of dY are that many widths apart
+    void* dXrow;             // dY W^T (+ dY2 W2^T)
+    int dx_f32 = 0;
+    int accumulate = 0;      // fp32 dXrow += result
+    float* dW;               // [segs][d][d]
+    float* dW2 = nullptr;
+    float* part;             // scratch: num_slots * d * d floats per weight
     const char* label;
     // optional row selector for dY (ungathered dY only): row i is dY[ysel[i]], or dY_alt[ysel[i] & 0x7FFFFFFF]
-    // when the top bit of ysel[i] is set
+    // when the top bit of ysel[i] is set; with yscale it is also multiplied by yscale[i]
     const int32_t* ysel = nullptr;
     const void* dY_alt = nullptr;
-    const float* yscale = nullptr;   // with ysel: row i is also multiplied by yscale[i]
-    int dy_stride = 1;               // rows of dY are that many widths apart (not with ysel)
+    const float* yscale = nullptr;
 };
-rgnn_status_t typed_linear_wgrad_bf16(int d, const TypedLinearWgradBf16Args& a, hipStream_t st);
-rgnn_status_t typed_linear_slot_reduce(int d_in, int d_out, const TileList& tiles, const float* part, float* dW,
-                                       float* Avec, hipStream_t st);
+rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipStream_t st);
+// dW[s] (kn floats) and, when given, dW2[s] (kd floats) = sums of the segments' slots of kn + kd floats
+rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2, hipStream_t st);
 
 size_t typed_linear_bwd_scratch_floats(int d_in, int d_out, const TileList& t, int vectors = 1);   // vectors: of a slot's vector part
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st);

@@ -1199,8 +1199,10 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
     const dim3 grid(blocks_for((size_t)g->N, 256 / (D / (in_bf16 ? 8 : 4))));
     if (ds_dst)
         RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 1>), grid, dim3(256), 0, st, a));
+    else if (dXp2 && (in_bf16 || out_bf16))
+        RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: a second row tensor is built for fp32 rows");
     else if (dXp2)
-        RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 2>), grid, dim3(256), 0, st, a));
+        RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, 2>), grid, dim3(256), 0, st, a));
     else
         RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 0>), grid, dim3(256), 0, st, a));
     RGNN_CHECK_LAUNCH();

@@ -594,7 +594,7 @@ __global__ __launch_bounds__(G * C4) void slot_reduce_kernel(const float* __rest
 
 // Few segments with many slots each (a self-loop weight, node types, few relations): many lane groups on narrow column
 // ranges; many segments with a few slots each: few groups, wide ranges.
-static rgnn_status_t reduce_slots(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* Avec, hipStream_t st) {
+rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* Avec, hipStream_t st) {
     KernelTimer kt(st, "typed_linear_bwd.reduce");
     const int n4 = (kn + kd) / 4;
     if (tiles.num_slots > 8 * tiles.num_segs)
@@ -861,12 +861,7 @@ static rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
         }
         if (!done) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: this combination of gather / scatter / rowscale is not built");
     }
-    return reduce_slots(*a.tiles, a.part, KD * ND, KD * (KD <= 64 && a.ysel && a.hcoef ? a.sel_heads : 1), a.dW, a.Avec, st);
-}
-
-rgnn_status_t typed_linear_slot_reduce(int d_in, int d_out, const TileList& tiles, const float* part, float* dW,
-                                       float* Avec, hipStream_t st) {
-    return reduce_slots(tiles, part, d_in * d_out, d_in, dW, Avec, st);
+    return typed_linear_slot_reduce(*a.tiles, a.part, KD * ND, KD * (KD <= 64 && a.ysel && a.hcoef ? a.sel_heads : 1), a.dW, a.Avec, st);
 }
 
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st) {

@@ -129,6 +129,30 @@ def test_walk_lengths(dtype, d, H):
          dtype=dtype)
 
 
+@pytest.mark.parametrize("tied", [True, False])
+@pytest.mark.parametrize("dtype,d,H", [("bf16", 128, 4), ("f32", 128, 4), ("f32", 64, 4)])
+def test_relation_sizes_around_the_row_tiles(dtype, d, H, tied):
+    """Relations whose pairs fill the 64-row tiles of the typed linears exactly, less one and plus one, a single pair, none,
+    and several tiles, with sources of one node type per relation (folded weights, key and message half in one kernel)
+    and of mixed types (node linears of their own)."""
+    rng = np.random.default_rng(700 + d)
+    sizes = [64, 1, 63, 0, 65, 128, 31, 129, 300]
+    T, R, per = 3, len(sizes), 310
+    N = T * per + 1
+    ntype = np.minimum(np.arange(N) // per, T - 1).astype(np.int32)
+    src, rel = [], np.repeat(np.arange(R), sizes)
+    for r, n in enumerate(sizes):
+        src.append(rng.permutation(per)[:n] + (per * (r % T) if tied else 0))
+        if not tied and n > 1:
+            src[-1][: n // 2] += per
+    src = np.concatenate(src)
+    dst = rng.integers(0, N, len(src))
+    p = synth.hgt_params(rng, N, T, R, d, H, with_mu=True)
+    if dtype == "bf16":
+        p = {k: (None if v is None else synth.round_to_bf16(v)) for k, v in p.items()}
+    _run(N, T, R, src.astype(np.int32), dst.astype(np.int32), rel.astype(np.int32), ntype, p, d, H, f"tiles-{dtype}-{tied}", dtype=dtype)
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None

@@ -163,3 +163,23 @@ def test_config5_full_size_bf16():
     c = synth.config(5)
     _run(c["N"], c["R"], c["src"], c["dst"], c["rel"], c, 128, "in_degree_per_rel", "none", False, tag="C5",
          dtype="bf16")
+
+
+@pytest.mark.parametrize("norm", ["none", "in_degree_per_rel"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 128), ("f32", 64), ("f32", 32)])
+def test_relation_sizes_around_the_row_tiles(dtype, d, norm):
+    """Relations whose pairs fill the 64-row tiles of the typed linears exactly, less one and plus one, one of a single
+    pair, an empty one and one of several tiles; a third of the pairs have two edges."""
+    rng = np.random.default_rng(600 + d)
+    sizes = [64, 1, 63, 0, 65, 128, 31, 33, 127, 129, 300, 16, 15]
+    N, R = 310, len(sizes)
+    src = np.concatenate([rng.permutation(N)[:n] for n in sizes])
+    rel = np.repeat(np.arange(R), sizes)
+    dst = rng.integers(0, N, len(src))
+    two = rng.random(len(src)) < 0.33
+    src, rel, dst = (np.concatenate([a, b]).astype(np.int32) for a, b in
+                     ((src, src[two]), (rel, rel[two]), (dst, rng.integers(0, N, int(two.sum())))))
+    p = synth.rgcn_params(rng, N, R, d, d, self_loop=True)
+    if dtype == "bf16":
+        p = {k: (None if v is None else synth.round_to_bf16(v)) for k, v in p.items()}
+    _run(N, R, src, dst, rel, p, d, norm, "none", True, tag=f"tiles-{dtype}-d{d}", dtype=dtype)
