@@ -247,7 +247,7 @@ size_t carve_hgt_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* 
 size_t carve_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, HgtFwdWs* w) {
     Carver c(base);
     const size_t rdd = (size_t)g->R * d->d_out * d->d_out, fdd = hgt_folded(g, d) ? rdd : 0;
-    w->Wbd_att = c.take<float>(rdd); w->Wbd_msg = c.take<float>(rdd);
+    w->Wbd_att = c.take<float>(rdd - fdd); w->Wbd_msg = c.take<float>(rdd - fdd);
     w->Wf_att = c.take<float>(fdd); w->Wf_msg = c.take<float>(fdd);
     w->part_ms = c.take<float>(2 * (size_t)g->dst_items.num_partials * d->heads);
     w->partial = c.take<float>((size_t)g->dst_items.num_partials * d->d_out);
@@ -258,8 +258,8 @@ size_t carve_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     const bool h = rows_bf16(d);
     const bool fold = hgt_folded(g, d);
     const size_t D = d->d_out, rdd = (size_t)g->R * D * D, nd = (size_t)g->N * D, pd = (size_t)g->P * D;
-    w->Wbd_att = c.take<float>(rdd); w->Wbd_msg = c.take<float>(rdd);
-    w->dWbd_att = c.take<float>(rdd); w->dWbd_msg = c.take<float>(rdd);
+    w->Wbd_att = c.take<float>(fold ? 0 : rdd); w->Wbd_msg = c.take<float>(fold ? 0 : rdd);
+    w->dWbd_att = c.take<float>(fold ? 0 : rdd); w->dWbd_msg = c.take<float>(fold ? 0 : rdd);
     w->Wf_att = c.take<float>(fold ? rdd : 0); w->Wf_msg = c.take<float>(fold ? rdd : 0);
     w->dWf_att = c.take<float>(fold ? rdd : 0); w->dWf_msg = c.take<float>(fold ? rdd : 0);
     w->dZ = c.rows(nd, h); w->adl = c.take<float>(2 * (size_t)g->E * d->heads);
@@ -754,18 +754,16 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
     const size_t carved = carve_hgt_fwd(g, desc, workspace, &w);
     saved = saved_or_scratch(g, RGNN_LAYER_HGT, desc, saved, workspace, carved);
     Bf16Stage stg(workspace, carved, bf16, st);
-    const size_t tdd = (size_t)g->T * D * D, rh = (size_t)g->R * H, dh = D / H;
-    // fp32 copies: at width 128 only of the small per-relation parameters (their expansion is an fp32 kernel)
+    const size_t tdd = (size_t)g->T * D * D;
+    // fp32 copies of what the fp32 kernels read (below width 128; the kernels on weights alone read the caller's storage)
     const bool fold = hgt_folded(g, desc);
     const float* X32 = !h ? stg.in(X, (size_t)g->N * D) : nullptr;
-    const float* Wk32 = !h || fold ? stg.in(Wk, tdd) : nullptr;      // folding multiplies weights in fp32
+    const float* Wk32 = !h && !fold ? stg.in(Wk, tdd) : nullptr;
     const float* Wq32 = !h ? stg.in(Wq, tdd) : nullptr;
-    const float* Wv32 = !h || fold ? stg.in(Wv, tdd) : nullptr;
+    const float* Wv32 = !h && !fold ? stg.in(Wv, tdd) : nullptr;
     const float* Wo32 = !h ? stg.in(Wo, tdd) : nullptr;
-    const float* Watt32 = stg.in(Watt, rh * dh * dh);
-    const float* Wmsg32 = stg.in(Wmsg, rh * dh * dh);
-    const float* mu32 = stg.in(mu, rh);
     RGNN_TRY(stg.status);
+    const HgtWeights hw{Wk, Wv, Watt, Wmsg, mu, bf16, g->rel_src_type, D, H};
     carve_hgt_saved(g, desc, saved, &sv);
     const int32_t* perm = g->idx[RGNN_IDX_NTYPE_PERM];
     const int32_t* psrc = g->idx[RGNN_IDX_PAIR_SRC];
@@ -778,27 +776,25 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
         RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, X32, X16, perm, 1, Wk32, Wk16, sv.K, h, "node_linear_k", st));
         RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, X32, X16, perm, 1, Wv32, Wv16, sv.V, h, "node_linear_v", st));
     }
-    // 2. per (relation, head) matrices as block-diagonal d x d weights; mu / sqrt(dh) folded into the attention one
-    RGNN_TRY(hgt_expand(g->R, D, H, Watt32, mu32, 1, w.Wbd_att, st));
-    RGNN_TRY(hgt_expand(g->R, D, H, Wmsg32, nullptr, 0, w.Wbd_msg, st));
-    // 3. compact per pair, side by side in KM[p]: Ka[p] = K[src_p] Watt[r], M[p] = V[src_p] Wmsg[r]
+    // 2. compact per pair, side by side in KM[p]: Ka[p] = K[src_p] Watt[r], M[p] = V[src_p] Wmsg[r]
     void* const Mrow = h ? static_cast<void*>(static_cast<uint16_t*>(sv.KM) + D) : static_cast<void*>(static_cast<float*>(sv.KM) + D);
     if (fold) {
         //    = X[src_p] (Wk[type of r's sources] Watt[r]) and X[src_p] (Wv[type] Wmsg[r])
         //    With bf16 rows the products are rounded to bf16 once (as K and V would have been) and feed the
         //    matrix cores as they are; rows in the storage of the intermediates: the caller's bf16 X at width
         //    128, its fp32 copy otherwise.
-        RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, st));
-        RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, st));
+        RGNN_TRY(hgt_fold(g->R, hw, w.Wf_att, w.Wf_msg, h, st));
         RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_att), R16(w.Wf_att), sv.KM, h, "pair_linear_att", st, 0, 2));
         RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_msg), R16(w.Wf_msg), Mrow, h, "pair_linear_msg", st, 0, 2));
     } else {
+        //    with the per-(relation, head) matrices as block-diagonal d x d weights
+        RGNN_TRY(hgt_expand(g->R, hw, w.Wbd_att, w.Wbd_msg, st));
         RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.K), R16(sv.K), psrc, 0, w.Wbd_att, nullptr, sv.KM, h, "pair_linear_att", st, 0, 2));
         RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.V), R16(sv.V), psrc, 0, w.Wbd_msg, nullptr, Mrow, h, "pair_linear_msg", st, 0, 2));
     }
-    // 4. one walk per destination: logit per edge and head, softmax over the destination's edges, Z[v][h] = sum_e att[e][h] M[pair_e][h]
+    // 3. one walk per destination: logit per edge and head, softmax over the destination's edges, Z[v][h] = sum_e att[e][h] M[pair_e][h]
     RGNN_TRY(hgt_attend_fwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.partial, w.part_ms, st, h));
-    // 5. out = Z Wo[type]
+    // 4. out = Z Wo[type]
     RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, R32(sv.Z), R16(sv.Z), perm, 1, Wo32, Wo16, out, false, "node_linear_out", st));
     return RGNN_OK;
 }
@@ -825,13 +821,11 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     const size_t tdd = (size_t)g->T * D * D, rh = (size_t)g->R * H, dh = D / H;
     const bool fold = hgt_folded(g, desc);
     const float* X32 = !h ? stg.in(X, (size_t)g->N * D) : nullptr;
-    const float* Wk32 = !h || fold ? stg.in(Wk, tdd) : nullptr;
+    const float* Wk32 = !h && !fold ? stg.in(Wk, tdd) : nullptr;
     const float* Wq32 = !h ? stg.in(Wq, tdd) : nullptr;
-    const float* Wv32 = !h || fold ? stg.in(Wv, tdd) : nullptr;
+    const float* Wv32 = !h && !fold ? stg.in(Wv, tdd) : nullptr;
     const float* Wo32 = !h ? stg.in(Wo, tdd) : nullptr;
-    const float* Watt32 = stg.in(Watt, rh * dh * dh);
-    const float* Wmsg32 = stg.in(Wmsg, rh * dh * dh);
-    const float* mu32 = stg.in(mu, rh);
+    const HgtWeights hw{Wk, Wv, Watt, Wmsg, mu, bf16, g->rel_src_type, D, H};
     const float* dO32 = !h ? stg.in(dOut, (size_t)g->N * D) : nullptr;
     RGNN_TRY(stg.status);
     carve_hgt_saved(g, desc, const_cast<void*>(saved), &sv);
@@ -856,13 +850,10 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     const void* dKa = w.dKM;
     const void* dM = h ? static_cast<const void*>(static_cast<const uint16_t*>(w.dKM) + D) : static_cast<const void*>(static_cast<const float*>(w.dKM) + D);
     // 4. per-pair linears backward
-    RGNN_TRY(hgt_expand(g->R, D, H, Watt32, mu32, 1, w.Wbd_att, st));
-    RGNN_TRY(hgt_expand(g->R, D, H, Wmsg32, nullptr, 0, w.Wbd_msg, st));
     if (fold) {
         // the folded weights take the per-pair gradients straight to X's rows; their own gradients are
         // unfolded into those of the node-type and of the per-relation matrices
-        RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, h ? nullptr : w.Wf_att, h ? w.Wf_att : nullptr, st));
-        RGNN_TRY(hgt_fold(g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, h ? nullptr : w.Wf_msg, h ? w.Wf_msg : nullptr, st));
+        RGNN_TRY(hgt_fold(g->R, hw, w.Wf_att, w.Wf_msg, h, st));
         if (h) {
             //   dKp[p] = dKa Wf_att^T + dM Wf_msg^T in one kernel, with both weight gradients
             TypedLinearBwdBf16Args b{};
@@ -875,10 +866,8 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
             RGNN_TRY(tl_bwd(false, pair_bwd_tiles(g), D, Xr, psrc, 0, w.Wf_msg, nullptr, dM, w.dVp, false, w.dWf_msg, w.tl_part,
                             "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
         }
-        RGNN_TRY(hgt_fold_bwd(g->T, g->R, D, H, g->rel_src_type, Wk32, w.Wbd_att, w.dWf_att, w.dWbd_att, static_cast<float*>(dWk), st));
-        RGNN_TRY(hgt_fold_bwd(g->T, g->R, D, H, g->rel_src_type, Wv32, w.Wbd_msg, w.dWf_msg, w.dWbd_msg, static_cast<float*>(dWv), st));
-        RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_att, Watt32, mu32, 1, static_cast<float*>(dWatt), static_cast<float*>(dmu), st));
-        RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_msg, Wmsg32, nullptr, 0, static_cast<float*>(dWmsg), nullptr, st));
+        RGNN_TRY(hgt_fold_bwd(g->T, g->R, hw, w.dWf_att, w.dWf_msg, static_cast<float*>(dWk), static_cast<float*>(dWv),
+                              static_cast<float*>(dWatt), static_cast<float*>(dWmsg), static_cast<float*>(dmu), st));
         // dX = dQ Wq^T + sums over each node's pairs of the two per-pair gradients
         RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
                         w.tl_part, "node_linear_q_bwd", st));
@@ -886,12 +875,13 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
         RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, w.dXq, dX, st, h, 0, 1, h ? nullptr : w.dVp));
         return ga.flush(st);
     }
+    RGNN_TRY(hgt_expand(g->R, hw, w.Wbd_att, w.Wbd_msg, st));
     RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.tl_part,
                     "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
     RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.tl_part,
                     "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
-    RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_att, Watt32, mu32, 1, static_cast<float*>(dWatt), static_cast<float*>(dmu), st));
-    RGNN_TRY(hgt_extract(g->R, D, H, w.dWbd_msg, Wmsg32, nullptr, 0, static_cast<float*>(dWmsg), nullptr, st));
+    RGNN_TRY(hgt_extract(g->R, hw, w.dWbd_att, w.dWbd_msg, static_cast<float*>(dWatt), static_cast<float*>(dWmsg),
+                         static_cast<float*>(dmu), st));
     // 5. dK[u], dV[u] = sums over u's pairs
     RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, nullptr, w.dK, st, h, h));
     RGNN_TRY(node_grad_sum(g, D, w.dVp, nullptr, nullptr, nullptr, w.dV, st, h, h));

@@ -56,20 +56,19 @@ rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, c
 rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const float* ds_dst, const float* wtp,
                             const float* extra, void* dX, hipStream_t st, int in_bf16 = 0, int out_bf16 = 0, int heads = 1,
                             const void* dXp2 = nullptr);
-// hgt.hip: products of a node-type weight with the expanded per-relation weight of the relation's source type
-//   Wf[r] = Wnode[rel_type[r]] Wbd[r], stored as fp32 (Wf) or rounded to bf16 (Wf16); pass one of the two
-rgnn_status_t hgt_fold(int R, int d, int H, const int32_t* rel_type, const float* Wnode, const float* Wbd, float* Wf,
-                       void* Wf16, hipStream_t st);
-//   dWbd[r] (entries inside the head blocks) = Wnode[rel_type[r]]^T dWf[r]
-//   dWnode[t] = sum over the relations r of source type t, in ascending r, of dWf[r] Wbd[r]^T
-rgnn_status_t hgt_fold_bwd(int T, int R, int d, int H, const int32_t* rel_type, const float* Wnode, const float* Wbd,
-                           const float* dWf, float* dWbd, float* dWnode, hipStream_t st);
+// hgt.hip: the layer's weights in the caller's storage (fp32 or bf16); rel_type = node type of each relation's sources
+struct HgtWeights { const void* Wk; const void* Wv; const void* Watt; const void* Wmsg; const void* mu; bool bf16; const int32_t* rel_type; int d; int H; };
+//   folded weights of both halves: Wf_att[r] = Wk[rel_type[r]] blockdiag(mu / sqrt(dh) Watt[r]), Wf_msg[r] = Wv[..] blockdiag(Wmsg[r])
+rgnn_status_t hgt_fold(int R, const HgtWeights& w, void* Wf_att, void* Wf_msg, int out_bf16, hipStream_t st);
+//   and the gradients of all the weights from those of the folded ones (dWk, dWv: sums over a type's relations in ascending order)
+rgnn_status_t hgt_fold_bwd(int T, int R, const HgtWeights& w, float* dWf_att, float* dWf_msg, float* dWk, float* dWv, float* dWatt,
+                           float* dWmsg, float* dmu, hipStream_t st);
+//   block-diagonal expansion of both per-(relation, head) weights (the attention one scaled) and its backward
+rgnn_status_t hgt_expand(int R, const HgtWeights& w, float* Wbd_att, float* Wbd_msg, hipStream_t st);
+rgnn_status_t hgt_extract(int R, const HgtWeights& w, float* dWbd_att, float* dWbd_msg, float* dWatt, float* dWmsg, float* dmu,
+                          hipStream_t st);
 rgnn_status_t rgat_param_finish(int R, int kd, int nd, const float* W, const float* w_s, const float* w_t,
                                 const float* A, const float* U, float* dW, float* dw_s, float* dw_t, hipStream_t st);
-// hgt.hip
-rgnn_status_t hgt_expand(int R, int d, int H, const float* W, const float* mu, int scaled, float* Wbd, hipStream_t st);
-rgnn_status_t hgt_extract(int R, int d, int H, const float* dWbd, const float* W, const float* mu, int scaled, float* dW,
-                          float* dmu, hipStream_t st);
 // hgt_walk.hip: the edge walks of HGT over the key / message rows KM[p][2][D] of the pairs (rows fp32 or bf16)
 //   forward: Z[v] = sum_e att_e M[pair_e], att = softmax per head of Ka[pair_e] . Q[v]; ms[v][h] = (max, sum of exp)
 rgnn_status_t hgt_attend_fwd(const rgnn_graph* g, int D, int H, const void* KM, const void* Q, void* Z, float* ms,
