@@ -271,65 +271,6 @@ __global__ __launch_bounds__(kFusedThreads) void rgat_aggregate_fwd_kernel(Fused
     for (int g4 = first; 4 * g4 < a.single_n; g4 += stride) fwd_single<D, LPH, LDSW>(a, ws_lds, g4, c);
 }
 
-// Cut destinations: out[v] = sum_i exp(m_i - M) partial_i / S with M = max_i m_i, S = sum_i s_i exp(m_i - M) over the
-// destination's pieces i, in piece order, per head.  One workgroup per cut destination; a lane works on the head its
-// columns belong to (every lane walks the piece statistics of its head itself: a destination has few pieces).
-template <int D, int LPH>
-__global__ __launch_bounds__(1024) void rgat_combine_fwd_kernel(const int32_t* __restrict__ split_row,
-                                                                const int32_t* __restrict__ split_ptr,
-                                                                const float* __restrict__ partial,
-                                                                const float2* __restrict__ part_ms, float* __restrict__ out,
-                                                                float2* __restrict__ ms) {
-    constexpr int LPR = D / 4, G = 1024 / LPR, H = LPR / LPH;
-    __shared__ float4 red[1024];
-    __shared__ float redw[H][16];
-    const int sidx = blockIdx.x, g = threadIdx.x / LPR, c = threadIdx.x % LPR, head = c / LPH;
-    const int p0 = split_ptr[sidx], p1 = split_ptr[sidx + 1];
-    // maximum and sum per head over the pieces: thread t takes head t % H of pieces t / H, t / H + 1024 / H, ...;
-    // the lanes of a wavefront that share a head are reduced with a butterfly over the strides H, 2H, ..., 32, the
-    // sixteen wavefronts' results are combined in wavefront order
-    const int rh = threadIdx.x % H, wv = threadIdx.x >> 6;
-    float mloc = -INFINITY;
-    for (int p = p0 + (int)threadIdx.x / H; p < p1; p += 1024 / H) mloc = fmaxf(mloc, part_ms[(size_t)p * H + rh].x);
-#pragma unroll
-    for (int o = 32; o >= H; o >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, o));
-    if ((threadIdx.x & 63) < H) redw[rh][wv] = mloc;
-    __syncthreads();
-    float M = redw[head][0];
-    for (int k = 1; k < 16; ++k) M = fmaxf(M, redw[head][k]);
-    float Mr = redw[rh][0];
-    for (int k = 1; k < 16; ++k) Mr = fmaxf(Mr, redw[rh][k]);
-    __syncthreads();
-    float sloc = 0.f;
-    for (int p = p0 + (int)threadIdx.x / H; p < p1; p += 1024 / H) {
-        const float2 t = part_ms[(size_t)p * H + rh];
-        sloc += t.y * __expf(t.x - Mr);
-    }
-#pragma unroll
-    for (int o = 32; o >= H; o >>= 1) sloc += __shfl_xor(sloc, o);
-    if ((threadIdx.x & 63) < H) redw[rh][wv] = sloc;
-    __syncthreads();
-    float S = redw[head][0];
-    for (int k = 1; k < 16; ++k) S += redw[head][k];
-    float4 acc0 = make_float4(0.f, 0.f, 0.f, 0.f), acc1 = acc0;
-    for (int p = p0 + g; p < p1; p += 2 * G) {
-        fma4(acc0, __expf(part_ms[(size_t)p * H + head].x - M), *reinterpret_cast<const float4*>(partial + (size_t)p * D + c * 4));
-        if (p + G < p1)
-            fma4(acc1, __expf(part_ms[(size_t)(p + G) * H + head].x - M), *reinterpret_cast<const float4*>(partial + (size_t)(p + G) * D + c * 4));
-    }
-    fma4(acc0, 1.f, acc1);
-    red[threadIdx.x] = acc0;
-    __syncthreads();
-    if (g == 0) {
-        float4 t = red[c];
-        for (int k = 1; k < G; ++k) fma4(t, 1.f, red[k * LPR + c]);
-        const float inv = 1.f / S;
-        const size_t v = (size_t)split_row[sidx];
-        *reinterpret_cast<float4*>(out + v * D + c * 4) = make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv);
-        if (c % LPH == 0) ms[v * H + head] = make_float2(M, S);
-    }
-}
-
 // ---------------------------------------------------------------- backward
 
 // For every CSR edge e of destination v, with the row h = Hs[pair_e] gathered once:
@@ -491,14 +432,7 @@ rgnn_status_t rgat_aggregate_fwd(const rgnn_graph* g, int D, int H, const float*
         if (ldsw) RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, true>, g, lds, groups, DD / 4, a, st)));
         else RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, false>, g, 0, groups, DD / 4, a, st)));
     }
-    if (L.num_split > 0) {
-        KernelTimer kt(st, "aggregate_fwd.combine");
-        RGNN_DISPATCH_DH(D, H, hipLaunchKernelGGL((rgat_combine_fwd_kernel<DD, LL>), dim3(L.num_split), dim3(1024), 0, st, L.split_row,
-                                                  L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), out,
-                                                  reinterpret_cast<float2*>(ms)));
-        RGNN_CHECK_LAUNCH();
-    }
-    return RGNN_OK;
+    return combine_softmax(L, D, H, partial, part_ms, out, 0, ms, "aggregate_fwd.combine", st);
 }
 
 rgnn_status_t rgat_edge_dot_bwd(const rgnn_graph* g, int D, int H, const float* Hs, const float* w_s, const float* s_dst,

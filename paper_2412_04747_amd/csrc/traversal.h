@@ -44,9 +44,10 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
                          int src_bf16 = 0, int out_bf16 = 0, const Rank1* r1 = nullptr, float* sum2 = nullptr,
                          int sum2_stride = 1);
 // rows of the cut segments of a list from their pieces: plain sums (widths 32 .. 256), and sums whose pieces carry their
-// own softmax statistics (max, sum) per head
+// own softmax statistics (max, sum) per head.  copies: that many independent sets of partial rows (one after the other)
+// and of output rows (out_copy elements apart).
 rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, void* out, int out_bf16, const char* label,
-                               hipStream_t st, const Rank1* r1 = nullptr, int heads = 1);
+                               hipStream_t st, const Rank1* r1 = nullptr, int heads = 1, int copies = 1, size_t out_copy = 0);
 rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
                               int out_bf16, float* ms, const char* label, hipStream_t st);
 // H weighted sums of the same gathered rows in one walk (coef [entries][H]); out [H][out_rows][D]

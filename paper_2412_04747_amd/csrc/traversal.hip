@@ -605,34 +605,49 @@ __global__ __launch_bounds__(256) void gather_heads_rows_kernel(GatherArgs a, in
     }
 }
 
-// out[split_row[s]] = sum of partial rows [split_ptr[s], split_ptr[s+1]).  One workgroup per
-// cut segment: group g of D/4 lanes sums partial rows g, g + G, g + 2G, ... (two at a time),
-// then the G group sums are added in group order through LDS, so the summation order is fixed.
-template <int D, typename TO>
-__global__ __launch_bounds__(1024) void combine_partials_kernel(const int32_t* __restrict__ split_row,
-                                                                const int32_t* __restrict__ split_ptr,
-                                                                const float* __restrict__ partial,
-                                                                TO* __restrict__ out, Rank1 r1, int lanes_per_head) {
-    constexpr int LPR = D / 4, G = 1024 / LPR;
-    __shared__ float4 red[1024];
-    const int s = blockIdx.x, g = threadIdx.x / LPR, c4 = threadIdx.x % LPR;
+// out[split_row[s]] = sum of partial rows [split_ptr[s], split_ptr[s+1]).  A workgroup of TH threads owns C4 float4 columns
+// (blockIdx.z) of one cut segment (and of one copy of the rows, blockIdx.y): group g of C4 lanes sums partial rows g, g + G,
+// g + 2G, ..., four at a time with their loads independent, then the G group sums are added in group order through LDS,
+// so the summation order is fixed.
+template <int D, typename TO, int TH, int C4>
+__global__ __launch_bounds__(TH) void combine_partials_kernel(const int32_t* __restrict__ split_row,
+                                                              const int32_t* __restrict__ split_ptr,
+                                                              const float* __restrict__ partial, TO* __restrict__ out,
+                                                              size_t partial_copy, size_t out_copy, Rank1 r1, int lanes_per_head) {
+    constexpr int G = TH / C4;
+    __shared__ float4 red[TH];
+    partial += blockIdx.y * partial_copy;
+    out += blockIdx.y * out_copy;
+    const int s = blockIdx.x, g = threadIdx.x / C4, c = threadIdx.x % C4, c4 = blockIdx.z * C4 + c;
     const int p0 = split_ptr[s], p1 = split_ptr[s + 1];
     float4 acc0 = make_float4(0.f, 0.f, 0.f, 0.f), acc1 = acc0;
-    for (int p = p0 + g; p < p1; p += 2 * G) {
-        fma4(acc0, 1.f, *reinterpret_cast<const float4*>(partial + (size_t)p * D + c4 * 4));
-        if (p + G < p1) fma4(acc1, 1.f, *reinterpret_cast<const float4*>(partial + (size_t)(p + G) * D + c4 * 4));
+    for (int p = p0 + g; p < p1; p += 4 * G) {
+        float4 r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = *reinterpret_cast<const float4*>(partial + (size_t)min(p + u * G, p1 - 1) * D + c4 * 4);
+        fma4(acc0, 1.f, r[0]);
+        if (p + G < p1) fma4(acc1, 1.f, r[1]);
+        if (p + 2 * G < p1) fma4(acc0, 1.f, r[2]);
+        if (p + 3 * G < p1) fma4(acc1, 1.f, r[3]);
     }
     fma4(acc0, 1.f, acc1);
     red[threadIdx.x] = acc0;
     __syncthreads();
     if (g == 0) {
-        float4 t = red[c4];
-        for (int k = 1; k < G; ++k) fma4(t, 1.f, red[k * LPR + c4]);
+        float4 t = red[c];
+        const int n = min(G, p1 - p0);            // groups that had a piece
+        for (int k = 1; k < n; ++k) fma4(t, 1.f, red[k * C4 + c]);
         float tv[4] = {t.x, t.y, t.z, t.w};
         add_rank1<D>(r1, lanes_per_head, (size_t)split_row[s], c4, tv);
         store_cols(out + (size_t)split_row[s] * D + c4 * 4, tv);
     }
 }
+// Hub nodes and pairs: mostly two or three pieces per cut segment and thousands of segments, so small workgroups (1024
+// threads with two loads in flight took 33 us for the destinations of a graph of 2M edges at width 128, 256 threads with
+// four 11 us).  Run lists of relations: a few dozen segments with thousands of pieces, so large workgroups on narrow
+// column ranges (843k runs of 60 relations in 13k pieces, width 128: 256 threads 61 us, 1024 on whole rows 26 us, on 8
+// float4 13 us).
+inline bool few_long_segments(const ItemList& L) { return L.num_partials > 32 * L.num_split; }
 
 // Cut destinations of a softmax-weighted sum: the pieces carry (max m_i, sum s_i of exp(l - m_i)) per head and the
 // unnormalised row; out[v] = sum_i exp(m_i - M) partial_i / S with M = max_i m_i, S = sum_i s_i exp(m_i - M).  One workgroup
@@ -1072,13 +1087,19 @@ rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* part
 }
 
 rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, void* out, int out_bf16, const char* label,
-                               hipStream_t st, const Rank1* r1, int heads) {
+                               hipStream_t st, const Rank1* r1, int heads, int copies, size_t out_copy) {
     if (L.num_split == 0) return RGNN_OK;
     const Rank1 r1v = r1 ? *r1 : Rank1{nullptr, 0, nullptr, nullptr};
     KernelTimer kt(st, label);
 #define RGNN_LAUNCH_COMBINE(DD_, TO_)                                                                                  \
-    hipLaunchKernelGGL((combine_partials_kernel<DD_, TO_>), dim3(L.num_split), dim3(1024), 0, st, L.split_row, L.split_ptr, \
-                       partial, static_cast<TO_*>(out), r1v, (DD_ / 4) / heads)
+    do {                                                                                                               \
+        if (few_long_segments(L))                                                                                      \
+            hipLaunchKernelGGL((combine_partials_kernel<DD_, TO_, 1024, 8>), dim3(L.num_split, copies, DD_ / 32), dim3(1024), 0, st, L.split_row, \
+                               L.split_ptr, partial, static_cast<TO_*>(out), (size_t)L.num_partials * DD_, out_copy, r1v, (DD_ / 4) / heads); \
+        else                                                                                                           \
+            hipLaunchKernelGGL((combine_partials_kernel<DD_, TO_, 256, DD_ / 4>), dim3(L.num_split, copies), dim3(256), 0, st, L.split_row, \
+                               L.split_ptr, partial, static_cast<TO_*>(out), (size_t)L.num_partials * DD_, out_copy, r1v, (DD_ / 4) / heads); \
+    } while (0)
     if (D == 256) {
         if (out_bf16) RGNN_LAUNCH_COMBINE(256, bf16_t);
         else RGNN_LAUNCH_COMBINE(256, float);
@@ -1160,16 +1181,7 @@ rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, c
 #undef RGNN_LAUNCH_NH
         RGNN_CHECK_LAUNCH();
     }
-    if (L.num_split > 0) {
-        KernelTimer kt(st, combine_label);
-        for (int h = 0; h < H; ++h) {
-            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_partials_kernel<DD, float>), dim3(L.num_split), dim3(1024), 0, st,
-                                                  L.split_row, L.split_ptr, partial + (size_t)h * L.num_partials * D,
-                                                  out + (size_t)h * out_rows * D, Rank1{nullptr, 0, nullptr, nullptr}, 1));
-            RGNN_CHECK_LAUNCH();
-        }
-    }
-    return RGNN_OK;
+    return combine_partials(L, D, partial, out, 0, combine_label, st, nullptr, 1, H, (size_t)out_rows * D);
 }
 
 rgnn_status_t aggregate_edge_parallel(const rgnn_graph* g, int D, const float* att, const float* Hs, float* out,

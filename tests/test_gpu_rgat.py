@@ -248,6 +248,23 @@ def test_edge_parallel_aggregation_flag(d):
     g.close()
 
 
+@pytest.mark.parametrize("n_hub", [33, 1025, 1700])
+@pytest.mark.parametrize("d,H", [(32, 1), (64, 1), (128, 1), (64, 4), (64, 2), (128, 8)])
+def test_one_segment_of_many_pieces(d, H, n_hub):
+    """One destination and one (source, relation) pair hold most edges and are cut into 2 to 54 pieces, so that the pieces'
+    sums are formed by small workgroups or, beyond 32 pieces per cut segment, by large ones on column ranges."""
+    rng = np.random.default_rng(900 + n_hub)
+    N, R, E = 60, 3, 2 * n_hub + 100
+    src, dst, rel = (rng.integers(0, n, E).astype(np.int32) for n in (N, N, R))
+    dst[:n_hub] = 7
+    src[n_hub:2 * n_hub] = 11; rel[n_hub:2 * n_hub] = 2
+    p = synth.rgat_params(rng, N, R, d, d)
+    if H == 1:
+        _run(N, R, src, dst, rel, p, d, f"pieces-d{d}-{n_hub}")
+    else:
+        _run_heads(N, R, src, dst, rel, p, d, H, f"pieces-d{d}-H{H}-{n_hub}")
+
+
 def test_hub_empty_relation_isolated_nodes():
     rng, src, dst, rel, _ = synth.tiny(70, N=300, R=5, E=4000)
     rel[rel == 4] = 0       # relation 4 has no edge
