@@ -11,6 +11,7 @@
 #include <stdio.h>
 #include <string.h>
 #include <algorithm>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <new>
@@ -87,13 +88,21 @@ struct Uploader {
     }
 };
 
-static void build_tiles(Uploader& U, TileList& t, const std::vector<int32_t>& seg_ptr, int tile_rows,
-                        int max_chunks = kMaxChunks) {
-    const TilePlan p = plan_tiles(seg_ptr, tile_rows, max_chunks);
-    t.tile_rows = p.tile_rows; t.num_tiles = p.num_tiles; t.num_chunks = p.num_chunks; t.num_slots = p.num_slots;
-    t.num_segs = p.num_segs;
-    t.tile_seg = U.up(p.tile_seg); t.tile_row0 = U.up(p.tile_row0); t.tile_row1 = U.up(p.tile_row1);
-    t.chunk_tile = U.up(p.chunk_tile); t.chunk_slot = U.up(p.chunk_slot); t.seg_slot_ptr = U.up(p.seg_slot_ptr);
+// Tile lists over one segmentation: the tiles are planned and uploaded once, every list gets its own chunks.
+struct Chunking { TileList* list; int max_chunks; };
+static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int tile_rows, std::initializer_list<Chunking> lists) {
+    TilePlan p = plan_tiles(seg_ptr, tile_rows);
+    int32_t* const seg = U.up(p.tile_seg);
+    int32_t* const row0 = U.up(p.tile_row0);
+    int32_t* const row1 = U.up(p.tile_row1);
+    for (const Chunking& c : lists) {
+        chunk_tiles(p, c.max_chunks);
+        TileList& t = *c.list;
+        t.tile_rows = p.tile_rows; t.num_tiles = p.num_tiles; t.num_chunks = p.num_chunks; t.num_slots = p.num_slots;
+        t.num_segs = p.num_segs;
+        t.tile_seg = seg; t.tile_row0 = row0; t.tile_row1 = row1;
+        t.chunk_tile = U.up(p.chunk_tile); t.chunk_slot = U.up(p.chunk_slot); t.seg_slot_ptr = U.up(p.seg_slot_ptr);
+    }
 }
 
 static void build_items(Uploader& U, ItemList& L, const std::vector<int32_t>& ptr, int max_len, int min_len = 0) {
@@ -141,19 +150,15 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
         g->num_single_pairs += (out_ptr[p + 1] - out_ptr[p] == 1);
     }
     Uploader U{g};
-    build_tiles(U, g->pair_tiles, pair_ptr, kTileRows);
-    build_tiles(U, g->node_tiles, ntype_ptr, kTileRows);
-    build_tiles(U, g->all_tiles, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows);
     int dev = 0, cus = 0;
     RGNN_HIP(hipGetDevice(&dev));
     RGNN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    g->num_cus = std::max(cus, 1);
-    const int wide = kWideChunksPerCU * std::max(cus, 1);
-    build_tiles(U, g->pair_tiles_wide, pair_ptr, kTileRows, wide);
-    build_tiles(U, g->node_tiles_wide, ntype_ptr, kTileRows, wide);
-    build_tiles(U, g->pair_tiles_cu2, pair_ptr, kTileRows, 2 * g->num_cus);
-    build_tiles(U, g->pair_tiles_cu1, pair_ptr, kTileRows, g->num_cus);
-    build_tiles(U, g->node_tiles_cu2, ntype_ptr, kTileRows, 2 * g->num_cus);
+    g->num_cus = cus = std::max(cus, 1);
+    build_tiles(U, pair_ptr, kTileRows, {{&g->pair_tiles, kMaxChunks}, {&g->pair_tiles_wide, kWideChunksPerCU * cus},
+                                         {&g->pair_tiles_cu2, 2 * cus}, {&g->pair_tiles_cu1, cus}});
+    build_tiles(U, ntype_ptr, kTileRows, {{&g->node_tiles, kMaxChunks}, {&g->node_tiles_wide, kWideChunksPerCU * cus},
+                                          {&g->node_tiles_cu2, 2 * cus}});
+    build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles, kMaxChunks}});
     build_items(U, g->dst_items, in_ptr, item_cut(g->E));
     build_items(U, g->pair_items, out_ptr, item_cut(g->E));
     build_items(U, g->relrun_items, relrun_ptr, item_cut(g->E));

@@ -35,16 +35,9 @@ struct TilePlan {
     std::vector<int32_t> seg_slot_ptr;                     // [num_segs + 1]
 };
 
-inline TilePlan plan_tiles(const std::vector<int32_t>& seg_ptr, int tile_rows, int max_chunks = kMaxChunks) {
-    TilePlan t;
-    const int S = (int)seg_ptr.size() - 1;
-    for (int s = 0; s < S; ++s)
-        for (int32_t a = seg_ptr[s]; a < seg_ptr[s + 1]; a += tile_rows) {
-            t.tile_seg.push_back(s);
-            t.tile_row0.push_back(a);
-            t.tile_row1.push_back(std::min<int32_t>(a + tile_rows, seg_ptr[s + 1]));
-        }
-    const int nt = (int)t.tile_seg.size();
+// (Re)groups the tiles of a plan into chunks: fills the chunk and slot fields.
+inline void chunk_tiles(TilePlan& t, int max_chunks) {
+    const int nt = t.num_tiles, S = t.num_segs;
     // a chunk pays for one weight-tile load and one weight-gradient flush, so it should span several
     // tiles; but small inputs still need a few hundred chunks to occupy the compute units
     const int nc = std::min(max_chunks, std::max(std::min(nt, kMinChunks), nt / kChunkTiles));
@@ -64,11 +57,23 @@ inline TilePlan plan_tiles(const std::vector<int32_t>& seg_ptr, int tile_rows, i
             }
     }
     for (int s = 0; s < S; ++s) t.seg_slot_ptr[s + 1] = t.seg_slot_ptr[s] + seg_slots[s];
-    t.tile_rows = tile_rows;
-    t.num_tiles = nt;
     t.num_chunks = nc;
     t.num_slots = slots;
+}
+
+inline TilePlan plan_tiles(const std::vector<int32_t>& seg_ptr, int tile_rows, int max_chunks = kMaxChunks) {
+    TilePlan t;
+    const int S = (int)seg_ptr.size() - 1;
+    for (int s = 0; s < S; ++s)
+        for (int32_t a = seg_ptr[s]; a < seg_ptr[s + 1]; a += tile_rows) {
+            t.tile_seg.push_back(s);
+            t.tile_row0.push_back(a);
+            t.tile_row1.push_back(std::min<int32_t>(a + tile_rows, seg_ptr[s + 1]));
+        }
+    t.tile_rows = tile_rows;
+    t.num_tiles = (int)t.tile_seg.size();
     t.num_segs = S;
+    chunk_tiles(t, max_chunks);
     return t;
 }
 
