@@ -182,6 +182,37 @@ __device__ __forceinline__ float dot_cols(const float (&a)[V], const float (&b)[
     return s;
 }
 
+// The entries of a tile list that a wavefront works through, 64 tiles at a time, lane l holding tile first + l: a tile's rows
+// and segment then cost three register reads instead of scalar loads, whose latency every tile would wait for.  The loads of
+// a refill are waited for on the spot, so that the code that reads the registers waits for nothing else under way.
+struct TileTable {
+    const int32_t* tile_seg;
+    const int32_t* tile_row0;
+    const int32_t* tile_row1;
+    int first, end;          // tile of lane 0; end of the chunk
+    int seg, row0, row1;
+    __device__ __forceinline__ TileTable(const int32_t* s, const int32_t* r0, const int32_t* r1, int t0, int t1)
+        : tile_seg(s), tile_row0(r0), tile_row1(r1), first(t0), end(t1) { fill(); }
+    __device__ __forceinline__ void fill() {
+        const int ti = min(first + (int)(threadIdx.x & 63), end - 1);
+        seg = tile_seg[ti];
+        row0 = tile_row0[ti];
+        row1 = tile_row1[ti];
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+    }
+    // Lane of tile ti (the same ti in all lanes).  Callers move forward through the chunk and look back at most 8 tiles.
+    __device__ __forceinline__ int lane_of(int ti) {
+        if (ti >= first + 64) {
+            first = ti - 8;
+            fill();
+        }
+        return ti - first;
+    }
+    __device__ __forceinline__ int seg_at(int l) const { return __builtin_amdgcn_readlane(seg, l); }
+    __device__ __forceinline__ int row0_at(int l) const { return __builtin_amdgcn_readlane(row0, l); }
+    __device__ __forceinline__ int row1_at(int l) const { return __builtin_amdgcn_readlane(row1, l); }
+};
+
 inline unsigned blocks_for(size_t n, unsigned per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 #define RGNN_CHECK_LAUNCH() RGNN_HIP(hipGetLastError())

@@ -5,8 +5,8 @@
 //
 // Bound by HBM: the two products together need a tenth of the matrix cores' rate at the speed the rows arrive.  As two
 // kernels the dY rows were read twice (and for two weights the X rows twice, the dXrow rows written twice and summed
-// later).  14.5M pairs (single-edge rows through the selector, 500 relations): 1.33 + 1.40 ms as two kernels, now 1.94 ms
-// (11.1 GB, 5.7 TB/s); 5.4M pairs with two weights: 2.12 ms as four kernels, now 1.08 ms (5.5 GB, 5.1 TB/s).
+// later).  14.5M pairs (single-edge rows through the selector, 500 relations): 1.33 + 1.40 ms as two kernels, now 1.83 ms
+// (11.1 GB, 6.1 TB/s); 5.4M pairs with two weights: 2.12 ms as four kernels, now 1.08 ms (5.5 GB, 5.1 TB/s).
 //
 // A workgroup of eight wavefronts takes a chunk of 64-row tiles.  A tile's X and dY rows are brought to registers one tile
 // ahead and written to LDS row-major.  dXrow^T = W dY^T takes W's rows and the dY rows as its operands straight from LDS
@@ -108,8 +108,9 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
     rgnn_v4u xr[2], yr[NB][2];
     int gi[2], gy[2], gcur[2];
     float sc[2] = {1.f, 1.f}, scc[2] = {1.f, 1.f};
+    TileTable tt(a.tile_seg, a.tile_row0, a.tile_row1, t0, t1);
     auto fetch_idx = [&](int ti) {
-        const int row0 = a.tile_row0[ti], row1 = a.tile_row1[ti];
+        const int l = tt.lane_of(ti), row0 = tt.row0_at(l), row1 = tt.row1_at(l);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int row = min(row0 + lr + 32 * k, row1 - 1);
@@ -130,26 +131,26 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
             scc[k] = sc[k];
         }
     };
-    if (t0 < t1) {
-        fetch_idx(t0);
-        fetch();
-        fetch_idx(min(t0 + 1, t1 - 1));
-    }
+    if (t0 >= t1) return;
+    fetch_idx(t0);
+    fetch();
+    fetch_idx(min(t0 + 1, t1 - 1));
     int cur_seg = -1, slot = a.chunk_slot[blockIdx.x] - 1;
     for (int ti = t0; ti <= t1; ++ti) {
-        const int seg = ti < t1 ? a.tile_seg[ti] : -2;
+        const int tl = tt.lane_of(min(ti, t1 - 1)), seg = ti < t1 ? tt.seg_at(tl) : -2;
         if (seg != cur_seg) {
             if (cur_seg >= 0) {
-                float* ps = a.part + (size_t)slot * SLOT;
+                // (the lane's place is made opaque so that the addresses are formed here and not kept across the loop)
+                int at = (16 * fb + 4 * kh) * D + 16 * cb + (m & 15) + 64 * (m >> 4);
+                asm volatile("" : "+v"(at));
+                float* ps = a.part + (size_t)slot * SLOT + at;
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                     for (int x = 0; x < 2; ++x)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const int i = 8 * (v >> 2) + 4 * kh + (v & 3);
-                            const int f = 16 * fb + (i & 15) + 64 * (i >> 4), c = 16 * (cb + x) + (m & 15) + 64 * (m >> 4);
-                            ps[nb * D * D + f * D + c] = acc[nb][x][v];
+                        for (int v = 0; v < 16; ++v) {     // block row 8 (v / 4) + 4 kh + v % 4: features 16 fb + (0..15), then 64 further
+                            ps[nb * D * D + ((v & 3) + 8 * ((v >> 2) & 1) + 64 * (v >> 3)) * D + 16 * x] = acc[nb][x][v];
                             acc[nb][x][v] = 0.f;
                         }
             }
@@ -180,7 +181,7 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
                 }
             }
         }
-        const int row0 = a.tile_row0[ti], rows = a.tile_row1[ti] - row0;
+        const int row0 = tt.row0_at(tl), rows = tt.row1_at(tl) - row0;
         int gout[2];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -197,10 +198,10 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
             if (DX32 && BOTH && lc == 0) gidx[lr + 32 * k] = gcur[k];
         }
         __syncthreads();   // the tile is complete
-        if (ti + 1 < t1) {
-            fetch();
-            fetch_idx(min(ti + 2, t1 - 1));
-        }
+        // (unconditional, past the end the last tile again: were the loads skipped on some path, the waits for the rows would
+        // have to drain the stores issued after them as well)
+        fetch();
+        fetch_idx(min(ti + 2, t1 - 1));
         v16f d;
 #pragma unroll
         for (int v = 0; v < 16; ++v) d[v] = 0.f;
