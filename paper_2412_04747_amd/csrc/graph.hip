@@ -157,8 +157,8 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     build_tiles(U, pair_ptr, kTileRows, {{&g->pair_tiles, kMaxChunks}, {&g->pair_tiles_wide, kWideChunksPerCU * cus},
                                          {&g->pair_tiles_cu2, 2 * cus}, {&g->pair_tiles_cu1, cus}});
     build_tiles(U, ntype_ptr, kTileRows, {{&g->node_tiles, kMaxChunks}, {&g->node_tiles_wide, kWideChunksPerCU * cus},
-                                          {&g->node_tiles_cu2, 2 * cus}});
-    build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles, kMaxChunks}});
+                                          {&g->node_tiles_cu2, 2 * cus}, {&g->node_tiles_cu1, cus}});
+    build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles, kMaxChunks}, {&g->all_tiles_cu1, cus}});
     build_items(U, g->dst_items, in_ptr, item_cut(g->E));
     build_items(U, g->pair_items, out_ptr, item_cut(g->E));
     build_items(U, g->relrun_items, relrun_ptr, item_cut(g->E));

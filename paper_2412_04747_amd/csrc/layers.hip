@@ -117,6 +117,24 @@ struct GradAcc {
     }
 };
 
+// The chunkings of one list of row tiles that the typed linears pick from:
+//   many, wide  bf16 rows, forward: weight in bf16 / an fp32 weight to be split
+//   f32         the fp32 kernels: one resident round, of three workgroups per compute unit up to width 64, of one at width 128
+//   cu2, cu1    bf16 rows, backward: one bf16 weight / two weights or a split one
+struct Chunkings { const rgnn::TileList* many; const rgnn::TileList* wide; const rgnn::TileList* f32; const rgnn::TileList* cu2; const rgnn::TileList* cu1; };
+inline Chunkings pair_chunks(const rgnn_graph_t* g, int width) {
+    return {&g->pair_tiles, &g->pair_tiles_wide, width == 128 ? &g->pair_tiles_cu1 : &g->pair_tiles_wide, &g->pair_tiles_cu2, &g->pair_tiles_cu1};
+}
+inline Chunkings node_chunks(const rgnn_graph_t* g, int width) {
+    return {&g->node_tiles, &g->node_tiles_wide, width == 128 ? &g->node_tiles_cu1 : &g->node_tiles_wide, &g->node_tiles_cu2, nullptr};
+}
+inline const rgnn::TileList* all_chunks(const rgnn_graph_t* g, int width) { return width == 128 ? &g->all_tiles_cu1 : &g->all_tiles; }
+// floats of scratch a backward typed linear needs on a list
+size_t tl_bwd_scratch(bool rows16, const Chunkings& t, int d_in, int d_out) {
+    if (!rows16) return typed_linear_bwd_scratch_floats(d_in, d_out, *t.f32);
+    return (size_t)d_in * d_out * std::max((size_t)t.cu2->num_slots, t.cu1 ? 2 * (size_t)t.cu1->num_slots : 0);
+}
+
 // ---- RGAT buffers -----------------------------------------------------------------------
 // Hs, the destination halves of the logits per (run, head) and (max, sum) of every (destination, head) softmax.
 struct RgatSaved { float* Hs; float* s_dst; float* ms; };
@@ -170,7 +188,7 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->dXp = c.take<float>((size_t)g->P * d->d_in);
     w->A = c.take<float>(H * g->R * d->d_in);
     w->U = c.take<float>(H * g->R * d->d_in);
-    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles_wide, (int)H));
+    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, *pair_chunks(g, d->d_out).f32, (int)H));
     const size_t parts = std::max<size_t>({(size_t)g->pair_items.num_partials, (size_t)g->relrun_items.num_partials,
                                            (size_t)g->relpair_items.num_partials});
     w->partial = c.take<float>(parts * std::max(d->d_in, d->d_out) * H);   // the run walk keeps one partial row per head
@@ -179,16 +197,6 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->acc_dws = acc ? c.take<float>((size_t)g->R * d->d_out) : nullptr;
     w->acc_dwt = acc ? c.take<float>((size_t)g->R * d->d_out) : nullptr;
     return c.off;
-}
-
-// the chunkings of one list of row tiles that a backward typed linear picks from, and the scratch it needs on them
-struct BwdTiles { const rgnn::TileList* f32; const rgnn::TileList* cu2; const rgnn::TileList* cu1; };
-inline BwdTiles pair_bwd_tiles(const rgnn_graph_t* g) { return {&g->pair_tiles_wide, &g->pair_tiles_cu2, &g->pair_tiles_cu1}; }
-inline BwdTiles node_bwd_tiles(const rgnn_graph_t* g) { return {&g->node_tiles_wide, &g->node_tiles_cu2, nullptr}; }
-size_t tl_bwd_scratch(bool rows16, const BwdTiles& t, int d_in, int d_out) {
-    if (!rows16) return typed_linear_bwd_scratch_floats(d_in, d_out, *t.f32);
-    // two weights, or a split one, use the one-chunk-per-compute-unit list
-    return (size_t)d_in * d_out * std::max((size_t)t.cu2->num_slots, t.cu1 ? 2 * (size_t)t.cu1->num_slots : 0);
 }
 
 // ---- RGCN buffers -----------------------------------------------------------------------
@@ -209,8 +217,8 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->G = c.rows((size_t)g->P * d->d_out, h);
     w->dXp = c.rows((size_t)g->P * d->d_in, h);
     w->dX0 = c.take<float>((size_t)g->N * d->d_in);
-    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_bwd_tiles(g), d->d_in, d->d_out),
-                                        typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles)));
+    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out),
+                                        typed_linear_bwd_scratch_floats(d->d_in, d->d_out, *all_chunks(g, d->d_out))));
     w->partial = c.take<float>((size_t)g->pair_items.num_partials * d->d_out);
     const bool acc = grads_accumulate(d);
     w->acc_dW = acc ? c.take<float>((size_t)g->R * d->d_in * d->d_out) : nullptr;
@@ -267,8 +275,8 @@ size_t carve_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     w->dKp = c.rows(pd, h); w->dVp = c.rows(h && fold ? 0 : pd, h);     // folded, bf16 rows: dKp holds the sum of both
     w->dK = c.rows(fold ? 0 : nd, h); w->dV = c.rows(fold ? 0 : nd, h);
     w->dXk = c.take<float>(h || fold ? 0 : nd); w->dXq = c.take<float>(h && !fold ? 0 : nd); w->dXv = c.take<float>(h || fold ? 0 : nd);
-    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_bwd_tiles(g), d->d_in, d->d_out),
-                                        tl_bwd_scratch(h, node_bwd_tiles(g), d->d_in, d->d_out)));
+    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out),
+                                        tl_bwd_scratch(h, node_chunks(g, d->d_out), d->d_in, d->d_out)));
     w->partial = c.take<float>(std::max(2 * (size_t)g->pair_items.num_partials, (size_t)g->dst_items.num_partials) * D);
     const bool acc = grads_accumulate(d);
     const size_t dh = D / d->heads;
@@ -306,25 +314,24 @@ void* saved_or_scratch(const rgnn_graph_t* g, int layer, const rgnn_layer_desc_t
 // Forward typed linear  Y[g(i)] / Y[i] = A[g(i)] W[seg].  In bf16 mode it runs on the bf16 matrix
 // cores: an operand whose bf16 form exists (A16 / W16) is used as is, an fp32-only one is split.
 // y16: the output rows are stored as bf16 (width 128 only).
-// Chunking: the bf16 kernel with the weight in bf16 does best on many short chunks (`tiles`); when
-// the weight has to be split, and in the fp32 kernels, loading a segment's weight costs more and one
-// resident round of long chunks (`wide`) wins.
+// Chunking: the bf16 kernel with the weight in bf16 does best on many short chunks; when the weight has to be
+// split, and in the fp32 kernels, loading a segment's weight costs more and one resident round of long chunks wins.
 // d_in (fp32 kernels only): width of the input rows when it differs from the output width d.
 // y_stride: the output rows are y_stride * d elements apart.
-rgnn_status_t tl_fwd(bool bf16, const rgnn::TileList* tiles, const rgnn::TileList* wide, int d, const float* A32,
+rgnn_status_t tl_fwd(bool bf16, const Chunkings& tiles, int d, const float* A32,
                      const void* A16, const int32_t* gather, int scatter, const float* W32, const void* W16, void* Y,
                      bool y16, const char* label, hipStream_t st, int d_in = 0, int y_stride = 1) {
     if (d_in == 0) d_in = d;
     if (bf16) {
         if (d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear on the bf16 matrix cores: equal widths only");
         TypedLinearBf16Args a{};
-        a.tiles = W16 ? tiles : wide; a.A = A16 ? A16 : A32; a.a_bf16 = A16 != nullptr; a.gather = gather; a.scatter_out = scatter;
+        a.tiles = W16 ? tiles.many : tiles.wide; a.A = A16 ? A16 : A32; a.a_bf16 = A16 != nullptr; a.gather = gather; a.scatter_out = scatter;
         a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.Y = Y; a.y_bf16 = y16; a.label = label;
         a.y_stride = y_stride;
         return typed_linear_bf16(d, a, st);
     }
     TypedLinearArgs a{};
-    a.tiles = wide; a.X = A32; a.gather = gather; a.W = W32; a.Y = static_cast<float*>(Y); a.scatter_out = scatter;
+    a.tiles = tiles.f32; a.X = A32; a.gather = gather; a.W = W32; a.Y = static_cast<float*>(Y); a.scatter_out = scatter;
     a.label = label; a.y_stride = y_stride;
     return typed_linear_fwd(d_in, d, a, st);
 }
@@ -338,7 +345,7 @@ rgnn_status_t tl_fwd(bool bf16, const rgnn::TileList* tiles, const rgnn::TileLis
 //   dy_stride: the rows of dY are dy_stride * d elements apart (dY not gathered)
 //   ysel / y_alt (rows16, dY not gathered): row i of dY is dY[ysel[i]], or y_alt[ysel[i] & 0x7FFFFFFF] when the
 //     top bit of ysel[i] is set; with yscale it is also multiplied by yscale[i]
-rgnn_status_t tl_bwd(bool rows16, const BwdTiles& tiles, int d, const void* X,
+rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
                      const int32_t* gather, int both_gathered, const float* W32, const void* W16, const void* dY,
                      void* dXrow, bool dx16, float* dW, float* part, const char* label, hipStream_t st,
                      bool dx_acc = false, const int32_t* ysel = nullptr, const void* y_alt = nullptr,
@@ -432,7 +439,7 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* W032 = stg.in(W0, (size_t)desc->d_in * D);
     RGNN_TRY(stg.status);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
-    RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
+    RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
                     desc->d_in));
     // 2. out[v] = sum_e (1/c) Hs[pair_e]
     const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
@@ -441,7 +448,7 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     // 3. self-loop: out += X W0
     if (W0) {
         TypedLinearArgs s{};
-        s.tiles = &g->all_tiles; s.X = X32; s.W = W032;
+        s.tiles = all_chunks(g, D); s.X = X32; s.W = W032;
         s.Y = static_cast<float*>(out); s.accumulate = 1; s.label = "self_loop_fwd";
         RGNN_TRY(typed_linear_fwd(desc->d_in, D, s, st));
     }
@@ -502,12 +509,12 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     RGNN_TRY(gather_sum(sel ? g->pair_items_multi : g->pair_items, D, nullptr, g->idx[RGNN_IDX_OUT_DST], 0, ocoef, 1, 0, dPre, w.G,
                         w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", 1, h, h));
     // 2. per pair dXp = dHs W^T; dW[r] = sum X^T dHs
-    RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
+    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
                     w.dXp, h, static_cast<float*>(dW), w.tl_part, "typed_linear_bwd", st, false, ysel, y_alt, yscale, K));
     // 3. self-loop: dX0 = dPre W0^T, dW0 = X^T dPre
     if (W0) {
         TypedLinearBwdArgs s{};
-        s.tiles = &g->all_tiles; s.X = X32; s.W = W032; s.dY = dPre32;
+        s.tiles = all_chunks(g, D); s.X = X32; s.W = W032; s.dY = dPre32;
         s.dXrow = w.dX0; s.dW = static_cast<float*>(dW0); s.part = w.tl_part; s.label = "self_loop_bwd";
         RGNN_TRY(typed_linear_bwd(K, D, s, st));
     }
@@ -598,7 +605,7 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[r]
     //    (the comparison schedules also take the source half of the logit per pair, s_src[p] = Hs[p] . w_s[r])
     TypedLinearArgs a{};
-    a.tiles = &g->pair_tiles_wide; a.X = Xf; a.gather = g->idx[RGNN_IDX_PAIR_SRC]; a.W = Wf; a.Y = sv.Hs;
+    a.tiles = pair_chunks(g, D).f32; a.X = Xf; a.gather = g->idx[RGNN_IDX_PAIR_SRC]; a.W = Wf; a.Y = sv.Hs;
     if (!fused) { a.vec = static_cast<const float*>(w_s); a.s_out = w.s_src; }
     RGNN_TRY(typed_linear_fwd(K, D, a, st));
     // 2. destination half, once per (dst, rel) run, reordered: s_dst[q] = X[dst] . (W[r] w_t[r])  (per head: the head's columns)
@@ -678,7 +685,7 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
                             sel ? w.ds_src : nullptr, 2 * H));
         // 4. dXp = dHs W^T, dW = sum X^T dHs; with the selector also A[r][h] = sum over r's pairs of ds_src[p][h] X[src_p]
         TypedLinearBwdArgs b{};
-        b.tiles = &g->pair_tiles_wide; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
+        b.tiles = pair_chunks(g, D).f32; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
         b.dW = static_cast<float*>(dW); b.part = w.tl_part;
         if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.hcoef = w.ds_src; b.wvec = ws; b.sel_heads = H; b.Avec = w.A; }
         RGNN_TRY(typed_linear_bwd(K, D, b, st));
@@ -719,7 +726,7 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     //    A[r] = sum ds_src X
     RGNN_TRY(fold_weight(g->R, K, D, Wf, static_cast<const float*>(w_s), w.wsp, st, static_cast<const float*>(w_t), w.wtp));   // wtp: step 7
     TypedLinearBwdArgs b{};
-    b.tiles = &g->pair_tiles_wide; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
+    b.tiles = pair_chunks(g, D).f32; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
     b.rowscale = sel ? nullptr : w.ds_src; b.vec = w.wsp; b.dW = static_cast<float*>(dW); b.Avec = w.A;
     b.part = w.tl_part;
     if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.ds_yscale = reinterpret_cast<const float2*>(w.ds_src); }
@@ -771,10 +778,10 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
     auto R16 = [h](const void* p) { return h ? p : nullptr; };
     auto R32 = [h](const void* p) { return h ? nullptr : static_cast<const float*>(p); };
     // 1. per node type: Q, and K, V unless they are folded into the per-pair linears
-    RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, X32, X16, perm, 1, Wq32, Wq16, sv.Q, h, "node_linear_q", st));
+    RGNN_TRY(tl_fwd(bf16, node_chunks(g, D), D, X32, X16, perm, 1, Wq32, Wq16, sv.Q, h, "node_linear_q", st));
     if (!fold) {
-        RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, X32, X16, perm, 1, Wk32, Wk16, sv.K, h, "node_linear_k", st));
-        RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, X32, X16, perm, 1, Wv32, Wv16, sv.V, h, "node_linear_v", st));
+        RGNN_TRY(tl_fwd(bf16, node_chunks(g, D), D, X32, X16, perm, 1, Wk32, Wk16, sv.K, h, "node_linear_k", st));
+        RGNN_TRY(tl_fwd(bf16, node_chunks(g, D), D, X32, X16, perm, 1, Wv32, Wv16, sv.V, h, "node_linear_v", st));
     }
     // 2. compact per pair, side by side in KM[p]: Ka[p] = K[src_p] Watt[r], M[p] = V[src_p] Wmsg[r]
     void* const Mrow = h ? static_cast<void*>(static_cast<uint16_t*>(sv.KM) + D) : static_cast<void*>(static_cast<float*>(sv.KM) + D);
@@ -784,18 +791,18 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
         //    matrix cores as they are; rows in the storage of the intermediates: the caller's bf16 X at width
         //    128, its fp32 copy otherwise.
         RGNN_TRY(hgt_fold(g->R, hw, w.Wf_att, w.Wf_msg, h, st));
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_att), R16(w.Wf_att), sv.KM, h, "pair_linear_att", st, 0, 2));
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, X32, R16(X), psrc, 0, R32(w.Wf_msg), R16(w.Wf_msg), Mrow, h, "pair_linear_msg", st, 0, 2));
+        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, R16(X), psrc, 0, R32(w.Wf_att), R16(w.Wf_att), sv.KM, h, "pair_linear_att", st, 0, 2));
+        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, R16(X), psrc, 0, R32(w.Wf_msg), R16(w.Wf_msg), Mrow, h, "pair_linear_msg", st, 0, 2));
     } else {
         //    with the per-(relation, head) matrices as block-diagonal d x d weights
         RGNN_TRY(hgt_expand(g->R, hw, w.Wbd_att, w.Wbd_msg, st));
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.K), R16(sv.K), psrc, 0, w.Wbd_att, nullptr, sv.KM, h, "pair_linear_att", st, 0, 2));
-        RGNN_TRY(tl_fwd(bf16, &g->pair_tiles, &g->pair_tiles_wide, D, R32(sv.V), R16(sv.V), psrc, 0, w.Wbd_msg, nullptr, Mrow, h, "pair_linear_msg", st, 0, 2));
+        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, R32(sv.K), R16(sv.K), psrc, 0, w.Wbd_att, nullptr, sv.KM, h, "pair_linear_att", st, 0, 2));
+        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, R32(sv.V), R16(sv.V), psrc, 0, w.Wbd_msg, nullptr, Mrow, h, "pair_linear_msg", st, 0, 2));
     }
     // 3. one walk per destination: logit per edge and head, softmax over the destination's edges, Z[v][h] = sum_e att[e][h] M[pair_e][h]
     RGNN_TRY(hgt_attend_fwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.partial, w.part_ms, st, h));
     // 4. out = Z Wo[type]
-    RGNN_TRY(tl_fwd(bf16, &g->node_tiles, &g->node_tiles_wide, D, R32(sv.Z), R16(sv.Z), perm, 1, Wo32, Wo16, out, false, "node_linear_out", st));
+    RGNN_TRY(tl_fwd(bf16, node_chunks(g, D), D, R32(sv.Z), R16(sv.Z), perm, 1, Wo32, Wo16, out, false, "node_linear_out", st));
     return RGNN_OK;
 }
 
@@ -841,7 +848,7 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     dWatt = ga.route(w.acc_rel[0], dWatt, rh * dh * dh); dWmsg = ga.route(w.acc_rel[1], dWmsg, rh * dh * dh);
     dmu = ga.route(w.acc_mu, dmu, rh);
     // 1. output linear: dZ = dOut Wo^T, dWo = Z^T dOut
-    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, sv.Z, perm, 1, Wo32, Wo16, dOr, w.dZ, h, static_cast<float*>(dWo), w.tl_part,
+    RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, sv.Z, perm, 1, Wo32, Wo16, dOr, w.dZ, h, static_cast<float*>(dWo), w.tl_part,
                     "node_linear_out_bwd", st));
     // 2. per destination: att (recomputed) and d logit per edge and head, dQ[v][h] = sum dl Ka[pair][h]
     RGNN_TRY(hgt_attend_bwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.dZ, w.dQ, w.adl, w.partial, st, h));
@@ -861,24 +868,24 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
             b.dy_stride = 2; b.dXrow = w.dKp; b.dW = w.dWf_att; b.dW2 = w.dWf_msg; b.part = w.tl_part; b.label = "pair_linear_bwd";
             RGNN_TRY(typed_linear_bwd_bf16(D, b, st));
         } else {
-            RGNN_TRY(tl_bwd(false, pair_bwd_tiles(g), D, Xr, psrc, 0, w.Wf_att, nullptr, dKa, w.dKp, false, w.dWf_att, w.tl_part,
+            RGNN_TRY(tl_bwd(false, pair_chunks(g, D), D, Xr, psrc, 0, w.Wf_att, nullptr, dKa, w.dKp, false, w.dWf_att, w.tl_part,
                             "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
-            RGNN_TRY(tl_bwd(false, pair_bwd_tiles(g), D, Xr, psrc, 0, w.Wf_msg, nullptr, dM, w.dVp, false, w.dWf_msg, w.tl_part,
+            RGNN_TRY(tl_bwd(false, pair_chunks(g, D), D, Xr, psrc, 0, w.Wf_msg, nullptr, dM, w.dVp, false, w.dWf_msg, w.tl_part,
                             "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
         }
         RGNN_TRY(hgt_fold_bwd(g->T, g->R, hw, w.dWf_att, w.dWf_msg, static_cast<float*>(dWk), static_cast<float*>(dWv),
                               static_cast<float*>(dWatt), static_cast<float*>(dWmsg), static_cast<float*>(dmu), st));
         // dX = dQ Wq^T + sums over each node's pairs of the two per-pair gradients
-        RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
+        RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
                         w.tl_part, "node_linear_q_bwd", st));
         if (acc) RGNN_TRY(add_into((size_t)g->N * D, static_cast<const float*>(dX), w.dXq, st));
         RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, w.dXq, dX, st, h, 0, 1, h ? nullptr : w.dVp));
         return ga.flush(st);
     }
     RGNN_TRY(hgt_expand(g->R, hw, w.Wbd_att, w.Wbd_msg, st));
-    RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.tl_part,
+    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.tl_part,
                     "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
-    RGNN_TRY(tl_bwd(h, pair_bwd_tiles(g), D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.tl_part,
+    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.tl_part,
                     "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
     RGNN_TRY(hgt_extract(g->R, hw, w.dWbd_att, w.dWbd_msg, static_cast<float*>(dWatt), static_cast<float*>(dWmsg),
                          static_cast<float*>(dmu), st));
@@ -887,11 +894,11 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     RGNN_TRY(node_grad_sum(g, D, w.dVp, nullptr, nullptr, nullptr, w.dV, st, h, h));
     // 6. node linears backward and dX
     //    (bf16 rows: the three input gradients are accumulated into dX by the kernels themselves)
-    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wk32, Wk16, w.dK, h ? dX : static_cast<void*>(w.dXk),
+    RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wk32, Wk16, w.dK, h ? dX : static_cast<void*>(w.dXk),
                     false, static_cast<float*>(dWk), w.tl_part, "node_linear_k_bwd", st, h && acc));
-    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wq32, Wq16, w.dQ, h ? dX : static_cast<void*>(w.dXq),
+    RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wq32, Wq16, w.dQ, h ? dX : static_cast<void*>(w.dXq),
                     false, static_cast<float*>(dWq), w.tl_part, "node_linear_q_bwd", st, h));
-    RGNN_TRY(tl_bwd(h, node_bwd_tiles(g), D, Xr, perm, 1, Wv32, Wv16, w.dV, h ? dX : static_cast<void*>(w.dXv),
+    RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wv32, Wv16, w.dV, h ? dX : static_cast<void*>(w.dXv),
                     false, static_cast<float*>(dWv), w.tl_part, "node_linear_v_bwd", st, h));
     if (!h) {
         if (acc) RGNN_TRY(add_into((size_t)g->N * D, static_cast<const float*>(dX), w.dXk, st));

@@ -115,6 +115,8 @@ struct rgnn_graph {
     rgnn::TileList pair_tiles_cu2;         // the same in one chunk per workgroup of a kernel that keeps two (one)
     rgnn::TileList pair_tiles_cu1;         // workgroups per compute unit
     rgnn::TileList node_tiles_cu2;
+    rgnn::TileList node_tiles_cu1;
+    rgnn::TileList all_tiles_cu1;
     rgnn::ItemList dst_items;              // CSR edges by destination
     rgnn::ItemList pair_items;             // transposed edges by pair
     rgnn::ItemList pair_items_multi;       // the same, pairs with two or more edges only
@@ -135,9 +137,6 @@ struct rgnn_graph {
 namespace rgnn {
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
-
-// "<label>.wgrad", with static storage (kernel-timer names must outlive the call)
-const char* wgrad_label(const char* label);
 
 // Raises a kernel's dynamic LDS limit once per (kernel, device) instead of on every launch.
 rgnn_status_t allow_dynamic_lds(const void* kernel, size_t bytes);
@@ -237,5 +236,8 @@ rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part,
 
 size_t typed_linear_bwd_scratch_floats(int d_in, int d_out, const TileList& t, int vectors = 1);   // vectors: of a slot's vector part
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st);
+// width 128 (typed_linear_split.hip): fp32 operands split into three bf16 planes; the backward fills the slots only
+rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st);
+rgnn_status_t typed_linear_split_bwd(const TypedLinearBwdArgs& a, hipStream_t st);
 
 }  // namespace rgnn

@@ -1,4 +1,4 @@
-// Relation-segmented typed linear layer on the CDNA4 matrix cores, fp32.
+// Relation-segmented typed linear layer on the fp32 matrix cores, widths 32 and 64 (width 128: typed_linear_split.hip).
 //
 // Forward   Y[i] = X[gather[i]] W[seg(i)]          (thesis Ch.3: segment MM, Y[S] = X[G] x W[T];
 //                                                   rows are presorted by type so one weight serves a segment)
@@ -72,16 +72,13 @@ __device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int
 //   ACCUM    forward: Y += result                         VEC      forward: s_out = Y_row . vec[seg], per head:
 //                                                                  s_out[row][h] over the h-th of s_heads column slices
 //   DYG      backward: dY rows are read through the list  RS       backward: rowscale / Avec / xvec in use
-//   WT       multiply by W[seg]^T (W stored [ND][KD]): the input-gradient product dY W^T
-//   ADDV     Y_row += rowscale[row] * vec[seg]  (the rank-1 part of single-head RGAT's input gradient)
-//   IS, OS   the rows of X / Y are IS * KD / OS * ND floats apart (2: the key or message half of HGT's pair rows)
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool WT = false, bool ADDV = false, int IS = 1, int OS = 1>
+//   OS       the rows of Y are OS * ND floats apart (2: the key or message half of HGT's pair rows)
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1>
 __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X,
                                                                     const int32_t* __restrict__ gather,
                                                                     const float* __restrict__ W, float* __restrict__ Y,
                                                                     const float* __restrict__ vec,
-                                                                    float* __restrict__ s_out,
-                                                                    const float* __restrict__ rowscale, int s_heads) {
+                                                                    float* __restrict__ s_out, int s_heads) {
     constexpr int NW = 4;                                   // wavefronts per workgroup
     constexpr int XS = (KD > ND ? KD : ND) + 4;             // row stride of the per-wave stage
     constexpr int CB = ND / 32;
@@ -101,25 +98,11 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
         const int ra = t.tile_row0[ta], rbnd = t.tile_row1[tb - 1];   // rows [ra, rbnd) of this segment
         const int nu = (rbnd - ra + 31) / 32;
         __syncthreads();                                    // every wavefront is done with the previous weight
-        if (!WT) {
-            const float4* Wg = reinterpret_cast<const float4*>(W + (size_t)seg * KD * ND);
-            for (int i = tid; i < KD * ND / 4; i += 64 * NW) reinterpret_cast<float4*>(Ws)[i] = Wg[i];
-        } else {
-            // Ws[k][n] = W[n][k]: neighbouring lanes take neighbouring n, so the LDS writes of a
-            // wavefront fall on different banks (the strided global reads hit the cache)
-            const float* Wg = W + (size_t)seg * KD * ND;
-            for (int i = tid; i < ND * (KD / 4); i += 64 * NW) {
-                const int n = i % ND, k4 = i / ND;
-                const float4 w4 = *reinterpret_cast<const float4*>(Wg + (size_t)n * KD + k4 * 4);
-                Ws[(k4 * 4 + 0) * ND + n] = w4.x;
-                Ws[(k4 * 4 + 1) * ND + n] = w4.y;
-                Ws[(k4 * 4 + 2) * ND + n] = w4.z;
-                Ws[(k4 * 4 + 3) * ND + n] = w4.w;
-            }
-        }
+        const float4* Wg = reinterpret_cast<const float4*>(W + (size_t)seg * KD * ND);
+        for (int i = tid; i < KD * ND / 4; i += 64 * NW) reinterpret_cast<float4*>(Ws)[i] = Wg[i];
         __syncthreads();
         float4 wv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (VEC || ADDV) wv = *reinterpret_cast<const float4*>(vec + (size_t)seg * ND + co * 4);
+        if (VEC) wv = *reinterpret_cast<const float4*>(vec + (size_t)seg * ND + co * 4);
         // lanes per head of an output row (a power of two, like the head count), and its log2
         const int lls = (31 - __clz(LPRO)) - (VEC ? 31 - __clz(s_heads) : 0), lph = 1 << lls;
         // Rows past the end of the run are clamped to its last row, so every load below is
@@ -133,7 +116,7 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
     }
 #define RGNN_FETCH_ROWS()                                                           \
     _Pragma("unroll") for (int it = 0; it < NX; ++it) {                             \
-        xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gi[it] * (IS * KD) + ci * 4); \
+        xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gi[it] * KD + ci * 4); \
         gcur[it] = gi[it];                                                          \
     }
         RGNN_FETCH_IDX(wave)
@@ -180,10 +163,6 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
                 if (ACCUM) {
                     const float4 o = *yp;
                     y.x += o.x; y.y += o.y; y.z += o.z; y.w += o.w;
-                }
-                if (ADDV) {
-                    const float sc = rowscale[min(row, rbnd - 1)];
-                    y.x += sc * wv.x; y.y += sc * wv.y; y.z += sc * wv.z; y.w += sc * wv.w;
                 }
                 if (ok) {   // rows of a large tensor that is read again only after it has left the caches: non-temporal
                     const v4f yv = {y.x, y.y, y.z, y.w};
@@ -606,138 +585,18 @@ rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part,
 }
 
 // ---------------------------------------------------------------------------------------
-// Weight gradient alone, fp32, for width 128, where the fused backward kernel above no longer fits
-// (a wavefront cannot hold a 128 x 128 gradient):  part[slot] = sum over the chunk's rows of
-// X[g(i)]^T dY[i].  Four wavefronts; each owns a 32-feature band of X and all four 32-column blocks
-// of dY (64 accumulator registers), kept across the tiles of a segment.  The 64-row tile of X and of
-// dY sits row-major in LDS: the MFMA contracts over rows two at a time, so a lane's A operand is
-// X[row 2s + kh][band + m] and its B operand dY[row 2s + kh][block + m], both conflict-free 4-byte
-// reads.  The next tile's rows are in flight in registers while the current one is multiplied.
-// RS: the slot's vector part gets sum over the rows of rowscale[i] * X[g(i)] (otherwise zeros).
-// DS: the rows of dY are DS * D floats apart.
-template <int D, bool GATHER, bool DYG, bool RS, int DS = 1>
-__global__ __launch_bounds__(256) void typed_linear_wgrad_f32_kernel(TileArgs t, const float* __restrict__ X,
-                                                                     const int32_t* __restrict__ gather,
-                                                                     const float* __restrict__ dY,
-                                                                     const float* __restrict__ rowscale,
-                                                                     float* __restrict__ part) {
-    static_assert(D == 128, "four wavefronts x four 32-column blocks");
-    constexpr int XS = D + 4;                              // LDS row stride
-    constexpr int LPR = D / 4, RPP = 256 / LPR, NL = 64 / RPP;   // lanes per row, rows per pass, passes per tile
-    constexpr int SLOT = D * D + D;
-    extern __shared__ __align__(16) float smem[];
-    float* Xt = smem;                                      // [64][XS]
-    float* Yt = smem + 64 * XS;                            // [64][XS]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = lane & 31, kh = lane >> 5;
-    const int cx = tid % LPR, rx = tid / LPR;
-    v16f acc[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
-    const int t0 = t.chunk_tile[blockIdx.x], t1 = t.chunk_tile[blockIdx.x + 1];
-    v4f xr[NL], yr[NL];
-    int gi[NL];
-    float rs[NL];
-    v4f avec = {0.f, 0.f, 0.f, 0.f};                      // this thread's share of the vector part (columns 4 cx ..)
-#define RGNN_WF_FETCH_IDX(TI)                                                       \
-    {                                                                               \
-        const int row0_ = t.tile_row0[TI], row1_ = t.tile_row1[TI];                 \
-        _Pragma("unroll") for (int it = 0; it < NL; ++it) {                         \
-            const int row_ = min(row0_ + rx + it * RPP, row1_ - 1);                 \
-            gi[it] = GATHER ? gather[row_] : row_;                                  \
-        }                                                                           \
-    }
-#define RGNN_WF_FETCH(TI)                                                           \
-    {                                                                               \
-        const int row0_ = t.tile_row0[TI], row1_ = t.tile_row1[TI];                 \
-        _Pragma("unroll") for (int it = 0; it < NL; ++it) {                         \
-            xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gi[it] * D + cx * 4); \
-            const int row_ = min(row0_ + rx + it * RPP, row1_ - 1);                 \
-            const size_t s_ = (DYG && GATHER) ? (size_t)gi[it] : (size_t)row_;      \
-            yr[it] = *reinterpret_cast<const v4f*>(dY + s_ * (DS * D) + cx * 4);           \
-            if (RS) rs[it] = rowscale[row_];                                        \
-        }                                                                           \
-    }
-    if (t0 < t1) {
-        RGNN_WF_FETCH_IDX(t0)
-        RGNN_WF_FETCH(t0)
-    }
-    if (t0 + 1 < t1) RGNN_WF_FETCH_IDX(t0 + 1)
-    int cur_seg = -1;
-    int slot = t.chunk_slot[blockIdx.x] - 1;
-    for (int ti = t0; ti <= t1; ++ti) {
-        const int seg = (ti < t1) ? t.tile_seg[ti] : -2;
-        if (seg != cur_seg) {
-            if (cur_seg >= 0) {   // flush: band `wave` of the gradient, four column blocks
-                float* ps = part + (size_t)slot * SLOT;
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        ps[(wave * 32 + acc_row(v, kh)) * D + b * 32 + m] = acc[b][v];
-                        acc[b][v] = 0.f;
-                    }
-                if (RS) {   // the eight threads sharing a column group add their shares in order, through LDS
-                    __syncthreads();
-                    *reinterpret_cast<v4f*>(Xt + rx * XS + cx * 4) = avec;
-                    avec = v4f{0.f, 0.f, 0.f, 0.f};
-                    __syncthreads();
-                    if (tid < D) {
-                        float sum = 0.f;
-#pragma unroll
-                        for (int r = 0; r < RPP; ++r) sum += Xt[r * XS + tid];
-                        ps[D * D + tid] = sum;
-                    }
-                    __syncthreads();
-                } else if (tid < D) {
-                    ps[D * D + tid] = 0.f;
-                }
-            }
-            if (ti == t1) break;
-            ++slot;
-            cur_seg = seg;
-        }
-        const int rows = t.tile_row1[ti] - t.tile_row0[ti];
-#pragma unroll
-        for (int it = 0; it < NL; ++it) {
-            const int r = rx + it * RPP;
-            const bool ok = r < rows;                      // rows past the end of the tile count as zeros
-            const v4f z = {0.f, 0.f, 0.f, 0.f};
-            *reinterpret_cast<v4f*>(Xt + r * XS + cx * 4) = ok ? xr[it] : z;
-            *reinterpret_cast<v4f*>(Yt + r * XS + cx * 4) = ok ? yr[it] : z;
-            if (RS && ok) avec += rs[it] * xr[it];
-        }
-        __syncthreads();
-        if (ti + 1 < t1) RGNN_WF_FETCH(ti + 1)
-        if (ti + 2 < t1) RGNN_WF_FETCH_IDX(ti + 2)
-#pragma unroll 4
-        for (int s = 0; s < 32; ++s) {
-            const int r = 2 * s + kh;
-            const float a = Xt[r * XS + wave * 32 + m];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) acc[b] = mfma32(a, Yt[r * XS + b * 32 + m], acc[b]);
-        }
-        __syncthreads();   // operand reads are done before the next tile is written
-    }
-#undef RGNN_WF_FETCH_IDX
-#undef RGNN_WF_FETCH
-}
-
-// ---------------------------------------------------------------------------------------
 static TileArgs tile_args(const TileList& t) {
     return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot};
 }
 
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool WT = false, bool ADDV = false, int IS = 1, int OS = 1>
-static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st, const float* rowscale = nullptr) {
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1>
+static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st) {
     const size_t lds = sizeof(float) * (KD * ND + 4 * 32 * ((KD > ND ? KD : ND) + 4));
-    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, WT, ADDV, IS, OS>;
+    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, OS>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
-                       a.vec, a.s_out, rowscale, a.s_heads);
+                       a.vec, a.s_out, a.s_heads);
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -750,7 +609,7 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, ND);
     if (a.y_stride == 2) {
         if constexpr (KD == ND) {
-            if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false, false, false, 1, 2>(a, st);
+            if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false, 2>(a, st);
         }
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built for gathered rows of equal widths only");
     }
@@ -768,7 +627,7 @@ rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hi
     if (a.tiles->num_tiles == 0) return RGNN_OK;
     if (d_in == 64 && d_out == 64) return launch_fwd<64, 64>(a, st);
     if (d_in == 32 && d_out == 32) return launch_fwd<32, 32>(a, st);
-    if (d_in == 128 && d_out == 128) return launch_fwd<128, 128>(a, st);
+    if (d_in == 128 && d_out == 128) return typed_linear_split_fwd(a, st);
     if (d_in == 32 && d_out == 64) return launch_fwd<32, 64>(a, st);
     if (d_in == 64 && d_out == 32) return launch_fwd<64, 32>(a, st);
     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: d_in = %d, d_out = %d not supported (need 32 / 64 / 128, different widths only among 32 and 64)", d_in, d_out);
@@ -792,49 +651,12 @@ static rgnn_status_t launch_bwd_wave(const TypedLinearBwdArgs& a, hipStream_t st
     return RGNN_OK;
 }
 
-// Width 128: dXrow = dY W^T (+ rowscale (x) vec) with the forward wave kernel on the transposed weight,
-// then the weight-gradient kernel; two passes over dY, but both near the matrix cores' rate.
-template <int D>
-static rgnn_status_t launch_bwd_split(const TypedLinearBwdArgs& a, hipStream_t st) {
-    const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
-    TypedLinearArgs f{};
-    f.tiles = a.tiles; f.X = a.dY; f.gather = dg ? a.gather : nullptr; f.W = a.W; f.Y = a.dXrow;
-    f.scatter_out = sc; f.vec = a.vec; f.label = a.label ? a.label : "typed_linear_bwd";
-    if (dg != sc) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY gathered and dXrow scattered must go together");
-    if (rs && (dg || !a.vec)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: rowscale needs vec and ungathered dY");
-    const bool two = a.dy_stride == 2;
-    if (two && (rs || dg || !g)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY rows two widths apart are built for gathered X, ungathered dY and no rowscale only");
-    if (two) RGNN_TRY((launch_fwd_wave<D, D, false, false, false, false, true, false, 2, 1>(f, st)));
-    else if (rs) RGNN_TRY((launch_fwd_wave<D, D, false, false, false, false, true, true>(f, st, a.rowscale)));
-    else if (dg) RGNN_TRY((launch_fwd_wave<D, D, true, true, false, false, true>(f, st)));
-    else RGNN_TRY((launch_fwd_wave<D, D, false, false, false, false, true>(f, st)));
-    const size_t lds = sizeof(float) * 2 * 64 * (D + 4);
-    KernelTimer kt(st, wgrad_label(f.label));
-#define RGNN_LAUNCH_WGRAD(G_, DG_, RS_, DS_)                                                                              \
-    {                                                                                                                \
-        auto kern = typed_linear_wgrad_f32_kernel<D, G_, DG_, RS_, DS_>;                                               \
-        RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));                                       \
-        hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, tile_args(*a.tiles), a.X, a.gather, \
-                           a.dY, a.rowscale, a.part);                                                                \
-    }
-    if (two) RGNN_LAUNCH_WGRAD(true, false, false, 2)
-    else if (g && dg) RGNN_LAUNCH_WGRAD(true, true, false, 1)
-    else if (g && rs) RGNN_LAUNCH_WGRAD(true, false, true, 1)
-    else if (g) RGNN_LAUNCH_WGRAD(true, false, false, 1)
-    else if (!rs) RGNN_LAUNCH_WGRAD(false, false, false, 1)
-    else RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: rowscale needs gathered X");
-#undef RGNN_LAUNCH_WGRAD
-    RGNN_HIP(hipGetLastError());
-    return RGNN_OK;
-}
-
 template <int KD, int ND>
 static rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
     if (a.tiles->num_tiles > 0) {
         bool done = false;
         if constexpr (KD == 128 && ND == 128) {
-            if (a.ysel) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: no row selector at width 128");
-            RGNN_TRY(launch_bwd_split<128>(a, st));
+            RGNN_TRY(typed_linear_split_bwd(a, st));
             done = true;
         }
         if constexpr (KD <= 64 && ND <= 64) {

@@ -1,0 +1,619 @@
+// fp32 typed linear layer of width 128 on the bf16 matrix cores, without loss of fp32 accuracy.
+//
+// Every fp32 operand is split exactly into three bf16 planes, x = hi + mid + lo (round to nearest even: |mid| <= 2^-9 |x|,
+// |lo| <= 2^-18 |x|), and a product is the six plane products down to 2^-18: hi hi + (hi mid + mid hi) + (hi lo + mid mid +
+// lo hi); what is left out is below 2^-26 of |x y|, a quarter of a rounding of the fp32 product.  Products are exact and sums
+// are fp32, one rounding per 16 terms and plane product against one per 2 terms of v_mfma_f32_32x32x2_f32, so the result is
+// as close to 64 bits as that of the fp32 matrix instructions, at 16 / 6 of their rate.  Beyond the range of bf16 (an
+// operand above 3.38e38, or infinite) the split does not hold: a tile that contains such a value is multiplied with the fp32
+// matrix instructions, straight from global memory.
+//
+// Why: at width 128 a row costs 32 kflop per product against 1.5 KB of traffic, twice what the fp32 matrix cores do in the time
+// the rows need.  1.43M pairs of 60 relations: forward 0.52 -> 0.31 ms (4.7 TB/s), backward (two kernels before, dY read
+// twice) 1.18 -> 0.60 ms (3.7 TB/s; the loading wavefronts' chain of waits, splits and LDS writes per unit).
+//
+// A workgroup takes a chunk of 64-row tiles in units of 32 rows, one workgroup per compute unit, its wavefronts specialised:
+//   4 load:     rows of unit u + 1 from registers (fetched two units ahead) split into planes in LDS, result rows of unit
+//               u - 1 from LDS to memory
+//   4 multiply: dXrow = dY W^T (forward: Y = X W); a wavefront keeps 32 rows (columns) of W as planes in 96 registers
+//   4 multiply (backward only): the weight gradient X^T dY, whose row contraction reads the planes through the transposing
+//               LDS read ds_read_b64_tr_b16
+// Planes and result tiles are double-buffered and one barrier per unit separates the stages, so that splitting, matrix
+// products and stores of neighbouring units overlap (with all wavefronts going through the phases together the backward took
+// 0.70 ms at the sizes above, 15,400 clocks per 64 rows of which the matrix instructions are 6,100).
+// A plane is [32 rows][256 bytes], piece c (16 bytes) of row r at c ^ swz(r), as in the bf16 backward.
+#include "rgnn_internal.h"
+#include "device_utils.h"
+
+namespace rgnn {
+
+namespace {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) v4s* lds_v4s;
+
+constexpr int D = 128;
+constexpr int UNIT = 32;                     // rows of a unit
+constexpr int PLANE = UNIT * 2 * D;          // bytes of one plane of a unit
+constexpr int STAGE = UNIT * 4 * D;          // bytes of a result tile
+constexpr float kSplitMax = 3.38e38f;        // largest magnitude whose bf16 rounding is finite
+
+struct TileArgs {
+    const int32_t* tile_seg;
+    const int32_t* tile_row0;
+    const int32_t* tile_row1;
+    const int32_t* chunk_tile;
+    const int32_t* chunk_slot;
+};
+
+__device__ __forceinline__ int swz(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
+__device__ __forceinline__ float lo_half(unsigned u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float hi_half(unsigned u) { return __uint_as_float(u & 0xFFFF0000u); }
+// planes of the pair (a, b), packed
+__device__ __forceinline__ void split2(float a, float b, unsigned (&p)[3]) {
+    p[0] = bf16_pack2(a, b);
+    const float a1 = a - lo_half(p[0]), b1 = b - hi_half(p[0]);
+    p[1] = bf16_pack2(a1, b1);
+    p[2] = bf16_pack2(a1 - lo_half(p[1]), b1 - hi_half(p[1]));
+}
+__device__ __forceinline__ bf16x8 tr8(const unsigned char* p, const unsigned char* q) {
+    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)p), b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)q);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ v16f mfma16(bf16x8 a, bf16x8 b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ v16f mfma32(float a, float b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+// Rows of unit u of the tile list: [row0, row0 + rows), rows <= 0 for the second half of a short tile.
+struct Unit { int row0, rows, seg; };
+struct Units {
+    TileTable t;
+    __device__ __forceinline__ Units(const TileArgs& a, int t0, int t1) : t(a.tile_seg, a.tile_row0, a.tile_row1, t0, t1) {}
+    __device__ __forceinline__ Unit get(int u) {
+        const int l = t.lane_of(u >> 1), r = t.row0_at(l) + (u & 1) * UNIT;
+        return Unit{r, min(t.row1_at(l) - r, UNIT), t.seg_at(l)};
+    }
+};
+
+// Two products of three-plane operands, the six plane products of each in turn, so that no matrix instruction waits for the
+// one before it.
+__device__ __forceinline__ void mfma_split2(const bf16x8 (&a)[3], const bf16x8 (&b)[3], v16f& c, const bf16x8 (&a1)[3], const bf16x8 (&b1)[3], v16f& c1) {
+    constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};      // the small products first
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        c = mfma16(a[pa[i]], b[pb[i]], c);
+        c1 = mfma16(a1[pa[i]], b1[pb[i]], c1);
+    }
+}
+
+// The loading threads' view of a unit: 256 threads, 32 lanes per row (16 bytes each), rows lr + 8 k.
+struct Loader {
+    int c4, lr;
+    __device__ __forceinline__ explicit Loader(int tid) : c4(tid & 31), lr(tid >> 5) {}
+    // row lr + 8 k into the planes at `t` (zeros when !ok); returns the largest magnitude
+    __device__ __forceinline__ float put(unsigned char* t, int k, float4 x, bool ok) const {
+        if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
+        const int r = lr + 8 * k, at = r * 256 + (((c4 >> 1) ^ swz(r)) << 4) + (c4 & 1) * 8;
+        unsigned p[3], q[3];
+        split2(x.x, x.y, p);
+        split2(x.z, x.w, q);
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2*>(t + pl * PLANE + at) = make_uint2(p[pl], q[pl]);
+        return fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w)));
+    }
+};
+
+// Rows of a result tile: [32][512 bytes], 16-byte piece p of row r at p ^ (r & 15).
+__device__ __forceinline__ float4* stage_at(unsigned char* st, int row, int piece) {
+    return reinterpret_cast<float4*>(st + row * 512 + ((piece ^ (row & 15)) << 4));
+}
+
+// One 32 x 32 block (rows of the unit x this wavefront's 32 columns `band`) of rows times W, to the result tile:
+// planes of the rows at `t`, of W in w; slow: from memory, with wp[k * wk] = W's operand and xp[k] = the row of lane m.
+__device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16x8 (&w)[3][8], unsigned char* st, int band, int m, int kh,
+                                              bool slow, const float* wp, size_t wk, const float* xp) {
+    v16f d, d1;                                            // two chains of matrix instructions
+#pragma unroll
+    for (int v = 0; v < 16; ++v) d[v] = d1[v] = 0.f;
+    if (!slow) {
+        const unsigned char* row = t + m * 256;
+        const int sw = (kh ^ swz(m)) << 4;
+#pragma unroll
+        for (int s = 0; s < 8; s += 2) {
+            bf16x8 x[2][3], ws[2][3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    x[j][q] = *reinterpret_cast<const bf16x8*>(row + q * PLANE + (sw ^ ((s + j) << 5)));
+                    ws[j][q] = w[q][s + j];
+                }
+            mfma_split2(ws[0], x[0], d, ws[1], x[1], d1);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) d[v] += d1[v];
+    } else {
+        for (int k = 0; k < D; k += 2) d = mfma32(wp[(size_t)k * wk], xp[k], d);
+    }
+    // d[v] = result[row m][column band * 32 + 8 (v / 4) + 4 kh + v % 4]
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        *stage_at(st, m, band * 8 + 2 * q + kh) = make_float4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+}
+
+// planes of eight values
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8& a, bf16x8& b, bf16x8& c, float& mx) {
+    rgnn_v4u pl[3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        unsigned p[3];
+        split2(x[2 * e], x[2 * e + 1], p);
+        mx = fmaxf(mx, fmaxf(fabsf(x[2 * e]), fabsf(x[2 * e + 1])));
+#pragma unroll
+        for (int q = 0; q < 3; ++q) pl[q][e] = p[q];
+    }
+    a = __builtin_bit_cast(bf16x8, pl[0]);
+    b = __builtin_bit_cast(bf16x8, pl[1]);
+    c = __builtin_bit_cast(bf16x8, pl[2]);
+}
+
+// Out-of-range flags, one per unit in a ring of four: the loaders set unit u + 1's flag while unit u is multiplied and
+// clear unit u + 2's, which nobody reads or sets then.
+__device__ __forceinline__ void clear_flag(int* bad, int u, int tid) { if (tid == 0) bad[(u + 2) & 3] = 0; }
+
+// ------------------------------------------------------------------------------------------------ forward
+
+struct FwdArgs {
+    TileArgs t;
+    const float* X;
+    const int32_t* gather;
+    const float* W;          // [segs][D][D]
+    float* Y;
+    int ldy;                 // floats from one row of Y to the next
+    const float* vec;        // VEC: s_out[row][h] = Y_row . vec[seg] over head h's columns
+    float* s_out;
+    int s_heads;
+};
+
+template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+__device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
+    constexpr int DEPTH = 3;                               // units in flight per thread: 48 KB per compute unit
+    const int tid = threadIdx.x & 255;
+    const Loader ld(tid);
+    Units units(a.t, u0 >> 1, u1 >> 1);
+    unsigned char* const St = lds + 2 * 3 * PLANE;
+    // Rows are asked for DEPTH units before they are used, and their indices DEPTH units before that: loads complete in issue
+    // order, so an index that is needed while newer rows are under way must be older than all rows that are not needed yet.
+    float4 xr[DEPTH][4];
+    int gi[2 * DEPTH][4];
+    auto fetch_idx = [&](int p, int u) {
+        const Unit n = units.get(min(u, u1 - 1));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1);      // (an empty second half: the tile's last row)
+            gi[p][k] = GATHER ? a.gather[row] : row;
+        }
+    };
+    auto fetch = [&](int p, int q) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xr[p][k] = *reinterpret_cast<const float4*>(a.X + (size_t)gi[q][k] * D + ld.c4 * 4);
+    };
+#pragma unroll
+    for (int p = 0; p < 2 * DEPTH; ++p) fetch_idx(p, u0 + p);
+#pragma unroll
+    for (int p = 0; p < DEPTH; ++p) fetch(p, p);
+    int gout[2][4];                                        // destination rows of the units u and u - 1
+#pragma unroll
+    for (int k = 0; k < 4; ++k) gout[0][k] = gout[1][k] = 0;
+    for (int ub = u0 - 1; ub <= u1; ub += 2 * DEPTH) {
+#pragma unroll
+        for (int p = 0; p < 2 * DEPTH; ++p) {
+            const int u = ub + p;
+            if (u > u1) break;
+            __syncthreads();
+            clear_flag(bad, u, tid);
+            if (u - 1 >= u0) {                             // result rows of the unit before
+                const Unit n = units.get(u - 1);
+                float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (VEC) v4 = *reinterpret_cast<const float4*>(a.vec + (size_t)n.seg * D + ld.c4 * 4);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int r = ld.lr + 8 * k;
+                    const bool ok = r < n.rows;
+                    float4 y = *stage_at(St + ((u - 1) & 1) * STAGE, r, ld.c4);
+                    if (ok) {
+                        float* o = a.Y + (SCATTER ? (size_t)gout[1][k] : (size_t)(n.row0 + r)) * a.ldy + ld.c4 * 4;
+                        if (ACCUM) {
+                            const float4 old = *reinterpret_cast<const float4*>(o);
+                            y.x += old.x; y.y += old.y; y.z += old.z; y.w += old.w;
+                        }
+                        const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
+                        __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
+                    }
+                    if (VEC) {
+                        float s = dot4(y, v4);
+                        const int lph = 32 / a.s_heads;
+                        for (int x = lph / 2; x > 0; x >>= 1) s += __shfl_xor(s, x);
+                        if (ok && (ld.c4 & (lph - 1)) == 0) a.s_out[(size_t)(n.row0 + r) * a.s_heads + ld.c4 / lph] = s;
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                gout[1][k] = gout[0][k];
+                gout[0][k] = gi[p][k];
+            }
+            // (every load of the loop is unconditional, past the end it repeats the last unit: were one skipped on some path,
+            // the waits would have to assume it everywhere and drain the rows under way)
+            {
+                const Unit n = units.get(min(u + 1, u1 - 1));
+                unsigned char* const t = lds + ((u + 1) & 1) * 3 * PLANE;
+                float mx = 0.f;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) mx = fmaxf(mx, ld.put(t, k, xr[p % DEPTH][k], ld.lr + 8 * k < n.rows));
+                if (mx > kSplitMax) bad[(u + 1) & 3] = 1;
+                fetch_idx(p, u + 1 + 2 * DEPTH);
+                fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH));
+            }
+        }
+    }
+}
+
+template <bool GATHER>
+__device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
+    const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
+    unsigned char* const St = lds + 2 * 3 * PLANE;
+    Units units(a.t, u0 >> 1, u1 >> 1);
+    bf16x8 w[3][8];
+    int cur_seg = -1;
+    bool wbad = false;
+    for (int u = u0 - 1; u <= u1; ++u) {
+        __syncthreads();
+        if (u < u0 || u >= u1) continue;
+        const Unit n = units.get(u);
+        const float* const wp = a.W + (size_t)n.seg * D * D + band * 32 + m;
+        if (n.seg != cur_seg) {
+            cur_seg = n.seg;
+            float mx = 0.f;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {                  // lane (m, kh) keeps W[16 s + 8 kh + 0..7][band * 32 + m]
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = wp[(size_t)(16 * s + 8 * kh + e) * D];
+                split8(x, w[0][s], w[1][s], w[2][s], mx);
+            }
+            wbad = __any(mx > kSplitMax);
+        }
+        if (n.rows <= 0) continue;
+        const bool slow = wbad || bad[u & 3];
+        const int r = n.row0 + min(m, n.rows - 1);
+        multiply_rows(lds + (u & 1) * 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp + (size_t)kh * D, D,
+                      a.X + (size_t)(GATHER && slow ? a.gather[r] : r) * D + kh);
+    }
+}
+
+// GATHER: X rows through the list; SCATTER: Y rows as well; ACCUM: Y += result
+template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_split_fwd_kernel(FwdArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes, [2] result tiles
+    __shared__ int bad[4];
+    const int u0 = 2 * a.t.chunk_tile[blockIdx.x], u1 = 2 * a.t.chunk_tile[blockIdx.x + 1];
+    if (threadIdx.x < 4) bad[threadIdx.x] = 0;
+    __syncthreads();
+    if (u0 >= u1) return;
+    if (threadIdx.x >= 256) fwd_load<GATHER, SCATTER, ACCUM, VEC>(a, lds, bad, u0, u1);
+    else fwd_multiply<GATHER>(a, lds, bad, u0, u1);
+}
+
+// ------------------------------------------------------------------------------------------------ backward
+
+struct BwdArgs {
+    TileArgs t;
+    const float* X;
+    const int32_t* gather;
+    const float* W;
+    const float* dY;
+    int ldd;                 // floats from one row of dY to the next
+    float* dX;
+    const float* rowscale;   // RS: dXrow[i] += rowscale[i] * vec[seg], and the slot's vector part is sum rowscale[i] X[g(i)]
+    const float* vec;
+    float* part;             // slots of D * D + D floats
+};
+constexpr int SLOT = D * D + D;
+struct RowOf { int to; float s; };           // destination and rowscale of a row on its way through the pipeline
+constexpr int BUF = 6 * PLANE;               // planes of a unit: X, then dY
+
+template <bool GATHER, bool BOTH, bool RS>
+__device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, float4* avb, float4* vec_of, RowOf* row_of, int* bad, int u0, int u1) {
+    constexpr int DEPTH = 2;                               // units in flight per thread: 64 KB per compute unit
+    const int tid = threadIdx.x & 255;
+    const Loader ld(tid);
+    Units units(a.t, u0 >> 1, u1 >> 1);
+    unsigned char* const St = lds + 2 * BUF;
+    float4 xr[DEPTH][4], yr[DEPTH][4], av = make_float4(0.f, 0.f, 0.f, 0.f);
+    int gi[2 * DEPTH][4];                                  // indices run further ahead (see the forward)
+    float rs[DEPTH][4];
+    rgnn_v4f xv[DEPTH];                                    // RS: columns of vec[seg], through LDS to the threads that store
+    auto fetch_idx = [&](int p, int u) {
+        const Unit n = units.get(min(u, u1 - 1));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1);      // (an empty second half: the tile's last row)
+            gi[p][k] = GATHER ? a.gather[row] : row;
+        }
+    };
+    auto fetch = [&](int p, int q, int u) {
+        const Unit n = units.get(min(u, u1 - 1));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1);
+            xr[p][k] = *reinterpret_cast<const float4*>(a.X + (size_t)gi[q][k] * D + ld.c4 * 4);
+            yr[p][k] = *reinterpret_cast<const float4*>(a.dY + (size_t)(BOTH ? gi[q][k] : row) * a.ldd + ld.c4 * 4);
+            rs[p][k] = RS ? a.rowscale[row] : 0.f;
+        }
+        if (RS) xv[p] = *reinterpret_cast<const rgnn_v4f*>(a.vec + (size_t)n.seg * D + ld.c4 * 4);
+    };
+#pragma unroll
+    for (int p = 0; p < 2 * DEPTH; ++p) fetch_idx(p, u0 + p);
+#pragma unroll
+    for (int p = 0; p < DEPTH; ++p) fetch(p, p, u0 + p);
+    // the vector part of a slot: the eight threads of a column group leave their sums in avb when the segment ends, and after
+    // the next barrier one of them adds them in order
+    int seg = -1, slot = a.t.chunk_slot[blockIdx.x] - 1, pending = -1, pending_buf = 0;
+    for (int ub = u0 - 1; ub <= u1 + 1; ub += 2 * DEPTH) {
+#pragma unroll
+        for (int p = 0; p < 2 * DEPTH; ++p) {
+            const int u = ub + p;
+            if (u > u1 + 1) break;
+            __syncthreads();
+            clear_flag(bad, u, tid);
+            if (pending >= 0 && tid < 32) {
+                float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (RS) {
+                    s = avb[pending_buf * 256 + tid];
+                    for (int r = 1; r < 8; ++r) fma4(s, 1.f, avb[pending_buf * 256 + r * 32 + tid]);
+                }
+                reinterpret_cast<float4*>(a.part + (size_t)pending * SLOT + D * D)[tid] = s;
+            }
+            pending = -1;
+            if (u - 1 >= u0 && u - 1 < u1) {               // result rows of the unit before
+                const Unit n = units.get(u - 1);
+                float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (RS) v4 = vec_of[((u - 1) & 3) * 32 + ld.c4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int r = ld.lr + 8 * k;
+                    if (r < n.rows) {
+                        float4 y = *stage_at(St + ((u - 1) & 1) * STAGE, r, ld.c4);
+                        if (RS) fma4(y, row_of[((u - 1) & 3) * UNIT + r].s, v4);
+                        const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
+                        float* o = a.dX + (BOTH ? (size_t)row_of[((u - 1) & 3) * UNIT + r].to : (size_t)(n.row0 + r)) * D + ld.c4 * 4;
+                        __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
+                    }
+                }
+            }
+            const Unit n = units.get(min(u + 1, u1 - 1));
+            const int next_seg = u + 1 < u1 ? n.seg : -2;
+            if (next_seg != seg && u + 1 <= u1) {
+                if (seg >= 0) {
+                    pending = slot;
+                    pending_buf = u & 1;
+                    if (RS) avb[pending_buf * 256 + tid] = av;
+                    av = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+                ++slot;
+                seg = next_seg;
+            }
+            {                                              // (unconditional loads: see the forward)
+                unsigned char* const t = lds + ((u + 1) & 1) * BUF;
+                if (RS && tid < 32) *reinterpret_cast<rgnn_v4f*>(vec_of + ((u + 1) & 3) * 32 + tid) = xv[p % DEPTH];
+                float mx = 0.f;
+                float4 au = make_float4(0.f, 0.f, 0.f, 0.f);     // the unit's share first: fewer roundings at the sum's magnitude
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const bool ok = u + 1 < u1 && ld.lr + 8 * k < n.rows;
+                    if (RS && ld.c4 == 0) row_of[((u + 1) & 3) * UNIT + ld.lr + 8 * k].s = rs[p % DEPTH][k];
+                    if (BOTH && ld.c4 == 0) row_of[((u + 1) & 3) * UNIT + ld.lr + 8 * k].to = gi[p][k];
+                    float4 x = xr[p % DEPTH][k];
+                    if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (RS) fma4(au, ok ? rs[p % DEPTH][k] : 0.f, x);
+                    mx = fmaxf(mx, ld.put(t, k, x, ok));
+                    mx = fmaxf(mx, ld.put(t + 3 * PLANE, k, yr[p % DEPTH][k], ok));
+                }
+                if (RS) fma4(av, 1.f, au);
+                if (mx > kSplitMax) bad[(u + 1) & 3] = 1;
+                fetch_idx(p, u + 1 + 2 * DEPTH);
+                fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH), u + 1 + DEPTH);
+            }
+        }
+    }
+}
+
+template <bool GATHER, bool BOTH>
+__device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
+    const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
+    unsigned char* const St = lds + 2 * BUF;
+    Units units(a.t, u0 >> 1, u1 >> 1);
+    bf16x8 w[3][8];
+    int cur_seg = -1;
+    bool wbad = false;
+    for (int u = u0 - 1; u <= u1 + 1; ++u) {
+        __syncthreads();
+        if (u < u0 || u >= u1) continue;
+        const Unit n = units.get(u);
+        const float* const wp = a.W + (size_t)n.seg * D * D + (size_t)(band * 32 + m) * D;
+        if (n.seg != cur_seg) {
+            cur_seg = n.seg;
+            float mx = 0.f;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {                  // lane (m, kh) keeps W[band * 32 + m][16 s + 8 kh + 0..7]
+                float x[8];
+                load_cols(wp + 16 * s + 8 * kh, x);
+                split8(x, w[0][s], w[1][s], w[2][s], mx);
+            }
+            wbad = __any(mx > kSplitMax);
+        }
+        if (n.rows <= 0) continue;
+        const bool slow = wbad || bad[u & 3];
+        const int r = n.row0 + min(m, n.rows - 1);
+        multiply_rows(lds + (u & 1) * BUF + 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp + kh, 1,
+                      a.dY + (size_t)(BOTH && slow ? a.gather[r] : r) * a.ldd + kh);
+    }
+}
+
+template <bool GATHER, bool BOTH>
+__device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
+    const int lane = threadIdx.x & 63, band = (threadIdx.x >> 6) & 3, m = lane & 31, kh = lane >> 5;
+    // Transposing reads: the 16-column groups g and g + 4 of the 128 form a 32 x 32 block (see the bf16 backward); this
+    // wavefront owns feature groups band and band + 4 of X and all four column blocks of dY.
+    const int i16 = lane & 15, tg = (lane >> 4) & 1;
+    // The first read's place is base; other column groups and the second four rows are XORs of it with constants
+    // (row 8 kh + 4 t + q has swz 8 t + 2 q + kh, group b sits at piece 2 b), formed where they are used.
+    const int q16 = i16 >> 2, base = (8 * kh + q16) * 256 + (((8 * tg + ((i16 & 3) >> 1)) ^ (2 * q16 + kh)) << 4) + (i16 & 1) * 8;
+    v16f acc[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+    Units units(a.t, u0 >> 1, u1 >> 1);
+    int cur_seg = -1, slot = a.t.chunk_slot[blockIdx.x] - 1;
+    for (int u = u0 - 1; u <= u1 + 1; ++u) {
+        __syncthreads();
+        if (u < u0 || u > u1) continue;
+        const Unit n = units.get(min(u, u1 - 1));
+        const int seg = u < u1 ? n.seg : -2;
+        if (seg != cur_seg) {
+            if (cur_seg >= 0) {
+                // (the lane's place is made opaque so that the 64 addresses are formed here and not kept across the loop)
+                int at = (16 * band + 4 * kh) * D + (m & 15) + 64 * (m >> 4);
+                asm volatile("" : "+v"(at));
+                float* ps = a.part + (size_t)slot * SLOT + at;
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {         // block row 8 (v / 4) + 4 kh + v % 4: features 16 band + (0..15), then 64 further
+                        ps[((v & 3) + 8 * ((v >> 2) & 1) + 64 * (v >> 3)) * D + 16 * b] = acc[b][v];
+                        acc[b][v] = 0.f;
+                    }
+            }
+            ++slot;
+            cur_seg = seg;
+        }
+        if (u >= u1 || n.rows <= 0) continue;
+        if (!bad[u & 3]) {
+            int at = base;
+            asm volatile("" : "+v"(at));                   // (not kept per group across the loop)
+            const unsigned char* const Xt = lds + (u & 1) * BUF + (at ^ (band << 5));
+            const unsigned char* const Xu = lds + (u & 1) * BUF + (at ^ (band << 5) ^ 128) + 1024;
+            // The unit's products are summed on their own and then added to the running gradient: one rounding at the
+            // gradient's magnitude per 32 rows (16 with the fp32 matrix instructions).
+#pragma unroll
+            for (int hb = 0; hb < 4; hb += 2) {            // two column blocks at a time
+                v16f t0, t1;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) t0[v] = t1[v] = 0.f;
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    bf16x8 x[3], y0[3], y1[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        const unsigned char* yt = lds + (u & 1) * BUF + (3 + q) * PLANE + s * 4096;
+                        x[q] = tr8(Xt + q * PLANE + s * 4096, Xu + q * PLANE + s * 4096);
+                        y0[q] = tr8(yt + (at ^ (hb << 5)), yt + (at ^ (hb << 5) ^ 128) + 1024);
+                        y1[q] = tr8(yt + (at ^ ((hb + 1) << 5)), yt + (at ^ ((hb + 1) << 5) ^ 128) + 1024);
+                    }
+                    mfma_split2(x, y0, t0, x, y1, t1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    acc[hb][v] += t0[v];
+                    acc[hb + 1][v] += t1[v];
+                }
+            }
+        } else {
+            const int f = 16 * band + (m & 15) + 64 * (m >> 4);
+            for (int k = 0; k < UNIT; k += 2) {
+                const int r = n.row0 + min(k + kh, n.rows - 1), g = GATHER ? a.gather[r] : r;
+                const bool ok = k + kh < n.rows;
+                const float x = ok ? a.X[(size_t)g * D + f] : 0.f;
+                const float* yp = a.dY + (size_t)(BOTH ? g : r) * a.ldd + (m & 15) + 64 * (m >> 4);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) acc[b] = mfma32(x, ok ? yp[16 * b] : 0.f, acc[b]);
+            }
+        }
+    }
+}
+
+// GATHER: X rows through the list; BOTH: dY rows and dXrow rows as well
+template <bool GATHER, bool BOTH, bool RS>
+__global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) void typed_linear_split_bwd_kernel(BwdArgs a) {
+    static_assert(!(BOTH && RS) && (GATHER || !BOTH), "combinations the layers use");
+    extern __shared__ __align__(16) unsigned char lds[];   // [2] plane buffers, [2] result tiles, [2][8][32] float4 vector sums
+    __shared__ int bad[4];
+    __shared__ RowOf row_of[4 * UNIT];
+    __shared__ float4 vec_of[4 * 32];
+    const int u0 = 2 * a.t.chunk_tile[blockIdx.x], u1 = 2 * a.t.chunk_tile[blockIdx.x + 1];
+    if (threadIdx.x < 4) bad[threadIdx.x] = 0;
+    __syncthreads();
+    if (u0 >= u1) return;
+    if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH>(a, lds, bad, u0, u1);
+    else if (threadIdx.x < 512) bwd_gradient<GATHER, BOTH>(a, lds, bad, u0, u1);
+    else bwd_load<GATHER, BOTH, RS>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF + 2 * STAGE), vec_of, row_of, bad, u0, u1);
+}
+
+TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
+
+template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_t st) {
+    const size_t lds = 2 * 3 * PLANE + 2 * STAGE;
+    auto kern = typed_linear_split_fwd_kernel<GATHER, SCATTER, ACCUM, VEC>;
+    RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
+    KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
+    hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st,
+                       FwdArgs{tile_args(t), a.X, a.gather, a.W, a.Y, a.y_stride * D, a.vec, a.s_out, a.s_heads});
+    RGNN_HIP(hipGetLastError());
+    return RGNN_OK;
+}
+template <bool GATHER, bool BOTH, bool RS>
+rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, const TileList& t, hipStream_t st) {
+    const size_t lds = 2 * BUF + 2 * STAGE + 2 * 256 * sizeof(float4);
+    auto kern = typed_linear_split_bwd_kernel<GATHER, BOTH, RS>;
+    RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
+    KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
+    hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(768), lds, st,
+                       BwdArgs{tile_args(t), a.X, a.gather, a.W, a.dY, a.dy_stride * D, a.dXrow, a.rowscale, a.vec, a.part});
+    RGNN_HIP(hipGetLastError());
+    return RGNN_OK;
+}
+
+}  // namespace
+
+rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
+    const TileList& t = *a.tiles;
+    if (t.num_tiles == 0) return RGNN_OK;
+    const bool g = a.gather != nullptr, sc = g && a.scatter_out, ac = a.accumulate != 0, v = a.vec != nullptr;
+    if (v && (a.s_heads < 1 || (a.s_heads & (a.s_heads - 1)) || a.s_heads > 32))
+        RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, D);
+    if (g && !sc && !ac && v) return launch_fwd<true, false, false, true>(a, t, st);
+    if (g && !sc && !ac) return launch_fwd<true, false, false, false>(a, t, st);
+    if (g && sc && !ac && !v) return launch_fwd<true, true, false, false>(a, t, st);
+    if (!g && !ac && !v) return launch_fwd<false, false, false, false>(a, t, st);
+    if (!g && ac && !v) return launch_fwd<false, false, true, false>(a, t, st);
+    RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: this combination of gather / scatter / accumulate / vec is not built");
+}
+
+rgnn_status_t typed_linear_split_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
+    const TileList& t = *a.tiles;
+    const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
+    if (a.ysel) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: no row selector at width 128");
+    if (dg != sc) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY gathered and dXrow scattered must go together");
+    if (rs && (dg || !g || !a.vec)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: rowscale needs vec, gathered X and ungathered dY");
+    if (t.num_tiles == 0) return RGNN_OK;
+    if (rs) return launch_bwd<true, false, true>(a, t, st);
+    if (dg) return launch_bwd<true, true, false>(a, t, st);
+    if (g) return launch_bwd<true, false, false>(a, t, st);
+    return launch_bwd<false, false, false>(a, t, st);
+}
+
+}  // namespace rgnn

@@ -183,3 +183,49 @@ def test_relation_sizes_around_the_row_tiles(dtype, d, norm):
     if dtype == "bf16":
         p = {k: (None if v is None else synth.round_to_bf16(v)) for k, v in p.items()}
     _run(N, R, src, dst, rel, p, d, norm, "none", True, tag=f"tiles-{dtype}-d{d}", dtype=dtype)
+
+
+@pytest.mark.parametrize("value", [3.39e38, float("inf")])
+@pytest.mark.parametrize("where", ["X", "W", "dOut"])
+def test_operands_beyond_the_range_of_bfloat16(where, value):
+    """Width 128, fp32: an operand whose bfloat16 rounding is not finite (the largest fp32 values, infinity) takes the tile
+    through the fp32 matrix instructions.  One edge per destination, so every result row is one product; the other operand is
+    scaled by 2^-126 for the finite value, which keeps the products near 1.  Errors are fp32 roundings of 128-term
+    sums: at most 128 * 2^-24 of the sum of magnitudes."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    rng = np.random.default_rng(41)
+    N, R, d = 200, 3, 128
+    src, dst = rng.permutation(N).astype(np.int32), np.arange(N, dtype=np.int32)
+    rel = np.repeat(np.arange(R, dtype=np.int32), [70, 66, 64])
+    p = synth.rgcn_params(rng, N, R, d, d)
+    tiny = np.float32(2.0 ** -126) if np.isfinite(value) else np.float32(1.0)
+    at = {"X": (src[5], 7), "W": (0, 7, 9), "dOut": (5, 11)}[where]
+    p[where][at] = value
+    for k in ("X", "W", "dOut"):
+        if k != where and (where == "W") == (k != "W"):       # the operands that meet it in a product
+            p[k] = p[k] * tiny
+    g = Graph(N, R, src, dst, rel)
+    L = RgcnLayer(g, d, "none")
+    L.load(p["X"], p["W"], None, p["dOut"])
+    L.fwd(); L.bwd()
+    torch.cuda.synchronize()
+    X, W, dO = (p[k].astype(np.float64) for k in ("X", "W", "dOut"))
+    with np.errstate(invalid="ignore"):
+        out, dX, dW = np.zeros((N, d)), np.zeros((N, d)), np.zeros((R, d, d))
+        mag = {"out": np.zeros((N, d)), "dX": np.zeros((N, d)), "dW": np.zeros((R, d, d))}
+        for r in range(R):
+            e = rel == r
+            out[dst[e]], dX[src[e]], dW[r] = X[src[e]] @ W[r], dO[dst[e]] @ W[r].T, X[src[e]].T @ dO[dst[e]]
+            mag["out"][dst[e]], mag["dX"][src[e]] = abs(X[src[e]]) @ abs(W[r]), abs(dO[dst[e]]) @ abs(W[r]).T
+            mag["dW"][r] = abs(X[src[e]]).T @ abs(dO[dst[e]])
+    top = float(np.finfo(np.float32).max)
+    for name, got, want in (("out", L.out, out), ("dX", L.dX, dX), ("dW", L.dW, dW)):
+        got = got.cpu().numpy().astype(np.float64)
+        over = ~(mag[name] < top / 2)                # where fp32 partial sums may overflow only non-finite values are compared
+        assert (np.isfinite(got) | over).all(), name
+        bad = ~np.isfinite(want)
+        assert (~np.isfinite(got[bad])).all(), name
+        ok = ~over & np.isfinite(want)
+        assert (np.abs(got - want)[ok] <= 128 * 2.0 ** -24 * mag[name][ok] + 1e-37).all(), name
+    g.close()
