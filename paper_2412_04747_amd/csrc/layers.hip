@@ -119,20 +119,24 @@ struct GradAcc {
 
 // The chunkings of one list of row tiles that the typed linears pick from:
 //   many, wide  bf16 rows, forward: weight in bf16 / an fp32 weight to be split
-//   f32         the fp32 kernels: one resident round, of three workgroups per compute unit up to width 64, of one at width 128
-//   cu2, cu1    bf16 rows, backward: one bf16 weight / two weights or a split one
+//   f32         the fp32 forward: one resident round, of three workgroups per compute unit up to width 64, of one at width 128
+//   cu2         bf16 rows, backward with one bf16 weight: two workgroups per compute unit
+//   cu1         the fp32 backward, and the bf16 one with two weights or a split one: one workgroup per compute unit.  (The
+//               fused fp32 backward up to width 64 fills a compute unit's LDS; as three rounds of shorter chunks, each with
+//               its weight load, flush and slots, it took 62 us for 48 at 141k pairs and 108 for 82 at 349k, and the
+//               same within 1 % at 7.3M.)
 struct Chunkings { const rgnn::TileList* many; const rgnn::TileList* wide; const rgnn::TileList* f32; const rgnn::TileList* cu2; const rgnn::TileList* cu1; };
 inline Chunkings pair_chunks(const rgnn_graph_t* g, int width) {
     return {&g->pair_tiles, &g->pair_tiles_wide, width == 128 ? &g->pair_tiles_cu1 : &g->pair_tiles_wide, &g->pair_tiles_cu2, &g->pair_tiles_cu1};
 }
 inline Chunkings node_chunks(const rgnn_graph_t* g, int width) {
-    return {&g->node_tiles, &g->node_tiles_wide, width == 128 ? &g->node_tiles_cu1 : &g->node_tiles_wide, &g->node_tiles_cu2, nullptr};
+    return {&g->node_tiles, &g->node_tiles_wide, width == 128 ? &g->node_tiles_cu1 : &g->node_tiles_wide, &g->node_tiles_cu2, &g->node_tiles_cu1};
 }
 inline const rgnn::TileList* all_chunks(const rgnn_graph_t* g, int width) { return width == 128 ? &g->all_tiles_cu1 : &g->all_tiles; }
 // floats of scratch a backward typed linear needs on a list
 size_t tl_bwd_scratch(bool rows16, const Chunkings& t, int d_in, int d_out) {
-    if (!rows16) return typed_linear_bwd_scratch_floats(d_in, d_out, *t.f32);
-    return (size_t)d_in * d_out * std::max((size_t)t.cu2->num_slots, t.cu1 ? 2 * (size_t)t.cu1->num_slots : 0);
+    if (!rows16) return typed_linear_bwd_scratch_floats(d_in, d_out, *t.cu1);
+    return (size_t)d_in * d_out * std::max((size_t)t.cu2->num_slots, 2 * (size_t)t.cu1->num_slots);
 }
 
 // ---- RGAT buffers -----------------------------------------------------------------------
@@ -188,7 +192,7 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->dXp = c.take<float>((size_t)g->P * d->d_in);
     w->A = c.take<float>(H * g->R * d->d_in);
     w->U = c.take<float>(H * g->R * d->d_in);
-    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, *pair_chunks(g, d->d_out).f32, (int)H));
+    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles_cu1, (int)H));
     const size_t parts = std::max<size_t>({(size_t)g->pair_items.num_partials, (size_t)g->relrun_items.num_partials,
                                            (size_t)g->relpair_items.num_partials});
     w->partial = c.take<float>(parts * std::max(d->d_in, d->d_out) * H);   // the run walk keeps one partial row per head
@@ -218,7 +222,7 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->dXp = c.rows((size_t)g->P * d->d_in, h);
     w->dX0 = c.take<float>((size_t)g->N * d->d_in);
     w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out),
-                                        typed_linear_bwd_scratch_floats(d->d_in, d->d_out, *all_chunks(g, d->d_out))));
+                                        typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_cu1)));
     w->partial = c.take<float>((size_t)g->pair_items.num_partials * d->d_out);
     const bool acc = grads_accumulate(d);
     w->acc_dW = acc ? c.take<float>((size_t)g->R * d->d_in * d->d_out) : nullptr;
@@ -358,12 +362,11 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
         a.tiles = W16 ? tiles.cu2 : tiles.cu1; a.X = X; a.gather = gather; a.both_gathered = both_gathered;
         a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.dY = dY; a.dy_stride = dy_stride; a.dXrow = dXrow; a.dx_f32 = !dx16;
         a.accumulate = dx_acc; a.dW = dW; a.part = part; a.label = label; a.ysel = ysel; a.dY_alt = y_alt; a.yscale = yscale;
-        if (!a.tiles) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: no chunking of this list for an fp32 weight");
         return typed_linear_bwd_bf16(d, a, st);
     }
     if (dx_acc) RGNN_FAIL(RGNN_EUNSUPPORTED, "accumulating input gradient needs bf16 rows");
     TypedLinearBwdArgs b{};
-    b.tiles = tiles.f32; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
+    b.tiles = tiles.cu1; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
     b.dy_gathered = both_gathered; b.dXrow = static_cast<float*>(dXrow); b.scatter_dx = both_gathered; b.dW = dW;
     b.part = part; b.label = label; b.dy_stride = dy_stride;
     return typed_linear_bwd(d_in, d, b, st);
@@ -514,7 +517,7 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     // 3. self-loop: dX0 = dPre W0^T, dW0 = X^T dPre
     if (W0) {
         TypedLinearBwdArgs s{};
-        s.tiles = all_chunks(g, D); s.X = X32; s.W = W032; s.dY = dPre32;
+        s.tiles = &g->all_tiles_cu1; s.X = X32; s.W = W032; s.dY = dPre32;
         s.dXrow = w.dX0; s.dW = static_cast<float*>(dW0); s.part = w.tl_part; s.label = "self_loop_bwd";
         RGNN_TRY(typed_linear_bwd(K, D, s, st));
     }
@@ -685,7 +688,7 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
                             sel ? w.ds_src : nullptr, 2 * H));
         // 4. dXp = dHs W^T, dW = sum X^T dHs; with the selector also A[r][h] = sum over r's pairs of ds_src[p][h] X[src_p]
         TypedLinearBwdArgs b{};
-        b.tiles = pair_chunks(g, D).f32; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
+        b.tiles = &g->pair_tiles_cu1; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
         b.dW = static_cast<float*>(dW); b.part = w.tl_part;
         if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.hcoef = w.ds_src; b.wvec = ws; b.sel_heads = H; b.Avec = w.A; }
         RGNN_TRY(typed_linear_bwd(K, D, b, st));
@@ -726,7 +729,7 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     //    A[r] = sum ds_src X
     RGNN_TRY(fold_weight(g->R, K, D, Wf, static_cast<const float*>(w_s), w.wsp, st, static_cast<const float*>(w_t), w.wtp));   // wtp: step 7
     TypedLinearBwdArgs b{};
-    b.tiles = pair_chunks(g, D).f32; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
+    b.tiles = &g->pair_tiles_cu1; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
     b.rowscale = sel ? nullptr : w.ds_src; b.vec = w.wsp; b.dW = static_cast<float*>(dW); b.Avec = w.A;
     b.part = w.tl_part;
     if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.ds_yscale = reinterpret_cast<const float2*>(w.ds_src); }

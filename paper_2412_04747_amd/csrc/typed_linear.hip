@@ -197,8 +197,8 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
 //
 // Backward, wave-independent: eight wavefronts per workgroup, each owning 32-row units of
 // the run.  Per unit a wavefront forms dXrow = dY W^T (+ rowscale (x) xvec) and adds its
-// rows' contribution to the full KD x ND weight gradient (KB*NB blocks, kept in registers
-// for the whole run) and to Avec.  At the end of a run the eight wavefronts' partial weight
+// rows' contribution, summed over the unit first, to the full KD x ND weight gradient (KB*NB blocks, kept in
+// registers for the whole run) and to Avec.  At the end of a run the eight wavefronts' partial weight
 // gradients are summed in wavefront order through LDS and written to the chunk's slot.
 //
 // SEL (row selector): row i of dY is either dY[ysel[i]] or, when the top bit of ysel[i] is set, row
@@ -382,9 +382,59 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
             // The wavefront that is in its MFMA section goes first at instruction issue: the other wavefront
             // of the SIMD then fills the gaps with its loads and stores instead of interleaving its own MFMAs.
             __builtin_amdgcn_s_setprio(2);
+            // Weight gradient: KD x ND, contraction over the unit's 32 rows (two rows per MFMA), one 32 x 32 block at a
+            // time.  A unit's products are summed on their own and then added to the running gradient: one rounding at
+            // the gradient's magnitude per 32 rows instead of sixteen.  With a whole chunk in one chain of MFMAs the
+            // error of dW against 64 bits grows with the chunk's length (7.3M pairs in 256 chunks: 9.1e-7; so: 2.7e-7).
+            // This section comes before the dXrow one, whose accumulators have to live until the rows are stored: the
+            // other way round the unit's block spills.  The rows' contribution to Avec rides along with the first
+            // columns: lane (m, kh) holds X[2 s + kh][kb * 32 + m] as its A operand and adds rowscale[2 s + kh] times it
+            // to its partial of column kb * 32 + m.  With heads, a 4x4x1 MFMA does that for four heads at once: each
+            // group of four lanes forms the outer product of the rowscale of its row for heads 0..3 (lane j of the
+            // group brings head j's) with the group's four X values, and lane (m, kh) gets the four heads' partials of
+            // its column.
+#pragma unroll
+            for (int b = 0; b < WB; ++b) {
+                const int kb = b % KB, nb = b / KB;
+                float av = Xw[kh * XS + kb * 32 + m], bv = Yw[kh * YS + nb * 32 + m], pu = 0.f, c1 = 0.f;
+                v4f ph{0.f, 0.f, 0.f, 0.f};
+                v16f t;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) t[v] = 0.f;
+                if (HS && nb == 0) c1 = Xw[kh * XS + KD + (lane & (HS - 1))];
+#pragma unroll
+                for (int s2 = 0; s2 < 16; ++s2) {
+                    float an = 0.f, bn = 0.f, c1n = 0.f;
+                    if (s2 + 1 < 16) {
+                        const int r = 2 * (s2 + 1) + kh;
+                        an = Xw[r * XS + kb * 32 + m];
+                        bn = Yw[r * YS + nb * 32 + m];
+                        if (HS && nb == 0) c1n = Xw[r * XS + KD + (lane & (HS - 1))];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (RS && nb == 0) {
+                        const float w0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dsc), 2 * s2));
+                        const float w1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dsc), 2 * s2 + 1));
+                        pu += (kh ? w1 : w0) * av;
+                    }
+                    if (HS && nb == 0) ph = __builtin_amdgcn_mfma_f32_4x4x1f32(c1, av, ph, 0, 0, 0);
+                    t = mfma32(av, bv, t);
+                    av = an;
+                    bv = bn;
+                    c1 = c1n;
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    accw[b][v] += t[v];
+                    asm volatile("" : "+v"(accw[b][v]));    // done here, not delayed: t's registers are needed again
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (RS && nb == 0) pa[kb] += pu;
+                if (HS && nb == 0) pah[HS ? kb : 0] += ph;
+            }
             // dXrow unit: 32 x KD, contraction over the output features.  The LDS operands of both MFMA
             // sections are read ahead of the MFMAs that use them (a ring of B operands two steps deep here,
-            // one step in the weight-gradient section), so a wavefront alone on its SIMD keeps the pipe fed.
+            // one step above), so a wavefront alone on its SIMD keeps the pipe fed.
             v16f accx[KB];
 #pragma unroll
             for (int b = 0; b < KB; ++b)
@@ -414,57 +464,7 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
                     if (s2 % 4 == 3) a4 = a4n;
                 }
             }
-            // weight gradient: KD x ND, contraction over the unit's 32 rows (two rows per MFMA).  The rows'
-            // contribution to Avec rides along: lane (m, kh) holds X[2 s + kh][kb * 32 + m] as its A operand
-            // and adds rowscale[2 s + kh] times it to its partial of column kb * 32 + m.  With heads, a 4x4x1 MFMA
-            // does that for four heads at once: each group of four lanes forms the outer product of the rowscale of
-            // its row for heads 0..3 (lane j of the group brings head j's) with the group's four X values, and lane
-            // (m, kh) gets the four heads' partials of its column.
-            {
-                float av[KB], bv[NB];
-                float c1 = 0.f, c1n = 0.f;
-                if (HS) c1 = Xw[kh * XS + KD + (lane & (HS - 1))];
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) av[kb] = Xw[kh * XS + kb * 32 + m];
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) bv[nb] = Yw[kh * YS + nb * 32 + m];
-#pragma unroll
-                for (int s2 = 0; s2 < 16; ++s2) {
-                    float an[KB], bn[NB];
-                    if (s2 + 1 < 16) {
-                        const int r = 2 * (s2 + 1) + kh;
-#pragma unroll
-                        for (int kb = 0; kb < KB; ++kb) an[kb] = Xw[r * XS + kb * 32 + m];
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) bn[nb] = Yw[r * YS + nb * 32 + m];
-                        if (HS) c1n = Xw[r * XS + KD + (lane & (HS - 1))];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (RS) {
-                        const float w0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dsc), 2 * s2));
-                        const float w1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dsc), 2 * s2 + 1));
-                        const float w = kh ? w1 : w0;
-#pragma unroll
-                        for (int kb = 0; kb < KB; ++kb) pa[kb] += w * av[kb];
-                    }
-                    if (HS) {
-#pragma unroll
-                        for (int kb = 0; kb < KB; ++kb) pah[HS ? kb : 0] = __builtin_amdgcn_mfma_f32_4x4x1f32(c1, av[kb], pah[HS ? kb : 0], 0, 0, 0);
-                        c1 = c1n;
-                    }
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                        for (int kb = 0; kb < KB; ++kb) accw[nb * KB + kb] = mfma32(av[kb], bv[nb], accw[nb * KB + kb]);
-
-                    if (s2 + 1 < 16) {
-#pragma unroll
-                        for (int kb = 0; kb < KB; ++kb) av[kb] = an[kb];
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) bv[nb] = bn[nb];
-                    }
-                }
-            }
+            __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_setprio(0);
             wave_lds_fence();             // all reads of Yw are done before it becomes the dXrow stage
 #pragma unroll
