@@ -213,6 +213,11 @@ struct TileTable {
     __device__ __forceinline__ int row1_at(int l) const { return __builtin_amdgcn_readlane(row1, l); }
 };
 
+// max(v, 0), NaN to 0
+__device__ __forceinline__ float4 positive(float4 v) {
+    return make_float4(v.x > 0.f ? v.x : 0.f, v.y > 0.f ? v.y : 0.f, v.z > 0.f ? v.z : 0.f, v.w > 0.f ? v.w : 0.f);
+}
+
 inline unsigned blocks_for(size_t n, unsigned per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 #define RGNN_CHECK_LAUNCH() RGNN_HIP(hipGetLastError())

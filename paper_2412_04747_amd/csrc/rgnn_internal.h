@@ -158,6 +158,7 @@ struct TypedLinearArgs {
     int s_heads = 1;         // a power of two with ND / s_heads >= 16
     const char* label;       // name in the timing report (nullptr: default)
     int y_stride = 1;        // rows of Y are y_stride * d_out floats apart (1 or 2)
+    int relu = 0;            // with accumulate: Y = max(Y + result, 0)
 };
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st);
 

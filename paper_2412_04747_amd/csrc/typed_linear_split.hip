@@ -173,6 +173,7 @@ struct FwdArgs {
     const float* vec;        // VEC: s_out[row][h] = Y_row . vec[seg] over head h's columns
     float* s_out;
     int s_heads;
+    int relu;
 };
 
 template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
@@ -226,6 +227,7 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
                         if (ACCUM) {
                             const float4 old = *reinterpret_cast<const float4*>(o);
                             y.x += old.x; y.y += old.y; y.z += old.z; y.w += old.w;
+                            if (a.relu) y = positive(y);
                         }
                         const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
                         __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
@@ -292,7 +294,7 @@ __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* ld
     }
 }
 
-// GATHER: X rows through the list; SCATTER: Y rows as well; ACCUM: Y += result
+// GATHER: X rows through the list; SCATTER: Y rows as well; ACCUM: Y += result (relu: then max(Y, 0))
 template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_split_fwd_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes, [2] result tiles
@@ -571,7 +573,7 @@ rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st,
-                       FwdArgs{tile_args(t), a.X, a.gather, a.W, a.Y, a.y_stride * D, a.vec, a.s_out, a.s_heads});
+                       FwdArgs{tile_args(t), a.X, a.gather, a.W, a.Y, a.y_stride * D, a.vec, a.s_out, a.s_heads, a.relu});
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -595,6 +597,7 @@ rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
     const bool g = a.gather != nullptr, sc = g && a.scatter_out, ac = a.accumulate != 0, v = a.vec != nullptr;
     if (v && (a.s_heads < 1 || (a.s_heads & (a.s_heads - 1)) || a.s_heads > 32))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, D);
+    if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
     if (g && !sc && !ac && v) return launch_fwd<true, false, false, true>(a, t, st);
     if (g && !sc && !ac) return launch_fwd<true, false, false, false>(a, t, st);
     if (g && sc && !ac && !v) return launch_fwd<true, true, false, false>(a, t, st);

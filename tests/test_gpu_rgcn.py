@@ -229,3 +229,34 @@ def test_operands_beyond_the_range_of_bfloat16(where, value):
         ok = ~over & np.isfinite(want)
         assert (np.abs(got - want)[ok] <= 128 * 2.0 ** -24 * mag[name][ok] + 1e-37).all(), name
     g.close()
+
+
+@pytest.mark.parametrize("N", [700, 701])
+@pytest.mark.parametrize("dtype,d", [("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 32), ("bf16", 128)])
+def test_relu_mask_of_an_output_off_the_16_byte_grid(dtype, d, N):
+    """The backward reads `out` four elements at a time where its address allows it: the same bits, masked one by one, when
+    it does not; and the forward's activation, in the self-loop's epilogue, is max(0, .) of the run without one."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    rng, src, dst, rel, _ = synth.tiny(70 + d, N=N, R=5, E=6000)
+    p = synth.rgcn_params(rng, N, 5, d, d, self_loop=True)
+    g = Graph(N, 5, src, dst, rel)
+    outs = {}
+    for act in ("none", "relu"):
+        L = RgcnLayer(g, d, "in_degree_per_rel", act, True, dtype=dtype)
+        L.load(p["X"], p["W"], p["W0"], p["dOut"])
+        L.fwd()
+        torch.cuda.synchronize()
+        outs[act] = L.out.clone()
+    assert torch.equal(outs["relu"], outs["none"].clamp(min=0))
+    L.bwd()
+    torch.cuda.synchronize()
+    want = {k: v.clone() for k, v in L.grads().items()}
+    buf = torch.empty(L.out.numel() + 1, device="cuda")
+    L.out = buf[1:].view_as(outs["relu"]).copy_(outs["relu"])
+    assert L.out.data_ptr() % 16 == 4
+    L.bwd()
+    torch.cuda.synchronize()
+    for k, v in L.grads().items():
+        assert torch.equal(v, want[k]), k
+    g.close()
