@@ -324,7 +324,7 @@ void* saved_or_scratch(const rgnn_graph_t* g, int layer, const rgnn_layer_desc_t
 // y_stride: the output rows are y_stride * d elements apart.
 rgnn_status_t tl_fwd(bool bf16, const Chunkings& tiles, int d, const float* A32,
                      const void* A16, const int32_t* gather, int scatter, const float* W32, const void* W16, void* Y,
-                     bool y16, const char* label, hipStream_t st, int d_in = 0, int y_stride = 1) {
+                     bool y16, const char* label, hipStream_t st, int d_in = 0, int y_stride = 1, bool sign_matters = false) {
     if (d_in == 0) d_in = d;
     if (bf16) {
         if (d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear on the bf16 matrix cores: equal widths only");
@@ -336,7 +336,7 @@ rgnn_status_t tl_fwd(bool bf16, const Chunkings& tiles, int d, const float* A32,
     }
     TypedLinearArgs a{};
     a.tiles = tiles.f32; a.X = A32; a.gather = gather; a.W = W32; a.Y = static_cast<float*>(Y); a.scatter_out = scatter;
-    a.label = label; a.y_stride = y_stride;
+    a.label = label; a.y_stride = y_stride; a.sign_matters = sign_matters;
     return typed_linear_fwd(d_in, d, a, st);
 }
 
@@ -432,7 +432,7 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int D = desc->d_out;
     RgcnFwdWs w;
-    const bool bf16 = desc->dtype == RGNN_BF16, h = rows_bf16(desc);
+    const bool bf16 = desc->dtype == RGNN_BF16, h = rows_bf16(desc), relu = desc->activation == RGNN_ACT_RELU;
     const void* X16 = bf16 ? X : nullptr;
     const void* W16 = bf16 ? W : nullptr;
     Bf16Stage stg(workspace, carve_rgcn_fwd(g, desc, workspace, &w), bf16, st);
@@ -443,18 +443,17 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     RGNN_TRY(stg.status);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
     RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
-                    desc->d_in));
+                    desc->d_in, 1, relu));
     // 2. out[v] = sum_e (1/c) Hs[pair_e]
     const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
     RGNN_TRY(gather_sum(g->dst_items, D, nullptr, g->idx[RGNN_IDX_IN_PAIR], 0, coef, 1, 0, w.Hs, out, w.partial, st, 0,
                         "aggregate_fwd", "aggregate_fwd.combine", 1, h, 0));
     // 3. self-loop: out += X W0, and the activation on the way out (a pass of its own over out took 16.5 us at 120k
     //    nodes of width 64; without a self-loop it still is one)
-    const bool relu = desc->activation == RGNN_ACT_RELU;
     if (W0) {
         TypedLinearArgs s{};
         s.tiles = all_chunks(g, D); s.X = X32; s.W = W032;
-        s.Y = static_cast<float*>(out); s.accumulate = 1; s.relu = relu; s.label = "self_loop_fwd";
+        s.Y = static_cast<float*>(out); s.accumulate = 1; s.relu = s.sign_matters = relu; s.label = "self_loop_fwd";
         RGNN_TRY(typed_linear_fwd(desc->d_in, D, s, st));
     }
     if (relu && !W0) RGNN_TRY(relu_inplace((size_t)g->N * D, static_cast<float*>(out), st));
@@ -606,6 +605,7 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[r]
     //    (the comparison schedules also take the source half of the logit per pair, s_src[p] = Hs[p] . w_s[r])
     TypedLinearArgs a{};
+    a.sign_matters = 1;
     a.tiles = pair_chunks(g, D).f32; a.X = Xf; a.gather = g->idx[RGNN_IDX_PAIR_SRC]; a.W = Wf; a.Y = sv.Hs;
     if (!fused) { a.vec = static_cast<const float*>(w_s); a.s_out = w.s_src; }
     RGNN_TRY(typed_linear_fwd(K, D, a, st));

@@ -1,4 +1,5 @@
-// Relation-segmented typed linear layer on the fp32 matrix cores, widths 32 and 64 (width 128: typed_linear_split.hip).
+// Relation-segmented typed linear layer on the fp32 matrix cores, widths 32 and 64 (width 128: typed_linear_split.hip,
+// and the forward here where the sign of its result matters).
 //
 // Forward   Y[i] = X[gather[i]] W[seg(i)]          (thesis Ch.3: segment MM, Y[S] = X[G] x W[T];
 //                                                   rows are presorted by type so one weight serves a segment)
@@ -618,14 +619,14 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, ND);
     if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
     if (a.y_stride == 2) {
-        if constexpr (KD == ND) {
+        if constexpr (KD == ND && KD < 128) {
             if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false, 2>(a, st);
         }
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built for gathered rows of equal widths only");
     }
     if (g && !sc && !ac && v) return launch_fwd_wave<KD, ND, true, false, false, true>(a, st);
     if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false>(a, st);
-    if constexpr (KD == ND) {
+    if constexpr (KD == ND && KD < 128) {
         if (g && sc && !ac && !v) return launch_fwd_wave<KD, ND, true, true, false, false>(a, st);
     }
     if (!g && !ac && !v) return launch_fwd_wave<KD, ND, false, false, false, false>(a, st);
@@ -637,7 +638,10 @@ rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hi
     if (a.tiles->num_tiles == 0) return RGNN_OK;
     if (d_in == 64 && d_out == 64) return launch_fwd<64, 64>(a, st);
     if (d_in == 32 && d_out == 32) return launch_fwd<32, 32>(a, st);
-    if (d_in == 128 && d_out == 128) return typed_linear_split_fwd(a, st);
+    // Width 128: the split product, except where a sign of the result selects a branch of the backward.  A value within
+    // rounding of zero then decides a gradient row, and the rounding stays the one of the fp32 instructions (1.43M pairs:
+    // 0.52 ms, split 0.31).
+    if (d_in == 128 && d_out == 128) return a.sign_matters ? launch_fwd<128, 128>(a, st) : typed_linear_split_fwd(a, st);
     if (d_in == 32 && d_out == 64) return launch_fwd<32, 64>(a, st);
     if (d_in == 64 && d_out == 32) return launch_fwd<64, 32>(a, st);
     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: d_in = %d, d_out = %d not supported (need 32 / 64 / 128, different widths only among 32 and 64)", d_in, d_out);

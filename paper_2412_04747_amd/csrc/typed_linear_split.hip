@@ -9,7 +9,8 @@
 // matrix instructions, straight from global memory.
 //
 // Why: at width 128 a row costs 32 kflop per product against 1.5 KB of traffic, twice what the fp32 matrix cores do in the time
-// the rows need.  1.43M pairs of 60 relations: forward 0.52 -> 0.31 ms (4.7 TB/s), backward (two kernels before, dY read
+// the rows need.  (RGAT's forward and RGCN's with ReLU stay on those: the sign of a result selects a branch of their backward.)
+// 1.43M pairs of 60 relations: forward 0.52 -> 0.31 ms (4.7 TB/s), backward (two kernels before, dY read
 // twice) 1.18 -> 0.60 ms (3.7 TB/s; the loading wavefronts' chain of waits, splits and LDS writes per unit).
 //
 // A workgroup takes a chunk of 64-row tiles in units of 32 rows, one workgroup per compute unit, its wavefronts specialised:
@@ -170,13 +171,9 @@ struct FwdArgs {
     const float* W;          // [segs][D][D]
     float* Y;
     int ldy;                 // floats from one row of Y to the next
-    const float* vec;        // VEC: s_out[row][h] = Y_row . vec[seg] over head h's columns
-    float* s_out;
-    int s_heads;
-    int relu;
 };
 
-template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+template <bool GATHER, bool SCATTER, bool ACCUM>
 __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     constexpr int DEPTH = 3;                               // units in flight per thread: 48 KB per compute unit
     const int tid = threadIdx.x & 255;
@@ -215,8 +212,6 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
             clear_flag(bad, u, tid);
             if (u - 1 >= u0) {                             // result rows of the unit before
                 const Unit n = units.get(u - 1);
-                float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (VEC) v4 = *reinterpret_cast<const float4*>(a.vec + (size_t)n.seg * D + ld.c4 * 4);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int r = ld.lr + 8 * k;
@@ -227,16 +222,9 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
                         if (ACCUM) {
                             const float4 old = *reinterpret_cast<const float4*>(o);
                             y.x += old.x; y.y += old.y; y.z += old.z; y.w += old.w;
-                            if (a.relu) y = positive(y);
                         }
                         const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
                         __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
-                    }
-                    if (VEC) {
-                        float s = dot4(y, v4);
-                        const int lph = 32 / a.s_heads;
-                        for (int x = lph / 2; x > 0; x >>= 1) s += __shfl_xor(s, x);
-                        if (ok && (ld.c4 & (lph - 1)) == 0) a.s_out[(size_t)(n.row0 + r) * a.s_heads + ld.c4 / lph] = s;
                     }
                 }
             }
@@ -294,8 +282,8 @@ __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* ld
     }
 }
 
-// GATHER: X rows through the list; SCATTER: Y rows as well; ACCUM: Y += result (relu: then max(Y, 0))
-template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+// GATHER: X rows through the list; SCATTER: Y rows as well; ACCUM: Y += result
+template <bool GATHER, bool SCATTER, bool ACCUM>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_split_fwd_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes, [2] result tiles
     __shared__ int bad[4];
@@ -303,7 +291,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x >= 256) fwd_load<GATHER, SCATTER, ACCUM, VEC>(a, lds, bad, u0, u1);
+    if (threadIdx.x >= 256) fwd_load<GATHER, SCATTER, ACCUM>(a, lds, bad, u0, u1);
     else fwd_multiply<GATHER>(a, lds, bad, u0, u1);
 }
 
@@ -566,14 +554,14 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 
 TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
 
-template <bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+template <bool GATHER, bool SCATTER, bool ACCUM>
 rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_t st) {
     const size_t lds = 2 * 3 * PLANE + 2 * STAGE;
-    auto kern = typed_linear_split_fwd_kernel<GATHER, SCATTER, ACCUM, VEC>;
+    auto kern = typed_linear_split_fwd_kernel<GATHER, SCATTER, ACCUM>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st,
-                       FwdArgs{tile_args(t), a.X, a.gather, a.W, a.Y, a.y_stride * D, a.vec, a.s_out, a.s_heads, a.relu});
+                       FwdArgs{tile_args(t), a.X, a.gather, a.W, a.Y, a.y_stride * D});
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -595,14 +583,11 @@ rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
     const TileList& t = *a.tiles;
     if (t.num_tiles == 0) return RGNN_OK;
     const bool g = a.gather != nullptr, sc = g && a.scatter_out, ac = a.accumulate != 0, v = a.vec != nullptr;
-    if (v && (a.s_heads < 1 || (a.s_heads & (a.s_heads - 1)) || a.s_heads > 32))
-        RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, D);
-    if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
-    if (g && !sc && !ac && v) return launch_fwd<true, false, false, true>(a, t, st);
-    if (g && !sc && !ac) return launch_fwd<true, false, false, false>(a, t, st);
-    if (g && sc && !ac && !v) return launch_fwd<true, true, false, false>(a, t, st);
-    if (!g && !ac && !v) return launch_fwd<false, false, false, false>(a, t, st);
-    if (!g && ac && !v) return launch_fwd<false, false, true, false>(a, t, st);
+    if (a.relu) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: no activation on the split product");
+    if (g && !sc && !ac && !v) return launch_fwd<true, false, false>(a, t, st);
+    if (g && sc && !ac && !v) return launch_fwd<true, true, false>(a, t, st);
+    if (!g && !ac && !v) return launch_fwd<false, false, false>(a, t, st);
+    if (!g && ac && !v) return launch_fwd<false, false, true>(a, t, st);
     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: this combination of gather / scatter / accumulate / vec is not built");
 }
 
