@@ -443,7 +443,7 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     RGNN_TRY(stg.status);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
     RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
-                    desc->d_in, 1, relu));
+                    desc->d_in, 1, true));
     // 2. out[v] = sum_e (1/c) Hs[pair_e]
     const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
     RGNN_TRY(gather_sum(g->dst_items, D, nullptr, g->idx[RGNN_IDX_IN_PAIR], 0, coef, 1, 0, w.Hs, out, w.partial, st, 0,
@@ -453,7 +453,7 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     if (W0) {
         TypedLinearArgs s{};
         s.tiles = all_chunks(g, D); s.X = X32; s.W = W032;
-        s.Y = static_cast<float*>(out); s.accumulate = 1; s.relu = s.sign_matters = relu; s.label = "self_loop_fwd";
+        s.Y = static_cast<float*>(out); s.accumulate = 1; s.relu = relu; s.sign_matters = 1; s.label = "self_loop_fwd";
         RGNN_TRY(typed_linear_fwd(desc->d_in, D, s, st));
     }
     if (relu && !W0) RGNN_TRY(relu_inplace((size_t)g->N * D, static_cast<float*>(out), st));

@@ -159,7 +159,7 @@ struct TypedLinearArgs {
     const char* label;       // name in the timing report (nullptr: default)
     int y_stride = 1;        // rows of Y are y_stride * d_out floats apart (1 or 2)
     int relu = 0;            // with accumulate: Y = max(Y + result, 0)
-    int sign_matters = 0;    // 1: the backward takes a branch on the sign of what becomes of Y (ReLU, leaky ReLU)
+    int sign_matters = 0;    // 1: a backward takes a branch on the sign of what becomes of Y (leaky ReLU; ReLU, also the caller's own)
 };
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st);
 

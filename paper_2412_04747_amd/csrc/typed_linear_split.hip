@@ -9,7 +9,7 @@
 // matrix instructions, straight from global memory.
 //
 // Why: at width 128 a row costs 32 kflop per product against 1.5 KB of traffic, twice what the fp32 matrix cores do in the time
-// the rows need.  (RGAT's forward and RGCN's with ReLU stay on those: the sign of a result selects a branch of their backward.)
+// the rows need.  (RGAT's and RGCN's forward stay on those: the sign of a result selects a branch of their backward.)
 // 1.43M pairs of 60 relations: forward 0.52 -> 0.31 ms (4.7 TB/s), backward (two kernels before, dY read
 // twice) 1.18 -> 0.60 ms (3.7 TB/s; the loading wavefronts' chain of waits, splits and LDS writes per unit).
 //
@@ -173,7 +173,7 @@ struct FwdArgs {
     int ldy;                 // floats from one row of Y to the next
 };
 
-template <bool GATHER, bool SCATTER, bool ACCUM>
+template <bool GATHER, bool SCATTER>
 __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     constexpr int DEPTH = 3;                               // units in flight per thread: 48 KB per compute unit
     const int tid = threadIdx.x & 255;
@@ -219,10 +219,6 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
                     float4 y = *stage_at(St + ((u - 1) & 1) * STAGE, r, ld.c4);
                     if (ok) {
                         float* o = a.Y + (SCATTER ? (size_t)gout[1][k] : (size_t)(n.row0 + r)) * a.ldy + ld.c4 * 4;
-                        if (ACCUM) {
-                            const float4 old = *reinterpret_cast<const float4*>(o);
-                            y.x += old.x; y.y += old.y; y.z += old.z; y.w += old.w;
-                        }
                         const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
                         __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
                     }
@@ -282,8 +278,8 @@ __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* ld
     }
 }
 
-// GATHER: X rows through the list; SCATTER: Y rows as well; ACCUM: Y += result
-template <bool GATHER, bool SCATTER, bool ACCUM>
+// GATHER: X rows through the list; SCATTER: Y rows as well
+template <bool GATHER, bool SCATTER>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_split_fwd_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes, [2] result tiles
     __shared__ int bad[4];
@@ -291,7 +287,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x >= 256) fwd_load<GATHER, SCATTER, ACCUM>(a, lds, bad, u0, u1);
+    if (threadIdx.x >= 256) fwd_load<GATHER, SCATTER>(a, lds, bad, u0, u1);
     else fwd_multiply<GATHER>(a, lds, bad, u0, u1);
 }
 
@@ -554,10 +550,10 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 
 TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
 
-template <bool GATHER, bool SCATTER, bool ACCUM>
+template <bool GATHER, bool SCATTER>
 rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_t st) {
     const size_t lds = 2 * 3 * PLANE + 2 * STAGE;
-    auto kern = typed_linear_split_fwd_kernel<GATHER, SCATTER, ACCUM>;
+    auto kern = typed_linear_split_fwd_kernel<GATHER, SCATTER>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st,
@@ -584,10 +580,9 @@ rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
     if (t.num_tiles == 0) return RGNN_OK;
     const bool g = a.gather != nullptr, sc = g && a.scatter_out, ac = a.accumulate != 0, v = a.vec != nullptr;
     if (a.relu) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: no activation on the split product");
-    if (g && !sc && !ac && !v) return launch_fwd<true, false, false>(a, t, st);
-    if (g && sc && !ac && !v) return launch_fwd<true, true, false>(a, t, st);
-    if (!g && !ac && !v) return launch_fwd<false, false, false>(a, t, st);
-    if (!g && ac && !v) return launch_fwd<false, false, true>(a, t, st);
+    if (g && !sc && !ac && !v) return launch_fwd<true, false>(a, t, st);
+    if (g && sc && !ac && !v) return launch_fwd<true, true>(a, t, st);
+    if (!g && !ac && !v) return launch_fwd<false, false>(a, t, st);
     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: this combination of gather / scatter / accumulate / vec is not built");
 }
 
