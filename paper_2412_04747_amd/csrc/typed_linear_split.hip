@@ -4,9 +4,15 @@
 // |lo| <= 2^-18 |x|), and a product is the six plane products down to 2^-18: hi hi + (hi mid + mid hi) + (hi lo + mid mid +
 // lo hi); what is left out is below 2^-26 of |x y|, a quarter of a rounding of the fp32 product.  Products are exact and sums
 // are fp32, one rounding per 16 terms and plane product against one per 2 terms of v_mfma_f32_32x32x2_f32, so the result is
-// as close to 64 bits as that of the fp32 matrix instructions, at 16 / 6 of their rate.  Beyond the range of bf16 (an
-// operand above 3.38e38, or infinite) the split does not hold: a tile that contains such a value is multiplied with the fp32
-// matrix instructions, straight from global memory.
+// as close to 64 bits as that of the fp32 matrix instructions, at 16 / 6 of their rate.  (The technique: G. Henry, P. Tang,
+// A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019.)
+//
+// The split holds for zero and for magnitudes from 2^-110, the least fp32 whose last bit, 2^-133, is a (subnormal) bf16, to
+// 3.38e38, the greatest whose bf16 is finite.  A unit of rows, or a weight's band of 32 rows or columns, with an operand
+// outside is multiplied with the fp32 matrix instructions, straight from global memory (a backward whose every unit goes that
+// way, 1.43M pairs: 1.9 ms for 0.7).  NaN needs no such care: its planes are NaN.  Without the lower bound the error of dX and
+// dW, 1.1e-7 and 1.7e-7 in the range, was 2.2e-6 with one operand near 2^-116 and 3.5e-5 near 2^-120; the check costs 1.3 % of an
+// RGAT forward + backward on those pairs.
 //
 // Why: at width 128 a row costs 32 kflop per product against 1.5 KB of traffic, twice what the fp32 matrix cores do in the time
 // the rows need.  (RGAT's and RGCN's forward stay on those: the sign of a result selects a branch of their backward.)
@@ -40,6 +46,7 @@ constexpr int UNIT = 32;                     // rows of a unit
 constexpr int PLANE = UNIT * 2 * D;          // bytes of one plane of a unit
 constexpr int STAGE = UNIT * 4 * D;          // bytes of a result tile
 constexpr float kSplitMax = 3.38e38f;        // largest magnitude whose bf16 rounding is finite
+constexpr unsigned kSplitMin = 17u << 23;    // bits of 2^-110: smallest magnitude above zero that three planes hold exactly
 
 struct TileArgs {
     const int32_t* tile_seg;
@@ -87,12 +94,23 @@ __device__ __forceinline__ void mfma_split2(const bf16x8 (&a)[3], const bf16x8 (
     }
 }
 
+// Whether any of the operands seen is one that the split does not hold for.
+struct Range {
+    float mx = 0.f;
+    unsigned mn = 0xFFFFFFFFu;               // least 2 * bits(|x|) - 1: zero wraps round to the top
+    __device__ __forceinline__ void see(float x) {
+        mx = fmaxf(mx, fabsf(x));
+        mn = min(mn, (__float_as_uint(x) << 1) - 1u);
+    }
+    __device__ __forceinline__ bool outside() const { return mx > kSplitMax || mn < 2u * kSplitMin - 1u; }
+};
+
 // The loading threads' view of a unit: 256 threads, 32 lanes per row (16 bytes each), rows lr + 8 k.
 struct Loader {
     int c4, lr;
     __device__ __forceinline__ explicit Loader(int tid) : c4(tid & 31), lr(tid >> 5) {}
-    // row lr + 8 k into the planes at `t` (zeros when !ok); returns the largest magnitude
-    __device__ __forceinline__ float put(unsigned char* t, int k, float4 x, bool ok) const {
+    // row lr + 8 k into the planes at `t` (zeros when !ok)
+    __device__ __forceinline__ void put(unsigned char* t, int k, float4 x, bool ok, Range& seen) const {
         if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
         const int r = lr + 8 * k, at = r * 256 + (((c4 >> 1) ^ swz(r)) << 4) + (c4 & 1) * 8;
         unsigned p[3], q[3];
@@ -100,7 +118,7 @@ struct Loader {
         split2(x.z, x.w, q);
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2*>(t + pl * PLANE + at) = make_uint2(p[pl], q[pl]);
-        return fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w)));
+        seen.see(x.x); seen.see(x.y); seen.see(x.z); seen.see(x.w);
     }
 };
 
@@ -110,9 +128,10 @@ __device__ __forceinline__ float4* stage_at(unsigned char* st, int row, int piec
 }
 
 // One 32 x 32 block (rows of the unit x this wavefront's 32 columns `band`) of rows times W, to the result tile:
-// planes of the rows at `t`, of W in w; slow: from memory, with wp[k * wk] = W's operand and xp[k] = the row of lane m.
+// planes of the rows at `t`, of W in w; slow: from memory, with wp[k * WK] = W's operand and xp[k] = the row of lane m.
+template <int WK>
 __device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16x8 (&w)[3][8], unsigned char* st, int band, int m, int kh,
-                                              bool slow, const float* wp, size_t wk, const float* xp) {
+                                              bool slow, const float* wp, const float* xp) {
     v16f d, d1;                                            // two chains of matrix instructions
 #pragma unroll
     for (int v = 0; v < 16; ++v) d[v] = d1[v] = 0.f;
@@ -134,7 +153,19 @@ __device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16
 #pragma unroll
         for (int v = 0; v < 16; ++v) d[v] += d1[v];
     } else {
-        for (int k = 0; k < D; k += 2) d = mfma32(wp[(size_t)k * wk], xp[k], d);
+        // (the order of k is free: a half of the wavefront takes k = 64 kh + 0..63, 16 of them in flight)
+#pragma unroll 1
+        for (int k = 64 * kh; k < 64 * kh + 64; k += 16) {
+            float wv[16], xv[16];
+            load_cols(xp + k, xv);
+            if constexpr (WK == 1) load_cols(wp + k, wv);
+            else {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) wv[e] = wp[(size_t)(k + e) * WK];
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) d = mfma32(wv[e], xv[e], d);
+        }
     }
     // d[v] = result[row m][column band * 32 + 8 (v / 4) + 4 kh + v % 4]
 #pragma unroll
@@ -143,13 +174,14 @@ __device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16
 }
 
 // planes of eight values
-__device__ __forceinline__ void split8(const float (&x)[8], bf16x8& a, bf16x8& b, bf16x8& c, float& mx) {
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8& a, bf16x8& b, bf16x8& c, Range& seen) {
     rgnn_v4u pl[3];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         unsigned p[3];
         split2(x[2 * e], x[2 * e + 1], p);
-        mx = fmaxf(mx, fmaxf(fabsf(x[2 * e]), fabsf(x[2 * e + 1])));
+        seen.see(x[2 * e]);
+        seen.see(x[2 * e + 1]);
 #pragma unroll
         for (int q = 0; q < 3; ++q) pl[q][e] = p[q];
     }
@@ -234,10 +266,10 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
             {
                 const Unit n = units.get(min(u + 1, u1 - 1));
                 unsigned char* const t = lds + ((u + 1) & 1) * 3 * PLANE;
-                float mx = 0.f;
+                Range seen;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) mx = fmaxf(mx, ld.put(t, k, xr[p % DEPTH][k], ld.lr + 8 * k < n.rows));
-                if (mx > kSplitMax) bad[(u + 1) & 3] = 1;
+                for (int k = 0; k < 4; ++k) ld.put(t, k, xr[p % DEPTH][k], ld.lr + 8 * k < n.rows, seen);
+                if (seen.outside()) bad[(u + 1) & 3] = 1;
                 fetch_idx(p, u + 1 + 2 * DEPTH);
                 fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH));
             }
@@ -260,21 +292,21 @@ __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* ld
         const float* const wp = a.W + (size_t)n.seg * D * D + band * 32 + m;
         if (n.seg != cur_seg) {
             cur_seg = n.seg;
-            float mx = 0.f;
+            Range seen;
 #pragma unroll
             for (int s = 0; s < 8; ++s) {                  // lane (m, kh) keeps W[16 s + 8 kh + 0..7][band * 32 + m]
                 float x[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] = wp[(size_t)(16 * s + 8 * kh + e) * D];
-                split8(x, w[0][s], w[1][s], w[2][s], mx);
+                split8(x, w[0][s], w[1][s], w[2][s], seen);
             }
-            wbad = __any(mx > kSplitMax);
+            wbad = __any(seen.outside());
         }
         if (n.rows <= 0) continue;
         const bool slow = wbad || bad[u & 3];
         const int r = n.row0 + min(m, n.rows - 1);
-        multiply_rows(lds + (u & 1) * 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp + (size_t)kh * D, D,
-                      a.X + (size_t)(GATHER && slow ? a.gather[r] : r) * D + kh);
+        multiply_rows<D>(lds + (u & 1) * 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp,
+                         a.X + (size_t)(GATHER && slow ? a.gather[r] : r) * D);
     }
 }
 
@@ -393,7 +425,7 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
             {                                              // (unconditional loads: see the forward)
                 unsigned char* const t = lds + ((u + 1) & 1) * BUF;
                 if (RS && tid < 32) *reinterpret_cast<rgnn_v4f*>(vec_of + ((u + 1) & 3) * 32 + tid) = xv[p % DEPTH];
-                float mx = 0.f;
+                Range seen;
                 float4 au = make_float4(0.f, 0.f, 0.f, 0.f);     // the unit's share first: fewer roundings at the sum's magnitude
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -403,11 +435,11 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
                     float4 x = xr[p % DEPTH][k];
                     if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
                     if (RS) fma4(au, ok ? rs[p % DEPTH][k] : 0.f, x);
-                    mx = fmaxf(mx, ld.put(t, k, x, ok));
-                    mx = fmaxf(mx, ld.put(t + 3 * PLANE, k, yr[p % DEPTH][k], ok));
+                    ld.put(t, k, x, ok, seen);
+                    ld.put(t + 3 * PLANE, k, yr[p % DEPTH][k], ok, seen);
                 }
                 if (RS) fma4(av, 1.f, au);
-                if (mx > kSplitMax) bad[(u + 1) & 3] = 1;
+                if (seen.outside()) bad[(u + 1) & 3] = 1;
                 fetch_idx(p, u + 1 + 2 * DEPTH);
                 fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH), u + 1 + DEPTH);
             }
@@ -430,20 +462,20 @@ __device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* ld
         const float* const wp = a.W + (size_t)n.seg * D * D + (size_t)(band * 32 + m) * D;
         if (n.seg != cur_seg) {
             cur_seg = n.seg;
-            float mx = 0.f;
+            Range seen;
 #pragma unroll
             for (int s = 0; s < 8; ++s) {                  // lane (m, kh) keeps W[band * 32 + m][16 s + 8 kh + 0..7]
                 float x[8];
                 load_cols(wp + 16 * s + 8 * kh, x);
-                split8(x, w[0][s], w[1][s], w[2][s], mx);
+                split8(x, w[0][s], w[1][s], w[2][s], seen);
             }
-            wbad = __any(mx > kSplitMax);
+            wbad = __any(seen.outside());
         }
         if (n.rows <= 0) continue;
         const bool slow = wbad || bad[u & 3];
         const int r = n.row0 + min(m, n.rows - 1);
-        multiply_rows(lds + (u & 1) * BUF + 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp + kh, 1,
-                      a.dY + (size_t)(BOTH && slow ? a.gather[r] : r) * a.ldd + kh);
+        multiply_rows<1>(lds + (u & 1) * BUF + 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp,
+                         a.dY + (size_t)(BOTH && slow ? a.gather[r] : r) * a.ldd);
     }
 }
 
@@ -518,14 +550,24 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
                 }
             }
         } else {
-            const int f = 16 * band + (m & 15) + 64 * (m >> 4);
-            for (int k = 0; k < UNIT; k += 2) {
-                const int r = n.row0 + min(k + kh, n.rows - 1), g = GATHER ? a.gather[r] : r;
-                const bool ok = k + kh < n.rows;
-                const float x = ok ? a.X[(size_t)g * D + f] : 0.f;
-                const float* yp = a.dY + (size_t)(BOTH ? g : r) * a.ldd + (m & 15) + 64 * (m >> 4);
+            const int f = (m & 15) + 64 * (m >> 4);
+            const int gm = GATHER ? a.gather[n.row0 + min(m, n.rows - 1)] : 0;      // of row m of the unit
+#pragma unroll 1
+            for (int k = 0; k < UNIT; k += 8) {
+                float x[4], y[4][4];
 #pragma unroll
-                for (int b = 0; b < 4; ++b) acc[b] = mfma32(x, ok ? yp[16 * b] : 0.f, acc[b]);
+                for (int j = 0; j < 4; ++j) {
+                    const int q = min(k + 2 * j + kh, n.rows - 1), r = n.row0 + q, g = GATHER ? __shfl(gm, q) : r;
+                    x[j] = a.X[(size_t)g * D + 16 * band + f];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) y[j][b] = a.dY[(size_t)(BOTH ? g : r) * a.ldd + f + 16 * b];
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bool ok = k + 2 * j + kh < n.rows;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) acc[b] = mfma32(ok ? x[j] : 0.f, ok ? y[j][b] : 0.f, acc[b]);
+                }
             }
         }
     }

@@ -153,6 +153,85 @@ def test_relation_sizes_around_the_row_tiles(dtype, d, H, tied):
     _run(N, T, R, src.astype(np.int32), dst.astype(np.int32), rel.astype(np.int32), ntype, p, d, H, f"tiles-{dtype}-{tied}", dtype=dtype)
 
 
+def _wide_case(seed, tied):
+    """Width 128, four heads: 230 nodes of two types, five relations, 700 edges; with `tied` the sources of a relation are
+    of one type."""
+    rng = np.random.default_rng(seed)
+    N, T, R, E = 230, 2, 5, 700
+    ntype = (np.arange(N) >= 120).astype(np.int32)
+    rel = rng.integers(0, R, E).astype(np.int32)
+    src = rng.integers(0, N, E)
+    if tied:
+        src = np.where(rel % 2 == 0, src % 120, 120 + src % 110)
+    dst = rng.integers(0, N, E).astype(np.int32)
+    return N, T, R, src.astype(np.int32), dst, rel, ntype, synth.hgt_params(rng, N, T, R, 128, 4, with_mu=True)
+
+
+@pytest.mark.parametrize("tied", [True, False])
+@pytest.mark.parametrize("exponent", [-120, -116, -112, -109, -104])
+def test_operands_of_small_magnitude(exponent, tied):
+    """fp32: X scaled by 2^exponent and the node weights that it meets by 2^-exponent, so that every product is as without
+    the scales and the errors relative to the largest entry stay below those of fp32 sums of 128 terms, 128 * 2^-24."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, HgtLayer
+    N, T, R, src, dst, rel, ntype, p = _wide_case(800, tied)
+    p["X"] = p["X"] * np.float32(2.0 ** exponent)
+    for k in ("Wk", "Wq", "Wv"):
+        p[k] = p[k] * np.float32(2.0 ** -exponent)
+    g = Graph(N, R, src, dst, rel, ntype, T)
+    L = HgtLayer(g, 128, 4)
+    L.load(*[p[k] for k in NAMES], dOut=p["dOut"])
+    L.fwd(); L.bwd()
+    torch.cuda.synchronize()
+    wg = O.hgt_bwd(N, src, dst, rel, ntype, *[p[k] for k in NAMES], p["dOut"])
+    pairs = {"out": (L.out, O.hgt_fwd(N, src, dst, rel, ntype, *[p[k] for k in NAMES])), **{k: (v, wg[k]) for k, v in L.grads().items()}}
+    for k, (got, want) in pairs.items():
+        unit = np.abs(want).max()                       # `check` does not divide by less than 1e-30
+        check(got.cpu().numpy().astype(np.float64) / unit, want / unit, 128 * 2.0 ** -24, k)
+    g.close()
+
+
+@pytest.mark.parametrize("tied", [True, False])
+@pytest.mark.parametrize("value", [3.39e38, float("inf")])
+@pytest.mark.parametrize("where", ["X", "Wv"])
+def test_operands_beyond_the_range_of_bfloat16(where, value, tied):
+    """fp32 forward with one operand whose bfloat16 rounding is not finite (the largest fp32 values, infinity): its unit of rows,
+    or its weight's band, takes the fp32 matrix instructions.  For the finite value the operands that it meets are scaled by
+    2^-126, which keeps the products near 1.  Rows that it does not reach keep the accuracy of fp32 sums of 128 terms; those
+    that an infinity reaches are not finite."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, HgtLayer
+    N, T, R, src, dst, rel, ntype, p = _wide_case(801, tied)
+    u, c, finite = 130, 7, np.isfinite(value)
+    if where == "X":
+        if finite:
+            for k in ("Wk", "Wq", "Wv"):
+                p[k][:, c] *= np.float32(2.0 ** -126)
+        p["X"][u, c] = value
+        reached = (dst[:, None] == np.arange(N))[src == u].any(0) | (np.arange(N) == u)      # as a source or on its own as a destination
+        reached &= np.isin(np.arange(N), dst)
+    else:
+        if finite:
+            p["X"][:, c] *= np.float32(2.0 ** -126)
+        p["Wv"][0, c, 9] = value
+        reached = (dst[:, None] == np.arange(N))[ntype[src] == 0].any(0)
+    g = Graph(N, R, src, dst, rel, ntype, T)
+    L = HgtLayer(g, 128, 4)
+    L.load(*[p[k] for k in NAMES], dOut=p["dOut"])
+    L.fwd()
+    torch.cuda.synchronize()
+    got = L.out.cpu().numpy().astype(np.float64)
+    if not finite:
+        p[where][(u, c) if where == "X" else (0, c, 9)] = 0
+    want = O.hgt_fwd(N, src, dst, rel, ntype, *[p[k] for k in NAMES])
+    ok = np.full(N, True) if finite else ~reached
+    assert ok.sum() > 0 and reached.sum() > 0
+    check(got[ok], want[ok], 128 * 2.0 ** -24, "out")
+    if not finite:
+        assert (~np.isfinite(got[reached])).any(1).all()
+    g.close()
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None

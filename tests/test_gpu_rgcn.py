@@ -189,9 +189,10 @@ def test_relation_sizes_around_the_row_tiles(dtype, d, norm):
 @pytest.mark.parametrize("where", ["X", "W", "dOut"])
 def test_operands_beyond_the_range_of_bfloat16(where, value):
     """Width 128, fp32: an operand whose bfloat16 rounding is not finite (the largest fp32 values, infinity) takes the tile
-    through the fp32 matrix instructions.  One edge per destination, so every result row is one product; the other operand is
-    scaled by 2^-126 for the finite value, which keeps the products near 1.  Errors are fp32 roundings of 128-term
-    sums: at most 128 * 2^-24 of the sum of magnitudes."""
+    through the fp32 matrix instructions in the backward (RGCN's forward is on them throughout; HGT's forward has a test of
+    its own).  One edge per destination, so every result row is one product; the other operand is scaled by 2^-126 for the
+    finite value, which keeps the products near 1.  Errors are fp32 roundings of 128-term sums: at most 128 * 2^-24 of the
+    sum of magnitudes, or 128 roundings of subnormal sums."""
     import torch
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
     rng = np.random.default_rng(41)
@@ -227,7 +228,7 @@ def test_operands_beyond_the_range_of_bfloat16(where, value):
         bad = ~np.isfinite(want)
         assert (~np.isfinite(got[bad])).all(), name
         ok = ~over & np.isfinite(want)
-        assert (np.abs(got - want)[ok] <= 128 * 2.0 ** -24 * mag[name][ok] + 1e-37).all(), name
+        assert (np.abs(got - want)[ok] <= 128 * 2.0 ** -24 * mag[name][ok] + 128 * 2.0 ** -149).all(), name
     g.close()
 
 
@@ -259,4 +260,38 @@ def test_relu_mask_of_an_output_off_the_16_byte_grid(dtype, d, N):
     torch.cuda.synchronize()
     for k, v in L.grads().items():
         assert torch.equal(v, want[k]), k
+    g.close()
+
+
+@pytest.mark.parametrize("exponent", [-126, -118, -112, -109, -104])
+@pytest.mark.parametrize("where", ["dOut", "X and W"])
+def test_backward_operands_of_small_magnitude(where, exponent):
+    """Width 128, fp32: operands scaled by 2^exponent, where the low planes of a split into bfloat16 numbers would be subnormal
+    or lost, against operands scaled up by as much (2^120 at most).  One edge per destination and per pair, so a row of dX is one
+    product and dW a sum over a relation's rows: errors are fp32 roundings of sums of at most 128 terms, 128 * 2^-24 of the
+    sum of magnitudes."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    rng = np.random.default_rng(43)
+    N, R, d = 200, 3, 128
+    src, dst = rng.permutation(N).astype(np.int32), np.arange(N, dtype=np.int32)
+    rel = np.repeat(np.arange(R, dtype=np.int32), [70, 66, 64])
+    p = synth.rgcn_params(rng, N, R, d, d)
+    small, large = np.float32(2.0 ** exponent), np.float32(2.0 ** min(-exponent, 120))
+    for k in ("X", "W", "dOut"):
+        p[k] = p[k] * (small if (k == "dOut") == (where == "dOut") else large)
+    p["dOut"][3, 40:80] = 0                              # zeros are no small numbers
+    g = Graph(N, R, src, dst, rel)
+    L = RgcnLayer(g, d, "none")
+    L.load(p["X"], p["W"], None, p["dOut"])
+    L.bwd()
+    torch.cuda.synchronize()
+    X, W, dO = (p[k].astype(np.float64) for k in ("X", "W", "dOut"))
+    for r in range(R):
+        e = rel == r
+        x, y = X[src[e]], dO[dst[e]]
+        for name, got, want, mag in (("dX", L.dX[torch.as_tensor(src[e]).long()], y @ W[r].T, abs(y) @ abs(W[r]).T),
+                                     ("dW", L.dW[r], x.T @ y, abs(x).T @ abs(y))):
+            err = np.abs(got.cpu().numpy().astype(np.float64) - want)
+            assert (err <= 128 * 2.0 ** -24 * mag).all(), (name, r, (err / mag).max())
     g.close()
