@@ -295,3 +295,31 @@ def test_backward_operands_of_small_magnitude(where, exponent):
             err = np.abs(got.cpu().numpy().astype(np.float64) - want)
             assert (err <= 128 * 2.0 ** -24 * mag).all(), (name, r, (err / mag).max())
     g.close()
+
+
+def test_weight_gradient_of_long_chunks_bf16():
+    """A relation of 16 row tiles per workgroup (two workgroups per compute unit).  Every product is 1 but the first of dW[0][0],
+    2^28, where a unit in the last place is 32: that workgroup's share is off by at most half a unit per tile and per step of 16
+    rows within the first tile.  The other shares are multiples of 32 and add up without error."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    d, tiles = 128, 16
+    N = 2 * torch.cuda.get_device_properties(0).multi_processor_count * tiles * 64
+    src = dst = np.arange(N, dtype=np.int32)
+    g = Graph(N, 1, src, dst, np.zeros(N, np.int32))
+    L = RgcnLayer(g, d, "none", dtype="bf16")
+    ones = lambda *s: torch.ones(*s, device="cuda", dtype=torch.bfloat16)
+    L.X, L.W, L.W0, L.dOut = ones(N, d), ones(1, d, d), None, ones(N, d)
+    L.X[0, 0] = 2.0 ** 14
+    L.dOut[0, 0] = 2.0 ** 14
+    L.bwd()
+    torch.cuda.synchronize()
+    want = torch.full((d, d), float(N), device="cuda", dtype=torch.float64)
+    want[0, :] += 2.0 ** 14 - 1
+    want[:, 0] += 2.0 ** 14 - 1
+    want[0, 0] = 2.0 ** 28 + N - 1
+    err = (L.dW[0].double() - want).abs()
+    assert err[0, 0].item() <= 16 * (tiles + 4), err[0, 0].item()
+    err[0, 0] = 0
+    assert err.max().item() == 0
+    g.close()
