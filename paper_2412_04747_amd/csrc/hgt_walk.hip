@@ -15,7 +15,8 @@
 // re-read per edge between them) the same work took 7.95 ms.
 //
 // A row of D columns is read by D / V lanes with 16-byte loads (V = 4 fp32 or 8 bf16 columns); the LPH lanes of a
-// head reduce by DPP.  Arithmetic is fp32.
+// head reduce by DPP.  Arithmetic is fp32.  Weights come from expf: __expf is off by 2e-6 at a logit 60 below the maximum, expf by
+// a rounding (no difference in time on the graphs above and at 2M edges, 1 % of the layer at 300k edges in fp32).
 #include "rgnn_internal.h"
 #include "traversal.h"
 #include "device_utils.h"
@@ -80,13 +81,13 @@ struct FwdState {
             l[u] = u < n ? x : -INFINITY;
             mn = fmaxf(mn, l[u]);
         }
-        const float sc = __expf(m - mn);          // 0 in the first batch (m = -inf), 1 while the maximum stands
+        const float sc = expf(m - mn);          // 0 in the first batch (m = -inf), 1 while the maximum stands
         float t = 0.f;
 #pragma unroll
         for (int c = 0; c < V; ++c) acc[c] *= sc;
 #pragma unroll
         for (int u = 0; u < NE; ++u) {
-            const float p = __expf(l[u] - mn);
+            const float p = expf(l[u] - mn);
             float mv[V];
             widen_raw(mr[u], mv);
             t += p;
@@ -135,7 +136,7 @@ __device__ __forceinline__ void fwd_walk(const WalkArgs& a, int i) {
         float mn = f.m;
 #pragma unroll
         for (int o = LPR; o < 64; o <<= 1) mn = fmaxf(mn, __shfl_xor(mn, o));
-        const float sc = __expf(f.m - mn);
+        const float sc = expf(f.m - mn);
         f.m = mn;
         f.s *= sc;
 #pragma unroll
@@ -250,7 +251,7 @@ struct BwdBatch {
             widen_raw(mr[u], mv);
             const float l = group_sum<LPH>(dot_cols(q, kv));
             const float g = group_sum<LPH>(dot_cols(gz, mv));
-            const float att = __expf(l - ms.x) * inv;
+            const float att = expf(l - ms.x) * inv;
             const float dl = u < n ? att * (g - gbar) : 0.f;
             if (u < n) fma_cols(dq, dl, kv);
             if (t == u % LPH) mine[u / LPH] = make_float2(att, dl);
@@ -574,7 +575,7 @@ rgnn_status_t hgt_attend_fwd(const rgnn_graph* g, int D, int H, const void* KM, 
         KernelTimer kt(st, "hgt_attend_fwd");
         RGNN_HGT_WALK(hgt_attend_fwd, true);
     }
-    return combine_softmax(L, D, H, partial, part_ms, Z, rows_bf16, ms, "hgt_attend_fwd.combine", st);
+    return combine_softmax(L, D, H, partial, part_ms, Z, rows_bf16, ms, true, "hgt_attend_fwd.combine", st);
 }
 
 rgnn_status_t hgt_attend_bwd(const rgnn_graph* g, int D, int H, const void* KM, const void* Q, const void* Z, const float* ms,

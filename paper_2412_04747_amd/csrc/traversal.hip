@@ -665,13 +665,15 @@ inline bool few_long_segments(const ItemList& L) { return L.num_partials > 32 * 
 // unnormalised row; out[v] = sum_i exp(m_i - M) partial_i / S with M = max_i m_i, S = sum_i s_i exp(m_i - M).  One workgroup
 // per cut destination: group g of D/4 lanes takes the pieces g, g + G, ... four at a time (their loads independent) in the
 // running-maximum form, and the G group results are merged in group order through LDS.  H heads are equal column slices.
-template <int D, int H, typename TO>
+// FULL: expf (HGT, like its walks), otherwise __expf (RGAT, like its walks; expf adds 1 us at 300k nodes).
+template <int D, int H, typename TO, bool FULL>
 __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __restrict__ split_row,
                                                               const int32_t* __restrict__ split_ptr,
                                                               const float* __restrict__ partial,
                                                               const float2* __restrict__ part_ms, TO* __restrict__ out,
                                                               float2* __restrict__ ms) {
     constexpr int LPR = D / 4, G = 256 / LPR, LPH = LPR / H;
+    auto ex = [](float x) { return FULL ? expf(x) : __expf(x); };
     __shared__ float4 red[256];
     __shared__ float2 redms[G][H];
     const int s = blockIdx.x, g = threadIdx.x / LPR, c = threadIdx.x % LPR, head = c / LPH;
@@ -691,12 +693,12 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (p + u * G < p1) mn = fmaxf(mn, t[u].x);
-        const float sc = __expf(M - mn);          // 0 for the first four pieces
+        const float sc = ex(M - mn);          // 0 for the first four pieces
         S *= sc;
         acc.x *= sc; acc.y *= sc; acc.z *= sc; acc.w *= sc;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const float w = p + u * G < p1 ? __expf(t[u].x - mn) : 0.f;
+            const float w = p + u * G < p1 ? ex(t[u].x - mn) : 0.f;
             S += w * t[u].y;
             fma4(acc, w, r[u]);
         }
@@ -712,7 +714,7 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
         float t[4] = {0.f, 0.f, 0.f, 0.f};
         for (int k = 0; k < n; ++k) {
             const float2 q = redms[k][head];
-            const float w = __expf(q.x - M);
+            const float w = ex(q.x - M);
             const float4 r = red[k * LPR + c];
             S += w * q.y;
             t[0] += w * r.x; t[1] += w * r.y; t[2] += w * r.z; t[3] += w * r.w;
@@ -1081,19 +1083,18 @@ rgnn_status_t edge_softmax(const rgnn_graph* g, const float* s_src, const float*
     } while (0)
 
 rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
-                              int out_bf16, float* ms, const char* label, hipStream_t st) {
+                              int out_bf16, float* ms, bool full_exp, const char* label, hipStream_t st) {
     if (L.num_split == 0) return RGNN_OK;
     KernelTimer kt(st, label);
+#define RGNN_COMBINE(HH, TO_, FULL_)                                                                                  \
+    RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_softmax_kernel<DD, (DD / (HH) >= 16 ? (HH) : 1), TO_, FULL_>), dim3(L.num_split), dim3(256), 0, st, \
+                                          L.split_row, L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), \
+                                          static_cast<TO_*>(out), reinterpret_cast<float2*>(ms)))
 #define RGNN_COMBINE_H(HH)                                                                                            \
     do {                                                                                                              \
-        if (out_bf16)                                                                                                 \
-            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_softmax_kernel<DD, (DD / (HH) >= 16 ? (HH) : 1), bf16_t>), dim3(L.num_split), dim3(256), 0, st, \
-                                                  L.split_row, L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), \
-                                                  static_cast<bf16_t*>(out), reinterpret_cast<float2*>(ms)));          \
-        else                                                                                                          \
-            RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_softmax_kernel<DD, (DD / (HH) >= 16 ? (HH) : 1), float>), dim3(L.num_split), dim3(256), 0, st, \
-                                                  L.split_row, L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), \
-                                                  static_cast<float*>(out), reinterpret_cast<float2*>(ms)));           \
+        if (out_bf16) RGNN_COMBINE(HH, bf16_t, true);                                                                 \
+        else if (full_exp) RGNN_COMBINE(HH, float, true);                                                             \
+        else RGNN_COMBINE(HH, float, false);                                                                          \
     } while (0)
     if (H < 1 || D / H < 16) { if (H != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "combine_softmax: %d heads at width %d not built", H, D); }
     if (H == 1) RGNN_COMBINE_H(1);
@@ -1102,6 +1103,7 @@ rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* part
     else if (H == 8) RGNN_COMBINE_H(8);
     else RGNN_FAIL(RGNN_EUNSUPPORTED, "combine_softmax: %d heads not built (1, 2, 4, 8)", H);
 #undef RGNN_COMBINE_H
+#undef RGNN_COMBINE
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }

@@ -232,6 +232,39 @@ def test_operands_beyond_the_range_of_bfloat16(where, value, tied):
     g.close()
 
 
+@pytest.mark.parametrize("far", [-60.3, -20.7])
+def test_small_attention_weights(far):
+    """fp32: an edge far below the maximum, whose weight shows in a column that only its message has.  Identity weights make
+    the logit the product of the first columns (mu undoes the scale), so the oracle's value is a few exponentials; the
+    result is off by the exponential's last place, and one rounding per product, quotient and sum on the way: 16 * 2^-24.
+    Destinations of one batch, of a wavefront's batches, and cut ones whose far edges share a piece with the near ones or not."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, HgtLayer
+    d, H = 64, 4
+    lists = ["ab", "aaaab", "a" * 29 + "bb", "a" * 64 + "b" * 6, "ab" * 20 + "a" * 60]
+    N, big = 2 + len(lists), np.float32(2.0 ** 80)
+    src = np.array([0 if c == "a" else 1 for w in lists for c in w], np.int32)
+    dst = np.repeat(np.arange(2, N, dtype=np.int32), [len(w) for w in lists])
+    X = np.zeros((N, d), np.float32)
+    X[1, 0], X[1, 1], X[2:, 0] = far, big, 1
+    I = np.eye(d, dtype=np.float32)[None]
+    i = np.tile(np.eye(d // H, dtype=np.float32), (1, H, 1, 1))
+    dOut = np.zeros((N, d), np.float32)
+    dOut[2:, 1] = 1
+    g = Graph(N, 1, src, dst, np.zeros(len(src), np.int32))
+    L = HgtLayer(g, d, H)
+    L.load(X, I, I, I, I, i, i, np.full((1, H), np.sqrt(d // H), np.float32), dOut)
+    L.fwd(); L.bwd()
+    torch.cuda.synchronize()
+    w = np.exp(np.float64(np.float32(far)))
+    att = np.array([w * k.count("b") / (k.count("a") + w * k.count("b")) for k in lists])
+    out = L.out.cpu().numpy().astype(np.float64)[2:, 1]
+    assert (np.abs(out - att * big) <= 16 * 2.0 ** -24 * att * big).all(), out / (att * big) - 1
+    got = float(L.dX[1, 1])                                # the sum of the far edges' weights
+    assert abs(got - att.sum()) <= 16 * 2.0 ** -24 * att.sum(), got / att.sum() - 1
+    g.close()
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None
