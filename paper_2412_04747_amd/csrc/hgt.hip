@@ -103,7 +103,9 @@ __global__ __launch_bounds__(256) void hgt_fold_kernel(int R, Halves<T> w, Pair2
 //                             dmu[r][h] = sum(G .* W[r][h]) / sqrt(dh) (attention half)
 //   (t, h, 32 rows k), the others:  dWnode[t][k][h dh + j] = sum over the relations r with t(r) = t, ascending, of
 //                                   c(r, h) sum_n dWf[r][k][h dh + n] W[r][h][j][n]
-// The operands of a step (32 rows of both) are staged in LDS; a thread forms DH * DH / 256 (or DH * 32 / 256) results.
+// The operands of a step (32 rows of both) are staged in LDS; a thread forms DH * DH / 256 (or DH * 32 / 256) results, each in
+// four chains over k mod 4, or in steps of four n (as one chain dWmsg at 300k edges, width 64, was
+// 2.9e-7 off, 2.6e-7 so).
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void hgt_fold_bwd_kernel(int R, Halves<T> w, Pair2 dWf_, Pair2 dW, Pair2 dWnode, float* __restrict__ dmu) {
     __shared__ float A[32][DH + 1], B[DH > 32 ? DH : 32][DH + 1], red[4];
@@ -113,9 +115,9 @@ __global__ __launch_bounds__(256) void hgt_fold_bwd_kernel(int R, Halves<T> w, P
         constexpr int NO = DH * DH / 256;
         const int r = blockIdx.x / H, h = blockIdx.x % H;
         const size_t wn = (size_t)w.rel_type[r] * d * d + h * DH, g0 = (size_t)r * d * d + h * DH;
-        float acc[NO];
+        float part[NO][4], acc[NO];
 #pragma unroll
-        for (int q = 0; q < NO; ++q) acc[q] = 0.f;
+        for (int q = 0; q < NO; ++q) part[q][0] = part[q][1] = part[q][2] = part[q][3] = 0.f;
         for (int k0 = 0; k0 < d; k0 += 32) {
             __syncthreads();
             for (int i = tid; i < 32 * DH; i += 256) {
@@ -127,8 +129,10 @@ __global__ __launch_bounds__(256) void hgt_fold_bwd_kernel(int R, Halves<T> w, P
 #pragma unroll 8
             for (int k = 0; k < 32; ++k)
 #pragma unroll
-                for (int q = 0; q < NO; ++q) acc[q] += A[k][(tid + 256 * q) / DH] * B[k][tid % DH];
+                for (int q = 0; q < NO; ++q) part[q][k & 3] += A[k][(tid + 256 * q) / DH] * B[k][tid % DH];
         }
+#pragma unroll
+        for (int q = 0; q < NO; ++q) acc[q] = (part[q][0] + part[q][1]) + (part[q][2] + part[q][3]);
         const float c = w.scale(x, r, h);
         float s = 0.f;
 #pragma unroll
@@ -160,10 +164,14 @@ __global__ __launch_bounds__(256) void hgt_fold_bwd_kernel(int R, Halves<T> w, P
         float p[NO];                              // one relation's sum first, then the relations in order
 #pragma unroll
         for (int q = 0; q < NO; ++q) p[q] = 0.f;
-#pragma unroll 8
-        for (int n = 0; n < DH; ++n)
+#pragma unroll 4
+        for (int n = 0; n < DH; n += 4)
 #pragma unroll
-            for (int q = 0; q < NO; ++q) p[q] += A[(tid + 256 * q) / DH][n] * B[tid % DH][n];
+            for (int q = 0; q < NO; ++q) {
+                const float* const g = A[(tid + 256 * q) / DH] + n;
+                const float* const wr = B[tid % DH] + n;
+                p[q] += (g[0] * wr[0] + g[1] * wr[1]) + (g[2] * wr[2] + g[3] * wr[3]);
+            }
 #pragma unroll
         for (int q = 0; q < NO; ++q) acc[q] += p[q];
     }

@@ -265,6 +265,27 @@ def test_small_attention_weights(far):
     g.close()
 
 
+@pytest.mark.parametrize("d,H", [(32, 1), (64, 4), (128, 2)])
+def test_sums_of_the_unfolding(d, H):
+    """fp32: dWmsg and dWv from the gradient of the folded weight, here all ones (one edge, X and dOut of ones), in sums of a
+    2^24, where a unit in the last place is 2, and ones: four chains, or steps of four, lose at most one per addition."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, HgtLayer
+    dh = d // H
+    g = Graph(2, 1, np.zeros(1, np.int32), np.ones(1, np.int32), np.zeros(1, np.int32))
+    L = HgtLayer(g, d, H)
+    I = np.eye(d, dtype=np.float32)[None]
+    Wv, Wmsg = np.ones((1, d, d), np.float32), np.ones((1, H, dh, dh), np.float32)
+    Wv[0, 0] = 2.0 ** 24
+    Wmsg[0, :, :, 0] = 2.0 ** 24
+    L.load(np.ones((2, d), np.float32), np.zeros_like(I), I, Wv, I, np.ones_like(Wmsg), Wmsg, None, np.ones((2, d), np.float32))
+    L.fwd(); L.bwd()
+    torch.cuda.synchronize()
+    assert (L.dWmsg.double() - (2.0 ** 24 + d - 1)).abs().max().item() <= d // 4 + 2
+    assert (L.dWv.double() - (2.0 ** 24 + dh - 1)).abs().max().item() <= dh // 4 + 2
+    g.close()
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None
