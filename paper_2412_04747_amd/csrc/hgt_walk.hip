@@ -41,6 +41,27 @@ __device__ __forceinline__ void widen_raw(rgnn_v4u t, float (&v)[4]) {
 template <typename T>
 __device__ __forceinline__ rgnn_v4u load_raw(const T* p) { return *reinterpret_cast<const rgnn_v4u*>(p); }
 
+// acc += sum of c[u] * row u over a batch.  fp32 rows: the batch is summed in two chains of its own first, one rounding at
+// acc's magnitude per batch; bf16 rows are rounded to 8 bits in the end, and one chain does.
+template <typename T, int V, int NE>
+__device__ __forceinline__ void add_rows(float (&acc)[V], const float (&c)[NE], const rgnn_v4u (&rows)[NE]) {
+    float t0[V], t1[V];
+    zero_cols(t0);
+    zero_cols(t1);
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+        float v[V];
+        widen_raw(rows[u], v);
+        if (sizeof(T) == 2) fma_cols(acc, c[u], v);
+        else if (2 * u < NE) fma_cols(t0, c[u], v);
+        else fma_cols(t1, c[u], v);
+    }
+    if (sizeof(T) == 4) {
+#pragma unroll
+        for (int q = 0; q < V; ++q) acc[q] += t0[q] + t1[q];
+    }
+}
+
 struct WalkArgs {
     Items it;
     int wide_n, wide_blocks;                              // items [0, wide_n): a wavefront each
@@ -85,14 +106,13 @@ struct FwdState {
         float t = 0.f;
 #pragma unroll
         for (int c = 0; c < V; ++c) acc[c] *= sc;
+        float p[NE];
 #pragma unroll
         for (int u = 0; u < NE; ++u) {
-            const float p = expf(l[u] - mn);
-            float mv[V];
-            widen_raw(mr[u], mv);
-            t += p;
-            fma_cols(acc, p, mv);
+            p[u] = expf(l[u] - mn);
+            t += p[u];
         }
+        add_rows<T>(acc, p, mr);
         s = s * sc + t;
         m = mn;
     }
@@ -238,12 +258,13 @@ __global__ __launch_bounds__(256) void hgt_attend_fwd_few_kernel(WalkArgs a) {
 
 // One batch of NE edges (n of them exist): dq += dl Ka; lane t of a head's LPH lanes keeps (att, dl) of the edges t, t + LPH, ...
 // of the batch in `mine`.
-template <int V, int LPH, int NE>
+template <typename T, int V, int LPH, int NE>
 struct BwdBatch {
     static constexpr int NS = (NE + LPH - 1) / LPH;
     float2 mine[NS];
     __device__ __forceinline__ void form(const float (&q)[V], const float (&gz)[V], float gbar, float2 ms, float inv,
                                          const rgnn_v4u (&k)[NE], const rgnn_v4u (&mr)[NE], int n, int t, float (&dq)[V]) {
+        float dl[NE];
 #pragma unroll
         for (int u = 0; u < NE; ++u) {
             float kv[V], mv[V];
@@ -252,10 +273,10 @@ struct BwdBatch {
             const float l = group_sum<LPH>(dot_cols(q, kv));
             const float g = group_sum<LPH>(dot_cols(gz, mv));
             const float att = expf(l - ms.x) * inv;
-            const float dl = u < n ? att * (g - gbar) : 0.f;
-            if (u < n) fma_cols(dq, dl, kv);
-            if (t == u % LPH) mine[u / LPH] = make_float2(att, dl);
+            dl[u] = u < n ? att * (g - gbar) : 0.f;
+            if (t == u % LPH) mine[u / LPH] = make_float2(att, dl[u]);
         }
+        add_rows<T>(dq, dl, k);
     }
     // adl: the entry of the batch's first edge and this lane's head; the lanes of a group fill whole lines
     __device__ __forceinline__ void store(float2* __restrict__ adl, int n, int H, int t) const {
@@ -287,7 +308,7 @@ __device__ __forceinline__ void bwd_walk(const WalkArgs& a, int i) {
         const float gbar = group_sum<LPH>(dot_cols(gz, zz)), inv = 1.f / ms.y;
         // A batch's (att, dl) leave after the next batch's rows have been asked for: loads and stores complete in issue
         // order, so a store issued before the loads would have to be acknowledged before the rows can be used.
-        BwdBatch<V, LPH, 4> batch;
+        BwdBatch<T, V, LPH, 4> batch;
         float2* adl = a.adl + (size_t)b * H + head;
         int j = j0;
         for (; j < e; j += 4 * NG) {
@@ -376,7 +397,7 @@ __device__ __forceinline__ void bwd_few(const WalkArgs& a, int blk, int first, i
         widen_raw(zz[x], zv);
         zero_cols(dq);
         const float gbar = group_sum<LPH>(dot_cols(gv, zv));
-        BwdBatch<V, LPH, NE> batch;
+        BwdBatch<T, V, LPH, NE> batch;
         batch.form(qv, gv, gbar, ms[x], 1.f / ms[x].y, k[x], m[x], e[x] - b[x], t, dq);
         batch.store(a.adl + (size_t)b[x] * H + head, e[x] - b[x], H, t);
         store_cols(static_cast<T*>(a.dQ) + (size_t)row[x] * D + cv * V, dq);
@@ -419,22 +440,17 @@ __global__ __launch_bounds__(256) void hgt_pair_bwd_kernel(WalkArgs a) {
     if (b < e) fetch(b);
     for (int j = b; j < e; j += 4) {
         rgnn_v4u q[4], z[4];
-        float2 cc[4];
+        float att[4], dl[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             q[u] = load_raw(Q + (size_t)row[u] * D);
             z[u] = load_raw(dZ + (size_t)row[u] * D);
-            cc[u] = c[u];
+            att[u] = c[u].x;
+            dl[u] = c[u].y;
         }
         if (j + 4 < e) fetch(j + 4);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float qv[V], zv[V];
-            widen_raw(q[u], qv);
-            widen_raw(z[u], zv);
-            fma_cols(dk, cc[u].y, qv);
-            fma_cols(dm, cc[u].x, zv);
-        }
+        add_rows<T>(dk, dl, q);
+        add_rows<T>(dm, att, z);
     }
     if (slot < 0) {
         T* o = static_cast<T*>(a.dKM) + (size_t)a.it.row[i] * 2 * D + cv * V;
@@ -487,15 +503,15 @@ __device__ __forceinline__ void pair_few(const WalkArgs& a, int blk, int first, 
         float dk[V], dm[V];
         zero_cols(dk);
         zero_cols(dm);
+        float att[NE], dl[NE];
 #pragma unroll
         for (int u = 0; u < NE; ++u) {
-            float qv[V], zv[V];
-            widen_raw(q[x][u], qv);
-            widen_raw(z[x][u], zv);
             const bool ok = b[x] + u < e[x];
-            fma_cols(dk, ok ? c[x][u].y : 0.f, qv);
-            fma_cols(dm, ok ? c[x][u].x : 0.f, zv);
+            att[u] = ok ? c[x][u].x : 0.f;
+            dl[u] = ok ? c[x][u].y : 0.f;
         }
+        add_rows<T>(dk, dl, q[x]);
+        add_rows<T>(dm, att, z[x]);
         T* o = static_cast<T*>(a.dKM) + (size_t)orow[x] * 2 * D + cv * V;
         store_cols(o, dk);
         store_cols(o + D, dm);

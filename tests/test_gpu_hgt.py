@@ -286,6 +286,33 @@ def test_sums_of_the_unfolding(d, H):
     g.close()
 
 
+@pytest.mark.parametrize("d,H", [(32, 1), (64, 4), (128, 2)])
+def test_sums_of_rows_in_batches(d, H):
+    """fp32: a destination of 24 edges (equal logits) and a pair of 24 edges (one to each of 24 destinations) sum a 2^24, where a
+    unit in the last place is 2, and 23 ones, in batches of four: the first batch loses at most one, the others none.  The
+    destination's sum is then divided by 24: two more roundings."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, HgtLayer
+    n = 24
+    N = 2 * n + 2                                         # sources 0..n-1, their destination n, pair's source n + 1, its destinations
+    src = np.concatenate([np.arange(n), np.full(n, n + 1)]).astype(np.int32)
+    dst = np.concatenate([np.full(n, n), np.arange(n + 2, N)]).astype(np.int32)
+    X, dOut = np.zeros((N, d), np.float32), np.zeros((N, d), np.float32)
+    X[:n, 0], dOut[n + 2:, 0] = 1, 1
+    X[0, 0] = dOut[n + 2, 0] = 2.0 ** 24
+    I = np.eye(d, dtype=np.float32)[None]
+    i = np.tile(np.eye(d // H, dtype=np.float32), (1, H, 1, 1))
+    g = Graph(N, 1, src, dst, np.zeros(2 * n, np.int32))
+    L = HgtLayer(g, d, H)
+    L.load(X, np.zeros_like(I), I, I, I, i, i, None, dOut)
+    L.fwd(); L.bwd()
+    torch.cuda.synchronize()
+    want = (2.0 ** 24 + n - 1) / n
+    assert abs(float(L.out[n, 0]) - want) <= 1.0 / n + 2 * 2.0 ** -24 * want, float(L.out[n, 0]) - want
+    assert abs(float(L.dX[n + 1, 0].double()) - (2.0 ** 24 + n - 1)) <= 1, float(L.dX[n + 1, 0])
+    g.close()
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None
