@@ -698,7 +698,8 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
         acc.x *= sc; acc.y *= sc; acc.z *= sc; acc.w *= sc;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const float w = p + u * G < p1 ? ex(t[u].x - mn) : 0.f;
+            if (p + u * G >= p1) break;           // (not a zero weight: the repeated row may be infinite, and 0 inf is NaN)
+            const float w = ex(t[u].x - mn);
             S += w * t[u].y;
             fma4(acc, w, r[u]);
         }

@@ -265,6 +265,29 @@ def test_one_segment_of_many_pieces(d, H, n_hub):
         _run_heads(N, R, src, dst, rel, p, d, H, f"pieces-d{d}-H{H}-{n_hub}")
 
 
+@pytest.mark.parametrize("H", [1, 4])
+def test_overflowing_piece_of_a_cut_destination(H):
+    """A destination of five pieces whose last one sums messages of 3e38 to infinity: infinity it stays (not NaN), in that
+    column alone.  With w_s = w_t = 0 the other columns are the mean of their messages."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    d, n = 64, 150
+    src, dst = np.zeros(n, np.int32), np.full(n, 3, np.int32)
+    src[-8:] = 1
+    X, W = np.zeros((4, d), np.float32), np.eye(d, dtype=np.float32)[None]
+    X[0, 1] = X[1, 1] = 1
+    X[1, 0] = 3e38
+    w = np.zeros((1, d), np.float32)
+    g = Graph(4, 1, src, dst, np.zeros(n, np.int32))
+    L = RgatLayer(g, d, heads=H)
+    L.load(X, W, w, w)
+    L.fwd()
+    torch.cuda.synchronize()
+    got = L.out.cpu().numpy()[3]
+    assert got[0] == np.inf and abs(got[1] - 1) <= 8 * 2.0 ** -24 and (got[2:] == 0).all(), got[:4]
+    g.close()
+
+
 def test_hub_empty_relation_isolated_nodes():
     rng, src, dst, rel, _ = synth.tiny(70, N=300, R=5, E=4000)
     rel[rel == 4] = 0       # relation 4 has no edge
