@@ -76,6 +76,7 @@ struct WalkArgs {
     float2* ms;              // [N][H]
     float* partial;
     float2* part_ms;
+    int piece_len;           // longest piece of a cut destination
     const void* dZ;          // [N][D]
     void* dQ;                // [N][D]
     float2* adl;             // [E][H] (att, dl)
@@ -87,10 +88,14 @@ struct WalkArgs {
 
 // ------------------------------------------------------------------------------------------------ forward
 
-// One batch of NE edges of an item: logits, running maximum, weighted sum.
+// One batch of NE edges of an item: logits, running maximum, weighted sum.  The weights are not normalised yet, and a sum of n
+// messages may exceed fp32 where their mean does not: acc carries the factor c = pow2_share(n), exact like its removal.
 template <int V, int LPH, int NE>
 struct FwdState {
-    float m = -INFINITY, s = 0.f, acc[V];
+    float m = -INFINITY, s = 0.f, c, acc[V];
+    __device__ __forceinline__ explicit FwdState(float share) : c(share) { zero_cols(acc); }
+    // the factor that makes acc the mean
+    __device__ __forceinline__ float inverse() const { return 1.f / s * (1.f / c); }
     template <typename T>
     __device__ __forceinline__ void batch(const float (&q)[V], const rgnn_v4u (&k)[NE], const rgnn_v4u (&mr)[NE], int n) {
         float l[NE], mn = m;
@@ -111,6 +116,7 @@ struct FwdState {
         for (int u = 0; u < NE; ++u) {
             p[u] = expf(l[u] - mn);
             t += p[u];
+            p[u] *= c;
         }
         add_rows<T>(acc, p, mr);
         s = s * sc + t;
@@ -130,8 +136,7 @@ __device__ __forceinline__ void fwd_walk(const WalkArgs& a, int i) {
     const T* __restrict__ KM = static_cast<const T*>(a.KM) + cv * V;
     const int b = a.it.beg[i], e = a.it.end[i], slot = a.it.slot[i];
     const size_t v = (size_t)a.it.row[i];
-    FwdState<V, LPH, 4> f;
-    zero_cols(f.acc);
+    FwdState<V, LPH, 4> f(slot < 0 ? pow2_share(e - b) : pow2_share(a.piece_len));
     if (b < e) {
         const int j0 = b + 4 * sub;
         int pr[4];
@@ -170,7 +175,7 @@ __device__ __forceinline__ void fwd_walk(const WalkArgs& a, int i) {
         if (sub != 0) return;
     }
     if (slot < 0) {
-        const float inv = b < e ? 1.f / f.s : 0.f;        // a destination without edges gets the zero row
+        const float inv = b < e ? f.inverse() : 0.f;      // a destination without edges gets the zero row
 #pragma unroll
         for (int c = 0; c < V; ++c) f.acc[c] *= inv;
         store_cols(static_cast<T*>(a.Z) + v * D + cv * V, f.acc);
@@ -237,10 +242,9 @@ __device__ __forceinline__ void fwd_few(const WalkArgs& a, int blk, int first, i
         if (i0 + x >= n) break;
         float qv[V];
         widen_raw(q[x], qv);
-        FwdState<V, LPH, NE> f;
-        zero_cols(f.acc);
+        FwdState<V, LPH, NE> f(pow2_share(e[x] - b[x]));
         f.template batch<T>(qv, k[x], m[x], e[x] - b[x]);
-        const float inv = 1.f / f.s;
+        const float inv = f.inverse();
 #pragma unroll
         for (int c = 0; c < V; ++c) f.acc[c] *= inv;
         store_cols(static_cast<T*>(a.Z) + (size_t)row[x] * D + cv * V, f.acc);
@@ -586,12 +590,12 @@ rgnn_status_t hgt_attend_fwd(const rgnn_graph* g, int D, int H, const void* KM, 
     if (L.num_items == 0) return RGNN_OK;
     WalkArgs a{};
     a.in_pair = g->idx[RGNN_IDX_IN_PAIR]; a.KM = KM; a.Q = Q; a.Z = Z; a.ms = reinterpret_cast<float2*>(ms);
-    a.partial = partial; a.part_ms = reinterpret_cast<float2*>(part_ms);
+    a.partial = partial; a.part_ms = reinterpret_cast<float2*>(part_ms); a.piece_len = item_cut(g->E);
     {
         KernelTimer kt(st, "hgt_attend_fwd");
         RGNN_HGT_WALK(hgt_attend_fwd, true);
     }
-    return combine_softmax(L, D, H, partial, part_ms, Z, rows_bf16, ms, true, "hgt_attend_fwd.combine", st);
+    return combine_softmax(L, D, H, partial, part_ms, Z, rows_bf16, ms, true, a.piece_len, "hgt_attend_fwd.combine", st);
 }
 
 rgnn_status_t hgt_attend_bwd(const rgnn_graph* g, int D, int H, const void* KM, const void* Q, const void* Z, const float* ms,

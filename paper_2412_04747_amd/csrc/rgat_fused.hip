@@ -432,7 +432,7 @@ rgnn_status_t rgat_aggregate_fwd(const rgnn_graph* g, int D, int H, const float*
         if (ldsw) RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, true>, g, lds, groups, DD / 4, a, st)));
         else RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, false>, g, 0, groups, DD / 4, a, st)));
     }
-    return combine_softmax(L, D, H, partial, part_ms, out, 0, ms, false, "aggregate_fwd.combine", st);
+    return combine_softmax(L, D, H, partial, part_ms, out, 0, ms, false, 1, "aggregate_fwd.combine", st);
 }
 
 rgnn_status_t rgat_edge_dot_bwd(const rgnn_graph* g, int D, int H, const float* Hs, const float* w_s, const float* s_dst,

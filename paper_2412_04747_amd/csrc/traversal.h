@@ -45,11 +45,12 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
                          int sum2_stride = 1);
 // rows of the cut segments of a list from their pieces: plain sums (widths 32 .. 256), and sums whose pieces carry their
 // own softmax statistics (max, sum) per head.  copies: that many independent sets of partial rows (one after the other)
-// and of output rows (out_copy elements apart).  full_exp: expf instead of __expf (bf16 rows: always).
+// and of output rows (out_copy elements apart).  full_exp: expf instead of __expf (bf16 rows: always).  The partial rows carry the factor
+// pow2_share(piece_len) (device_utils.h).
 rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, void* out, int out_bf16, const char* label,
                                hipStream_t st, const Rank1* r1 = nullptr, int heads = 1, int copies = 1, size_t out_copy = 0);
 rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
-                              int out_bf16, float* ms, bool full_exp, const char* label, hipStream_t st);
+                              int out_bf16, float* ms, bool full_exp, int piece_len, const char* label, hipStream_t st);
 // H weighted sums of the same gathered rows in one walk (coef [entries][H]); out [H][out_rows][D]
 rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, const int32_t* via, const int32_t* rowidx,
                                 int row_by_k, const float* coef, const float* src, float* out, float* partial,

@@ -665,19 +665,21 @@ inline bool few_long_segments(const ItemList& L) { return L.num_partials > 32 * 
 // unnormalised row; out[v] = sum_i exp(m_i - M) partial_i / S with M = max_i m_i, S = sum_i s_i exp(m_i - M).  One workgroup
 // per cut destination: group g of D/4 lanes takes the pieces g, g + G, ... four at a time (their loads independent) in the
 // running-maximum form, and the G group results are merged in group order through LDS.  H heads are equal column slices.
+// The rows carry pow2_share(piece_len) and get pow2_share(number of pieces) here, so that a sum whose mean fits in fp32 does too.
 // FULL: expf (HGT, like its walks), otherwise __expf (RGAT, like its walks; expf adds 1 us at 300k nodes).
 template <int D, int H, typename TO, bool FULL>
 __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __restrict__ split_row,
                                                               const int32_t* __restrict__ split_ptr,
                                                               const float* __restrict__ partial,
                                                               const float2* __restrict__ part_ms, TO* __restrict__ out,
-                                                              float2* __restrict__ ms) {
+                                                              float2* __restrict__ ms, int piece_len) {
     constexpr int LPR = D / 4, G = 256 / LPR, LPH = LPR / H;
     auto ex = [](float x) { return FULL ? expf(x) : __expf(x); };
     __shared__ float4 red[256];
     __shared__ float2 redms[G][H];
     const int s = blockIdx.x, g = threadIdx.x / LPR, c = threadIdx.x % LPR, head = c / LPH;
     const int p0 = split_ptr[s], p1 = split_ptr[s + 1];
+    const float share = pow2_share(p1 - p0);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float M = -INFINITY, S = 0.f;
     for (int p = p0 + g; p < p1; p += 4 * G) {
@@ -691,17 +693,21 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
         }
         float mn = M;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (p + u * G < p1) mn = fmaxf(mn, t[u].x);
+        for (int u = 0; u < 4; ++u) {
+            if (p + u * G >= p1) {                // the repeated piece counts as nothing (it may be infinite: no weight 0)
+                t[u] = make_float2(-INFINITY, 0.f);
+                r[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+            mn = fmaxf(mn, t[u].x);
+        }
         const float sc = ex(M - mn);          // 0 for the first four pieces
         S *= sc;
         acc.x *= sc; acc.y *= sc; acc.z *= sc; acc.w *= sc;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (p + u * G >= p1) break;           // (not a zero weight: the repeated row may be infinite, and 0 inf is NaN)
             const float w = ex(t[u].x - mn);
             S += w * t[u].y;
-            fma4(acc, w, r[u]);
+            fma4(acc, w * share, r[u]);
         }
         M = mn;
     }
@@ -720,7 +726,7 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
             S += w * q.y;
             t[0] += w * r.x; t[1] += w * r.y; t[2] += w * r.z; t[3] += w * r.w;
         }
-        const float inv = 1.f / S;
+        const float inv = 1.f / S * (1.f / share) * (1.f / pow2_share(piece_len));
         const size_t v = (size_t)split_row[s];
 #pragma unroll
         for (int q = 0; q < 4; ++q) t[q] *= inv;
@@ -1084,13 +1090,13 @@ rgnn_status_t edge_softmax(const rgnn_graph* g, const float* s_src, const float*
     } while (0)
 
 rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
-                              int out_bf16, float* ms, bool full_exp, const char* label, hipStream_t st) {
+                              int out_bf16, float* ms, bool full_exp, int piece_len, const char* label, hipStream_t st) {
     if (L.num_split == 0) return RGNN_OK;
     KernelTimer kt(st, label);
 #define RGNN_COMBINE(HH, TO_, FULL_)                                                                                  \
     RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_softmax_kernel<DD, (DD / (HH) >= 16 ? (HH) : 1), TO_, FULL_>), dim3(L.num_split), dim3(256), 0, st, \
                                           L.split_row, L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), \
-                                          static_cast<TO_*>(out), reinterpret_cast<float2*>(ms)))
+                                          static_cast<TO_*>(out), reinterpret_cast<float2*>(ms), piece_len))
 #define RGNN_COMBINE_H(HH)                                                                                            \
     do {                                                                                                              \
         if (out_bf16) RGNN_COMBINE(HH, bf16_t, true);                                                                 \

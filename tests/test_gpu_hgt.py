@@ -313,6 +313,34 @@ def test_sums_of_rows_in_batches(d, H):
     g.close()
 
 
+@pytest.mark.parametrize("dtype,d,H", [("f32", 32, 1), ("f32", 64, 4), ("f32", 128, 2), ("bf16", 128, 4), ("bf16", 128, 8)])
+def test_messages_near_the_top_of_the_range(dtype, d, H):
+    """Destinations of 1 to 700 edges (one batch, a wavefront's batches, two pieces, many pieces) whose messages are all 2^126 in
+    one column: so is their mean, although four of them exceed fp32.  It may be off by roundings, 8 * 2^-24 in fp32 and one
+    of bf16.  With one edge a message near the bottom, 3 * 2^-127, passes unchanged."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, HgtLayer
+    lengths = [1, 2, 3, 4, 5, 7, 24, 29, 32, 33, 40, 300, 700]
+    N = len(lengths) + 3
+    dst = np.append(np.repeat(np.arange(len(lengths)), lengths), N - 3).astype(np.int32)
+    src = np.full(len(dst), N - 2, np.int32)
+    src[-1] = N - 1
+    X = np.zeros((N, d), np.float32)
+    X[N - 2, 0], X[N - 1, 0] = 2.0 ** 126, 3 * 2.0 ** -127
+    I = np.eye(d, dtype=np.float32)[None]
+    i = np.tile(np.eye(d // H, dtype=np.float32), (1, H, 1, 1))
+    g = Graph(N, 1, src, dst, np.zeros(len(src), np.int32))
+    L = HgtLayer(g, d, H, dtype=dtype)
+    L.load(X, np.zeros_like(I), np.zeros_like(I), I, I, i, i, None)
+    L.fwd()
+    torch.cuda.synchronize()
+    got = L.out.cpu().numpy().astype(np.float64)[:, 0]
+    tol = 2.0 ** -8 if dtype == "bf16" else 8 * 2.0 ** -24
+    assert (np.abs(got[:len(lengths)] * 2.0 ** -126 - 1) <= tol).all(), got
+    assert got[N - 3] == 3 * 2.0 ** -127
+    g.close()
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None
