@@ -538,9 +538,9 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
 
 // dW[s] (and Avec[s]) = sum of the partial slots of segment s; kn / kd = floats of a slot's matrix / vector part, both
 // multiples of 4.  A workgroup owns C4 consecutive float4 of one segment's slots; its G lane groups take the slots in turn,
-// four loads in flight each, and the group sums are added by halves through LDS, so the result does not depend on
-// scheduling (in group order, a chain of 31 additions, the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.21e-7,
-// and dWmsg of HGT at 300k edges 2.65e-7, now 2.55e-7; the same time).  Bound by the chain of loads of the segment with the most slots: with one lane per float and four loads in
+// four loads in flight each, and the group sums are added in four chains through LDS, so the result does not depend on
+// scheduling (in one chain of 31 additions the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.24e-7, and dWmsg
+// of HGT at 300k edges 2.65e-7, now 2.53e-7, in the same time; by halves with a barrier each 1.21e-7 and 2.55e-7, 1 us more).  Bound by the chain of loads of the segment with the most slots: with one lane per float and four loads in
 // flight, a self-loop's one segment of 512 slots plus a 45-relation list took 30 us each, now 7 us; 768 slots of 64 KB
 // (50 MB) in 5 and 17 segments 24 us each, now 13 us.
 template <int G, int C4>
@@ -571,16 +571,19 @@ __global__ __launch_bounds__(G * C4) void slot_reduce_kernel(const float* __rest
     }
     red[g][c] = make_float4(s0.x + s1.x, s0.y + s1.y, s0.z + s1.z, s0.w + s1.w);
     __syncthreads();
+    constexpr int CH = G * C4 >= 512 ? 64 / C4 : 1;        // chains over the groups, one wavefront's worth of lanes
+    if (g >= CH) return;
+    float4 t = red[g][c];
 #pragma unroll
-    for (int h = G / 2; h > 0; h /= 2) {
-        if (g < h) {
-            const float4 x = red[g + h][c];
-            red[g][c].x += x.x; red[g][c].y += x.y; red[g][c].z += x.z; red[g][c].w += x.w;
-        }
-        __syncthreads();
+    for (int k = g + CH; k < G; k += CH) {
+        const float4 x = red[k][c];
+        t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w;
+    }
+#pragma unroll
+    for (int o = C4; o < CH * C4; o <<= 1) {
+        t.x += __shfl_xor(t.x, o); t.y += __shfl_xor(t.y, o); t.z += __shfl_xor(t.z, o); t.w += __shfl_xor(t.w, o);
     }
     if (g != 0 || !on) return;
-    const float4 t = red[0][c];
     if (i < kn) *reinterpret_cast<float4*>(dW + (size_t)seg * kn + i) = t;
     else if (Avec) *reinterpret_cast<float4*>(Avec + (size_t)seg * kd + (i - kn)) = t;
 }

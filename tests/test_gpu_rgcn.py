@@ -328,8 +328,8 @@ def test_weight_gradient_of_long_chunks_bf16():
 def test_weight_gradient_of_many_shares():
     """fp32 self-loop weight whose gradient comes in one share per compute unit, each the sum of a 64-row tile: all products are 1
     but the first of dW0[0][0], 2^33, where half a unit in the last place is 512, as much as eight shares.  32 groups take the
-    shares in turn and are added by halves, five times; a group's own eight shares and the tile's 63 ones stay below one more
-    half unit each."""
+    shares in turn and are added in four chains of eight and then by halves: nine additions; a group's own eight shares and
+    the tile's 63 ones stay below one more half unit each."""
     import torch
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
     d = 64
@@ -343,5 +343,5 @@ def test_weight_gradient_of_many_shares():
     L.bwd()
     torch.cuda.synchronize()
     err = abs(float(L.dW0[0, 0].double()) - (2.0 ** 33 + N - 1))
-    assert err <= 512 * (5 + -(-cus // 256) + 1), err
+    assert err <= 512 * (9 + -(-cus // 256) + 1), err
     g.close()
