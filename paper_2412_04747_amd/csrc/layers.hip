@@ -411,7 +411,9 @@ extern "C" rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, con
     ScheduleIn in;
     in.layer = layer; in.dtype = desc->dtype; in.d = desc->d_out; in.heads = layer == RGNN_LAYER_RGCN ? 1 : desc->heads;
     in.flags = desc->flags; in.R = g->R; in.rel_src_tied = g->rel_src_tied;
-    in.item_len = item_cut(g->E); in.tile_chunks = g->pair_tiles.num_chunks; in.wide_chunks = g->pair_tiles_wide.num_chunks;
+    const Chunkings pc = pair_chunks(g, desc->d_out);
+    in.item_len = item_cut(g->E); in.tile_chunks = pc.many->num_chunks;
+    in.wide_chunks = (layer == RGNN_LAYER_RGCN && rows_bf16(desc) ? pc.cu2 : pc.cu1)->num_chunks;
     in.dst = {g->dst_items.num_single, g->dst_items.num_short};
     in.pair = {g->pair_items.num_single, g->pair_items.num_short};
     in.pair_multi = {g->pair_items_multi.num_single, g->pair_items_multi.num_short};

@@ -111,7 +111,7 @@ struct rgnn_graph {
     rgnn::TileList node_tiles;             // nodes (in ntype_perm order) segmented by type
     rgnn::TileList all_tiles;              // all nodes as one segment (RGCN self-loop)
     rgnn::TileList pair_tiles_wide;        // same tiles as pair_tiles / node_tiles in fewer, longer chunks: for the
-    rgnn::TileList node_tiles_wide;        // weight-gradient kernels, whose chunks each flush a d x d partial
+    rgnn::TileList node_tiles_wide;        // forward kernels whose chunks each load, or split, an fp32 weight
     rgnn::TileList pair_tiles_cu2;         // the same in one chunk per workgroup of a kernel that keeps two (one)
     rgnn::TileList pair_tiles_cu1;         // workgroups per compute unit
     rgnn::TileList node_tiles_cu2;
