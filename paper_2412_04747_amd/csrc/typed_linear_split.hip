@@ -205,7 +205,7 @@ struct FwdArgs {
     int ldy;                 // floats from one row of Y to the next
 };
 
-template <bool GATHER, bool SCATTER>
+template <bool SCATTER>
 __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     constexpr int DEPTH = 3;                               // units in flight per thread: 48 KB per compute unit
     const int tid = threadIdx.x & 255;
@@ -220,8 +220,7 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
         const Unit n = units.get(min(u, u1 - 1));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1);      // (an empty second half: the tile's last row)
-            gi[p][k] = GATHER ? a.gather[row] : row;
+            gi[p][k] = a.gather[n.row0 + min(ld.lr + 8 * k, n.rows - 1)];     // (an empty second half: the tile's last row)
         }
     };
     auto fetch = [&](int p, int q) {
@@ -277,7 +276,6 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
     }
 }
 
-template <bool GATHER>
 __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
     unsigned char* const St = lds + 2 * 3 * PLANE;
@@ -306,12 +304,12 @@ __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* ld
         const bool slow = wbad || bad[u & 3];
         const int r = n.row0 + min(m, n.rows - 1);
         multiply_rows<D>(lds + (u & 1) * 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp,
-                         a.X + (size_t)(GATHER && slow ? a.gather[r] : r) * D);
+                         a.X + (size_t)(slow ? a.gather[r] : r) * D);
     }
 }
 
-// GATHER: X rows through the list; SCATTER: Y rows as well
-template <bool GATHER, bool SCATTER>
+// X rows through the gather list; SCATTER: Y rows as well
+template <bool SCATTER>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_split_fwd_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes, [2] result tiles
     __shared__ int bad[4];
@@ -319,8 +317,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x >= 256) fwd_load<GATHER, SCATTER>(a, lds, bad, u0, u1);
-    else fwd_multiply<GATHER>(a, lds, bad, u0, u1);
+    if (threadIdx.x >= 256) fwd_load<SCATTER>(a, lds, bad, u0, u1);
+    else fwd_multiply(a, lds, bad, u0, u1);
 }
 
 // ------------------------------------------------------------------------------------------------ backward
@@ -592,10 +590,10 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 
 TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
 
-template <bool GATHER, bool SCATTER>
+template <bool SCATTER>
 rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_t st) {
     const size_t lds = 2 * 3 * PLANE + 2 * STAGE;
-    auto kern = typed_linear_split_fwd_kernel<GATHER, SCATTER>;
+    auto kern = typed_linear_split_fwd_kernel<SCATTER>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st,
@@ -620,12 +618,9 @@ rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, const TileList& t, hipStre
 rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
     const TileList& t = *a.tiles;
     if (t.num_tiles == 0) return RGNN_OK;
-    const bool g = a.gather != nullptr, sc = g && a.scatter_out, ac = a.accumulate != 0, v = a.vec != nullptr;
-    if (a.relu) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: no activation on the split product");
-    if (g && !sc && !ac && !v) return launch_fwd<true, false>(a, t, st);
-    if (g && sc && !ac && !v) return launch_fwd<true, true>(a, t, st);
-    if (!g && !ac && !v) return launch_fwd<false, false>(a, t, st);
-    RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: this combination of gather / scatter / accumulate / vec is not built");
+    if (!a.gather || a.accumulate || a.vec || a.relu)
+        RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the split product is built for gathered rows, without accumulate / vec / activation");
+    return a.scatter_out ? launch_fwd<true>(a, t, st) : launch_fwd<false>(a, t, st);
 }
 
 rgnn_status_t typed_linear_split_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
