@@ -97,13 +97,13 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
     row = d * 2 if half else r32      # an input / intermediate row
     wb = 2 if half else 4             # element size of a given weight
     if half:
-        rows = {"typed_linear": P, "pair_linear": P, "node_linear": N, "self_loop": N}
+        rows = {"typed_linear": P, "pair_linear": P, "node_linear": N}       # (the self-loop runs on fp32 copies: below)
         key = name.split(".")[0]
         n = next((v for k, v in rows.items() if key.startswith(k)), None)
         if n is not None:
             bound = "hbm"
             # one row in, one row out, + the gather index; backward: two rows in (both products in one kernel)
-            segs = T if key.startswith("node_linear") else (1 if key.startswith("self_loop") else R)
+            segs = T if key.startswith("node_linear") else R
             w2 = d * d * (4 if key.startswith("pair_linear") else wb)       # block-diagonal weights are fp32
             if name == "pair_linear_bwd":      # key and message halves together: X row, two gradient rows in, one row out
                 return (bound, n * (4 * row + 4) + 2 * segs * d * d * (wb + 4), 8.0 * n * d * d)
@@ -120,7 +120,8 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
     sel = bool(sched.get("row_select", layer == "rgat" and H == 1 and d <= 64)) and layer == "rgat"
     fused = bool(sched.get("fused_softmax", layer == "rgat" and H == 1))       # single-head RGAT: softmax inside the walks
     P1s = P1 if sel or H == 1 else 0      # single-edge pairs that the edge walk / the row selector serve
-    # width 128: fp32 products by three bf16 planes on the bf16 matrix cores, bound by the rows
+    # width 128: fp32 products by three bf16 planes on the bf16 matrix cores, bound by the rows, except the forward of RGAT and
+    # RGCN, which stays on the fp32 instructions
     mm = "hbm" if d == 128 else "mfma"
     pair_fwd = (mm, P * (2 * row + 4) + R * w2, 2.0 * P * d * d)        # gathered row + stored row + pair_src
     pair_bwd = (mm, P * (3 * row + 4) + R * w2, 4.0 * P * d * d)        # dY row + gathered row + stored row
@@ -130,9 +131,9 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
     agg_dst = ("hbm", E * (row + 4 + 4 * H) + N * (out_dst + 8), 2.0 * E * d)  # row + in_pair + coefficient(s); out row + item
     table = {
         # RGAT: + s_src per pair and head; backward also reads ds_src
-        "typed_linear_fwd": (mm, pair_fwd[1] + (P * 4 * H if layer == "rgat" and not fused else 0), pair_fwd[2]),
+        "typed_linear_fwd": ("mfma", pair_fwd[1] + (P * 4 * H if layer == "rgat" and not fused else 0), pair_fwd[2]),
         "typed_linear_bwd": (mm, pair_bwd[1] + ((P * (4 + 8 * H) if sel else P * 4 if H == 1 else 0) if layer == "rgat" else 0), pair_bwd[2]),
-        "self_loop_fwd": (mm, N * 3 * r32 + w2, 2.0 * N * d * d),         # X row + out row read and written
+        "self_loop_fwd": ("mfma", N * 3 * r32 + w2, 2.0 * N * d * d),         # X row + out row read and written
         "self_loop_bwd": (mm, N * 3 * r32 + w2, 4.0 * N * d * d),
         # fused RGAT walk: row + in_pair + in_rel + in_run per edge, s_dst per run and head, out row + item + (m, s) per head per node
         "aggregate_fwd": ("hbm", E * (row + 12) + Q * 4 * H + N * (r32 + 8 + 8 * H), 4.0 * E * d) if fused else agg_dst,
