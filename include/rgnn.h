@@ -212,7 +212,8 @@ typedef struct {
     int32_t item_len;            /* longest traversal item in edges: longer segments (hub nodes) are cut into pieces */
     int32_t tile_chunks;         /* workgroups of the typed-linear kernels over the pair tiles (short chunks) */
     int32_t wide_chunks;         /* the same tiles in one resident round of long chunks, as the backward takes them: one
-                                    workgroup per compute unit, two for RGCN with rows_bf16 */
+                                    workgroup per compute unit, two for RGCN with rows_bf16, three for fp32 up to
+                                    width 64 where the relations are short */
     int32_t rows_bf16;           /* intermediate row tensors stored as bfloat16 */
     int32_t row_select;          /* single-edge pairs: gradient row read through the row selector, not materialised */
     int32_t hgt_folded;          /* HGT key / message linears folded into the per-relation weights */

@@ -121,21 +121,33 @@ struct GradAcc {
 //   many, wide  bf16 rows, forward: weight in bf16 / an fp32 weight to be split
 //   f32         the fp32 forward: one resident round, of three workgroups per compute unit up to width 64, of one at width 128
 //   cu2         bf16 rows, backward with one bf16 weight: two workgroups per compute unit
-//   cu1         the fp32 backward, and the bf16 one with two weights or a split one: one workgroup per compute unit.  (The
-//               fused fp32 backward up to width 64 fills a compute unit's LDS; as three rounds of shorter chunks, each with
-//               its weight load, flush and slots, it took 62 us for 48 at 141k pairs and 108 for 82 at 349k, and the
-//               same within 1 % at 7.3M.)
-struct Chunkings { const rgnn::TileList* many; const rgnn::TileList* wide; const rgnn::TileList* f32; const rgnn::TileList* cu2; const rgnn::TileList* cu1; };
+//   cu1         the bf16 backward with two weights or a split one, and the fp32 one at width 128: one workgroup per compute unit
+//   f32_bwd     the fp32 backward.  Up to width 64 it fills a compute unit's LDS, and one chunk per compute unit saves the weight
+//               loads, flushes and slots of three rounds of shorter ones (62 us for 48 at 141k pairs and 108 for 82 at 349k, the
+//               same within 1 % at 7.3M).  But where relations are short a chunk is a row of runs (segments), each with a load, one
+//               or two rounds of units and a flush, and its length depends on how many: then the dispatcher has to even out the
+//               chunks of `wide`.  Pairs of relations with Zipf 1.2 frequencies, cu1 / wide, width 64: 0.91, 0.93 and 0.98 of the
+//               time with 1.7 runs per chunk (200k, 1M and 4M edges), 1.18, 1.02 and 1.03 with 2.1, 1.13 to 1.11 with 2.8 to 2.9;
+//               with Zipf 1.0 the lines cross at 2.5.  With five tiles per chunk or fewer cu1 wins at any number of runs
+//               (0.78 to 0.97 at 40k and 70k edges; 1.00 to 1.11 with six to eight tiles and two to four runs).
+struct Chunkings {
+    const rgnn::TileList* many; const rgnn::TileList* wide; const rgnn::TileList* f32; const rgnn::TileList* f32_bwd; const rgnn::TileList* cu2;
+    const rgnn::TileList* cu1;
+};
+inline Chunkings chunkings(const rgnn::TileList& many, const rgnn::TileList& wide, const rgnn::TileList& cu2, const rgnn::TileList& cu1, int width) {
+    const bool few_runs = 8 * (int64_t)cu1.num_slots <= 15 * (int64_t)cu1.num_chunks || cu1.num_tiles <= 5 * cu1.num_chunks;
+    return {&many, &wide, width == 128 ? &cu1 : &wide, width == 128 || few_runs ? &cu1 : &wide, &cu2, &cu1};
+}
 inline Chunkings pair_chunks(const rgnn_graph_t* g, int width) {
-    return {&g->pair_tiles, &g->pair_tiles_wide, width == 128 ? &g->pair_tiles_cu1 : &g->pair_tiles_wide, &g->pair_tiles_cu2, &g->pair_tiles_cu1};
+    return chunkings(g->pair_tiles, g->pair_tiles_wide, g->pair_tiles_cu2, g->pair_tiles_cu1, width);
 }
 inline Chunkings node_chunks(const rgnn_graph_t* g, int width) {
-    return {&g->node_tiles, &g->node_tiles_wide, width == 128 ? &g->node_tiles_cu1 : &g->node_tiles_wide, &g->node_tiles_cu2, &g->node_tiles_cu1};
+    return chunkings(g->node_tiles, g->node_tiles_wide, g->node_tiles_cu2, g->node_tiles_cu1, width);
 }
 inline const rgnn::TileList* all_chunks(const rgnn_graph_t* g, int width) { return width == 128 ? &g->all_tiles_cu1 : &g->all_tiles; }
 // floats of scratch a backward typed linear needs on a list
 size_t tl_bwd_scratch(bool rows16, const Chunkings& t, int d_in, int d_out) {
-    if (!rows16) return typed_linear_bwd_scratch_floats(d_in, d_out, *t.cu1);
+    if (!rows16) return typed_linear_bwd_scratch_floats(d_in, d_out, *t.f32_bwd);
     return (size_t)d_in * d_out * std::max((size_t)t.cu2->num_slots, 2 * (size_t)t.cu1->num_slots);
 }
 
@@ -192,7 +204,7 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->dXp = c.take<float>((size_t)g->P * d->d_in);
     w->A = c.take<float>(H * g->R * d->d_in);
     w->U = c.take<float>(H * g->R * d->d_in);
-    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles_cu1, (int)H));
+    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, *pair_chunks(g, d->d_out).f32_bwd, (int)H));
     const size_t parts = std::max<size_t>({(size_t)g->pair_items.num_partials, (size_t)g->relrun_items.num_partials,
                                            (size_t)g->relpair_items.num_partials});
     w->partial = c.take<float>(parts * std::max(d->d_in, d->d_out) * H);   // the run walk keeps one partial row per head
@@ -366,7 +378,7 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
     }
     if (dx_acc) RGNN_FAIL(RGNN_EUNSUPPORTED, "accumulating input gradient needs bf16 rows");
     TypedLinearBwdArgs b{};
-    b.tiles = tiles.cu1; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
+    b.tiles = tiles.f32_bwd; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
     b.dy_gathered = both_gathered; b.dXrow = static_cast<float*>(dXrow); b.scatter_dx = both_gathered; b.dW = dW;
     b.part = part; b.label = label; b.dy_stride = dy_stride;
     return typed_linear_bwd(d_in, d, b, st);
@@ -413,7 +425,8 @@ extern "C" rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, con
     in.flags = desc->flags; in.R = g->R; in.rel_src_tied = g->rel_src_tied;
     const Chunkings pc = pair_chunks(g, desc->d_out);
     in.item_len = item_cut(g->E); in.tile_chunks = pc.many->num_chunks;
-    in.wide_chunks = (layer == RGNN_LAYER_RGCN && rows_bf16(desc) ? pc.cu2 : pc.cu1)->num_chunks;
+    const bool rows16 = layer != RGNN_LAYER_RGAT && rows_bf16(desc);
+    in.wide_chunks = (!rows16 ? pc.f32_bwd : layer == RGNN_LAYER_RGCN ? pc.cu2 : pc.cu1)->num_chunks;
     in.dst = {g->dst_items.num_single, g->dst_items.num_short};
     in.pair = {g->pair_items.num_single, g->pair_items.num_short};
     in.pair_multi = {g->pair_items_multi.num_single, g->pair_items_multi.num_short};
@@ -688,7 +701,7 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
                             sel ? w.ds_src : nullptr, 2 * H));
         // 4. dXp = dHs W^T, dW = sum X^T dHs; with the selector also A[r][h] = sum over r's pairs of ds_src[p][h] X[src_p]
         TypedLinearBwdArgs b{};
-        b.tiles = &g->pair_tiles_cu1; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
+        b.tiles = pair_chunks(g, D).f32_bwd; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
         b.dW = static_cast<float*>(dW); b.part = w.tl_part;
         if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.hcoef = w.ds_src; b.wvec = ws; b.sel_heads = H; b.Avec = w.A; }
         RGNN_TRY(typed_linear_bwd(K, D, b, st));
@@ -729,7 +742,7 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     //    A[r] = sum ds_src X
     RGNN_TRY(fold_weight(g->R, K, D, Wf, static_cast<const float*>(w_s), w.wsp, st, static_cast<const float*>(w_t), w.wtp));   // wtp: step 7
     TypedLinearBwdArgs b{};
-    b.tiles = &g->pair_tiles_cu1; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
+    b.tiles = pair_chunks(g, D).f32_bwd; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
     b.rowscale = sel ? nullptr : w.ds_src; b.vec = w.wsp; b.dW = static_cast<float*>(dW); b.Avec = w.A;
     b.part = w.tl_part;
     if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.ds_yscale = reinterpret_cast<const float2*>(w.ds_src); }

@@ -129,3 +129,49 @@ def test_hgt_unfolded_on_a_graph_that_could_fold(dtype, d):
             check(v, wg[k], tol, f"{k} flags={flags}")
     assert sizes[0] < max(sizes.values())            # the folded path saves the K and V rows
     g.close()
+
+
+@pytest.mark.parametrize("layer,d,H", [("rgat", 64, 1), ("rgat", 64, 2), ("rgat", 32, 2), ("rgcn", 64, 1), ("hgt", 64, 4)])
+def test_chunks_of_many_relations(wl, layer, d, H):
+    """1,500 relations of one row tile each: the fp32 backward takes the shorter chunks (twice as many here), within the
+    workspace that is reported for them and with the oracle's results."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd import harness as Hn
+    from test_gpu_workspace_bounds import _guarded, _intact
+    N, R = 400, 1500
+    rng = np.random.default_rng(1500 + d)
+    rel = np.repeat(np.arange(R, dtype=np.int32), 4)
+    src, dst = rng.integers(0, N, len(rel)).astype(np.int32), rng.integers(0, N, len(rel)).astype(np.int32)
+    g = Hn.Graph(N, R, src, dst, rel)
+    if layer == "rgat":
+        p = synth.rgat_params(rng, N, R, d, d)
+        L = Hn.RgatLayer(g, d, heads=H)
+        L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+        a = (N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"])
+        want = O.rgat_heads_bwd(*a, p["dOut"], H) if H > 1 else O.rgat_bwd(*a, p["dOut"])
+    elif layer == "rgcn":
+        p = synth.rgcn_params(rng, N, R, d, d)
+        L = Hn.RgcnLayer(g, d, "none")
+        L.load(p["X"], p["W"], None, p["dOut"])
+        want = O.rgcn_bwd(N, src, dst, rel, p["X"], p["W"], None, p["dOut"], "none", "none", out=np.zeros((N, d)))
+    else:
+        p = synth.hgt_params(rng, N, 1, R, d, H, with_mu=True)
+        names = ("X", "Wk", "Wq", "Wv", "Wo", "Watt", "Wmsg", "mu")
+        L = Hn.HgtLayer(g, d, H)
+        L.load(*[p[k] for k in names], dOut=p["dOut"])
+        want = O.hgt_bwd(N, src, dst, rel, None, *[p[k] for k in names], p["dOut"])
+    ptr, cus = g.export("pair_ptr"), torch.cuda.get_device_properties(0).multi_processor_count
+    n = np.zeros((2, 3), np.int32)
+    for row, most in zip(n, (cus, wl.wl_constant(WL.K["wide_chunks"]) * cus)):
+        wl.wl_plan_tiles(ptr.ctypes.data_as(C.c_void_p), R, wl.wl_constant(WL.K["tile_rows"]), most)
+        wl.wl_tiles_scalars(row.ctypes.data_as(C.c_void_p))
+    assert n[0, 0] < n[1, 0] and B.rgnn_schedule(g.handle, WL.LAYER[layer], L.desc)["wide_chunks"] == n[1, 0]
+    L.fwd()
+    ws, L.ws = _guarded(B.rgnn_workspace_bytes(g.handle, WL.LAYER[layer], L.desc)[1])
+    L.bwd()
+    torch.cuda.synchronize()
+    _intact(ws, "backward workspace")
+    for k, v in L.grads().items():
+        check(v, want[k], TOL_F32, k)
+    g.close()
