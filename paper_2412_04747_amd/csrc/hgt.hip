@@ -105,7 +105,8 @@ __global__ __launch_bounds__(256) void hgt_fold_kernel(int R, Halves<T> w, Pair2
 //                                   c(r, h) sum_n dWf[r][k][h dh + n] W[r][h][j][n]
 // The operands of a step (32 rows of both) are staged in LDS; a thread forms DH * DH / 256 (or DH * 32 / 256) results, each in
 // four chains over k mod 4, or in steps of four n (as one chain dWmsg at 300k edges, width 64, was
-// 2.9e-7 off, 2.6e-7 so).
+// 2.9e-7 off, 2.6e-7 so).  Both loops are unrolled as wholes: in steps of 4 and 8 they took 64 us for 50 (60 relations,
+// heads of 32 columns) and 189 for 123 (heads of 64).
 template <typename T, int DH>
 __global__ __launch_bounds__(256) void hgt_fold_bwd_kernel(int R, Halves<T> w, Pair2 dWf_, Pair2 dW, Pair2 dWnode, float* __restrict__ dmu) {
     __shared__ float A[32][DH + 1], B[DH > 32 ? DH : 32][DH + 1], red[4];
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(256) void hgt_fold_bwd_kernel(int R, Halves<T> w, P
                 B[i / DH][i % DH] = dWf[g0 + at];
             }
             __syncthreads();
-#pragma unroll 8
+#pragma unroll
             for (int k = 0; k < 32; ++k)
 #pragma unroll
                 for (int q = 0; q < NO; ++q) part[q][k & 3] += A[k][(tid + 256 * q) / DH] * B[k][tid % DH];
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(256) void hgt_fold_bwd_kernel(int R, Halves<T> w, P
         float p[NO];                              // one relation's sum first, then the relations in order
 #pragma unroll
         for (int q = 0; q < NO; ++q) p[q] = 0.f;
-#pragma unroll 4
+#pragma unroll
         for (int n = 0; n < DH; n += 4)
 #pragma unroll
             for (int q = 0; q < NO; ++q) {
