@@ -10,7 +10,7 @@
 //                              dQ[v] = sum dl Ka;  (att, dl) stored side by side per edge and head
 //   backward, per pair:        dKM[p] = (sum dl Q[dst], sum att dZ[dst])
 // All three are bound by the gathered rows.  On 20M edges (5.4M pairs, 2M nodes), width 128 in bf16, 4 heads, they take
-// 2.01 + 2.46 + 2.05 ms: 5.6, 5.3 and 5.8 TB/s of the bytes they cannot avoid.  With the logits, softmax, weighted sum, edge
+// 2.01 + 2.48 + 2.05 ms: 5.6, 5.3 and 5.8 TB/s of the bytes they cannot avoid.  With the logits, softmax, weighted sum, edge
 // dot and the three gradient sums as walks of their own (six gathers of D columns per edge, and weights stored and
 // re-read per edge between them) the same work took 7.95 ms.
 //

@@ -5,8 +5,8 @@
 //
 // Bound by HBM: the two products together need a tenth of the matrix cores' rate at the speed the rows arrive.  As two
 // kernels the dY rows were read twice (and for two weights the X rows twice, the dXrow rows written twice and summed
-// later).  14.5M pairs (single-edge rows through the selector, 500 relations): 1.33 + 1.40 ms as two kernels, now 1.83 ms
-// (11.1 GB, 6.1 TB/s); 5.4M pairs with two weights: 2.12 ms as four kernels, now 1.08 ms (5.5 GB, 5.1 TB/s).
+// later).  14.5M pairs (single-edge rows through the selector, 500 relations): 1.33 + 1.40 ms as two kernels, now 1.84 ms
+// (11.1 GB, 6.0 TB/s); 5.4M pairs with two weights: 2.12 ms as four kernels, now 1.10 ms (5.5 GB, 5.0 TB/s).
 //
 // A workgroup of eight wavefronts takes a chunk of 64-row tiles.  A tile's X and dY rows are brought to registers one tile
 // ahead and written to LDS row-major.  dXrow^T = W dY^T takes W's rows and the dY rows as its operands straight from LDS

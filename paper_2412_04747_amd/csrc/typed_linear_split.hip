@@ -1,6 +1,6 @@
 // fp32 typed linear layer of width 128 on the bf16 matrix cores, without loss of fp32 accuracy.
 //
-// Every fp32 operand is split exactly into three bf16 planes, x = hi + mid + lo (round to nearest even: |mid| <= 2^-9 |x|,
+// Every fp32 operand is split into three bf16 planes, x = hi + mid + lo (round to nearest even: |mid| <= 2^-9 |x|,
 // |lo| <= 2^-18 |x|), and a product is the six plane products down to 2^-18: hi hi + (hi mid + mid hi) + (hi lo + mid mid +
 // lo hi); what is left out is below 2^-26 of |x y|, a quarter of a rounding of the fp32 product.  Products are exact and sums
 // are fp32, one rounding per 16 terms and plane product against one per 2 terms of v_mfma_f32_32x32x2_f32, so the result is
@@ -10,14 +10,15 @@
 // The split holds for zero and for magnitudes from 2^-110, the least fp32 whose last bit, 2^-133, is a (subnormal) bf16, to
 // 3.38e38, the greatest whose bf16 is finite.  A unit of rows, or a weight's band of 32 rows or columns, with an operand
 // outside is multiplied with the fp32 matrix instructions, straight from global memory (a backward whose every unit goes that
-// way, 1.43M pairs: 1.9 ms for 0.7).  NaN needs no such care: its planes are NaN.  Without the lower bound the error of dX and
+// way, 1.43M pairs: 1.9 ms for 0.7).  NaN needs no such care: its planes are NaN.  (A
+// sum within 1 % of the largest float may overflow: the product of the high planes can be that much above it.)  Without the lower bound the error of dX and
 // dW, 1.1e-7 and 1.7e-7 in the range, was 2.2e-6 with one operand near 2^-116 and 3.5e-5 near 2^-120; the check costs 1.3 % of an
 // RGAT forward + backward on those pairs.
 //
 // Why: at width 128 a row costs 32 kflop per product against 1.5 KB of traffic, twice what the fp32 matrix cores do in the time
 // the rows need.  (RGAT's and RGCN's forward stay on those: the sign of a result selects a branch of their backward.)
 // 1.43M pairs of 60 relations: forward 0.52 -> 0.31 ms (4.7 TB/s), backward (two kernels before, dY read
-// twice) 1.18 -> 0.60 ms (3.7 TB/s; the loading wavefronts' chain of waits, splits and LDS writes per unit).
+// twice) 1.18 -> 0.61 ms (3.6 TB/s; the loading wavefronts' chain of waits, splits and LDS writes per unit).
 //
 // A workgroup takes a chunk of 64-row tiles in units of 32 rows, one workgroup per compute unit, its wavefronts specialised:
 //   4 load:     rows of unit u + 1 from registers (fetched two units ahead) split into planes in LDS, result rows of unit
