@@ -216,6 +216,10 @@ struct TileTable {
 // 2^-ceil(log2 n), n >= 1: n terms of weight up to 1 times this stay within the largest of them
 __device__ __forceinline__ float pow2_share(int n) { return __uint_as_float((unsigned)(127 - (n > 1 ? 32 - __clz(n - 1) : 0)) << 23); }
 
+// What the logits of a softmax with maximum m are measured against: while every one of them is minus infinity, 0, so that they
+// weigh 0 and not NaN.
+__device__ __forceinline__ float softmax_base(float m) { return m == -INFINITY ? 0.f : m; }
+
 // max(v, 0), NaN to 0
 __device__ __forceinline__ float4 positive(float4 v) {
     return make_float4(v.x > 0.f ? v.x : 0.f, v.y > 0.f ? v.y : 0.f, v.z > 0.f ? v.z : 0.f, v.w > 0.f ? v.w : 0.f);

@@ -107,14 +107,14 @@ struct FwdState {
             l[u] = u < n ? x : -INFINITY;
             mn = fmaxf(mn, l[u]);
         }
-        const float sc = expf(m - mn);          // 0 in the first batch (m = -inf), 1 while the maximum stands
+        const float base = softmax_base(mn), sc = expf(m - base);     // 0 in the first batch (m = -inf), 1 while the maximum stands
         float t = 0.f;
 #pragma unroll
         for (int c = 0; c < V; ++c) acc[c] *= sc;
         float p[NE];
 #pragma unroll
         for (int u = 0; u < NE; ++u) {
-            p[u] = expf(l[u] - mn);
+            p[u] = expf(l[u] - base);
             t += p[u];
             p[u] *= c;
         }
@@ -161,7 +161,7 @@ __device__ __forceinline__ void fwd_walk(const WalkArgs& a, int i) {
         float mn = f.m;
 #pragma unroll
         for (int o = LPR; o < 64; o <<= 1) mn = fmaxf(mn, __shfl_xor(mn, o));
-        const float sc = expf(f.m - mn);
+        const float sc = expf(f.m - softmax_base(mn));
         f.m = mn;
         f.s *= sc;
 #pragma unroll

@@ -700,12 +700,12 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
             }
             mn = fmaxf(mn, t[u].x);
         }
-        const float sc = ex(M - mn);          // 0 for the first four pieces
+        const float base = softmax_base(mn), sc = ex(M - base);       // 0 for the first four pieces
         S *= sc;
         acc.x *= sc; acc.y *= sc; acc.z *= sc; acc.w *= sc;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const float w = ex(t[u].x - mn);
+            const float w = ex(t[u].x - base);
             S += w * t[u].y;
             fma4(acc, w * share, r[u]);
         }
@@ -721,7 +721,7 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
         float t[4] = {0.f, 0.f, 0.f, 0.f};
         for (int k = 0; k < n; ++k) {
             const float2 q = redms[k][head];
-            const float w = ex(q.x - M);
+            const float w = ex(q.x - softmax_base(M));
             const float4 r = red[k * LPR + c];
             S += w * q.y;
             t[0] += w * r.x; t[1] += w * r.y; t[2] += w * r.z; t[3] += w * r.w;

@@ -341,6 +341,34 @@ def test_messages_near_the_top_of_the_range(dtype, d, H):
     g.close()
 
 
+@pytest.mark.parametrize("dtype,d,H", [("bf16", 128, 8), ("bf16", 128, 2), ("f32", 64, 4)])
+def test_logits_of_minus_infinity(dtype, d, H):
+    """Edges whose logit overflows to minus infinity weigh nothing, also where they fill a destination's first batch, a lane
+    group's share of a long item, or a whole piece of a cut destination: the result is the other edges' message, 5."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, HgtLayer
+    lists = ["aaaab", "a" * 8 + "bbb", "a" * 26 + "bbbb", "a" * 40 + "bbbb", "a" * 70 + "b", "a" * 64 + "b" * 90, "ab"]
+    N = 2 + len(lists)
+    src = np.array([0 if c == "a" else 1 for w in lists for c in w], np.int32)
+    dst = np.repeat(np.arange(2, N, dtype=np.int32), [len(w) for w in lists])
+    X = np.zeros((N, d), np.float32)
+    X[0, 0], X[2:, 0], X[0, 1], X[1, 1] = -2.0 ** 70, 2.0 ** 64, 3, 5
+    I = np.eye(d, dtype=np.float32)[None]
+    i = np.tile(np.eye(d // H, dtype=np.float32), (1, H, 1, 1))
+    dOut = np.zeros((N, d), np.float32)
+    dOut[2:, 1] = 1
+    g = Graph(N, 1, src, dst, np.zeros(len(src), np.int32))
+    L = HgtLayer(g, d, H, dtype=dtype)
+    L.load(X, I, I, I, I, i, i, None, dOut)
+    L.fwd(); L.bwd()
+    torch.cuda.synchronize()
+    out = L.out.cpu().numpy()
+    assert (np.abs(out[2:, 1] - 5) <= 5 * 8 * 2.0 ** -24).all(), out[2:, 1]
+    dX = L.dX.cpu().numpy()
+    assert dX[0, 1] == 0 and abs(dX[1, 1] - len(lists)) <= 2.0 ** -7 * len(lists), dX[:2, 1]
+    g.close()
+
+
 def test_scaled_config4_bf16():
     c = synth.config(4, scale=0.01)          # 20k nodes, 200k edges, 8 node types, 30 relations, d=128, H=4
     c["mu"] = None
