@@ -132,7 +132,8 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
     table = {
         # RGAT: + s_src per pair and head; backward also reads ds_src
         "typed_linear_fwd": ("mfma", pair_fwd[1] + (P * 4 * H if layer == "rgat" and not fused else 0), pair_fwd[2]),
-        "typed_linear_bwd": (mm, pair_bwd[1] + ((P * (4 + 8 * H) if sel else P * 4 if H == 1 else 0) if layer == "rgat" else 0), pair_bwd[2]),
+        # RGCN: the selector and the scale with the row selector, nothing without
+        "typed_linear_bwd": (mm, pair_bwd[1] + ((P * (4 + 8 * H) if sel else P * 4 if H == 1 else 0) if layer == "rgat" else P * 8 if sched.get("row_select") else 0), pair_bwd[2]),
         "self_loop_fwd": ("mfma", N * 3 * r32 + w2, 2.0 * N * d * d),         # X row + out row read and written
         "self_loop_bwd": (mm, N * 3 * r32 + w2, 4.0 * N * d * d),
         # fused RGAT walk: row + in_pair + in_rel + in_run per edge, s_dst per run and head, out row + item + (m, s) per head per node
@@ -148,10 +149,10 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
         # RGAT: only the E - P1 edges of the P - P1 pairs with several edges; coefficient = the (att, dz) pair;
         # with one head the walk also writes ds_src per pair.
         # RGCN: every edge; row + out_dst + coefficient
-        # RGCN with bf16 rows: likewise only pairs with several edges (the typed-linear backward reads the
+        # RGCN with the row selector: likewise only pairs with several edges (the typed-linear backward reads the
         # others' rows straight from the destinations' gradient rows)
         "aggregate_bwd_pair": ("hbm", (E - P1s) * (row + 8 + 8 * H) + (P - P1s) * (row + 8 + 4 * H), 2.0 * (E - P1s) * d) if layer == "rgat"
-                              else ("hbm", (E - P1) * (row + 8) + (P - P1) * (row + 8), 2.0 * (E - P1) * d) if half
+                              else ("hbm", (E - P1) * (row + 8) + (P - P1) * (row + 8), 2.0 * (E - P1) * d) if sched.get("row_select", half)
                               else ("hbm", E * (row + 8) + P * (row + 8), 2.0 * E * d),
         # per run: X row + relrun_idx + run_dst + ds_dst
         "dst_side_wgrad": ("hbm", Q * (row + 12), 2.0 * Q * d),

@@ -162,7 +162,7 @@ struct RgatBwdWs {
 };
 // Single-head RGAT at widths up to 64: the gradient rows of single-edge pairs are not written per pair;
 // the typed-linear backward reads att_e * dOut[dst_e] through its row selector.
-inline bool rgat_row_select(const rgnn_layer_desc_t* d) { return sched_row_select(RGNN_LAYER_RGAT, d->dtype, d->d_out, d->heads, d->flags); }
+inline bool rgat_row_select(const rgnn_layer_desc_t* d) { return sched_row_select(RGNN_LAYER_RGAT, d->dtype, d->d_out, d->heads, 0, d->flags); }
 inline bool rgat_edge_parallel(const rgnn_layer_desc_t* d) { return (d->flags & RGNN_FLAG_EDGE_PARALLEL_AGGREGATION) != 0; }
 inline bool rgat_fused(const rgnn_layer_desc_t* d) { return sched_fused_softmax(d->flags); }
 
@@ -359,7 +359,7 @@ rgnn_status_t tl_fwd(bool bf16, const Chunkings& tiles, int d, const float* A32,
 //   otherwise: the fused fp32 kernel on fp32 X, W, dY.
 //   dx_acc: dXrow += (fp32 dXrow, rows16)
 //   dy_stride: the rows of dY are dy_stride * d elements apart (dY not gathered)
-//   ysel / y_alt (rows16, dY not gathered): row i of dY is dY[ysel[i]], or y_alt[ysel[i] & 0x7FFFFFFF] when the
+//   ysel / y_alt (dY not gathered): row i of dY is dY[ysel[i]], or y_alt[ysel[i] & 0x7FFFFFFF] when the
 //     top bit of ysel[i] is set; with yscale it is also multiplied by yscale[i]
 rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
                      const int32_t* gather, int both_gathered, const float* W32, const void* W16, const void* dY,
@@ -368,7 +368,7 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
                      const float* yscale = nullptr, int d_in = 0, int dy_stride = 1) {
     if (d_in == 0) d_in = d;
     if (rows16 && d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward on the bf16 matrix cores: equal widths only");
-    if (ysel && (!rows16 || both_gathered)) RGNN_FAIL(RGNN_EUNSUPPORTED, "row selector: bf16 rows and ungathered dY only");
+    if (ysel && both_gathered) RGNN_FAIL(RGNN_EUNSUPPORTED, "row selector: ungathered dY only");
     if (rows16) {
         TypedLinearBwdBf16Args a{};
         a.tiles = W16 ? tiles.cu2 : tiles.cu1; a.X = X; a.gather = gather; a.both_gathered = both_gathered;
@@ -381,6 +381,7 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
     b.tiles = tiles.f32_bwd; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
     b.dy_gathered = both_gathered; b.dXrow = static_cast<float*>(dXrow); b.scatter_dx = both_gathered; b.dW = dW;
     b.part = part; b.label = label; b.dy_stride = dy_stride;
+    b.ysel = ysel; b.dY_alt = static_cast<const float*>(y_alt); b.yscale = yscale;
     return typed_linear_bwd(d_in, d, b, st);
 }
 }  // namespace
@@ -515,9 +516,9 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
     //    (coefficients from the pair-major copy, so no per-edge indirection is left)
     const float* ocoef = coef ? g->out_invc : nullptr;
-    //    With bf16 rows the row of a pair with a single edge is not written per pair: the typed-linear backward
-    //    reads dPre[dst_e] through its row selector and multiplies it by 1/c_e on the way in.
-    const bool sel = sched_row_select(RGNN_LAYER_RGCN, desc->dtype, D, 1, desc->flags);
+    //    With the row selector the row of a pair with a single edge is not written per pair: the typed-linear backward
+    //    reads dPre[dst_e] instead and multiplies it by 1/c_e on the way in.
+    const bool sel = sched_row_select(RGNN_LAYER_RGCN, desc->dtype, D, 1, g->pair_items.num_single, desc->flags);
     const int32_t* ysel = sel ? g->pair_ysel : nullptr;
     const void* y_alt = sel ? dPre : nullptr;
     const float* yscale = sel && coef ? g->pair_scale : nullptr;

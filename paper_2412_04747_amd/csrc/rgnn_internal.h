@@ -179,12 +179,13 @@ struct TypedLinearBwdArgs {
     float* part;             // scratch [num_slots][KD*ND + KD]
     const char* label;
     // Optional row selector (widths up to 64, ungathered dY): row i of dY is
-    // ysel[i] < 0 ? scale_i * dY_alt[ysel[i] & 0x7FFFFFFF] : dY[ysel[i]].  rowscale[i] and scale_i then come
-    // interleaved as ds_yscale[i] = (rowscale_i, scale_i) and `rowscale` stays null (scale_i is read only where
-    // the top bit of ysel[i] is set).
+    // ysel[i] < 0 ? scale_i * dY_alt[ysel[i] & 0x7FFFFFFF] : dY[ysel[i]].  With `vec`, rowscale[i] and scale_i come
+    // interleaved as ds_yscale[i] = (rowscale_i, scale_i) and `rowscale` stays null; without, scale_i is yscale[i], or 1
+    // where yscale is null (either way scale_i counts only where the top bit of ysel[i] is set).
     const int32_t* ysel = nullptr;
     const float* dY_alt = nullptr;
     const float2* ds_yscale = nullptr;
+    const float* yscale = nullptr;
     // Per-head row selector (widths up to 64, sel_heads in {2, 4}, instead of rowscale / vec / ds_yscale): a selected
     // row is dY_alt[row] * a[h] + b[h] * wvec[seg] on the columns of head h, (b[0..H), a[0..H)) = hcoef[i] for row i
     const float* hcoef = nullptr;    // [rows][2][sel_heads]

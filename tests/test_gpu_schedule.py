@@ -99,6 +99,40 @@ def test_rgcn_bf16_forced_alternatives(flags):
     g.close()
 
 
+@pytest.mark.parametrize("k,d,norm,dtype", [(k, d, n, "f32") for k, d in ((32, 32), (64, 64), (32, 64), (64, 32))
+                                            for n in ("in_degree_per_rel", "none")] +
+                         [(d, d, "in_degree_per_rel", "bf16") for d in (32, 64)])
+def test_rgcn_row_select(k, d, norm, dtype):
+    """Widths up to 64: the rows of the single-edge pairs are read from the destinations' gradient rows.  Products and sums
+    are those of the plain walk in the same order, so the gradients are the same bits; and they are the oracle's."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    N, R, E = 9001, 7, 40037
+    rng, src, dst, rel, _ = _hub_graph(741 + k + d, N, R, E)
+    rel[-1000:] = np.where(rel[-1000:] == 4, 3, rel[-1000:])
+    print(f"schedule case rgcn row select {k}->{d} {norm} {dtype}", flush=True)
+    p = synth.rgcn_params(rng, N, R, k, d, self_loop=True)
+    if dtype == "bf16":
+        p = {n: synth.round_to_bf16(v) for n, v in p.items()}
+    g = Graph(N, R, src, dst, rel)
+    want = O.rgcn_fwd(N, src, dst, rel, p["X"], p["W"], p["W0"], norm, "none")
+    wg = O.rgcn_bwd(N, src, dst, rel, p["X"], p["W"], p["W0"], p["dOut"], norm, "none", out=want)
+    got = []
+    for flags in (0, B.RGNN_FLAG_NO_ROW_SELECT):
+        L = RgcnLayer(g, d, norm, "none", True, dtype=dtype, flags=flags, d_in=k)
+        assert B.rgnn_schedule(g.handle, B.RGNN_LAYER_RGCN, L.desc)["row_select"] == (flags == 0)
+        L.load(p["X"], p["W"], p["W0"], p["dOut"])
+        L.fwd(); L.bwd()
+        torch.cuda.synchronize()
+        got.append({n: v.clone() for n, v in L.grads().items()})
+        for n, v in L.grads().items():
+            check(v, wg[n], TOL_F32, n)
+    for n in got[0]:
+        assert torch.equal(got[0][n], got[1][n]), n
+    g.close()
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
 def test_hgt_unfolded_on_a_graph_that_could_fold(dtype, d):
     import torch
