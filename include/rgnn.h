@@ -104,7 +104,7 @@ typedef struct {
 #define RGNN_FLAG_EDGE_PARALLEL_AGGREGATION 1u
 /* every segment takes the general walk: no batched kernels for the segments with one or with 2..4 entries */
 #define RGNN_FLAG_NO_BATCHED_WALKS 2u
-/* RGAT with 1, 2 or 4 heads (width <= 64), RGCN (bf16 rows; width <= 64): the gradient row of every (source, relation) pair is
+/* RGAT with one head (2 or 4 up to width 64), RGCN: the gradient row of every (source, relation) pair is
  * written per pair, also for the pairs with one edge, instead of being read through the row selector */
 #define RGNN_FLAG_NO_ROW_SELECT 4u
 /* HGT: keep the key / message node linears and the per-relation matrices apart even when every relation's

@@ -160,8 +160,8 @@ struct RgatBwdWs {
     float* tl_part; float* partial;
     float* acc_dW; float* acc_dws; float* acc_dwt;      // RGNN_FLAG_ACCUMULATE: the parameter gradients of this call
 };
-// Single-head RGAT at widths up to 64: the gradient rows of single-edge pairs are not written per pair;
-// the typed-linear backward reads att_e * dOut[dst_e] through its row selector.
+// RGAT with one head, and up to width 64 with two or four: the gradient rows of single-edge pairs are not written per
+// pair; the typed-linear backward reads att_e * dOut[dst_e] through its row selector.
 inline bool rgat_row_select(const rgnn_layer_desc_t* d) { return sched_row_select(RGNN_LAYER_RGAT, d->dtype, d->d_out, d->heads, 0, d->flags); }
 inline bool rgat_edge_parallel(const rgnn_layer_desc_t* d) { return (d->flags & RGNN_FLAG_EDGE_PARALLEL_AGGREGATION) != 0; }
 inline bool rgat_fused(const rgnn_layer_desc_t* d) { return sched_fused_softmax(d->flags); }

@@ -28,14 +28,14 @@ inline int batched_count(int count, uint32_t flags) {
 // bf16 inputs at width 128: every row tensor (inputs, intermediates, saved tensors, incoming gradients) is bf16 storage
 inline bool sched_rows_bf16(int dtype, int d) { return dtype == RGNN_BF16 && d == 128; }
 // The gradient row of a (source, relation) pair with one edge is not materialised: the typed-linear backward reads
-// it from the destination's gradient row through a row selector.  Built for RGAT up to width 64 with one, two or
-// four heads (the fused fp32 backward kernel) and for RGCN with bf16 rows, and up to width 64 where the batched walk would
-// take the pairs with one edge.  Training passes with and without at 1.2M edges 462 / 508 us (width 64), 226 / 244 (width 32);
-// 300k edges 171 / 174 (width 64); at 20k edges no difference, and below that the plain walk stays.
+// it from the destination's gradient row through a row selector.  Built for RGAT with one head, and up to width 64 with two
+// or four (the fused fp32 backward kernel); and for RGCN, with fp32 rows where the batched walk would take the pairs with
+// one edge.  Training passes with and without at 1.2M edges 462 / 508 us (width 64), 226 / 244 (width 32);
+// 1M edges 820 / 917 (width 128); 300k edges 171 / 174 (width 64); at 20k edges no difference, and below that the plain walk stays.
 inline bool sched_row_select(int layer, int dtype, int d, int heads, int single_pairs, uint32_t flags) {
     if (flag_set(flags, RGNN_FLAG_NO_ROW_SELECT)) return false;
-    if (layer == RGNN_LAYER_RGAT) return d <= 64 && (heads == 1 || ((heads == 2 || heads == 4) && d % (4 * heads) == 0));
-    if (layer == RGNN_LAYER_RGCN) return sched_rows_bf16(dtype, d) || (d <= 64 && single_pairs >= kBatchedMin);
+    if (layer == RGNN_LAYER_RGAT) return heads == 1 || (d <= 64 && (heads == 2 || heads == 4) && d % (4 * heads) == 0);
+    if (layer == RGNN_LAYER_RGCN) return sched_rows_bf16(dtype, d) || single_pairs >= kBatchedMin;
     return false;
 }
 // HGT: the key and message linears of the nodes are folded into the per-relation weights when every relation's

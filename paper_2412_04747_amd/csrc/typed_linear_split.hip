@@ -20,6 +20,10 @@
 // 1.43M pairs of 60 relations: forward 0.52 -> 0.31 ms (4.7 TB/s), backward (two kernels before, dY read
 // twice) 1.18 -> 0.61 ms (3.6 TB/s; the loading wavefronts' chain of waits, splits and LDS writes per unit).
 //
+// Row selector (RGAT with one head, RGCN): rows of single-edge pairs come straight from the destinations' gradient rows, as in
+// typed_linear.hip.  With 77 % such pairs, 716k in all: this kernel 307 -> 321 us, RGAT's edge walk 189 -> 143 us, RGCN's pair
+// walk 139 -> 52 us; at 68k pairs 48 -> 50, 31 -> 26 and 14 -> 10.
+//
 // A workgroup takes a chunk of 64-row tiles in units of 32 rows, one workgroup per compute unit, its wavefronts specialised:
 //   4 load:     rows of unit u + 1 from registers (fetched two units ahead) split into planes in LDS, result rows of unit
 //               u - 1 from LDS to memory
@@ -129,10 +133,10 @@ __device__ __forceinline__ float4* stage_at(unsigned char* st, int row, int piec
 }
 
 // One 32 x 32 block (rows of the unit x this wavefront's 32 columns `band`) of rows times W, to the result tile:
-// planes of the rows at `t`, of W in w; slow: from memory, with wp[k * WK] = W's operand and xp[k] = the row of lane m.
+// planes of the rows at `t`, of W in w; slow: from memory, with wp[k * WK] = W's operand and xs * xp[k] = the row of lane m.
 template <int WK>
 __device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16x8 (&w)[3][8], unsigned char* st, int band, int m, int kh,
-                                              bool slow, const float* wp, const float* xp) {
+                                              bool slow, const float* wp, const float* xp, float xs = 1.f) {
     v16f d, d1;                                            // two chains of matrix instructions
 #pragma unroll
     for (int v = 0; v < 16; ++v) d[v] = d1[v] = 0.f;
@@ -165,7 +169,7 @@ __device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16
                 for (int e = 0; e < 16; ++e) wv[e] = wp[(size_t)(k + e) * WK];
             }
 #pragma unroll
-            for (int e = 0; e < 16; ++e) d = mfma32(wv[e], xv[e], d);
+            for (int e = 0; e < 16; ++e) d = mfma32(wv[e], xv[e] * xs, d);
         }
     }
     // d[v] = result[row m][column band * 32 + 8 (v / 4) + 4 kh + v % 4]
@@ -335,12 +339,25 @@ struct BwdArgs {
     const float* rowscale;   // RS: dXrow[i] += rowscale[i] * vec[seg], and the slot's vector part is sum rowscale[i] X[g(i)]
     const float* vec;
     float* part;             // slots of D * D + D floats
+    // SEL: row i of dY is dY[ysel[i]], or, when the top bit of ysel[i] is set, row ysel[i] & 0x7FFFFFFF of dY_alt times a
+    // scale: with RS that of the pair (rowscale, scale) = ds_yscale[i], otherwise yscale[i] (null: 1)
+    const int32_t* ysel;
+    const float* dY_alt;
+    const float2* ds_yscale;
+    const float* yscale;
 };
+__device__ __forceinline__ const float* selected_row(const BwdArgs& a, int sl) { return (sl < 0 ? a.dY_alt : a.dY) + (size_t)(sl & 0x7FFFFFFF) * D; }
+template <bool RS>
+__device__ __forceinline__ float selected_scale(const BwdArgs& a, int row, int sl) {
+    // (without scales the load goes to the selectors, any bits, and is not used: no conditional load)
+    const float sc = RS ? a.ds_yscale[row].y : (a.yscale ? a.yscale : reinterpret_cast<const float*>(a.ysel))[row];
+    return sl < 0 && (RS || a.yscale) ? sc : 1.f;
+}
 constexpr int SLOT = D * D + D;
 struct RowOf { int to; float s; };           // destination and rowscale of a row on its way through the pipeline
 constexpr int BUF = 6 * PLANE;               // planes of a unit: X, then dY
 
-template <bool GATHER, bool BOTH, bool RS>
+template <bool GATHER, bool BOTH, bool RS, bool SEL>
 __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, float4* avb, float4* vec_of, RowOf* row_of, int* bad, int u0, int u1) {
     constexpr int DEPTH = 2;                               // units in flight per thread: 64 KB per compute unit
     const int tid = threadIdx.x & 255;
@@ -348,26 +365,30 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
     Units units(a.t, u0 >> 1, u1 >> 1);
     unsigned char* const St = lds + 2 * BUF;
     float4 xr[DEPTH][4], yr[DEPTH][4], av = make_float4(0.f, 0.f, 0.f, 0.f);
-    int gi[2 * DEPTH][4];                                  // indices run further ahead (see the forward)
-    float rs[DEPTH][4];
+    // Lane j of a wavefront keeps the index, selector and scales of row jrow, its row j of the eight that the wavefront loads
+    // (a register instead of four), and hands them to the 32 lanes of that row.
+    const int lane = tid & 63, half = lane >> 5, jrow = 2 * (tid >> 6) + (lane & 1) + 8 * ((lane >> 1) & 3);
+    int gi[2 * DEPTH], yi[2 * DEPTH];                      // indices run further ahead (see the forward)
+    float rs[DEPTH], sc[DEPTH];
     rgnn_v4f xv[DEPTH];                                    // RS: columns of vec[seg], through LDS to the threads that store
     auto fetch_idx = [&](int p, int u) {
         const Unit n = units.get(min(u, u1 - 1));
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1);      // (an empty second half: the tile's last row)
-            gi[p][k] = GATHER ? a.gather[row] : row;
-        }
+        const int row = n.row0 + min(jrow, n.rows - 1);    // (an empty second half: the tile's last row)
+        gi[p] = GATHER ? a.gather[row] : row;
+        yi[p] = SEL ? a.ysel[row] : row;
     };
     auto fetch = [&](int p, int q, int u) {
         const Unit n = units.get(min(u, u1 - 1));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1);
-            xr[p][k] = *reinterpret_cast<const float4*>(a.X + (size_t)gi[q][k] * D + ld.c4 * 4);
-            yr[p][k] = *reinterpret_cast<const float4*>(a.dY + (size_t)(BOTH ? gi[q][k] : row) * a.ldd + ld.c4 * 4);
-            rs[p][k] = RS ? a.rowscale[row] : 0.f;
+            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1), g = GATHER ? __shfl(gi[q], half + 2 * k) : row;
+            xr[p][k] = *reinterpret_cast<const float4*>(a.X + (size_t)g * D + ld.c4 * 4);
+            const float* const y = SEL ? selected_row(a, __shfl(yi[q], half + 2 * k)) : a.dY + (size_t)(BOTH ? g : row) * a.ldd;
+            yr[p][k] = *reinterpret_cast<const float4*>(y + ld.c4 * 4);
         }
+        const int row = n.row0 + min(jrow, n.rows - 1);
+        rs[p] = RS ? (SEL ? a.ds_yscale[row].x : a.rowscale[row]) : 0.f;
+        sc[p] = SEL ? selected_scale<RS>(a, row, yi[q]) : 1.f;
         if (RS) xv[p] = *reinterpret_cast<const rgnn_v4f*>(a.vec + (size_t)n.seg * D + ld.c4 * 4);
     };
 #pragma unroll
@@ -426,16 +447,24 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
                 if (RS && tid < 32) *reinterpret_cast<rgnn_v4f*>(vec_of + ((u + 1) & 3) * 32 + tid) = xv[p % DEPTH];
                 Range seen;
                 float4 au = make_float4(0.f, 0.f, 0.f, 0.f);     // the unit's share first: fewer roundings at the sum's magnitude
+                if (RS && lane < 8) row_of[((u + 1) & 3) * UNIT + jrow].s = rs[p % DEPTH];
+                if (BOTH && lane < 8) row_of[((u + 1) & 3) * UNIT + jrow].to = gi[p];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const bool ok = u + 1 < u1 && ld.lr + 8 * k < n.rows;
-                    if (RS && ld.c4 == 0) row_of[((u + 1) & 3) * UNIT + ld.lr + 8 * k].s = rs[p % DEPTH][k];
-                    if (BOTH && ld.c4 == 0) row_of[((u + 1) & 3) * UNIT + ld.lr + 8 * k].to = gi[p][k];
                     float4 x = xr[p % DEPTH][k];
                     if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (RS) fma4(au, ok ? rs[p % DEPTH][k] : 0.f, x);
+                    if (RS) {
+                        const float r = __shfl(rs[p % DEPTH], half + 2 * k);
+                        fma4(au, ok ? r : 0.f, x);
+                    }
                     ld.put(t, k, x, ok, seen);
-                    ld.put(t + 3 * PLANE, k, yr[p % DEPTH][k], ok, seen);
+                    float4 y = yr[p % DEPTH][k];
+                    if (SEL) {
+                        const float s = __shfl(sc[p % DEPTH], half + 2 * k);
+                        y = make_float4(y.x * s, y.y * s, y.z * s, y.w * s);
+                    }
+                    ld.put(t + 3 * PLANE, k, y, ok, seen);
                 }
                 if (RS) fma4(av, 1.f, au);
                 if (seen.outside()) bad[(u + 1) & 3] = 1;
@@ -446,7 +475,7 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
     }
 }
 
-template <bool GATHER, bool BOTH>
+template <bool GATHER, bool BOTH, bool RS, bool SEL>
 __device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
     unsigned char* const St = lds + 2 * BUF;
@@ -473,12 +502,18 @@ __device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* ld
         if (n.rows <= 0) continue;
         const bool slow = wbad || bad[u & 3];
         const int r = n.row0 + min(m, n.rows - 1);
-        multiply_rows<1>(lds + (u & 1) * BUF + 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp,
-                         a.dY + (size_t)(BOTH && slow ? a.gather[r] : r) * a.ldd);
+        const float* xp = a.dY + (size_t)(BOTH && slow ? a.gather[r] : r) * a.ldd;
+        float xs = 1.f;
+        if (SEL && slow) {
+            const int sl = a.ysel[r];
+            xp = selected_row(a, sl);
+            xs = selected_scale<RS>(a, r, sl);
+        }
+        multiply_rows<1>(lds + (u & 1) * BUF + 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp, xp, xs);
     }
 }
 
-template <bool GATHER, bool BOTH>
+template <bool GATHER, bool BOTH, bool RS, bool SEL>
 __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = (threadIdx.x >> 6) & 3, m = lane & 31, kh = lane >> 5;
     // Transposing reads: the 16-column groups g and g + 4 of the 128 form a 32 x 32 block (see the bf16 backward); this
@@ -550,16 +585,20 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
             }
         } else {
             const int f = (m & 15) + 64 * (m >> 4);
-            const int gm = GATHER ? a.gather[n.row0 + min(m, n.rows - 1)] : 0;      // of row m of the unit
+            const int rm = n.row0 + min(m, n.rows - 1);
+            const int gm = GATHER ? a.gather[rm] : 0, ym = SEL ? a.ysel[rm] : 0;    // of row m of the unit
+            const float sm = SEL ? selected_scale<RS>(a, rm, ym) : 1.f;
 #pragma unroll 1
             for (int k = 0; k < UNIT; k += 8) {
                 float x[4], y[4][4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int q = min(k + 2 * j + kh, n.rows - 1), r = n.row0 + q, g = GATHER ? __shfl(gm, q) : r;
+                    const float* const yp = SEL ? selected_row(a, __shfl(ym, q)) : a.dY + (size_t)(BOTH ? g : r) * a.ldd;
+                    const float s = SEL ? __shfl(sm, q) : 1.f;
                     x[j] = a.X[(size_t)g * D + 16 * band + f];
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) y[j][b] = a.dY[(size_t)(BOTH ? g : r) * a.ldd + f + 16 * b];
+                    for (int b = 0; b < 4; ++b) y[j][b] = yp[f + 16 * b] * s;
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -572,10 +611,10 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
     }
 }
 
-// GATHER: X rows through the list; BOTH: dY rows and dXrow rows as well
-template <bool GATHER, bool BOTH, bool RS>
+// GATHER: X rows through the list; BOTH: dY rows and dXrow rows as well; SEL: dY rows through the row selector
+template <bool GATHER, bool BOTH, bool RS, bool SEL = false>
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) void typed_linear_split_bwd_kernel(BwdArgs a) {
-    static_assert(!(BOTH && RS) && (GATHER || !BOTH), "combinations the layers use");
+    static_assert(!(BOTH && (RS || SEL)) && (GATHER || !BOTH), "combinations the layers use");
     extern __shared__ __align__(16) unsigned char lds[];   // [2] plane buffers, [2] result tiles, [2][8][32] float4 vector sums
     __shared__ int bad[4];
     __shared__ RowOf row_of[4 * UNIT];
@@ -584,9 +623,9 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH>(a, lds, bad, u0, u1);
-    else if (threadIdx.x < 512) bwd_gradient<GATHER, BOTH>(a, lds, bad, u0, u1);
-    else bwd_load<GATHER, BOTH, RS>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF + 2 * STAGE), vec_of, row_of, bad, u0, u1);
+    if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH, RS, SEL>(a, lds, bad, u0, u1);
+    else if (threadIdx.x < 512) bwd_gradient<GATHER, BOTH, RS, SEL>(a, lds, bad, u0, u1);
+    else bwd_load<GATHER, BOTH, RS, SEL>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF + 2 * STAGE), vec_of, row_of, bad, u0, u1);
 }
 
 TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
@@ -602,14 +641,15 @@ rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
-template <bool GATHER, bool BOTH, bool RS>
+template <bool GATHER, bool BOTH, bool RS, bool SEL = false>
 rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, const TileList& t, hipStream_t st) {
     const size_t lds = 2 * BUF + 2 * STAGE + 2 * 256 * sizeof(float4);
-    auto kern = typed_linear_split_bwd_kernel<GATHER, BOTH, RS>;
+    auto kern = typed_linear_split_bwd_kernel<GATHER, BOTH, RS, SEL>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(768), lds, st,
-                       BwdArgs{tile_args(t), a.X, a.gather, a.W, a.dY, a.dy_stride * D, a.dXrow, a.rowscale, a.vec, a.part});
+                       BwdArgs{tile_args(t), a.X, a.gather, a.W, a.dY, a.dy_stride * D, a.dXrow, a.rowscale, a.vec, a.part, a.ysel, a.dY_alt,
+                               a.ds_yscale, a.yscale});
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -627,10 +667,12 @@ rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
 rgnn_status_t typed_linear_split_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
     const TileList& t = *a.tiles;
     const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
-    if (a.ysel) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: no row selector at width 128");
+    if (a.ysel && (dg || !g || rs || a.dy_stride != 1 || a.hcoef || !a.dY_alt || (a.ds_yscale ? !a.vec || a.yscale : a.vec != nullptr)))
+        RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: the row selector needs gathered X, ungathered dY, and vec with the (rowscale, scale) pairs or neither; no heads at width 128");
     if (dg != sc) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY gathered and dXrow scattered must go together");
     if (rs && (dg || !g || !a.vec)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: rowscale needs vec, gathered X and ungathered dY");
     if (t.num_tiles == 0) return RGNN_OK;
+    if (a.ysel) return a.ds_yscale ? launch_bwd<true, false, true, true>(a, t, st) : launch_bwd<true, false, false, true>(a, t, st);
     if (rs) return launch_bwd<true, false, true>(a, t, st);
     if (dg) return launch_bwd<true, true, false>(a, t, st);
     if (g) return launch_bwd<true, false, false>(a, t, st);

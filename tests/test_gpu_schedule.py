@@ -101,10 +101,12 @@ def test_rgcn_bf16_forced_alternatives(flags):
 
 @pytest.mark.parametrize("k,d,norm,dtype", [(k, d, n, "f32") for k, d in ((32, 32), (64, 64), (32, 64), (64, 32))
                                             for n in ("in_degree_per_rel", "none")] +
-                         [(d, d, "in_degree_per_rel", "bf16") for d in (32, 64)])
+                         [(d, d, "in_degree_per_rel", "bf16") for d in (32, 64)] +
+                         [(128, 128, n, m) for n in ("in_degree_per_rel", "none") for m in ("f32", "f32 small")])
 def test_rgcn_row_select(k, d, norm, dtype):
-    """Widths up to 64: the rows of the single-edge pairs are read from the destinations' gradient rows.  Products and sums
-    are those of the plain walk in the same order, so the gradients are the same bits; and they are the oracle's."""
+    """fp32 rows: the rows of the single-edge pairs are read from the destinations' gradient rows.  Products and sums
+    are those of the plain walk in the same order, so the gradients are the same bits; and they are the oracle's.  (small:
+    some rows hold values below 2^-110, which take the fp32 matrix instructions at width 128.)"""
     import torch
     from paper_2412_04747_amd import binding as B
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
@@ -115,6 +117,9 @@ def test_rgcn_row_select(k, d, norm, dtype):
     p = synth.rgcn_params(rng, N, R, k, d, self_loop=True)
     if dtype == "bf16":
         p = {n: synth.round_to_bf16(v) for n, v in p.items()}
+    if dtype == "f32 small":
+        dtype = "f32"
+        p["dOut"][::101] *= np.float32(2.0 ** -114)
     g = Graph(N, R, src, dst, rel)
     want = O.rgcn_fwd(N, src, dst, rel, p["X"], p["W"], p["W0"], norm, "none")
     wg = O.rgcn_bwd(N, src, dst, rel, p["X"], p["W"], p["W0"], p["dOut"], norm, "none", out=want)
@@ -123,6 +128,35 @@ def test_rgcn_row_select(k, d, norm, dtype):
         L = RgcnLayer(g, d, norm, "none", True, dtype=dtype, flags=flags, d_in=k)
         assert B.rgnn_schedule(g.handle, B.RGNN_LAYER_RGCN, L.desc)["row_select"] == (flags == 0)
         L.load(p["X"], p["W"], p["W0"], p["dOut"])
+        L.fwd(); L.bwd()
+        torch.cuda.synchronize()
+        got.append({n: v.clone() for n, v in L.grads().items()})
+        for n, v in L.grads().items():
+            check(v, wg[n], TOL_F32, n)
+    for n in got[0]:
+        assert torch.equal(got[0][n], got[1][n]), n
+    g.close()
+
+
+@pytest.mark.parametrize("small", [False, True])
+def test_rgat_row_select_of_width_128(small):
+    """As above for RGAT with one head, whose rows also carry a rank-1 term."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    N, R, E, d = 3001, 5, 15013, 128
+    rng, src, dst, rel, _ = _hub_graph(761, N, R, E)
+    print(f"schedule case rgat row select d={d} small={small}", flush=True)
+    p = synth.rgat_params(rng, N, R, d, d)
+    if small:
+        p["dOut"][::101] *= np.float32(2.0 ** -114)
+    g = Graph(N, R, src, dst, rel)
+    wg = O.rgat_bwd(N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    got = []
+    for flags in (0, B.RGNN_FLAG_NO_ROW_SELECT):
+        L = RgatLayer(g, d, flags=flags)
+        assert B.rgnn_schedule(g.handle, B.RGNN_LAYER_RGAT, L.desc)["row_select"] == (flags == 0)
+        L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
         L.fwd(); L.bwd()
         torch.cuda.synchronize()
         got.append({n: v.clone() for n, v in L.grads().items()})
