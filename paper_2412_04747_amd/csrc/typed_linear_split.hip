@@ -17,21 +17,24 @@
 //
 // Why: at width 128 a row costs 32 kflop per product against 1.5 KB of traffic, twice what the fp32 matrix cores do in the time
 // the rows need.  (RGAT's and RGCN's forward stay on those: the sign of a result selects a branch of their backward.)
-// 1.43M pairs of 60 relations: forward 0.52 -> 0.31 ms (4.7 TB/s), backward (two kernels before, dY read
-// twice) 1.18 -> 0.61 ms (3.6 TB/s; the loading wavefronts' chain of waits, splits and LDS writes per unit).
+// 1.43M pairs of 60 relations: forward 0.52 -> 0.30 ms (4.8 TB/s), backward (two kernels before, dY read
+// twice) 1.18 -> 0.54 ms (4.1 TB/s; without its matrix instructions and stores, which mostly run beside the loading
+// wavefronts' chain of waits, splits and LDS writes, it would be 0.37).
 //
 // Row selector (RGAT with one head, RGCN): rows of single-edge pairs come straight from the destinations' gradient rows, as in
-// typed_linear.hip.  With 77 % such pairs, 716k in all: this kernel 307 -> 321 us, RGAT's edge walk 189 -> 143 us, RGCN's pair
+// typed_linear.hip.  With 77 % such pairs, 716k in all: this kernel 307 -> 321 us (before the stores moved), RGAT's edge walk 189 -> 143 us, RGCN's pair
 // walk 139 -> 52 us; at 68k pairs 48 -> 50, 31 -> 26 and 14 -> 10.
 //
 // A workgroup takes a chunk of 64-row tiles in units of 32 rows, one workgroup per compute unit, its wavefronts specialised:
-//   4 load:     rows of unit u + 1 from registers (fetched two units ahead) split into planes in LDS, result rows of unit
-//               u - 1 from LDS to memory
-//   4 multiply: dXrow = dY W^T (forward: Y = X W); a wavefront keeps 32 rows (columns) of W as planes in 96 registers
+//   4 load:     rows of unit u + 1 from registers (fetched two units ahead) split into planes in LDS
+//   4 multiply: dXrow = dY W^T (forward: Y = X W); a wavefront keeps 32 rows (columns) of W as planes in 96 registers and
+//               stores its columns of the result itself, in whole 128-byte lines (handed back through LDS to the loading
+//               wavefronts, whose chain the kernel waits for, the stores made the backward 0.61 ms with the rows of every
+//               pair in one tensor, 0.65 with the row selector; now 0.54 with it)
 //   4 multiply (backward only): the weight gradient X^T dY, whose row contraction reads the planes through the transposing
 //               LDS read ds_read_b64_tr_b16
-// Planes and result tiles are double-buffered and one barrier per unit separates the stages, so that splitting, matrix
-// products and stores of neighbouring units overlap (with all wavefronts going through the phases together the backward took
+// The planes are double-buffered and one barrier per unit separates the stages, so that splitting and matrix
+// products of neighbouring units overlap (with all wavefronts going through the phases together the backward took
 // 0.70 ms at the sizes above, 15,400 clocks per 64 rows of which the matrix instructions are 6,100).
 // A plane is [32 rows][256 bytes], piece c (16 bytes) of row r at c ^ swz(r), as in the bf16 backward.
 #include "rgnn_internal.h"
@@ -49,7 +52,6 @@ typedef __attribute__((address_space(3))) v4s* lds_v4s;
 constexpr int D = 128;
 constexpr int UNIT = 32;                     // rows of a unit
 constexpr int PLANE = UNIT * 2 * D;          // bytes of one plane of a unit
-constexpr int STAGE = UNIT * 4 * D;          // bytes of a result tile
 constexpr float kSplitMax = 3.38e38f;        // largest magnitude whose bf16 rounding is finite
 constexpr unsigned kSplitMin = 17u << 23;    // bits of 2^-110: smallest magnitude above zero that three planes hold exactly
 
@@ -89,13 +91,14 @@ struct Units {
 };
 
 // Two products of three-plane operands, the six plane products of each in turn, so that no matrix instruction waits for the
-// one before it.
+// one before it.  ORDER: which operand's low plane comes first.
+template <int ORDER>
 __device__ __forceinline__ void mfma_split2(const bf16x8 (&a)[3], const bf16x8 (&b)[3], v16f& c, const bf16x8 (&a1)[3], const bf16x8 (&b1)[3], v16f& c1) {
-    constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};      // the small products first
+    constexpr int p[2][6] = {{0, 2, 1, 0, 1, 0}, {2, 0, 1, 1, 0, 0}};          // the small products first
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-        c = mfma16(a[pa[i]], b[pb[i]], c);
-        c1 = mfma16(a1[pa[i]], b1[pb[i]], c1);
+        c = mfma16(a[p[ORDER][i]], b[p[1 - ORDER][i]], c);
+        c1 = mfma16(a1[p[ORDER][i]], b1[p[1 - ORDER][i]], c1);
     }
 }
 
@@ -127,22 +130,20 @@ struct Loader {
     }
 };
 
-// Rows of a result tile: [32][512 bytes], 16-byte piece p of row r at p ^ (r & 15).
-__device__ __forceinline__ float4* stage_at(unsigned char* st, int row, int piece) {
-    return reinterpret_cast<float4*>(st + row * 512 + ((piece ^ (row & 15)) << 4));
-}
-
-// One 32 x 32 block (rows of the unit x this wavefront's 32 columns `band`) of rows times W, to the result tile:
-// planes of the rows at `t`, of W in w; slow: from memory, with wp[k * WK] = W's operand and xs * xp[k] = the row of lane m.
-template <int WK>
-__device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16x8 (&w)[3][8], unsigned char* st, int band, int m, int kh,
-                                              bool slow, const float* wp, const float* xp, float xs = 1.f) {
+// One 32 x 32 block (rows of the unit x this wavefront's 32 columns) of rows times W, d[v] = result[row 8 (v / 4) + 4 kh +
+// v % 4][column m]: planes of the rows at `t`, of W in w; slow: from memory, with wp[k * WK] = W's operand and the row of lane
+// m as row_at() says (pointer and scale).
+struct RowAt { const float* p; float scale; };
+template <int WK, typename F>
+__device__ __forceinline__ v16f multiply_rows(const unsigned char* t, const bf16x8 (&w)[3][8], int m, int kh, bool slow, const float* wp, F row_at) {
     v16f d, d1;                                            // two chains of matrix instructions
 #pragma unroll
     for (int v = 0; v < 16; ++v) d[v] = d1[v] = 0.f;
     if (!slow) {
-        const unsigned char* row = t + m * 256;
-        const int sw = (kh ^ swz(m)) << 4;
+        int rm = m;
+        asm volatile("" : "+v"(rm));                       // (the places in LDS are formed here, not kept across the unit loop)
+        const unsigned char* row = t + rm * 256;
+        const int sw = (kh ^ swz(rm)) << 4;
 #pragma unroll
         for (int s = 0; s < 8; s += 2) {
             bf16x8 x[2][3], ws[2][3];
@@ -153,29 +154,57 @@ __device__ __forceinline__ void multiply_rows(const unsigned char* t, const bf16
                     x[j][q] = *reinterpret_cast<const bf16x8*>(row + q * PLANE + (sw ^ ((s + j) << 5)));
                     ws[j][q] = w[q][s + j];
                 }
-            mfma_split2(ws[0], x[0], d, ws[1], x[1], d1);
+            mfma_split2<1>(x[0], ws[0], d, x[1], ws[1], d1);
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) d[v] += d1[v];
     } else {
         // (the order of k is free: a half of the wavefront takes k = 64 kh + 0..63, 16 of them in flight)
+        const RowAt x = row_at();
 #pragma unroll 1
         for (int k = 64 * kh; k < 64 * kh + 64; k += 16) {
             float wv[16], xv[16];
-            load_cols(xp + k, xv);
+            load_cols(x.p + k, xv);
             if constexpr (WK == 1) load_cols(wp + k, wv);
             else {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) wv[e] = wp[(size_t)(k + e) * WK];
             }
 #pragma unroll
-            for (int e = 0; e < 16; ++e) d = mfma32(wv[e], xv[e] * xs, d);
+            for (int e = 0; e < 16; ++e) d = mfma32(xv[e] * x.scale, wv[e], d);
         }
     }
-    // d[v] = result[row m][column band * 32 + 8 (v / 4) + 4 kh + v % 4]
+    return d;
+}
+
+// The block's rows r < rows to memory: row r at out + to[r] * ld (TO) or out + r * ld, where `out` points at the lane's column,
+// with s[r] * vcol added (RS).  The wavefront writes whole 128-byte lines, two rows per store.
+template <bool TO, bool RS>
+__device__ __forceinline__ void store_rows(const v16f& d, float* out, int rows, int kh, int ld, const int* to, const float* s, float vcol) {
+    const bool full = rows == UNIT;
+    int at = 4 * kh * ld;
+    asm volatile("" : "+v"(at));                           // (the rows' places are formed here, not kept across the unit loop)
+    float* const mine = out + at;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-        *stage_at(st, m, band * 8 + 2 * q + kh) = make_float4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+    for (int q = 0; q < 4; ++q) {
+        const int r = 8 * q + 4 * kh;
+        int t[4];
+        float sv[4];
+        if (TO) {
+            const int4 t4 = *reinterpret_cast<const int4*>(to + r);
+            t[0] = t4.x; t[1] = t4.y; t[2] = t4.z; t[3] = t4.w;
+        }
+        if (RS) {
+            const float4 s4 = *reinterpret_cast<const float4*>(s + r);
+            sv[0] = s4.x; sv[1] = s4.y; sv[2] = s4.z; sv[3] = s4.w;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float y = d[4 * q + j];
+            if (RS) y += sv[j] * vcol;
+            if (full || r + j < rows) __builtin_nontemporal_store(y, TO ? out + (size_t)t[j] * ld : mine + (8 * q + j) * ld);
+        }
+    }
 }
 
 // planes of eight values
@@ -211,12 +240,11 @@ struct FwdArgs {
 };
 
 template <bool SCATTER>
-__device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
+__device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* row_to, int* bad, int u0, int u1) {
     constexpr int DEPTH = 3;                               // units in flight per thread: 48 KB per compute unit
     const int tid = threadIdx.x & 255;
     const Loader ld(tid);
     Units units(a.t, u0 >> 1, u1 >> 1);
-    unsigned char* const St = lds + 2 * 3 * PLANE;
     // Rows are asked for DEPTH units before they are used, and their indices DEPTH units before that: loads complete in issue
     // order, so an index that is needed while newer rows are under way must be older than all rows that are not needed yet.
     float4 xr[DEPTH][4];
@@ -236,61 +264,46 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
     for (int p = 0; p < 2 * DEPTH; ++p) fetch_idx(p, u0 + p);
 #pragma unroll
     for (int p = 0; p < DEPTH; ++p) fetch(p, p);
-    int gout[2][4];                                        // destination rows of the units u and u - 1
-#pragma unroll
-    for (int k = 0; k < 4; ++k) gout[0][k] = gout[1][k] = 0;
-    for (int ub = u0 - 1; ub <= u1; ub += 2 * DEPTH) {
-#pragma unroll
-        for (int p = 0; p < 2 * DEPTH; ++p) {
-            const int u = ub + p;
-            if (u > u1) break;
-            __syncthreads();
-            clear_flag(bad, u, tid);
-            if (u - 1 >= u0) {                             // result rows of the unit before
-                const Unit n = units.get(u - 1);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int r = ld.lr + 8 * k;
-                    const bool ok = r < n.rows;
-                    float4 y = *stage_at(St + ((u - 1) & 1) * STAGE, r, ld.c4);
-                    if (ok) {
-                        float* o = a.Y + (SCATTER ? (size_t)gout[1][k] : (size_t)(n.row0 + r)) * a.ldy + ld.c4 * 4;
-                        const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
-                        __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
-                    }
-                }
-            }
+    auto step = [&](int p, int u) __attribute__((always_inline)) {
+        __syncthreads();
+        clear_flag(bad, u, tid);
+        // (every load of the loop is unconditional, past the end it repeats the last unit: were one skipped on some path,
+        // the waits would have to assume it everywhere and drain the rows under way)
+        {
+            const Unit n = units.get(min(u + 1, u1 - 1));
+            unsigned char* const t = lds + ((u + 1) & 1) * 3 * PLANE;
+            Range seen;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                gout[1][k] = gout[0][k];
-                gout[0][k] = gi[p][k];
+                if (SCATTER && ld.c4 == 0) row_to[((u + 1) & 3) * UNIT + ld.lr + 8 * k] = gi[p][k];
+                ld.put(t, k, xr[p % DEPTH][k], ld.lr + 8 * k < n.rows, seen);
             }
-            // (every load of the loop is unconditional, past the end it repeats the last unit: were one skipped on some path,
-            // the waits would have to assume it everywhere and drain the rows under way)
-            {
-                const Unit n = units.get(min(u + 1, u1 - 1));
-                unsigned char* const t = lds + ((u + 1) & 1) * 3 * PLANE;
-                Range seen;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) ld.put(t, k, xr[p % DEPTH][k], ld.lr + 8 * k < n.rows, seen);
-                if (seen.outside()) bad[(u + 1) & 3] = 1;
-                fetch_idx(p, u + 1 + 2 * DEPTH);
-                fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH));
-            }
+            if (seen.outside()) bad[(u + 1) & 3] = 1;
+            fetch_idx(p, u + 1 + 2 * DEPTH);
+            fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH));
         }
+    };
+    // (whole rounds of the ring without an exit inside: see the backward)
+    int u = u0 - 1;
+    for (; u + 2 * DEPTH - 1 < u1; u += 2 * DEPTH) {
+#pragma unroll
+        for (int p = 0; p < 2 * DEPTH; ++p) step(p, u + p);
     }
+#pragma unroll
+    for (int p = 0; p < 2 * DEPTH - 1; ++p)
+        if (u + p < u1) step(p, u + p);
 }
 
-__device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
+template <bool SCATTER>
+__device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* lds, const int* row_to, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
-    unsigned char* const St = lds + 2 * 3 * PLANE;
     Units units(a.t, u0 >> 1, u1 >> 1);
     bf16x8 w[3][8];
     int cur_seg = -1;
     bool wbad = false;
-    for (int u = u0 - 1; u <= u1; ++u) {
+    for (int u = u0 - 1; u < u1; ++u) {
         __syncthreads();
-        if (u < u0 || u >= u1) continue;
+        if (u < u0) continue;
         const Unit n = units.get(u);
         const float* const wp = a.W + (size_t)n.seg * D * D + band * 32 + m;
         if (n.seg != cur_seg) {
@@ -307,23 +320,26 @@ __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* ld
         }
         if (n.rows <= 0) continue;
         const bool slow = wbad || bad[u & 3];
-        const int r = n.row0 + min(m, n.rows - 1);
-        multiply_rows<D>(lds + (u & 1) * 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp,
-                         a.X + (size_t)(slow ? a.gather[r] : r) * D);
+        const v16f d = multiply_rows<D>(lds + (u & 1) * 3 * PLANE, w, m, kh, slow, wp, [&] {
+            return RowAt{a.X + (size_t)a.gather[n.row0 + min(m, n.rows - 1)] * D, 1.f};
+        });
+        store_rows<SCATTER, false>(d, a.Y + (SCATTER ? 0 : (size_t)n.row0 * a.ldy) + band * 32 + m, n.rows, kh, a.ldy,
+                                   row_to + (u & 3) * UNIT, nullptr, 0.f);
     }
 }
 
 // X rows through the gather list; SCATTER: Y rows as well
 template <bool SCATTER>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_split_fwd_kernel(FwdArgs a) {
-    extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes, [2] result tiles
+    extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes
     __shared__ int bad[4];
+    __shared__ __align__(16) int row_to[4 * UNIT];         // destination rows of the units on their way
     const int u0 = 2 * a.t.chunk_tile[blockIdx.x], u1 = 2 * a.t.chunk_tile[blockIdx.x + 1];
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x >= 256) fwd_load<SCATTER>(a, lds, bad, u0, u1);
-    else fwd_multiply(a, lds, bad, u0, u1);
+    if (threadIdx.x >= 256) fwd_load<SCATTER>(a, lds, row_to, bad, u0, u1);
+    else fwd_multiply<SCATTER>(a, lds, row_to, bad, u0, u1);
 }
 
 // ------------------------------------------------------------------------------------------------ backward
@@ -354,23 +370,26 @@ __device__ __forceinline__ float selected_scale(const BwdArgs& a, int row, int s
     return sl < 0 && (RS || a.yscale) ? sc : 1.f;
 }
 constexpr int SLOT = D * D + D;
-struct RowOf { int to; float s; };           // destination and rowscale of a row on its way through the pipeline
+struct RowOf { int to[UNIT]; float s[UNIT]; };   // destinations and rowscales of a unit's rows on its way through the pipeline
 constexpr int BUF = 6 * PLANE;               // planes of a unit: X, then dY
 
+// A value that lane half + 2 k keeps, for the 32 lanes of that half of the wavefront (no trip through LDS).
+__device__ __forceinline__ int of_row(int v, int k, int half) {
+    const int a = __builtin_amdgcn_readlane(v, 2 * k), b = __builtin_amdgcn_readlane(v, 2 * k + 1);
+    return half ? b : a;
+}
 template <bool GATHER, bool BOTH, bool RS, bool SEL>
-__device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, float4* avb, float4* vec_of, RowOf* row_of, int* bad, int u0, int u1) {
+__device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, float4* avb, RowOf* row_of, int* bad, int u0, int u1) {
     constexpr int DEPTH = 2;                               // units in flight per thread: 64 KB per compute unit
     const int tid = threadIdx.x & 255;
     const Loader ld(tid);
     Units units(a.t, u0 >> 1, u1 >> 1);
-    unsigned char* const St = lds + 2 * BUF;
     float4 xr[DEPTH][4], yr[DEPTH][4], av = make_float4(0.f, 0.f, 0.f, 0.f);
     // Lane j of a wavefront keeps the index, selector and scales of row jrow, its row j of the eight that the wavefront loads
     // (a register instead of four), and hands them to the 32 lanes of that row.
     const int lane = tid & 63, half = lane >> 5, jrow = 2 * (tid >> 6) + (lane & 1) + 8 * ((lane >> 1) & 3);
     int gi[2 * DEPTH], yi[2 * DEPTH];                      // indices run further ahead (see the forward)
     float rs[DEPTH], sc[DEPTH];
-    rgnn_v4f xv[DEPTH];                                    // RS: columns of vec[seg], through LDS to the threads that store
     auto fetch_idx = [&](int p, int u) {
         const Unit n = units.get(min(u, u1 - 1));
         const int row = n.row0 + min(jrow, n.rows - 1);    // (an empty second half: the tile's last row)
@@ -381,15 +400,14 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
         const Unit n = units.get(min(u, u1 - 1));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1), g = GATHER ? __shfl(gi[q], half + 2 * k) : row;
+            const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1), g = GATHER ? of_row(gi[q], k, half) : row;
             xr[p][k] = *reinterpret_cast<const float4*>(a.X + (size_t)g * D + ld.c4 * 4);
-            const float* const y = SEL ? selected_row(a, __shfl(yi[q], half + 2 * k)) : a.dY + (size_t)(BOTH ? g : row) * a.ldd;
+            const float* const y = SEL ? selected_row(a, of_row(yi[q], k, half)) : a.dY + (size_t)(BOTH ? g : row) * a.ldd;
             yr[p][k] = *reinterpret_cast<const float4*>(y + ld.c4 * 4);
         }
         const int row = n.row0 + min(jrow, n.rows - 1);
         rs[p] = RS ? (SEL ? a.ds_yscale[row].x : a.rowscale[row]) : 0.f;
         sc[p] = SEL ? selected_scale<RS>(a, row, yi[q]) : 1.f;
-        if (RS) xv[p] = *reinterpret_cast<const rgnn_v4f*>(a.vec + (size_t)n.seg * D + ld.c4 * 4);
     };
 #pragma unroll
     for (int p = 0; p < 2 * DEPTH; ++p) fetch_idx(p, u0 + p);
@@ -398,92 +416,80 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
     // the vector part of a slot: the eight threads of a column group leave their sums in avb when the segment ends, and after
     // the next barrier one of them adds them in order
     int seg = -1, slot = a.t.chunk_slot[blockIdx.x] - 1, pending = -1, pending_buf = 0;
-    for (int ub = u0 - 1; ub <= u1 + 1; ub += 2 * DEPTH) {
-#pragma unroll
-        for (int p = 0; p < 2 * DEPTH; ++p) {
-            const int u = ub + p;
-            if (u > u1 + 1) break;
-            __syncthreads();
-            clear_flag(bad, u, tid);
-            if (pending >= 0 && tid < 32) {
-                float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (RS) {
-                    s = avb[pending_buf * 256 + tid];
-                    for (int r = 1; r < 8; ++r) fma4(s, 1.f, avb[pending_buf * 256 + r * 32 + tid]);
-                }
-                reinterpret_cast<float4*>(a.part + (size_t)pending * SLOT + D * D)[tid] = s;
+    auto step = [&](int p, int u) __attribute__((always_inline)) {
+        __syncthreads();
+        clear_flag(bad, u, tid);
+        if (pending >= 0 && tid < 32) {
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (RS) {
+                s = avb[pending_buf * 256 + tid];
+                for (int r = 1; r < 8; ++r) fma4(s, 1.f, avb[pending_buf * 256 + r * 32 + tid]);
             }
-            pending = -1;
-            if (u - 1 >= u0 && u - 1 < u1) {               // result rows of the unit before
-                const Unit n = units.get(u - 1);
-                float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (RS) v4 = vec_of[((u - 1) & 3) * 32 + ld.c4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int r = ld.lr + 8 * k;
-                    if (r < n.rows) {
-                        float4 y = *stage_at(St + ((u - 1) & 1) * STAGE, r, ld.c4);
-                        if (RS) fma4(y, row_of[((u - 1) & 3) * UNIT + r].s, v4);
-                        const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
-                        float* o = a.dX + (BOTH ? (size_t)row_of[((u - 1) & 3) * UNIT + r].to : (size_t)(n.row0 + r)) * D + ld.c4 * 4;
-                        __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
-                    }
-                }
-            }
-            const Unit n = units.get(min(u + 1, u1 - 1));
-            const int next_seg = u + 1 < u1 ? n.seg : -2;
-            if (next_seg != seg && u + 1 <= u1) {
-                if (seg >= 0) {
-                    pending = slot;
-                    pending_buf = u & 1;
-                    if (RS) avb[pending_buf * 256 + tid] = av;
-                    av = make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-                ++slot;
-                seg = next_seg;
-            }
-            {                                              // (unconditional loads: see the forward)
-                unsigned char* const t = lds + ((u + 1) & 1) * BUF;
-                if (RS && tid < 32) *reinterpret_cast<rgnn_v4f*>(vec_of + ((u + 1) & 3) * 32 + tid) = xv[p % DEPTH];
-                Range seen;
-                float4 au = make_float4(0.f, 0.f, 0.f, 0.f);     // the unit's share first: fewer roundings at the sum's magnitude
-                if (RS && lane < 8) row_of[((u + 1) & 3) * UNIT + jrow].s = rs[p % DEPTH];
-                if (BOTH && lane < 8) row_of[((u + 1) & 3) * UNIT + jrow].to = gi[p];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool ok = u + 1 < u1 && ld.lr + 8 * k < n.rows;
-                    float4 x = xr[p % DEPTH][k];
-                    if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (RS) {
-                        const float r = __shfl(rs[p % DEPTH], half + 2 * k);
-                        fma4(au, ok ? r : 0.f, x);
-                    }
-                    ld.put(t, k, x, ok, seen);
-                    float4 y = yr[p % DEPTH][k];
-                    if (SEL) {
-                        const float s = __shfl(sc[p % DEPTH], half + 2 * k);
-                        y = make_float4(y.x * s, y.y * s, y.z * s, y.w * s);
-                    }
-                    ld.put(t + 3 * PLANE, k, y, ok, seen);
-                }
-                if (RS) fma4(av, 1.f, au);
-                if (seen.outside()) bad[(u + 1) & 3] = 1;
-                fetch_idx(p, u + 1 + 2 * DEPTH);
-                fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH), u + 1 + DEPTH);
-            }
+            reinterpret_cast<float4*>(a.part + (size_t)pending * SLOT + D * D)[tid] = s;
         }
+        pending = -1;
+        const Unit n = units.get(min(u + 1, u1 - 1));
+        const int next_seg = u + 1 < u1 ? n.seg : -2;
+        if (next_seg != seg && u + 1 <= u1) {
+            if (seg >= 0) {
+                pending = slot;
+                pending_buf = u & 1;
+                if (RS) avb[pending_buf * 256 + tid] = av;
+                av = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+            ++slot;
+            seg = next_seg;
+        }
+        {                                              // (unconditional loads: see the forward)
+            unsigned char* const t = lds + ((u + 1) & 1) * BUF;
+            Range seen;
+            float4 au = make_float4(0.f, 0.f, 0.f, 0.f);     // the unit's share first: fewer roundings at the sum's magnitude
+            if (RS && lane < 8) row_of[(u + 1) & 3].s[jrow] = rs[p % DEPTH];
+            if (BOTH && lane < 8) row_of[(u + 1) & 3].to[jrow] = gi[p];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool ok = u + 1 < u1 && ld.lr + 8 * k < n.rows;
+                float4 x = xr[p % DEPTH][k];
+                if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (RS) {
+                    const float r = __int_as_float(of_row(__float_as_int(rs[p % DEPTH]), k, half));
+                    fma4(au, ok ? r : 0.f, x);
+                }
+                ld.put(t, k, x, ok, seen);
+                float4 y = yr[p % DEPTH][k];
+                if (SEL) {
+                    const float s = __int_as_float(of_row(__float_as_int(sc[p % DEPTH]), k, half));
+                    y = make_float4(y.x * s, y.y * s, y.z * s, y.w * s);
+                }
+                ld.put(t + 3 * PLANE, k, y, ok, seen);
+            }
+            if (RS) fma4(av, 1.f, au);
+            if (seen.outside()) bad[(u + 1) & 3] = 1;
+            fetch_idx(p, u + 1 + 2 * DEPTH);
+            fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH), u + 1 + DEPTH);
+        }
+    };
+    // (whole rounds of the ring without an exit inside: a path from the middle of a round to its beginning would make the
+    // waits there drain the rows under way)
+    int u = u0 - 1;
+    for (; u + 2 * DEPTH - 1 <= u1; u += 2 * DEPTH) {
+#pragma unroll
+        for (int p = 0; p < 2 * DEPTH; ++p) step(p, u + p);
     }
+#pragma unroll
+    for (int p = 0; p < 2 * DEPTH - 1; ++p)
+        if (u + p <= u1) step(p, u + p);
 }
 
 template <bool GATHER, bool BOTH, bool RS, bool SEL>
-__device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
+__device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* lds, const RowOf* row_of, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
-    unsigned char* const St = lds + 2 * BUF;
+    float vcol = 0.f;                                      // RS: this lane's column of vec[seg]
     Units units(a.t, u0 >> 1, u1 >> 1);
     bf16x8 w[3][8];
     int cur_seg = -1;
     bool wbad = false;
-    for (int u = u0 - 1; u <= u1 + 1; ++u) {
+    for (int u = u0 - 1; u <= u1; ++u) {
         __syncthreads();
         if (u < u0 || u >= u1) continue;
         const Unit n = units.get(u);
@@ -498,18 +504,20 @@ __device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* ld
                 split8(x, w[0][s], w[1][s], w[2][s], seen);
             }
             wbad = __any(seen.outside());
+            if (RS) {
+                vcol = a.vec[(size_t)n.seg * D + band * 32 + m];
+                asm volatile("" : "+v"(vcol));             // waited for here: at each use the wait would drain the stores under way
+            }
         }
         if (n.rows <= 0) continue;
         const bool slow = wbad || bad[u & 3];
-        const int r = n.row0 + min(m, n.rows - 1);
-        const float* xp = a.dY + (size_t)(BOTH && slow ? a.gather[r] : r) * a.ldd;
-        float xs = 1.f;
-        if (SEL && slow) {
+        const v16f d = multiply_rows<1>(lds + (u & 1) * BUF + 3 * PLANE, w, m, kh, slow, wp, [&] {
+            const int r = n.row0 + min(m, n.rows - 1);
+            if (!SEL) return RowAt{a.dY + (size_t)(BOTH ? a.gather[r] : r) * a.ldd, 1.f};
             const int sl = a.ysel[r];
-            xp = selected_row(a, sl);
-            xs = selected_scale<RS>(a, r, sl);
-        }
-        multiply_rows<1>(lds + (u & 1) * BUF + 3 * PLANE, w, St + (u & 1) * STAGE, band, m, kh, slow, wp, xp, xs);
+            return RowAt{selected_row(a, sl), selected_scale<RS>(a, r, sl)};
+        });
+        store_rows<BOTH, RS>(d, a.dX + (BOTH ? 0 : (size_t)n.row0 * D) + band * 32 + m, n.rows, kh, D, row_of[u & 3].to, row_of[u & 3].s, vcol);
     }
 }
 
@@ -529,7 +537,7 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
         for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
     Units units(a.t, u0 >> 1, u1 >> 1);
     int cur_seg = -1, slot = a.t.chunk_slot[blockIdx.x] - 1;
-    for (int u = u0 - 1; u <= u1 + 1; ++u) {
+    for (int u = u0 - 1; u <= u1; ++u) {
         __syncthreads();
         if (u < u0 || u > u1) continue;
         const Unit n = units.get(min(u, u1 - 1));
@@ -574,7 +582,7 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
                         y0[q] = tr8(yt + (at ^ (hb << 5)), yt + (at ^ (hb << 5) ^ 128) + 1024);
                         y1[q] = tr8(yt + (at ^ ((hb + 1) << 5)), yt + (at ^ ((hb + 1) << 5) ^ 128) + 1024);
                     }
-                    mfma_split2(x, y0, t0, x, y1, t1);
+                    mfma_split2<0>(x, y0, t0, x, y1, t1);
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
@@ -584,15 +592,16 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
                 }
             }
         } else {
+            constexpr int J = SEL ? 2 : 4;                 // rows in flight per half (the selector needs the registers)
             const int f = (m & 15) + 64 * (m >> 4);
             const int rm = n.row0 + min(m, n.rows - 1);
             const int gm = GATHER ? a.gather[rm] : 0, ym = SEL ? a.ysel[rm] : 0;    // of row m of the unit
             const float sm = SEL ? selected_scale<RS>(a, rm, ym) : 1.f;
 #pragma unroll 1
-            for (int k = 0; k < UNIT; k += 8) {
-                float x[4], y[4][4];
+            for (int k = 0; k < UNIT; k += 2 * J) {
+                float x[J], y[J][4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < J; ++j) {
                     const int q = min(k + 2 * j + kh, n.rows - 1), r = n.row0 + q, g = GATHER ? __shfl(gm, q) : r;
                     const float* const yp = SEL ? selected_row(a, __shfl(ym, q)) : a.dY + (size_t)(BOTH ? g : r) * a.ldd;
                     const float s = SEL ? __shfl(sm, q) : 1.f;
@@ -601,7 +610,7 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
                     for (int b = 0; b < 4; ++b) y[j][b] = yp[f + 16 * b] * s;
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < J; ++j) {
                     const bool ok = k + 2 * j + kh < n.rows;
 #pragma unroll
                     for (int b = 0; b < 4; ++b) acc[b] = mfma32(ok ? x[j] : 0.f, ok ? y[j][b] : 0.f, acc[b]);
@@ -615,24 +624,23 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
 template <bool GATHER, bool BOTH, bool RS, bool SEL = false>
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) void typed_linear_split_bwd_kernel(BwdArgs a) {
     static_assert(!(BOTH && (RS || SEL)) && (GATHER || !BOTH), "combinations the layers use");
-    extern __shared__ __align__(16) unsigned char lds[];   // [2] plane buffers, [2] result tiles, [2][8][32] float4 vector sums
+    extern __shared__ __align__(16) unsigned char lds[];   // [2] plane buffers, [2][8][32] float4 vector sums
     __shared__ int bad[4];
-    __shared__ RowOf row_of[4 * UNIT];
-    __shared__ float4 vec_of[4 * 32];
+    __shared__ __align__(16) RowOf row_of[4];
     const int u0 = 2 * a.t.chunk_tile[blockIdx.x], u1 = 2 * a.t.chunk_tile[blockIdx.x + 1];
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH, RS, SEL>(a, lds, bad, u0, u1);
+    if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH, RS, SEL>(a, lds, row_of, bad, u0, u1);
     else if (threadIdx.x < 512) bwd_gradient<GATHER, BOTH, RS, SEL>(a, lds, bad, u0, u1);
-    else bwd_load<GATHER, BOTH, RS, SEL>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF + 2 * STAGE), vec_of, row_of, bad, u0, u1);
+    else bwd_load<GATHER, BOTH, RS, SEL>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF), row_of, bad, u0, u1);
 }
 
 TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
 
 template <bool SCATTER>
 rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_t st) {
-    const size_t lds = 2 * 3 * PLANE + 2 * STAGE;
+    const size_t lds = 2 * 3 * PLANE;
     auto kern = typed_linear_split_fwd_kernel<SCATTER>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
@@ -643,7 +651,7 @@ rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_
 }
 template <bool GATHER, bool BOTH, bool RS, bool SEL = false>
 rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, const TileList& t, hipStream_t st) {
-    const size_t lds = 2 * BUF + 2 * STAGE + 2 * 256 * sizeof(float4);
+    const size_t lds = 2 * BUF + 2 * 256 * sizeof(float4);
     auto kern = typed_linear_split_bwd_kernel<GATHER, BOTH, RS, SEL>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
