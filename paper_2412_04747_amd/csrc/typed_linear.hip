@@ -58,12 +58,15 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// First tile index >= ti whose segment differs from tile ti's (or t1).
-__device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int ti, int t1) {
+// First tile index >= ti whose segment differs from tile ti's (or t1): 64 tiles per step (one after the other they cost a chunk
+// of 149 tiles some 5 us before its first row).
+__device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int ti, int t1, int lane) {
     const int seg = tile_seg[ti];
-    int e = ti + 1;
-    while (e < t1 && tile_seg[e] == seg) ++e;
-    return e;
+    for (int e = ti; e < t1; e += 64) {
+        const unsigned long long other = __ballot(tile_seg[min(e + lane, t1 - 1)] != seg);
+        if (other) return e + __builtin_ctzll(other);
+    }
+    return t1;
 }
 
 // Compile-time switches of the wave kernels.  They are template parameters rather than
@@ -75,18 +78,34 @@ __device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int
 //                                                                  s_out[row][h] over the h-th of s_heads column slices
 //   DYG      backward: dY rows are read through the list  RS       backward: rowscale / Avec / xvec in use
 //   OS       the rows of Y are OS * ND floats apart (2: the key or message half of HGT's pair rows)
+//
+// At width 128 the stage holds half of the columns at a time, so that eight wavefronts fit beside the 64 KB weight: two per
+// SIMD, one multiplying while the other stages; and the result goes to memory straight from the accumulators, a 128-byte line
+// of two rows per store.  (Four wavefronts with whole rows, result through the stage: 235 us for 702k pairs, now 205; 977 us for
+// 2.46M pairs of 500 relations, now 785.)  At 64 x 64, where the rows' bytes bound the kernel, direct stores take 186 us
+// for the 175 of whole 256-byte rows through the stage (2.1M pairs); from 32 to 64 columns 120 for 130, but 40 for 38 where
+// the rows of Y are read first (300k rows).
+template <int KD, int ND, bool VEC, bool ACCUM>
+struct FwdShape {
+    static constexpr bool HALVES = KD == 128 && !VEC;
+    static constexpr int NW = HALVES ? 8 : 4;               // wavefronts per workgroup
+    static constexpr int KS = HALVES ? KD / 2 : KD;         // columns in the stage
+    static constexpr bool DIRECT = HALVES || (KD < ND && !VEC && !ACCUM);   // result straight from the accumulators
+    static constexpr int XS = (!DIRECT && ND > KS ? ND : KS) + 4;   // row stride of the per-wave stage
+    static constexpr size_t LDS = sizeof(float) * (KD * ND + NW * 32 * XS);
+};
 template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1>
-__global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X,
-                                                                    const int32_t* __restrict__ gather,
-                                                                    const float* __restrict__ W, float* __restrict__ Y,
-                                                                    const float* __restrict__ vec,
-                                                                    float* __restrict__ s_out, int s_heads, int relu) {
-    constexpr int NW = 4;                                   // wavefronts per workgroup
-    constexpr int XS = (KD > ND ? KD : ND) + 4;             // row stride of the per-wave stage
+__global__ __launch_bounds__((64 * FwdShape<KD, ND, VEC, ACCUM>::NW))
+void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const int32_t* __restrict__ gather,
+                                  const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
+                                  float* __restrict__ s_out, int s_heads, int relu) {
+    using S = FwdShape<KD, ND, VEC, ACCUM>;
+    constexpr int NW = S::NW, XS = S::XS, KS = S::KS, PH = KD / KS;
     constexpr int CB = ND / 32;
+    constexpr bool DIRECT = S::DIRECT;
     constexpr int LPRI = KD / 4, RPI = 64 / LPRI, NX = 32 / RPI;   // input: lanes per row, rows per load, loads per unit
     constexpr int LPRO = ND / 4, RPO = 64 / LPRO, NO = 32 / RPO;
-    static_assert(!SCATTER || KD == ND, "scattered output reuses the input rows' lane mapping");
+    static_assert(!SCATTER || (KD == ND && !DIRECT), "scattered output reuses the input rows' lane mapping");
     extern __shared__ __align__(16) float smem[];
     float* Ws = smem;                                       // [KD][ND]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -95,7 +114,7 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
     const int ci = lane % LPRI, ri = lane / LPRI, co = lane % LPRO, ro = lane / LPRO;
     const int t0 = t.chunk_tile[blockIdx.x], t1 = t.chunk_tile[blockIdx.x + 1];
     for (int ta = t0; ta < t1;) {
-        const int tb = run_end(t.tile_seg, ta, t1);
+        const int tb = run_end(t.tile_seg, ta, t1, lane);
         const int seg = t.tile_seg[ta];
         const int ra = t.tile_row0[ta], rbnd = t.tile_row1[tb - 1];   // rows [ra, rbnd) of this segment
         const int nu = (rbnd - ra + 31) / 32;
@@ -108,88 +127,134 @@ __global__ __launch_bounds__(256) void typed_linear_fwd_wave_kernel(TileArgs t, 
         // lanes per head of an output row (a power of two, like the head count), and its log2
         const int lls = (31 - __clz(LPRO)) - (VEC ? 31 - __clz(s_heads) : 0), lph = 1 << lls;
         // Rows past the end of the run are clamped to its last row, so every load below is
-        // unconditional; what they bring in is never stored.
+        // unconditional; what they bring in is never stored.  LANEIDX: lane r keeps the index of row r (one register for NX)
+        // and hands it to the lanes that load the row.
+        constexpr bool LANEIDX = GATHER && KD == 128;
         v4f xr[NX];
-        int gi[NX], gcur[NX];
+        int gi[LANEIDX ? 1 : NX], gcur[SCATTER ? NX : 1];
 #define RGNN_FETCH_IDX(U)                                                           \
-    _Pragma("unroll") for (int it = 0; it < NX; ++it) {                             \
-        const int row_ = min(ra + (U) * 32 + ri + it * RPI, rbnd - 1);              \
-        gi[it] = GATHER ? gather[row_] : row_;                                      \
+    if (LANEIDX) gi[0] = gather[min(ra + (U) * 32 + m, rbnd - 1)];                  \
+    else {                                                                          \
+        _Pragma("unroll") for (int it = 0; it < NX; ++it) {                         \
+            const int row_ = min(ra + (U) * 32 + ri + it * RPI, rbnd - 1);          \
+            gi[LANEIDX ? 0 : it] = GATHER ? gather[row_] : row_;                    \
+        }                                                                           \
     }
 #define RGNN_FETCH_ROWS()                                                           \
     _Pragma("unroll") for (int it = 0; it < NX; ++it) {                             \
-        xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gi[it] * KD + ci * 4); \
-        gcur[it] = gi[it];                                                          \
+        const int g_ = LANEIDX ? __shfl(gi[0], ri + it * RPI) : gi[LANEIDX ? 0 : it]; \
+        xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)g_ * KD + ci * 4);       \
+        if (SCATTER) gcur[SCATTER ? it : 0] = g_;                                   \
     }
         RGNN_FETCH_IDX(wave)
         RGNN_FETCH_ROWS()
         RGNN_FETCH_IDX(wave + NW)
         for (int u = wave; u < nu; u += NW) {
-            int gout[NX];
+            int gout[SCATTER ? NX : 1];
+            if (SCATTER) {
 #pragma unroll
-            for (int it = 0; it < NX; ++it) {
-                *reinterpret_cast<v4f*>(Xw + (ri + it * RPI) * XS + ci * 4) = xr[it];
-                gout[it] = gcur[it];
+                for (int it = 0; it < NX; ++it) gout[SCATTER ? it : 0] = gcur[SCATTER ? it : 0];
             }
-            wave_lds_fence();
-            // (ACCUM: the rows of Y are asked for before the next unit's rows, or the wait for them would drain those: 21.4 us
-            // became 18.4 at 120k rows of width 64)
-            v4f old[ACCUM ? NO : 1];
-            if (ACCUM) {
-#pragma unroll
-                for (int it = 0; it < NO; ++it)
-                    old[ACCUM ? it : 0] = *reinterpret_cast<const v4f*>(Y + (size_t)min(ra + u * 32 + ro + it * RPO, rbnd - 1) * (OS * ND) + co * 4);
-            }
-            RGNN_FETCH_ROWS()             // unit u + NW
-            RGNN_FETCH_IDX(u + 2 * NW)
             v16f acc[CB];
 #pragma unroll
             for (int b = 0; b < CB; ++b)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+            // (ACCUM: the rows of Y are asked for before the next unit's rows, or the wait for them would drain those: 21.4 us
+            // became 18.4 at 120k rows of width 64)
+            // (the lane's place is made opaque so that the rows' addresses are formed here, not kept across the loop)
+            int at = 4 * kh * (OS * ND) + m;
+            asm volatile("" : "+v"(at));
+            const int left = rbnd - (ra + u * 32);
+            const bool full = left >= 32;
+            float* const yu = Y + (size_t)(ra + u * 32) * (OS * ND) + at;   // DIRECT: this lane's first row and column
+            float old1[ACCUM && DIRECT ? CB * 16 : 1];
+            v4f old[ACCUM && !DIRECT ? NO : 1];
+            if (ACCUM && DIRECT) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+#pragma unroll
+                    for (int b = 0; b < CB; ++b)
+                        old1[DIRECT && ACCUM ? b * 16 + v : 0] = yu[(full ? acc_row(v, 0) : min(acc_row(v, kh), left - 1) - 4 * kh) * (OS * ND) + b * 32];
+            } else if (ACCUM) {
+#pragma unroll
+                for (int it = 0; it < NO; ++it)
+                    old[ACCUM && !DIRECT ? it : 0] = *reinterpret_cast<const v4f*>(Y + (size_t)min(ra + u * 32 + ro + it * RPO, rbnd - 1) * (OS * ND) + co * 4);
+            }
+#pragma unroll
+            for (int ph = 0; ph < PH; ++ph) {
+                // columns [ph, ph + 1) * KS / 2 of both halves of k: 4 * ci = kh' * KD / 2 + ph * KS / 2 + column
+                if (PH == 1 || ((ci >> 3) & 1) == ph) {
+                    const int c = PH == 1 ? ci * 4 : (ci >> 4) * (KS / 2) + (ci & 7) * 4;
+#pragma unroll
+                    for (int it = 0; it < NX; ++it) *reinterpret_cast<v4f*>(Xw + (ri + it * RPI) * XS + c) = xr[it];
+                }
+                wave_lds_fence();
+                if (ph == PH - 1) {
+                    RGNN_FETCH_ROWS()             // unit u + NW
+                    RGNN_FETCH_IDX(u + 2 * NW)
+                }
 #pragma unroll 2
-            for (int tt = 0; tt < KD / 8; ++tt) {
-                const int k0 = kh * (KD / 2) + 4 * tt;
-                const float4 a4 = *reinterpret_cast<const float4*>(Xw + m * XS + k0);
-                const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+                for (int tt = 0; tt < KS / 8; ++tt) {
+                    const int k0 = kh * (KD / 2) + ph * (KS / 2) + 4 * tt;
+                    const float4 a4 = *reinterpret_cast<const float4*>(Xw + m * XS + kh * (KS / 2) + 4 * tt);
+                    const float av[4] = {a4.x, a4.y, a4.z, a4.w};
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int b = 0; b < CB; ++b) acc[b] = mfma32(av[i], Ws[(k0 + i) * ND + b * 32 + m], acc[b]);
+                        for (int b = 0; b < CB; ++b) acc[b] = mfma32(av[i], Ws[(k0 + i) * ND + b * 32 + m], acc[b]);
+                }
+                wave_lds_fence();             // all reads of the input rows are done before the stage is overwritten
             }
-            wave_lds_fence();             // all reads of the input rows are done before the stage is overwritten
+            if (DIRECT) {
 #pragma unroll
-            for (int b = 0; b < CB; ++b)
+                for (int v = 0; v < 16; ++v)
+                    if (full || acc_row(v, kh) < left) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) Xw[acc_row(v, kh) * XS + b * 32 + m] = acc[b][v];
-            wave_lds_fence();
-#pragma unroll
-            for (int it = 0; it < NO; ++it) {
-                const int r = ro + it * RPO, row = ra + u * 32 + r;
-                const bool ok = row < rbnd;
-                float4 y = *reinterpret_cast<const float4*>(Xw + r * XS + co * 4);
-                const size_t d = SCATTER ? (size_t)gout[it] : (size_t)min(row, rbnd - 1);
-                float4* yp = reinterpret_cast<float4*>(Y + d * (OS * ND) + co * 4);
-                if (ACCUM) {
-                    y.x += old[ACCUM ? it : 0][0]; y.y += old[ACCUM ? it : 0][1]; y.z += old[ACCUM ? it : 0][2]; y.w += old[ACCUM ? it : 0][3];
-                    if (relu) y = positive(y);
-                }
-                if (ok) {   // rows of a large tensor that is read again only after it has left the caches: non-temporal
-                    const v4f yv = {y.x, y.y, y.z, y.w};
-                    __builtin_nontemporal_store(yv, reinterpret_cast<v4f*>(yp));
-                }
-                if (VEC) {
-                    // the lanes of a head's column slice are added (the slices are aligned groups of lph lanes)
-                    float sdot = y.x * wv.x + y.y * wv.y + y.z * wv.z + y.w * wv.w;
-#pragma unroll
-                    for (int o = LPRO / 2; o > 0; o >>= 1) {
-                        const float other = __shfl_xor(sdot, o);
-                        if (o < lph) sdot += other;
+                        for (int b = 0; b < CB; ++b) {
+                            float y = acc[b][v];
+                            if (ACCUM) {
+                                y += old1[DIRECT && ACCUM ? b * 16 + v : 0];
+                                if (relu) y = y > 0.f ? y : 0.f;
+                            }
+                            __builtin_nontemporal_store(y, yu + acc_row(v, 0) * (OS * ND) + b * 32);
+                        }
                     }
-                    if (ok && (co & (lph - 1)) == 0) s_out[(size_t)row * s_heads + (co >> lls)] = sdot;
+            } else {
+#pragma unroll
+                for (int b = 0; b < CB; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) Xw[acc_row(v, kh) * XS + b * 32 + m] = acc[b][v];
+                wave_lds_fence();
+#pragma unroll
+                for (int it = 0; it < NO; ++it) {
+                    const int r = ro + it * RPO, row = ra + u * 32 + r;
+                    const bool ok = row < rbnd;
+                    float4 y = *reinterpret_cast<const float4*>(Xw + r * XS + co * 4);
+                    const size_t d = SCATTER ? (size_t)gout[SCATTER ? it : 0] : (size_t)min(row, rbnd - 1);
+                    float4* yp = reinterpret_cast<float4*>(Y + d * (OS * ND) + co * 4);
+                    if (ACCUM) {
+                        const v4f o = old[ACCUM && !DIRECT ? it : 0];
+                        y.x += o[0]; y.y += o[1]; y.z += o[2]; y.w += o[3];
+                        if (relu) y = positive(y);
+                    }
+                    if (ok) {   // rows of a large tensor that is read again only after it has left the caches: non-temporal
+                        const v4f yv = {y.x, y.y, y.z, y.w};
+                        __builtin_nontemporal_store(yv, reinterpret_cast<v4f*>(yp));
+                    }
+                    if (VEC) {
+                        // the lanes of a head's column slice are added (the slices are aligned groups of lph lanes)
+                        float sdot = y.x * wv.x + y.y * wv.y + y.z * wv.z + y.w * wv.w;
+#pragma unroll
+                        for (int o = LPRO / 2; o > 0; o >>= 1) {
+                            const float other = __shfl_xor(sdot, o);
+                            if (o < lph) sdot += other;
+                        }
+                        if (ok && (co & (lph - 1)) == 0) s_out[(size_t)row * s_heads + (co >> lls)] = sdot;
+                    }
                 }
+                wave_lds_fence();         // the stage is read out before the next unit's rows overwrite it
             }
-            wave_lds_fence();             // the stage is read out before the next unit's rows overwrite it
         }
 #undef RGNN_FETCH_IDX
 #undef RGNN_FETCH_ROWS
@@ -262,7 +327,7 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
     const int t0 = t.chunk_tile[blockIdx.x], t1 = t.chunk_tile[blockIdx.x + 1];
     int slot = t.chunk_slot[blockIdx.x];
     for (int ta = t0; ta < t1; ++slot) {
-        const int tb = run_end(t.tile_seg, ta, t1);
+        const int tb = run_end(t.tile_seg, ta, t1, lane);
         const int seg = t.tile_seg[ta];
         const int ra = t.tile_row0[ta], rbnd = t.tile_row1[tb - 1];
         const int nu = (rbnd - ra + 31) / 32;
@@ -618,11 +683,12 @@ static TileArgs tile_args(const TileList& t) {
 
 template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1>
 static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st) {
-    const size_t lds = sizeof(float) * (KD * ND + 4 * 32 * ((KD > ND ? KD : ND) + 4));
+    using S = FwdShape<KD, ND, VEC, ACCUM>;
+    constexpr size_t lds = S::LDS;
     auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, OS>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
-    hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(256), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
+    hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(64 * S::NW), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
                        a.vec, a.s_out, a.s_heads, a.relu);
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
