@@ -67,7 +67,7 @@ struct WalkArgs {
     int wide_n, wide_blocks;                              // items [0, wide_n): a wavefront each
     int general_n, skip_first, skip_n;                    // items [wide_n, skip_first) and [skip_first + skip_n, n): a lane group each
     int short_first, short_n, single_first, single_n;     // whole segments with 2..kShortLen entries / with one entry
-    int short_blocks;
+    int general_blocks, short_blocks;                     // blocks of the items before the short segments; of the short ones
     // destination-major
     const int32_t* in_pair;
     const void* KM;          // [P][2][D]
@@ -193,17 +193,6 @@ __device__ __forceinline__ int group_item(const WalkArgs& a) {
     const int i = a.wide_n + k;
     return i >= a.skip_first ? i + a.skip_n : i;
 }
-template <int D, typename T, int LPH>
-__global__ __launch_bounds__(256) void hgt_attend_fwd_kernel(WalkArgs a) {
-    constexpr int LPR = D / RowT<T>::V;
-    if ((int)blockIdx.x < a.wide_blocks) {
-        const int i = blockIdx.x * 4 + threadIdx.x / 64;
-        if (i < a.wide_n) fwd_walk<D, T, LPH, 64 / LPR>(a, i);
-    } else {
-        const int i = group_item<LPR>(a);
-        if (i >= 0) fwd_walk<D, T, LPH, 1>(a, i);
-    }
-}
 
 // Whole destinations of at most NE edges, NI of them per lane group with all their loads independent: such a
 // destination is a single batch, and alone it would leave the group waiting on its item -> pair -> row chain.
@@ -251,10 +240,19 @@ __device__ __forceinline__ void fwd_few(const WalkArgs& a, int blk, int first, i
         if (cv % LPH == 0) a.ms[(size_t)row[x] * H + head] = make_float2(f.m, f.s);
     }
 }
+// One launch for all items: the long ones first (a wavefront each), then the ordinary ones, then the short segments, which fill
+// the machine while the long ones drain.  (Two launches cost 6 us of the 31 that 300k edges take, and a tail each.)
 template <int D, typename T, int LPH>
-__global__ __launch_bounds__(256) void hgt_attend_fwd_few_kernel(WalkArgs a) {
-    const int blk = blockIdx.x;
-    if (blk < a.short_blocks) fwd_few<D, T, LPH, 2, kShortLen>(a, blk, a.short_first, a.short_n);
+__global__ __launch_bounds__(256) void hgt_attend_fwd_kernel(WalkArgs a) {
+    constexpr int LPR = D / RowT<T>::V;
+    const int blk = (int)blockIdx.x - a.general_blocks;
+    if ((int)blockIdx.x < a.wide_blocks) {
+        const int i = blockIdx.x * 4 + threadIdx.x / 64;
+        if (i < a.wide_n) fwd_walk<D, T, LPH, 64 / LPR>(a, i);
+    } else if (blk < 0) {
+        const int i = group_item<LPR>(a);
+        if (i >= 0) fwd_walk<D, T, LPH, 1>(a, i);
+    } else if (blk < a.short_blocks) fwd_few<D, T, LPH, 2, kShortLen>(a, blk, a.short_first, a.short_n);
     else fwd_few<D, T, LPH, 4, 1>(a, blk - a.short_blocks, a.single_first, a.single_n);
 }
 
@@ -342,17 +340,6 @@ __device__ __forceinline__ void bwd_walk(const WalkArgs& a, int i) {
     if (slot < 0) store_cols(static_cast<T*>(a.dQ) + v * D + cv * V, dq);
     else store_cols(a.partial + (size_t)slot * D + cv * V, dq);
 }
-template <int D, typename T, int LPH>
-__global__ __launch_bounds__(256) void hgt_attend_bwd_kernel(WalkArgs a) {
-    constexpr int LPR = D / RowT<T>::V;
-    if ((int)blockIdx.x < a.wide_blocks) {
-        const int i = blockIdx.x * 4 + threadIdx.x / 64;
-        if (i < a.wide_n) bwd_walk<D, T, LPH, 64 / LPR>(a, i);
-    } else {
-        const int i = group_item<LPR>(a);
-        if (i >= 0) bwd_walk<D, T, LPH, 1>(a, i);
-    }
-}
 
 template <int D, typename T, int LPH, int NI, int NE>
 __device__ __forceinline__ void bwd_few(const WalkArgs& a, int blk, int first, int n) {
@@ -408,20 +395,25 @@ __device__ __forceinline__ void bwd_few(const WalkArgs& a, int blk, int first, i
     }
 }
 template <int D, typename T, int LPH>
-__global__ __launch_bounds__(256) void hgt_attend_bwd_few_kernel(WalkArgs a) {
-    const int blk = blockIdx.x;
-    if (blk < a.short_blocks) bwd_few<D, T, LPH, 2, kShortLen>(a, blk, a.short_first, a.short_n);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hgt_attend_bwd_kernel(WalkArgs a) {
+    constexpr int LPR = D / RowT<T>::V;
+    const int blk = (int)blockIdx.x - a.general_blocks;
+    if ((int)blockIdx.x < a.wide_blocks) {
+        const int i = blockIdx.x * 4 + threadIdx.x / 64;
+        if (i < a.wide_n) bwd_walk<D, T, LPH, 64 / LPR>(a, i);
+    } else if (blk < 0) {
+        const int i = group_item<LPR>(a);
+        if (i >= 0) bwd_walk<D, T, LPH, 1>(a, i);
+    } else if (blk < a.short_blocks) bwd_few<D, T, LPH, 2, kShortLen>(a, blk, a.short_first, a.short_n);
     else bwd_few<D, T, LPH, 4, 1>(a, blk - a.short_blocks, a.single_first, a.single_n);
 }
 
 // ------------------------------------------------------------------------------------------------ backward, pair-major
 
 template <int D, typename T, int LPH>
-__global__ __launch_bounds__(256) void hgt_pair_bwd_kernel(WalkArgs a) {
+__device__ __forceinline__ void pair_walk(const WalkArgs& a, int i) {
     constexpr int V = RowT<T>::V, LPR = D / V, H = LPR / LPH;
-    const int i = group_item<LPR>(a);
     const int cv = threadIdx.x % LPR, head = cv / LPH;
-    if (i < 0) return;
     const T* __restrict__ Q = static_cast<const T*>(a.Q) + cv * V;
     const T* __restrict__ dZ = static_cast<const T*>(a.dZ) + cv * V;
     const int b = a.it.beg[i], e = a.it.end[i], slot = a.it.slot[i];
@@ -522,14 +514,17 @@ __device__ __forceinline__ void pair_few(const WalkArgs& a, int blk, int first, 
     }
 }
 template <int D, typename T, int LPH>
-__global__ __launch_bounds__(256) void hgt_pair_bwd_few_kernel(WalkArgs a) {
-    const int blk = blockIdx.x;
-    if (blk < a.short_blocks) pair_few<D, T, LPH, 2, kShortLen>(a, blk, a.short_first, a.short_n);
+__global__ __launch_bounds__(256) void hgt_pair_bwd_kernel(WalkArgs a) {
+    const int blk = (int)blockIdx.x - a.general_blocks;
+    if (blk < 0) {
+        const int i = group_item<D / RowT<T>::V>(a);
+        if (i >= 0) pair_walk<D, T, LPH>(a, i);
+    } else if (blk < a.short_blocks) pair_few<D, T, LPH, 2, kShortLen>(a, blk, a.short_first, a.short_n);
     else pair_few<D, T, LPH, 4, 1>(a, blk - a.short_blocks, a.single_first, a.single_n);
 }
 
-// Fills the item ranges of a walk over L; returns the number of blocks of the walk over the short segments.
-int split_ranges(const ItemList& L, int groups_per_block, bool wide, WalkArgs& a, int* general_blocks) {
+// Fills the item ranges of a walk over L; returns its number of blocks.
+int split_ranges(const ItemList& L, int groups_per_block, bool wide, WalkArgs& a) {
     const int ns = batched_count(L.num_single, current_schedule_flags());
     const int nsh = batched_count(L.num_short, current_schedule_flags());
     a.it = dev_items(L);
@@ -541,8 +536,8 @@ int split_ranges(const ItemList& L, int groups_per_block, bool wide, WalkArgs& a
     a.short_first = L.first_short; a.short_n = nsh;
     a.single_first = L.first_single; a.single_n = ns;
     a.short_blocks = nsh > 0 ? (int)blocks_for((size_t)(nsh + 1) / 2, groups_per_block) : 0;
-    *general_blocks = a.wide_blocks + (int)blocks_for((size_t)a.general_n, groups_per_block);
-    return a.short_blocks + (ns > 0 ? (int)blocks_for((size_t)(ns + 3) / 4, groups_per_block) : 0);
+    a.general_blocks = a.wide_blocks + (int)blocks_for((size_t)a.general_n, groups_per_block);
+    return a.general_blocks + a.short_blocks + (ns > 0 ? (int)blocks_for((size_t)(ns + 3) / 4, groups_per_block) : 0);
 }
 
 }  // namespace
@@ -570,18 +565,11 @@ int split_ranges(const ItemList& L, int groups_per_block, bool wide, WalkArgs& a
         else RGNN_FAIL(RGNN_EUNSUPPORTED, "feature width %d not supported (32/64/128)", (int)(D_)); \
     } while (0)
 
-#define RGNN_HGT_WALK(KERNEL, WIDE)                                                                                                     \
+#define RGNN_HGT_WALK(KERNEL, WIDE)                                                                                              \
     do {                                                                                                                          \
-        int gb = 0;                                                                                                               \
-        const int few = split_ranges(L, 256 / (D / (rows_bf16 ? 8 : 4)), WIDE, a, &gb);                                                 \
-        if (gb > 0) {                                                                                                             \
-            RGNN_HGT_DISPATCH(D, H, rows_bf16, hipLaunchKernelGGL((KERNEL##_kernel<DD, TT, LL>), dim3(gb), dim3(256), 0, st, a)); \
-            RGNN_CHECK_LAUNCH();                                                                                                  \
-        }                                                                                                                         \
-        if (few > 0) {                                                                                                            \
-            RGNN_HGT_DISPATCH(D, H, rows_bf16, hipLaunchKernelGGL((KERNEL##_few_kernel<DD, TT, LL>), dim3(few), dim3(256), 0, st, a)); \
-            RGNN_CHECK_LAUNCH();                                                                                                  \
-        }                                                                                                                         \
+        const int blocks = split_ranges(L, 256 / (D / (rows_bf16 ? 8 : 4)), WIDE, a);                                              \
+        RGNN_HGT_DISPATCH(D, H, rows_bf16, hipLaunchKernelGGL((KERNEL##_kernel<DD, TT, LL>), dim3(blocks), dim3(256), 0, st, a));  \
+        RGNN_CHECK_LAUNCH();                                                                                                      \
     } while (0)
 
 rgnn_status_t hgt_attend_fwd(const rgnn_graph* g, int D, int H, const void* KM, const void* Q, void* Z, float* ms,
