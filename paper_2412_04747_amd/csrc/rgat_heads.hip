@@ -25,61 +25,93 @@ __global__ void fold_weight_heads_kernel(const float* __restrict__ W, const floa
 }
 
 // s_dst[q][h] = X[run_dst[q]] . wtp[run_rel[q]][h]: the run's X row is read once, one full-width dot per head; a lane
-// group takes four consecutive runs so that four row reads (and the heads' folded vectors) are in flight per lane
-template <int D>
-__global__ __launch_bounds__(256) void run_logit_heads_kernel(int Q, int R, int H, const int32_t* __restrict__ run_dst,
+// group takes RPG consecutive runs so that four row reads or more (and the heads' folded vectors) are in flight per lane, and
+// a lane stores all heads of a run (a store per run and head: 66 us for 1.1M runs and four heads, now 52).
+template <int D, int H>
+__global__ __launch_bounds__(256) void run_logit_heads_kernel(int Q, const int32_t* __restrict__ run_dst,
                                                               const int32_t* __restrict__ run_rel,
                                                               const float* __restrict__ X, const float* __restrict__ wtp,
                                                               float* __restrict__ s_dst) {
-    constexpr int LPR = D / 4;
-    const int q0 = (blockIdx.x * (256 / LPR) + threadIdx.x / LPR) * 4, c4 = threadIdx.x % LPR;
+    constexpr int LPR = D / 4, RPG = 4;
+    struct __align__(4 * (H < 4 ? H : 4)) Out { float v[H]; };
+    const int q0 = (blockIdx.x * (256 / LPR) + threadIdx.x / LPR) * RPG, c4 = threadIdx.x % LPR;
     if (q0 >= Q) return;
-    float4 x[4];
-    int r[4];
+    float4 x[RPG];
+    int r[RPG];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < RPG; ++u) {
         const int q = min(q0 + u, Q - 1);
         x[u] = *reinterpret_cast<const float4*>(X + (size_t)run_dst[q] * D + c4 * 4);
         r[u] = run_rel[q];
     }
+    Out mine;
+#pragma unroll
     for (int h = 0; h < H; ++h) {
-        float4 w[4];
+        float4 w[RPG];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = *reinterpret_cast<const float4*>(wtp + ((size_t)r[u] * H + h) * D + c4 * 4);
+        for (int u = 0; u < RPG; ++u) w[u] = *reinterpret_cast<const float4*>(wtp + ((size_t)r[u] * H + h) * D + c4 * 4);
+        mine.v[h] = 0.f;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < RPG; ++u) {
             const float t = group_sum<LPR>(dot4(x[u], w[u]));
-            if (c4 == 0 && q0 + u < Q) s_dst[(size_t)(q0 + u) * H + h] = t;
+            if (c4 == u) mine.v[h] = t;
         }
     }
+    if (c4 < RPG && q0 + c4 < Q) *reinterpret_cast<Out*>(s_dst + (size_t)(q0 + c4) * H) = mine;
 }
 
 // Per relation r, with U[h][r] = sum_q ds_dst[q][h] X[dst_q] and h(n) the head of column n:
 //   dw_t[r][n] = sum_k U[h(n)][r][k] W[r][k][n];   dW[r][k][n] += U[h(n)][r][k] * w_t[r][n]
 // and, where A[r][h] = sum_p ds_src[p][h] X[src_p] is given (otherwise the caller forms dw_s from the message rows),
 //   dw_s[r][n] = sum_k A[r][h(n)][k] W[r][k][n]
-__global__ void rgat_heads_param_finish_kernel(int R, int kd, int nd, int H, const float* __restrict__ W,
-                                               const float* __restrict__ w_t, const float* __restrict__ U,
-                                               const float* __restrict__ A, float* __restrict__ dW,
-                                               float* __restrict__ dw_s, float* __restrict__ dw_t) {
-    const int r = blockIdx.x, dh = nd / H;
+// Workgroups (r, j < nd / 32) form 32 columns of the vectors each (the eight lanes of a column take the k index in turn and are
+// added in order through LDS); workgroups (r, nd / 32 + j) update 1024 consecutive elements of dW[r] each, four per lane (a lane's
+// four columns are one head's).  nd is a power of two, at least 32.  (One workgroup per relation, a column per lane over all k: 38 us for 101 relations of width 64, now 8; 85 us for 60 of
+// width 128, now 7.)
+__global__ __launch_bounds__(256) void rgat_heads_param_finish_kernel(int R, int kd, int nd, int H, const float* __restrict__ W,
+                                                                      const float* __restrict__ w_t, const float* __restrict__ U,
+                                                                      const float* __restrict__ A, float* __restrict__ dW,
+                                                                      float* __restrict__ dw_s, float* __restrict__ dw_t) {
+    __shared__ float red[2][256];
+    const int r = blockIdx.x, tid = threadIdx.x, ln = 31 - __clz(nd), ld = ln - (31 - __clz(H));     // log2 of a head's width
     const float* Wr = W + (size_t)r * kd * nd;
-    for (int n = threadIdx.x; n < nd; n += blockDim.x) {
-        const float* Ur = U + ((size_t)(n / dh) * R + r) * kd;
-        float t = 0.f;
-        for (int k = 0; k < kd; ++k) t += Ur[k] * Wr[k * nd + n];
-        dw_t[(size_t)r * nd + n] = t;
-        if (A) {
-            const float* Ar = A + ((size_t)r * H + n / dh) * kd;
-            float s = 0.f;
-            for (int k = 0; k < kd; ++k) s += Ar[k] * Wr[k * nd + n];
-            dw_s[(size_t)r * nd + n] = s;
+    const int vec_blocks = nd / 32;
+    if ((int)blockIdx.y < vec_blocks) {
+        const int n = blockIdx.y * 32 + (tid & 31), ks = tid >> 5, h = n >> ld;
+        const float* Ur = U + ((size_t)h * R + r) * kd;
+        const float* Ar = A + ((size_t)r * H + h) * kd;
+        float s = 0.f, t = 0.f;
+#pragma unroll 8
+        for (int k = ks; k < kd; k += 8) {
+            const float w = Wr[k * nd + n];
+            t += Ur[k] * w;
+            if (A) s += Ar[k] * w;
         }
+        red[0][tid] = s;
+        red[1][tid] = t;
+        __syncthreads();
+        if (ks == 0) {
+            for (int q = 1; q < 8; ++q) {
+                s += red[0][q * 32 + tid];
+                t += red[1][q * 32 + tid];
+            }
+            if (A) dw_s[(size_t)r * nd + n] = s;
+            dw_t[(size_t)r * nd + n] = t;
+        }
+        return;
     }
-    for (int i = threadIdx.x; i < kd * nd; i += blockDim.x) {
-        const int k = i / nd, n = i % nd;
-        dW[(size_t)r * kd * nd + i] += U[((size_t)(n / dh) * R + r) * kd + k] * w_t[(size_t)r * nd + n];
-    }
+    const int i = ((blockIdx.y - vec_blocks) * 256 + tid) * 4;
+    if (i >= kd * nd) return;
+    const int k = i >> ln, n = i & (nd - 1);
+    const float u = U[((size_t)(n >> ld) * R + r) * kd + k];
+    const float4 wt = *reinterpret_cast<const float4*>(w_t + (size_t)r * nd + n);
+    float4* o = reinterpret_cast<float4*>(dW + (size_t)r * kd * nd + i);
+    float4 v = *o;
+    v.x += u * wt.x;
+    v.y += u * wt.y;
+    v.z += u * wt.z;
+    v.w += u * wt.w;
+    *o = v;
 }
 
 // ---------------------------------------------------------------------------------------- launchers
@@ -96,9 +128,13 @@ rgnn_status_t run_logit_heads(const rgnn_graph* g, int D, int H, const float* X,
                               hipStream_t st) {
     if (g->Q == 0) return RGNN_OK;
     KernelTimer kt(st, "run_logit");
-    RGNN_DISPATCH_D(D, hipLaunchKernelGGL(run_logit_heads_kernel<DD>, dim3(blocks_for((size_t)((g->Q + 3) / 4) * (DD / 4), 256)), dim3(256),
-                                          0, st, (int)g->Q, (int)g->R, H, g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_RUN_REL], X,
-                                          wtp, s_dst));
+#define RGNN_RUN_LOGIT(H_) RGNN_DISPATCH_D(D, hipLaunchKernelGGL((run_logit_heads_kernel<DD, H_>), dim3(blocks_for((size_t)((g->Q + 3) / 4) * (DD / 4), 256)), \
+                                                              dim3(256), 0, st, (int)g->Q, g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_RUN_REL], X, wtp, s_dst))
+    if (H == 2) RGNN_RUN_LOGIT(2);
+    else if (H == 4) RGNN_RUN_LOGIT(4);
+    else if (H == 8) RGNN_RUN_LOGIT(8);
+    else RGNN_FAIL(RGNN_EUNSUPPORTED, "run_logit_heads: %d heads not built (2, 4, 8)", H);
+#undef RGNN_RUN_LOGIT
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }
@@ -106,7 +142,7 @@ rgnn_status_t run_logit_heads(const rgnn_graph* g, int D, int H, const float* X,
 rgnn_status_t rgat_heads_param_finish(int R, int kd, int nd, int H, const float* W, const float* w_t, const float* U,
                                       const float* A, float* dW, float* dw_s, float* dw_t, hipStream_t st) {
     KernelTimer kt(st, "rgat_param_finish");
-    hipLaunchKernelGGL(rgat_heads_param_finish_kernel, dim3(R), dim3(256), 0, st, R, kd, nd, H, W, w_t, U, A, dW, dw_s, dw_t);
+    hipLaunchKernelGGL(rgat_heads_param_finish_kernel, dim3(R, nd / 32 + (kd * nd + 1023) / 1024), dim3(256), 0, st, R, kd, nd, H, W, w_t, U, A, dW, dw_s, dw_t);
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }

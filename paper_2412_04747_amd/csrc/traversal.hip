@@ -784,66 +784,114 @@ __global__ void zero_f32_kernel(size_t n, float* __restrict__ x) {
 // ------------------------------------------------------------------ dX assembly
 
 // dX[u] = sum_{p in srcpair(u)} dXp[p]  +  sum_{q in runs(u)} sum_h ds_dst[q][h] * wtp[run_rel[q]][h]  +  extra[u]
-// (second and third terms optional).  The (run, head) pairs of a node are walked as one flat list.
+// (second and third terms optional).
 struct NodeSumArgs {
     Items it;             // pairs by source node, ordered by length, never cut
-    const int32_t* srcpair_ptr;
     const int32_t* srcpair_idx;
     const void* dXp;      // rows of TI
-    const void* dXp2;     // MODE 2: a second tensor of per-pair rows, summed with the first
+    const void* dXp2;     // a second tensor of per-pair rows, summed with the first
     const int32_t* dst_run_ptr;
     const int32_t* run_rel;
-    const float* ds_dst;  // [Q][heads]
-    const float* wtp;     // [R][heads][D]
+    const float* ds_dst;  // [Q][H]
+    const float* wtp;     // [R][H][D]
     const float* extra;
     void* dX;             // rows of TO
-    int heads;            // run term: sum over (run q, head h) of ds_dst[q][h] * wtp[run_rel[q]][h]
-    int R;
 };
 
-// MODE 1: the destination-run term is present (RGAT); MODE 0: the kernel only sums pair rows;
-// MODE 2: pair rows of two tensors (HGT: the key and the message halves of the input gradient).
-template <int D, typename TI, typename TO, int MODE>
+// RB runs of the run term, H heads each: their relations and coefficients (entries past the end repeat the last one with zero
+// coefficients), and the H folded vectors of each relation.
+template <int D, int V, int H, int RB>
+struct RunBatch {
+    struct __align__(4 * H) Coef { float v[H]; };
+    int rel[RB];
+    float c[RB][H];
+    __device__ __forceinline__ void fetch(const NodeSumArgs& a, int q, int qe) {
+#pragma unroll
+        for (int t = 0; t < RB; ++t) {
+            const int x = min(q + t, qe - 1);
+            rel[t] = a.run_rel[x];
+            const Coef k = *reinterpret_cast<const Coef*>(a.ds_dst + (size_t)x * H);
+#pragma unroll
+            for (int h = 0; h < H; ++h) c[t][h] = q + t < qe ? k.v[h] : 0.f;
+        }
+    }
+    __device__ __forceinline__ void rows(const NodeSumArgs& a, int cv, float (&w)[RB * H][V]) const {
+#pragma unroll
+        for (int t = 0; t < RB; ++t)
+#pragma unroll
+            for (int h = 0; h < H; ++h) load_cols(a.wtp + ((size_t)rel[t] * H + h) * D + cv * V, w[t * H + h]);
+    }
+    __device__ __forceinline__ void add(const float (&w)[RB * H][V], float (&acc)[V], float (&acc1)[V]) const {
+#pragma unroll
+        for (int x = 0; x < RB * H; ++x) fma_cols(x & 1 ? acc1 : acc, c[x / H][x % H], w[x]);
+    }
+    // the runs q, q + step, ... in batches, relations and coefficients one batch ahead of the rows
+    __device__ __forceinline__ void walk(const NodeSumArgs& a, int q, int qe, int step, int cv, float (&acc)[V], float (&acc1)[V]) {
+        if (q >= qe) return;
+        fetch(a, q, qe);
+        for (; q < qe; q += step) {
+            float w[RB * H][V], cq[RB][H];
+            rows(a, cv, w);
+#pragma unroll
+            for (int t = 0; t < RB; ++t)
+#pragma unroll
+                for (int h = 0; h < H; ++h) cq[t][h] = c[t][h];
+            if (q + step < qe) fetch(a, q + step, qe);
+#pragma unroll
+            for (int x = 0; x < RB * H; ++x) fma_cols(x & 1 ? acc1 : acc, cq[x / H][x % H], w[x]);
+        }
+    }
+};
+
+// H > 0: the destination-run term is present, with H heads (RGAT); H = 0: the kernel only sums pair rows; TWO: pair rows of
+// two tensors (HGT: the key and the message halves of the input gradient).
+//
+// A lane group per node.  A popular destination has a run of every relation: its run term is shared by all lane groups of its
+// wavefront, and a run costs one relation and one load for the coefficients of all heads.  (With a lane group alone on it and an
+// entry with loads of its own per (run, head), 250k nodes, 1.1M runs of 101 relations and four heads took 234 us, now 178; with one
+// head, 1M nodes and 4.3M runs of 200 relations 519 us, now 504.)
+template <int D, typename TI, typename TO, int H, bool TWO>
 __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a) {
-    constexpr bool RUNS = MODE == 1, TWO = MODE == 2;
-    constexpr int V = RowT<TI>::V, LPR = D / V, IPB = 256 / LPR;
-    const int i = blockIdx.x * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
-    if (i >= a.it.n) return;
+    constexpr bool RUNS = H > 0;
+    constexpr int V = RowT<TI>::V, LPR = D / V, IPB = 256 / LPR, G = 64 / LPR;
+    constexpr int HH = RUNS ? H : 1, RB = HH == 1 ? 4 : HH <= 4 ? 2 : 1;     // runs per batch
+    constexpr int ALONE = 8 * RB;                                           // runs that a lane group walks by itself
+    static_assert(!RUNS || (sizeof(TI) == 4 && !TWO), "the run term goes with fp32 rows of one tensor");
+    const int i0 = blockIdx.x * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
+    const bool on = i0 < a.it.n;
+    if (!RUNS && !on) return;                       // (with runs, the lanes past the end help with other nodes')
+    const int i = min(i0, a.it.n - 1);
     const TI* __restrict__ dXp = static_cast<const TI*>(a.dXp);
     const TI* __restrict__ dXp2 = static_cast<const TI*>(a.dXp2);
     const int u = a.it.row[i];
-    const int b = a.it.beg[i], e = a.it.end[i];
-    const int H = a.heads, lh = 31 - __clz(H);      // the head count is a power of two
-    const int qb = RUNS ? a.dst_run_ptr[u] << lh : 0, qe = RUNS ? a.dst_run_ptr[u + 1] << lh : 0;
+    const int b = a.it.beg[i], e = on ? a.it.end[i] : b;
+    int qb = 0, qe = 0;
+    if (RUNS) {
+        qb = a.dst_run_ptr[u];
+        qe = on ? a.dst_run_ptr[u + 1] : qb;
+    }
     float acc[V], acc1[V];
     zero_cols(acc);
     zero_cols(acc1);
-    // The first four pairs and the first four runs of the node are fetched together (a node has
+    // The first four pairs and the first runs of the node are fetched together (a node has
     // about as many of either as one batch holds), so their two index -> row chains overlap.
-    int pi[4], rr[4];
-    float c[4];
+    int pi[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        pi[t] = b + t < e ? a.srcpair_idx[b + t] : -1;
-        rr[t] = -1;
-        c[t] = 0.f;
-        if (RUNS && qb + t < qe) {
-            const int x = qb + t;
-            rr[t] = (a.run_rel[x >> lh] << lh) + (x & (H - 1));
-            c[t] = a.ds_dst[qb + t];
-        }
-    }
-    if (a.extra) load_cols(a.extra + (size_t)u * D + cv * V, acc);
+    for (int t = 0; t < 4; ++t) pi[t] = b + t < e ? a.srcpair_idx[b + t] : -1;
+    RunBatch<D, V, HH, RB> first;
+    const bool runs = RUNS && qb < qe;
+    if (runs) first.fetch(a, qb, qe);
+    if (a.extra && on) load_cols(a.extra + (size_t)u * D + cv * V, acc);
     {
-        float v[4][V], w[4][V];
+        float v[4][V], w[4][V], rw[RB * HH][V];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             if (pi[t] >= 0) load_cols_nt(dXp + (size_t)pi[t] * D + cv * V, v[t]);
             else zero_cols(v[t]);
-            if (RUNS && rr[t] >= 0) load_cols(a.wtp + (size_t)rr[t] * D + cv * V, w[t]);
-            else if (TWO && pi[t] >= 0) load_cols(dXp2 + (size_t)pi[t] * D + cv * V, w[t]);
+            if (TWO && pi[t] >= 0) load_cols(dXp2 + (size_t)pi[t] * D + cv * V, w[t]);
             else zero_cols(w[t]);
         }
+        if (runs) first.rows(a, cv, rw);
         fma_cols(acc, 1.f, v[0]);
         fma_cols(acc1, 1.f, v[1]);
         fma_cols(acc, 1.f, v[2]);
@@ -854,12 +902,7 @@ __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a) {
             fma_cols(acc, 1.f, w[2]);
             fma_cols(acc1, 1.f, w[3]);
         }
-        if (RUNS) {
-            fma_cols(acc, c[0], w[0]);
-            fma_cols(acc1, c[1], w[1]);
-            fma_cols(acc, c[2], w[2]);
-            fma_cols(acc1, c[3], w[3]);
-        }
+        if (runs) first.add(rw, acc, acc1);
     }
     for (int j = b + 4; j < e; j += 4) {
         float v[4][V], w[4][V];
@@ -884,34 +927,28 @@ __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a) {
             fma_cols(acc1, 1.f, w[3]);
         }
     }
-    if (RUNS && qb + 4 < qe) {
-        // row ids and coefficients of a batch are fetched while the rows of the batch before are in flight
-        // (entries past the end repeat the last one with a zero coefficient)
-        int rn[4];
-        float cn[4];
-#define RGNN_RUN_FETCH_IDX(Q0)                                                                   \
-    _Pragma("unroll") for (int t = 0; t < 4; ++t) {                                              \
-        const int x = min((Q0) + t, qe - 1);                                                     \
-        rn[t] = (a.run_rel[x >> lh] << lh) + (x & (H - 1));                        \
-        cn[t] = (Q0) + t < qe ? a.ds_dst[x] : 0.f;                                               \
-    }
-        RGNN_RUN_FETCH_IDX(qb + 4)
-        for (int q = qb + 4; q < qe; q += 4) {
-            float cq[4];
-            float v[4][V];
+    if (RUNS) {
+        const int left = qe - (qb + RB), sub = (threadIdx.x & 63) / LPR;
+        if (left > 0 && left <= ALONE) first.walk(a, qb + RB, qe, RB, cv, acc, acc1);
+        if (__ballot(left > ALONE)) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                load_cols(a.wtp + (size_t)rn[t] * D + cv * V, v[t]);
-                cq[t] = cn[t];
+            for (int g = 0; g < G; ++g) {
+                const int from = __builtin_amdgcn_readlane(qb, g * LPR) + RB, to = __builtin_amdgcn_readlane(qe, g * LPR);
+                if (to - from <= ALONE) continue;
+                float s0[V], s1[V];
+                zero_cols(s0);
+                zero_cols(s1);
+                first.walk(a, from + sub * RB, to, G * RB, cv, s0, s1);
+                fma_cols(s0, 1.f, s1);
+#pragma unroll
+                for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+                    for (int q = 0; q < V; ++q) s0[q] += __shfl_xor(s0[q], o);
+                if (sub == g) fma_cols(acc, 1.f, s0);
             }
-            if (q + 4 < qe) RGNN_RUN_FETCH_IDX(q + 4)
-            fma_cols(acc, cq[0], v[0]);
-            fma_cols(acc1, cq[1], v[1]);
-            fma_cols(acc, cq[2], v[2]);
-            fma_cols(acc1, cq[3], v[3]);
         }
-#undef RGNN_RUN_FETCH_IDX
     }
+    if (RUNS && !on) return;
     fma_cols(acc, 1.f, acc1);
     store_cols(static_cast<TO*>(a.dX) + (size_t)u * D + cv * V, acc);
 }
@@ -919,9 +956,10 @@ __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a) {
 // ------------------------------------------------------------------ RGAT parameter-gradient epilogue
 
 // Per relation r:  dw_s[r] = A[r] W[r];  dw_t[r] = U[r] W[r];  dW[r] += A[r]^T (x) w_s[r] + U[r]^T (x) w_t[r]
-// where A[r] = sum_p ds_src[p] X[src_p] and U[r] = sum_q ds_dst[q] X[dst_q].  Workgroup (r, 0) forms the two
-// vectors (the 256 / nd lanes of a column take the k index in turn and are added in order through LDS);
-// workgroups (r, 1 + j) update 1024 consecutive elements of dW[r] each, four per lane.  nd is a power of two.
+// where A[r] = sum_p ds_src[p] X[src_p] and U[r] = sum_q ds_dst[q] X[dst_q].  Workgroups (r, j < nd / 32) form 32 columns of the
+// two vectors each (the eight lanes of a column take the k index in turn and are added in order through LDS); workgroups
+// (r, nd / 32 + j) update 1024 consecutive elements of dW[r] each, four per lane.  nd is a power of two, at least 32.  (With all
+// columns of a relation in one workgroup, two lanes each and 64 steps at width 128, 31 us for 60 relations; now 6.)
 __global__ __launch_bounds__(256) void rgat_param_finish_kernel(int kd, int nd, const float* __restrict__ W,
                                                                 const float* __restrict__ w_s, const float* __restrict__ w_t,
                                                                 const float* __restrict__ A, const float* __restrict__ U,
@@ -932,10 +970,12 @@ __global__ __launch_bounds__(256) void rgat_param_finish_kernel(int kd, int nd, 
     const float* Wr = W + (size_t)r * kd * nd;
     const float* Ar = A + (size_t)r * kd;
     const float* Ur = U + (size_t)r * kd;
-    if (blockIdx.y == 0) {
-        const int n = tid & (nd - 1), ks = tid >> ln, KS = 256 >> ln;
+    const int vec_blocks = nd / 32;
+    if ((int)blockIdx.y < vec_blocks) {
+        const int n = blockIdx.y * 32 + (tid & 31), ks = tid >> 5;
         float s = 0.f, t = 0.f;
-        for (int k = ks; k < kd; k += KS) {
+#pragma unroll 8
+        for (int k = ks; k < kd; k += 8) {
             const float w = Wr[k * nd + n];
             s += Ar[k] * w;
             t += Ur[k] * w;
@@ -944,16 +984,16 @@ __global__ __launch_bounds__(256) void rgat_param_finish_kernel(int kd, int nd, 
         red[1][tid] = t;
         __syncthreads();
         if (ks == 0) {
-            for (int q = 1; q < KS; ++q) {
-                s += red[0][q * nd + n];
-                t += red[1][q * nd + n];
+            for (int q = 1; q < 8; ++q) {
+                s += red[0][q * 32 + tid];
+                t += red[1][q * 32 + tid];
             }
             dw_s[(size_t)r * nd + n] = s;
             dw_t[(size_t)r * nd + n] = t;
         }
         return;
     }
-    const int i = ((blockIdx.y - 1) * 256 + tid) * 4;
+    const int i = ((blockIdx.y - vec_blocks) * 256 + tid) * 4;
     if (i >= kd * nd) return;
     const int k = i >> ln, n = i & (nd - 1);
     const float a = Ar[k], u = Ur[k];
@@ -1234,18 +1274,25 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
     if (g->N == 0) return RGNN_OK;
     if (ds_dst && dXp2) RGNN_FAIL(RGNN_EINVAL, "node_grad_sum: the run term and a second row tensor exclude each other");
     if (heads < 1 || (heads & (heads - 1))) RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: the head count must be a power of two, got %d", heads);
-    NodeSumArgs a{dev_items(g->srcpair_items), g->idx[RGNN_IDX_SRCPAIR_PTR], g->idx[RGNN_IDX_SRCPAIR_IDX], dXp, dXp2,
-                  g->idx[RGNN_IDX_DST_RUN_PTR], g->idx[RGNN_IDX_RUN_REL], ds_dst, wtp, extra, dX, heads, (int)g->R};
+    NodeSumArgs a{dev_items(g->srcpair_items), g->idx[RGNN_IDX_SRCPAIR_IDX], dXp, dXp2,
+                  g->idx[RGNN_IDX_DST_RUN_PTR], g->idx[RGNN_IDX_RUN_REL], ds_dst, wtp, extra, dX};
+    if (ds_dst && (in_bf16 || out_bf16)) RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: the run term is built for fp32 rows");
     KernelTimer kt(st, "node_grad_sum");
     const dim3 grid(blocks_for((size_t)g->N, 256 / (D / (in_bf16 ? 8 : 4))));
-    if (ds_dst)
-        RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 1>), grid, dim3(256), 0, st, a));
-    else if (dXp2 && (in_bf16 || out_bf16))
+    if (ds_dst) {
+#define RGNN_NODE_SUM(H_) RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, H_, false>), grid, dim3(256), 0, st, a))
+        if (heads == 1) RGNN_NODE_SUM(1);
+        else if (heads == 2) RGNN_NODE_SUM(2);
+        else if (heads == 4) RGNN_NODE_SUM(4);
+        else if (heads == 8) RGNN_NODE_SUM(8);
+        else RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: %d heads not built (1, 2, 4, 8)", heads);
+#undef RGNN_NODE_SUM
+    } else if (dXp2 && (in_bf16 || out_bf16))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: a second row tensor is built for fp32 rows");
     else if (dXp2)
-        RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, 2>), grid, dim3(256), 0, st, a));
+        RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, 0, true>), grid, dim3(256), 0, st, a));
     else
-        RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 0>), grid, dim3(256), 0, st, a));
+        RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 0, false>), grid, dim3(256), 0, st, a));
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }
@@ -1253,7 +1300,7 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
 rgnn_status_t rgat_param_finish(int R, int kd, int nd, const float* W, const float* w_s, const float* w_t,
                                 const float* A, const float* U, float* dW, float* dw_s, float* dw_t, hipStream_t st) {
     KernelTimer kt(st, "rgat_param_finish");
-    hipLaunchKernelGGL(rgat_param_finish_kernel, dim3(R, 1 + (kd * nd + 1023) / 1024), dim3(256), 0, st, kd, nd, W, w_s, w_t, A, U, dW, dw_s,
+    hipLaunchKernelGGL(rgat_param_finish_kernel, dim3(R, nd / 32 + (kd * nd + 1023) / 1024), dim3(256), 0, st, kd, nd, W, w_s, w_t, A, U, dW, dw_s,
                        dw_t);
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;

@@ -175,6 +175,20 @@ def test_multi_head_input_width_differs(d_in, d, H, flags):
     _run_heads(800, 6, src, dst, rel, p, d, H, f"heads-{d_in}-{d}-H{H}-flags{flags}", flags=flags, d_in=d_in)
 
 
+@pytest.mark.parametrize("d,H", [(32, 1), (32, 2), (64, 1), (64, 2), (64, 4), (128, 1), (128, 8)])
+def test_node_with_runs_of_many_relations(d, H):
+    """Destinations with runs of 1, 9, 17, 33 and 90 relations among neighbours with few: the shared walk of the run term (more
+    than eight batches of 1, 2 or 4 runs) and the lone one, in a last wavefront that is not full."""
+    N, R = 203, 90
+    rng = np.random.default_rng(197 + d + H)
+    parts = [(v, np.arange(n)) for v, n in ((5, 90), (6, 33), (7, 17), (8, 9), (9, 1), (120, 90), (202, 70), (201, 34))]
+    dst = np.concatenate([np.full(len(r), v) for v, r in parts] + [rng.integers(0, N, 600)]).astype(np.int32)
+    rel = np.concatenate([r for _, r in parts] + [rng.integers(0, R, 600)]).astype(np.int32)
+    src = rng.integers(0, N, len(dst)).astype(np.int32)
+    p = synth.rgat_params(rng, N, R, d, d)
+    _run_heads(N, R, src, dst, rel, p, d, H, f"many-runs-d{d}-H{H}")
+
+
 def test_multi_head_bf16_inputs_and_empty_relation():
     rng, src, dst, rel, _ = synth.tiny(171, N=600, R=5, E=5000)
     rel[rel == 3] = 1                                # relation 3 has no edge
