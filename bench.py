@@ -54,7 +54,7 @@ def counter_traffic(label, sha):
     return rows[label], f"{rel} (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command at lib_sha16 {sha}; not measured by this run)"
 
 
-def step_rooflines(kern_ms, E, N, P, P1, d):
+def step_rooflines(kern_ms, E, N, P, P1, Q, d):
     """Single-head RGAT: the traversal steps as wholes against the HBM peak: all kernels that implement a step, over
     the bytes the step itself needs per edge / node / pair (listed with each step below), whatever else the kernels move."""
     row = 4 * d
@@ -66,9 +66,10 @@ def step_rooflines(kern_ms, E, N, P, P1, d):
         # S4 backward, destination-major: per edge the message row, index, weight, dz store; per node the gradient row
         "S4_traversal_bwd_dst": (E * (row + 12) + N * row, ("edge_dot_bwd", "ds_dst_sum")),
         # S5 backward, pair-major, over the pairs with several edges (the others are served by the row selector):
-        # per edge the gradient row, position, weight, dz, destination; per pair the stored row and its offset
-        "S5_traversal_bwd_pair": ((E - P1) * (row + 16) + (P - P1) * (row + 4),
-                                  ("aggregate_bwd_pair", "aggregate_bwd_pair.combine", "ds_src_sum")),
+        # per edge the gradient row, position, weight, dz, destination; per pair the stored row and its offset.  The launch
+        # also walks the runs of the destination-side weight gradient: per run the destination's row, its id, run and ds_dst
+        "S5_traversal_bwd_pair": ((E - P1) * (row + 16) + (P - P1) * (row + 4) + Q * (row + 12),
+                                  ("pair_run_walks", "aggregate_bwd_pair.combine", "ds_src_sum")),
     }
     out = {}
     for k, (nbytes, names) in steps.items():
@@ -154,7 +155,8 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
         "aggregate_bwd_pair": ("hbm", (E - P1s) * (row + 8 + 8 * H) + (P - P1s) * (row + 8 + 4 * H), 2.0 * (E - P1s) * d) if layer == "rgat"
                               else ("hbm", (E - P1) * (row + 8) + (P - P1) * (row + 8), 2.0 * (E - P1) * d) if sched.get("row_select", half)
                               else ("hbm", E * (row + 8) + P * (row + 8), 2.0 * E * d),
-        # per run: X row + relrun_idx + run_dst + ds_dst
+        # RGAT: the two walks in one launch; per run X row + relrun_idx + run_dst + ds_dst per head
+        "pair_run_walks": ("hbm", (E - P1s) * (row + 8 + 8 * H) + (P - P1s) * (row + 8 + 4 * H) + Q * (row + 8 + 4 * H), 2.0 * (E - P1s + Q * H) * d),
         "dst_side_wgrad": ("hbm", Q * (row + 12), 2.0 * Q * d),
         # per pair: dXp row + srcpair_idx; per run (RGAT): ds_dst + run_rel; per node: result row + 2 ptrs
         # (HGT on the folded path: two per-pair tensors are summed and the query part, an fp32 row per node, is added;
@@ -493,7 +495,7 @@ def main():
     roof["launches_timed"] = dom_n
     roof["algorithmic_bytes"] = w[1] if w else None
     kern_ms = {k["name"]: k["ms_per_step"] for k in kernels}
-    steps_roof = step_rooflines(kern_ms, E, N, P, P1, d) if c["layer"] == "rgat" and H == 1 and not fwd_only else None
+    steps_roof = step_rooflines(kern_ms, E, N, P, P1, Q, d) if c["layer"] == "rgat" and H == 1 and not fwd_only else None
     if steps_roof:
         for k, v in steps_roof.items():
             print(f"[bench] {k:24s} {v['ms']:.3f} ms  {v['achieved']:.0f} GB/s = {v['frac']:.2f} of HBM peak", file=sys.stderr, flush=True)

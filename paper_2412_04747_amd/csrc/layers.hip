@@ -157,7 +157,7 @@ struct RgatSaved { float* Hs; float* s_dst; float* ms; };
 struct RgatFwdWs { float* wtp; float* s_src; float* att; float* part_m; float* part_s; float* part_ms; float* partial; };
 struct RgatBwdWs {
     float* wtp; float* wsp; float* adz; float* ds_dst; float* ds_src; float* G; float* dXp; float* A; float* U;
-    float* tl_part; float* partial;
+    float* tl_part; float* partial; float* run_partial;
     float* acc_dW; float* acc_dws; float* acc_dwt;      // RGNN_FLAG_ACCUMULATE: the parameter gradients of this call
 };
 // RGAT with one head, and up to width 64 with two or four: the gradient rows of single-edge pairs are not written per
@@ -205,9 +205,10 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->A = c.take<float>(H * g->R * d->d_in);
     w->U = c.take<float>(H * g->R * d->d_in);
     w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, *pair_chunks(g, d->d_out).f32_bwd, (int)H));
-    const size_t parts = std::max<size_t>({(size_t)g->pair_items.num_partials, (size_t)g->relrun_items.num_partials,
+    const size_t parts = std::max<size_t>({(size_t)g->pair_items.num_partials, (size_t)g->pair_items_multi.num_partials,
                                            (size_t)g->relpair_items.num_partials});
-    w->partial = c.take<float>(parts * std::max(d->d_in, d->d_out) * H);   // the run walk keeps one partial row per head
+    w->partial = c.take<float>(parts * d->d_out);
+    w->run_partial = c.take<float>((size_t)g->relrun_items.num_partials * d->d_in * H);   // one partial row per head
     const bool acc = grads_accumulate(d);
     w->acc_dW = acc ? c.take<float>((size_t)g->R * d->d_in * d->d_out) : nullptr;
     w->acc_dws = acc ? c.take<float>((size_t)g->R * d->d_out) : nullptr;
@@ -628,10 +629,10 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     // 2. destination half, once per (dst, rel) run, reordered: s_dst[q] = X[dst] . (W[r] w_t[r])  (per head: the head's columns)
     const int H = desc->heads;
     if (H > 1) {
-        RGNN_TRY(fold_weight_heads(g->R, K, D, H, Wf, static_cast<const float*>(w_t), w.wtp, st));
+        RGNN_TRY(fold_weight(fold_args(g->R, K, D, H, Wf, static_cast<const float*>(w_t), w.wtp), st));
         RGNN_TRY(run_logit_heads(g, K, H, Xf, w.wtp, sv.s_dst, st));
     } else {
-        RGNN_TRY(fold_weight(g->R, K, D, Wf, static_cast<const float*>(w_t), w.wtp, st));
+        RGNN_TRY(fold_weight(fold_args(g->R, K, D, 1, Wf, static_cast<const float*>(w_t), w.wtp), st));
         RGNN_TRY(run_logit(g, K, Xf, w.wtp, sv.s_dst, st));
     }
     if (!fused) {
@@ -676,6 +677,9 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     dw_s = ga.route(w.acc_dws, dw_s, (size_t)g->R * D);
     dw_t = ga.route(w.acc_dwt, dw_t, (size_t)g->R * D);
     const float* dX_old = acc ? static_cast<const float*>(dX) : nullptr;      // added by the kernel that writes dX
+    // U[h][r]: the relations whose runs were walked in pieces (step 3), added with the shares of the weight gradients
+    const SumArgs run_sums{w.run_partial, g->relrun_items.split_row, g->relrun_items.split_ptr, w.U, (size_t)g->relrun_items.num_partials * K,
+                           (size_t)g->R * K, g->relrun_items.num_split, K, desc->heads};
     if (desc->heads > 1) {
         const int H = desc->heads;
         const float *ws = static_cast<const float*>(w_s), *wt = static_cast<const float*>(w_t);
@@ -688,37 +692,42 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
                                    nullptr, nullptr, sel ? w.ds_src : nullptr, st));
         // 2. per-head sums of dz over runs and over pairs: ds_src[p][h] is element p * 2 H + h (step 1 wrote the pairs
         //    with one edge when the selector is on)
+        //    (in the same launch the vectors W[r] w_t[r] per head for step 7)
+        const FoldArgs fold = fold_args(g->R, K, D, H, Wf, wt, w.wtp);
         RGNN_TRY(segment_scalar_sum((int)g->Q, g->idx[RGNN_IDX_RUN_PTR], g->long_runs, nullptr, w.adz, 2 * H, H, w.ds_dst, st,
-                                    "ds_dst_sum", 0, H));
+                                    "ds_dst_sum", 0, H, false, 0, &fold));
         RGNN_TRY(segment_scalar_sum((int)g->P, g->idx[RGNN_IDX_OUT_PTR], g->long_pairs, g->idx[RGNN_IDX_OUT_EPOS], w.adz, 2 * H, H,
                                     w.ds_src, st, "ds_src_sum", sel ? 2 : 0, H, sel, 2 * H));
         // 3. dHs[p] = sum_{e in out(p)} att_e dOut[dst_e] (per head)  +  ds_src[p][h] w_s[r] (per head).  With the
         //    selector only for the pairs with several edges (step 4 forms the other rows from dOut as it reads them),
         //    and the walk sums ds_src[p][h] itself over the same (att, dz) entries; step 2 then covered only the pairs
         //    with more edges than a lane sums, among them the ones the walk cuts into pieces.
+        //    The same launch then forms U[h][r] = sum over r's runs of ds_dst[q][h] X[run_dst[q]] for step 6.
         const Rank1 r1{w.ds_src, 2 * H, g->idx[RGNN_IDX_PAIR_REL], ws};      // the second term, added when a pair's row is stored
-        RGNN_TRY(gather_sum(sel ? g->pair_items_multi : g->pair_items, D, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_DST], 0, w.adz,
-                            2 * H, 0, dO, w.G, w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", H, 0, 0, &r1,
-                            sel ? w.ds_src : nullptr, 2 * H));
+        if (sel)
+            RGNN_TRY(rgat_bwd_walks(g, RgatBwdWalks{K, D, H, w.adz, dO, w.G, w.ds_src, 2 * H, ws, w.partial, w.ds_dst, Xf, w.U, w.run_partial}, st));
+        else
+            RGNN_TRY(gather_sum(g->pair_items, D, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_DST], 0, w.adz, 2 * H, 0, dO, w.G, w.partial,
+                                st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", H, 0, 0, &r1));
         // 4. dXp = dHs W^T, dW = sum X^T dHs; with the selector also A[r][h] = sum over r's pairs of ds_src[p][h] X[src_p]
         TypedLinearBwdArgs b{};
         b.tiles = pair_chunks(g, D).f32_bwd; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
         b.dW = static_cast<float*>(dW); b.part = w.tl_part;
-        if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.hcoef = w.ds_src; b.wvec = ws; b.sel_heads = H; b.Avec = w.A; }
+        if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.hcoef = w.ds_src; b.wvec = ws; b.sel_heads = H; b.Avec = w.A; b.with_sums = &run_sums; }
         RGNN_TRY(typed_linear_bwd(K, D, b, st));
         // 5. dw_s[r] = sum over r's pairs of ds_src[p][h] Hs[p] (per head; the pair rows are in relation order);
         //    with the selector from A instead, in step 6: dw_s[r] = (A[r][h] W[r]) on the columns of head h
-        if (!sel)
+        // 6. U as above;  dw_t and the w_t part of dW from it
+        if (!sel) {
             RGNN_TRY(gather_sum(g->relpair_items, D, nullptr, nullptr, 0, w.ds_src, 2 * H, 0, sv.Hs, dw_s, w.partial, st, 2,
                                 "src_vec_grad", "src_vec_grad.combine", H));
-        // 6. U[h][r] = sum over r's runs of ds_dst[q][h] X[run_dst[q]];  dw_t and the w_t part of dW from it
-        RGNN_TRY(gather_heads_rows(g->relrun_items, K, H, g->R, g->idx[RGNN_IDX_RELRUN_IDX], g->relrun_dst, 0, w.ds_dst,
-                                   Xf, w.U, w.partial, st, "dst_side_wgrad", "dst_side_wgrad.combine"));
-        RGNN_TRY(rgat_heads_param_finish(g->R, K, D, H, Wf, wt, w.U, sel ? w.A : nullptr, static_cast<float*>(dW),
-                                         static_cast<float*>(dw_s), static_cast<float*>(dw_t), st));
+            RGNN_TRY(gather_heads_rows(g->relrun_items, K, H, g->R, g->idx[RGNN_IDX_RELRUN_IDX], g->relrun_dst, 0, w.ds_dst,
+                                       Xf, w.U, w.run_partial, st, "dst_side_wgrad", "dst_side_wgrad.combine"));
+        }
+        const RgatFinish fin{g->R, K, D, H, Wf, ws, wt, sel ? w.A : nullptr, w.U, static_cast<float*>(dW), static_cast<float*>(dw_s),
+                             static_cast<float*>(dw_t), 0};
         // 7. dX[u] = sum over u's pairs of dXp + sum over u's runs and heads of ds_dst[q][h] (W[r] w_t[r])_h
-        RGNN_TRY(fold_weight_heads(g->R, K, D, H, Wf, wt, w.wtp, st));
-        RGNN_TRY(node_grad_sum(g, K, w.dXp, w.ds_dst, w.wtp, dX_old, dX, st, 0, 0, H));
+        RGNN_TRY(node_grad_sum(g, K, w.dXp, w.ds_dst, w.wtp, dX_old, dX, st, 0, 0, H, nullptr, &fin));
         return ga.flush(st);
     }
     // 1. per CSR edge: (att_e, dz_e), att_e recomputed from the gathered row and the saved (m, s); for single-edge pairs also ds_src[p] and G[p] = att_e dOut[dst_e] (or, with
@@ -729,33 +738,31 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     const int dss = sel ? 2 : 1;
     RGNN_TRY(rgat_edge_dot_bwd(g, D, 1, sv.Hs, static_cast<const float*>(w_s), sv.s_dst, sv.ms, dO, static_cast<const float*>(out),
                                desc->slope, w.adz, w.G, w.ds_src, sel ? w.ds_src : nullptr, st));
-    // 2. ds_dst[q] = sum over the run's edges of dz
-    RGNN_TRY(segment_scalar_sum((int)g->Q, g->idx[RGNN_IDX_RUN_PTR], g->long_runs, nullptr, w.adz, 2, 1, w.ds_dst, st, "ds_dst_sum"));
+    // 2. ds_dst[q] = sum over the run's edges of dz; in the same launch the folded vectors W[r] w_s[r] (step 4) and W[r] w_t[r] (step 6)
+    const FoldArgs fold = fold_args(g->R, K, D, 1, Wf, static_cast<const float*>(w_s), w.wsp, static_cast<const float*>(w_t), w.wtp);
+    RGNN_TRY(segment_scalar_sum((int)g->Q, g->idx[RGNN_IDX_RUN_PTR], g->long_runs, nullptr, w.adz, 2, 1, w.ds_dst, st, "ds_dst_sum", 0, 1,
+                                false, 0, &fold));
     // 3. for the pairs with several edges (step 1 wrote the others): G[p] = sum_{e in out(p)} att_e dOut[dst_e] and, in
     //    the same walk over (att_e, dz_e), ds_src[p] = sum of dz_e; the pairs with more edges than a lane sums
     //    (among them the ones the walk cuts into pieces) get ds_src from the workgroup-per-segment sum afterwards
-    RGNN_TRY(gather_sum(g->pair_items_multi, D, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_DST], 0, w.adz, 2, 0, dO, w.G,
-                        w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", 1, 0, 0, nullptr, w.ds_src, dss));
+    //    Also U[r] = sum over r's runs of ds_dst[q] X[run_dst[q]] (step 4 adds the pieces of the relations that are cut)
+    RGNN_TRY(rgat_bwd_walks(g, RgatBwdWalks{K, D, 1, w.adz, dO, w.G, w.ds_src, dss, nullptr, w.partial, w.ds_dst, Xf, w.U, w.run_partial}, st));
     RGNN_TRY(segment_scalar_sum((int)g->P, g->idx[RGNN_IDX_OUT_PTR], g->long_pairs, g->idx[RGNN_IDX_OUT_EPOS], w.adz, 2, 1, w.ds_src, st,
                                 "ds_src_sum", 2, 1, true, dss));
     // 4. with dHs[p] = G[p] + ds_src[p] w_s[r]:
-    //    dXp[p] = dHs[p] W[r]^T = G[p] W[r]^T + ds_src[p] (W[r] w_s[r]);  dW[r] = sum X^T G (+ A^T (x) w_s in step 6);
+    //    dXp[p] = dHs[p] W[r]^T = G[p] W[r]^T + ds_src[p] (W[r] w_s[r]);  dW[r] = sum X^T G (+ A^T (x) w_s in step 5);
     //    A[r] = sum ds_src X
-    RGNN_TRY(fold_weight(g->R, K, D, Wf, static_cast<const float*>(w_s), w.wsp, st, static_cast<const float*>(w_t), w.wtp));   // wtp: step 7
     TypedLinearBwdArgs b{};
     b.tiles = pair_chunks(g, D).f32_bwd; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
     b.rowscale = sel ? nullptr : w.ds_src; b.vec = w.wsp; b.dW = static_cast<float*>(dW); b.Avec = w.A;
-    b.part = w.tl_part;
+    b.part = w.tl_part; b.with_sums = &run_sums;
     if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.ds_yscale = reinterpret_cast<const float2*>(w.ds_src); }
     RGNN_TRY(typed_linear_bwd(K, D, b, st));
-    // 5. U[r] = sum over r's runs of ds_dst[q] X[run_dst[q]]
-    RGNN_TRY(gather_sum(g->relrun_items, K, g->idx[RGNN_IDX_RELRUN_IDX], g->relrun_dst, 0, w.ds_dst, 1, 0, Xf,
-                        w.U, w.partial, st, 2, "dst_side_wgrad", "dst_side_wgrad.combine"));
-    // 6. dw_s = A W, dw_t = U W, dW += A^T (x) w_s + U^T (x) w_t
-    RGNN_TRY(rgat_param_finish(g->R, K, D, Wf, static_cast<const float*>(w_s), static_cast<const float*>(w_t), w.A, w.U,
-                               static_cast<float*>(dW), static_cast<float*>(dw_s), static_cast<float*>(dw_t), st));
-    // 7. dX[u] = sum over u's pairs of dXp + sum over u's runs of ds_dst[q] (W[r] w_t[r])
-    RGNN_TRY(node_grad_sum(g, K, w.dXp, w.ds_dst, w.wtp, dX_old, static_cast<float*>(dX), st));
+    // 5. dw_s = A W, dw_t = U W, dW += A^T (x) w_s + U^T (x) w_t
+    const RgatFinish fin{g->R, K, D, 1, Wf, static_cast<const float*>(w_s), static_cast<const float*>(w_t), w.A, w.U, static_cast<float*>(dW),
+                         static_cast<float*>(dw_s), static_cast<float*>(dw_t), 0};
+    // 6. dX[u] = sum over u's pairs of dXp + sum over u's runs of ds_dst[q] (W[r] w_t[r])
+    RGNN_TRY(node_grad_sum(g, K, w.dXp, w.ds_dst, w.wtp, dX_old, static_cast<float*>(dX), st, 0, 0, 1, nullptr, &fin));
     return ga.flush(st);
 }
 

@@ -163,6 +163,12 @@ struct TypedLinearArgs {
 };
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st);
 
+// pieces of D floats (a multiple of 16), `copies` sets of them, summed per cut segment
+struct SumArgs {
+    const float* partial; const int32_t* split_row; const int32_t* split_ptr; float* out;
+    size_t partial_copy, out_copy;       // floats from one set to the next
+    int num_split, D, copies;
+};
 struct TypedLinearBwdArgs {
     const TileList* tiles;
     const float* X;          // forward input rows
@@ -192,6 +198,7 @@ struct TypedLinearBwdArgs {
     const float* wvec = nullptr;     // [segs][ND]
     int sel_heads = 0;
     int dy_stride = 1;               // rows of dY are dy_stride * d_out floats apart (1 or 2)
+    const SumArgs* with_sums = nullptr;   // summed in the launch that sums the slots
 };
 // bf16 matrix-core variant (typed_linear_bf16.hip): Y[i] = A[g(i)] W[seg]
 struct TypedLinearBf16Args {
@@ -234,8 +241,10 @@ struct TypedLinearBwdBf16Args {
     const float* yscale = nullptr;
 };
 rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipStream_t st);
-// dW[s] (kn floats) and, when given, dW2[s] (kd floats) = sums of the segments' slots of kn + kd floats
-rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2, hipStream_t st);
+// dW[s] (kn floats) and, when given, dW2[s] (kd floats) = sums of the segments' slots of kn + kd floats (traversal.hip); with_sums: and the
+// rows of a list's cut segments from their pieces in the same launch, out[h][split_row[s]] = sum of partial[h][split_ptr[s] ..)
+rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2, hipStream_t st,
+                                       const SumArgs* with_sums = nullptr);
 
 size_t typed_linear_bwd_scratch_floats(int d_in, int d_out, const TileList& t, int vectors = 1);   // vectors: of a slot's vector part
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st);

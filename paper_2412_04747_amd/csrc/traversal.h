@@ -13,13 +13,16 @@ struct ScheduleFlagsScope {
     uint32_t prev;
 };
 
-// wv[r] = W[r] w[r]; optionally a second vector per relation in the same pass (wv2[r] = W[r] w2[r])
-rgnn_status_t fold_weight(int R, int kd, int nd, const float* W, const float* w, float* wv, hipStream_t st,
-                          const float* w2 = nullptr, float* wv2 = nullptr);
+// wv[r] = W[r] w[r]; optionally a second vector per relation in the same pass (wv2[r] = W[r] w2[r]).  H > 1: wv[r][h], over the
+// columns of head h
+struct FoldArgs { const float* W; const float* w; const float* w2; int R, kd, nd, H; float* wv; float* wv2; int blocks; };
+FoldArgs fold_args(int R, int kd, int nd, int H, const float* W, const float* w, float* wv, const float* w2 = nullptr, float* wv2 = nullptr);
+rgnn_status_t fold_weight(const FoldArgs& f, hipStream_t st);
 rgnn_status_t run_logit(const rgnn_graph* g, int D, const float* X, const float* wtp, float* s_dst, hipStream_t st);
 rgnn_status_t segment_scalar_sum(int n, const int32_t* ptr, const LongList& lng, const int32_t* via, const float* val,
                                  int stride, int off, float* out, hipStream_t st, const char* label, int min_len = 0,
-                                 int heads = 1, bool long_only = false, int ostride = 0);   // ostride 0: heads
+                                 int heads = 1, bool long_only = false, int ostride = 0,     // ostride 0: heads
+                                 const FoldArgs* with_fold = nullptr);                      // folds weights in the same launch
 // ms (optional, [N] pairs of floats): (max, sum of exp) of the logits of every destination with edges
 rgnn_status_t edge_softmax(const rgnn_graph* g, const float* s_src, const float* s_dst, float slope, float* att,
                            float* part_m, float* part_s, hipStream_t st, float* ms = nullptr);
@@ -41,8 +44,17 @@ struct Rank1 { const float* coef; int stride; const int32_t* seg; const float* v
 rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int32_t* rowidx, int row_by_k,
                          const float* coef, int cstride, int cabs, const void* src, void* out, float* partial,
                          hipStream_t st, int role, const char* label, const char* combine_label, int heads = 1,
-                         int src_bf16 = 0, int out_bf16 = 0, const Rank1* r1 = nullptr, float* sum2 = nullptr,
-                         int sum2_stride = 1);
+                         int src_bf16 = 0, int out_bf16 = 0, const Rank1* r1 = nullptr);
+// RGAT's backward (heads 1, 2 or 4), one launch: for the pairs with several edges G[p] = sum_e att_e dOut[dst_e] (+ ds_src[p] ws[r] per
+// head, with ws) and ds_src[p] = sum_e dz_e per head (element p * ds_src_stride + h; not for the pairs that are cut: the caller sums
+// those); by relation U[h][r] = sum_q ds_dst[q][h] X[dst_q], whose cut relations stay as pieces in run_partial
+// (typed_linear_slot_reduce adds them).
+struct RgatBwdWalks {
+    int d_in, d_out, heads;
+    const float* adz; const float* dOut; float* G; float* ds_src; int ds_src_stride; const float* ws; float* pair_partial;
+    const float* ds_dst; const float* X; float* U; float* run_partial;
+};
+rgnn_status_t rgat_bwd_walks(const rgnn_graph* g, const RgatBwdWalks& a, hipStream_t st);
 // rows of the cut segments of a list from their pieces: plain sums (widths 32 .. 256), and sums whose pieces carry their
 // own softmax statistics (max, sum) per head.  copies: that many independent sets of partial rows (one after the other)
 // and of output rows (out_copy elements apart).  full_exp: expf instead of __expf (bf16 rows: always).  The partial rows carry the factor
@@ -55,9 +67,16 @@ rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* part
 rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, const int32_t* via, const int32_t* rowidx,
                                 int row_by_k, const float* coef, const float* src, float* out, float* partial,
                                 hipStream_t st, const char* label, const char* combine_label);
+// RGAT's parameter gradients from A, U and the typed linear's share of dW (A null: dw_s is not formed)
+struct RgatFinish {
+    int R, kd, nd, H;
+    const float* W; const float* w_s; const float* w_t; const float* A; const float* U;
+    float* dW; float* dw_s; float* dw_t;
+    int blocks;          // set by the launcher
+};
 rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const float* ds_dst, const float* wtp,
                             const float* extra, void* dX, hipStream_t st, int in_bf16 = 0, int out_bf16 = 0, int heads = 1,
-                            const void* dXp2 = nullptr);
+                            const void* dXp2 = nullptr, const RgatFinish* finish = nullptr);
 // hgt.hip: the layer's weights in the caller's storage (fp32 or bf16); rel_type = node type of each relation's sources
 struct HgtWeights { const void* Wk; const void* Wv; const void* Watt; const void* Wmsg; const void* mu; bool bf16; const int32_t* rel_type; int d; int H; };
 //   folded weights of both halves: Wf_att[r] = Wk[rel_type[r]] blockdiag(mu / sqrt(dh) Watt[r]), Wf_msg[r] = Wv[..] blockdiag(Wmsg[r])
@@ -69,8 +88,6 @@ rgnn_status_t hgt_fold_bwd(int T, int R, const HgtWeights& w, float* dWf_att, fl
 rgnn_status_t hgt_expand(int R, const HgtWeights& w, float* Wbd_att, float* Wbd_msg, hipStream_t st);
 rgnn_status_t hgt_extract(int R, const HgtWeights& w, float* dWbd_att, float* dWbd_msg, float* dWatt, float* dWmsg, float* dmu,
                           hipStream_t st);
-rgnn_status_t rgat_param_finish(int R, int kd, int nd, const float* W, const float* w_s, const float* w_t,
-                                const float* A, const float* U, float* dW, float* dw_s, float* dw_t, hipStream_t st);
 // hgt_walk.hip: the edge walks of HGT over the key / message rows KM[p][2][D] of the pairs (rows fp32 or bf16)
 //   forward: Z[v] = sum_e att_e M[pair_e], att = softmax per head of Ka[pair_e] . Q[v]; ms[v][h] = (max, sum of exp)
 rgnn_status_t hgt_attend_fwd(const rgnn_graph* g, int D, int H, const void* KM, const void* Q, void* Z, float* ms,
@@ -82,11 +99,8 @@ rgnn_status_t hgt_attend_bwd(const rgnn_graph* g, int D, int H, const void* KM, 
 rgnn_status_t hgt_pair_bwd(const rgnn_graph* g, int D, int H, const void* Q, const void* dZ, const float* adl, void* dKM,
                            float* partial, hipStream_t st, int rows_bf16);
 // rgat_heads.hip: pieces of multi-head RGAT
-rgnn_status_t fold_weight_heads(int R, int kd, int nd, int H, const float* W, const float* w, float* wv, hipStream_t st);
 rgnn_status_t run_logit_heads(const rgnn_graph* g, int D, int H, const float* X, const float* wtp, float* s_dst,
                               hipStream_t st);
-rgnn_status_t rgat_heads_param_finish(int R, int kd, int nd, int H, const float* W, const float* w_t, const float* U, const float* A,
-                                      float* dW, float* dw_s, float* dw_t, hipStream_t st);
 // out[v] = sum_e |att_e| Hs[pair_e] edge by edge with atomic adds (zeroes out first); fp32 rows
 rgnn_status_t aggregate_edge_parallel(const rgnn_graph* g, int D, const float* att, const float* Hs, float* out,
                                       hipStream_t st);

@@ -29,27 +29,38 @@ ScheduleFlagsScope::~ScheduleFlagsScope() { g_schedule_flags = prev; }
 
 // wv[r][k] = sum_n W[r][k][n] * w[r][n]      (linear operator reordering, Ch.3: x (W w) instead of (x W) w)
 // for one vector per relation or two (w2 / wv2 optional) in the same pass over W.  Eight lanes per weight row,
-// 16-byte loads; nd is a multiple of 32.
-__global__ __launch_bounds__(256) void fold_weight_kernel(const float* __restrict__ W, const float* __restrict__ w,
-                                                          const float* __restrict__ w2, int kd, int nd, int total,
-                                                          float* __restrict__ wv, float* __restrict__ wv2) {
-    const int i = (blockIdx.x * 256 + threadIdx.x) >> 3, l = threadIdx.x & 7;  // (r, k)
-    if (i >= total) return;
-    const int r = i / kd;
-    const float* Wr = W + (size_t)i * nd;
+// 16-byte loads; nd is a multiple of 32.  H > 1: wv[r][h][k], the same sum over head h's columns alone (one vector; the H vectors
+// of a relation are adjacent, so the walks that need all of them touch one short block).
+__device__ __forceinline__ void fold_weight_block(const FoldArgs& f, int blk) {
+    if (f.H > 1) {
+        const int i = blk * 256 + threadIdx.x;             // (r, h, k)
+        if (i >= f.H * f.R * f.kd) return;
+        const int dh = f.nd / f.H, r = i / (f.H * f.kd), h = i / f.kd % f.H, k = i % f.kd;
+        const float* Wr = f.W + ((size_t)r * f.kd + k) * f.nd + h * dh;
+        const float* wr = f.w + (size_t)r * f.nd + h * dh;
+        float s = 0.f;
+        for (int n = 0; n < dh; ++n) s += Wr[n] * wr[n];
+        f.wv[i] = s;
+        return;
+    }
+    const int i = (blk * 256 + threadIdx.x) >> 3, l = threadIdx.x & 7;  // (r, k)
+    if (i >= f.R * f.kd) return;
+    const int r = i / f.kd, nd = f.nd;
+    const float* Wr = f.W + (size_t)i * nd;
     float s = 0.f, s2 = 0.f;
     for (int n = 4 * l; n < nd; n += 32) {
         const float4 x = *reinterpret_cast<const float4*>(Wr + n);
-        s += dot4(x, *reinterpret_cast<const float4*>(w + (size_t)r * nd + n));
-        if (w2) s2 += dot4(x, *reinterpret_cast<const float4*>(w2 + (size_t)r * nd + n));
+        s += dot4(x, *reinterpret_cast<const float4*>(f.w + (size_t)r * nd + n));
+        if (f.w2) s2 += dot4(x, *reinterpret_cast<const float4*>(f.w2 + (size_t)r * nd + n));
     }
     s = group_sum<8>(s);
     s2 = group_sum<8>(s2);
     if (l == 0) {
-        wv[i] = s;
-        if (w2) wv2[i] = s2;
+        f.wv[i] = s;
+        if (f.w2) f.wv2[i] = s2;
     }
 }
+__global__ __launch_bounds__(256) void fold_weight_kernel(FoldArgs f) { fold_weight_block(f, blockIdx.x); }
 
 // s_dst[q] = X[run_dst[q]] . wtp[run_rel[q]]; each lane group takes four consecutive runs so
 // that four row reads are in flight per lane.
@@ -77,13 +88,19 @@ __global__ void run_logit_kernel(int Q, const int32_t* __restrict__ run_dst, con
 // than kSerialMax entries, listed by the graph index; the hub runs are thousands of entries long), the
 // others one lane per (segment, head) for the segments up to that length.  The long ones come first so
 // that the few workgroups that walk a hub run start at once and the short segments fill the machine
-// around them.
-__global__ __launch_bounds__(256) void segment_scalar_sum_kernel(int n, int heads, const int32_t* __restrict__ ptr,
+// around them.  The last `fold.blocks` workgroups fold weights (RGAT's backward: the two do not depend on each other, and a
+// launch that is over in two microseconds costs five in a row of dependent ones).
+__global__ __launch_bounds__(256) void segment_scalar_sum_kernel(FoldArgs fold, int n, int heads, const int32_t* __restrict__ ptr,
                                                                  const int32_t* __restrict__ via,
                                                                  const float* __restrict__ val, int stride, int off,
                                                                  int min_len, float* __restrict__ out, int n_long,
                                                                  const int32_t* __restrict__ long_ids, int ostride) {
     __shared__ float red[4];
+    const int rest = (int)gridDim.x - fold.blocks;
+    if ((int)blockIdx.x >= rest) {
+        fold_weight_block(fold, blockIdx.x - rest);
+        return;
+    }
     const int lh = 31 - __clz(heads);            // the head count is a power of two (checked by the launcher)
     const int long_blocks = n_long << lh;
     if ((int)blockIdx.x < long_blocks) {
@@ -132,12 +149,17 @@ __global__ __launch_bounds__(256) void segment_scalar_sum_kernel(int n, int head
 // and out aligned to HV floats): one lane per segment adds all HV heads at once with vector loads, one workgroup per
 // long segment.  The order of the additions per head is the one of the kernel above.
 template <int HV>
-__global__ __launch_bounds__(256) void segment_vec_sum_kernel(int n, const int32_t* __restrict__ ptr,
+__global__ __launch_bounds__(256) void segment_vec_sum_kernel(FoldArgs fold, int n, const int32_t* __restrict__ ptr,
                                                               const int32_t* __restrict__ via, const float* __restrict__ val,
                                                               int stride, int off, int min_len, float* __restrict__ out,
                                                               int n_long, const int32_t* __restrict__ long_ids, int ostride) {
     struct __align__(4 * HV) Vec { float v[HV]; };
     __shared__ float red[4][HV];
+    const int rest = (int)gridDim.x - fold.blocks;
+    if ((int)blockIdx.x >= rest) {
+        fold_weight_block(fold, blockIdx.x - rest);
+        return;
+    }
     auto load = [&](int j) { return *reinterpret_cast<const Vec*>(val + (size_t)(via ? via[j] : j) * stride + off); };
     if ((int)blockIdx.x < n_long) {
         const int i = long_ids[blockIdx.x];
@@ -551,15 +573,6 @@ __global__ __launch_bounds__(256) void gather_sum_kernel(GatherArgs a, GatherRan
     else if (blk < r.general_blocks + r.short_blocks) gather_short<D, TI, TO, R1, ROLE == 0>(a, blk - r.general_blocks, r.short_first, r.short_n);
     else gather_single<D, TI, TO, R1, ROLE == 0>(a, blk - r.general_blocks - r.short_blocks, r.single_first, r.single_n);
 }
-// The pair-major walk that also sums the second coefficient of every entry per segment and head (GatherArgs::sum2;
-// fp32 rows, lists without single-entry segments), held to the register budget of eight wavefronts per SIMD like
-// the plain walk.
-template <int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void gather_sum_s2_kernel(GatherArgs a, GatherRanges r) {
-    const int blk = blockIdx.x;
-    if (blk < r.general_blocks) gather_general<D, float, float, false, false, true>(a, blk);
-    else gather_short<D, float, float, false, false, true>(a, blk - r.general_blocks, r.short_first, r.short_n);
-}
 template <int D, int ROLE, typename TI, typename TO>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void gather_general_kernel(GatherArgs a) { gather_general<D, TI, TO, false, ROLE == 0>(a, blockIdx.x); }
 template <int D, int ROLE, typename TI, typename TO>
@@ -570,9 +583,9 @@ __global__ __launch_bounds__(256) void gather_single_kernel(GatherArgs a, int fi
 // NH weighted sums of the same rows in one walk: out[h][row_i] = sum_j coef[k][h] * src[row], k and row as
 // in gather_sum_kernel (fp32 rows).  out is [NH][out_rows][D], the partial rows [NH][num_partials][D].
 template <int D, int NH>
-__global__ __launch_bounds__(256) void gather_heads_rows_kernel(GatherArgs a, int out_rows, int num_partials) {
+__device__ __forceinline__ void gather_heads_rows(const GatherArgs& a, int blk, int out_rows, int num_partials) {
     constexpr int LPR = D / 4, IPB = 256 / LPR;
-    const int i = blockIdx.x * IPB + threadIdx.x / LPR, c4 = threadIdx.x % LPR;
+    const int i = blk * IPB + threadIdx.x / LPR, c4 = threadIdx.x % LPR;
     if (i >= a.it.n) return;
     const float* __restrict__ src = static_cast<const float*>(a.src);
     const int b = a.it.beg[i], e = a.it.end[i];
@@ -603,6 +616,29 @@ __global__ __launch_bounds__(256) void gather_heads_rows_kernel(GatherArgs a, in
                             : a.partial + ((size_t)h * num_partials + slot) * D;
         *reinterpret_cast<float4*>(o + c4 * 4) = acc[h];
     }
+}
+template <int D, int NH>
+__global__ __launch_bounds__(256) void gather_heads_rows_kernel(GatherArgs a, int out_rows, int num_partials) {
+    gather_heads_rows<D, NH>(a, blockIdx.x, out_rows, num_partials);
+}
+
+// The two walks of RGAT's backward that need only the edges' (att, dz) and the runs' ds_dst: the first blocks walk the runs by
+// relation (U[r][h] = sum_q ds_dst[q][h] X[dst_q], KR columns), the others the pairs with several edges (the gradient rows, D
+// columns, and ds_src).  Each is bound by its gathers, and each drains for some microseconds when it is alone: the items of
+// the relations are long and few, those of the pairs short and many.  As launches of their own 12.5 and 19 us at 200k edges, so 21;
+// 96 and 78 at 2.5M edges and four heads, so 159; 345 and 233 at 10M, so 549.
+template <int D, int KR, int NH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void pair_run_walks_kernel(GatherArgs pair, GatherRanges r, GatherArgs run, int run_blocks,
+                                                                                                     int out_rows, int num_partials) {
+    int blk = blockIdx.x;
+    if (blk < run_blocks) {
+        if constexpr (NH == 1) gather_general<KR, float, float, false, false>(run, blk);
+        else gather_heads_rows<KR, NH>(run, blk, out_rows, num_partials);
+        return;
+    }
+    blk -= run_blocks;
+    if (blk < r.general_blocks) gather_general<D, float, float, false, false, true>(pair, blk);
+    else gather_short<D, float, float, false, false, true>(pair, blk - r.general_blocks, r.short_first, r.short_n);
 }
 
 // out[split_row[s]] = sum of partial rows [split_ptr[s], split_ptr[s+1]).  A workgroup of TH threads owns C4 float4 columns
@@ -781,6 +817,184 @@ __global__ void zero_f32_kernel(size_t n, float* __restrict__ x) {
     if (i < n) x[i] = 0.f;
 }
 
+// ------------------------------------------------------------------ sums of the weight gradients' shares
+
+// dW[s] (and Avec[s]) = sum of the partial slots of segment s; kn / kd = floats of a slot's matrix / vector part, both
+// multiples of 4.  A workgroup owns C4 consecutive float4 of one segment's slots; its G lane groups take the slots in turn,
+// four loads in flight each, and the group sums are added in four chains through LDS, so the result does not depend on
+// scheduling (in one chain of 31 additions the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.24e-7, and dWmsg
+// of HGT at 300k edges 2.65e-7, now 2.53e-7, in the same time; by halves with a barrier each 1.21e-7 and 2.55e-7, 1 us more).  Bound by the chain of loads of the segment with the most slots: with one lane per float and four loads in
+// flight, a self-loop's one segment of 512 slots plus a 45-relation list took 30 us each, now 7 us; 768 slots of 64 KB
+// (50 MB) in 5 and 17 segments 24 us each, now 13 us.
+template <int G, int C4>
+__device__ __forceinline__ void slot_reduce_block(const float* __restrict__ part, const int32_t* __restrict__ seg_slot_ptr, int seg, int col_blk,
+                                                  int kn, int kd, float* __restrict__ dW, float* __restrict__ Avec, float4* red) {
+    const int c = threadIdx.x % C4, g = threadIdx.x / C4;
+    const int i = (col_blk * C4 + c) * 4, slot_sz = kn + kd;
+    const bool on = i < slot_sz;
+    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f), s1 = s0;
+    const int b = seg_slot_ptr[seg], e = seg_slot_ptr[seg + 1];
+    if (on) {
+        const float* p = part + i;
+        int sl = b + g;
+        for (; sl + 3 * G < e; sl += 4 * G) {
+            const float4 x0 = *reinterpret_cast<const float4*>(p + (size_t)sl * slot_sz);
+            const float4 x1 = *reinterpret_cast<const float4*>(p + (size_t)(sl + G) * slot_sz);
+            const float4 x2 = *reinterpret_cast<const float4*>(p + (size_t)(sl + 2 * G) * slot_sz);
+            const float4 x3 = *reinterpret_cast<const float4*>(p + (size_t)(sl + 3 * G) * slot_sz);
+            s0.x += x0.x + x2.x; s0.y += x0.y + x2.y; s0.z += x0.z + x2.z; s0.w += x0.w + x2.w;
+            s1.x += x1.x + x3.x; s1.y += x1.y + x3.y; s1.z += x1.z + x3.z; s1.w += x1.w + x3.w;
+        }
+        for (; sl < e; sl += G) {
+            const float4 x0 = *reinterpret_cast<const float4*>(p + (size_t)sl * slot_sz);
+            s0.x += x0.x; s0.y += x0.y; s0.z += x0.z; s0.w += x0.w;
+        }
+    }
+    red[g * C4 + c] = make_float4(s0.x + s1.x, s0.y + s1.y, s0.z + s1.z, s0.w + s1.w);
+    __syncthreads();
+    constexpr int CH = G * C4 >= 512 ? 64 / C4 : 1;        // chains over the groups, one wavefront's worth of lanes
+    if (g >= CH) return;
+    float4 t = red[g * C4 + c];
+#pragma unroll
+    for (int k = g + CH; k < G; k += CH) {
+        const float4 x = red[k * C4 + c];
+        t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w;
+    }
+#pragma unroll
+    for (int o = C4; o < CH * C4; o <<= 1) {
+        t.x += __shfl_xor(t.x, o); t.y += __shfl_xor(t.y, o); t.z += __shfl_xor(t.z, o); t.w += __shfl_xor(t.w, o);
+    }
+    if (g != 0 || !on) return;
+    if (i < kn) *reinterpret_cast<float4*>(dW + (size_t)seg * kn + i) = t;
+    else if (Avec) *reinterpret_cast<float4*>(Avec + (size_t)seg * kd + (i - kn)) = t;
+}
+
+
+// The other kind of shares that RGAT's backward leaves per relation: U[h][r] from the pieces of r's run list (SumArgs: one copy of
+// rows per head).  Independent of the slots, so one launch sums both.  A workgroup takes 16 columns of one relation and head,
+// 128 lane groups take its pieces in turn, eight loads in flight in four chains, and the group sums are added by halves.  Bound by
+// the chain of loads of the largest relation (4.3M runs of 200 relations, 17k pieces, width 64: both sums 17 us, as launches of
+// their own 7 and 8.5; at 93k runs of 50 relations 6 us, two launches of 6).
+__device__ __forceinline__ void piece_sum_block(const SumArgs& u, int blk, float4* red) {
+    constexpr int C4 = 4, G = 128;
+    const int cols = u.D / (4 * C4), s = blk / (cols * u.copies), h = blk / cols % u.copies;
+    const int c = threadIdx.x % C4, g = threadIdx.x / C4, c4 = blk % cols * C4 + c;
+    const float* __restrict__ p = u.partial + (size_t)h * u.partial_copy + c4 * 4;
+    const int p0 = u.split_ptr[s], p1 = u.split_ptr[s + 1];
+    float4 acc[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[x] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k = p0 + g; k < p1; k += 8 * G) {
+        float4 r[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) r[x] = *reinterpret_cast<const float4*>(p + (size_t)min(k + x * G, p1 - 1) * u.D);
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+            if (k + x * G < p1) fma4(acc[x & 3], 1.f, r[x]);
+    }
+    fma4(acc[0], 1.f, acc[1]);
+    fma4(acc[2], 1.f, acc[3]);
+    fma4(acc[0], 1.f, acc[2]);
+    red[threadIdx.x] = acc[0];
+    __syncthreads();
+#pragma unroll
+    for (int o = G / 2; o > 0; o /= 2) {
+        if (g < o) fma4(red[threadIdx.x], 1.f, red[threadIdx.x + o * C4]);
+        __syncthreads();
+    }
+    if (g == 0) *reinterpret_cast<float4*>(u.out + (size_t)h * u.out_copy + (size_t)u.split_row[s] * u.D + c4 * 4) = red[c];
+}
+template <int G, int C4>
+__global__ __launch_bounds__(512) void sum_shares_kernel(const float* __restrict__ part, const int32_t* __restrict__ seg_slot_ptr, int num_segs,
+                                                         int col_blocks, int kn, int kd, float* __restrict__ dW, float* __restrict__ Avec, SumArgs u) {
+    static_assert(G * C4 == 512, "workgroups of 512 threads");
+    __shared__ float4 red[512];
+    const int slot_blocks = num_segs * col_blocks;
+    if ((int)blockIdx.x < slot_blocks) slot_reduce_block<G, C4>(part, seg_slot_ptr, blockIdx.x / col_blocks, blockIdx.x % col_blocks, kn, kd, dW, Avec, red);
+    else piece_sum_block(u, blockIdx.x - slot_blocks, red);
+}
+
+// Few segments with many slots each (a self-loop weight, node types, few relations): many lane groups on narrow column
+// ranges; many segments with a few slots each: few groups, wide ranges.
+rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* Avec, hipStream_t st,
+                                       const SumArgs* with_sums) {
+    KernelTimer kt(st, "typed_linear_bwd.reduce");
+    const SumArgs u = with_sums ? *with_sums : SumArgs{};
+    const int n4 = (kn + kd) / 4, more = u.num_split > 0 ? u.num_split * u.copies * (u.D / 16) : 0;
+    const bool many = tiles.num_slots > 8 * tiles.num_segs;
+    const int col_blocks = many ? (n4 + 15) / 16 : (n4 + 63) / 64;
+    const int64_t blocks = (int64_t)tiles.num_segs * col_blocks + more;
+    if (blocks > INT32_MAX) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: %d segments are too many", tiles.num_segs);
+    if (blocks == 0) return RGNN_OK;
+    if (many)
+        hipLaunchKernelGGL((sum_shares_kernel<32, 16>), dim3((unsigned)blocks), dim3(512), 0, st, part, tiles.seg_slot_ptr, tiles.num_segs, col_blocks, kn, kd, dW, Avec, u);
+    else
+        hipLaunchKernelGGL((sum_shares_kernel<8, 64>), dim3((unsigned)blocks), dim3(512), 0, st, part, tiles.seg_slot_ptr, tiles.num_segs, col_blocks, kn, kd, dW, Avec, u);
+    RGNN_CHECK_LAUNCH();
+    return RGNN_OK;
+}
+
+// ------------------------------------------------------------------ RGAT parameter-gradient epilogue
+
+// Per relation r, with A[r][h] = sum_p ds_src[p][h] X[src_p], U[h][r] = sum_q ds_dst[q][h] X[dst_q] and h(n) the head of column n:
+//   dw_s[r][n] = sum_k A[r][h(n)][k] W[r][k][n] (without A the caller forms dw_s from the message rows),
+//   dw_t[r][n] = sum_k U[h(n)][r][k] W[r][k][n],
+//   dW[r][k][n] += U[h(n)][r][k] w_t[r][n], and with one head + A[r][k] w_s[r][n] (with several, the rows that dW came from hold it).
+// Blocks (r, j < nd / 32) form 32 columns of the two vectors each (the eight lanes of a column take the k index in turn and are
+// added in order through LDS); blocks (r, nd / 32 + j) update 1024 consecutive elements of dW[r] each, four per lane (a lane's four
+// columns are one head's).  nd is a power of two, at least 32.  (With all columns of a relation in one workgroup, 31 us for 60
+// relations of width 128 and one head, 38 for 101 of width 64 and four; so, 6 and 8.)
+__device__ __forceinline__ void param_finish_block(const RgatFinish& f, int blk, float* red) {
+    const int per_rel = f.nd / 32 + (f.kd * f.nd + 1023) / 1024, r = blk / per_rel, y = blk % per_rel;
+    const int tid = threadIdx.x, kd = f.kd, nd = f.nd, ln = 31 - __clz(nd), ld = ln - (31 - __clz(f.H));     // log2 of a head's width
+    const float* Wr = f.W + (size_t)r * kd * nd;
+    if (y < nd / 32) {
+        const int n = y * 32 + (tid & 31), ks = tid >> 5, h = n >> ld;
+        const float* Ur = f.U + ((size_t)h * f.R + r) * kd;
+        const float* Ar = f.A + ((size_t)r * f.H + h) * kd;
+        float s = 0.f, t = 0.f;
+#pragma unroll 8
+        for (int k = ks; k < kd; k += 8) {
+            const float w = Wr[k * nd + n];
+            t += Ur[k] * w;
+            if (f.A) s += Ar[k] * w;
+        }
+        red[tid] = s;
+        red[256 + tid] = t;
+        __syncthreads();
+        if (ks == 0) {
+            for (int q = 1; q < 8; ++q) {
+                s += red[q * 32 + tid];
+                t += red[256 + q * 32 + tid];
+            }
+            if (f.A) f.dw_s[(size_t)r * nd + n] = s;
+            f.dw_t[(size_t)r * nd + n] = t;
+        }
+        return;
+    }
+    const int i = ((y - nd / 32) * 256 + tid) * 4;
+    if (i >= kd * nd) return;
+    const int k = i >> ln, n = i & (nd - 1);
+    const float u = f.U[((size_t)(n >> ld) * f.R + r) * kd + k];
+    const float4 wt = *reinterpret_cast<const float4*>(f.w_t + (size_t)r * nd + n);
+    float4* o = reinterpret_cast<float4*>(f.dW + (size_t)r * kd * nd + i);
+    float4 v = *o;
+    if (f.H == 1) {
+        const float a = f.A[(size_t)r * kd + k];
+        const float4 ws = *reinterpret_cast<const float4*>(f.w_s + (size_t)r * nd + n);
+        v.x += a * ws.x + u * wt.x;
+        v.y += a * ws.y + u * wt.y;
+        v.z += a * ws.z + u * wt.z;
+        v.w += a * ws.w + u * wt.w;
+    } else {
+        v.x += u * wt.x;
+        v.y += u * wt.y;
+        v.z += u * wt.z;
+        v.w += u * wt.w;
+    }
+    *o = v;
+}
+
 // ------------------------------------------------------------------ dX assembly
 
 // dX[u] = sum_{p in srcpair(u)} dXp[p]  +  sum_{q in runs(u)} sum_h ds_dst[q][h] * wtp[run_rel[q]][h]  +  extra[u]
@@ -849,15 +1063,21 @@ struct RunBatch {
 // A lane group per node.  A popular destination has a run of every relation: its run term is shared by all lane groups of its
 // wavefront, and a run costs one relation and one load for the coefficients of all heads.  (With a lane group alone on it and an
 // entry with loads of its own per (run, head), 250k nodes, 1.1M runs of 101 relations and four heads took 234 us, now 178; with one
-// head, 1M nodes and 4.3M runs of 200 relations 519 us, now 504.)
+// head, 1M nodes and 4.3M runs of 200 relations 519 us, now 504.)  With the run term, the first `fin.blocks` blocks finish the
+// layer's parameter gradients, which nothing here reads.
 template <int D, typename TI, typename TO, int H, bool TWO>
-__global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a) {
+__global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a, RgatFinish fin) {
     constexpr bool RUNS = H > 0;
+    __shared__ float red[RUNS ? 512 : 1];
+    if (RUNS && (int)blockIdx.x < fin.blocks) {
+        param_finish_block(fin, blockIdx.x, red);
+        return;
+    }
     constexpr int V = RowT<TI>::V, LPR = D / V, IPB = 256 / LPR, G = 64 / LPR;
     constexpr int HH = RUNS ? H : 1, RB = HH == 1 ? 4 : HH <= 4 ? 2 : 1;     // runs per batch
     constexpr int ALONE = 8 * RB;                                           // runs that a lane group walks by itself
     static_assert(!RUNS || (sizeof(TI) == 4 && !TWO), "the run term goes with fp32 rows of one tensor");
-    const int i0 = blockIdx.x * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
+    const int i0 = (blockIdx.x - (RUNS ? fin.blocks : 0)) * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
     const bool on = i0 < a.it.n;
     if (!RUNS && !on) return;                       // (with runs, the lanes past the end help with other nodes')
     const int i = min(i0, a.it.n - 1);
@@ -953,61 +1173,6 @@ __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a) {
     store_cols(static_cast<TO*>(a.dX) + (size_t)u * D + cv * V, acc);
 }
 
-// ------------------------------------------------------------------ RGAT parameter-gradient epilogue
-
-// Per relation r:  dw_s[r] = A[r] W[r];  dw_t[r] = U[r] W[r];  dW[r] += A[r]^T (x) w_s[r] + U[r]^T (x) w_t[r]
-// where A[r] = sum_p ds_src[p] X[src_p] and U[r] = sum_q ds_dst[q] X[dst_q].  Workgroups (r, j < nd / 32) form 32 columns of the
-// two vectors each (the eight lanes of a column take the k index in turn and are added in order through LDS); workgroups
-// (r, nd / 32 + j) update 1024 consecutive elements of dW[r] each, four per lane.  nd is a power of two, at least 32.  (With all
-// columns of a relation in one workgroup, two lanes each and 64 steps at width 128, 31 us for 60 relations; now 6.)
-__global__ __launch_bounds__(256) void rgat_param_finish_kernel(int kd, int nd, const float* __restrict__ W,
-                                                                const float* __restrict__ w_s, const float* __restrict__ w_t,
-                                                                const float* __restrict__ A, const float* __restrict__ U,
-                                                                float* __restrict__ dW, float* __restrict__ dw_s,
-                                                                float* __restrict__ dw_t) {
-    __shared__ float red[2][256];
-    const int r = blockIdx.x, tid = threadIdx.x, ln = 31 - __clz(nd);
-    const float* Wr = W + (size_t)r * kd * nd;
-    const float* Ar = A + (size_t)r * kd;
-    const float* Ur = U + (size_t)r * kd;
-    const int vec_blocks = nd / 32;
-    if ((int)blockIdx.y < vec_blocks) {
-        const int n = blockIdx.y * 32 + (tid & 31), ks = tid >> 5;
-        float s = 0.f, t = 0.f;
-#pragma unroll 8
-        for (int k = ks; k < kd; k += 8) {
-            const float w = Wr[k * nd + n];
-            s += Ar[k] * w;
-            t += Ur[k] * w;
-        }
-        red[0][tid] = s;
-        red[1][tid] = t;
-        __syncthreads();
-        if (ks == 0) {
-            for (int q = 1; q < 8; ++q) {
-                s += red[0][q * 32 + tid];
-                t += red[1][q * 32 + tid];
-            }
-            dw_s[(size_t)r * nd + n] = s;
-            dw_t[(size_t)r * nd + n] = t;
-        }
-        return;
-    }
-    const int i = ((blockIdx.y - vec_blocks) * 256 + tid) * 4;
-    if (i >= kd * nd) return;
-    const int k = i >> ln, n = i & (nd - 1);
-    const float a = Ar[k], u = Ur[k];
-    const float4 ws = *reinterpret_cast<const float4*>(w_s + (size_t)r * nd + n);
-    const float4 wt = *reinterpret_cast<const float4*>(w_t + (size_t)r * nd + n);
-    float4* o = reinterpret_cast<float4*>(dW + (size_t)r * kd * nd + i);
-    float4 v = *o;
-    v.x += a * ws.x + u * wt.x;
-    v.y += a * ws.y + u * wt.y;
-    v.z += a * ws.z + u * wt.z;
-    v.w += a * ws.w + u * wt.w;
-    *o = v;
-}
-
 // ------------------------------------------------------------------ elementwise
 
 __global__ void relu_kernel(size_t n, float* __restrict__ x) {
@@ -1051,12 +1216,16 @@ __global__ void widen_bf16_kernel(size_t n, const uint16_t* __restrict__ src, fl
 // ==================================================================== host launchers
 
 
-rgnn_status_t fold_weight(int R, int kd, int nd, const float* W, const float* w, float* wv, hipStream_t st, const float* w2,
-                          float* wv2) {
-    const int total = R * kd;
-    if (nd % 32) RGNN_FAIL(RGNN_EUNSUPPORTED, "fold_weight: width %d is not a multiple of 32", nd);
+FoldArgs fold_args(int R, int kd, int nd, int H, const float* W, const float* w, float* wv, const float* w2, float* wv2) {
+    const size_t lanes = (size_t)R * kd * (H > 1 ? H : 8);
+    return FoldArgs{W, w, w2, R, kd, nd, H, wv, wv2, (int)blocks_for(lanes, 256)};
+}
+
+rgnn_status_t fold_weight(const FoldArgs& f, hipStream_t st) {
+    if (f.nd % 32) RGNN_FAIL(RGNN_EUNSUPPORTED, "fold_weight: width %d is not a multiple of 32", f.nd);
+    if (f.H > 1 && f.w2) RGNN_FAIL(RGNN_EUNSUPPORTED, "fold_weight: two vectors per relation are built for one head");
     KernelTimer kt(st, "fold_weight");
-    hipLaunchKernelGGL(fold_weight_kernel, dim3(blocks_for((size_t)total * 8, 256)), dim3(256), 0, st, W, w, w2, kd, nd, total, wv, wv2);
+    hipLaunchKernelGGL(fold_weight_kernel, dim3(f.blocks), dim3(256), 0, st, f);
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }
@@ -1072,21 +1241,23 @@ rgnn_status_t run_logit(const rgnn_graph* g, int D, const float* X, const float*
 
 rgnn_status_t segment_scalar_sum(int n, const int32_t* ptr, const LongList& lng, const int32_t* via, const float* val,
                                  int stride, int off, float* out, hipStream_t st, const char* label, int min_len,
-                                 int heads, bool long_only, int ostride) {
+                                 int heads, bool long_only, int ostride, const FoldArgs* with_fold) {
+    const FoldArgs fold = with_fold ? *with_fold : FoldArgs{};
+    if (fold.blocks > 0 && (fold.nd % 32 || (fold.H > 1 && fold.w2))) RGNN_FAIL(RGNN_EUNSUPPORTED, "segment_scalar_sum: this fold is not built");
     if (heads < 1 || (heads & (heads - 1))) RGNN_FAIL(RGNN_EUNSUPPORTED, "segment_scalar_sum: the head count must be a power of two, got %d", heads);
-    if (n == 0 || (long_only && lng.n == 0)) return RGNN_OK;
+    if (n == 0 || (long_only && lng.n == 0)) return fold.blocks > 0 ? fold_weight(fold, st) : RGNN_OK;
     KernelTimer kt(st, label);
     const size_t long_blocks = (size_t)lng.n * heads;
     if (ostride <= 0) ostride = heads;
     if (long_only) n = 0;   // only the first kind of workgroups: the caller has summed the segments of up to kSerialMax entries
     if ((heads == 2 || heads == 4) && stride % heads == 0 && off % heads == 0 && ostride % heads == 0) {
-        const dim3 grid((unsigned)(lng.n + blocks_for((size_t)n, 256)));
-        if (heads == 2) hipLaunchKernelGGL(segment_vec_sum_kernel<2>, grid, dim3(256), 0, st, n, ptr, via, val, stride, off, min_len, out, lng.n, lng.ids, ostride);
-        else hipLaunchKernelGGL(segment_vec_sum_kernel<4>, grid, dim3(256), 0, st, n, ptr, via, val, stride, off, min_len, out, lng.n, lng.ids, ostride);
+        const dim3 grid((unsigned)(lng.n + blocks_for((size_t)n, 256) + fold.blocks));
+        if (heads == 2) hipLaunchKernelGGL(segment_vec_sum_kernel<2>, grid, dim3(256), 0, st, fold, n, ptr, via, val, stride, off, min_len, out, lng.n, lng.ids, ostride);
+        else hipLaunchKernelGGL(segment_vec_sum_kernel<4>, grid, dim3(256), 0, st, fold, n, ptr, via, val, stride, off, min_len, out, lng.n, lng.ids, ostride);
         RGNN_CHECK_LAUNCH();
         return RGNN_OK;
     }
-    hipLaunchKernelGGL(segment_scalar_sum_kernel, dim3((unsigned)(long_blocks + blocks_for((size_t)n * heads, 256))), dim3(256), 0, st, n,
+    hipLaunchKernelGGL(segment_scalar_sum_kernel, dim3((unsigned)(long_blocks + blocks_for((size_t)n * heads, 256) + fold.blocks)), dim3(256), 0, st, fold, n,
                        heads, ptr, via, val, stride, off, min_len, out, lng.n, lng.ids, ostride);
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
@@ -1185,7 +1356,7 @@ rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, v
 rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int32_t* rowidx, int row_by_k,
                          const float* coef, int cstride, int cabs, const void* src, void* out, float* partial,
                          hipStream_t st, int role, const char* label, const char* combine_label, int heads,
-                         int src_bf16, int out_bf16, const Rank1* r1, float* sum2, int sum2_stride) {
+                         int src_bf16, int out_bf16, const Rank1* r1) {
     if (L.num_items == 0) return RGNN_OK;
     const Rank1 r1v = r1 ? *r1 : Rank1{nullptr, 0, nullptr, nullptr};
     const int lpr = D / (src_bf16 ? 8 : 4);
@@ -1193,7 +1364,7 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
     const int ns = batched_count(L.num_single, current_schedule_flags());
     const int nsh = batched_count(L.num_short, current_schedule_flags());
     const int skip_first = nsh > 0 ? L.first_short : L.first_single;
-    GatherArgs a{dev_items(L), via, rowidx, row_by_k, coef, cstride, cabs, lpr / heads, src, out, partial, skip_first, nsh + ns, r1v, sum2, sum2_stride, heads};
+    GatherArgs a{dev_items(L), via, rowidx, row_by_k, coef, cstride, cabs, lpr / heads, src, out, partial, skip_first, nsh + ns, r1v, nullptr, 1, heads};
     {
         KernelTimer kt(st, label);
         GatherRanges r{};
@@ -1210,16 +1381,9 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
         RGNN_CHECK_LAUNCH();                                                                                               \
     } while (0)
         if (r1 && (src_bf16 || out_bf16 || role != 1)) RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: the rank-1 term is built for fp32 rows of the pair-major walk");
-        if (sum2 && (src_bf16 || out_bf16 || role != 1 || !coef || cstride < 2 * heads || ns > 0 || L.num_single > 0))
-            RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: the second sum is built for fp32 rows of the pair-major walk over lists without single-entry segments");
-        if (r1 && !sum2) {
+        if (r1) {
             if (grid.x > 0) {
                 RGNN_DISPATCH_D(D, hipLaunchKernelGGL((gather_sum_kernel<DD, 1, float, float, true>), grid, dim3(256), 0, st, a, r));
-                RGNN_CHECK_LAUNCH();
-            }
-        } else if (sum2) {
-            if (grid.x > 0) {
-                RGNN_DISPATCH_D(D, hipLaunchKernelGGL((gather_sum_s2_kernel<DD>), grid, dim3(256), 0, st, a, r));
                 RGNN_CHECK_LAUNCH();
             }
         } else if (!src_bf16) {
@@ -1253,6 +1417,45 @@ rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, c
     return combine_partials(L, D, partial, out, 0, combine_label, st, nullptr, 1, H, (size_t)out_rows * D);
 }
 
+rgnn_status_t rgat_bwd_walks(const rgnn_graph* g, const RgatBwdWalks& a, hipStream_t st) {
+    const ItemList &L = g->pair_items_multi, &R = g->relrun_items;
+    const int D = a.d_out, K = a.d_in, H = a.heads;
+    if (L.num_single > 0) RGNN_FAIL(RGNN_EUNSUPPORTED, "rgat_bwd_walks: the list of the pairs with several edges has single-entry segments");
+    const Rank1 r1 = a.ws ? Rank1{a.ds_src, a.ds_src_stride, g->idx[RGNN_IDX_PAIR_REL], a.ws} : Rank1{nullptr, 0, nullptr, nullptr};
+    const int nsh = batched_count(L.num_short, current_schedule_flags());
+    const GatherArgs pair{dev_items(L), g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_DST], 0, a.adz, 2 * H, 0, D / 4 / H, a.dOut, a.G,
+                          a.pair_partial, L.first_short, nsh, r1, a.ds_src, a.ds_src_stride, H};
+    const GatherArgs run{dev_items(R), g->idx[RGNN_IDX_RELRUN_IDX], g->relrun_dst, 0, a.ds_dst, H, 0, H > 1 ? 1 : K / 4, a.X, a.U,
+                         a.run_partial, R.num_items, 0, Rank1{nullptr, 0, nullptr, nullptr}, nullptr, 1, 1};
+    GatherRanges r{};
+    r.general_blocks = (int)blocks_for((size_t)(L.num_items - nsh), 256 / (D / 4));
+    r.short_blocks = nsh > 0 ? (int)blocks_for((size_t)(nsh + 1) / 2, 256 / (D / 4)) : 0;
+    r.short_first = L.first_short; r.short_n = nsh;
+    const int run_blocks = (int)blocks_for((size_t)R.num_items, 256 / (K / 4));
+    const dim3 grid(run_blocks + r.general_blocks + r.short_blocks);
+    if (grid.x > 0) {
+        KernelTimer kt(st, "pair_run_walks");
+#define RGNN_WALKS(D_, K_, H_) hipLaunchKernelGGL((pair_run_walks_kernel<D_, K_, H_>), grid, dim3(256), 0, st, pair, r, run, run_blocks, g->R, R.num_partials)
+#define RGNN_WALKS_DK(H_)                                                                                    \
+    do {                                                                                                     \
+        if (D == 64 && K == 64) RGNN_WALKS(64, 64, H_);                                                      \
+        else if (D == 32 && K == 32) RGNN_WALKS(32, 32, H_);                                                 \
+        else if (D == 64 && K == 32) RGNN_WALKS(64, 32, H_);                                                 \
+        else if (D == 32 && K == 64) RGNN_WALKS(32, 64, H_);                                                 \
+        else RGNN_FAIL(RGNN_EUNSUPPORTED, "rgat_bwd_walks: widths %d -> %d not built", K, D);                \
+    } while (0)
+        if (H == 1 && D == 128 && K == 128) RGNN_WALKS(128, 128, 1);
+        else if (H == 1) RGNN_WALKS_DK(1);
+        else if (H == 2) RGNN_WALKS_DK(2);
+        else if (H == 4) RGNN_WALKS_DK(4);
+        else RGNN_FAIL(RGNN_EUNSUPPORTED, "rgat_bwd_walks: %d heads not built (1, 2, 4)", H);
+#undef RGNN_WALKS_DK
+#undef RGNN_WALKS
+        RGNN_CHECK_LAUNCH();
+    }
+    return combine_partials(L, D, a.pair_partial, a.G, 0, "aggregate_bwd_pair.combine", st, &r1, H);
+}
+
 rgnn_status_t aggregate_edge_parallel(const rgnn_graph* g, int D, const float* att, const float* Hs, float* out,
                                       hipStream_t st) {
     if (g->N == 0) return RGNN_OK;
@@ -1270,17 +1473,20 @@ rgnn_status_t aggregate_edge_parallel(const rgnn_graph* g, int D, const float* a
 
 rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const float* ds_dst, const float* wtp,
                             const float* extra, void* dX, hipStream_t st, int in_bf16, int out_bf16, int heads,
-                            const void* dXp2) {
-    if (g->N == 0) return RGNN_OK;
+                            const void* dXp2, const RgatFinish* finish) {
+    RgatFinish fin = finish ? *finish : RgatFinish{};
+    if (finish) fin.blocks = fin.R * (fin.nd / 32 + (fin.kd * fin.nd + 1023) / 1024);
+    if (finish && !ds_dst) RGNN_FAIL(RGNN_EINVAL, "node_grad_sum: the parameter gradients go with the run term");
+    if (g->N == 0 && fin.blocks == 0) return RGNN_OK;
     if (ds_dst && dXp2) RGNN_FAIL(RGNN_EINVAL, "node_grad_sum: the run term and a second row tensor exclude each other");
     if (heads < 1 || (heads & (heads - 1))) RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: the head count must be a power of two, got %d", heads);
     NodeSumArgs a{dev_items(g->srcpair_items), g->idx[RGNN_IDX_SRCPAIR_IDX], dXp, dXp2,
                   g->idx[RGNN_IDX_DST_RUN_PTR], g->idx[RGNN_IDX_RUN_REL], ds_dst, wtp, extra, dX};
     if (ds_dst && (in_bf16 || out_bf16)) RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: the run term is built for fp32 rows");
     KernelTimer kt(st, "node_grad_sum");
-    const dim3 grid(blocks_for((size_t)g->N, 256 / (D / (in_bf16 ? 8 : 4))));
+    const dim3 grid(blocks_for((size_t)g->N, 256 / (D / (in_bf16 ? 8 : 4))) + fin.blocks);
     if (ds_dst) {
-#define RGNN_NODE_SUM(H_) RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, H_, false>), grid, dim3(256), 0, st, a))
+#define RGNN_NODE_SUM(H_) RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, H_, false>), grid, dim3(256), 0, st, a, fin))
         if (heads == 1) RGNN_NODE_SUM(1);
         else if (heads == 2) RGNN_NODE_SUM(2);
         else if (heads == 4) RGNN_NODE_SUM(4);
@@ -1290,18 +1496,9 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
     } else if (dXp2 && (in_bf16 || out_bf16))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: a second row tensor is built for fp32 rows");
     else if (dXp2)
-        RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, 0, true>), grid, dim3(256), 0, st, a));
+        RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, 0, true>), grid, dim3(256), 0, st, a, fin));
     else
-        RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 0, false>), grid, dim3(256), 0, st, a));
-    RGNN_CHECK_LAUNCH();
-    return RGNN_OK;
-}
-
-rgnn_status_t rgat_param_finish(int R, int kd, int nd, const float* W, const float* w_s, const float* w_t,
-                                const float* A, const float* U, float* dW, float* dw_s, float* dw_t, hipStream_t st) {
-    KernelTimer kt(st, "rgat_param_finish");
-    hipLaunchKernelGGL(rgat_param_finish_kernel, dim3(R, nd / 32 + (kd * nd + 1023) / 1024), dim3(256), 0, st, kd, nd, W, w_s, w_t, A, U, dW, dw_s,
-                       dw_t);
+        RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 0, false>), grid, dim3(256), 0, st, a, fin));
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }

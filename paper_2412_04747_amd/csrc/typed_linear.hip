@@ -611,71 +611,6 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
     }
 }
 
-// dW[s] (and Avec[s]) = sum of the partial slots of segment s; kn / kd = floats of a slot's matrix / vector part, both
-// multiples of 4.  A workgroup owns C4 consecutive float4 of one segment's slots; its G lane groups take the slots in turn,
-// four loads in flight each, and the group sums are added in four chains through LDS, so the result does not depend on
-// scheduling (in one chain of 31 additions the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.24e-7, and dWmsg
-// of HGT at 300k edges 2.65e-7, now 2.53e-7, in the same time; by halves with a barrier each 1.21e-7 and 2.55e-7, 1 us more).  Bound by the chain of loads of the segment with the most slots: with one lane per float and four loads in
-// flight, a self-loop's one segment of 512 slots plus a 45-relation list took 30 us each, now 7 us; 768 slots of 64 KB
-// (50 MB) in 5 and 17 segments 24 us each, now 13 us.
-template <int G, int C4>
-__global__ __launch_bounds__(G * C4) void slot_reduce_kernel(const float* __restrict__ part, const int32_t* __restrict__ seg_slot_ptr,
-                                                             int kn, int kd, float* __restrict__ dW, float* __restrict__ Avec) {
-    __shared__ float4 red[G][C4];
-    const int seg = blockIdx.x;                 // segments on the x dimension: their count has no 65535 limit there
-    const int c = threadIdx.x % C4, g = threadIdx.x / C4;
-    const int i = (blockIdx.y * C4 + c) * 4, slot_sz = kn + kd;
-    const bool on = i < slot_sz;
-    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f), s1 = s0;
-    const int b = seg_slot_ptr[seg], e = seg_slot_ptr[seg + 1];
-    if (on) {
-        const float* p = part + i;
-        int sl = b + g;
-        for (; sl + 3 * G < e; sl += 4 * G) {
-            const float4 x0 = *reinterpret_cast<const float4*>(p + (size_t)sl * slot_sz);
-            const float4 x1 = *reinterpret_cast<const float4*>(p + (size_t)(sl + G) * slot_sz);
-            const float4 x2 = *reinterpret_cast<const float4*>(p + (size_t)(sl + 2 * G) * slot_sz);
-            const float4 x3 = *reinterpret_cast<const float4*>(p + (size_t)(sl + 3 * G) * slot_sz);
-            s0.x += x0.x + x2.x; s0.y += x0.y + x2.y; s0.z += x0.z + x2.z; s0.w += x0.w + x2.w;
-            s1.x += x1.x + x3.x; s1.y += x1.y + x3.y; s1.z += x1.z + x3.z; s1.w += x1.w + x3.w;
-        }
-        for (; sl < e; sl += G) {
-            const float4 x0 = *reinterpret_cast<const float4*>(p + (size_t)sl * slot_sz);
-            s0.x += x0.x; s0.y += x0.y; s0.z += x0.z; s0.w += x0.w;
-        }
-    }
-    red[g][c] = make_float4(s0.x + s1.x, s0.y + s1.y, s0.z + s1.z, s0.w + s1.w);
-    __syncthreads();
-    constexpr int CH = G * C4 >= 512 ? 64 / C4 : 1;        // chains over the groups, one wavefront's worth of lanes
-    if (g >= CH) return;
-    float4 t = red[g][c];
-#pragma unroll
-    for (int k = g + CH; k < G; k += CH) {
-        const float4 x = red[k][c];
-        t.x += x.x; t.y += x.y; t.z += x.z; t.w += x.w;
-    }
-#pragma unroll
-    for (int o = C4; o < CH * C4; o <<= 1) {
-        t.x += __shfl_xor(t.x, o); t.y += __shfl_xor(t.y, o); t.z += __shfl_xor(t.z, o); t.w += __shfl_xor(t.w, o);
-    }
-    if (g != 0 || !on) return;
-    if (i < kn) *reinterpret_cast<float4*>(dW + (size_t)seg * kn + i) = t;
-    else if (Avec) *reinterpret_cast<float4*>(Avec + (size_t)seg * kd + (i - kn)) = t;
-}
-
-// Few segments with many slots each (a self-loop weight, node types, few relations): many lane groups on narrow column
-// ranges; many segments with a few slots each: few groups, wide ranges.
-rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* Avec, hipStream_t st) {
-    KernelTimer kt(st, "typed_linear_bwd.reduce");
-    const int n4 = (kn + kd) / 4;
-    if (tiles.num_slots > 8 * tiles.num_segs)
-        hipLaunchKernelGGL((slot_reduce_kernel<32, 16>), dim3(tiles.num_segs, (n4 + 15) / 16), dim3(512), 0, st, part, tiles.seg_slot_ptr, kn, kd, dW, Avec);
-    else
-        hipLaunchKernelGGL((slot_reduce_kernel<4, 64>), dim3(tiles.num_segs, (n4 + 63) / 64), dim3(256), 0, st, part, tiles.seg_slot_ptr, kn, kd, dW, Avec);
-    RGNN_HIP(hipGetLastError());
-    return RGNN_OK;
-}
-
 // ---------------------------------------------------------------------------------------
 static TileArgs tile_args(const TileList& t) {
     return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot};
@@ -782,7 +717,8 @@ static rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
         }
         if (!done) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: this combination of gather / scatter / rowscale is not built");
     }
-    return typed_linear_slot_reduce(*a.tiles, a.part, KD * ND, KD * (KD <= 64 && a.ysel && a.hcoef ? a.sel_heads : 1), a.dW, a.Avec, st);
+    const int kd = KD * (KD <= 64 && a.ysel && a.hcoef ? a.sel_heads : 1);
+    return typed_linear_slot_reduce(*a.tiles, a.part, KD * ND, kd, a.dW, a.Avec, st, a.with_sums);
 }
 
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st) {

@@ -279,6 +279,23 @@ def test_one_segment_of_many_pieces(d, H, n_hub):
         _run_heads(N, R, src, dst, rel, p, d, H, f"pieces-d{d}-H{H}-{n_hub}")
 
 
+@pytest.mark.parametrize("d,H", [(32, 2), (64, 1), (64, 4), (128, 1)])
+def test_relations_of_many_run_pieces(d, H):
+    """Relations whose run lists are cut at 32 runs: whole ones, and 2, 127, 128, 129 and 1025 pieces (128 lane groups sum a
+    relation's pieces, eight at a time)."""
+    runs = [1, 32, 33, 127 * 32, 128 * 32, 128 * 32 + 1, 1024 * 32 + 7]
+    N, R = max(runs), len(runs) + 1                                   # the last relation has no edge
+    rng = np.random.default_rng(d + H)
+    dst = np.concatenate([rng.permutation(N)[:n] for n in runs]).astype(np.int32)
+    rel = np.repeat(np.arange(len(runs), dtype=np.int32), runs)
+    src = rng.integers(0, N, len(dst)).astype(np.int32)
+    p = synth.rgat_params(rng, N, R, d, d)
+    if H == 1:
+        _run(N, R, src, dst, rel, p, d, "run-pieces", check_saved=False)
+    else:
+        _run_heads(N, R, src, dst, rel, p, d, H, "run-pieces")
+
+
 @pytest.mark.parametrize("H", [1, 4])
 def test_overflowing_piece_of_a_cut_destination(H):
     """A destination of five pieces whose last one sums messages of 3e38 to infinity: infinity it stays (not NaN), in that
