@@ -172,6 +172,10 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
         "node_linear_k_bwd": node_bwd, "node_linear_q_bwd": node_bwd, "node_linear_v_bwd": node_bwd,
         "node_linear_out_bwd": node_bwd,
         "pair_linear_att": pair_fwd, "pair_linear_msg": pair_fwd,
+        # several products in one launch: query and both pair linears (folded), or the node and the pair linears (unfolded)
+        "node_pair_linears": (mm, node_fwd[1] + 2 * pair_fwd[1], node_fwd[2] + 2 * pair_fwd[2]),
+        "node_linears": (mm, 3 * node_fwd[1], 3 * node_fwd[2]), "pair_linears": (mm, 2 * pair_fwd[1], 2 * pair_fwd[2]),
+        "node_pair_linears_bwd": (mm, node_bwd[1] + 2 * pair_bwd[1], node_bwd[2] + 2 * pair_bwd[2]),
         "pair_linear_att_bwd": pair_bwd, "pair_linear_msg_bwd": pair_bwd,
         # the walks gather the key and the message row of a pair together (2 rows per edge).  Forward: + pair id; per node the
         # query row, the result row, (max, sum) per head and the item.  Backward: + pair id and the (att, dl) pair per head;

@@ -88,6 +88,11 @@ struct Uploader {
     }
 };
 
+// Chunks for one of two lists of P rows that share `cus` compute units with a list of N rows.
+static int pair_share(int64_t P, int64_t N, int cus) {
+    return (int)std::min<int64_t>(std::max<int64_t>((P * cus + (2 * P + N) / 2) / std::max<int64_t>(2 * P + N, 1), 1), std::max((cus - 1) / 2, 1));
+}
+
 // Tile lists over one segmentation: the tiles are planned and uploaded once, every list gets its own chunks.
 struct Chunking { TileList* list; int max_chunks; };
 static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int tile_rows, std::initializer_list<Chunking> lists) {
@@ -154,9 +159,10 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     RGNN_HIP(hipGetDevice(&dev));
     RGNN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     g->num_cus = cus = std::max(cus, 1);
-    build_tiles(U, pair_ptr, kTileRows, {{&g->pair_tiles, kMaxChunks}, {&g->pair_tiles_wide, kWideChunksPerCU * cus},
+    const int hgt_pairs = pair_share(g->P, g->N, cus);
+    build_tiles(U, pair_ptr, kTileRows, {{&g->pair_tiles_hgt, hgt_pairs}, {&g->pair_tiles, kMaxChunks}, {&g->pair_tiles_wide, kWideChunksPerCU * cus},
                                          {&g->pair_tiles_cu2, 2 * cus}, {&g->pair_tiles_cu1, cus}});
-    build_tiles(U, ntype_ptr, kTileRows, {{&g->node_tiles, kMaxChunks}, {&g->node_tiles_wide, kWideChunksPerCU * cus},
+    build_tiles(U, ntype_ptr, kTileRows, {{&g->node_tiles_hgt, std::max(cus - 2 * hgt_pairs, 1)}, {&g->node_tiles, kMaxChunks}, {&g->node_tiles_wide, kWideChunksPerCU * cus},
                                           {&g->node_tiles_cu2, 2 * cus}, {&g->node_tiles_cu1, cus}});
     build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles, kMaxChunks}, {&g->all_tiles_cu1, cus}});
     build_items(U, g->dst_items, in_ptr, item_cut(g->E));

@@ -218,7 +218,7 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 
 // ---- RGCN buffers -----------------------------------------------------------------------
 struct RgcnFwdWs { void* Hs; float* partial; };
-struct RgcnBwdWs { void* dPre; float* dPre32; void* G; void* dXp; float* dX0; float* tl_part; float* partial; float* acc_dW; float* acc_dW0; };
+struct RgcnBwdWs { void* dPre; float* dPre32; void* G; void* dXp; float* dX0; float* tl_part; float* loop_part; float* partial; float* acc_dW; float* acc_dW0; };
 
 size_t carve_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgcnFwdWs* w) {
     Carver c(base);
@@ -234,8 +234,8 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->G = c.rows((size_t)g->P * d->d_out, h);
     w->dXp = c.rows((size_t)g->P * d->d_in, h);
     w->dX0 = c.take<float>((size_t)g->N * d->d_in);
-    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out),
-                                        typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_cu1)));
+    w->tl_part = c.take<float>(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out));
+    w->loop_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_cu1));
     w->partial = c.take<float>((size_t)g->pair_items.num_partials * d->d_out);
     const bool acc = grads_accumulate(d);
     w->acc_dW = acc ? c.take<float>((size_t)g->R * d->d_in * d->d_out) : nullptr;
@@ -249,13 +249,15 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // of the nodes are folded into the per-relation weights (Wf = Wk[type] Watt[r], Wv[type] Wmsg[r]), so
 // K, V and their gradients do not exist and the per-pair rows come straight from X.
 inline bool hgt_folded(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_hgt_folded(g->rel_src_tied, d->flags); }
+// folded path, fp32 rows up to width 64: the backwards of the two pair linears and of the query linear in one launch
+inline bool hgt_bwd_jobs(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return hgt_folded(g, d) && d->d_out <= 64; }
 // KM holds the key row and the message row of a pair side by side; ms the (max, sum) of every (destination, head) softmax.
-struct HgtSaved { void* K; void* Q; void* V; void* Z; void* KM; float* ms; };
-struct HgtFwdWs { float* Wbd_att; float* Wbd_msg; float* Wf_att; float* Wf_msg; float* part_ms; float* partial; };
+struct HgtSaved { void* K; void* Q; void* V; void* Z; void* KM; float* ms; void* Wf_att; void* Wf_msg; };
+struct HgtFwdWs { float* Wbd_att; float* Wbd_msg; float* part_ms; float* partial; };
 struct HgtBwdWs {
-    float* Wbd_att; float* Wbd_msg; float* dWbd_att; float* dWbd_msg; float* Wf_att; float* Wf_msg; float* dWf_att;
+    float* Wbd_att; float* Wbd_msg; float* dWbd_att; float* dWbd_msg; float* dWf_att;
     float* dWf_msg; void* dZ; float* adl; void* dKM;
-    void* dQ; void* dKp; void* dVp; void* dK; void* dV; float* dXk; float* dXq; float* dXv; float* tl_part;
+    void* dQ; void* dKp; void* dVp; void* dK; void* dV; float* dXk; float* dXq; float* dXv; float* node_part[3]; float* pair_part[2];
     float* partial;
     float* acc_node[4]; float* acc_rel[2]; float* acc_mu;     // RGNN_FLAG_ACCUMULATE: dWk, dWq, dWv, dWo; dWatt, dWmsg; dmu
 };
@@ -267,13 +269,15 @@ size_t carve_hgt_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* 
     s->K = c.rows(kv, h); s->Q = c.rows(nd, h); s->V = c.rows(kv, h); s->Z = c.rows(nd, h);
     s->KM = c.rows(2 * pd, h);
     s->ms = c.take<float>(2 * (size_t)g->N * d->heads);
+    // the folded weights (the backward needs them too: formed again there they cost a launch of 6 to 12 us)
+    const size_t fdd = hgt_folded(g, d) ? (size_t)g->R * d->d_out * d->d_out : 0;
+    s->Wf_att = c.rows(fdd, h); s->Wf_msg = c.rows(fdd, h);
     return c.off;
 }
 size_t carve_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, HgtFwdWs* w) {
     Carver c(base);
     const size_t rdd = (size_t)g->R * d->d_out * d->d_out, fdd = hgt_folded(g, d) ? rdd : 0;
     w->Wbd_att = c.take<float>(rdd - fdd); w->Wbd_msg = c.take<float>(rdd - fdd);
-    w->Wf_att = c.take<float>(fdd); w->Wf_msg = c.take<float>(fdd);
     w->part_ms = c.take<float>(2 * (size_t)g->dst_items.num_partials * d->heads);
     w->partial = c.take<float>((size_t)g->dst_items.num_partials * d->d_out);
     return c.off;
@@ -285,15 +289,18 @@ size_t carve_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     const size_t D = d->d_out, rdd = (size_t)g->R * D * D, nd = (size_t)g->N * D, pd = (size_t)g->P * D;
     w->Wbd_att = c.take<float>(fold ? 0 : rdd); w->Wbd_msg = c.take<float>(fold ? 0 : rdd);
     w->dWbd_att = c.take<float>(fold ? 0 : rdd); w->dWbd_msg = c.take<float>(fold ? 0 : rdd);
-    w->Wf_att = c.take<float>(fold ? rdd : 0); w->Wf_msg = c.take<float>(fold ? rdd : 0);
     w->dWf_att = c.take<float>(fold ? rdd : 0); w->dWf_msg = c.take<float>(fold ? rdd : 0);
     w->dZ = c.rows(nd, h); w->adl = c.take<float>(2 * (size_t)g->E * d->heads);
     w->dKM = c.rows(2 * pd, h); w->dQ = c.rows(nd, h);
     w->dKp = c.rows(pd, h); w->dVp = c.rows(h && fold ? 0 : pd, h);     // folded, bf16 rows: dKp holds the sum of both
     w->dK = c.rows(fold ? 0 : nd, h); w->dV = c.rows(fold ? 0 : nd, h);
     w->dXk = c.take<float>(h || fold ? 0 : nd); w->dXq = c.take<float>(h && !fold ? 0 : nd); w->dXv = c.take<float>(h || fold ? 0 : nd);
-    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out),
-                                        tl_bwd_scratch(h, node_chunks(g, d->d_out), d->d_in, d->d_out)));
+    // shares of the weight gradients, which one launch adds: output, query (and unfolded value) linears; both pair linears
+    const bool jobs = hgt_bwd_jobs(g, d);
+    const size_t nodes = std::max(tl_bwd_scratch(h, node_chunks(g, d->d_out), d->d_in, d->d_out), jobs ? typed_linear_bwd_scratch_floats(D, D, g->node_tiles_hgt) : 0);
+    const size_t pairs = std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out), jobs ? typed_linear_bwd_scratch_floats(D, D, g->pair_tiles_hgt) : 0);
+    w->node_part[0] = c.take<float>(nodes); w->node_part[1] = c.take<float>(nodes); w->node_part[2] = c.take<float>(fold ? 0 : nodes);
+    w->pair_part[0] = c.take<float>(pairs); w->pair_part[1] = c.take<float>(h && fold ? 0 : pairs);
     w->partial = c.take<float>(std::max(2 * (size_t)g->pair_items.num_partials, (size_t)g->dst_items.num_partials) * D);
     const bool acc = grads_accumulate(d);
     const size_t dh = D / d->heads;
@@ -366,7 +373,7 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
                      const int32_t* gather, int both_gathered, const float* W32, const void* W16, const void* dY,
                      void* dXrow, bool dx16, float* dW, float* part, const char* label, hipStream_t st,
                      bool dx_acc = false, const int32_t* ysel = nullptr, const void* y_alt = nullptr,
-                     const float* yscale = nullptr, int d_in = 0, int dy_stride = 1) {
+                     const float* yscale = nullptr, int d_in = 0, int dy_stride = 1, ShareSums* sums = nullptr) {
     if (d_in == 0) d_in = d;
     if (rows16 && d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward on the bf16 matrix cores: equal widths only");
     if (ysel && both_gathered) RGNN_FAIL(RGNN_EUNSUPPORTED, "row selector: ungathered dY only");
@@ -374,7 +381,7 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
         TypedLinearBwdBf16Args a{};
         a.tiles = W16 ? tiles.cu2 : tiles.cu1; a.X = X; a.gather = gather; a.both_gathered = both_gathered;
         a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.dY = dY; a.dy_stride = dy_stride; a.dXrow = dXrow; a.dx_f32 = !dx16;
-        a.accumulate = dx_acc; a.dW = dW; a.part = part; a.label = label; a.ysel = ysel; a.dY_alt = y_alt; a.yscale = yscale;
+        a.accumulate = dx_acc; a.dW = dW; a.part = part; a.label = label; a.ysel = ysel; a.dY_alt = y_alt; a.yscale = yscale; a.sums = sums;
         return typed_linear_bwd_bf16(d, a, st);
     }
     if (dx_acc) RGNN_FAIL(RGNN_EUNSUPPORTED, "accumulating input gradient needs bf16 rows");
@@ -382,7 +389,7 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
     b.tiles = tiles.f32_bwd; b.X = static_cast<const float*>(X); b.gather = gather; b.W = W32; b.dY = static_cast<const float*>(dY);
     b.dy_gathered = both_gathered; b.dXrow = static_cast<float*>(dXrow); b.scatter_dx = both_gathered; b.dW = dW;
     b.part = part; b.label = label; b.dy_stride = dy_stride;
-    b.ysel = ysel; b.dY_alt = static_cast<const float*>(y_alt); b.yscale = yscale;
+    b.ysel = ysel; b.dY_alt = static_cast<const float*>(y_alt); b.yscale = yscale; b.sums = sums;
     return typed_linear_bwd(d_in, d, b, st);
 }
 }  // namespace
@@ -525,16 +532,18 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* yscale = sel && coef ? g->pair_scale : nullptr;
     RGNN_TRY(gather_sum(sel ? g->pair_items_multi : g->pair_items, D, nullptr, g->idx[RGNN_IDX_OUT_DST], 0, ocoef, 1, 0, dPre, w.G,
                         w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", 1, h, h));
-    // 2. per pair dXp = dHs W^T; dW[r] = sum X^T dHs
+    // 2. per pair dXp = dHs W^T; dW[r] = sum X^T dHs (its shares are added with those of the self-loop)
+    ShareSums sums;
     RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
-                    w.dXp, h, static_cast<float*>(dW), w.tl_part, "typed_linear_bwd", st, false, ysel, y_alt, yscale, K));
+                    w.dXp, h, static_cast<float*>(dW), w.tl_part, "typed_linear_bwd", st, false, ysel, y_alt, yscale, K, 1, &sums));
     // 3. self-loop: dX0 = dPre W0^T, dW0 = X^T dPre
     if (W0) {
         TypedLinearBwdArgs s{};
         s.tiles = &g->all_tiles_cu1; s.X = X32; s.W = W032; s.dY = dPre32;
-        s.dXrow = w.dX0; s.dW = static_cast<float*>(dW0); s.part = w.tl_part; s.label = "self_loop_bwd";
+        s.dXrow = w.dX0; s.dW = static_cast<float*>(dW0); s.part = w.loop_part; s.label = "self_loop_bwd"; s.sums = &sums;
         RGNN_TRY(typed_linear_bwd(K, D, s, st));
     }
+    RGNN_TRY(sums.launch(st));
     // 4. dX[u] = sum over u's pairs of dXp (+ dX0[u]) (+ what dX holds, when gradients accumulate)
     const float* extra = W0 ? w.dX0 : nullptr;
     if (acc && W0) RGNN_TRY(add_into((size_t)g->N * K, static_cast<const float*>(dX), w.dX0, st));
@@ -678,7 +687,8 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     dw_t = ga.route(w.acc_dwt, dw_t, (size_t)g->R * D);
     const float* dX_old = acc ? static_cast<const float*>(dX) : nullptr;      // added by the kernel that writes dX
     // U[h][r]: the relations whose runs were walked in pieces (step 3), added with the shares of the weight gradients
-    const SumArgs run_sums{w.run_partial, g->relrun_items.split_row, g->relrun_items.split_ptr, w.U, (size_t)g->relrun_items.num_partials * K,
+    ShareSums sums;
+    sums.pieces = SumArgs{w.run_partial, g->relrun_items.split_row, g->relrun_items.split_ptr, w.U, (size_t)g->relrun_items.num_partials * K,
                            (size_t)g->R * K, g->relrun_items.num_split, K, desc->heads};
     if (desc->heads > 1) {
         const int H = desc->heads;
@@ -713,8 +723,9 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
         TypedLinearBwdArgs b{};
         b.tiles = pair_chunks(g, D).f32_bwd; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
         b.dW = static_cast<float*>(dW); b.part = w.tl_part;
-        if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.hcoef = w.ds_src; b.wvec = ws; b.sel_heads = H; b.Avec = w.A; b.with_sums = &run_sums; }
+        if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.hcoef = w.ds_src; b.wvec = ws; b.sel_heads = H; b.Avec = w.A; b.sums = &sums; }
         RGNN_TRY(typed_linear_bwd(K, D, b, st));
+        if (sel) RGNN_TRY(sums.launch(st));
         // 5. dw_s[r] = sum over r's pairs of ds_src[p][h] Hs[p] (per head; the pair rows are in relation order);
         //    with the selector from A instead, in step 6: dw_s[r] = (A[r][h] W[r]) on the columns of head h
         // 6. U as above;  dw_t and the w_t part of dW from it
@@ -755,9 +766,10 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     TypedLinearBwdArgs b{};
     b.tiles = pair_chunks(g, D).f32_bwd; b.X = Xf; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = Wf; b.dY = w.G; b.dXrow = w.dXp;
     b.rowscale = sel ? nullptr : w.ds_src; b.vec = w.wsp; b.dW = static_cast<float*>(dW); b.Avec = w.A;
-    b.part = w.tl_part; b.with_sums = &run_sums;
+    b.part = w.tl_part; b.sums = &sums;
     if (sel) { b.ysel = g->pair_ysel; b.dY_alt = dO; b.ds_yscale = reinterpret_cast<const float2*>(w.ds_src); }
     RGNN_TRY(typed_linear_bwd(K, D, b, st));
+    RGNN_TRY(sums.launch(st));
     // 5. dw_s = A W, dw_t = U W, dW += A^T (x) w_s + U^T (x) w_t
     const RgatFinish fin{g->R, K, D, 1, Wf, static_cast<const float*>(w_s), static_cast<const float*>(w_t), w.A, w.U, static_cast<float*>(dW),
                          static_cast<float*>(dw_s), static_cast<float*>(dw_t), 0};
@@ -801,27 +813,45 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
     // bf16 form of an intermediate row tensor (nullptr when the rows are fp32) and its fp32 form
     auto R16 = [h](const void* p) { return h ? p : nullptr; };
     auto R32 = [h](const void* p) { return h ? nullptr : static_cast<const float*>(p); };
-    // 1. per node type: Q, and K, V unless they are folded into the per-pair linears
-    RGNN_TRY(tl_fwd(bf16, node_chunks(g, D), D, X32, X16, perm, 1, Wq32, Wq16, sv.Q, h, "node_linear_q", st));
-    if (!fold) {
-        RGNN_TRY(tl_fwd(bf16, node_chunks(g, D), D, X32, X16, perm, 1, Wk32, Wk16, sv.K, h, "node_linear_k", st));
-        RGNN_TRY(tl_fwd(bf16, node_chunks(g, D), D, X32, X16, perm, 1, Wv32, Wv16, sv.V, h, "node_linear_v", st));
-    }
-    // 2. compact per pair, side by side in KM[p]: Ka[p] = K[src_p] Watt[r], M[p] = V[src_p] Wmsg[r]
+    // Row products of one step, which do not depend on each other: one launch where they are built as one (fp32 rows up to width
+    // 64), a launch each otherwise.
+    struct Product { bool pairs; const void* in; const void* w32; const void* w16; void* out; const char* label; };
     void* const Mrow = h ? static_cast<void*>(static_cast<uint16_t*>(sv.KM) + D) : static_cast<void*>(static_cast<float*>(sv.KM) + D);
+    auto products = [&](std::initializer_list<Product> list, const char* label) -> rgnn_status_t {
+        if (bf16 || D == 128) {
+            for (const Product& p : list)
+                RGNN_TRY(tl_fwd(bf16, p.pairs ? pair_chunks(g, D) : node_chunks(g, D), D, p.in == X ? X32 : R32(p.in), p.in == X ? X16 : R16(p.in),
+                                p.pairs ? psrc : perm, !p.pairs, static_cast<const float*>(p.w32), p.w16, p.out, h, p.label, st, 0, p.pairs ? 2 : 1));
+            return RGNN_OK;
+        }
+        TypedLinearArgs a[3] = {};
+        int n = 0;
+        for (const Product& p : list) {
+            TypedLinearArgs& t = a[n++];
+            t.tiles = p.pairs ? pair_chunks(g, D).cu1 : node_chunks(g, D).cu1;
+            t.X = static_cast<const float*>(p.in); t.gather = p.pairs ? psrc : perm; t.scatter_out = !p.pairs;
+            t.W = static_cast<const float*>(p.w32); t.Y = static_cast<float*>(p.out); t.y_stride = p.pairs ? 2 : 1;
+        }
+        return typed_linear_fwd_jobs(D, a, n, label, st);
+    };
+    // 1. per node type: Q, and K, V unless they are folded into the per-pair linears
+    // 2. compact per pair, side by side in KM[p]: Ka[p] = K[src_p] Watt[r], M[p] = V[src_p] Wmsg[r]
+    const Product q{false, X, Wq32, Wq16, sv.Q, "node_linear_q"};
     if (fold) {
         //    = X[src_p] (Wk[type of r's sources] Watt[r]) and X[src_p] (Wv[type] Wmsg[r])
         //    With bf16 rows the products are rounded to bf16 once (as K and V would have been) and feed the
         //    matrix cores as they are; rows in the storage of the intermediates: the caller's bf16 X at width
         //    128, its fp32 copy otherwise.
-        RGNN_TRY(hgt_fold(g->R, hw, w.Wf_att, w.Wf_msg, h, st));
-        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, R16(X), psrc, 0, R32(w.Wf_att), R16(w.Wf_att), sv.KM, h, "pair_linear_att", st, 0, 2));
-        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, R16(X), psrc, 0, R32(w.Wf_msg), R16(w.Wf_msg), Mrow, h, "pair_linear_msg", st, 0, 2));
+        RGNN_TRY(hgt_fold(g->R, hw, sv.Wf_att, sv.Wf_msg, h, st));
+        const void* in = h ? X : static_cast<const void*>(X32);
+        RGNN_TRY(products({q, {true, in, R32(sv.Wf_att), R16(sv.Wf_att), sv.KM, "pair_linear_att"},
+                           {true, in, R32(sv.Wf_msg), R16(sv.Wf_msg), Mrow, "pair_linear_msg"}}, "node_pair_linears"));
     } else {
         //    with the per-(relation, head) matrices as block-diagonal d x d weights
         RGNN_TRY(hgt_expand(g->R, hw, w.Wbd_att, w.Wbd_msg, st));
-        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, R32(sv.K), R16(sv.K), psrc, 0, w.Wbd_att, nullptr, sv.KM, h, "pair_linear_att", st, 0, 2));
-        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, R32(sv.V), R16(sv.V), psrc, 0, w.Wbd_msg, nullptr, Mrow, h, "pair_linear_msg", st, 0, 2));
+        RGNN_TRY(products({q, {false, X, Wk32, Wk16, sv.K, "node_linear_k"}, {false, X, Wv32, Wv16, sv.V, "node_linear_v"}}, "node_linears"));
+        RGNN_TRY(products({{true, sv.K, w.Wbd_att, nullptr, sv.KM, "pair_linear_att"}, {true, sv.V, w.Wbd_msg, nullptr, Mrow, "pair_linear_msg"}},
+                          "pair_linears"));
     }
     // 3. one walk per destination: logit per edge and head, softmax over the destination's edges, Z[v][h] = sum_e att[e][h] M[pair_e][h]
     RGNN_TRY(hgt_attend_fwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.partial, w.part_ms, st, h));
@@ -871,9 +901,11 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     dWv = ga.route(w.acc_node[2], dWv, tdd); dWo = ga.route(w.acc_node[3], dWo, tdd);
     dWatt = ga.route(w.acc_rel[0], dWatt, rh * dh * dh); dWmsg = ga.route(w.acc_rel[1], dWmsg, rh * dh * dh);
     dmu = ga.route(w.acc_mu, dmu, rh);
-    // 1. output linear: dZ = dOut Wo^T, dWo = Z^T dOut
-    RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, sv.Z, perm, 1, Wo32, Wo16, dOr, w.dZ, h, static_cast<float*>(dWo), w.tl_part,
-                    "node_linear_out_bwd", st));
+    // 1. output linear: dZ = dOut Wo^T, dWo = Z^T dOut (the shares of the weight gradients are added by one launch, before their
+    //    first use)
+    ShareSums sums;
+    RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, sv.Z, perm, 1, Wo32, Wo16, dOr, w.dZ, h, static_cast<float*>(dWo), w.node_part[0],
+                    "node_linear_out_bwd", st, false, nullptr, nullptr, nullptr, 0, 1, &sums));
     // 2. per destination: att (recomputed) and d logit per edge and head, dQ[v][h] = sum dl Ka[pair][h]
     RGNN_TRY(hgt_attend_bwd(g, D, H, sv.KM, sv.Q, sv.Z, sv.ms, w.dZ, w.dQ, w.adl, w.partial, st, h));
     // 3. per pair: dKa[p][h] = sum dl Q[dst][h], dM[p][h] = sum att dZ[dst][h]
@@ -884,33 +916,47 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     if (fold) {
         // the folded weights take the per-pair gradients straight to X's rows; their own gradients are
         // unfolded into those of the node-type and of the per-relation matrices
-        RGNN_TRY(hgt_fold(g->R, hw, w.Wf_att, w.Wf_msg, h, st));
         if (h) {
             //   dKp[p] = dKa Wf_att^T + dM Wf_msg^T in one kernel, with both weight gradients
             TypedLinearBwdBf16Args b{};
-            b.tiles = &g->pair_tiles_cu1; b.X = X; b.gather = psrc; b.W = w.Wf_att; b.W2 = w.Wf_msg; b.w_bf16 = 1; b.dY = w.dKM;
-            b.dy_stride = 2; b.dXrow = w.dKp; b.dW = w.dWf_att; b.dW2 = w.dWf_msg; b.part = w.tl_part; b.label = "pair_linear_bwd";
+            b.tiles = &g->pair_tiles_cu1; b.X = X; b.gather = psrc; b.W = sv.Wf_att; b.W2 = sv.Wf_msg; b.w_bf16 = 1; b.dY = w.dKM;
+            b.dy_stride = 2; b.dXrow = w.dKp; b.dW = w.dWf_att; b.dW2 = w.dWf_msg; b.part = w.pair_part[0]; b.label = "pair_linear_bwd"; b.sums = &sums;
             RGNN_TRY(typed_linear_bwd_bf16(D, b, st));
-        } else {
-            RGNN_TRY(tl_bwd(false, pair_chunks(g, D), D, Xr, psrc, 0, w.Wf_att, nullptr, dKa, w.dKp, false, w.dWf_att, w.tl_part,
-                            "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
-            RGNN_TRY(tl_bwd(false, pair_chunks(g, D), D, Xr, psrc, 0, w.Wf_msg, nullptr, dM, w.dVp, false, w.dWf_msg, w.tl_part,
-                            "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
+        } else if (!hgt_bwd_jobs(g, desc)) {
+            RGNN_TRY(tl_bwd(false, pair_chunks(g, D), D, Xr, psrc, 0, static_cast<const float*>(sv.Wf_att), nullptr, dKa, w.dKp, false, w.dWf_att,
+                            w.pair_part[0], "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2, &sums));
+            RGNN_TRY(tl_bwd(false, pair_chunks(g, D), D, Xr, psrc, 0, static_cast<const float*>(sv.Wf_msg), nullptr, dM, w.dVp, false, w.dWf_msg,
+                            w.pair_part[1], "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2, &sums));
         }
+        // dX = dQ Wq^T + sums over each node's pairs of the two per-pair gradients
+        if (hgt_bwd_jobs(g, desc)) {
+            TypedLinearBwdArgs b[3] = {};
+            for (int k = 0; k < 2; ++k) {
+                b[k].tiles = &g->pair_tiles_hgt; b[k].gather = psrc; b[k].W = static_cast<const float*>(k ? sv.Wf_msg : sv.Wf_att);
+                b[k].dY = static_cast<const float*>(k ? dM : dKa); b[k].dy_stride = 2; b[k].dXrow = static_cast<float*>(k ? w.dVp : w.dKp);
+                b[k].dW = k ? w.dWf_msg : w.dWf_att; b[k].part = w.pair_part[k];
+            }
+            b[2].tiles = &g->node_tiles_hgt; b[2].gather = perm; b[2].dy_gathered = b[2].scatter_dx = 1; b[2].W = Wq32;
+            b[2].dY = static_cast<const float*>(w.dQ); b[2].dXrow = w.dXq; b[2].dW = static_cast<float*>(dWq); b[2].part = w.node_part[1];
+            for (TypedLinearBwdArgs& x : b) { x.X = static_cast<const float*>(Xr); x.sums = &sums; }
+            RGNN_TRY(typed_linear_bwd_jobs(D, b, 3, "node_pair_linears_bwd", st));
+        } else {
+            RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
+                            w.node_part[1], "node_linear_q_bwd", st, false, nullptr, nullptr, nullptr, 0, 1, &sums));
+        }
+        RGNN_TRY(sums.launch(st));
         RGNN_TRY(hgt_fold_bwd(g->T, g->R, hw, w.dWf_att, w.dWf_msg, static_cast<float*>(dWk), static_cast<float*>(dWv),
                               static_cast<float*>(dWatt), static_cast<float*>(dWmsg), static_cast<float*>(dmu), st));
-        // dX = dQ Wq^T + sums over each node's pairs of the two per-pair gradients
-        RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
-                        w.tl_part, "node_linear_q_bwd", st));
         if (acc) RGNN_TRY(add_into((size_t)g->N * D, static_cast<const float*>(dX), w.dXq, st));
         RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, w.dXq, dX, st, h, 0, 1, h ? nullptr : w.dVp));
         return ga.flush(st);
     }
     RGNN_TRY(hgt_expand(g->R, hw, w.Wbd_att, w.Wbd_msg, st));
-    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.tl_part,
-                    "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
-    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.tl_part,
-                    "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2));
+    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, sv.K, psrc, 0, w.Wbd_att, nullptr, dKa, w.dKp, h, w.dWbd_att, w.pair_part[0],
+                    "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2, &sums));
+    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, sv.V, psrc, 0, w.Wbd_msg, nullptr, dM, w.dVp, h, w.dWbd_msg, w.pair_part[1],
+                    "pair_linear_msg_bwd", st, false, nullptr, nullptr, nullptr, 0, 2, &sums));
+    RGNN_TRY(sums.launch(st));
     RGNN_TRY(hgt_extract(g->R, hw, w.dWbd_att, w.dWbd_msg, static_cast<float*>(dWatt), static_cast<float*>(dWmsg),
                          static_cast<float*>(dmu), st));
     // 5. dK[u], dV[u] = sums over u's pairs
@@ -919,11 +965,12 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
     // 6. node linears backward and dX
     //    (bf16 rows: the three input gradients are accumulated into dX by the kernels themselves)
     RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wk32, Wk16, w.dK, h ? dX : static_cast<void*>(w.dXk),
-                    false, static_cast<float*>(dWk), w.tl_part, "node_linear_k_bwd", st, h && acc));
+                    false, static_cast<float*>(dWk), w.node_part[0], "node_linear_k_bwd", st, h && acc, nullptr, nullptr, nullptr, 0, 1, &sums));
     RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wq32, Wq16, w.dQ, h ? dX : static_cast<void*>(w.dXq),
-                    false, static_cast<float*>(dWq), w.tl_part, "node_linear_q_bwd", st, h));
+                    false, static_cast<float*>(dWq), w.node_part[1], "node_linear_q_bwd", st, h, nullptr, nullptr, nullptr, 0, 1, &sums));
     RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wv32, Wv16, w.dV, h ? dX : static_cast<void*>(w.dXv),
-                    false, static_cast<float*>(dWv), w.tl_part, "node_linear_v_bwd", st, h));
+                    false, static_cast<float*>(dWv), w.node_part[2], "node_linear_v_bwd", st, h, nullptr, nullptr, nullptr, 0, 1, &sums));
+    RGNN_TRY(sums.launch(st));
     if (!h) {
         if (acc) RGNN_TRY(add_into((size_t)g->N * D, static_cast<const float*>(dX), w.dXk, st));
         RGNN_TRY(add3((size_t)g->N * D, w.dXk, w.dXq, w.dXv, static_cast<float*>(dX), st));

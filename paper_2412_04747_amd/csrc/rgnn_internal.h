@@ -117,6 +117,8 @@ struct rgnn_graph {
     rgnn::TileList node_tiles_cu2;
     rgnn::TileList node_tiles_cu1;
     rgnn::TileList all_tiles_cu1;
+    rgnn::TileList pair_tiles_hgt;         // the shares of two lists of the pairs and one of the nodes in one chunk per compute unit
+    rgnn::TileList node_tiles_hgt;         // for all three together
     rgnn::ItemList dst_items;              // CSR edges by destination
     rgnn::ItemList pair_items;             // transposed edges by pair
     rgnn::ItemList pair_items_multi;       // the same, pairs with two or more edges only
@@ -169,6 +171,21 @@ struct SumArgs {
     size_t partial_copy, out_copy;       // floats from one set to the next
     int num_split, D, copies;
 };
+// What backward typed linears leave to be summed: dW[s] (kn floats) and, when given, dW2[s] (kd floats) = sums of segment s's slots of
+// kn + kd floats each, for up to kMax lists, and optionally pieces as above.  One launch (traversal.hip) sums them all.
+struct ShareSums {
+    static constexpr int kMax = 4;
+    struct Job {
+        const float* part; const int32_t* seg_slot_ptr;
+        int blocks, col_blocks, many, kn, kd;
+        float* dW; float* dW2;
+    };
+    Job job[kMax];
+    int n = 0;
+    SumArgs pieces{};
+    rgnn_status_t add(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2);
+    rgnn_status_t launch(hipStream_t st);      // and is empty again
+};
 struct TypedLinearBwdArgs {
     const TileList* tiles;
     const float* X;          // forward input rows
@@ -198,7 +215,7 @@ struct TypedLinearBwdArgs {
     const float* wvec = nullptr;     // [segs][ND]
     int sel_heads = 0;
     int dy_stride = 1;               // rows of dY are dy_stride * d_out floats apart (1 or 2)
-    const SumArgs* with_sums = nullptr;   // summed in the launch that sums the slots
+    ShareSums* sums = nullptr;       // the slots are left to the caller's sums (part then has to last until they are launched)
 };
 // bf16 matrix-core variant (typed_linear_bf16.hip): Y[i] = A[g(i)] W[seg]
 struct TypedLinearBf16Args {
@@ -239,15 +256,18 @@ struct TypedLinearBwdBf16Args {
     const int32_t* ysel = nullptr;
     const void* dY_alt = nullptr;
     const float* yscale = nullptr;
+    ShareSums* sums = nullptr;   // as in TypedLinearBwdArgs
 };
 rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipStream_t st);
-// dW[s] (kn floats) and, when given, dW2[s] (kd floats) = sums of the segments' slots of kn + kd floats (traversal.hip); with_sums: and the
-// rows of a list's cut segments from their pieces in the same launch, out[h][split_row[s]] = sum of partial[h][split_ptr[s] ..)
+// the slots of a list go to the caller's sums, or are summed by a launch of their own (sums null)
 rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2, hipStream_t st,
-                                       const SumArgs* with_sums = nullptr);
+                                       ShareSums* sums);
 
 size_t typed_linear_bwd_scratch_floats(int d_in, int d_out, const TileList& t, int vectors = 1);   // vectors: of a slot's vector part
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st);
+// up to three products of gathered rows in one launch, widths 32 and 64: rows scattered back the same way, or two widths apart
+rgnn_status_t typed_linear_fwd_jobs(int d, const TypedLinearArgs* a, int n, const char* label, hipStream_t st);
+rgnn_status_t typed_linear_bwd_jobs(int d, const TypedLinearBwdArgs* a, int n, const char* label, hipStream_t st);   // with sums
 // width 128 (typed_linear_split.hip): fp32 operands split into three bf16 planes; the backward fills the slots only
 rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st);
 rgnn_status_t typed_linear_split_bwd(const TypedLinearBwdArgs& a, hipStream_t st);

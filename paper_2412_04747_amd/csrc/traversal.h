@@ -48,7 +48,7 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
 // RGAT's backward (heads 1, 2 or 4), one launch: for the pairs with several edges G[p] = sum_e att_e dOut[dst_e] (+ ds_src[p] ws[r] per
 // head, with ws) and ds_src[p] = sum_e dz_e per head (element p * ds_src_stride + h; not for the pairs that are cut: the caller sums
 // those); by relation U[h][r] = sum_q ds_dst[q][h] X[dst_q], whose cut relations stay as pieces in run_partial
-// (typed_linear_slot_reduce adds them).
+// (ShareSums adds them).
 struct RgatBwdWalks {
     int d_in, d_out, heads;
     const float* adz; const float* dOut; float* G; float* ds_src; int ds_src_stride; const float* ws; float* pair_partial;

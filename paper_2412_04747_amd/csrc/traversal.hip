@@ -822,10 +822,8 @@ __global__ void zero_f32_kernel(size_t n, float* __restrict__ x) {
 // dW[s] (and Avec[s]) = sum of the partial slots of segment s; kn / kd = floats of a slot's matrix / vector part, both
 // multiples of 4.  A workgroup owns C4 consecutive float4 of one segment's slots; its G lane groups take the slots in turn,
 // four loads in flight each, and the group sums are added in four chains through LDS, so the result does not depend on
-// scheduling (in one chain of 31 additions the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.24e-7, and dWmsg
-// of HGT at 300k edges 2.65e-7, now 2.53e-7, in the same time; by halves with a barrier each 1.21e-7 and 2.55e-7, 1 us more).  Bound by the chain of loads of the segment with the most slots: with one lane per float and four loads in
-// flight, a self-loop's one segment of 512 slots plus a 45-relation list took 30 us each, now 7 us; 768 slots of 64 KB
-// (50 MB) in 5 and 17 segments 24 us each, now 13 us.
+// scheduling (as one chain the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.27e-7).  Bound by the chain of loads of the
+// segment with the most slots, and with thousands of segments by their workgroups' start.
 template <int G, int C4>
 __device__ __forceinline__ void slot_reduce_block(const float* __restrict__ part, const int32_t* __restrict__ seg_slot_ptr, int seg, int col_blk,
                                                   int kn, int kd, float* __restrict__ dW, float* __restrict__ Avec, float4* red) {
@@ -852,7 +850,7 @@ __device__ __forceinline__ void slot_reduce_block(const float* __restrict__ part
     }
     red[g * C4 + c] = make_float4(s0.x + s1.x, s0.y + s1.y, s0.z + s1.z, s0.w + s1.w);
     __syncthreads();
-    constexpr int CH = G * C4 >= 512 ? 64 / C4 : 1;        // chains over the groups, one wavefront's worth of lanes
+    constexpr int CH = C4 < 64 ? 64 / C4 : 1;              // chains over the groups, one wavefront's worth of lanes
     if (g >= CH) return;
     float4 t = red[g * C4 + c];
 #pragma unroll
@@ -872,11 +870,11 @@ __device__ __forceinline__ void slot_reduce_block(const float* __restrict__ part
 
 // The other kind of shares that RGAT's backward leaves per relation: U[h][r] from the pieces of r's run list (SumArgs: one copy of
 // rows per head).  Independent of the slots, so one launch sums both.  A workgroup takes 16 columns of one relation and head,
-// 128 lane groups take its pieces in turn, eight loads in flight in four chains, and the group sums are added by halves.  Bound by
+// 64 lane groups take its pieces in turn in four chains, and the group sums are added by halves.  Bound by
 // the chain of loads of the largest relation (4.3M runs of 200 relations, 17k pieces, width 64: both sums 17 us, as launches of
 // their own 7 and 8.5; at 93k runs of 50 relations 6 us, two launches of 6).
 __device__ __forceinline__ void piece_sum_block(const SumArgs& u, int blk, float4* red) {
-    constexpr int C4 = 4, G = 128;
+    constexpr int C4 = 4, G = 64;
     const int cols = u.D / (4 * C4), s = blk / (cols * u.copies), h = blk / cols % u.copies;
     const int c = threadIdx.x % C4, g = threadIdx.x / C4, c4 = blk % cols * C4 + c;
     const float* __restrict__ p = u.partial + (size_t)h * u.partial_copy + c4 * 4;
@@ -884,13 +882,13 @@ __device__ __forceinline__ void piece_sum_block(const SumArgs& u, int blk, float
     float4 acc[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) acc[x] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k = p0 + g; k < p1; k += 8 * G) {
-        float4 r[8];
+    for (int k = p0 + g; k < p1; k += 4 * G) {
+        float4 r[4];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) r[x] = *reinterpret_cast<const float4*>(p + (size_t)min(k + x * G, p1 - 1) * u.D);
+        for (int x = 0; x < 4; ++x) r[x] = *reinterpret_cast<const float4*>(p + (size_t)min(k + x * G, p1 - 1) * u.D);
 #pragma unroll
-        for (int x = 0; x < 8; ++x)
-            if (k + x * G < p1) fma4(acc[x & 3], 1.f, r[x]);
+        for (int x = 0; x < 4; ++x)
+            if (k + x * G < p1) fma4(acc[x], 1.f, r[x]);
     }
     fma4(acc[0], 1.f, acc[1]);
     fma4(acc[2], 1.f, acc[3]);
@@ -904,34 +902,58 @@ __device__ __forceinline__ void piece_sum_block(const SumArgs& u, int blk, float
     }
     if (g == 0) *reinterpret_cast<float4*>(u.out + (size_t)h * u.out_copy + (size_t)u.split_row[s] * u.D + c4 * 4) = red[c];
 }
-template <int G, int C4>
-__global__ __launch_bounds__(512) void sum_shares_kernel(const float* __restrict__ part, const int32_t* __restrict__ seg_slot_ptr, int num_segs,
-                                                         int col_blocks, int kn, int kd, float* __restrict__ dW, float* __restrict__ Avec, SumArgs u) {
-    static_assert(G * C4 == 512, "workgroups of 512 threads");
-    __shared__ float4 red[512];
-    const int slot_blocks = num_segs * col_blocks;
-    if ((int)blockIdx.x < slot_blocks) slot_reduce_block<G, C4>(part, seg_slot_ptr, blockIdx.x / col_blocks, blockIdx.x % col_blocks, kn, kd, dW, Avec, red);
-    else piece_sum_block(u, blockIdx.x - slot_blocks, red);
+// One launch for all shares of a backward pass.  Few segments with many slots each (a self-loop weight, node types, few relations):
+// many lane groups on narrow column ranges; many segments with a few slots each: few groups, wide ranges.  HGT in bf16, three lists:
+// 54 us as three launches, now 38 (2M nodes, 5.4M pairs), 34 and 27 (200k nodes); in fp32 at 300k edges four launches of 6, now one
+// of 7; RGCN with a self-loop 13 and 7.  (With workgroups of 512 threads 59 and 39 us in the first two; 500 relations of width 128,
+// one list, 29 us with a grid of segments x columns, 34 here, 45 with 512 threads.  N is a template parameter so that the jobs'
+// fields are loaded together.)
+template <int N>
+__global__ __launch_bounds__(256) void sum_shares_kernel(ShareSums s) {
+    __shared__ float4 red[256];
+    int blk = blockIdx.x;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const ShareSums::Job& j = s.job[k];
+        if (blk < j.blocks) {
+            const int seg = blk / j.col_blocks, cb = blk % j.col_blocks;
+            if (j.many) slot_reduce_block<16, 16>(j.part, j.seg_slot_ptr, seg, cb, j.kn, j.kd, j.dW, j.dW2, red);
+            else slot_reduce_block<4, 64>(j.part, j.seg_slot_ptr, seg, cb, j.kn, j.kd, j.dW, j.dW2, red);
+            return;
+        }
+        blk -= j.blocks;
+    }
+    piece_sum_block(s.pieces, blk, red);
 }
 
-// Few segments with many slots each (a self-loop weight, node types, few relations): many lane groups on narrow column
-// ranges; many segments with a few slots each: few groups, wide ranges.
-rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* Avec, hipStream_t st,
-                                       const SumArgs* with_sums) {
-    KernelTimer kt(st, "typed_linear_bwd.reduce");
-    const SumArgs u = with_sums ? *with_sums : SumArgs{};
-    const int n4 = (kn + kd) / 4, more = u.num_split > 0 ? u.num_split * u.copies * (u.D / 16) : 0;
+rgnn_status_t ShareSums::add(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2) {
+    if (n == kMax) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: more than %d lists", kMax);
+    const int n4 = (kn + kd) / 4;
     const bool many = tiles.num_slots > 8 * tiles.num_segs;
-    const int col_blocks = many ? (n4 + 15) / 16 : (n4 + 63) / 64;
-    const int64_t blocks = (int64_t)tiles.num_segs * col_blocks + more;
-    if (blocks > INT32_MAX) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: %d segments are too many", tiles.num_segs);
-    if (blocks == 0) return RGNN_OK;
-    if (many)
-        hipLaunchKernelGGL((sum_shares_kernel<32, 16>), dim3((unsigned)blocks), dim3(512), 0, st, part, tiles.seg_slot_ptr, tiles.num_segs, col_blocks, kn, kd, dW, Avec, u);
-    else
-        hipLaunchKernelGGL((sum_shares_kernel<8, 64>), dim3((unsigned)blocks), dim3(512), 0, st, part, tiles.seg_slot_ptr, tiles.num_segs, col_blocks, kn, kd, dW, Avec, u);
-    RGNN_CHECK_LAUNCH();
+    const int cols = many ? (n4 + 15) / 16 : (n4 + 63) / 64;
+    if ((int64_t)tiles.num_segs * cols > INT32_MAX / (kMax + 1)) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: %d segments are too many", tiles.num_segs);
+    job[n++] = Job{part, tiles.seg_slot_ptr, tiles.num_segs * cols, cols, many, kn, kd, dW, dW2};
     return RGNN_OK;
+}
+rgnn_status_t ShareSums::launch(hipStream_t st) {
+    int64_t blocks = pieces.num_split > 0 ? (int64_t)pieces.num_split * pieces.copies * (pieces.D / 16) : 0;
+    for (int k = 0; k < n; ++k) blocks += job[k].blocks;
+    if (blocks > INT32_MAX) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: too many segments");
+    if (blocks > 0) {
+        KernelTimer kt(st, "typed_linear_bwd.reduce");
+        auto kern = n == 1 ? sum_shares_kernel<1> : n == 2 ? sum_shares_kernel<2> : n == 3 ? sum_shares_kernel<3> : sum_shares_kernel<4>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, *this);
+        RGNN_CHECK_LAUNCH();
+    }
+    n = 0;
+    pieces = SumArgs{};
+    return RGNN_OK;
+}
+rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2, hipStream_t st,
+                                       ShareSums* sums) {
+    ShareSums own;
+    RGNN_TRY((sums ? sums : &own)->add(tiles, part, kn, kd, dW, dW2));
+    return sums ? RGNN_OK : own.launch(st);
 }
 
 // ------------------------------------------------------------------ RGAT parameter-gradient epilogue

@@ -95,10 +95,9 @@ struct FwdShape {
     static constexpr size_t LDS = sizeof(float) * (KD * ND + NW * 32 * XS);
 };
 template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1>
-__global__ __launch_bounds__((64 * FwdShape<KD, ND, VEC, ACCUM>::NW))
-void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const int32_t* __restrict__ gather,
-                                  const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
-                                  float* __restrict__ s_out, int s_heads, int relu) {
+__device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const float* __restrict__ X, const int32_t* __restrict__ gather,
+                                         const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
+                                         float* __restrict__ s_out, int s_heads, int relu) {
     using S = FwdShape<KD, ND, VEC, ACCUM>;
     constexpr int NW = S::NW, XS = S::XS, KS = S::KS, PH = KD / KS;
     constexpr int CB = ND / 32;
@@ -112,7 +111,7 @@ void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const
     float* Xw = smem + KD * ND + wave * 32 * XS;            // [32][XS] private to this wavefront
     const int m = lane & 31, kh = lane >> 5;
     const int ci = lane % LPRI, ri = lane / LPRI, co = lane % LPRO, ro = lane / LPRO;
-    const int t0 = t.chunk_tile[blockIdx.x], t1 = t.chunk_tile[blockIdx.x + 1];
+    const int t0 = t.chunk_tile[chunk], t1 = t.chunk_tile[chunk + 1];
     for (int ta = t0; ta < t1;) {
         const int tb = run_end(t.tile_seg, ta, t1, lane);
         const int seg = t.tile_seg[ta];
@@ -262,6 +261,39 @@ void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const
     }
 }
 
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+__global__ __launch_bounds__((64 * FwdShape<KD, ND, VEC, ACCUM>::NW))
+void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const int32_t* __restrict__ gather,
+                                  const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
+                                  float* __restrict__ s_out, int s_heads, int relu) {
+    fwd_wave<KD, ND, GATHER, SCATTER, ACCUM, VEC>(t, blockIdx.x, X, gather, W, Y, vec, s_out, s_heads, relu);
+}
+
+// Several products that do not depend on each other in one launch (HGT: a node linear, rows gathered and scattered, and the two
+// linears of the pairs, whose results lie side by side): workgroup b takes the b-th chunk of the jobs' chunks in a row.  Short
+// products leave the chip half empty at their ends, and each costs a launch: 30k nodes and 75k pairs of width 64, 12.4 + 21.9 + 17.7
+// us one by one, 29 together.
+struct FwdJob { TileArgs t; int chunks, pairs; const float* X; const int32_t* gather; const float* W; float* Y; };
+struct BwdJob {
+    TileArgs t; int chunks, pairs; const float* X; const int32_t* gather; const float* W; const float* dY; float* dX; float* part;
+};
+constexpr int kMaxJobs = 3;
+struct FwdJobs { FwdJob job[kMaxJobs]; int n; };
+struct BwdJobs { BwdJob job[kMaxJobs]; int n; };
+template <typename J>
+__device__ __forceinline__ int job_of(const J& jobs, int& chunk) {
+    int k = 0;
+    while (k + 1 < jobs.n && chunk >= jobs.job[k].chunks) chunk -= jobs.job[k++].chunks;
+    return k;
+}
+template <int D>
+__global__ __launch_bounds__((64 * FwdShape<D, D, false, false>::NW)) void typed_linear_fwd_jobs_kernel(FwdJobs jobs) {
+    int chunk = blockIdx.x;
+    const FwdJob& j = jobs.job[job_of(jobs, chunk)];
+    if (j.pairs) fwd_wave<D, D, true, false, false, false, 2>(j.t, chunk, j.X, j.gather, j.W, j.Y, nullptr, nullptr, 1, 0);
+    else fwd_wave<D, D, true, true, false, false, 1>(j.t, chunk, j.X, j.gather, j.W, j.Y, nullptr, nullptr, 1, 0);
+}
+
 // Backward of a segment's rows:
 //   dXrow[i]  = dY[i] W^T + rowscale[i] * xvec[seg]   (MFMA, contraction over the output features;
 //                                                     the rank-1 term is added when the row is stored)
@@ -297,14 +329,10 @@ void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const
 struct RowSelect { const int32_t* sel; const float* alt; const float2* ds_scale; const float* scale; const float* hcoef; const float* wvec; };
 // DS: the rows of dY are DS * ND floats apart (not with SEL).
 template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1>
-__global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, const float* __restrict__ X,
-                                                                    const int32_t* __restrict__ gather,
-                                                                    const float* __restrict__ W,
-                                                                    const float* __restrict__ dY,
-                                                                    float* __restrict__ dXrow,
-                                                                    const float* __restrict__ rowscale,
-                                                                    const float* __restrict__ vec,
-                                                                    float* __restrict__ part, RowSelect ys) {
+__device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const float* __restrict__ X, const int32_t* __restrict__ gather,
+                                         const float* __restrict__ W, const float* __restrict__ dY, float* __restrict__ dXrow,
+                                         const float* __restrict__ rowscale, const float* __restrict__ vec,
+                                         float* __restrict__ part, const RowSelect& ys) {
     static_assert(!SEL || (!DYG && DS == 1), "the row selector replaces the dY gather");
     static_assert(HS == 0 || (SEL && !RS && (HS == 2 || HS == 4)), "per-head row selector: two or four heads, no rowscale");
     constexpr int NW = 8;
@@ -324,8 +352,8 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
     float* dsw = Yw + 32 * YS;                              // [32]      rowscale of the unit's rows
     const int m = lane & 31, kh = lane >> 5;
     const int cx = lane % LPRX, rx = lane / LPRX, cy = lane % LPRY, ry = lane / LPRY;
-    const int t0 = t.chunk_tile[blockIdx.x], t1 = t.chunk_tile[blockIdx.x + 1];
-    int slot = t.chunk_slot[blockIdx.x];
+    const int t0 = t.chunk_tile[chunk], t1 = t.chunk_tile[chunk + 1];
+    int slot = t.chunk_slot[chunk];
     for (int ta = t0; ta < t1; ++slot) {
         const int tb = run_end(t.tile_seg, ta, t1, lane);
         const int seg = t.tile_seg[ta];
@@ -611,16 +639,39 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
     }
 }
 
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1>
+__global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, const float* __restrict__ X,
+                                                                    const int32_t* __restrict__ gather,
+                                                                    const float* __restrict__ W,
+                                                                    const float* __restrict__ dY,
+                                                                    float* __restrict__ dXrow,
+                                                                    const float* __restrict__ rowscale,
+                                                                    const float* __restrict__ vec,
+                                                                    float* __restrict__ part, RowSelect ys) {
+    bwd_wave<KD, ND, GATHER, DYG, SCATTER, RS, SEL, HS, DS>(t, blockIdx.x, X, gather, W, dY, dXrow, rowscale, vec, part, ys);
+}
+// The backward of the products above.  A workgroup has a compute unit to itself, and a chunk costs a load of the weight and a flush
+// of the gradient whatever its length, so the chunks of all jobs together are one per compute unit (sizes as above: 30 + 29 + 21.5 us
+// one by one, 47 together).
+template <int D>
+__global__ __launch_bounds__(512) void typed_linear_bwd_jobs_kernel(BwdJobs jobs) {
+    int chunk = blockIdx.x;
+    const BwdJob& j = jobs.job[job_of(jobs, chunk)];
+    const RowSelect none{};
+    if (j.pairs) bwd_wave<D, D, true, false, false, false, false, 0, 2>(j.t, chunk, j.X, j.gather, j.W, j.dY, j.dX, nullptr, nullptr, j.part, none);
+    else bwd_wave<D, D, true, true, true, false>(j.t, chunk, j.X, j.gather, j.W, j.dY, j.dX, nullptr, nullptr, j.part, none);
+}
+
 // ---------------------------------------------------------------------------------------
 static TileArgs tile_args(const TileList& t) {
     return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot};
 }
 
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1>
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
 static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st) {
     using S = FwdShape<KD, ND, VEC, ACCUM>;
     constexpr size_t lds = S::LDS;
-    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, OS>;
+    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(64 * S::NW), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
@@ -636,12 +687,7 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
     if (v && (a.s_heads < 1 || (a.s_heads & (a.s_heads - 1)) || a.s_heads > ND / 4))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, ND);
     if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
-    if (a.y_stride == 2) {
-        if constexpr (KD == ND && KD < 128) {
-            if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false, 2>(a, st);
-        }
-        RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built for gathered rows of equal widths only");
-    }
+    if (a.y_stride != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built in the launches of several products only");
     if (g && !sc && !ac && v) return launch_fwd_wave<KD, ND, true, false, false, true>(a, st);
     if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false>(a, st);
     if constexpr (KD == ND && KD < 128) {
@@ -718,7 +764,7 @@ static rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
         if (!done) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: this combination of gather / scatter / rowscale is not built");
     }
     const int kd = KD * (KD <= 64 && a.ysel && a.hcoef ? a.sel_heads : 1);
-    return typed_linear_slot_reduce(*a.tiles, a.part, KD * ND, kd, a.dW, a.Avec, st, a.with_sums);
+    return typed_linear_slot_reduce(*a.tiles, a.part, KD * ND, kd, a.dW, a.Avec, st, a.sums);
 }
 
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st) {
@@ -728,6 +774,62 @@ rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a,
     if (d_in == 32 && d_out == 64) return launch_bwd<32, 64>(a, st);
     if (d_in == 64 && d_out == 32) return launch_bwd<64, 32>(a, st);
     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: d_in = %d, d_out = %d not supported (need 32 / 64 / 128, different widths only among 32 and 64)", d_in, d_out);
+}
+
+// The products of several argument sets in one launch: gathered rows, either scattered back (y_stride 1) or two widths apart.
+static rgnn_status_t jobs_check(bool ok, int n) {
+    if (!ok || n < 1 || n > kMaxJobs) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear jobs: one to %d plain products of gathered rows, width 32 or 64", kMaxJobs);
+    return RGNN_OK;
+}
+rgnn_status_t typed_linear_fwd_jobs(int d, const TypedLinearArgs* a, int n, const char* label, hipStream_t st) {
+    FwdJobs jobs{};
+    int blocks = 0;
+    for (int k = 0; k < n; ++k) {
+        const bool pairs = a[k].y_stride == 2;
+        RGNN_TRY(jobs_check((d == 32 || d == 64) && a[k].gather && !a[k].accumulate && !a[k].vec && (pairs ? !a[k].scatter_out : a[k].scatter_out && a[k].y_stride == 1), n));
+        if (a[k].tiles->num_tiles == 0) continue;
+        jobs.job[jobs.n++] = FwdJob{tile_args(*a[k].tiles), a[k].tiles->num_chunks, pairs, a[k].X, a[k].gather, a[k].W, a[k].Y};
+        blocks += a[k].tiles->num_chunks;
+    }
+    if (blocks == 0) return RGNN_OK;
+    KernelTimer kt(st, label);
+#define RGNN_JOBS(D_)                                                                                               \
+    do {                                                                                                            \
+        constexpr size_t lds = FwdShape<D_, D_, false, false>::LDS;                                                 \
+        RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(typed_linear_fwd_jobs_kernel<D_>), lds));          \
+        hipLaunchKernelGGL(typed_linear_fwd_jobs_kernel<D_>, dim3(blocks), dim3(64 * FwdShape<D_, D_, false, false>::NW), lds, st, jobs); \
+    } while (0)
+    if (d == 64) RGNN_JOBS(64);
+    else RGNN_JOBS(32);
+#undef RGNN_JOBS
+    RGNN_HIP(hipGetLastError());
+    return RGNN_OK;
+}
+rgnn_status_t typed_linear_bwd_jobs(int d, const TypedLinearBwdArgs* a, int n, const char* label, hipStream_t st) {
+    BwdJobs jobs{};
+    int blocks = 0;
+    for (int k = 0; k < n; ++k) {
+        const bool pairs = a[k].dy_stride == 2;
+        RGNN_TRY(jobs_check((d == 32 || d == 64) && a[k].gather && !a[k].rowscale && !a[k].ysel && a[k].sums &&
+                            (pairs ? !a[k].dy_gathered && !a[k].scatter_dx : a[k].dy_gathered && a[k].scatter_dx && a[k].dy_stride == 1), n));
+        RGNN_TRY(typed_linear_slot_reduce(*a[k].tiles, a[k].part, d * d, d, a[k].dW, nullptr, st, a[k].sums));
+        if (a[k].tiles->num_tiles == 0) continue;
+        jobs.job[jobs.n++] = BwdJob{tile_args(*a[k].tiles), a[k].tiles->num_chunks, pairs, a[k].X, a[k].gather, a[k].W, a[k].dY, a[k].dXrow, a[k].part};
+        blocks += a[k].tiles->num_chunks;
+    }
+    if (blocks == 0) return RGNN_OK;
+    KernelTimer kt(st, label);
+#define RGNN_JOBS(D_)                                                                                               \
+    do {                                                                                                            \
+        constexpr size_t lds = sizeof(float) * (D_ * (D_ + 1) + 8 * (64 * (D_ + 4) + 32));                          \
+        RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(typed_linear_bwd_jobs_kernel<D_>), lds));          \
+        hipLaunchKernelGGL(typed_linear_bwd_jobs_kernel<D_>, dim3(blocks), dim3(512), lds, st, jobs);               \
+    } while (0)
+    if (d == 64) RGNN_JOBS(64);
+    else RGNN_JOBS(32);
+#undef RGNN_JOBS
+    RGNN_HIP(hipGetLastError());
+    return RGNN_OK;
 }
 
 }  // namespace rgnn

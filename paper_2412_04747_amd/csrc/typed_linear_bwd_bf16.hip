@@ -334,7 +334,7 @@ rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipS
             RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: this combination is not built");
         }
     }
-    return typed_linear_slot_reduce(*a.tiles, a.part, d * d, a.W2 ? d * d : 0, a.dW, a.dW2, st);
+    return typed_linear_slot_reduce(*a.tiles, a.part, d * d, a.W2 ? d * d : 0, a.dW, a.dW2, st, a.sums);
 }
 
 }  // namespace rgnn

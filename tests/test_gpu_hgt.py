@@ -153,6 +153,17 @@ def test_relation_sizes_around_the_row_tiles(dtype, d, H, tied):
     _run(N, T, R, src.astype(np.int32), dst.astype(np.int32), rel.astype(np.int32), ntype, p, d, H, f"tiles-{dtype}-{tied}", dtype=dtype)
 
 
+@pytest.mark.parametrize("d,H", [(32, 1), (64, 4)])
+@pytest.mark.parametrize("N,R,E", [(1, 1, 1), (40000, 3, 0), (40000, 3, 70), (300, 40, 30000), (3000, 2, 40000)])
+def test_nodes_and_pairs_share_the_compute_units(N, R, E, d, H):
+    """The node and pair products of one launch split the compute units by their rows: none, few and nearly all of them pairs."""
+    rng = np.random.default_rng(N + E + d)
+    src, dst = rng.integers(0, N, E).astype(np.int32), rng.integers(0, N, E).astype(np.int32)
+    rel = rng.integers(0, R, E).astype(np.int32)
+    p = synth.hgt_params(rng, N, 1, R, d, H, with_mu=True)
+    _run(N, 1, R, src, dst, rel, np.zeros(N, np.int32), p, d, H, "shared-units")
+
+
 def _wide_case(seed, tied):
     """Width 128, four heads: 230 nodes of two types, five relations, 700 edges; with `tied` the sources of a relation are
     of one type."""

@@ -281,8 +281,8 @@ def test_one_segment_of_many_pieces(d, H, n_hub):
 
 @pytest.mark.parametrize("d,H", [(32, 2), (64, 1), (64, 4), (128, 1)])
 def test_relations_of_many_run_pieces(d, H):
-    """Relations whose run lists are cut at 32 runs: whole ones, and 2, 127, 128, 129 and 1025 pieces (128 lane groups sum a
-    relation's pieces, eight at a time)."""
+    """Relations whose run lists are cut at 32 runs: whole ones, and 2, 127, 128, 129 and 1025 pieces (64 lane groups sum a
+    relation's pieces, four at a time)."""
     runs = [1, 32, 33, 127 * 32, 128 * 32, 128 * 32 + 1, 1024 * 32 + 7]
     N, R = max(runs), len(runs) + 1                                   # the last relation has no edge
     rng = np.random.default_rng(d + H)
