@@ -139,6 +139,8 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
         "self_loop_bwd": (mm, N * 3 * r32 + w2, 4.0 * N * d * d),
         # fused RGAT walk: row + in_pair + in_rel + in_run per edge, s_dst per run and head, out row + item + (m, s) per head per node
         "aggregate_fwd": ("hbm", E * (row + 12) + Q * 4 * H + N * (r32 + 8 + 8 * H), 4.0 * E * d) if fused else agg_dst,
+        # the whole RGCN forward of a small graph: rows in and out, the edges' sources, every weight once
+        "rgcn_small_fwd": ("hbm", 2 * N * r32 + E * 4 + Q * 8 + R * w2, 2.0 * Q * d * d),
         # the same sum edge by edge with atomic adds: + in_run and run_dst per edge, and the zero fill
         "aggregate_fwd_edge_parallel": ("hbm", agg_dst[1] + E * 8 + N * r32, 2.0 * E * d),
         # per edge: Hs row + in_pair + att + (att, dz) store; per node: dOut row + out row + item;

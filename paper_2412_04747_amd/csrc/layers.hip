@@ -465,6 +465,8 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* W32 = !h ? stg.in(W, (size_t)g->R * desc->d_in * D) : nullptr;
     const float* W032 = stg.in(W0, (size_t)desc->d_in * D);
     RGNN_TRY(stg.status);
+    if (sched_rgcn_small(desc->dtype, desc->d_in, D, g->Q, g->N, g->max_in_degree, desc->flags))
+        return rgcn_small_fwd(g, desc->d_in, D, X32, W32, W032, desc->norm == RGNN_NORM_IN_DEGREE_PER_REL, relu, static_cast<float*>(out), st);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
     RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
                     desc->d_in, 1, true));

@@ -50,6 +50,15 @@ inline bool sched_fused_softmax(uint32_t flags) {
 }
 inline bool sched_ws_in_lds(int R, int d) { return (size_t)R * d * sizeof(float) <= kWsLdsMax; }
 
+// RGCN forward of a small graph in one launch (rgcn_small.hip), which reads a weight per (relation, destination) run where the
+// general plan reads one per tile of pairs; a workgroup per destination, and a destination's longest run is walked by one half
+// wavefront.  Against the general plan, us: 32 x 32 8.1 / 12.3 at 5.7k runs, 17 / 19 at 24k, 26 / 21 at 45k; 32 x 64 13 / 19 at 12k,
+// 21 / 22 at 24k; 64 x 64 15 / 19 at 6.7k, 22 / 22 at 12k.
+inline bool sched_rgcn_small(int dtype, int d_in, int d, int64_t runs, int64_t nodes, int64_t max_in_degree, uint32_t flags) {
+    return dtype == RGNN_F32 && d_in <= 64 && d <= 64 && runs * (d_in * d + 2048) <= 72000000 && nodes <= 16384 && max_in_degree <= 256 &&
+           !flag_set(flags, RGNN_FLAG_NO_BATCHED_WALKS);
+}
+
 struct ListCounts { int32_t single = 0, short_ = 0; };   // whole segments with 1 / with 2..kShortLen entries
 struct ScheduleIn {
     int layer = 0, dtype = 0, d = 0, heads = 1;

@@ -77,6 +77,9 @@ struct RgatFinish {
 rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const float* ds_dst, const float* wtp,
                             const float* extra, void* dX, hipStream_t st, int in_bf16 = 0, int out_bf16 = 0, int heads = 1,
                             const void* dXp2 = nullptr, const RgatFinish* finish = nullptr);
+// rgcn_small.hip: the whole forward of a small graph in one launch (fp32, widths 32 and 64)
+rgnn_status_t rgcn_small_fwd(const rgnn_graph* g, int K, int D, const float* X, const float* W, const float* W0, int norm, int relu, float* out,
+                             hipStream_t st);
 // hgt.hip: the layer's weights in the caller's storage (fp32 or bf16); rel_type = node type of each relation's sources
 struct HgtWeights { const void* Wk; const void* Wv; const void* Watt; const void* Wmsg; const void* mu; bool bf16; const int32_t* rel_type; int d; int H; };
 //   folded weights of both halves: Wf_att[r] = Wk[rel_type[r]] blockdiag(mu / sqrt(dh) Watt[r]), Wf_msg[r] = Wv[..] blockdiag(Wmsg[r])

@@ -59,6 +59,36 @@ def test_input_width_differs_from_output_width(d_in, d):
     _run(700, 5, src, dst, rel, p, d, "none", "relu", False, tag=f"widths-{d_in}-{d}-relu", d_in=d_in)
 
 
+@pytest.mark.parametrize("norm,act,loop", [("in_degree_per_rel", "none", False), ("none", "relu", True), ("in_degree_per_rel", "none", True)])
+@pytest.mark.parametrize("d_in,d", [(32, 32), (32, 64), (64, 32), (64, 64)])
+def test_small_graph_in_one_launch(d_in, d, norm, act, loop):
+    """Destinations with runs of 1, 8, 9, 31, 32, 33 and 256 edges, with 7, 8, 9, 16 and 17 runs (eight half wavefronts take a
+    destination's runs in turn), and without any."""
+    rng = np.random.default_rng(d_in + 2 * d)
+    runs = [(v, 0, n) for v, n in enumerate((1, 8, 9, 31, 32, 33, 256))]
+    for v, n in enumerate((7, 8, 9, 16, 17), start=20):
+        runs += [(v, r, 1 + r % 3) for r in range(n)]
+    N, R = 60, 20
+    dst = np.concatenate([np.full(n, v) for v, _, n in runs]).astype(np.int32)
+    rel = np.concatenate([np.full(n, r) for _, r, n in runs]).astype(np.int32)
+    src = rng.integers(0, N, len(dst)).astype(np.int32)
+    p = synth.rgcn_params(rng, N, R, d_in, d, self_loop=True)
+    _run(N, R, src, dst, rel, p, d, norm, act, loop, tag=f"one-launch-{d_in}-{d}", d_in=d_in)
+
+
+@pytest.mark.parametrize("N,E,hub", [(16384, 3000, 256), (16385, 3000, 0), (1000, 3000, 257), (1000, 23436, 0), (1000, 23437, 0)])
+def test_either_side_of_the_small_graph_rule(N, E, hub):
+    """The largest graphs of the one-launch forward and the smallest beyond it, by nodes, by in-degree and by runs."""
+    rng = np.random.default_rng(N + E)
+    R = 40
+    pick = rng.permutation((N - 1) * R)[:E]                # a run per edge; node N - 1 is the hub
+    dst, rel = (pick // R).astype(np.int32), (pick % R).astype(np.int32)
+    dst[:hub], rel[:hub] = N - 1, 3
+    src = rng.integers(0, N, E).astype(np.int32)
+    p = synth.rgcn_params(rng, N, R, 32, 32, self_loop=False)
+    _run(N, R, src, dst, rel, p, 32, "in_degree_per_rel", "none", False, tag=f"rule-{N}-{E}-{hub}")
+
+
 def test_hub_and_isolated_nodes():
     rng, src, dst, rel, _ = synth.tiny(50, N=400, R=3, E=3000)
     dst[:1500] = 3          # hub far above the item length, many nodes left without in-edges
