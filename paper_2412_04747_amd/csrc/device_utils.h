@@ -225,6 +225,41 @@ __device__ __forceinline__ float4 positive(float4 v) {
     return make_float4(v.x > 0.f ? v.x : 0.f, v.y > 0.f ? v.y : 0.f, v.z > 0.f ? v.z : 0.f, v.w > 0.f ? v.w : 0.f);
 }
 
+// wv[r][k] = sum_n W[r][k][n] * w[r][n]      (linear operator reordering, Ch.3: x (W w) instead of (x W) w)
+// for one vector per relation or two (w2 / wv2 optional) in the same pass over W.  Eight lanes per weight row,
+// 16-byte loads; nd is a multiple of 32.  H > 1: wv[r][h][k], the same sum over head h's columns alone (one vector; the H vectors
+// of a relation are adjacent, so the walks that need all of them touch one short block).  Block blk of a share of a launch, 256
+// threads.
+__device__ __forceinline__ void fold_weight_block(const FoldArgs& f, int blk) {
+    if (f.H > 1) {
+        const int i = blk * 256 + threadIdx.x;             // (r, h, k)
+        if (i >= f.H * f.R * f.kd) return;
+        const int dh = f.nd / f.H, r = i / (f.H * f.kd), h = i / f.kd % f.H, k = i % f.kd;
+        const float* Wr = f.W + ((size_t)r * f.kd + k) * f.nd + h * dh;
+        const float* wr = f.w + (size_t)r * f.nd + h * dh;
+        float s = 0.f;
+        for (int n = 0; n < dh; ++n) s += Wr[n] * wr[n];
+        f.wv[i] = s;
+        return;
+    }
+    const int i = (blk * 256 + threadIdx.x) >> 3, l = threadIdx.x & 7;  // (r, k)
+    if (i >= f.R * f.kd) return;
+    const int r = i / f.kd, nd = f.nd;
+    const float* Wr = f.W + (size_t)i * nd;
+    float s = 0.f, s2 = 0.f;
+    for (int n = 4 * l; n < nd; n += 32) {
+        const float4 x = *reinterpret_cast<const float4*>(Wr + n);
+        s += dot4(x, *reinterpret_cast<const float4*>(f.w + (size_t)r * nd + n));
+        if (f.w2) s2 += dot4(x, *reinterpret_cast<const float4*>(f.w2 + (size_t)r * nd + n));
+    }
+    s = group_sum<8>(s);
+    s2 = group_sum<8>(s2);
+    if (l == 0) {
+        f.wv[i] = s;
+        if (f.w2) f.wv2[i] = s2;
+    }
+}
+
 inline unsigned blocks_for(size_t n, unsigned per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 #define RGNN_CHECK_LAUNCH() RGNN_HIP(hipGetLastError())

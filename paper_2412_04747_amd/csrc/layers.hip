@@ -636,14 +636,16 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     a.sign_matters = 1;
     a.tiles = pair_chunks(g, D).f32; a.X = Xf; a.gather = g->idx[RGNN_IDX_PAIR_SRC]; a.W = Wf; a.Y = sv.Hs;
     if (!fused) { a.vec = static_cast<const float*>(w_s); a.s_out = w.s_src; }
+    const int H = desc->heads;
+    const FoldArgs fold = fold_args(g->R, K, D, H, Wf, static_cast<const float*>(w_t), w.wtp);      // step 2; in the same launch if there is one
+    const bool with_fold = fused && a.tiles->num_tiles > 0;
+    if (with_fold) a.fold = &fold;
     RGNN_TRY(typed_linear_fwd(K, D, a, st));
     // 2. destination half, once per (dst, rel) run, reordered: s_dst[q] = X[dst] . (W[r] w_t[r])  (per head: the head's columns)
-    const int H = desc->heads;
+    if (!with_fold) RGNN_TRY(fold_weight(fold, st));
     if (H > 1) {
-        RGNN_TRY(fold_weight(fold_args(g->R, K, D, H, Wf, static_cast<const float*>(w_t), w.wtp), st));
         RGNN_TRY(run_logit_heads(g, K, H, Xf, w.wtp, sv.s_dst, st));
     } else {
-        RGNN_TRY(fold_weight(fold_args(g->R, K, D, 1, Wf, static_cast<const float*>(w_t), w.wtp), st));
         RGNN_TRY(run_logit(g, K, Xf, w.wtp, sv.s_dst, st));
     }
     if (!fused) {

@@ -146,6 +146,9 @@ rgnn_status_t allow_dynamic_lds(const void* kernel, size_t bytes);
 // Device address of the library's static scratch buffer on the current device (layers.hip); resolved once per device.
 rgnn_status_t static_scratch(void** p);
 
+// weight folds (fold_weight_block in device_utils.h), as a launch or `blocks` workgroups of another one
+struct FoldArgs { const float* W; const float* w; const float* w2; int R, kd, nd, H; float* wv; float* wv2; int blocks; };
+
 // ---- kernel launchers (typed_linear.hip) --------------------------------
 struct TypedLinearArgs {
     const TileList* tiles;
@@ -161,6 +164,7 @@ struct TypedLinearArgs {
     const char* label;       // name in the timing report (nullptr: default)
     int y_stride = 1;        // rows of Y are y_stride * d_out floats apart (1 or 2)
     int relu = 0;            // with accumulate: Y = max(Y + result, 0)
+    const FoldArgs* fold = nullptr;   // folds weights in the same launch (gathered rows, no scatter, accumulate or vec)
     int sign_matters = 0;    // 1: a backward takes a branch on the sign of what becomes of Y (leaky ReLU; ReLU, also the caller's own)
 };
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st);

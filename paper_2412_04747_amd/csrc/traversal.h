@@ -15,7 +15,6 @@ struct ScheduleFlagsScope {
 
 // wv[r] = W[r] w[r]; optionally a second vector per relation in the same pass (wv2[r] = W[r] w2[r]).  H > 1: wv[r][h], over the
 // columns of head h
-struct FoldArgs { const float* W; const float* w; const float* w2; int R, kd, nd, H; float* wv; float* wv2; int blocks; };
 FoldArgs fold_args(int R, int kd, int nd, int H, const float* W, const float* w, float* wv, const float* w2 = nullptr, float* wv2 = nullptr);
 rgnn_status_t fold_weight(const FoldArgs& f, hipStream_t st);
 rgnn_status_t run_logit(const rgnn_graph* g, int D, const float* X, const float* wtp, float* s_dst, hipStream_t st);

@@ -265,7 +265,12 @@ template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
 __global__ __launch_bounds__((64 * FwdShape<KD, ND, VEC, ACCUM>::NW))
 void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                   const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
-                                  float* __restrict__ s_out, int s_heads, int relu) {
+                                  float* __restrict__ s_out, int s_heads, int relu, FoldArgs fold) {
+    // RGAT: the folded vectors that the kernel after this one reads (a launch of their own cost 5 us behind this one)
+    if (GATHER && !SCATTER && !ACCUM && !VEC && (int)blockIdx.x >= (int)gridDim.x - fold.blocks) {
+        if (threadIdx.x < 256) fold_weight_block(fold, blockIdx.x - (gridDim.x - fold.blocks));
+        return;
+    }
     fwd_wave<KD, ND, GATHER, SCATTER, ACCUM, VEC>(t, blockIdx.x, X, gather, W, Y, vec, s_out, s_heads, relu);
 }
 
@@ -674,8 +679,9 @@ static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st) {
     auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
-    hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(64 * S::NW), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
-                       a.vec, a.s_out, a.s_heads, a.relu);
+    const FoldArgs fold = a.fold ? *a.fold : FoldArgs{};
+    hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks + fold.blocks), dim3(64 * S::NW), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
+                       a.vec, a.s_out, a.s_heads, a.relu, fold);
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -686,6 +692,7 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
     const bool g = a.gather != nullptr, sc = g && a.scatter_out, ac = a.accumulate != 0, v = a.vec != nullptr;
     if (v && (a.s_heads < 1 || (a.s_heads & (a.s_heads - 1)) || a.s_heads > ND / 4))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: %d heads for the row-vector products at width %d", a.s_heads, ND);
+    if (a.fold && (!g || sc || ac || v || a.fold->nd % 32)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: folds go with plain products of gathered rows");
     if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
     if (a.y_stride != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built in the launches of several products only");
     if (g && !sc && !ac && v) return launch_fwd_wave<KD, ND, true, false, false, true>(a, st);
@@ -699,6 +706,7 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
 }
 
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st) {
+    if (a.fold && d_in == 128 && !a.sign_matters) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: folds are not built into the split product");
     if (a.tiles->num_tiles == 0) return RGNN_OK;
     if (d_in == 64 && d_out == 64) return launch_fwd<64, 64>(a, st);
     if (d_in == 32 && d_out == 32) return launch_fwd<32, 32>(a, st);
