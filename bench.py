@@ -135,6 +135,7 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
         "typed_linear_fwd": ("mfma", pair_fwd[1] + (P * 4 * H if layer == "rgat" and not fused else 0), pair_fwd[2]),
         # RGCN: the selector and the scale with the row selector, nothing without
         "typed_linear_bwd": (mm, pair_bwd[1] + ((P * (4 + 8 * H) if sel else P * 4 if H == 1 else 0) if layer == "rgat" else P * 8 if sched.get("row_select") else 0), pair_bwd[2]),
+        "typed_linear_loop_bwd": ("mfma", pair_bwd[1] + (P * 8 if sched.get("row_select") else 0) + N * 3 * r32 + w2, pair_bwd[2] + 4.0 * N * d * d),
         "self_loop_fwd": ("mfma", N * 3 * r32 + w2, 2.0 * N * d * d),         # X row + out row read and written
         "self_loop_bwd": (mm, N * 3 * r32 + w2, 4.0 * N * d * d),
         # fused RGAT walk: row + in_pair + in_rel + in_run per edge, s_dst per run and head, out row + item + (m, s) per head per node

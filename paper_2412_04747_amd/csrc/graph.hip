@@ -88,9 +88,10 @@ struct Uploader {
     }
 };
 
-// Chunks for one of two lists of P rows that share `cus` compute units with a list of N rows.
-static int pair_share(int64_t P, int64_t N, int cus) {
-    return (int)std::min<int64_t>(std::max<int64_t>((P * cus + (2 * P + N) / 2) / std::max<int64_t>(2 * P + N, 1), 1), std::max((cus - 1) / 2, 1));
+// Chunks for each of `lists` lists of P rows that share `cus` compute units with a list of N rows.
+static int pair_share(int64_t P, int64_t N, int cus, int lists) {
+    const int64_t rows = std::max<int64_t>(lists * P + N, 1);
+    return (int)std::min<int64_t>(std::max<int64_t>((P * cus + rows / 2) / rows, 1), std::max((cus - 1) / lists, 1));
 }
 
 // Tile lists over one segmentation: the tiles are planned and uploaded once, every list gets its own chunks.
@@ -159,12 +160,12 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     RGNN_HIP(hipGetDevice(&dev));
     RGNN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     g->num_cus = cus = std::max(cus, 1);
-    const int hgt_pairs = pair_share(g->P, g->N, cus);
-    build_tiles(U, pair_ptr, kTileRows, {{&g->pair_tiles_hgt, hgt_pairs}, {&g->pair_tiles, kMaxChunks}, {&g->pair_tiles_wide, kWideChunksPerCU * cus},
+    const int hgt_pairs = pair_share(g->P, g->N, cus, 2), loop_pairs = pair_share(g->P, g->N, cus, 1);
+    build_tiles(U, pair_ptr, kTileRows, {{&g->pair_tiles_hgt, hgt_pairs}, {&g->pair_tiles_loop, loop_pairs}, {&g->pair_tiles, kMaxChunks}, {&g->pair_tiles_wide, kWideChunksPerCU * cus},
                                          {&g->pair_tiles_cu2, 2 * cus}, {&g->pair_tiles_cu1, cus}});
     build_tiles(U, ntype_ptr, kTileRows, {{&g->node_tiles_hgt, std::max(cus - 2 * hgt_pairs, 1)}, {&g->node_tiles, kMaxChunks}, {&g->node_tiles_wide, kWideChunksPerCU * cus},
                                           {&g->node_tiles_cu2, 2 * cus}, {&g->node_tiles_cu1, cus}});
-    build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles, kMaxChunks}, {&g->all_tiles_cu1, cus}});
+    build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles, kMaxChunks}, {&g->all_tiles_cu1, cus}, {&g->all_tiles_loop, std::max(cus - loop_pairs, 1)}});
     build_items(U, g->dst_items, in_ptr, item_cut(g->E));
     build_items(U, g->pair_items, out_ptr, item_cut(g->E));
     build_items(U, g->relrun_items, relrun_ptr, item_cut(g->E));

@@ -226,6 +226,11 @@ size_t carve_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->partial = c.take<float>((size_t)g->dst_items.num_partials * d->d_out);
     return c.off;
 }
+// RGCN with a self-loop, fp32 up to width 64: its backward runs with the pairs', where the pairs' chunks are one per compute unit
+// (see Chunkings; with many short relations they stay apart).
+inline bool rgcn_loop_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
+    return d->d_in <= 64 && d->d_out <= 64 && pair_chunks(g, d->d_out).f32_bwd == &g->pair_tiles_cu1;
+}
 size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgcnBwdWs* w) {
     Carver c(base);
     const bool h = rows_bf16(d), relu = d->activation == RGNN_ACT_RELU;
@@ -234,8 +239,11 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->G = c.rows((size_t)g->P * d->d_out, h);
     w->dXp = c.rows((size_t)g->P * d->d_in, h);
     w->dX0 = c.take<float>((size_t)g->N * d->d_in);
-    w->tl_part = c.take<float>(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out));
-    w->loop_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_cu1));
+    const bool with_loop = rgcn_loop_bwd(g, d);
+    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out),
+                                        with_loop ? typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles_loop) : 0));
+    w->loop_part = c.take<float>(std::max(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_cu1),
+                                          with_loop ? typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_loop) : 0));
     w->partial = c.take<float>((size_t)g->pair_items.num_partials * d->d_out);
     const bool acc = grads_accumulate(d);
     w->acc_dW = acc ? c.take<float>((size_t)g->R * d->d_in * d->d_out) : nullptr;
@@ -536,14 +544,21 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
                         w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", 1, h, h));
     // 2. per pair dXp = dHs W^T; dW[r] = sum X^T dHs (its shares are added with those of the self-loop)
     ShareSums sums;
-    RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
-                    w.dXp, h, static_cast<float*>(dW), w.tl_part, "typed_linear_bwd", st, false, ysel, y_alt, yscale, K, 1, &sums));
     // 3. self-loop: dX0 = dPre W0^T, dW0 = X^T dPre
-    if (W0) {
-        TypedLinearBwdArgs s{};
-        s.tiles = &g->all_tiles_cu1; s.X = X32; s.W = W032; s.dY = dPre32;
-        s.dXrow = w.dX0; s.dW = static_cast<float*>(dW0); s.part = w.loop_part; s.label = "self_loop_bwd"; s.sums = &sums;
-        RGNN_TRY(typed_linear_bwd(K, D, s, st));
+    TypedLinearBwdArgs s{};
+    s.tiles = &g->all_tiles_cu1; s.X = X32; s.W = W032; s.dY = dPre32;
+    s.dXrow = w.dX0; s.dW = static_cast<float*>(dW0); s.part = w.loop_part; s.label = "self_loop_bwd"; s.sums = &sums;
+    if (W0 && rgcn_loop_bwd(g, desc)) {
+        TypedLinearBwdArgs b{};
+        b.tiles = &g->pair_tiles_loop; b.X = X32; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = W32; b.dY = static_cast<const float*>(w.G);
+        b.dXrow = static_cast<float*>(w.dXp); b.dW = static_cast<float*>(dW); b.part = w.tl_part; b.sums = &sums;
+        b.ysel = ysel; b.dY_alt = static_cast<const float*>(y_alt); b.yscale = yscale;
+        s.tiles = &g->all_tiles_loop;
+        RGNN_TRY(typed_linear_bwd_loop(K, D, b, s, st));
+    } else {
+        RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
+                        w.dXp, h, static_cast<float*>(dW), w.tl_part, "typed_linear_bwd", st, false, ysel, y_alt, yscale, K, 1, &sums));
+        if (W0) RGNN_TRY(typed_linear_bwd(K, D, s, st));
     }
     RGNN_TRY(sums.launch(st));
     // 4. dX[u] = sum over u's pairs of dXp (+ dX0[u]) (+ what dX holds, when gradients accumulate)

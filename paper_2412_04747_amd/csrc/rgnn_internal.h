@@ -119,6 +119,8 @@ struct rgnn_graph {
     rgnn::TileList all_tiles_cu1;
     rgnn::TileList pair_tiles_hgt;         // the shares of two lists of the pairs and one of the nodes in one chunk per compute unit
     rgnn::TileList node_tiles_hgt;         // for all three together
+    rgnn::TileList pair_tiles_loop;        // likewise one list of the pairs and one of all nodes (RGCN with a self-loop)
+    rgnn::TileList all_tiles_loop;
     rgnn::ItemList dst_items;              // CSR edges by destination
     rgnn::ItemList pair_items;             // transposed edges by pair
     rgnn::ItemList pair_items_multi;       // the same, pairs with two or more edges only
@@ -269,6 +271,8 @@ rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part,
 
 size_t typed_linear_bwd_scratch_floats(int d_in, int d_out, const TileList& t, int vectors = 1);   // vectors: of a slot's vector part
 rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a, hipStream_t st);
+// RGCN, widths 32 and 64: the pairs' backward and the self-loop's (ungathered rows) in one launch, both with sums
+rgnn_status_t typed_linear_bwd_loop(int d_in, int d_out, const TypedLinearBwdArgs& pair, const TypedLinearBwdArgs& loop, hipStream_t st);
 // up to three products of gathered rows in one launch, widths 32 and 64: rows scattered back the same way, or two widths apart
 rgnn_status_t typed_linear_fwd_jobs(int d, const TypedLinearArgs* a, int n, const char* label, hipStream_t st);
 rgnn_status_t typed_linear_bwd_jobs(int d, const TypedLinearBwdArgs* a, int n, const char* label, hipStream_t st);   // with sums

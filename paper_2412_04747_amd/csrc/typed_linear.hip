@@ -311,7 +311,7 @@ __global__ __launch_bounds__((64 * FwdShape<D, D, false, false>::NW)) void typed
 // the run.  Per unit a wavefront forms dXrow = dY W^T (+ rowscale (x) xvec) and adds its
 // rows' contribution, summed over the unit first, to the full KD x ND weight gradient (KB*NB blocks, kept in
 // registers for the whole run) and to Avec.  At the end of a run the eight wavefronts' partial weight
-// gradients are summed in wavefront order through LDS and written to the chunk's slot.
+// gradients are summed through LDS and written to the chunk's slot.
 //
 // SEL (row selector): row i of dY is either dY[ysel[i]] or, when the top bit of ysel[i] is set, row
 // ysel[i] & 0x7FFFFFFF of a second tensor times a per-row scale; rowscale[i] and that scale come as one
@@ -607,7 +607,7 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
             wave_lds_fence();
         }
         // flush: every wavefront parks its partial weight gradient in its own LDS region, then
-        // all threads add the eight copies in wavefront order.
+        // all threads add the eight copies, by halves.
         __syncthreads();
         {
             float* mine = smem + KD * WS + wave * WREG;      // holds a slot's floats (checked on the host)
@@ -634,10 +634,14 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
         {
             float* ps = part + (size_t)slot * SLOT;
             for (int i = tid; i < SLOT; i += 64 * NW) {
-                float sum = 0.f;
+                float c[NW];
 #pragma unroll
-                for (int w2 = 0; w2 < NW; ++w2) sum += smem[KD * WS + w2 * WREG + i];
-                ps[i] = sum;
+                for (int w2 = 0; w2 < NW; ++w2) c[w2] = smem[KD * WS + w2 * WREG + i];
+#pragma unroll
+                for (int o = 1; o < NW; o <<= 1)
+#pragma unroll
+                    for (int w2 = 0; w2 < NW; w2 += 2 * o) c[w2] += c[w2 + o];
+                ps[i] = c[0];
             }
         }
         ta = tb;
@@ -665,6 +669,17 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_jobs_kernel(BwdJobs jobs
     const RowSelect none{};
     if (j.pairs) bwd_wave<D, D, true, false, false, false, false, 0, 2>(j.t, chunk, j.X, j.gather, j.W, j.dY, j.dX, nullptr, nullptr, j.part, none);
     else bwd_wave<D, D, true, true, true, false>(j.t, chunk, j.X, j.gather, j.W, j.dY, j.dX, nullptr, nullptr, j.part, none);
+}
+
+// RGCN: the pairs' product (with the row selector or without) and the self-loop's, the first `chunks` workgroups and the others; chunks
+// as above (833k pairs and 120k nodes, 32 -> 64 columns: 100 and 23 us, together 110).
+template <int KD, int ND, bool SEL>
+__global__ __launch_bounds__(512) void typed_linear_bwd_loop_kernel(BwdJob pair, RowSelect ys, BwdJob loop) {
+    const RowSelect none{};
+    if ((int)blockIdx.x < pair.chunks)
+        bwd_wave<KD, ND, true, false, false, false, SEL>(pair.t, blockIdx.x, pair.X, pair.gather, pair.W, pair.dY, pair.dX, nullptr, nullptr, pair.part, ys);
+    else
+        bwd_wave<KD, ND, false, false, false, false>(loop.t, blockIdx.x - pair.chunks, loop.X, nullptr, loop.W, loop.dY, loop.dX, nullptr, nullptr, loop.part, none);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -784,6 +799,31 @@ rgnn_status_t typed_linear_bwd(int d_in, int d_out, const TypedLinearBwdArgs& a,
     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: d_in = %d, d_out = %d not supported (need 32 / 64 / 128, different widths only among 32 and 64)", d_in, d_out);
 }
 
+template <int KD, int ND>
+static rgnn_status_t launch_bwd_loop(const TypedLinearBwdArgs& p, const TypedLinearBwdArgs& l, hipStream_t st) {
+    constexpr size_t lds = sizeof(float) * (KD * (ND + 1) + 8 * (32 * (KD + 4) + 32 * ((ND > KD ? ND : KD) + 4) + 32));
+    const BwdJob pair{tile_args(*p.tiles), p.tiles->num_chunks, 1, p.X, p.gather, p.W, p.dY, p.dXrow, p.part};
+    const BwdJob loop{tile_args(*l.tiles), l.tiles->num_chunks, 0, l.X, nullptr, l.W, l.dY, l.dXrow, l.part};
+    const RowSelect ys{p.ysel, p.dY_alt, nullptr, p.yscale, nullptr, nullptr};
+    auto kern = p.ysel ? typed_linear_bwd_loop_kernel<KD, ND, true> : typed_linear_bwd_loop_kernel<KD, ND, false>;
+    RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
+    KernelTimer kt(st, "typed_linear_loop_bwd");
+    hipLaunchKernelGGL(kern, dim3(pair.chunks + loop.chunks), dim3(512), lds, st, pair, ys, loop);
+    RGNN_HIP(hipGetLastError());
+    return RGNN_OK;
+}
+rgnn_status_t typed_linear_bwd_loop(int d_in, int d_out, const TypedLinearBwdArgs& p, const TypedLinearBwdArgs& l, hipStream_t st) {
+    const bool plain = !p.rowscale && !l.rowscale && !p.hcoef && !p.ds_yscale && p.gather && !l.gather && !p.dy_gathered && !p.scatter_dx && !l.ysel &&
+                       p.dy_stride == 1 && l.dy_stride == 1 && p.sums && l.sums && (!p.ysel || p.dY_alt);
+    if (!plain) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward with self-loop: plain products with their sums only");
+    for (const TypedLinearBwdArgs* a : {&p, &l}) RGNN_TRY(typed_linear_slot_reduce(*a->tiles, a->part, d_in * d_out, d_in, a->dW, nullptr, st, a->sums));
+    if (p.tiles->num_tiles + l.tiles->num_tiles == 0) return RGNN_OK;
+    if (d_in == 64 && d_out == 64) return launch_bwd_loop<64, 64>(p, l, st);
+    if (d_in == 32 && d_out == 32) return launch_bwd_loop<32, 32>(p, l, st);
+    if (d_in == 32 && d_out == 64) return launch_bwd_loop<32, 64>(p, l, st);
+    if (d_in == 64 && d_out == 32) return launch_bwd_loop<64, 32>(p, l, st);
+    RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward with self-loop: widths %d -> %d not built", d_in, d_out);
+}
 // The products of several argument sets in one launch: gathered rows, either scattered back (y_stride 1) or two widths apart.
 static rgnn_status_t jobs_check(bool ok, int n) {
     if (!ok || n < 1 || n > kMaxJobs) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear jobs: one to %d plain products of gathered rows, width 32 or 64", kMaxJobs);

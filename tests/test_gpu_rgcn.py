@@ -89,6 +89,17 @@ def test_either_side_of_the_small_graph_rule(N, E, hub):
     _run(N, R, src, dst, rel, p, 32, "in_degree_per_rel", "none", False, tag=f"rule-{N}-{E}-{hub}")
 
 
+@pytest.mark.parametrize("d_in,d", [(32, 32), (32, 64), (64, 32), (64, 64)])
+@pytest.mark.parametrize("N,R,E", [(1, 1, 0), (40000, 3, 70), (300, 40, 30000), (3000, 2, 40000)])
+def test_self_loop_and_pairs_share_the_compute_units(N, R, E, d_in, d):
+    """The self-loop's and the pairs' backward split the compute units by their rows: none, few and nearly all of them pairs."""
+    rng = np.random.default_rng(N + E + d)
+    src, dst = rng.integers(0, N, E).astype(np.int32), rng.integers(0, N, E).astype(np.int32)
+    rel = rng.integers(0, R, E).astype(np.int32)
+    p = synth.rgcn_params(rng, N, R, d_in, d, self_loop=True)
+    _run(N, R, src, dst, rel, p, d, "in_degree_per_rel", "none", True, tag="shared-units", d_in=d_in)
+
+
 def test_hub_and_isolated_nodes():
     rng, src, dst, rel, _ = synth.tiny(50, N=400, R=3, E=3000)
     dst[:1500] = 3          # hub far above the item length, many nodes left without in-edges
