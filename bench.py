@@ -106,6 +106,8 @@ def algorithmic_work(name, E, N, P, Q, R, T, d, H, P1=0, bf16=False, layer="rgat
             # one row in, one row out, + the gather index; backward: two rows in (both products in one kernel)
             segs = T if key.startswith("node_linear") else R
             w2 = d * d * (4 if key.startswith("pair_linear") else wb)       # block-diagonal weights are fp32
+            if name == "pair_linear":          # key and message halves together: X row in, two rows out
+                return (bound, n * (3 * row + 4) + 2 * segs * d * d * wb, 4.0 * n * d * d)
             if name == "pair_linear_bwd":      # key and message halves together: X row, two gradient rows in, one row out
                 return (bound, n * (4 * row + 4) + 2 * segs * d * d * (wb + 4), 8.0 * n * d * d)
             out_row = r32 if key in ("node_linear_out", "node_linear_k_bwd", "node_linear_q_bwd", "node_linear_v_bwd") else row

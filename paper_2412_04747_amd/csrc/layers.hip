@@ -863,7 +863,10 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
         //    128, its fp32 copy otherwise.
         RGNN_TRY(hgt_fold(g->R, hw, sv.Wf_att, sv.Wf_msg, h, st));
         const void* in = h ? X : static_cast<const void*>(X32);
-        RGNN_TRY(products({q, {true, in, R32(sv.Wf_att), R16(sv.Wf_att), sv.KM, "pair_linear_att"},
+        if (h) {
+            RGNN_TRY(products({q}, ""));
+            RGNN_TRY(typed_linear_pair_bf16(g->pair_tiles_cu1, X, psrc, sv.Wf_att, sv.Wf_msg, sv.KM, st));
+        } else RGNN_TRY(products({q, {true, in, R32(sv.Wf_att), R16(sv.Wf_att), sv.KM, "pair_linear_att"},
                            {true, in, R32(sv.Wf_msg), R16(sv.Wf_msg), Mrow, "pair_linear_msg"}}, "node_pair_linears"));
     } else {
         //    with the per-(relation, head) matrices as block-diagonal d x d weights

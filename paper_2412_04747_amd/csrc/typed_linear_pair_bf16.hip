@@ -1,0 +1,145 @@
+// The two per-pair products of HGT with folded weights in bf16, width 128, in one pass over the rows:
+//   Y[i] = (X[g(i)] W0[seg(i)], X[g(i)] W1[seg(i)])    side by side, 512 bytes per row, v_mfma_f32_32x32x16_bf16, fp32 accumulation.
+//
+// Bound by HBM: a row is gathered once and its two results leave as one row.  As two products the input rows were gathered twice and
+// the result rows written in halves.
+//
+// A workgroup of eight wavefronts takes a chunk of 64-row tiles.  A tile's rows are brought to registers one tile ahead and written to
+// LDS row-major, swizzled as in the backward (typed_linear_bwd_bf16.hip); the weights lie there as they are in memory, and their
+// operand (eight consecutive input features of an output feature) comes through the transposing LDS read.  Each wavefront forms 32 rows
+// x 32 output features of both products; the results are packed to bf16 into a tile in LDS, whose rows leave in 16-byte pieces.
+#include "rgnn_internal.h"
+#include "device_utils.h"
+
+namespace rgnn {
+
+namespace {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) v4s* lds_v4s;
+
+struct PairArgs {
+    const int32_t* tile_seg;
+    const int32_t* tile_row0;
+    const int32_t* tile_row1;
+    const int32_t* chunk_tile;
+    const bf16_t* X;
+    const int32_t* gather;
+    const bf16_t* W[2];
+    bf16_t* Y;
+};
+
+__device__ __forceinline__ int swz(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
+__device__ __forceinline__ bf16x8 tr8(const unsigned char* p, const unsigned char* q) {
+    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)p), b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)q);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+constexpr int D = 128, TILE = 64 * 2 * D, WT = D * 2 * D;      // bytes of 64 rows and of a weight
+constexpr size_t kPairLds = 2 * WT + 3 * TILE;
+
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_pair_bf16_kernel(PairArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    unsigned char* const Wl = lds;                        // [2][128][256]
+    unsigned char* const Xt = lds + 2 * WT;               // [64][256]
+    unsigned char* const St = Xt + TILE;                  // [2][64][256]  both halves of the result rows
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m = lane & 31, kh = lane >> 5;
+    // rows in and out: 16 lanes per 256 bytes, two rows per thread (in), four pieces (out)
+    const int lc = tid & 15, lr = tid >> 4;
+    const int io = lr * 256 + ((lc ^ swz(lr)) << 4);
+    // this wavefront's block: 32 rows x output features 16 fb + (0..15) and 64 further, of both weights
+    const int fb = wave & 3, rb = wave >> 2;
+    const int ti16 = lane & 15, tg = (lane >> 4) & 1;
+    int woff[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int r = 8 * kh + 4 * t + (ti16 >> 2), piece = (ti16 & 3) >> 1, half = (ti16 & 1) * 8;
+        woff[t] = r * 256 + (((2 * (fb + 4 * tg) + piece) ^ swz(r)) << 4) + half;
+    }
+    const int xrow = (rb * 32 + m) * 256, xsw = (kh ^ swz(m)) << 4;
+    const int t0 = a.chunk_tile[blockIdx.x], t1 = a.chunk_tile[blockIdx.x + 1];
+    if (t0 >= t1) return;
+    rgnn_v4u xr[2];
+    int gi[2];
+    TileTable tt(a.tile_seg, a.tile_row0, a.tile_row1, t0, t1);
+    auto fetch_idx = [&](int ti) {
+        const int l = tt.lane_of(ti), row0 = tt.row0_at(l), row1 = tt.row1_at(l);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) gi[k] = a.gather[min(row0 + lr + 32 * k, row1 - 1)];
+    };
+    auto fetch = [&]() {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) xr[k] = *reinterpret_cast<const rgnn_v4u*>(a.X + (size_t)gi[k] * D + lc * 8);
+    };
+    fetch_idx(t0);
+    fetch();
+    fetch_idx(min(t0 + 1, t1 - 1));
+    int cur_seg = -1;
+    for (int ti = t0; ti < t1; ++ti) {
+        const int tl = tt.lane_of(ti), seg = tt.seg_at(tl);
+        if (seg != cur_seg) {              // (all operand reads of the previous tile lie before its second barrier)
+            cur_seg = seg;
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    *reinterpret_cast<rgnn_v4u*>(Wl + nb * WT + io + k * 32 * 256) =
+                        *reinterpret_cast<const rgnn_v4u*>(a.W[nb] + (size_t)seg * D * D + (size_t)(lr + 32 * k) * D + lc * 8);
+        }
+        const int row0 = tt.row0_at(tl), rows = tt.row1_at(tl) - row0;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) *reinterpret_cast<rgnn_v4u*>(Xt + io + k * 32 * 256) = xr[k];   // past the end the last row again: not stored
+        __syncthreads();   // the tile is complete, and the previous one's result rows have been read out
+        fetch();           // unconditional, past the end the last tile again: see the backward
+        fetch_idx(min(ti + 2, t1 - 1));
+        v16f d[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) d[0][v] = d[1][v] = 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const bf16x8 bx = *reinterpret_cast<const bf16x8*>(Xt + xrow + (xsw ^ (s << 5)));
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                const unsigned char* w = Wl + nb * WT + s * 4096;
+                d[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr8(w + woff[0], w + woff[1]), bx, d[nb], 0, 0, 0);
+            }
+        }
+        // d[v] = row rb * 32 + m, block row 8 (v / 4) + 4 kh + v % 4: features 16 fb + (0..15), then 64 further
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int piece = 2 * fb + (q & 1) + 8 * (q >> 1);
+                *reinterpret_cast<uint2*>(St + nb * TILE + xrow + ((piece ^ swz(m)) << 4) + 8 * kh) =
+                    make_uint2(bf16_pack2(d[nb][4 * q], d[nb][4 * q + 1]), bf16_pack2(d[nb][4 * q + 2], d[nb][4 * q + 3]));
+            }
+        __syncthreads();   // operand reads are done, the result tile is complete
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                const int r = lr + 32 * k;
+                if (r < rows)
+                    __builtin_nontemporal_store(*reinterpret_cast<const rgnn_v4u*>(St + nb * TILE + io + k * 32 * 256),
+                                                reinterpret_cast<rgnn_v4u*>(a.Y + (size_t)(row0 + r) * 2 * D + nb * D + lc * 8));
+            }
+    }
+}
+
+}  // namespace
+
+rgnn_status_t typed_linear_pair_bf16(const TileList& t, const void* X, const int32_t* gather, const void* W0, const void* W1, void* Y, hipStream_t st) {
+    if (t.num_tiles == 0) return RGNN_OK;
+    RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(typed_linear_pair_bf16_kernel), kPairLds));
+    const PairArgs a{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, static_cast<const bf16_t*>(X), gather,
+                     {static_cast<const bf16_t*>(W0), static_cast<const bf16_t*>(W1)}, static_cast<bf16_t*>(Y)};
+    KernelTimer kt(st, "pair_linear");
+    hipLaunchKernelGGL(typed_linear_pair_bf16_kernel, dim3(t.num_chunks), dim3(512), kPairLds, st, a);
+    RGNN_HIP(hipGetLastError());
+    return RGNN_OK;
+}
+
+}  // namespace rgnn
