@@ -118,10 +118,10 @@ struct GradAcc {
 };
 
 // The chunkings of one list of row tiles that the typed linears pick from:
-//   many, wide  bf16 rows, forward: weight in bf16 / an fp32 weight to be split
+//   many, wide  bf16 inputs, forward with fp32 results or an fp32 operand: weight in bf16 / an fp32 weight to be split
 //   f32         the fp32 forward: one resident round, of three workgroups per compute unit up to width 64, of one at width 128
-//   cu2         bf16 rows, backward with one bf16 weight: two workgroups per compute unit
-//   cu1         the bf16 backward with two weights or a split one, and the fp32 one at width 128: one workgroup per compute unit
+//   cu2         bf16 rows on both sides, forward and backward with one bf16 weight: two workgroups per compute unit
+//   cu1         the bf16 forward and backward with two weights, the backward with a split one, and the fp32 one at width 128: one workgroup per compute unit
 //   f32_bwd     the fp32 backward.  Up to width 64 it fills a compute unit's LDS, and one chunk per compute unit saves the weight
 //               loads, flushes and slots of three rounds of shorter ones (62 us for 48 at 141k pairs and 108 for 82 at 349k, the
 //               same within 1 % at 7.3M).  But where relations are short a chunk is a row of runs (segments), each with a load, one
@@ -346,7 +346,7 @@ void* saved_or_scratch(const rgnn_graph_t* g, int layer, const rgnn_layer_desc_t
 // Forward typed linear  Y[g(i)] / Y[i] = A[g(i)] W[seg].  In bf16 mode it runs on the bf16 matrix
 // cores: an operand whose bf16 form exists (A16 / W16) is used as is, an fp32-only one is split.
 // y16: the output rows are stored as bf16 (width 128 only).
-// Chunking: the bf16 kernel with the weight in bf16 does best on many short chunks; when the weight has to be
+// Chunking: the bf16 kernel with fp32 results and the weight in bf16 does best on many short chunks; when the weight has to be
 // split, and in the fp32 kernels, loading a segment's weight costs more and one resident round of long chunks wins.
 // d_in (fp32 kernels only): width of the input rows when it differs from the output width d.
 // y_stride: the output rows are y_stride * d elements apart.
@@ -356,6 +356,7 @@ rgnn_status_t tl_fwd(bool bf16, const Chunkings& tiles, int d, const float* A32,
     if (d_in == 0) d_in = d;
     if (bf16) {
         if (d_in != d) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear on the bf16 matrix cores: equal widths only");
+        if (A16 && W16 && y16 && gather && y_stride == 1) return typed_linear_fwd_bf16({tiles.cu2, A16, gather, scatter, W16, nullptr, Y, label}, st);
         TypedLinearBf16Args a{};
         a.tiles = W16 ? tiles.many : tiles.wide; a.A = A16 ? A16 : A32; a.a_bf16 = A16 != nullptr; a.gather = gather; a.scatter_out = scatter;
         a.W = W16 ? W16 : W32; a.w_bf16 = W16 != nullptr; a.Y = Y; a.y_bf16 = y16; a.label = label;
@@ -865,7 +866,7 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
         const void* in = h ? X : static_cast<const void*>(X32);
         if (h) {
             RGNN_TRY(products({q}, ""));
-            RGNN_TRY(typed_linear_pair_bf16(g->pair_tiles_cu1, X, psrc, sv.Wf_att, sv.Wf_msg, sv.KM, st));
+            RGNN_TRY(typed_linear_fwd_bf16({&g->pair_tiles_cu1, X, psrc, 0, sv.Wf_att, sv.Wf_msg, sv.KM, "pair_linear"}, st));
         } else RGNN_TRY(products({q, {true, in, R32(sv.Wf_att), R16(sv.Wf_att), sv.KM, "pair_linear_att"},
                            {true, in, R32(sv.Wf_msg), R16(sv.Wf_msg), Mrow, "pair_linear_msg"}}, "node_pair_linears"));
     } else {

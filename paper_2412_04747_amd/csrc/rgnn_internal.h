@@ -238,8 +238,12 @@ struct TypedLinearBf16Args {
     int y_stride = 1;        // rows of Y are that many widths apart
 };
 rgnn_status_t typed_linear_bf16(int d, const TypedLinearBf16Args& a, hipStream_t st);
-// width 128, rows and weights in bf16 (typed_linear_pair_bf16.hip): Y[i] = (X[gather[i]] W0[seg], X[gather[i]] W1[seg]), rows 256 wide
-rgnn_status_t typed_linear_pair_bf16(const TileList& t, const void* X, const int32_t* gather, const void* W0, const void* W1, void* Y, hipStream_t st);
+// width 128, all rows and weights in bf16 (typed_linear_fwd_bf16.hip): Y[i] = X[gather[i]] W[seg], or with a second weight
+// (X[gather[i]] W[seg], X[gather[i]] W2[seg]) in rows 256 wide
+struct TypedLinearFwdBf16Args {
+    const TileList* tiles; const void* X; const int32_t* gather; int scatter_out; const void* W; const void* W2; void* Y; const char* label;
+};
+rgnn_status_t typed_linear_fwd_bf16(const TypedLinearFwdBf16Args& a, hipStream_t st);
 
 // Backward on the bf16 matrix cores (typed_linear_bwd_bf16.hip): X, dY and (unless dx_f32) dXrow rows in bf16.
 struct TypedLinearBwdBf16Args {

@@ -1,5 +1,6 @@
 // Typed linear layer on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation,
-// for the bfloat16-input workloads:   Y[i] = A[g(i)] W[seg(i)]   (the backward is in typed_linear_bwd_bf16.hip).
+// for the bfloat16-input workloads:   Y[i] = A[g(i)] W[seg(i)]   where an operand or the result is fp32 or the width is below 128
+// (all in bf16: typed_linear_fwd_bf16.hip; the backward: typed_linear_bwd_bf16.hip).
 //
 // Operands stored as bf16 (X, the given weights, and at width 128 every intermediate row
 // tensor) go to the MFMA as they are, so their products are exact.  Operands that only exist
@@ -253,7 +254,6 @@ static rgnn_status_t launch_d(const TypedLinearBf16Args& a, hipStream_t st) {
         if (!a.a_bf16 && !a.w_bf16) return launch_gs<D, false, false, false>(a, st);  // K Watt_bd
     } else {
         if (!a.a_bf16) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bf16: width 128 takes bf16 rows");
-        if (a.w_bf16 && a.y_bf16) return launch_gs<D, true, true, true>(a, st);    // X W -> Hs, K, Q, V
         if (a.w_bf16 && !a.y_bf16) return launch_gs<D, true, true, false>(a, st);  // Z Wo -> out
         if (!a.w_bf16 && a.y_bf16) return launch_gs<D, true, false, true>(a, st);  // K Watt_bd -> Ka
     }
