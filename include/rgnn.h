@@ -102,7 +102,8 @@ typedef struct {
  * atomically to global memory) instead of by the destination-segment walk; the order of the additions then varies
  * from run to run.  Implies RGNN_FLAG_SEPARATE_SOFTMAX. */
 #define RGNN_FLAG_EDGE_PARALLEL_AGGREGATION 1u
-/* every segment takes the general walk: no batched kernels for the segments with one or with 2..4 entries */
+/* every segment takes the general walk: no batched kernels for the segments with one or with 2..4 entries, and no RGCN forward
+ * of a small graph in one launch */
 #define RGNN_FLAG_NO_BATCHED_WALKS 2u
 /* RGAT with one head (2 or 4 up to width 64), RGCN: the gradient row of every (source, relation) pair is
  * written per pair, also for the pairs with one edge, instead of being read through the row selector */
