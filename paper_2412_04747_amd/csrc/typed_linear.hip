@@ -62,6 +62,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 // of 149 tiles some 5 us before its first row).
 __device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int ti, int t1, int lane) {
     const int seg = tile_seg[ti];
+    if (tile_seg[t1 - 1] == seg) return t1;              // (tiles lie in segment order) the usual case of a short chunk
     for (int e = ti; e < t1; e += 64) {
         const unsigned long long other = __ballot(tile_seg[min(e + lane, t1 - 1)] != seg);
         if (other) return e + __builtin_ctzll(other);
@@ -261,13 +262,13 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
     }
 }
 
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool FOLD = false>
 __global__ __launch_bounds__((64 * FwdShape<KD, ND, VEC, ACCUM>::NW))
 void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                   const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
                                   float* __restrict__ s_out, int s_heads, int relu, FoldArgs fold) {
     // RGAT: the folded vectors that the kernel after this one reads (a launch of their own cost 5 us behind this one)
-    if (GATHER && !SCATTER && !ACCUM && !VEC && (int)blockIdx.x >= (int)gridDim.x - fold.blocks) {
+    if (FOLD && (int)blockIdx.x >= (int)gridDim.x - fold.blocks) {
         if (threadIdx.x < 256) fold_weight_block(fold, blockIdx.x - (gridDim.x - fold.blocks));
         return;
     }
@@ -687,11 +688,11 @@ static TileArgs tile_args(const TileList& t) {
     return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot};
 }
 
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC>
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool FOLD = false>
 static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st) {
     using S = FwdShape<KD, ND, VEC, ACCUM>;
     constexpr size_t lds = S::LDS;
-    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC>;
+    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, FOLD>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     const FoldArgs fold = a.fold ? *a.fold : FoldArgs{};
@@ -711,6 +712,7 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
     if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
     if (a.y_stride != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built in the launches of several products only");
     if (g && !sc && !ac && v) return launch_fwd_wave<KD, ND, true, false, false, true>(a, st);
+    if (g && !sc && !ac && !v && a.fold) return launch_fwd_wave<KD, ND, true, false, false, false, true>(a, st);
     if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false>(a, st);
     if constexpr (KD == ND && KD < 128) {
         if (g && sc && !ac && !v) return launch_fwd_wave<KD, ND, true, true, false, false>(a, st);
