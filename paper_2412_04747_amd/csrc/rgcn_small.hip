@@ -10,6 +10,8 @@
 #include "traversal.h"
 #include "device_utils.h"
 
+#include <float.h>
+
 namespace rgnn {
 
 namespace {
@@ -26,8 +28,10 @@ struct SmallArgs {
     int norm, relu;
 };
 
+// (64 x 64 is given the registers of four wavefronts per SIMD: with fewer its rows of weights are not asked for together, 45 us
+// instead of 41 with 128 runs per destination, 133 instead of 89 with 256)
 template <int K, int D>
-__global__ __launch_bounds__(256) void rgcn_small_fwd_kernel(SmallArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K * D == 4096 ? 4 : 1, K * D == 4096 ? 4 : 8))) void rgcn_small_fwd_kernel(SmallArgs a) {
     constexpr int KR = K / 32, DR = D / 32;      // columns of a row per lane: lane + 32 * i
     __shared__ float red[8][D];
     const int v = blockIdx.x, lane = threadIdx.x & 31, half = threadIdx.x >> 5;
@@ -45,7 +49,6 @@ __global__ __launch_bounds__(256) void rgcn_small_fwd_kernel(SmallArgs a) {
             for (int k = 0; k < KR; ++k) x[k] = a.X[(size_t)v * K + lane + 32 * k];
         } else {
             const int b = a.run_ptr[qq], e = a.run_ptr[qq + 1];
-            const float share = pow2_share(e - b);           // exact, and the sum of the rows stays in range
             w = a.W + (size_t)a.run_rel[qq] * K * D;
 #pragma unroll
             for (int k = 0; k < KR; ++k) x[k] = 0.f;
@@ -62,10 +65,10 @@ __global__ __launch_bounds__(256) void rgcn_small_fwd_kernel(SmallArgs a) {
 #pragma unroll
                     for (int u = 0; u < 8; ++u)
 #pragma unroll
-                        for (int k = 0; k < KR; ++k) x[k] += j + u < n ? share * r[u][k] : 0.f;
+                        for (int k = 0; k < KR; ++k) x[k] += j + u < n ? r[u][k] : 0.f;
                 }
             }
-            f = (a.norm ? 1.f / (float)(e - b) : 1.f) / share;
+            f = a.norm ? 1.f / (float)(e - b) : 1.f;
         }
         // a run's product is summed in four chains before it joins the sum over the runs (in one chain for all of them the error
         // of out at 64 x 64 and 100 relations was 2.0e-7 against 64 bits, the general plan's 1.5e-7; so: 1.0e-7)
@@ -84,6 +87,45 @@ __global__ __launch_bounds__(256) void rgcn_small_fwd_kernel(SmallArgs a) {
             }
 #pragma unroll
         for (int n = 0; n < DR; ++n) acc[n] += f * ((t[0][n] + t[1][n]) + (t[2][n] + t[3][n]));
+    }
+    // The sum of a run's rows, or its product, may leave the range of fp32 where their mean does not: the columns that came out
+    // infinite or NaN once more, from rows times a power of two that keeps the sum inside.  (Rows scaled from the start would
+    // lose their last bits below 2^-118.)
+    bool outside[DR], any = false;
+#pragma unroll
+    for (int n = 0; n < DR; ++n) any |= outside[n] = !(fabsf(acc[n]) <= FLT_MAX);
+    if ((unsigned)(__ballot(any) >> (threadIdx.x & 32)) != 0) {       // in this half wavefront
+        float again[DR];
+#pragma unroll
+        for (int n = 0; n < DR; ++n) again[n] = 0.f;
+#pragma unroll 1
+        for (int q = q0 + half; q < end; q += 8) {
+            const bool loop = q == q1;
+            const int b = loop ? v : a.run_ptr[q], e = loop ? v + 1 : a.run_ptr[q + 1];
+            const float* const w = loop ? a.W0 : a.W + (size_t)a.run_rel[q] * K * D;
+            const float share = pow2_share(e - b), f = (a.norm && !loop ? 1.f / (float)(e - b) : 1.f) / share;
+            float x[KR], t[DR];
+#pragma unroll
+            for (int k = 0; k < KR; ++k) x[k] = 0.f;
+#pragma unroll 1
+            for (int j = b; j < e; ++j)
+#pragma unroll
+                for (int k = 0; k < KR; ++k) x[k] += share * a.X[(size_t)(loop ? v : a.in_src[j]) * K + lane + 32 * k];
+#pragma unroll
+            for (int n = 0; n < DR; ++n) t[n] = 0.f;
+#pragma unroll
+            for (int kr = 0; kr < KR; ++kr)
+#pragma unroll 1
+                for (int k = 0; k < 32; ++k) {
+                    const float xk = __shfl(x[kr], k, 32);
+#pragma unroll
+                    for (int n = 0; n < DR; ++n) t[n] += xk * w[(kr * 32 + k) * D + n * 32 + lane];
+                }
+#pragma unroll
+            for (int n = 0; n < DR; ++n) again[n] += f * t[n];
+        }
+#pragma unroll
+        for (int n = 0; n < DR; ++n) acc[n] = outside[n] ? again[n] : acc[n];
     }
 #pragma unroll
     for (int n = 0; n < DR; ++n) red[half][n * 32 + lane] = acc[n];

@@ -76,6 +76,46 @@ def test_small_graph_in_one_launch(d_in, d, norm, act, loop):
     _run(N, R, src, dst, rel, p, d, norm, act, loop, tag=f"one-launch-{d_in}-{d}", d_in=d_in)
 
 
+@pytest.mark.parametrize("d_in,d", [(32, 32), (32, 64), (64, 32), (64, 64)])
+def test_small_graph_with_rows_at_the_ends_of_the_range(d_in, d):
+    """The one-launch forward of a small graph: rows of subnormal numbers, whose sums and products are whole multiples of 2^-29 that
+    24 bits hold (256 rows of at most 63 units, 64 products with weights of at most 7), so the result is exact; and rows of 1.5 * 2^127,
+    whose mean fp32 holds where their sum overflows."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    rng = np.random.default_rng(d_in + d)
+    lengths = [1, 2, 7, 8, 9, 31, 32, 33, 64, 255, 256]
+    N, R = 40, 12                                          # nodes 20.. are the sources; destination 0 has all lengths, then one each
+    runs = [(0, r, n) for r, n in enumerate(lengths) if n < 64] + [(1 + r, r, n) for r, n in enumerate(lengths)]
+    dst = np.concatenate([np.full(n, v) for v, _, n in runs]).astype(np.int32)
+    rel = np.concatenate([np.full(n, r) for _, r, n in runs]).astype(np.int32)
+    src = rng.integers(20, 38, len(dst)).astype(np.int32)
+    big = np.array([(15, 11, 38)] * 128, np.int32)         # one destination of 128 rows near the largest number
+    dst, rel, src = np.concatenate([dst, big[:, 0]]), np.concatenate([rel, big[:, 1]]), np.concatenate([src, big[:, 2]])
+    X = rng.integers(-63, 64, (N, d_in)) * 2.0 ** -149
+    W = rng.integers(-7, 8, (R, d_in, d)) * 2.0 ** 120
+    X[38], W[11] = 0, 0
+    X[38, 5], W[11, 5, 3] = 1.5 * 2.0 ** 127, 1
+    g = Graph(N, R, src, dst, rel)
+    for norm in ("none", "in_degree_per_rel"):
+        L = RgcnLayer(g, d, norm, d_in=d_in)
+        L.load(X.astype(np.float32), W.astype(np.float32))
+        L.fwd()
+        torch.cuda.synchronize()
+        got = L.out.cpu().numpy().astype(np.float64)
+        if norm == "none":
+            want = np.zeros((N, d))
+            np.add.at(want, dst[:-128], np.einsum("ek,ekd->ed", X[src[:-128]], W[rel[:-128]]))
+            assert np.array_equal(np.delete(got, 15, 0), np.delete(want, 15, 0))
+            assert np.isinf(got[15, 3])
+        else:
+            assert got[15, 3] == 1.5 * 2.0 ** 127 and (np.delete(got[15], 3) == 0).all()
+            cnt = 2.0 ** 5                                  # a run of 32 rows: an exact mean
+            e = (dst == 1 + lengths.index(32)) & (rel == lengths.index(32))
+            assert np.array_equal(got[1 + lengths.index(32)], np.einsum("ek,kd->d", X[src[e]], W[lengths.index(32)]) / cnt)
+    g.close()
+
+
 @pytest.mark.parametrize("N,E,hub", [(16384, 3000, 256), (16385, 3000, 0), (1000, 3000, 257), (1000, 23436, 0), (1000, 23437, 0)])
 def test_either_side_of_the_small_graph_rule(N, E, hub):
     """The largest graphs of the one-launch forward and the smallest beyond it, by nodes, by in-degree and by runs."""
