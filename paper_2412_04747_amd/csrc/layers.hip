@@ -54,6 +54,9 @@ struct Bf16Stage {
 
 // A [num_nodes, d] tensor may be NULL when the graph has no nodes.
 inline bool missing(const rgnn_graph_t* g, const void* p) { return !p && g->N > 0; }
+inline bool overlap(const void* p, size_t np, const void* q, size_t nq) {
+    return reinterpret_cast<uintptr_t>(p) < reinterpret_cast<uintptr_t>(q) + nq && reinterpret_cast<uintptr_t>(q) < reinterpret_cast<uintptr_t>(p) + np;
+}
 
 rgnn_status_t check_desc(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, int layer) {
     if (!g || !d) RGNN_FAIL(RGNN_EINVAL, "graph or desc is NULL");
@@ -474,7 +477,10 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* W32 = !h ? stg.in(W, (size_t)g->R * desc->d_in * D) : nullptr;
     const float* W032 = stg.in(W0, (size_t)desc->d_in * D);
     RGNN_TRY(stg.status);
-    if (sched_rgcn_small(desc->dtype, desc->d_in, D, g->Q, g->N, g->max_in_degree, desc->flags))
+    // (one launch: rows of out are written while others of X are still read, so an out that shares memory with X goes to the
+    // general plan, which has read X by then unless there is a self-loop)
+    if (!overlap(X, (size_t)g->N * desc->d_in * sizeof(float), out, (size_t)g->N * D * sizeof(float)) &&
+        sched_rgcn_small(desc->dtype, desc->d_in, D, g->Q, g->N, g->max_in_degree, desc->flags))
         return rgcn_small_fwd(g, desc->d_in, D, X32, W32, W032, desc->norm == RGNN_NORM_IN_DEGREE_PER_REL, relu, static_cast<float*>(out), st);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
     RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,

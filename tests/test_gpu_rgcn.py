@@ -116,6 +116,27 @@ def test_small_graph_with_rows_at_the_ends_of_the_range(d_in, d):
     g.close()
 
 
+@pytest.mark.parametrize("shift", [0, 3])
+@pytest.mark.parametrize("d", [32, 64])
+def test_small_graph_whose_output_takes_the_place_of_its_input(d, shift):
+    """Without a self-loop the forward may write `out` over X, wholly or from some row on: X has been read by then, whatever the
+    size of the graph."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    rng, src, dst, rel, _ = synth.tiny(90 + d, N=600, R=5, E=5000)
+    p = synth.rgcn_params(rng, 600, 5, d, d)
+    g = Graph(600, 5, src, dst, rel)
+    L = RgcnLayer(g, d)
+    L.load(p["X"], p["W"])
+    buf = torch.empty((600 + shift) * d, device="cuda")
+    buf[:600 * d] = L.X.flatten()
+    L.X, L.out = buf[:600 * d].view(600, d), buf[shift * d:].view(600, d)
+    L.fwd()
+    torch.cuda.synchronize()
+    check(L.out, O.rgcn_fwd(600, src, dst, rel, p["X"], p["W"], None, "in_degree_per_rel", "none"), TOL_F32, "out")
+    g.close()
+
+
 @pytest.mark.parametrize("N,E,hub", [(16384, 3000, 256), (16385, 3000, 0), (1000, 3000, 257), (1000, 23436, 0), (1000, 23437, 0)])
 def test_either_side_of_the_small_graph_rule(N, E, hub):
     """The largest graphs of the one-launch forward and the smallest beyond it, by nodes, by in-degree and by runs."""
