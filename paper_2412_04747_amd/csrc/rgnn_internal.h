@@ -102,6 +102,7 @@ struct rgnn_graph {
     int32_t R = 0, T = 0;
     int num_cus = 0;                       // compute units of the device the graph lives on
     int64_t max_in_degree = 0, max_pair_out_degree = 0, num_single_pairs = 0;
+    int64_t max_runs_per_node = 0;         // of a destination (an upper bound above 65536 runs)
     size_t index_bytes = 0;
     int32_t* idx[RGNN_IDX_COUNT] = {};     // device arrays, see RGNN_IDX_*
     int64_t idx_len[RGNN_IDX_COUNT] = {};

@@ -50,13 +50,25 @@ inline bool sched_fused_softmax(uint32_t flags) {
 }
 inline bool sched_ws_in_lds(int R, int d) { return (size_t)R * d * sizeof(float) <= kWsLdsMax; }
 
-// RGCN forward of a small graph in one launch (rgcn_small.hip), which reads a weight per (relation, destination) run where the
-// general plan reads one per tile of pairs; a workgroup per destination, and a destination's longest run is walked by one half
-// wavefront.  Against the general plan, us: 32 x 32 8.1 / 12.3 at 5.7k runs, 17 / 19 at 24k, 26 / 21 at 45k; 32 x 64 13 / 19 at 12k,
-// 21 / 22 at 24k; 64 x 64 15 / 19 at 6.7k, 22 / 22 at 12k.
-inline bool sched_rgcn_small(int dtype, int d_in, int d, int64_t runs, int64_t nodes, int64_t max_in_degree, uint32_t flags) {
-    return dtype == RGNN_F32 && d_in <= 64 && d <= 64 && runs * (d_in * d + 2048) <= 72000000 && nodes <= 16384 && max_in_degree <= 256 &&
-           !flag_set(flags, RGNN_FLAG_NO_BATCHED_WALKS);
+// RGCN forward of a small graph in one launch (rgcn_small.hip), which reads a weight per (relation, destination) run, and one per
+// node for the self-loop, where the general plan reads one per tile of rows; a workgroup per destination, whose eight half wavefronts
+// take its runs in turn, each run walked by one of them.  Two lines, both in the cost of a run (its product and its rows: linear in the
+// weight's and the row's length):
+//   throughput  runs and nodes (a workgroup's start and end cost as much as two runs).  One launch / general plan, us, without a
+//               self-loop: 32 x 32 7.9 / 12.9 at 1000 nodes and 5.7k runs, 9.7 / 11.4 at 4000 and 18k, 11.5 / 10.8 at 8192 and 15k, 16.6 /
+//               10.9 at 16k and 16k; 64 x 64 9.6 / 14.2 at 2000 and 6.9k, 15.3 / 12.6 at 4000 and 10k, 37 / 14 at 16k and 16k.  With one,
+//               whose launch and pass over out the general plan pays for: 32 x 32 12.3 / 13.8 at 8192 and 15k, 17.1 / 13.8 at 16k and
+//               8.4k; 64 x 64 16.5 / 18.5 at 4000 and 10k, 24 / 17 at 8192 and 7.1k, 35 / 17 at 16k and 500.
+//   latency     the longest chain, an eighth of a destination's runs and all its edges in one of them.  Eight destinations of n edges
+//               each, n relations: 32 x 32 11.7 / 15.3 at 64, 20 / 15 at 128; 64 x 64 11.6 / 15.1 at 32, 21 / 18 at 64, 91 / 18 at 256;
+//               one relation: 32 x 32 12.6 / 16.6 at 256, 17.4 / 16.6 at 384; 64 x 64 14.4 / 18.3 at 192, 25.6 / 18.6 at 384.
+inline bool sched_rgcn_small(int dtype, int d_in, int d, bool self_loop, int64_t runs, int64_t nodes, int64_t max_in_degree,
+                             int64_t max_runs_per_node, uint32_t flags) {
+    if (dtype != RGNN_F32 || d_in > 64 || d > 64 || flag_set(flags, RGNN_FLAG_NO_BATCHED_WALKS)) return false;
+    const int64_t kd = d_in * d, run = kd + 48 * d_in + 1024;
+    const int64_t most = self_loop ? 128000000 + 12000 * kd : 90000000 + 8000 * kd;
+    return (2 * runs + (self_loop ? 5 : 4) * nodes) * run <= 2 * most &&
+           (max_runs_per_node + 7) / 8 * run + max_in_degree * (7 * d_in / 2) <= 24000 + 400 * d_in;
 }
 
 struct ListCounts { int32_t single = 0, short_ = 0; };   // whole segments with 1 / with 2..kShortLen entries

@@ -137,17 +137,42 @@ def test_small_graph_whose_output_takes_the_place_of_its_input(d, shift):
     g.close()
 
 
-@pytest.mark.parametrize("N,E,hub", [(16384, 3000, 256), (16385, 3000, 0), (1000, 3000, 257), (1000, 23436, 0), (1000, 23437, 0)])
-def test_either_side_of_the_small_graph_rule(N, E, hub):
-    """The largest graphs of the one-launch forward and the smallest beyond it, by nodes, by in-degree and by runs."""
-    rng = np.random.default_rng(N + E)
-    R = 40
-    pick = rng.permutation((N - 1) * R)[:E]                # a run per edge; node N - 1 is the hub
-    dst, rel = (pick // R).astype(np.int32), (pick % R).astype(np.int32)
-    dst[:hub], rel[:hub] = N - 1, 3
-    src = rng.integers(0, N, E).astype(np.int32)
-    p = synth.rgcn_params(rng, N, R, 32, 32, self_loop=False)
-    _run(N, R, src, dst, rel, p, 32, "in_degree_per_rel", "none", False, tag=f"rule-{N}-{E}-{hub}")
+def _launches(call):
+    """Names of the kernels a call launches."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    torch.cuda.synchronize()
+    B.rgnn_profile_start()
+    call()
+    return set(B.rgnn_profile_stop())
+
+
+@pytest.mark.parametrize("k,loop,N,E,hub,rels,one", [
+    (32, False, 1000, 25397, 0, 0, True), (32, False, 1000, 25398, 0, 0, False),             # nodes and runs
+    (32, False, 13698, 1, 0, 0, True), (32, False, 13699, 1, 0, 0, False),
+    (64, True, 2000, 16625, 0, 0, True), (64, True, 2000, 16626, 0, 0, False),
+    (64, True, 8650, 0, 0, 0, True), (64, True, 8651, 0, 0, 0, False),
+    (32, False, 500, 300, 296, 1, True), (32, False, 500, 300, 297, 1, False),               # edges of one destination
+    (64, True, 500, 300, 184, 1, True), (64, True, 500, 300, 185, 1, False),
+    (32, False, 500, 300, 64, 64, True), (32, False, 500, 300, 65, 65, False),               # relations of one destination
+    (64, False, 500, 300, 40, 40, False), (64, False, 500, 300, 32, 32, True), (64, False, 500, 300, 256, 256, False)])
+def test_either_side_of_the_small_graph_rule(k, loop, N, E, hub, rels, one):
+    """The largest graphs of the one-launch forward and the smallest beyond it: which plan runs, and its results."""
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    rng = np.random.default_rng(N + E + hub)
+    R = max(40, rels)
+    pick = rng.permutation((N - 1) * 40)[:E]               # a run per edge, none at node N - 1
+    dst, rel = np.concatenate([pick // 40, np.full(hub, N - 1)]), np.concatenate([pick % 40, np.arange(hub) % max(rels, 1)])
+    src, dst, rel = rng.integers(0, N, E + hub).astype(np.int32), dst.astype(np.int32), rel.astype(np.int32)
+    p = synth.rgcn_params(rng, N, R, k, k, self_loop=True)
+    g = Graph(N, R, src, dst, rel)
+    L = RgcnLayer(g, k, "in_degree_per_rel", "none", loop)
+    W0 = p["W0"] if loop else None
+    L.load(p["X"], p["W"], W0)
+    names = _launches(L.fwd)
+    assert ("rgcn_small_fwd" in names) == one and ("aggregate_fwd" in names) == (not one), names
+    check(L.out, O.rgcn_fwd(N, src, dst, rel, p["X"], p["W"], W0, "in_degree_per_rel", "none"), TOL_F32, "out")
+    g.close()
 
 
 @pytest.mark.parametrize("d_in,d", [(32, 32), (32, 64), (64, 32), (64, 64)])
