@@ -184,7 +184,7 @@ struct ShareSums {
     static constexpr int kMax = 4;
     struct Job {
         const float* part; const int32_t* seg_slot_ptr;
-        int blocks, col_blocks, many, kn, kd;
+        int blocks, col_blocks, many, kn, kd, used;      // used: floats of a slot that are summed
         float* dW; float* dW2;
     };
     Job job[kMax];

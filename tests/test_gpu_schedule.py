@@ -243,3 +243,38 @@ def test_chunks_of_many_relations(wl, layer, d, H):
     for k, v in L.grads().items():
         check(v, want[k], TOL_F32, k)
     g.close()
+
+
+@pytest.mark.parametrize("layer,d,dtype", [("rgcn", 32, "f32"), ("rgcn", 64, "f32"), ("rgcn", 128, "f32"), ("rgcn", 128, "bf16"), ("rgat", 64, "f32")])
+def test_weight_gradients_of_a_few_shares(layer, d, dtype):
+    """Relations whose weight gradient is the sum of 1, 2, .. 17 shares (a row tile per compute unit), an empty one among them."""
+    import torch
+    from paper_2412_04747_amd import harness as Hn
+    rng = np.random.default_rng(170 + d)
+    tiles = [0] + list(range(1, 18)) + [1] * 60
+    N, R = 64 * 17, len(tiles)
+    src = np.concatenate([rng.permutation(N)[:64 * t] for t in tiles]).astype(np.int32)
+    rel = np.repeat(np.arange(R, dtype=np.int32), [64 * t for t in tiles])
+    dst = rng.integers(0, N, len(src)).astype(np.int32)
+    print(f"schedule case few shares {layer} {dtype} d={d}: E={len(src)}", flush=True)
+    g = Hn.Graph(N, R, src, dst, rel)
+    tol = TOL_BF16 if dtype == "bf16" else TOL_F32
+    if layer == "rgat":
+        p = synth.rgat_params(rng, N, R, d, d)
+        L = Hn.RgatLayer(g, d)
+        L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+        want = O.rgat_bwd(N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    else:
+        p = synth.rgcn_params(rng, N, R, d, d)
+        if dtype == "bf16":
+            p = {k: (None if v is None else synth.round_to_bf16(v)) for k, v in p.items()}
+        L = Hn.RgcnLayer(g, d, "none", dtype=dtype)
+        L.load(p["X"], p["W"], None, p["dOut"])
+        want = O.rgcn_bwd(N, src, dst, rel, p["X"], p["W"], None, p["dOut"], "none", "none", out=np.zeros((N, d)))
+    L.fwd(); L.bwd()
+    torch.cuda.synchronize()
+    for k, v in L.grads().items():
+        check(v, want[k], tol, k)
+    for r in range(R):                                   # by relation: a lost share would hide among the others
+        check(L.dW[r], want["dW"][r], tol, f"dW[{r}]")
+    g.close()
