@@ -260,6 +260,14 @@ __device__ __forceinline__ void fold_weight_block(const FoldArgs& f, int blk) {
     }
 }
 
+// Grid of a launch of `blocks` workgroups of 256 threads, whose lanes HIP counts in 32 bits per dimension: the numbers run on in y, and
+// a few at the end belong to nobody.
+inline dim3 flat_grid(int64_t blocks) {
+    constexpr int64_t kRow = 1 << 22;
+    return blocks <= kRow ? dim3((unsigned)blocks) : dim3((unsigned)kRow, (unsigned)((blocks + kRow - 1) / kRow));
+}
+__device__ __forceinline__ int flat_block() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+
 inline unsigned blocks_for(size_t n, unsigned per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 #define RGNN_CHECK_LAUNCH() RGNN_HIP(hipGetLastError())

@@ -177,6 +177,7 @@ struct SumArgs {
     const float* partial; const int32_t* split_row; const int32_t* split_ptr; float* out;
     size_t partial_copy, out_copy;       // floats from one set to the next
     int num_split, D, copies;
+    __host__ __device__ int64_t blocks() const { return (int64_t)num_split * copies * (D / 16); }
 };
 // What backward typed linears leave to be summed: dW[s] (kn floats) and, when given, dW2[s] (kd floats) = sums of segment s's slots of
 // kn + kd floats each, for up to kMax lists, and optionally pieces as above.  One launch (traversal.hip) sums them all.

@@ -910,7 +910,7 @@ __device__ __forceinline__ void piece_sum_block(const SumArgs& u, int blk, float
 template <int N>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void sum_shares_kernel(ShareSums s) {
     __shared__ float4 red[256];
-    int blk = blockIdx.x;
+    int blk = flat_block();
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         const ShareSums::Job j = s.job[k];
@@ -922,7 +922,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void s
         }
         blk -= j.blocks;
     }
-    piece_sum_block(s.pieces, blk, red);
+    if (blk < s.pieces.blocks()) piece_sum_block(s.pieces, blk, red);
 }
 
 rgnn_status_t ShareSums::add(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2) {
@@ -935,13 +935,13 @@ rgnn_status_t ShareSums::add(const TileList& tiles, const float* part, int kn, i
     return RGNN_OK;
 }
 rgnn_status_t ShareSums::launch(hipStream_t st) {
-    int64_t blocks = pieces.num_split > 0 ? (int64_t)pieces.num_split * pieces.copies * (pieces.D / 16) : 0;
+    int64_t blocks = pieces.blocks();
     for (int k = 0; k < n; ++k) blocks += job[k].blocks;
-    if (blocks > INT32_MAX) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: too many segments");
+    if (blocks > INT32_MAX / 2) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: too many segments");
     if (blocks > 0) {
         KernelTimer kt(st, "typed_linear_bwd.reduce");
         auto kern = n == 1 ? sum_shares_kernel<1> : n == 2 ? sum_shares_kernel<2> : n == 3 ? sum_shares_kernel<3> : sum_shares_kernel<4>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, *this);
+        hipLaunchKernelGGL(kern, flat_grid(blocks), dim3(256), 0, st, *this);
         RGNN_CHECK_LAUNCH();
     }
     n = 0;
@@ -1090,17 +1090,18 @@ template <int D, typename TI, typename TO, int H, bool TWO>
 __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a, RgatFinish fin) {
     constexpr bool RUNS = H > 0;
     __shared__ float red[RUNS ? 512 : 1];
-    if (RUNS && (int)blockIdx.x < fin.blocks) {
-        param_finish_block(fin, blockIdx.x, red);
+    const int blk = flat_block();
+    if (RUNS && blk < fin.blocks) {
+        param_finish_block(fin, blk, red);
         return;
     }
     constexpr int V = RowT<TI>::V, LPR = D / V, IPB = 256 / LPR, G = 64 / LPR;
     constexpr int HH = RUNS ? H : 1, RB = HH == 1 ? 4 : HH <= 4 ? 2 : 1;     // runs per batch
     constexpr int ALONE = 8 * RB;                                           // runs that a lane group walks by itself
     static_assert(!RUNS || (sizeof(TI) == 4 && !TWO), "the run term goes with fp32 rows of one tensor");
-    const int i0 = (blockIdx.x - (RUNS ? fin.blocks : 0)) * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
+    const int i0 = (blk - (RUNS ? fin.blocks : 0)) * IPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
     const bool on = i0 < a.it.n;
-    if (!RUNS && !on) return;                       // (with runs, the lanes past the end help with other nodes')
+    if (RUNS ? !__any(on) : !on) return;            // (with runs, the lanes past the end help with other nodes')
     const int i = min(i0, a.it.n - 1);
     const TI* __restrict__ dXp = static_cast<const TI*>(a.dXp);
     const TI* __restrict__ dXp2 = static_cast<const TI*>(a.dXp2);
@@ -1496,7 +1497,9 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
                             const float* extra, void* dX, hipStream_t st, int in_bf16, int out_bf16, int heads,
                             const void* dXp2, const RgatFinish* finish) {
     RgatFinish fin = finish ? *finish : RgatFinish{};
-    if (finish) fin.blocks = fin.R * (fin.nd / 32 + (fin.kd * fin.nd + 1023) / 1024);
+    const int64_t fin_blocks = finish ? (int64_t)fin.R * (fin.nd / 32 + (fin.kd * fin.nd + 1023) / 1024) : 0;
+    if (fin_blocks > INT32_MAX / 2) RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: the parameter gradients of %d relations are too many", fin.R);
+    fin.blocks = (int)fin_blocks;
     if (finish && !ds_dst) RGNN_FAIL(RGNN_EINVAL, "node_grad_sum: the parameter gradients go with the run term");
     if (g->N == 0 && fin.blocks == 0) return RGNN_OK;
     if (ds_dst && dXp2) RGNN_FAIL(RGNN_EINVAL, "node_grad_sum: the run term and a second row tensor exclude each other");
@@ -1505,7 +1508,7 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
                   g->idx[RGNN_IDX_DST_RUN_PTR], g->idx[RGNN_IDX_RUN_REL], ds_dst, wtp, extra, dX};
     if (ds_dst && (in_bf16 || out_bf16)) RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: the run term is built for fp32 rows");
     KernelTimer kt(st, "node_grad_sum");
-    const dim3 grid(blocks_for((size_t)g->N, 256 / (D / (in_bf16 ? 8 : 4))) + fin.blocks);
+    const dim3 grid = flat_grid((int64_t)blocks_for((size_t)g->N, 256 / (D / (in_bf16 ? 8 : 4))) + fin.blocks);
     if (ds_dst) {
 #define RGNN_NODE_SUM(H_) RGNN_DISPATCH_D(D, hipLaunchKernelGGL((node_grad_sum_kernel<DD, float, float, H_, false>), grid, dim3(256), 0, st, a, fin))
         if (heads == 1) RGNN_NODE_SUM(1);

@@ -353,3 +353,49 @@ def test_edge_order_invariance_is_bitwise():
         res.append([L.out.clone()] + [v.clone() for v in L.grads().values()])
     for a, b in zip(*res):
         assert torch.equal(a, b)
+
+
+@pytest.mark.timeout(300)
+def test_more_parameters_than_one_row_of_workgroups():
+    """4.2M relations, 32 -> 64 columns, and 8.38M, 32 -> 32: the launches that sum the weight gradient's shares and finish the parameter
+    gradients have more workgroups of 256 threads than 2^32 lanes hold.  Fifty relations have edges; the gradients of the others are
+    zero."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph
+    rng = np.random.default_rng(88)
+    N, E, used = 40000, 4000, 50
+    for R, k, d in ((4_200_000, 32, 64), (8_388_000, 32, 32)):
+        print(f"rgat case many parameters: R={R} {k}->{d}", flush=True)
+        ids = np.sort(np.concatenate([[0, R - 1], rng.choice(np.arange(1, R - 1), used - 2, replace=False)]))
+        src, dst = rng.integers(0, N, E).astype(np.int32), rng.integers(0, N, E).astype(np.int32)
+        few = rng.integers(0, used, E).astype(np.int32)
+        p = synth.rgat_params(rng, N, used, k, d)
+        g = Graph(N, R, src, dst, ids[few].astype(np.int32))
+        desc = B.make_desc(B.RGNN_F32, k, d, 1, 0.2)
+        f, b, s = B.rgnn_workspace_bytes(g.handle, B.RGNN_LAYER_RGAT, desc)
+        at = torch.as_tensor(ids, device="cuda")
+        dev = lambda a: torch.from_numpy(a).cuda()
+        def spread(a):
+            t = torch.zeros((R,) + a.shape[1:], device="cuda")
+            t[at] = dev(a)
+            return t
+        X, dO, W, ws, wt = dev(p["X"]), dev(p["dOut"]), spread(p["W"]), spread(p["w_s"]), spread(p["w_t"])
+        e = lambda *shape: torch.full(shape, 7.0, device="cuda")
+        out, dX, dW, dws, dwt = e(N, d), e(N, k), e(R, k, d), e(R, d), e(R, d)
+        work, saved = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (max(f, b), s))
+        B.rgnn_rgat_fwd(g.handle, desc, X, W, ws, wt, out, saved, work)
+        B.rgnn_rgat_bwd(g.handle, desc, X, W, ws, wt, out, saved, dO, dX, dW, dws, dwt, work)
+        torch.cuda.synchronize()
+        a = (N, src, dst, few, p["X"], p["W"], p["w_s"], p["w_t"])
+        check(out, O.rgat_fwd(*a), TOL_F32, "out")
+        want = O.rgat_bwd(*a, p["dOut"])
+        check(dX, want["dX"], TOL_F32, "dX")
+        for name, got in (("dW", dW), ("dw_s", dws), ("dw_t", dwt)):
+            check(got[at], want[name], TOL_F32, name)
+            got[at] = 0
+            for part in got.view(R, -1).split(1 << 20):
+                assert not part.any(), name
+        g.close()
+        del X, dO, W, ws, wt, out, dX, dW, dws, dwt, work, saved, got, part
+        torch.cuda.empty_cache()
