@@ -105,7 +105,7 @@ static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int ti
         chunk_tiles(p, c.max_chunks);
         TileList& t = *c.list;
         t.tile_rows = p.tile_rows; t.num_tiles = p.num_tiles; t.num_chunks = p.num_chunks; t.num_slots = p.num_slots;
-        t.num_segs = p.num_segs;
+        t.num_segs = p.num_segs; t.max_seg_slots = p.max_seg_slots;
         t.tile_seg = seg; t.tile_row0 = row0; t.tile_row1 = row1;
         t.chunk_tile = U.up(p.chunk_tile); t.chunk_slot = U.up(p.chunk_slot); t.seg_slot_ptr = U.up(p.seg_slot_ptr);
     }

@@ -54,6 +54,7 @@ struct TileList {
     int32_t num_chunks = 0;
     int32_t num_slots = 0;
     int32_t num_segs = 0;
+    int32_t max_seg_slots = 0;       // slots of the segment with the most
     int32_t* tile_seg = nullptr;     // [num_tiles]  device
     int32_t* tile_row0 = nullptr;    // [num_tiles]  first row of the tile
     int32_t* tile_row1 = nullptr;    // [num_tiles]  end row (exclusive; <= row0 + tile_rows)
@@ -183,9 +184,10 @@ struct SumArgs {
 // kn + kd floats each, for up to kMax lists, and optionally pieces as above.  One launch (traversal.hip) sums them all.
 struct ShareSums {
     static constexpr int kMax = 4;
+    enum { kMany, kUneven, kFew };           // how a list's slots lie (traversal.hip)
     struct Job {
         const float* part; const int32_t* seg_slot_ptr;
-        int blocks, col_blocks, many, kn, kd, used;      // used: floats of a slot that are summed
+        int blocks, col_blocks, kind, kn, kd, used;      // used: floats of a slot that are summed
         float* dW; float* dW2;
     };
     Job job[kMax];

@@ -787,16 +787,16 @@ __global__ void zero_f32_kernel(size_t n, float* __restrict__ x) {
 // ------------------------------------------------------------------ sums of the weight gradients' shares
 
 // dW[s] (and Avec[s]) = sum of the partial slots of segment s; kn / kd = floats of a slot's matrix / vector part, both
-// multiples of 4.  Few segments with many slots each: a workgroup owns 16 consecutive float4 of one segment's slots; its 16 lane groups
-// take the slots in turn, four loads in flight each, and the group sums are added in four chains through LDS, so the result does not
-// depend on scheduling (as one chain the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.27e-7).  Bound by the chain of loads
-// of the segment with the most slots.
+// multiples of 4.  A workgroup owns C4 consecutive float4 of one segment's slots; its G lane groups take the slots in turn,
+// four loads in flight each, and the group sums are added in four chains through LDS, so the result does not depend on
+// scheduling (as one chain the error of a self-loop's dW at 120k nodes was 1.47e-7, now 1.27e-7).  Bound by the chain of loads of the
+// segment with the most slots, and with thousands of segments by their workgroups' start.
 __device__ __forceinline__ void store_slot_sum(const ShareSums::Job& j, int seg, int i, float4 t) {
     if (i < j.kn) *reinterpret_cast<float4*>(j.dW + (size_t)seg * j.kn + i) = t;
     else *reinterpret_cast<float4*>(j.dW2 + (size_t)seg * j.kd + (i - j.kn)) = t;
 }
-__device__ __forceinline__ void slot_sum_many(const ShareSums::Job& j, int seg, int col_blk, float4* red) {
-    constexpr int G = 16, C4 = 16;
+template <int G, int C4>
+__device__ __forceinline__ void slot_sum_groups(const ShareSums::Job& j, int seg, int col_blk, float4* red) {
     const int c = threadIdx.x % C4, g = threadIdx.x / C4;
     const int i = (col_blk * C4 + c) * 4, slot_sz = j.kn + j.kd;
     const bool on = i < j.used;
@@ -820,7 +820,7 @@ __device__ __forceinline__ void slot_sum_many(const ShareSums::Job& j, int seg, 
     }
     red[g * C4 + c] = make_float4(s0.x + s1.x, s0.y + s1.y, s0.z + s1.z, s0.w + s1.w);
     __syncthreads();
-    constexpr int CH = 64 / C4;                            // chains over the groups, one wavefront's worth of lanes
+    constexpr int CH = C4 < 64 ? 64 / C4 : 1;              // chains over the groups, one wavefront's worth of lanes
     if (g >= CH) return;
     float4 t = red[g * C4 + c];
 #pragma unroll
@@ -835,37 +835,37 @@ __device__ __forceinline__ void slot_sum_many(const ShareSums::Job& j, int seg, 
     if (g == 0 && on) store_slot_sum(j, seg, i, t);
 }
 // Many segments of a few slots each: a lane per float4 of the slot, eight slots in flight, added in four chains; bound by the slots'
-// bytes.  (Shared between four lane groups and LDS, with a quarter of the columns per workgroup, it was bound by the workgroups' start:
-// 2000 segments of width 64 in one or two slots each 24 us, so 13; 500 of width 128 in bf16 25, so 17; HGT's 300 folded pairs of
-// weights 54, so 36.  With 16 slots in flight the kernel's registers halve the wavefronts of the other kind of block: 42 us
-// for 31 with 30 relations in bf16.)
+// bytes.  (In blocks as above with G = 4 it was bound by the workgroups' start: 2000 segments of width 64 in one or two slots each 24 us,
+// so 14; 500 of width 128 in bf16 25, so 17; HGT's 300 folded pairs of weights 54, so 36.  With 16 slots in flight the kernel's
+// registers halve the wavefronts of the other blocks: 42 us for 31 with 30 relations in bf16.)
 __device__ __forceinline__ void slot_sum_few(const ShareSums::Job& j, int seg, int col_blk) {
-    const int i = (col_blk * 256 + (int)threadIdx.x) * 4, slot_sz = j.kn + j.kd;
-    if (i >= j.used) return;
+    const unsigned i = (col_blk * 256u + threadIdx.x) * 4;
+    const size_t slot_sz = j.kn + j.kd;
+    if ((int)i >= j.used) return;
     int sl = j.seg_slot_ptr[seg];
     const int e = j.seg_slot_ptr[seg + 1];
-    const float* const p = j.part + i;
+    auto load = [&](int slot) { return *reinterpret_cast<const float4*>(j.part + slot * slot_sz + i); };
     float4 s[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) s[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (; sl + 8 <= e; sl += 8) {
         float4 x[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const float4*>(p + (size_t)(sl + k) * slot_sz);
+        for (int k = 0; k < 8; ++k) x[k] = load(sl + k);
 #pragma unroll
         for (int k = 0; k < 8; ++k) fma4(s[k & 3], 1.f, x[k]);
     }
     for (; sl < e; sl += 4) {
         float4 x[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = sl + k < e ? *reinterpret_cast<const float4*>(p + (size_t)(sl + k) * slot_sz) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int k = 0; k < 4; ++k) x[k] = sl + k < e ? load(sl + k) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int k = 0; k < 4; ++k) fma4(s[k], 1.f, x[k]);
     }
     fma4(s[0], 1.f, s[1]);
     fma4(s[2], 1.f, s[3]);
     fma4(s[0], 1.f, s[2]);
-    store_slot_sum(j, seg, i, s[0]);
+    store_slot_sum(j, seg, (int)i, s[0]);
 }
 
 // The other kind of shares that RGAT's backward leaves per relation: U[h][r] from the pieces of r's run list (SumArgs: one copy of
@@ -902,11 +902,13 @@ __device__ __forceinline__ void piece_sum_block(const SumArgs& u, int blk, float
     }
     if (g == 0) *reinterpret_cast<float4*>(u.out + (size_t)h * u.out_copy + (size_t)u.split_row[s] * u.D + c4 * 4) = red[c];
 }
-// One launch for all shares of a backward pass, a list's blocks of either kind one after the other (above eight slots per segment
-// many lane groups on narrow column ranges win: a self-loop weight, node types, few relations).  HGT in bf16, three lists: 54 us as three
-// launches, now 38 (2M nodes, 5.4M pairs), 38 and 31 (200k nodes); in fp32 at 300k edges four launches of 6, now one of 7; RGCN
-// with a self-loop 13 and 7.  (With workgroups of 512 threads 59 and 39 us in the first two.  N is a template parameter so that the
-// jobs' fields are loaded together.)
+// One launch for all shares of a backward pass, a list's blocks of any kind one after the other.  Above eight slots per segment (a
+// self-loop weight, node types, few relations) many lane groups on narrow column ranges win.  Below, a lane alone on its slots, unless
+// the segment with the most slots would take it longer than the list's bytes take (frequencies of Zipf 1.2, 500 relations, 1.2M edges:
+// width 32 9.9 us, in four groups 7; width 64 11.9 and 10.7; in bf16 at width 128, where the bytes take longer, 20 and 30).  HGT
+// in bf16, three lists: 54 us as three launches, now 38 (2M nodes, 5.4M pairs), 38 and 31 (200k nodes); in fp32 at 300k edges four
+// launches of 6, now one of 7; RGCN with a self-loop 13 and 7.  (With workgroups of 512 threads 59 and 39 us in the first two.  N is
+// a template parameter so that the jobs' fields are loaded together.)
 template <int N>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void sum_shares_kernel(ShareSums s) {
     __shared__ float4 red[256];
@@ -916,7 +918,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void s
         const ShareSums::Job j = s.job[k];
         if (blk < j.blocks) {
             const int seg = blk / j.col_blocks, cb = blk % j.col_blocks;
-            if (j.many) slot_sum_many(j, seg, cb, red);
+            if (j.kind == ShareSums::kMany) slot_sum_groups<16, 16>(j, seg, cb, red);
+            else if (j.kind == ShareSums::kUneven) slot_sum_groups<4, 64>(j, seg, cb, red);
             else slot_sum_few(j, seg, cb);
             return;
         }
@@ -928,10 +931,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void s
 rgnn_status_t ShareSums::add(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2) {
     if (n == kMax) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: more than %d lists", kMax);
     const int used = dW2 ? kn + kd : kn;
-    const bool many = tiles.num_slots > 8 * tiles.num_segs;
-    const int cols = many ? (used + 63) / 64 : (used + 1023) / 1024;
+    const int kind = tiles.num_slots > 8 * tiles.num_segs ? kMany : (int64_t)tiles.max_seg_slots << 16 > (int64_t)tiles.num_slots * used ? kUneven : kFew;
+    const int floats = kind == kMany ? 64 : kind == kUneven ? 256 : 1024, cols = (used + floats - 1) / floats;
     if ((int64_t)tiles.num_segs * cols > INT32_MAX / (kMax + 1)) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: %d segments are too many", tiles.num_segs);
-    job[n++] = Job{part, tiles.seg_slot_ptr, tiles.num_segs * cols, cols, many, kn, kd, used, dW, dW2};
+    job[n++] = Job{part, tiles.seg_slot_ptr, tiles.num_segs * cols, cols, kind, kn, kd, used, dW, dW2};
     return RGNN_OK;
 }
 rgnn_status_t ShareSums::launch(hipStream_t st) {

@@ -29,6 +29,7 @@ constexpr int kSerialMax = 32;      // longest segment a single lane walks; long
 // are the consecutive range [seg_slot_ptr[s], seg_slot_ptr[s + 1]).
 struct TilePlan {
     int32_t tile_rows = 0, num_tiles = 0, num_chunks = 0, num_slots = 0, num_segs = 0;
+    int32_t max_seg_slots = 0;                             // of a segment
     std::vector<int32_t> tile_seg, tile_row0, tile_row1;   // [num_tiles] segment, first row, end row
     std::vector<int32_t> chunk_tile;                       // [num_chunks + 1]
     std::vector<int32_t> chunk_slot;                       // [num_chunks] first slot of the chunk
@@ -56,7 +57,11 @@ inline void chunk_tiles(TilePlan& t, int max_chunks) {
                 seg_slots[t.tile_seg[i]]++;
             }
     }
-    for (int s = 0; s < S; ++s) t.seg_slot_ptr[s + 1] = t.seg_slot_ptr[s] + seg_slots[s];
+    t.max_seg_slots = 0;
+    for (int s = 0; s < S; ++s) {
+        t.seg_slot_ptr[s + 1] = t.seg_slot_ptr[s] + seg_slots[s];
+        t.max_seg_slots = std::max(t.max_seg_slots, seg_slots[s]);
+    }
     t.num_chunks = nc;
     t.num_slots = slots;
 }

@@ -245,14 +245,17 @@ def test_chunks_of_many_relations(wl, layer, d, H):
     g.close()
 
 
+@pytest.mark.parametrize("uneven", [False, True])
 @pytest.mark.parametrize("layer,d,dtype", [("rgcn", 32, "f32"), ("rgcn", 64, "f32"), ("rgcn", 128, "f32"), ("rgcn", 128, "bf16"), ("rgat", 64, "f32")])
-def test_weight_gradients_of_a_few_shares(layer, d, dtype):
-    """Relations whose weight gradient is the sum of 1, 2, .. 17 shares (a row tile per compute unit), an empty one among them."""
+def test_weight_gradients_of_a_few_shares(layer, d, dtype, uneven):
+    """Relations whose weight gradient is the sum of a few shares (one per compute unit that has tiles of the relation), an empty one
+    among them: 1 to 10 shares of 1 to 40 row tiles, and 850 relations of one; 1 to 17, one of 150 and 60 of one, where four groups
+    of lanes share the shares."""
     import torch
     from paper_2412_04747_amd import harness as Hn
     rng = np.random.default_rng(170 + d)
-    tiles = [0] + list(range(1, 18)) + [1] * 60
-    N, R = 64 * 17, len(tiles)
+    tiles = [0] + list(range(1, 18)) + [150] + [1] * 60 if uneven else [0, 1, 2, 3, 5, 8, 12, 16, 20, 24, 28, 32, 36, 40] + [1] * 850
+    N, R = 64 * max(tiles), len(tiles)
     src = np.concatenate([rng.permutation(N)[:64 * t] for t in tiles]).astype(np.int32)
     rel = np.repeat(np.arange(R, dtype=np.int32), [64 * t for t in tiles])
     dst = rng.integers(0, N, len(src)).astype(np.int32)
