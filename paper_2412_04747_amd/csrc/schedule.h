@@ -29,13 +29,17 @@ inline int batched_count(int count, uint32_t flags) {
 inline bool sched_rows_bf16(int dtype, int d) { return dtype == RGNN_BF16 && d == 128; }
 // The gradient row of a (source, relation) pair with one edge is not materialised: the typed-linear backward reads
 // it from the destination's gradient row through a row selector.  Built for RGAT with one head, and up to width 64 with two
-// or four (the fused fp32 backward kernel); and for RGCN, with fp32 rows where the batched walk would take the pairs with
-// one edge.  Training passes with and without at 1.2M edges 462 / 508 us (width 64), 226 / 244 (width 32);
-// 1M edges 820 / 917 (width 128); 300k edges 171 / 174 (width 64); at 20k edges no difference, and below that the plain walk stays.
-inline bool sched_row_select(int layer, int dtype, int d, int heads, int single_pairs, uint32_t flags) {
+// or four (the fused fp32 backward kernel); and for RGCN, with bf16 rows and, with fp32 rows, where the walk it saves is longer
+// than what it adds to the backward: a run of a relation's rows then starts with one load more, selector before row.  Backward
+// with / without, us: width 64, 50 relations 38 / 38 at 30k edges (16k such pairs), 194 / 237 at 1M; 500 of equal frequency 43 / 41 at
+// 10k, 75 / 76 at 100k (198 such pairs per relation), 141 / 155 at 400k; 2000 129 / 123 at 100k (50), 159 / 157 at 200k (99), 194 /
+// 208 at 400k (198); 4000 243 / 243 at 200k (50), 281 / 313 at 400k (99: the rows of the pairs no longer fit the caches); width 32, 4000 139
+// / 135 at 400k, 176 / 201 at 1M; width 128, where the loads run two units ahead, 500 51 / 50 at 10k, 61 / 63 at 30k, 2000 252 / 278 at 200k.
+inline bool sched_row_select(int layer, int dtype, int d, int heads, int R, int64_t single_pairs, uint32_t flags) {
     if (flag_set(flags, RGNN_FLAG_NO_ROW_SELECT)) return false;
     if (layer == RGNN_LAYER_RGAT) return heads == 1 || (d <= 64 && (heads == 2 || heads == 4) && d % (4 * heads) == 0);
-    if (layer == RGNN_LAYER_RGCN) return sched_rows_bf16(dtype, d) || single_pairs >= kBatchedMin;
+    if (layer == RGNN_LAYER_RGCN)
+        return sched_rows_bf16(dtype, d) || (single_pairs * d >= 640000 && (d == 128 || single_pairs >= 160 * (int64_t)R || single_pairs * d >= 24000000));
     return false;
 }
 // HGT: the key and message linears of the nodes are folded into the per-relation weights when every relation's
@@ -87,7 +91,7 @@ inline rgnn_schedule_t pick_schedule(const ScheduleIn& in) {
     s.tile_chunks = in.tile_chunks;
     s.wide_chunks = in.wide_chunks;
     s.rows_bf16 = sched_rows_bf16(in.dtype, in.d) && in.layer != RGNN_LAYER_RGAT;
-    s.row_select = sched_row_select(in.layer, in.dtype, in.d, in.heads, in.pair.single, in.flags);
+    s.row_select = sched_row_select(in.layer, in.dtype, in.d, in.heads, in.R, in.pair.single, in.flags);
     s.hgt_folded = in.layer == RGNN_LAYER_HGT && sched_hgt_folded(in.rel_src_tied, in.flags);
     s.fused_softmax = in.layer == RGNN_LAYER_RGAT && sched_fused_softmax(in.flags);
     s.ws_in_lds = s.fused_softmax && sched_ws_in_lds(in.R, in.d);
