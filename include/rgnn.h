@@ -214,14 +214,18 @@ typedef struct {
     int32_t tile_chunks;         /* workgroups of the typed-linear kernels over the pair tiles (short chunks) */
     int32_t wide_chunks;         /* the same tiles in one resident round of long chunks, as the backward takes them: one
                                     workgroup per compute unit, two for RGCN with rows_bf16, three for fp32 up to
-                                    width 64 where the relations are short */
+                                    width 64 where the relations are short; with hgt_folded, in fp32 up to width 64, the
+                                    share of one per compute unit that falls to each of the two lists of the pairs beside
+                                    the nodes' (RGCN's share beside a self-loop, which desc does not tell, is not in here) */
     int32_t rows_bf16;           /* intermediate row tensors stored as bfloat16 */
     int32_t row_select;          /* single-edge pairs: gradient row read through the row selector, not materialised */
     int32_t hgt_folded;          /* HGT key / message linears folded into the per-relation weights */
     int32_t fused_softmax;       /* RGAT: edge softmax fused into the aggregation walk */
     int32_t ws_in_lds;           /* ... with w_s held in LDS */
     int32_t edge_parallel;       /* forward aggregation edge by edge with atomic adds */
-    int32_t dst_batched_single;  /* destination-major walk: batched kernel phase for destinations with one edge */
+    int32_t dst_batched_single;  /* destination-major walk: batched kernel phase for destinations with one edge (an RGCN forward of
+                                    a small graph in one launch has no such walk; whether it is taken also depends on the
+                                    self-loop, so no field tells: its kernel is rgcn_small_fwd in the timing report) */
     int32_t dst_batched_short;   /* ... and for those with 2..4 edges */
     int32_t pair_walk_multi_only;/* pair-major backward walk visits only the pairs with several edges */
     int32_t pair_batched_single; /* pair-major walk: batched phase for pairs with one edge */

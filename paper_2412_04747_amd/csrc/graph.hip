@@ -88,12 +88,6 @@ struct Uploader {
     }
 };
 
-// Chunks for each of `lists` lists of P rows that share `cus` compute units with a list of N rows.
-static int pair_share(int64_t P, int64_t N, int cus, int lists) {
-    const int64_t rows = std::max<int64_t>(lists * P + N, 1);
-    return (int)std::min<int64_t>(std::max<int64_t>((P * cus + rows / 2) / rows, 1), std::max((cus - 1) / lists, 1));
-}
-
 // Tile lists over one segmentation: the tiles are planned and uploaded once, every list gets its own chunks.
 struct Chunking { TileList* list; int max_chunks; };
 static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int tile_rows, std::initializer_list<Chunking> lists) {

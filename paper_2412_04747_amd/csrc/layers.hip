@@ -260,7 +260,10 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // of the nodes are folded into the per-relation weights (Wf = Wk[type] Watt[r], Wv[type] Wmsg[r]), so
 // K, V and their gradients do not exist and the per-pair rows come straight from X.
 inline bool hgt_folded(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_hgt_folded(g->rel_src_tied, d->flags); }
-// folded path, fp32 rows up to width 64: the backwards of the two pair linears and of the query linear in one launch
+// folded path, fp32 rows up to width 64: the backwards of the two pair linears and of the query linear in one launch, also where
+// relations are short (see Chunkings): three launches less outweigh the chunks' unevenness.  Backward of the layer with one launch / a
+// launch each, width 64: 30 relations 100 / 123 us at 100k edges, 706 / 752 at 1.5M; 500 of equal frequency 292 / 297 at 20k, 583 / 644
+// at 400k; 1500 871 / 892 at 100k, 2005 / 2022 at 1.5M; width 32, 1500 relations 563 / 570 at 20k, 633 / 603 at 100k, 790 / 811 at 400k.
 inline bool hgt_bwd_jobs(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return hgt_folded(g, d) && d->d_out <= 64; }
 // KM holds the key row and the message row of a pair side by side; ms the (max, sum) of every (destination, head) softmax.
 struct HgtSaved { void* K; void* Q; void* V; void* Z; void* KM; float* ms; void* Wf_att; void* Wf_msg; };
@@ -447,7 +450,8 @@ extern "C" rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, con
     const Chunkings pc = pair_chunks(g, desc->d_out);
     in.item_len = item_cut(g->E); in.tile_chunks = pc.many->num_chunks;
     const bool rows16 = layer != RGNN_LAYER_RGAT && rows_bf16(desc);
-    in.wide_chunks = (!rows16 ? pc.f32_bwd : layer == RGNN_LAYER_RGCN ? pc.cu2 : pc.cu1)->num_chunks;
+    in.wide_chunks = (rows16 ? (layer == RGNN_LAYER_RGCN ? pc.cu2 : pc.cu1)
+                             : layer == RGNN_LAYER_HGT && hgt_bwd_jobs(g, desc) ? &g->pair_tiles_hgt : pc.f32_bwd)->num_chunks;
     in.dst = {g->dst_items.num_single, g->dst_items.num_short};
     in.pair = {g->pair_items.num_single, g->pair_items.num_short};
     in.pair_multi = {g->pair_items_multi.num_single, g->pair_items_multi.num_short};

@@ -66,6 +66,12 @@ inline void chunk_tiles(TilePlan& t, int max_chunks) {
     t.num_slots = slots;
 }
 
+// Chunks for each of `lists` lists of P rows that share `cus` compute units with a list of N rows.
+inline int pair_share(int64_t P, int64_t N, int cus, int lists) {
+    const int64_t rows = std::max<int64_t>(lists * P + N, 1);
+    return (int)std::min<int64_t>(std::max<int64_t>((P * cus + rows / 2) / rows, 1), std::max((cus - 1) / lists, 1));
+}
+
 inline TilePlan plan_tiles(const std::vector<int32_t>& seg_ptr, int tile_rows, int max_chunks = kMaxChunks) {
     TilePlan t;
     const int S = (int)seg_ptr.size() - 1;

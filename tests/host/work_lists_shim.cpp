@@ -43,6 +43,7 @@ int wl_tiles_field(int which, int32_t* out, int cap) {
 void wl_tiles_scalars(int32_t* out3) {
     out3[0] = g_tiles.num_chunks; out3[1] = g_tiles.num_slots; out3[2] = g_tiles.num_segs;
 }
+int wl_pair_share(long long P, long long N, int cus, int lists) { return rgnn::pair_share(P, N, cus, lists); }
 int wl_item_cut(long long total) { return rgnn::item_cut(total); }
 int wl_constant(int which) {
     const int c[] = {rgnn::kTileRows, rgnn::kMaxChunks, rgnn::kWideChunksPerCU, rgnn::kMinChunks, rgnn::kChunkTiles,

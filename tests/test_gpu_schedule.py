@@ -199,10 +199,11 @@ def test_hgt_unfolded_on_a_graph_that_could_fold(dtype, d):
     g.close()
 
 
-@pytest.mark.parametrize("layer,d,H", [("rgat", 64, 1), ("rgat", 64, 2), ("rgat", 32, 2), ("rgcn", 64, 1), ("hgt", 64, 4)])
+@pytest.mark.parametrize("layer,d,H", [("rgat", 64, 1), ("rgat", 64, 2), ("rgat", 32, 2), ("rgcn", 64, 1), ("hgt", 64, 4), ("hgt unfolded", 64, 4)])
 def test_chunks_of_many_relations(wl, layer, d, H):
-    """1,500 relations of one row tile each: the fp32 backward takes the shorter chunks (twice as many here), within the
-    workspace that is reported for them and with the oracle's results."""
+    """1,500 relations of one row tile each: the fp32 backward takes the shorter chunks (twice as many here), HGT with folded weights the
+    share of each list of the pairs in one chunk per compute unit, within the workspace that is reported for them and with the
+    oracle's results."""
     import torch
     from paper_2412_04747_amd import binding as B
     from paper_2412_04747_amd import harness as Hn
@@ -226,17 +227,20 @@ def test_chunks_of_many_relations(wl, layer, d, H):
     else:
         p = synth.hgt_params(rng, N, 1, R, d, H, with_mu=True)
         names = ("X", "Wk", "Wq", "Wv", "Wo", "Watt", "Wmsg", "mu")
-        L = Hn.HgtLayer(g, d, H)
+        L = Hn.HgtLayer(g, d, H, flags=B.RGNN_FLAG_NO_WEIGHT_FOLDING if layer == "hgt unfolded" else 0)
         L.load(*[p[k] for k in names], dOut=p["dOut"])
         want = O.hgt_bwd(N, src, dst, rel, None, *[p[k] for k in names], p["dOut"])
     ptr, cus = g.export("pair_ptr"), torch.cuda.get_device_properties(0).multi_processor_count
-    n = np.zeros((2, 3), np.int32)
-    for row, most in zip(n, (cus, wl.wl_constant(WL.K["wide_chunks"]) * cus)):
+    n = np.zeros((3, 3), np.int32)
+    wl.wl_pair_share.argtypes = [C.c_longlong, C.c_longlong, C.c_int, C.c_int]
+    for row, most in zip(n, (cus, wl.wl_constant(WL.K["wide_chunks"]) * cus, wl.wl_pair_share(g.P, N, cus, 2))):
         wl.wl_plan_tiles(ptr.ctypes.data_as(C.c_void_p), R, wl.wl_constant(WL.K["tile_rows"]), most)
         wl.wl_tiles_scalars(row.ctypes.data_as(C.c_void_p))
-    assert n[0, 0] < n[1, 0] and B.rgnn_schedule(g.handle, WL.LAYER[layer], L.desc)["wide_chunks"] == n[1, 0]
+    code = WL.LAYER[layer.split()[0]]
+    assert n[0, 0] < n[1, 0] and n[2, 0] < n[0, 0]
+    assert B.rgnn_schedule(g.handle, code, L.desc)["wide_chunks"] == n[2 if layer == "hgt" else 1, 0]
     L.fwd()
-    ws, L.ws = _guarded(B.rgnn_workspace_bytes(g.handle, WL.LAYER[layer], L.desc)[1])
+    ws, L.ws = _guarded(B.rgnn_workspace_bytes(g.handle, code, L.desc)[1])
     L.bwd()
     torch.cuda.synchronize()
     _intact(ws, "backward workspace")
