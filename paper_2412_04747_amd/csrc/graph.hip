@@ -56,35 +56,45 @@ rgnn_status_t resident_blocks_per_cu(const void* kernel, int threads, size_t lds
     return RGNN_OK;
 }
 
+// Host arrays to the device.  Several go into one allocation, and while they are small in one copy: an allocation and a copy
+// cost the same whatever their size, and a graph has over a hundred arrays (10k edges: 2.1 ms one by one, so 1.1).
 struct Uploader {
     rgnn_graph* g;
     rgnn_status_t st = RGNN_OK;
-    template <typename Tv>
-    Tv* up(const std::vector<Tv>& h) {
-        if (st != RGNN_OK) return nullptr;
+    struct Array { const std::vector<int32_t>* from; int32_t** to; };
+    void up(std::initializer_list<Array> list) { up(list.begin(), list.end()); }
+    void up(const Array* begin, const Array* end) {
+        constexpr size_t kOneCopy = 4 << 20;
+        if (st != RGNN_OK) return;
+        auto room = [](const Array& a) { return align_up(std::max<size_t>(a.from->size(), 1) * sizeof(int32_t)); };
+        size_t bytes = 0;
+        for (const Array* a = begin; a != end; ++a) bytes += room(*a);
         void* d = nullptr;
-        const size_t bytes = std::max<size_t>(h.size(), 1) * sizeof(Tv);
         hipError_t e = hipMalloc(&d, bytes);
         if (e != hipSuccess) {
             set_error("hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
             st = (e == hipErrorOutOfMemory) ? RGNN_ENOMEM : RGNN_EHIP;
-            return nullptr;
+            return;
         }
         g->allocs.push_back(d);
         g->index_bytes += bytes;
-        if (!h.empty()) {
-            e = hipMemcpy(d, h.data(), h.size() * sizeof(Tv), hipMemcpyHostToDevice);
-            if (e != hipSuccess) {
-                set_error("hipMemcpy H2D failed: %s", hipGetErrorString(e));
-                st = RGNN_EHIP;
-                return nullptr;
-            }
+        std::vector<char> one(bytes <= kOneCopy ? bytes : 0);
+        size_t off = 0;
+        for (const Array* a = begin; a != end; off += room(*a), ++a) {
+            *a->to = reinterpret_cast<int32_t*>(static_cast<char*>(d) + off);
+            const size_t n = a->from->size() * sizeof(int32_t);
+            if (n == 0) continue;
+            if (!one.empty()) memcpy(one.data() + off, a->from->data(), n);
+            else if (!copy(*a->to, a->from->data(), n)) return;
         }
-        return static_cast<Tv*>(d);
+        if (!one.empty()) copy(d, one.data(), bytes);
     }
-    void idx(int which, const std::vector<int32_t>& h) {
-        g->idx[which] = up(h);
-        g->idx_len[which] = (int64_t)h.size();
+    bool copy(void* d, const void* h, size_t n) {
+        const hipError_t e = hipMemcpy(d, h, n, hipMemcpyHostToDevice);
+        if (e == hipSuccess) return true;
+        set_error("hipMemcpy H2D failed: %s", hipGetErrorString(e));
+        st = RGNN_EHIP;
+        return false;
     }
 };
 
@@ -92,17 +102,21 @@ struct Uploader {
 struct Chunking { TileList* list; int max_chunks; };
 static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int tile_rows, std::initializer_list<Chunking> lists) {
     TilePlan p = plan_tiles(seg_ptr, tile_rows);
-    int32_t* const seg = U.up(p.tile_seg);
-    int32_t* const row0 = U.up(p.tile_row0);
-    int32_t* const row1 = U.up(p.tile_row1);
+    std::vector<TilePlan> chunked(lists.size());
+    int32_t *seg = nullptr, *row0 = nullptr, *row1 = nullptr;
+    std::vector<Uploader::Array> all{{&p.tile_seg, &seg}, {&p.tile_row0, &row0}, {&p.tile_row1, &row1}};
+    size_t i = 0;
     for (const Chunking& c : lists) {
         chunk_tiles(p, c.max_chunks);
         TileList& t = *c.list;
         t.tile_rows = p.tile_rows; t.num_tiles = p.num_tiles; t.num_chunks = p.num_chunks; t.num_slots = p.num_slots;
         t.num_segs = p.num_segs; t.max_seg_slots = p.max_seg_slots;
-        t.tile_seg = seg; t.tile_row0 = row0; t.tile_row1 = row1;
-        t.chunk_tile = U.up(p.chunk_tile); t.chunk_slot = U.up(p.chunk_slot); t.seg_slot_ptr = U.up(p.seg_slot_ptr);
+        TilePlan& k = chunked[i++];
+        k.chunk_tile.swap(p.chunk_tile); k.chunk_slot.swap(p.chunk_slot); k.seg_slot_ptr.swap(p.seg_slot_ptr);
+        all.insert(all.end(), {{&k.chunk_tile, &t.chunk_tile}, {&k.chunk_slot, &t.chunk_slot}, {&k.seg_slot_ptr, &t.seg_slot_ptr}});
     }
+    U.up(all.data(), all.data() + all.size());
+    for (const Chunking& c : lists) { c.list->tile_seg = seg; c.list->tile_row0 = row0; c.list->tile_row1 = row1; }
 }
 
 static void build_items(Uploader& U, ItemList& L, const std::vector<int32_t>& ptr, int max_len, int min_len = 0) {
@@ -110,17 +124,15 @@ static void build_items(Uploader& U, ItemList& L, const std::vector<int32_t>& pt
     L.num_items = (int32_t)p.beg.size(); L.num_partials = p.num_partials; L.num_split = p.num_split;
     L.first_single = p.first_single; L.num_single = p.num_single;
     L.first_short = p.first_short; L.num_short = p.num_short; L.num_wide = p.num_wide;
-    L.beg = U.up(p.beg); L.end = U.up(p.end); L.row = U.up(p.row); L.slot = U.up(p.slot);
-    L.split_row = U.up(p.split_row); L.split_ptr = U.up(p.split_ptr);
-    L.part_item = U.up(p.part_item); L.part_split = U.up(p.part_split);
     L.num_long = (int32_t)p.long_item.size();
-    L.long_item = U.up(p.long_item);
+    U.up({{&p.beg, &L.beg}, {&p.end, &L.end}, {&p.row, &L.row}, {&p.slot, &L.slot}, {&p.split_row, &L.split_row},
+          {&p.split_ptr, &L.split_ptr}, {&p.part_item, &L.part_item}, {&p.part_split, &L.part_split}, {&p.long_item, &L.long_item}});
 }
 
 static void build_long(Uploader& U, LongList& L, const std::vector<int32_t>& ptr) {
     const std::vector<int32_t> ids = long_segments(ptr);
     L.n = (int)ids.size();
-    L.ids = U.up(ids);
+    U.up({{&ids, &L.ids}});
 }
 
 static rgnn_status_t download(std::vector<int32_t>& h, const int32_t* d, size_t n) {
