@@ -10,14 +10,14 @@
 // The split holds for zero and for magnitudes from 2^-110, the least fp32 whose last bit, 2^-133, is a (subnormal) bf16, to
 // 3.38e38, the greatest whose bf16 is finite.  A unit of rows, or a weight's band of 32 rows or columns, with an operand
 // outside is multiplied with the fp32 matrix instructions, straight from global memory (a backward whose every unit goes that
-// way, 1.43M pairs: 1.9 ms for 0.7).  NaN needs no such care: its planes are NaN.  (A
+// way, RGCN, 1.43M pairs: 1.75 ms for 0.63).  NaN needs no such care: its planes are NaN.  (A
 // sum within 1 % of the largest float may overflow: the product of the high planes can be that much above it.)  Without the lower bound the error of dX and
 // dW, 1.1e-7 and 1.7e-7 in the range, was 2.2e-6 with one operand near 2^-116 and 3.5e-5 near 2^-120; the check costs 1.3 % of an
 // RGAT forward + backward on those pairs.
 //
 // Why: at width 128 a row costs 32 kflop per product against 1.5 KB of traffic, twice what the fp32 matrix cores do in the time
 // the rows need.  (RGAT's and RGCN's forward stay on those: the sign of a result selects a branch of their backward.)
-// 1.43M pairs of 60 relations: forward 0.52 -> 0.30 ms (4.8 TB/s), backward (two kernels before, dY read
+// 1.43M pairs of 60 relations: forward 0.42 -> 0.28 ms (5.2 TB/s), backward (two kernels before, dY read
 // twice) 1.18 -> 0.54 ms (4.1 TB/s; without its matrix instructions and stores, which mostly run beside the loading
 // wavefronts' chain of waits, splits and LDS writes, it would be 0.37).
 //
@@ -26,15 +26,18 @@
 // walk 139 -> 52 us; at 68k pairs 48 -> 50, 31 -> 26 and 14 -> 10.
 //
 // A workgroup takes a chunk of 64-row tiles in units of 32 rows, one workgroup per compute unit, its wavefronts specialised:
-//   4 load:     rows of unit u + 1 from registers (fetched two units ahead) split into planes in LDS
-//   4 multiply: dXrow = dY W^T (forward: Y = X W); a wavefront keeps 32 rows (columns) of W as planes in 96 registers and
-//               stores its columns of the result itself, in whole 128-byte lines (handed back through LDS to the loading
+//   4 load:     rows of unit u + 1 from registers (fetched two units ahead) split into planes in LDS; forward: result rows of
+//               unit u - 1 from LDS to memory, 512 bytes each
+//   4 multiply: dXrow = dY W^T (forward: Y = X W); a wavefront keeps 32 rows (columns) of W as planes in 96 registers.  Backward:
+//               it stores its columns of the result itself, in whole 128-byte lines (handed back through LDS to the loading
 //               wavefronts, whose chain the kernel waits for, the stores made the backward 0.61 ms with the rows of every
-//               pair in one tensor, 0.65 with the row selector; now 0.54 with it)
+//               pair in one tensor, 0.65 with the row selector; now 0.54 with it).  The forward, whose loading wavefronts have
+//               half the rows to split, is nearer to the memory's rate, and there whole rows win: HGT's forward at 4M edges, result
+//               rows 1 KB apart, 2.86 ms with stores by column band, so 2.66 (300 relations), 2.02 and 1.87 (60), at 300k edges the same
 //   4 multiply (backward only): the weight gradient X^T dY, whose row contraction reads the planes through the transposing
 //               LDS read ds_read_b64_tr_b16
-// The planes are double-buffered and one barrier per unit separates the stages, so that splitting and matrix
-// products of neighbouring units overlap (with all wavefronts going through the phases together the backward took
+// The planes (and the forward's result tiles) are double-buffered and one barrier per unit separates the stages, so that splitting
+// and matrix products of neighbouring units overlap (with all wavefronts going through the phases together the backward took
 // 0.70 ms at the sizes above, 15,400 clocks per 64 rows of which the matrix instructions are 6,100).
 // A plane is [32 rows][256 bytes], piece c (16 bytes) of row r at c ^ swz(r), as in the bf16 backward.
 #include "rgnn_internal.h"
@@ -52,6 +55,7 @@ typedef __attribute__((address_space(3))) v4s* lds_v4s;
 constexpr int D = 128;
 constexpr int UNIT = 32;                     // rows of a unit
 constexpr int PLANE = UNIT * 2 * D;          // bytes of one plane of a unit
+constexpr int STAGE = UNIT * 4 * D;          // bytes of a result tile (forward)
 constexpr float kSplitMax = 3.38e38f;        // largest magnitude whose bf16 rounding is finite
 constexpr unsigned kSplitMin = 17u << 23;    // bits of 2^-110: smallest magnitude above zero that three planes hold exactly
 
@@ -130,11 +134,16 @@ struct Loader {
     }
 };
 
-// One 32 x 32 block (rows of the unit x this wavefront's 32 columns) of rows times W, d[v] = result[row 8 (v / 4) + 4 kh +
-// v % 4][column m]: planes of the rows at `t`, of W in w; slow: from memory, with wp[k * WK] = W's operand and the row of lane
-// m as row_at() says (pointer and scale).
+// Rows of a result tile: [32][512 bytes], 16-byte piece p of row r at p ^ (r & 15).
+__device__ __forceinline__ float4* stage_at(unsigned char* st, int row, int piece) {
+    return reinterpret_cast<float4*>(st + row * 512 + ((piece ^ (row & 15)) << 4));
+}
+
+// One 32 x 32 block (rows of the unit x this wavefront's 32 columns) of rows times W: d[v] = result[row 8 (v / 4) + 4 kh +
+// v % 4][column m], or TRANS result[row m][column 8 (v / 4) + 4 kh + v % 4]; planes of the rows at `t`, of W in w; slow: from
+// memory, with wp[k * WK] = W's operand and the row of lane m as row_at() says (pointer and scale).
 struct RowAt { const float* p; float scale; };
-template <int WK, typename F>
+template <int WK, bool TRANS, typename F>
 __device__ __forceinline__ v16f multiply_rows(const unsigned char* t, const bf16x8 (&w)[3][8], int m, int kh, bool slow, const float* wp, F row_at) {
     v16f d, d1;                                            // two chains of matrix instructions
 #pragma unroll
@@ -154,7 +163,8 @@ __device__ __forceinline__ v16f multiply_rows(const unsigned char* t, const bf16
                     x[j][q] = *reinterpret_cast<const bf16x8*>(row + q * PLANE + (sw ^ ((s + j) << 5)));
                     ws[j][q] = w[q][s + j];
                 }
-            mfma_split2<1>(x[0], ws[0], d, x[1], ws[1], d1);
+            if (TRANS) mfma_split2<0>(ws[0], x[0], d, ws[1], x[1], d1);
+            else mfma_split2<1>(x[0], ws[0], d, x[1], ws[1], d1);
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) d[v] += d1[v];
@@ -171,7 +181,7 @@ __device__ __forceinline__ v16f multiply_rows(const unsigned char* t, const bf16
                 for (int e = 0; e < 16; ++e) wv[e] = wp[(size_t)(k + e) * WK];
             }
 #pragma unroll
-            for (int e = 0; e < 16; ++e) d = mfma32(xv[e] * x.scale, wv[e], d);
+            for (int e = 0; e < 16; ++e) d = TRANS ? mfma32(wv[e], xv[e] * x.scale, d) : mfma32(xv[e] * x.scale, wv[e], d);
         }
     }
     return d;
@@ -240,11 +250,12 @@ struct FwdArgs {
 };
 
 template <bool SCATTER>
-__device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* row_to, int* bad, int u0, int u1) {
+__device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     constexpr int DEPTH = 3;                               // units in flight per thread: 48 KB per compute unit
     const int tid = threadIdx.x & 255;
     const Loader ld(tid);
     Units units(a.t, u0 >> 1, u1 >> 1);
+    unsigned char* const St = lds + 2 * 3 * PLANE;
     // Rows are asked for DEPTH units before they are used, and their indices DEPTH units before that: loads complete in issue
     // order, so an index that is needed while newer rows are under way must be older than all rows that are not needed yet.
     float4 xr[DEPTH][4];
@@ -264,46 +275,61 @@ __device__ __forceinline__ void fwd_load(const FwdArgs& a, unsigned char* lds, i
     for (int p = 0; p < 2 * DEPTH; ++p) fetch_idx(p, u0 + p);
 #pragma unroll
     for (int p = 0; p < DEPTH; ++p) fetch(p, p);
-    auto step = [&](int p, int u) __attribute__((always_inline)) {
-        __syncthreads();
-        clear_flag(bad, u, tid);
-        // (every load of the loop is unconditional, past the end it repeats the last unit: were one skipped on some path,
-        // the waits would have to assume it everywhere and drain the rows under way)
-        {
-            const Unit n = units.get(min(u + 1, u1 - 1));
-            unsigned char* const t = lds + ((u + 1) & 1) * 3 * PLANE;
-            Range seen;
+    int gout[2][4];                                        // destination rows of the units u and u - 1
+#pragma unroll
+    for (int k = 0; k < 4; ++k) gout[0][k] = gout[1][k] = 0;
+    for (int ub = u0 - 1; ub <= u1; ub += 2 * DEPTH) {
+#pragma unroll
+        for (int p = 0; p < 2 * DEPTH; ++p) {
+            const int u = ub + p;
+            if (u > u1) break;
+            __syncthreads();
+            clear_flag(bad, u, tid);
+            if (u - 1 >= u0) {                             // result rows of the unit before
+                const Unit n = units.get(u - 1);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int r = ld.lr + 8 * k;
+                    const bool ok = r < n.rows;
+                    float4 y = *stage_at(St + ((u - 1) & 1) * STAGE, r, ld.c4);
+                    if (ok) {
+                        float* o = a.Y + (SCATTER ? (size_t)gout[1][k] : (size_t)(n.row0 + r)) * a.ldy + ld.c4 * 4;
+                        const rgnn_v4f yv = {y.x, y.y, y.z, y.w};
+                        __builtin_nontemporal_store(yv, reinterpret_cast<rgnn_v4f*>(o));
+                    }
+                }
+            }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (SCATTER && ld.c4 == 0) row_to[((u + 1) & 3) * UNIT + ld.lr + 8 * k] = gi[p][k];
-                ld.put(t, k, xr[p % DEPTH][k], ld.lr + 8 * k < n.rows, seen);
+                gout[1][k] = gout[0][k];
+                gout[0][k] = gi[p][k];
             }
-            if (seen.outside()) bad[(u + 1) & 3] = 1;
-            fetch_idx(p, u + 1 + 2 * DEPTH);
-            fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH));
+            // (every load of the loop is unconditional, past the end it repeats the last unit: were one skipped on some path,
+            // the waits would have to assume it everywhere and drain the rows under way)
+            {
+                const Unit n = units.get(min(u + 1, u1 - 1));
+                unsigned char* const t = lds + ((u + 1) & 1) * 3 * PLANE;
+                Range seen;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) ld.put(t, k, xr[p % DEPTH][k], ld.lr + 8 * k < n.rows, seen);
+                if (seen.outside()) bad[(u + 1) & 3] = 1;
+                fetch_idx(p, u + 1 + 2 * DEPTH);
+                fetch(p % DEPTH, (p + DEPTH) % (2 * DEPTH));
+            }
         }
-    };
-    // (whole rounds of the ring without an exit inside: see the backward)
-    int u = u0 - 1;
-    for (; u + 2 * DEPTH - 1 < u1; u += 2 * DEPTH) {
-#pragma unroll
-        for (int p = 0; p < 2 * DEPTH; ++p) step(p, u + p);
     }
-#pragma unroll
-    for (int p = 0; p < 2 * DEPTH - 1; ++p)
-        if (u + p < u1) step(p, u + p);
 }
 
-template <bool SCATTER>
-__device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* lds, const int* row_to, int* bad, int u0, int u1) {
+__device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
+    unsigned char* const St = lds + 2 * 3 * PLANE;
     Units units(a.t, u0 >> 1, u1 >> 1);
     bf16x8 w[3][8];
     int cur_seg = -1;
     bool wbad = false;
-    for (int u = u0 - 1; u < u1; ++u) {
+    for (int u = u0 - 1; u <= u1; ++u) {
         __syncthreads();
-        if (u < u0) continue;
+        if (u < u0 || u >= u1) continue;
         const Unit n = units.get(u);
         const float* const wp = a.W + (size_t)n.seg * D * D + band * 32 + m;
         if (n.seg != cur_seg) {
@@ -320,26 +346,26 @@ __device__ __forceinline__ void fwd_multiply(const FwdArgs& a, unsigned char* ld
         }
         if (n.rows <= 0) continue;
         const bool slow = wbad || bad[u & 3];
-        const v16f d = multiply_rows<D>(lds + (u & 1) * 3 * PLANE, w, m, kh, slow, wp, [&] {
+        const v16f d = multiply_rows<D, true>(lds + (u & 1) * 3 * PLANE, w, m, kh, slow, wp, [&] {
             return RowAt{a.X + (size_t)a.gather[n.row0 + min(m, n.rows - 1)] * D, 1.f};
         });
-        store_rows<SCATTER, false>(d, a.Y + (SCATTER ? 0 : (size_t)n.row0 * a.ldy) + band * 32 + m, n.rows, kh, a.ldy,
-                                   row_to + (u & 3) * UNIT, nullptr, 0.f);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *stage_at(St + (u & 1) * STAGE, m, band * 8 + 2 * q + kh) = make_float4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
     }
 }
 
 // X rows through the gather list; SCATTER: Y rows as well
 template <bool SCATTER>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_split_fwd_kernel(FwdArgs a) {
-    extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes
+    extern __shared__ __align__(16) unsigned char lds[];   // [2][3] planes, [2] result tiles
     __shared__ int bad[4];
-    __shared__ __align__(16) int row_to[4 * UNIT];         // destination rows of the units on their way
     const int u0 = 2 * a.t.chunk_tile[blockIdx.x], u1 = 2 * a.t.chunk_tile[blockIdx.x + 1];
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x >= 256) fwd_load<SCATTER>(a, lds, row_to, bad, u0, u1);
-    else fwd_multiply<SCATTER>(a, lds, row_to, bad, u0, u1);
+    if (threadIdx.x >= 256) fwd_load<SCATTER>(a, lds, bad, u0, u1);
+    else fwd_multiply(a, lds, bad, u0, u1);
 }
 
 // ------------------------------------------------------------------------------------------------ backward
@@ -511,7 +537,7 @@ __device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* ld
         }
         if (n.rows <= 0) continue;
         const bool slow = wbad || bad[u & 3];
-        const v16f d = multiply_rows<1>(lds + (u & 1) * BUF + 3 * PLANE, w, m, kh, slow, wp, [&] {
+        const v16f d = multiply_rows<1, false>(lds + (u & 1) * BUF + 3 * PLANE, w, m, kh, slow, wp, [&] {
             const int r = n.row0 + min(m, n.rows - 1);
             if (!SEL) return RowAt{a.dY + (size_t)(BOTH ? a.gather[r] : r) * a.ldd, 1.f};
             const int sl = a.ysel[r];
@@ -640,7 +666,7 @@ TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0,
 
 template <bool SCATTER>
 rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_t st) {
-    const size_t lds = 2 * 3 * PLANE;
+    const size_t lds = 2 * 3 * PLANE + 2 * STAGE;
     auto kern = typed_linear_split_fwd_kernel<SCATTER>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
