@@ -230,7 +230,7 @@ __device__ __forceinline__ float4 positive(float4 v) {
 // 16-byte loads; nd is a multiple of 32.  H > 1: wv[r][h][k], the same sum over head h's columns alone (one vector; the H vectors
 // of a relation are adjacent, so the walks that need all of them touch one short block).  Block blk of a share of a launch, 256
 // threads.
-__device__ __forceinline__ void fold_weight_block(const FoldArgs& f, int blk) {
+__device__ __forceinline__ void fold_weight_block(const FoldArgs& f, unsigned blk) {
     if (f.H > 1) {
         const int i = blk * 256 + threadIdx.x;             // (r, h, k)
         if (i >= f.H * f.R * f.kd) return;

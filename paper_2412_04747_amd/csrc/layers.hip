@@ -664,7 +664,7 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     if (!fused) { a.vec = static_cast<const float*>(w_s); a.s_out = w.s_src; }
     const int H = desc->heads;
     const FoldArgs fold = fold_args(g->R, K, D, H, Wf, static_cast<const float*>(w_t), w.wtp);      // step 2; in the same launch if there is one
-    const bool with_fold = fused && a.tiles->num_tiles > 0;
+    const bool with_fold = fused && a.tiles->num_tiles > 0 && fold_rides(fold);
     if (with_fold) a.fold = &fold;
     RGNN_TRY(typed_linear_fwd(K, D, a, st));
     // 2. destination half, once per (dst, rel) run, reordered: s_dst[q] = X[dst] . (W[r] w_t[r])  (per head: the head's columns)

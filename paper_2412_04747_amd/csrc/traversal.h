@@ -17,6 +17,9 @@ struct ScheduleFlagsScope {
 // columns of head h
 FoldArgs fold_args(int R, int kd, int nd, int H, const float* W, const float* w, float* wv, const float* w2 = nullptr, float* wv2 = nullptr);
 rgnn_status_t fold_weight(const FoldArgs& f, hipStream_t st);
+// Folds go into another kernel's launch while their workgroups leave most of the 2^32 lanes of a grid to that kernel, whose workgroups
+// may have 512 threads (it saves a launch of some microseconds; with as many folds as this one the launch takes milliseconds).
+inline bool fold_rides(const FoldArgs& f) { return f.blocks <= 1 << 22; }
 rgnn_status_t run_logit(const rgnn_graph* g, int D, const float* X, const float* wtp, float* s_dst, hipStream_t st);
 rgnn_status_t segment_scalar_sum(int n, const int32_t* ptr, const LongList& lng, const int32_t* via, const float* val,
                                  int stride, int off, float* out, hipStream_t st, const char* label, int min_len = 0,

@@ -1267,7 +1267,11 @@ rgnn_status_t run_logit(const rgnn_graph* g, int D, const float* X, const float*
 rgnn_status_t segment_scalar_sum(int n, const int32_t* ptr, const LongList& lng, const int32_t* via, const float* val,
                                  int stride, int off, float* out, hipStream_t st, const char* label, int min_len,
                                  int heads, bool long_only, int ostride, const FoldArgs* with_fold) {
-    const FoldArgs fold = with_fold ? *with_fold : FoldArgs{};
+    FoldArgs fold = with_fold ? *with_fold : FoldArgs{};
+    if (!fold_rides(fold)) {
+        RGNN_TRY(fold_weight(fold, st));
+        fold = FoldArgs{};
+    }
     if (fold.blocks > 0 && (fold.nd % 32 || (fold.H > 1 && fold.w2))) RGNN_FAIL(RGNN_EUNSUPPORTED, "segment_scalar_sum: this fold is not built");
     if (heads < 1 || (heads & (heads - 1))) RGNN_FAIL(RGNN_EUNSUPPORTED, "segment_scalar_sum: the head count must be a power of two, got %d", heads);
     if (n == 0 || (long_only && lng.n == 0)) return fold.blocks > 0 ? fold_weight(fold, st) : RGNN_OK;

@@ -399,3 +399,36 @@ def test_more_parameters_than_one_row_of_workgroups():
         g.close()
         del X, dO, W, ws, wt, out, dX, dW, dws, dwt, work, saved, got, part
         torch.cuda.empty_cache()
+
+
+@pytest.mark.timeout(300)
+def test_more_folded_weights_than_a_launch_of_512_threads_holds():
+    """2.1M relations of width 128, 137 GB of weights: the workgroups that fold them are more than 2^32 lanes hold at the 512 threads of the
+    forward product, with which they share a launch where they are fewer.  Forty relations have edges."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph
+    rng = np.random.default_rng(89)
+    N, E, used, R, d = 3000, 4000, 40, 2_097_200, 128
+    ids = np.sort(np.concatenate([[0, R - 1], rng.choice(np.arange(1, R - 1), used - 2, replace=False)]))
+    src, dst = rng.integers(0, N, E).astype(np.int32), rng.integers(0, N, E).astype(np.int32)
+    few = rng.integers(0, used, E).astype(np.int32)
+    p = synth.rgat_params(rng, N, used, d, d)
+    print(f"rgat case many folds: R={R} d={d}", flush=True)
+    g = Graph(N, R, src, dst, ids[few].astype(np.int32))
+    desc = B.make_desc(B.RGNN_F32, d, d, 1, 0.2)
+    f, _, s = B.rgnn_workspace_bytes(g.handle, B.RGNN_LAYER_RGAT, desc)
+    at = torch.as_tensor(ids, device="cuda")
+    def spread(a):
+        t = torch.zeros((R,) + a.shape[1:], device="cuda")
+        t[at] = torch.from_numpy(a).cuda()
+        return t
+    X, W, ws, wt = torch.from_numpy(p["X"]).cuda(), spread(p["W"]), spread(p["w_s"]), spread(p["w_t"])
+    out = torch.full((N, d), 7.0, device="cuda")
+    work, saved = (torch.zeros(n, dtype=torch.uint8, device="cuda") for n in (f, s))
+    B.rgnn_rgat_fwd(g.handle, desc, X, W, ws, wt, out, saved, work)
+    torch.cuda.synchronize()
+    check(out, O.rgat_fwd(N, src, dst, few, p["X"], p["W"], p["w_s"], p["w_t"]), TOL_F32, "out")
+    g.close()
+    del X, W, ws, wt, out, work, saved
+    torch.cuda.empty_cache()
