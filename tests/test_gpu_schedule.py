@@ -99,11 +99,12 @@ def test_rgcn_bf16_forced_alternatives(flags):
     g.close()
 
 
+@pytest.mark.parametrize("loop", [True, False])
 @pytest.mark.parametrize("k,d,norm,dtype", [(k, d, n, "f32") for k, d in ((32, 32), (64, 64), (32, 64), (64, 32))
                                             for n in ("in_degree_per_rel", "none")] +
                          [(d, d, "in_degree_per_rel", "bf16") for d in (32, 64)] +
                          [(128, 128, n, m) for n in ("in_degree_per_rel", "none") for m in ("f32", "f32 small")])
-def test_rgcn_row_select(k, d, norm, dtype):
+def test_rgcn_row_select(k, d, norm, dtype, loop):
     """fp32 rows: the rows of the single-edge pairs are read from the destinations' gradient rows.  Products and sums
     are those of the plain walk in the same order, so the gradients are the same bits; and they are the oracle's.  (small:
     some rows hold values below 2^-110, which take the fp32 matrix instructions at width 128.)"""
@@ -114,9 +115,9 @@ def test_rgcn_row_select(k, d, norm, dtype):
     rng, src, dst, rel, _ = _hub_graph(741 + k + d, N, R, E)
     rel[-1000:] = np.where(rel[-1000:] == 4, 3, rel[-1000:])
     print(f"schedule case rgcn row select {k}->{d} {norm} {dtype}", flush=True)
-    p = synth.rgcn_params(rng, N, R, k, d, self_loop=True)
+    p = synth.rgcn_params(rng, N, R, k, d, self_loop=loop)
     if dtype == "bf16":
-        p = {n: synth.round_to_bf16(v) for n, v in p.items()}
+        p = {n: v if v is None else synth.round_to_bf16(v) for n, v in p.items()}
     if dtype == "f32 small":
         dtype = "f32"
         p["dOut"][::101] *= np.float32(2.0 ** -114)
@@ -125,11 +126,12 @@ def test_rgcn_row_select(k, d, norm, dtype):
     wg = O.rgcn_bwd(N, src, dst, rel, p["X"], p["W"], p["W0"], p["dOut"], norm, "none", out=want)
     got = []
     for flags in (0, B.RGNN_FLAG_NO_ROW_SELECT):
-        L = RgcnLayer(g, d, norm, "none", True, dtype=dtype, flags=flags, d_in=k)
+        L = RgcnLayer(g, d, norm, "none", loop, dtype=dtype, flags=flags, d_in=k)
         assert B.rgnn_schedule(g.handle, B.RGNN_LAYER_RGCN, L.desc)["row_select"] == (flags == 0)
         L.load(p["X"], p["W"], p["W0"], p["dOut"])
         L.fwd(); L.bwd()
         torch.cuda.synchronize()
+        check(L.out, want, TOL_F32, "out")
         got.append({n: v.clone() for n, v in L.grads().items()})
         for n, v in L.grads().items():
             check(v, wg[n], TOL_F32, n)
