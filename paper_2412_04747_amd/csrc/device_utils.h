@@ -225,6 +225,17 @@ __device__ __forceinline__ float4 positive(float4 v) {
     return make_float4(v.x > 0.f ? v.x : 0.f, v.y > 0.f ? v.y : 0.f, v.z > 0.f ? v.z : 0.f, v.w > 0.f ? v.w : 0.f);
 }
 
+// bf16 rows of 128 columns in LDS: 16-byte piece c of row r sits at piece c ^ swz(r), 16 different values over 16 consecutive rows.
+__device__ __forceinline__ int swz(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// The transposing LDS read: operand "eight consecutive rows of this lane's feature", rows 0..3 at p, rows 4..7 at q.
+__device__ __forceinline__ bf16x8 tr8(const unsigned char* p, const unsigned char* q) {
+    typedef short v4s __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4s* lds_v4s;
+    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)p), b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)q);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // wv[r][k] = sum_n W[r][k][n] * w[r][n]      (linear operator reordering, Ch.3: x (W w) instead of (x W) w)
 // for one vector per relation or two (w2 / wv2 optional) in the same pass over W.  Eight lanes per weight row,
 // 16-byte loads; nd is a multiple of 32.  H > 1: wv[r][h][k], the same sum over head h's columns alone (one vector; the H vectors

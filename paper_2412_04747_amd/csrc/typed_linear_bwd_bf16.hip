@@ -24,9 +24,6 @@ namespace rgnn {
 namespace {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) v4s* lds_v4s;
 
 struct BwdArgs {
     const int32_t* tile_seg;
@@ -46,7 +43,6 @@ struct BwdArgs {
     float* part;
 };
 
-__device__ __forceinline__ int swz(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
 
 // eight bf16 (four packed pairs) times s, rounded to nearest even again
 __device__ __forceinline__ rgnn_v4u scale8(rgnn_v4u x, float s) {
@@ -54,11 +50,6 @@ __device__ __forceinline__ rgnn_v4u scale8(rgnn_v4u x, float s) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = bf16_pack2(__uint_as_float(x[e] << 16) * s, __uint_as_float(x[e] & 0xFFFF0000u) * s);
     return y;
-}
-// operand "eight consecutive rows of this lane's feature": rows 0..3 at p, rows 4..7 at q
-__device__ __forceinline__ bf16x8 tr8(const unsigned char* p, const unsigned char* q) {
-    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)p), b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)q);
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 //   NB     weights (dY rows are NB * 128 wide)        WPL    planes of W: 1 = bf16, 2 = fp32 split into hi + lo

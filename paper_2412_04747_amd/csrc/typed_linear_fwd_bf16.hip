@@ -19,9 +19,6 @@ namespace rgnn {
 namespace {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) v4s* lds_v4s;
 
 struct FwdArgs {
     const int32_t* tile_seg;
@@ -34,11 +31,6 @@ struct FwdArgs {
     void* Y;
 };
 
-__device__ __forceinline__ int swz(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
-__device__ __forceinline__ bf16x8 tr8(const unsigned char* p, const unsigned char* q) {
-    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)p), b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)q);
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 
 constexpr int D = 128, TILE = 64 * 2 * D, WT = D * 2 * D;      // bytes of 64 rows and of a weight
 

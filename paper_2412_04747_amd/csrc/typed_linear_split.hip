@@ -48,9 +48,6 @@ namespace rgnn {
 namespace {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) v4s* lds_v4s;
 
 constexpr int D = 128;
 constexpr int UNIT = 32;                     // rows of a unit
@@ -67,7 +64,6 @@ struct TileArgs {
     const int32_t* chunk_slot;
 };
 
-__device__ __forceinline__ int swz(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
 __device__ __forceinline__ float lo_half(unsigned u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float hi_half(unsigned u) { return __uint_as_float(u & 0xFFFF0000u); }
 // planes of the pair (a, b), packed
@@ -76,10 +72,6 @@ __device__ __forceinline__ void split2(float a, float b, unsigned (&p)[3]) {
     const float a1 = a - lo_half(p[0]), b1 = b - hi_half(p[0]);
     p[1] = bf16_pack2(a1, b1);
     p[2] = bf16_pack2(a1 - lo_half(p[1]), b1 - hi_half(p[1]));
-}
-__device__ __forceinline__ bf16x8 tr8(const unsigned char* p, const unsigned char* q) {
-    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)p), b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)q);
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 __device__ __forceinline__ v16f mfma16(bf16x8 a, bf16x8 b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ v16f mfma32(float a, float b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
