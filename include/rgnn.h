@@ -216,7 +216,8 @@ typedef struct {
                                     workgroup per compute unit, two for RGCN with rows_bf16, three for fp32 up to
                                     width 64 where the relations are short; with hgt_folded, in fp32 up to width 64, the
                                     share of one per compute unit that falls to each of the two lists of the pairs beside
-                                    the nodes' (RGCN's share beside a self-loop, which desc does not tell, is not in here) */
+                                    the nodes', except where short relations make such chunks uneven (RGCN's share beside
+                                    a self-loop, which desc does not tell, is not in here) */
     int32_t rows_bf16;           /* intermediate row tensors stored as bfloat16 */
     int32_t row_select;          /* single-edge pairs: gradient row read through the row selector, not materialised */
     int32_t hgt_folded;          /* HGT key / message linears folded into the per-relation weights */

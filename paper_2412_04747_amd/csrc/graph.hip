@@ -110,7 +110,7 @@ static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int ti
         chunk_tiles(p, c.max_chunks);
         TileList& t = *c.list;
         t.tile_rows = p.tile_rows; t.num_tiles = p.num_tiles; t.num_chunks = p.num_chunks; t.num_slots = p.num_slots;
-        t.num_segs = p.num_segs; t.max_seg_slots = p.max_seg_slots;
+        t.num_segs = p.num_segs; t.max_seg_slots = p.max_seg_slots; t.max_chunk_slots = p.max_chunk_slots;
         TilePlan& k = chunked[i++];
         k.chunk_tile.swap(p.chunk_tile); k.chunk_slot.swap(p.chunk_slot); k.seg_slot_ptr.swap(p.seg_slot_ptr);
         all.insert(all.end(), {{&k.chunk_tile, &t.chunk_tile}, {&k.chunk_slot, &t.chunk_slot}, {&k.seg_slot_ptr, &t.seg_slot_ptr}});

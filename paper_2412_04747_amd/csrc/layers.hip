@@ -260,11 +260,25 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // of the nodes are folded into the per-relation weights (Wf = Wk[type] Watt[r], Wv[type] Wmsg[r]), so
 // K, V and their gradients do not exist and the per-pair rows come straight from X.
 inline bool hgt_folded(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_hgt_folded(g->rel_src_tied, d->flags); }
-// folded path, fp32 rows up to width 64: the backwards of the two pair linears and of the query linear in one launch, also where
-// relations are short (see Chunkings): three launches less outweigh the chunks' unevenness.  Backward of the layer with one launch / a
-// launch each, width 64: 30 relations 100 / 123 us at 100k edges, 706 / 752 at 1.5M; 500 of equal frequency 292 / 297 at 20k, 583 / 644
-// at 400k; 1500 871 / 892 at 100k, 2005 / 2022 at 1.5M; width 32, 1500 relations 563 / 570 at 20k, 633 / 603 at 100k, 790 / 811 at 400k.
+// folded path, fp32 rows up to width 64: the backwards of the two pair linears and of the query linear in one launch.  Backward of the
+// layer with one launch / a launch each, width 64: 30 relations 100 / 123 us at 100k edges, 706 / 752 at 1.5M; 500 of equal frequency
+// 292 / 297 at 20k, 583 / 644 at 400k; 1500 871 / 892 at 100k, 2005 / 2022 at 1.5M.
 inline bool hgt_bwd_jobs(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return hgt_folded(g, d) && d->d_out <= 64; }
+// Its lists: one chunk per compute unit for all three; where relations are short (see Chunkings) and the chunks uneven, the lists of
+// launches of their own.  Backward of the layer, us, shares / own lists, width 64, Zipf 1.1: 800 relations 843 / 717 at 400k edges, 2000 1098
+// / 1087 at 100k, 2122 / 1676 at 1M, 4170 / 3586 at 4M; equal frequencies, whose chunks are even: 400 297 / 327 at 100k, 2000 1768 / 1821 at 1M.
+inline bool hgt_own_lists(const rgnn_graph_t* g, int D) {
+    const Chunkings c = pair_chunks(g, D);
+    return c.f32_bwd != c.cu1 && g->pair_tiles_hgt.uneven();
+}
+inline const TileList* hgt_pair_list(const rgnn_graph_t* g, int D) { return hgt_own_lists(g, D) ? pair_chunks(g, D).f32_bwd : &g->pair_tiles_hgt; }
+inline const TileList* hgt_node_list(const rgnn_graph_t* g, int D) { return hgt_own_lists(g, D) ? node_chunks(g, D).f32_bwd : &g->node_tiles_hgt; }
+// The forward's products of one launch: one chunk per compute unit and list, or three where relations are short and the chunks uneven or
+// many runs long.  Forward of the layer, us, one / three, width 64 (32), Zipf 1.1: 400 relations 97 / 91 (54 / 48) at 100k edges, 2000 620 / 472 (272
+// / 202) at 1M, 1710 / 1438 at 4M; equal frequencies: 400 78 / 84 (50 / 48) at 100k, 1500 149 / 147 (72 / 64), 2000 443 / 439 at 1M.
+inline const TileList* jobs_fwd_list(const Chunkings& c) {
+    return c.f32_bwd != c.cu1 && (c.cu1->uneven() || c.cu1->num_slots >= 6 * (int64_t)c.cu1->num_chunks) ? c.wide : c.cu1;
+}
 // KM holds the key row and the message row of a pair side by side; ms the (max, sum) of every (destination, head) softmax.
 struct HgtSaved { void* K; void* Q; void* V; void* Z; void* KM; float* ms; void* Wf_att; void* Wf_msg; };
 struct HgtFwdWs { float* Wbd_att; float* Wbd_msg; float* part_ms; float* partial; };
@@ -451,7 +465,7 @@ extern "C" rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, con
     in.item_len = item_cut(g->E); in.tile_chunks = pc.many->num_chunks;
     const bool rows16 = layer != RGNN_LAYER_RGAT && rows_bf16(desc);
     in.wide_chunks = (rows16 ? (layer == RGNN_LAYER_RGCN ? pc.cu2 : pc.cu1)
-                             : layer == RGNN_LAYER_HGT && hgt_bwd_jobs(g, desc) ? &g->pair_tiles_hgt : pc.f32_bwd)->num_chunks;
+                             : layer == RGNN_LAYER_HGT && hgt_bwd_jobs(g, desc) ? hgt_pair_list(g, desc->d_out) : pc.f32_bwd)->num_chunks;
     in.dst = {g->dst_items.num_single, g->dst_items.num_short};
     in.pair = {g->pair_items.num_single, g->pair_items.num_short};
     in.pair_multi = {g->pair_items_multi.num_single, g->pair_items_multi.num_short};
@@ -858,7 +872,7 @@ extern "C" rgnn_status_t rgnn_hgt_fwd(const rgnn_graph_t* g, const rgnn_layer_de
         int n = 0;
         for (const Product& p : list) {
             TypedLinearArgs& t = a[n++];
-            t.tiles = p.pairs ? pair_chunks(g, D).cu1 : node_chunks(g, D).cu1;
+            t.tiles = jobs_fwd_list(p.pairs ? pair_chunks(g, D) : node_chunks(g, D));
             t.X = static_cast<const float*>(p.in); t.gather = p.pairs ? psrc : perm; t.scatter_out = !p.pairs;
             t.W = static_cast<const float*>(p.w32); t.Y = static_cast<float*>(p.out); t.y_stride = p.pairs ? 2 : 1;
         }
@@ -965,11 +979,11 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
         if (hgt_bwd_jobs(g, desc)) {
             TypedLinearBwdArgs b[3] = {};
             for (int k = 0; k < 2; ++k) {
-                b[k].tiles = &g->pair_tiles_hgt; b[k].gather = psrc; b[k].W = static_cast<const float*>(k ? sv.Wf_msg : sv.Wf_att);
+                b[k].tiles = hgt_pair_list(g, D); b[k].gather = psrc; b[k].W = static_cast<const float*>(k ? sv.Wf_msg : sv.Wf_att);
                 b[k].dY = static_cast<const float*>(k ? dM : dKa); b[k].dy_stride = 2; b[k].dXrow = static_cast<float*>(k ? w.dVp : w.dKp);
                 b[k].dW = k ? w.dWf_msg : w.dWf_att; b[k].part = w.pair_part[k];
             }
-            b[2].tiles = &g->node_tiles_hgt; b[2].gather = perm; b[2].dy_gathered = b[2].scatter_dx = 1; b[2].W = Wq32;
+            b[2].tiles = hgt_node_list(g, D); b[2].gather = perm; b[2].dy_gathered = b[2].scatter_dx = 1; b[2].W = Wq32;
             b[2].dY = static_cast<const float*>(w.dQ); b[2].dXrow = w.dXq; b[2].dW = static_cast<float*>(dWq); b[2].part = w.node_part[1];
             for (TypedLinearBwdArgs& x : b) { x.X = static_cast<const float*>(Xr); x.sums = &sums; }
             RGNN_TRY(typed_linear_bwd_jobs(D, b, 3, "node_pair_linears_bwd", st));

@@ -60,6 +60,10 @@ struct TileList {
     int32_t* tile_row1 = nullptr;    // [num_tiles]  end row (exclusive; <= row0 + tile_rows)
     int32_t* chunk_tile = nullptr;   // [num_chunks+1]
     int32_t* chunk_slot = nullptr;   // [num_chunks]  first slot of the chunk
+    int32_t max_chunk_slots = 0;     // ... and of the chunk
+    // chunks of as many tiles but very different numbers of segments, each with its weight load (and flush): the chunks of the long
+    // relations are done early
+    bool uneven() const { return 2 * (int64_t)max_chunk_slots * num_chunks > 3 * (int64_t)num_slots; }
     int32_t* seg_slot_ptr = nullptr; // [num_segs+1]
 };
 

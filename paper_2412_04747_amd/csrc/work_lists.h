@@ -29,7 +29,7 @@ constexpr int kSerialMax = 32;      // longest segment a single lane walks; long
 // are the consecutive range [seg_slot_ptr[s], seg_slot_ptr[s + 1]).
 struct TilePlan {
     int32_t tile_rows = 0, num_tiles = 0, num_chunks = 0, num_slots = 0, num_segs = 0;
-    int32_t max_seg_slots = 0;                             // of a segment
+    int32_t max_seg_slots = 0, max_chunk_slots = 0;        // of a segment; of a chunk
     std::vector<int32_t> tile_seg, tile_row0, tile_row1;   // [num_tiles] segment, first row, end row
     std::vector<int32_t> chunk_tile;                       // [num_chunks + 1]
     std::vector<int32_t> chunk_slot;                       // [num_chunks] first slot of the chunk
@@ -47,6 +47,7 @@ inline void chunk_tiles(TilePlan& t, int max_chunks) {
     t.seg_slot_ptr.assign(S + 1, 0);
     std::vector<int32_t> seg_slots(std::max(S, 0), 0);
     int slots = 0;
+    t.max_chunk_slots = 0;
     for (int c = 0; c < nc; ++c) {
         t.chunk_tile[c] = (int32_t)((int64_t)nt * c / nc);
         t.chunk_tile[c + 1] = (int32_t)((int64_t)nt * (c + 1) / nc);
@@ -56,6 +57,7 @@ inline void chunk_tiles(TilePlan& t, int max_chunks) {
                 ++slots;
                 seg_slots[t.tile_seg[i]]++;
             }
+        t.max_chunk_slots = std::max(t.max_chunk_slots, slots - t.chunk_slot[c]);
     }
     t.max_seg_slots = 0;
     for (int s = 0; s < S; ++s) {

@@ -201,19 +201,22 @@ def test_hgt_unfolded_on_a_graph_that_could_fold(dtype, d):
     g.close()
 
 
-@pytest.mark.parametrize("layer,d,H", [("rgat", 64, 1), ("rgat", 64, 2), ("rgat", 32, 2), ("rgcn", 64, 1), ("hgt", 64, 4), ("hgt unfolded", 64, 4)])
+@pytest.mark.parametrize("layer,d,H", [("rgat", 64, 1), ("rgat", 64, 2), ("rgat", 32, 2), ("rgcn", 64, 1), ("hgt", 64, 4), ("hgt unfolded", 64, 4), ("hgt uneven", 64, 4)])
 def test_chunks_of_many_relations(wl, layer, d, H):
     """1,500 relations of one row tile each: the fp32 backward takes the shorter chunks (twice as many here), HGT with folded weights the
     share of each list of the pairs in one chunk per compute unit, within the workspace that is reported for them and with the
-    oracle's results."""
+    oracle's results.  (uneven: three of them have 400 tiles, and HGT takes the shorter chunks as well.)"""
     import torch
     from paper_2412_04747_amd import binding as B
     from paper_2412_04747_amd import harness as Hn
     from test_gpu_workspace_bounds import _guarded, _intact
-    N, R = 400, 1500
+    N, R = 25600 if layer == "hgt uneven" else 400, 1500
     rng = np.random.default_rng(1500 + d)
     rel = np.repeat(np.arange(R, dtype=np.int32), 4)
     src, dst = rng.integers(0, N, len(rel)).astype(np.int32), rng.integers(0, N, len(rel)).astype(np.int32)
+    if layer == "hgt uneven":
+        rel = np.concatenate([rel, np.repeat(np.arange(3, dtype=np.int32), N)])
+        src, dst = np.concatenate([src] + [np.arange(N)] * 3).astype(np.int32), np.concatenate([dst, rng.integers(0, N, 3 * N)]).astype(np.int32)
     g = Hn.Graph(N, R, src, dst, rel)
     if layer == "rgat":
         p = synth.rgat_params(rng, N, R, d, d)
