@@ -678,7 +678,12 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     if (!fused) { a.vec = static_cast<const float*>(w_s); a.s_out = w.s_src; }
     const int H = desc->heads;
     const FoldArgs fold = fold_args(g->R, K, D, H, Wf, static_cast<const float*>(w_t), w.wtp);      // step 2; in the same launch if there is one
-    const bool with_fold = fused && a.tiles->num_tiles > 0 && fold_rides(fold);
+    // At width 128 the product's LDS leaves a compute unit one workgroup of folds at a time: with many relations they are faster in a
+    // launch of their own, unless uneven chunks leave compute units idle.  Forward, us, shared / apart, equal frequencies: 200 relations
+    // 76 / 76 at 100k edges, 800 111 / 104, 2000 192 / 152, 566 / 538 at 1M; Zipf 1.1: 400 55 / 49 at 10k, 97 / 102 at 100k, 2000 803 / 824 at 1M.
+    // (With heads the folds read W by columns and are slow alone: 2000 relations 234 / 392 at 100k.)
+    const bool lone_folds = K == 128 && H == 1 && fold.blocks > 4 * g->num_cus && !a.tiles->uneven();
+    const bool with_fold = fused && a.tiles->num_tiles > 0 && fold_rides(fold) && !lone_folds;
     if (with_fold) a.fold = &fold;
     RGNN_TRY(typed_linear_fwd(K, D, a, st));
     // 2. destination half, once per (dst, rel) run, reordered: s_dst[q] = X[dst] . (W[r] w_t[r])  (per head: the head's columns)
