@@ -157,17 +157,17 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     RGNN_TRY(download(ntype_ptr, g->idx[RGNN_IDX_NTYPE_PTR], (size_t)g->T + 1));
     RGNN_TRY(download(run_ptr, g->idx[RGNN_IDX_RUN_PTR], (size_t)g->Q + 1));
     for (int64_t v = 0; v < g->N; ++v) g->max_in_degree = std::max<int64_t>(g->max_in_degree, in_ptr[v + 1] - in_ptr[v]);
-    // (only schedules of small graphs ask for it)
-    g->max_runs_per_node = g->Q;
-    if (g->Q <= 65536) {
-        g->max_runs_per_node = 0;
-        int64_t q = 0;
-        for (int64_t v = 0; v < g->N && q < g->Q; ++v) {
-            const int64_t first = q;
-            while (q < g->Q && run_ptr[q] < in_ptr[v + 1]) ++q;
-            g->max_runs_per_node = std::max(g->max_runs_per_node, q - first);
+    // (only schedules of small graphs ask for it: a destination's runs are dealt to eight half wavefronts in turn)
+    for (int64_t v = 0, q = 0; g->Q <= 131072 && v < g->N && q < g->Q; ++v) {
+        RunChain half[8];
+        for (int h = 0; q < g->Q && run_ptr[q] < in_ptr[v + 1]; ++q, h = (h + 1) % 8) {
+            half[h].runs += 1;
+            half[h].edges += run_ptr[q + 1] - run_ptr[q];
         }
+        for (const RunChain& c : half)
+            if (c.length() > g->longest_chain.length()) g->longest_chain = c;
     }
+    if (g->Q > 131072) g->longest_chain = RunChain{(int32_t)g->Q, (int32_t)g->E};
     for (int64_t p = 0; p < g->P; ++p) {
         g->max_pair_out_degree = std::max<int64_t>(g->max_pair_out_degree, out_ptr[p + 1] - out_ptr[p]);
         g->num_single_pairs += (out_ptr[p + 1] - out_ptr[p] == 1);

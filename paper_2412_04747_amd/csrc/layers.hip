@@ -498,7 +498,8 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     // (one launch: rows of out are written while others of X are still read, so an out that shares memory with X goes to the
     // general plan, which has read X by then unless there is a self-loop)
     if (!overlap(X, (size_t)g->N * desc->d_in * sizeof(float), out, (size_t)g->N * D * sizeof(float)) &&
-        sched_rgcn_small(desc->dtype, desc->d_in, D, W0 != nullptr, g->Q, g->N, g->max_in_degree, g->max_runs_per_node, desc->flags))
+        sched_rgcn_small(desc->dtype, desc->d_in, D, W0 != nullptr, g->Q, g->N, g->dst_items.num_split > 0, g->longest_chain.runs,
+                         g->longest_chain.edges, desc->flags))
         return rgcn_small_fwd(g, desc->d_in, D, X32, W32, W032, desc->norm == RGNN_NORM_IN_DEGREE_PER_REL, relu, static_cast<float*>(out), st);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
     RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,

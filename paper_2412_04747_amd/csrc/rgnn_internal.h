@@ -43,6 +43,11 @@ class KernelTimer {
 };
 
 // ---- work lists ----------------------------------------------------------
+// Runs that one of the eight half wavefronts of a destination takes one after the other (rgcn_small.hip), and their edges.
+struct RunChain {
+    int32_t runs = 0, edges = 0;
+    int64_t length() const { return edges + 32 * (int64_t)runs; }      // in edges: a run costs about as much as 32 of them
+};
 // Row tiles of a segmented row range (rows grouped by relation or node type),
 // cut into `num_chunks` contiguous chunks, one per persistent workgroup.  A
 // chunk owns one partial-gradient slot per distinct segment it touches; slots
@@ -55,15 +60,15 @@ struct TileList {
     int32_t num_slots = 0;
     int32_t num_segs = 0;
     int32_t max_seg_slots = 0;       // slots of the segment with the most
+    int32_t max_chunk_slots = 0;     // ... and of the chunk
+    // chunks of as many tiles but very different numbers of segments, each with its weight load (and flush): the chunks of the long
+    // relations are done early
+    bool uneven() const { return 2 * (int64_t)max_chunk_slots * num_chunks > 3 * (int64_t)num_slots; }
     int32_t* tile_seg = nullptr;     // [num_tiles]  device
     int32_t* tile_row0 = nullptr;    // [num_tiles]  first row of the tile
     int32_t* tile_row1 = nullptr;    // [num_tiles]  end row (exclusive; <= row0 + tile_rows)
     int32_t* chunk_tile = nullptr;   // [num_chunks+1]
     int32_t* chunk_slot = nullptr;   // [num_chunks]  first slot of the chunk
-    int32_t max_chunk_slots = 0;     // ... and of the chunk
-    // chunks of as many tiles but very different numbers of segments, each with its weight load (and flush): the chunks of the long
-    // relations are done early
-    bool uneven() const { return 2 * (int64_t)max_chunk_slots * num_chunks > 3 * (int64_t)num_slots; }
     int32_t* seg_slot_ptr = nullptr; // [num_segs+1]
 };
 
@@ -107,7 +112,7 @@ struct rgnn_graph {
     int32_t R = 0, T = 0;
     int num_cus = 0;                       // compute units of the device the graph lives on
     int64_t max_in_degree = 0, max_pair_out_degree = 0, num_single_pairs = 0;
-    int64_t max_runs_per_node = 0;         // of a destination (an upper bound above 65536 runs)
+    rgnn::RunChain longest_chain;          // (an upper bound above 131072 runs)
     size_t index_bytes = 0;
     int32_t* idx[RGNN_IDX_COUNT] = {};     // device arrays, see RGNN_IDX_*
     int64_t idx_len[RGNN_IDX_COUNT] = {};

@@ -57,22 +57,26 @@ inline bool sched_ws_in_lds(int R, int d) { return (size_t)R * d * sizeof(float)
 // RGCN forward of a small graph in one launch (rgcn_small.hip), which reads a weight per (relation, destination) run, and one per
 // node for the self-loop, where the general plan reads one per tile of rows; a workgroup per destination, whose eight half wavefronts
 // take its runs in turn, each run walked by one of them.  Two lines, both in the cost of a run (its product and its rows: linear in the
-// weight's and the row's length):
-//   throughput  runs and nodes (a workgroup's start and end cost as much as two runs).  One launch / general plan, us, without a
-//               self-loop: 32 x 32 7.9 / 12.9 at 1000 nodes and 5.7k runs, 9.7 / 11.4 at 4000 and 18k, 11.5 / 10.8 at 8192 and 15k, 16.6 /
-//               10.9 at 16k and 16k; 64 x 64 9.6 / 14.2 at 2000 and 6.9k, 15.3 / 12.6 at 4000 and 10k, 37 / 14 at 16k and 16k.  With one,
-//               whose launch and pass over out the general plan pays for: 32 x 32 12.3 / 13.8 at 8192 and 15k, 17.1 / 13.8 at 16k and
-//               8.4k; 64 x 64 16.5 / 18.5 at 4000 and 10k, 24 / 17 at 8192 and 7.1k, 35 / 17 at 16k and 500.
-//   latency     the longest chain, an eighth of a destination's runs and all its edges in one of them.  Eight destinations of n edges
-//               each, n relations: 32 x 32 11.7 / 15.3 at 64, 20 / 15 at 128; 64 x 64 11.6 / 15.1 at 32, 21 / 18 at 64, 91 / 18 at 256;
-//               one relation: 32 x 32 12.6 / 16.6 at 256, 17.4 / 16.6 at 384; 64 x 64 14.4 / 18.3 at 192, 25.6 / 18.6 at 384.
-inline bool sched_rgcn_small(int dtype, int d_in, int d, bool self_loop, int64_t runs, int64_t nodes, int64_t max_in_degree,
-                             int64_t max_runs_per_node, uint32_t flags) {
+// weight's and the row's length), and both further out where the general plan has more launches: destinations that it cuts into
+// pieces (17 us for 10 at 10k edges), a self-loop.
+//   throughput  runs and nodes (a workgroup's start and end cost as much as two runs).  One launch / general plan, us: no self-loop, nothing
+//               cut, 32 x 32 7.9 / 12.9 at 1000 nodes and 5.7k runs, 9.7 / 11.4 at 4000 and 18k, 11.5 / 10.8 at 8192 and 15k; 64 x 64 9.6 / 14.2 at
+//               2000 and 6.9k, 15.3 / 12.6 at 4000 and 10k; with cut destinations 32 x 32 15.4 / 19.4 at 4000 and 24k, 16.6 / 18.8 at 20k and 10k, 64
+//               x 64 22 / 22 at 6700 and 12k; with both 32 x 32 18.4 / 23.1 at 13k and 17k, 64 x 64 24.6 / 27.1 at 4000 and 10k, 27.6 / 25.4 at 10k
+//               and 5.7k.
+//   latency     the longest chain of a half wavefront (long ones belong to cut destinations).  Eight destinations of n edges, n relations: 32
+//               x 32 11.7 / 15.3 at 64 (chains of 8), 20 / 15 at 128; 64 x 64 11.6 / 15.1 at 32, 21 / 18 at 64.  Runs and edges of the chain:
+//               64 x 64 13.2 / 19 at 1 and 188, 18.1 / 19.9 at 5 and 117, 19.6 / 20.3 at 8 and 32; 32 x 32 18.7 / 16.8 at 15 and 23; with a
+//               self-loop 64 x 64 20.2 / 25.3 at 1 and 300, 22.8 / 23.5 at 9 and 16, 34 / 24.5 at 12 and 15.
+// Over 720 graphs of 1k to 40k edges, four pairs of widths, with and without a self-loop, the pick takes 0.6 % longer than the faster of the
+// two on average (always one launch 15 %, never 73 %).
+inline bool sched_rgcn_small(int dtype, int d_in, int d, bool self_loop, int64_t runs, int64_t nodes, bool cut, int64_t chain_runs,
+                             int64_t chain_edges, uint32_t flags) {
     if (dtype != RGNN_F32 || d_in > 64 || d > 64 || flag_set(flags, RGNN_FLAG_NO_BATCHED_WALKS)) return false;
     const int64_t kd = d_in * d, run = kd + 48 * d_in + 1024;
-    const int64_t most = self_loop ? 128000000 + 12000 * kd : 90000000 + 8000 * kd;
-    return (2 * runs + (self_loop ? 5 : 4) * nodes) * run <= 2 * most &&
-           (max_runs_per_node + 7) / 8 * run + max_in_degree * (7 * d_in / 2) <= 24000 + 400 * d_in;
+    const int64_t most = (self_loop ? 128000000 + 12000 * kd : 90000000 + 8000 * kd) * (cut ? 13 : 10) / 10;
+    const int64_t longest = self_loop ? 40800 + 680 * d_in : 33600 + 560 * d_in;
+    return (2 * runs + (self_loop ? 5 : 4) * nodes) * run <= 2 * most && chain_runs * run + chain_edges * (7 * d_in / 2) <= longest;
 }
 
 struct ListCounts { int32_t single = 0, short_ = 0; };   // whole segments with 1 / with 2..kShortLen entries

@@ -52,12 +52,12 @@ def test_config1_forward():
     _run(c["N"], c["R"], c["src"], c["dst"], c["rel"], c, 32, "in_degree_per_rel", "none", False, bwd=False, tag="C1")
 
 
-# 400 edges at one destination: more than the forward of a small graph in one launch takes, so the general plan runs
-@pytest.mark.parametrize("hub", [0, 400])
+# 700 edges of one relation at one destination: more than the forward of a small graph in one launch takes, so the general plan runs
+@pytest.mark.parametrize("hub", [0, 700])
 @pytest.mark.parametrize("d", [32, 64, 128])
 def test_forward_backward_all_options(d, hub):
     rng, src, dst, rel, _ = synth.tiny(40 + d, N=700, R=5, E=6000)
-    dst[:hub] = 6
+    dst[:hub], rel[:hub] = 6, 2
     p = synth.rgcn_params(rng, 700, 5, d, d, self_loop=True)
     one = d < 128 and hub == 0
     _run(700, 5, src, dst, rel, p, d, "in_degree_per_rel", "none", True, tag=f"d{d}", one_launch=one)
@@ -68,7 +68,7 @@ def test_forward_backward_all_options(d, hub):
 @pytest.mark.parametrize("d_in,d", [(32, 64), (64, 32)])
 def test_input_width_differs_from_output_width(d_in, d):
     rng, src, dst, rel, _ = synth.tiny(45 + d, N=700, R=5, E=6000)
-    dst[:800] = 9           # a hub cut into pieces
+    dst[:800], rel[:800] = 9, 2         # a hub cut into pieces
     p = synth.rgcn_params(rng, 700, 5, d_in, d, self_loop=True)
     _run(700, 5, src, dst, rel, p, d, "in_degree_per_rel", "none", True, tag=f"widths-{d_in}-{d}", d_in=d_in, one_launch=False)
     _run(700, 5, src, dst, rel, p, d, "none", "relu", True, tag=f"widths-{d_in}-{d}-loop-relu", d_in=d_in, one_launch=False)
@@ -78,10 +78,10 @@ def test_input_width_differs_from_output_width(d_in, d):
 @pytest.mark.parametrize("norm,act,loop", [("in_degree_per_rel", "none", False), ("none", "relu", True), ("in_degree_per_rel", "none", True)])
 @pytest.mark.parametrize("d_in,d", [(32, 32), (32, 64), (64, 32), (64, 64)])
 def test_small_graph_in_one_launch(d_in, d, norm, act, loop):
-    """Destinations with runs of 1, 8, 9, 31, 32, 33 and 100 edges, with 7, 8, 9, 16 and 17 runs (eight half wavefronts take a
+    """Destinations with runs of 1, 8, 9, 31, 32, 33 and 256 edges, with 7, 8, 9, 16 and 17 runs (eight half wavefronts take a
     destination's runs in turn), and without any."""
     rng = np.random.default_rng(d_in + 2 * d)
-    runs = [(v, 0, n) for v, n in enumerate((1, 8, 9, 31, 32, 33, 100))]
+    runs = [(v, 0, n) for v, n in enumerate((1, 8, 9, 31, 32, 33, 256))]
     for v, n in enumerate((7, 8, 9, 16, 17), start=20):
         runs += [(v, r, 1 + r % 3) for r in range(n)]
     N, R = 60, 20
@@ -95,12 +95,12 @@ def test_small_graph_in_one_launch(d_in, d, norm, act, loop):
 @pytest.mark.parametrize("d_in,d", [(32, 32), (32, 64), (64, 32), (64, 64)])
 def test_small_graph_with_rows_at_the_ends_of_the_range(d_in, d):
     """The one-launch forward of a small graph: rows of subnormal numbers, whose sums and products are whole multiples of 2^-29 that
-    24 bits hold (128 rows of at most 63 units, 64 products with weights of at most 7), so the result is exact; and rows of 1.5 * 2^127,
+    24 bits hold (256 rows of at most 63 units, 64 products with weights of at most 7), so the result is exact; and rows of 1.5 * 2^127,
     whose mean fp32 holds where their sum overflows."""
     import torch
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
     rng = np.random.default_rng(d_in + d)
-    lengths = [1, 2, 7, 8, 9, 31, 32, 33, 64, 127, 128]
+    lengths = [1, 2, 7, 8, 9, 31, 32, 33, 64, 255, 256]
     N, R = 40, 12                                          # nodes 20.. are the sources; destination 0 has all lengths, then one each
     runs = [(0, r, n) for r, n in enumerate(lengths) if n < 64] + [(1 + r, r, n) for r, n in enumerate(lengths)]
     dst = np.concatenate([np.full(n, v) for v, _, n in runs]).astype(np.int32)
@@ -153,14 +153,16 @@ def test_small_graph_whose_output_takes_the_place_of_its_input(d, shift):
 
 
 @pytest.mark.parametrize("k,loop,N,E,hub,rels,one", [
-    (32, False, 1000, 25397, 0, 0, True), (32, False, 1000, 25398, 0, 0, False),             # nodes and runs
+    (32, False, 4000, 19397, 0, 0, True), (32, False, 4000, 19398, 0, 0, False),             # nodes and runs
     (32, False, 13698, 1, 0, 0, True), (32, False, 13699, 1, 0, 0, False),
-    (64, True, 2000, 16625, 0, 0, True), (64, True, 2000, 16626, 0, 0, False),
+    (64, True, 4000, 11625, 0, 0, True), (64, True, 4000, 11626, 0, 0, False),
     (64, True, 8650, 0, 0, 0, True), (64, True, 8651, 0, 0, 0, False),
-    (32, False, 500, 300, 296, 1, True), (32, False, 500, 300, 297, 1, False),               # edges of one destination
-    (64, True, 500, 300, 184, 1, True), (64, True, 500, 300, 185, 1, False),
-    (32, False, 500, 300, 64, 64, True), (32, False, 500, 300, 65, 65, False),               # relations of one destination
-    (64, False, 500, 300, 40, 40, False), (64, False, 500, 300, 32, 32, True), (64, False, 500, 300, 256, 256, False)])
+    (32, False, 4000, 27576, 40, 40, True), (32, False, 4000, 27577, 40, 40, False),         # ... with a destination that is cut
+    (32, False, 500, 300, 428, 1, True), (32, False, 500, 300, 429, 1, False),               # edges of one destination
+    (64, True, 500, 300, 339, 1, True), (64, True, 500, 300, 340, 1, False),
+    (32, False, 500, 300, 400, 10, True),                                                    # ... in short runs
+    (32, False, 500, 300, 104, 104, True), (32, False, 500, 300, 105, 105, False),           # relations of one destination
+    (64, False, 500, 300, 64, 64, True), (64, False, 500, 300, 65, 65, False), (64, False, 500, 300, 256, 256, False)])
 def test_either_side_of_the_small_graph_rule(k, loop, N, E, hub, rels, one):
     """The largest graphs of the one-launch forward and the smallest beyond it: which plan runs, and its results."""
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
@@ -364,7 +366,7 @@ def test_operands_beyond_the_range_of_bfloat16(where, value):
     g.close()
 
 
-@pytest.mark.parametrize("hub", [0, 400])
+@pytest.mark.parametrize("hub", [0, 700])
 @pytest.mark.parametrize("N", [700, 701])
 @pytest.mark.parametrize("dtype,d", [("f32", 32), ("f32", 64), ("f32", 128), ("bf16", 32), ("bf16", 128)])
 def test_relu_mask_of_an_output_off_the_16_byte_grid(dtype, d, N, hub):
@@ -374,7 +376,7 @@ def test_relu_mask_of_an_output_off_the_16_byte_grid(dtype, d, N, hub):
     import torch
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
     rng, src, dst, rel, _ = synth.tiny(70 + d, N=N, R=5, E=6000)
-    dst[:hub] = 6
+    dst[:hub], rel[:hub] = 6, 2
     p = synth.rgcn_params(rng, N, 5, d, d, self_loop=True)
     g = Graph(N, 5, src, dst, rel)
     outs = {}
