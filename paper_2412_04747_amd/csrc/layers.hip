@@ -165,7 +165,7 @@ struct RgatBwdWs {
 };
 // RGAT with one head, and up to width 64 with two or four: the gradient rows of single-edge pairs are not written per
 // pair; the typed-linear backward reads att_e * dOut[dst_e] through its row selector.
-inline bool rgat_row_select(const rgnn_layer_desc_t* d) { return sched_row_select(RGNN_LAYER_RGAT, d->dtype, d->d_out, d->heads, 0, 0, d->flags); }
+inline bool rgat_row_select(const rgnn_layer_desc_t* d) { return sched_row_select(RGNN_LAYER_RGAT, d->dtype, d->d_out, d->heads, 0, 0, 0, d->flags); }
 inline bool rgat_edge_parallel(const rgnn_layer_desc_t* d) { return (d->flags & RGNN_FLAG_EDGE_PARALLEL_AGGREGATION) != 0; }
 inline bool rgat_fused(const rgnn_layer_desc_t* d) { return sched_fused_softmax(d->flags); }
 
@@ -460,7 +460,7 @@ extern "C" rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, con
     if (!out) RGNN_FAIL(RGNN_EINVAL, "out is NULL");
     ScheduleIn in;
     in.layer = layer; in.dtype = desc->dtype; in.d = desc->d_out; in.heads = layer == RGNN_LAYER_RGCN ? 1 : desc->heads;
-    in.flags = desc->flags; in.R = g->R; in.rel_src_tied = g->rel_src_tied;
+    in.flags = desc->flags; in.R = g->R; in.edges = g->E; in.rel_src_tied = g->rel_src_tied;
     const Chunkings pc = pair_chunks(g, desc->d_out);
     in.item_len = item_cut(g->E); in.tile_chunks = pc.many->num_chunks;
     const bool rows16 = layer != RGNN_LAYER_RGAT && rows_bf16(desc);
@@ -562,7 +562,7 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* ocoef = coef ? g->out_invc : nullptr;
     //    With the row selector the row of a pair with a single edge is not written per pair: the typed-linear backward
     //    reads dPre[dst_e] instead and multiplies it by 1/c_e on the way in.
-    const bool sel = sched_row_select(RGNN_LAYER_RGCN, desc->dtype, D, 1, g->R, g->pair_items.num_single, desc->flags);
+    const bool sel = sched_row_select(RGNN_LAYER_RGCN, desc->dtype, D, 1, g->R, g->E, g->pair_items.num_single, desc->flags);
     const int32_t* ysel = sel ? g->pair_ysel : nullptr;
     const void* y_alt = sel ? dPre : nullptr;
     const float* yscale = sel && coef ? g->pair_scale : nullptr;

@@ -35,11 +35,14 @@ inline bool sched_rows_bf16(int dtype, int d) { return dtype == RGNN_BF16 && d =
 // 10k, 75 / 76 at 100k (198 such pairs per relation), 141 / 155 at 400k; 2000 129 / 123 at 100k (50), 159 / 157 at 200k (99), 194 /
 // 208 at 400k (198); 4000 243 / 243 at 200k (50), 281 / 313 at 400k (99: the rows of the pairs no longer fit the caches); width 32, 4000 139
 // / 135 at 400k, 176 / 201 at 1M; width 128, where the loads run two units ahead, 500 51 / 50 at 10k, 61 / 63 at 30k, 2000 252 / 278 at 200k.
-inline bool sched_row_select(int layer, int dtype, int d, int heads, int R, int64_t single_pairs, uint32_t flags) {
+// Where most edges lie in other pairs: 4 relations, 200k edges, 10 % in such pairs 46.6 / 43.8 (width 64), 1M edges 126.7 / 127.4.
+inline bool sched_row_select(int layer, int dtype, int d, int heads, int R, int64_t edges, int64_t single_pairs, uint32_t flags) {
     if (flag_set(flags, RGNN_FLAG_NO_ROW_SELECT)) return false;
     if (layer == RGNN_LAYER_RGAT) return heads == 1 || (d <= 64 && (heads == 2 || heads == 4) && d % (4 * heads) == 0);
     if (layer == RGNN_LAYER_RGCN)
-        return sched_rows_bf16(dtype, d) || (single_pairs * d >= 640000 && (d == 128 || single_pairs >= 160 * (int64_t)R || single_pairs * d >= 24000000));
+        return sched_rows_bf16(dtype, d) ||
+               (single_pairs * d >= 640000 && (d == 128 || ((single_pairs >= 160 * (int64_t)R || single_pairs * d >= 24000000) &&
+                                                            (6 * single_pairs >= edges || single_pairs * d >= 4000000))));
     return false;
 }
 // HGT: the key and message linears of the nodes are folded into the per-relation weights when every relation's
@@ -84,6 +87,7 @@ struct ScheduleIn {
     int layer = 0, dtype = 0, d = 0, heads = 1;
     uint32_t flags = 0;
     int R = 1;
+    int64_t edges = 0;
     bool rel_src_tied = false;
     int item_len = 0, tile_chunks = 0, wide_chunks = 0;
     ListCounts dst, pair, pair_multi;     // destination-major list, pair-major list, pair-major list of multi-edge pairs
@@ -95,7 +99,7 @@ inline rgnn_schedule_t pick_schedule(const ScheduleIn& in) {
     s.tile_chunks = in.tile_chunks;
     s.wide_chunks = in.wide_chunks;
     s.rows_bf16 = sched_rows_bf16(in.dtype, in.d) && in.layer != RGNN_LAYER_RGAT;
-    s.row_select = sched_row_select(in.layer, in.dtype, in.d, in.heads, in.R, in.pair.single, in.flags);
+    s.row_select = sched_row_select(in.layer, in.dtype, in.d, in.heads, in.R, in.edges, in.pair.single, in.flags);
     s.hgt_folded = in.layer == RGNN_LAYER_HGT && sched_hgt_folded(in.rel_src_tied, in.flags);
     s.fused_softmax = in.layer == RGNN_LAYER_RGAT && sched_fused_softmax(in.flags);
     s.ws_in_lds = s.fused_softmax && sched_ws_in_lds(in.R, in.d);

@@ -57,7 +57,7 @@ int wl_constant(int which) {
 void wl_pick_schedule(const long long* in, int32_t* out) {
     rgnn::ScheduleIn s;
     s.layer = (int)in[0]; s.dtype = (int)in[1]; s.d = (int)in[2]; s.heads = (int)in[3]; s.flags = (uint32_t)in[4];
-    s.R = (int)in[5]; s.rel_src_tied = in[6] != 0; s.item_len = rgnn::item_cut(in[7]);
+    s.R = (int)in[5]; s.rel_src_tied = in[6] != 0; s.item_len = rgnn::item_cut(in[7]); s.edges = in[7];
     s.dst = {(int32_t)in[8], (int32_t)in[9]}; s.pair = {(int32_t)in[10], (int32_t)in[11]};
     s.pair_multi = {(int32_t)in[12], (int32_t)in[13]};
     const rgnn_schedule_t r = rgnn::pick_schedule(s);

@@ -288,12 +288,15 @@ def test_schedule_flags_force_the_alternatives(wl):
 
 
 @pytest.mark.parametrize("d,R,singles,want", [
-    (32, 7, 19999, 0), (32, 7, 20000, 1), (64, 7, 9999, 0), (64, 7, 10000, 1), (128, 7, 4999, 0), (128, 7, 5000, 1),
+    (64, 4, (19999, 120000), 0), (64, 4, (20000, 120000), 1), (32, 4, (124999, 1000000), 0), (32, 4, (125000, 1000000), 1),
+    (128, 4, (5000, 500000), 1),    (32, 7, 19999, 0), (32, 7, 20000, 1), (64, 7, 9999, 0), (64, 7, 10000, 1), (128, 7, 4999, 0), (128, 7, 5000, 1),
     (64, 500, 79999, 0), (64, 500, 80000, 1), (32, 2000, 319999, 0), (32, 2000, 320000, 1), (128, 2000, 100000, 1),
     (64, 4000, 374999, 0), (64, 4000, 375000, 1), (32, 8000, 749999, 0), (32, 8000, 750000, 1)])
 def test_row_selector_of_rgcn_where_it_pays(wl, d, R, singles, want):
-    """fp32 rows: enough single-edge pairs, and enough of them per relation or more rows than the caches hold."""
-    c = dict(layer="rgcn", dtype="f32", d_out=d, H=1, R=R, E=2 * singles)
+    """fp32 rows: enough single-edge pairs, enough of them per relation or more rows than the caches hold, and a sixth of the edges in
+    them or many (singles: their number, or that and the number of edges)."""
+    singles, edges = singles if isinstance(singles, tuple) else (singles, 2 * singles)
+    c = dict(layer="rgcn", dtype="f32", d_out=d, H=1, R=R, E=edges)
     k = dict(dst=(0, 0), pair=(singles, 0), pair_multi=(0, 0), tied=True)
     assert pick(wl, c, k)["row_select"] == want
     assert pick(wl, c, k, flags=4)["row_select"] == 0
