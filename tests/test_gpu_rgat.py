@@ -432,3 +432,26 @@ def test_more_folded_weights_than_a_launch_of_512_threads_holds():
     g.close()
     del X, W, ws, wt, out, work, saved
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("R,tiles,apart", [(200, 1, False), (400, 1, True), (400, 1000, False)])
+def test_folds_of_width_128_apart_from_the_product(R, tiles, apart):
+    """The weight folds of the forward share the product's launch, unless there are many and its chunks hold about as many relations
+    each (`tiles`: row tiles of relation 0, the others have one)."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    rng = np.random.default_rng(R + tiles)
+    N, d = 64 * max(tiles, 8), 128
+    rel = np.concatenate([np.repeat(np.arange(R), 3), np.zeros(64 * tiles - 3)]).astype(np.int32)
+    src = np.concatenate([rng.integers(0, N, 3 * R), np.arange(64 * tiles - 3)]).astype(np.int32)
+    dst = rng.integers(0, N, len(rel)).astype(np.int32)
+    p = synth.rgat_params(rng, N, R, d, d)
+    g = Graph(N, R, src, dst, rel)
+    L = RgatLayer(g, d)
+    L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    B.rgnn_profile_start()
+    L.fwd()
+    assert ("fold_weight" in B.rgnn_profile_stop()) == apart
+    check(L.out, O.rgat_fwd(N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"]), TOL_F32, "out")
+    g.close()
