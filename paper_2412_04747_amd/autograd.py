@@ -76,10 +76,11 @@ class _Rgcn(torch.autograd.Function):
         desc = B.make_desc(B.RGNN_F32, d_in, d, 1, 0.0,
                            B.RGNN_NORM_IN_DEGREE_PER_REL if norm == "in_degree_per_rel" else B.RGNN_NORM_NONE,
                            B.RGNN_ACT_RELU if act == "relu" else B.RGNN_ACT_NONE)
-        ws, _ = _bufs(graph, B.RGNN_LAYER_RGCN, desc, (d_in, d, norm, act))
+        ws, s = _bufs(graph, B.RGNN_LAYER_RGCN, desc, (d_in, d, norm, act))
         out = torch.empty(graph.N, d, device=X.device)
-        B.rgnn_rgcn_fwd(graph.handle, desc, X, W, W0, out, None, ws, _stream())
-        ctx.graph, ctx.desc, ctx.ws, ctx.has_w0 = graph, desc, ws, W0 is not None
+        saved = _buf(s) if s else None
+        B.rgnn_rgcn_fwd(graph.handle, desc, X, W, W0, out, saved, ws, _stream())
+        ctx.graph, ctx.desc, ctx.ws, ctx.saved_buf, ctx.has_w0 = graph, desc, ws, saved, W0 is not None
         ctx.save_for_backward(X, W, out, *([W0] if W0 is not None else []))
         return out
 
@@ -90,7 +91,7 @@ class _Rgcn(torch.autograd.Function):
         dOut = _f32(dOut)
         dX, dW = torch.empty_like(X), torch.empty_like(W)
         dW0 = torch.empty_like(W0) if W0 is not None else None
-        B.rgnn_rgcn_bwd(ctx.graph.handle, ctx.desc, X, W, W0, out, None, dOut, dX, dW, dW0, ctx.ws, _stream())
+        B.rgnn_rgcn_bwd(ctx.graph.handle, ctx.desc, X, W, W0, out, ctx.saved_buf, dOut, dX, dW, dW0, ctx.ws, _stream())
         return None, None, None, dX, dW, dW0
 
 

@@ -423,4 +423,85 @@ rgnn_status_t build_index_device(rgnn_graph* g, int format, const int32_t* a, co
     return RGNN_OK;
 }
 
+// ---- rows per run ------------------------------------------------------------------------
+namespace {
+
+__global__ void k_several(long long Q, const int32_t* idx, const int32_t* run_ptr, int32_t* flag) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= Q) return;
+    const int32_t q = idx ? idx[i] : (int32_t)i;
+    flag[i] = run_ptr[q + 1] - run_ptr[q] > 1;
+}
+// run i of the (relation, destination) order; incl: running counts of the runs with several edges in that order, num: in run order
+__global__ void k_run_rows(long long Q, const int32_t* relrun_idx, const int32_t* relrun_ptr, const int32_t* run_rel, const int32_t* run_ptr,
+                           const int32_t* run_dst, const int32_t* in_src, const int32_t* incl, const int32_t* num, int32_t* run_row,
+                           int32_t* row_in, int32_t* row_dst, int32_t* multi_end) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= Q) return;
+    const int32_t q = relrun_idx[i], r = run_rel[q], b = relrun_ptr[r], e = relrun_ptr[r + 1], beg = run_ptr[q];
+    const int32_t before = b > 0 ? incl[b - 1] : 0, several = incl[e - 1] - before, mine = incl[i] - before;
+    const bool multi = run_ptr[q + 1] - beg > 1;
+    const int32_t row = multi ? b + mine - 1 : b + several + ((int32_t)i - b - mine);
+    run_row[q] = row;
+    row_dst[row] = run_dst[q];
+    row_in[row] = multi ? (int32_t)((uint32_t)(num[q] - 1) | 0x80000000u) : in_src[beg];
+    if (i == b) multi_end[r] = b + several;
+}
+__global__ void k_pair_len(long long P, const int32_t* srcpair_idx, const int32_t* out_ptr, int32_t* len) {
+    const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < P) len[k] = out_ptr[srcpair_idx[k] + 1] - out_ptr[srcpair_idx[k]];
+}
+// first edge of pair p in the order by source
+__global__ void k_pair_start(long long P, const int32_t* srcpair_idx, const int32_t* len, const int32_t* incl, int32_t* start) {
+    const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < P) start[srcpair_idx[k]] = incl[k] - len[k];
+}
+__global__ void k_src_ptr(long long N, long long P, long long E, const int32_t* srcpair_ptr, const int32_t* srcpair_idx, const int32_t* start,
+                          int32_t* src_ptr) {
+    const long long u = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u <= N) src_ptr[u] = srcpair_ptr[u] < P ? start[srcpair_idx[srcpair_ptr[u]]] : (int32_t)E;
+}
+__global__ void k_src_edges(long long E, const int32_t* out_epos, const int32_t* out_ptr, const int32_t* in_pair, const int32_t* in_run,
+                            const int32_t* run_row, const int32_t* start, const float* in_invc, int32_t* src_row, float* src_invc) {
+    const long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= E) return;
+    const int32_t c = out_epos[j], p = in_pair[c], at = start[p] + ((int32_t)j - out_ptr[p]);
+    src_row[at] = run_row[in_run[c]];
+    src_invc[at] = in_invc[c];
+}
+
+}  // namespace
+
+// Fills g->run_row .. g->src_invc; src_ptr ([N + 1], edges by source) goes to the host.  E > 0.  Synchronous.
+rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr) {
+    const long long N = g->N, E = g->E, P = g->P, Q = g->Q;
+    Tmp a, b, c, d;
+    RGNN_TRY(a.alloc((size_t)std::max(P, Q) * sizeof(int32_t)));
+    RGNN_TRY(b.alloc((size_t)std::max(P, Q) * sizeof(int32_t)));
+    RGNN_TRY(c.alloc((size_t)std::max(P, Q) * sizeof(int32_t)));
+    RGNN_TRY(d.alloc(((size_t)N + 1) * sizeof(int32_t)));
+    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->run_row));
+    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_in));
+    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_dst));
+    RGNN_TRY(keep<int32_t>(g, (size_t)g->R, &g->multi_end));
+    RGNN_TRY(keep<int32_t>(g, (size_t)E, &g->src_row));
+    RGNN_TRY(keep<float>(g, (size_t)E, &g->src_invc));
+    RGNN_HIP(hipMemset(g->multi_end, 0, (size_t)g->R * sizeof(int32_t)));
+    LAUNCH(k_several, (size_t)Q, Q, (const int32_t*)nullptr, g->idx[RGNN_IDX_RUN_PTR], a.as<int32_t>());
+    RGNN_TRY(inclusive_scan(a.as<int32_t>(), b.as<int32_t>(), (size_t)Q));
+    LAUNCH(k_several, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RUN_PTR], a.as<int32_t>());
+    RGNN_TRY(inclusive_scan(a.as<int32_t>(), c.as<int32_t>(), (size_t)Q));
+    LAUNCH(k_run_rows, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RELRUN_PTR], g->idx[RGNN_IDX_RUN_REL], g->idx[RGNN_IDX_RUN_PTR],
+           g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_IN_SRC], c.as<int32_t>(), b.as<int32_t>(), g->run_row, g->row_in, g->row_dst, g->multi_end);
+    LAUNCH(k_pair_len, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], g->idx[RGNN_IDX_OUT_PTR], a.as<int32_t>());
+    RGNN_TRY(inclusive_scan(a.as<int32_t>(), b.as<int32_t>(), (size_t)P));
+    LAUNCH(k_pair_start, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], a.as<int32_t>(), b.as<int32_t>(), c.as<int32_t>());
+    LAUNCH(k_src_ptr, (size_t)N + 1, N, P, E, g->idx[RGNN_IDX_SRCPAIR_PTR], g->idx[RGNN_IDX_SRCPAIR_IDX], c.as<int32_t>(), d.as<int32_t>());
+    LAUNCH(k_src_edges, (size_t)E, E, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_PTR], g->idx[RGNN_IDX_IN_PAIR], g->idx[RGNN_IDX_IN_RUN],
+           g->run_row, c.as<int32_t>(), g->in_invc, g->src_row, g->src_invc);
+    src_ptr.resize((size_t)N + 1);
+    RGNN_HIP(hipMemcpy(src_ptr.data(), d.p, src_ptr.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    return RGNN_OK;
+}
+
 }  // namespace rgnn

@@ -147,6 +147,10 @@ inline Chunkings pair_chunks(const rgnn_graph_t* g, int width) {
 inline Chunkings node_chunks(const rgnn_graph_t* g, int width) {
     return chunkings(g->node_tiles, g->node_tiles_wide, g->node_tiles_cu2, g->node_tiles_cu1, width);
 }
+// rows per run instead of per pair
+inline Chunkings run_chunks(const rgnn_graph_t* g, int width) {
+    return chunkings(g->run_tiles, g->run_tiles_wide, g->run_tiles_cu2, g->run_tiles_cu1, width);
+}
 inline const rgnn::TileList* all_chunks(const rgnn_graph_t* g, int width) { return width == 128 ? &g->all_tiles_cu1 : &g->all_tiles; }
 // floats of scratch a backward typed linear needs on a list
 size_t tl_bwd_scratch(bool rows16, const Chunkings& t, int d_in, int d_out) {
@@ -220,18 +224,30 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 }
 
 // ---- RGCN buffers -----------------------------------------------------------------------
-struct RgcnFwdWs { void* Hs; float* partial; };
-struct RgcnBwdWs { void* dPre; float* dPre32; void* G; void* dXp; float* dX0; float* tl_part; float* loop_part; float* partial; float* acc_dW; float* acc_dW0; };
+// Rows per run: A[m] = the mean (sum) of the input rows of the m-th run with several edges, fp32, or with bf16 rows in two planes of bf16; Hs holds a message row per run.
+struct RgcnFwdWs { void* Hs; float* partial; float* A; };
+inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_use_run_rows(g->run_rows, RGNN_LAYER_RGCN, g->E, d->d_out, d->flags); }
+size_t carve_rgcn_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, float** A) {
+    Carver c(base);
+    if (rgcn_run_rows(g, d)) *A = c.take<float>((size_t)g->num_multi_runs * d->d_in);
+    return c.off;
+}
+struct RgcnBwdWs { float* A; void* dPre; float* dPre32; void* G; void* dXp; float* dX0; float* tl_part; float* loop_part; float* partial; float* acc_dW; float* acc_dW0; };
 
 size_t carve_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgcnFwdWs* w) {
     Carver c(base);
-    w->Hs = c.rows((size_t)g->P * d->d_out, rows_bf16(d));
-    w->partial = c.take<float>((size_t)g->dst_items.num_partials * d->d_out);
+    // (a call without `saved` may take either plan and has to keep A here)
+    const bool runs = rgcn_run_rows(g, d);
+    w->Hs = c.rows((size_t)(runs ? std::max(g->P, g->Q) : g->P) * d->d_out, rows_bf16(d));
+    w->partial = c.take<float>(std::max({(size_t)g->dst_items.num_partials * d->d_out, runs ? (size_t)g->dstrun_items.num_partials * d->d_out : 0,
+                                         runs ? (size_t)g->multi_run_items.num_partials * d->d_in : 0}));
+    w->A = runs ? c.take<float>((size_t)g->num_multi_runs * d->d_in) : nullptr;
     return c.off;
 }
 // RGCN with a self-loop, fp32 up to width 64: its backward runs with the pairs', where the pairs' chunks are one per compute unit
 // (see Chunkings; with many short relations they stay apart).
 inline bool rgcn_loop_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
+    if (rgcn_run_rows(g, d)) return d->d_in <= 64 && d->d_out <= 64 && run_chunks(g, d->d_out).f32_bwd == &g->run_tiles_cu1;
     return d->d_in <= 64 && d->d_out <= 64 && pair_chunks(g, d->d_out).f32_bwd == &g->pair_tiles_cu1;
 }
 size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgcnBwdWs* w) {
@@ -239,15 +255,18 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     const bool h = rows_bf16(d), relu = d->activation == RGNN_ACT_RELU;
     w->dPre = c.rows(relu ? (size_t)g->N * d->d_out : 0, h);
     w->dPre32 = c.take<float>(relu && h ? (size_t)g->N * d->d_out : 0);   // fp32 copy for the self-loop kernels
-    w->G = c.rows((size_t)g->P * d->d_out, h);
-    w->dXp = c.rows((size_t)g->P * d->d_in, h);
+    const bool runs = rgcn_run_rows(g, d);
+    w->G = runs ? nullptr : c.rows((size_t)g->P * d->d_out, h);
+    w->dXp = c.rows((size_t)(runs ? g->Q : g->P) * d->d_in, h);        // (a row per run or per pair)
+    w->A = runs ? c.take<float>((size_t)g->num_multi_runs * d->d_in) : nullptr;
     w->dX0 = c.take<float>((size_t)g->N * d->d_in);
     const bool with_loop = rgcn_loop_bwd(g, d);
-    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out),
-                                        with_loop ? typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->pair_tiles_loop) : 0));
+    w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, runs ? run_chunks(g, d->d_out) : pair_chunks(g, d->d_out), d->d_in, d->d_out),
+                                        with_loop ? typed_linear_bwd_scratch_floats(d->d_in, d->d_out, runs ? g->run_tiles_loop : g->pair_tiles_loop) : 0));
     w->loop_part = c.take<float>(std::max(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_cu1),
-                                          with_loop ? typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_loop) : 0));
-    w->partial = c.take<float>((size_t)g->pair_items.num_partials * d->d_out);
+                                          with_loop ? typed_linear_bwd_scratch_floats(d->d_in, d->d_out, runs ? g->all_tiles_run_loop : g->all_tiles_loop) : 0));
+    w->partial = c.take<float>(runs ? (size_t)std::max(g->src_items.num_partials, g->multi_run_items.num_partials) * d->d_in
+                                    : (size_t)g->pair_items.num_partials * d->d_out);
     const bool acc = grads_accumulate(d);
     w->acc_dW = acc ? c.take<float>((size_t)g->R * d->d_in * d->d_out) : nullptr;
     w->acc_dW0 = acc ? c.take<float>((size_t)d->d_in * d->d_out) : nullptr;
@@ -438,7 +457,8 @@ extern "C" rgnn_status_t rgnn_workspace_bytes(const rgnn_graph_t* g, int32_t lay
         RgcnFwdWs fw; RgcnBwdWs bw;
         f = carve_rgcn_fwd(g, desc, nullptr, &fw);
         b = carve_rgcn_bwd(g, desc, nullptr, &bw);
-        s = 0;
+        float* A;
+        s = carve_rgcn_saved(g, desc, nullptr, &A);
     } else {
         HgtFwdWs fw; HgtBwdWs bw; HgtSaved sv;
         f = carve_hgt_fwd(g, desc, nullptr, &fw);
@@ -475,10 +495,16 @@ extern "C" rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, con
 
 // =========================================================================== RGCN
 
+// A[m] = sum over the edges of the m-th run with several edges of X[src_e] / c, or of X[src_e]
+static rgnn_status_t rgcn_run_inputs(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, bool x16, float* A, float* partial, hipStream_t st) {
+    const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
+    return gather_sum(g->multi_run_items, desc->d_in, nullptr, g->idx[RGNN_IDX_IN_SRC], 0, coef, 1, 0, X, A, partial, st, 1, "run_inputs", "run_inputs.combine",
+                      1, x16, x16 ? 2 : 0);
+}
+
 extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X,
                                        const void* W, const void* W0, void* out, void* saved, void* workspace,
                                        void* stream) {
-    (void)saved;
     RGNN_TRY(check_desc(g, desc, RGNN_LAYER_RGCN));
     ScheduleFlagsScope sched_scope(desc->flags);
     if (missing(g, X) || !W || missing(g, out)) RGNN_FAIL(RGNN_EINVAL, "X, W or out is NULL");
@@ -501,13 +527,32 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
         sched_rgcn_small(desc->dtype, desc->d_in, D, W0 != nullptr, g->Q, g->N, g->dst_items.num_split > 0, g->longest_chain.runs,
                          g->longest_chain.edges, desc->flags))
         return rgcn_small_fwd(g, desc->d_in, D, X32, W32, W032, desc->norm == RGNN_NORM_IN_DEGREE_PER_REL, relu, static_cast<float*>(out), st);
-    // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
-    RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
-                    desc->d_in, 1, true));
-    // 2. out[v] = sum_e (1/c) Hs[pair_e]
-    const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
-    RGNN_TRY(gather_sum(g->dst_items, D, nullptr, g->idx[RGNN_IDX_IN_PAIR], 0, coef, 1, 0, w.Hs, out, w.partial, st, 0,
-                        "aggregate_fwd", "aggregate_fwd.combine", 1, h, 0));
+    if (rgcn_run_rows(g, desc) && (saved || sched_run_rows_infer(h, g->E, D))) {
+        // The sum over a run's edges comes before the product: a row of messages per run, not per pair, and a run with one edge reads its
+        // source's row directly.
+        float* A = w.A;
+        if (saved) (void)carve_rgcn_saved(g, desc, saved, &A);
+        RGNN_TRY(rgcn_run_inputs(g, desc, h ? X : static_cast<const void*>(X32), h, A, w.partial, st));
+        if (h) {
+            TypedLinearFwdBf16Args a{&g->run_tiles_cu2, X, g->row_in, 0, W, nullptr, w.Hs, "typed_linear_fwd"};
+            a.A2 = A; a.planes_end = g->multi_end;
+            RGNN_TRY(typed_linear_fwd_bf16(a, st));
+        } else {
+            TypedLinearArgs a{};
+            a.tiles = run_chunks(g, D).f32; a.X = X32; a.X2 = A; a.gather = g->row_in; a.W = W32; a.Y = static_cast<float*>(w.Hs); a.sign_matters = 1;
+            RGNN_TRY(typed_linear_fwd(desc->d_in, D, a, st));
+        }
+        RGNN_TRY(gather_sum(g->dstrun_items, D, nullptr, g->run_row, 0, nullptr, 1, 0, w.Hs, out, w.partial, st, 0, "aggregate_fwd", "aggregate_fwd.combine",
+                            1, h, 0));
+    } else {
+        // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
+        RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
+                        desc->d_in, 1, true));
+        // 2. out[v] = sum_e (1/c) Hs[pair_e]
+        const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
+        RGNN_TRY(gather_sum(g->dst_items, D, nullptr, g->idx[RGNN_IDX_IN_PAIR], 0, coef, 1, 0, w.Hs, out, w.partial, st, 0,
+                            "aggregate_fwd", "aggregate_fwd.combine", 1, h, 0));
+    }
     // 3. self-loop: out += X W0, and the activation on the way out (a pass of its own over out took 16.5 us at 120k
     //    nodes of width 64; without a self-loop it still is one)
     if (W0) {
@@ -524,7 +569,6 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
                                        const void* W, const void* W0, const void* out, const void* saved,
                                        const void* dOut, void* dX, void* dW, void* dW0, void* workspace,
                                        void* stream) {
-    (void)saved;
     RGNN_TRY(check_desc(g, desc, RGNN_LAYER_RGCN));
     ScheduleFlagsScope sched_scope(desc->flags);
     if (missing(g, X) || !W || missing(g, dOut) || missing(g, dX) || !dW) RGNN_FAIL(RGNN_EINVAL, "a required tensor pointer is NULL");
@@ -556,7 +600,16 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
         dPre = w.dPre;
         dPre32 = both ? w.dPre32 : h ? nullptr : static_cast<const float*>(w.dPre);
     }
-    // 1. dHs[p] = sum_{e in out(p)} (1/c_e) dPre[dst_e]
+    const bool runs = rgcn_run_rows(g, desc);
+    const float* A = w.A;
+    if (runs && saved) {
+        float* kept = nullptr;
+        (void)carve_rgcn_saved(g, desc, const_cast<void*>(saved), &kept);
+        A = kept;
+    } else if (runs) {
+        RGNN_TRY(rgcn_run_inputs(g, desc, h ? X : static_cast<const void*>(X32), h, w.A, w.partial, st));
+    }
+    // 1. dHs[p] = sum_{e in out(p)} (1/c_e) dPre[dst_e]     (rows per run: the row of run q is dPre[dst_q])
     const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
     //    (coefficients from the pair-major copy, so no per-edge indirection is left)
     const float* ocoef = coef ? g->out_invc : nullptr;
@@ -566,21 +619,37 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     const int32_t* ysel = sel ? g->pair_ysel : nullptr;
     const void* y_alt = sel ? dPre : nullptr;
     const float* yscale = sel && coef ? g->pair_scale : nullptr;
-    RGNN_TRY(gather_sum(sel ? g->pair_items_multi : g->pair_items, D, nullptr, g->idx[RGNN_IDX_OUT_DST], 0, ocoef, 1, 0, dPre, w.G,
-                        w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", 1, h, h));
+    if (!runs)
+        RGNN_TRY(gather_sum(sel ? g->pair_items_multi : g->pair_items, D, nullptr, g->idx[RGNN_IDX_OUT_DST], 0, ocoef, 1, 0, dPre, w.G,
+                            w.partial, st, 1, "aggregate_bwd_pair", "aggregate_bwd_pair.combine", 1, h, h));
     // 2. per pair dXp = dHs W^T; dW[r] = sum X^T dHs (its shares are added with those of the self-loop)
     ShareSums sums;
     // 3. self-loop: dX0 = dPre W0^T, dW0 = X^T dPre
     TypedLinearBwdArgs s{};
     s.tiles = &g->all_tiles_cu1; s.X = X32; s.W = W032; s.dY = dPre32;
     s.dXrow = w.dX0; s.dW = static_cast<float*>(dW0); s.part = w.loop_part; s.label = "self_loop_bwd"; s.sums = &sums;
+    TypedLinearBwdArgs b{};
+    b.X = X32; b.W = W32; b.dXrow = static_cast<float*>(w.dXp); b.dW = static_cast<float*>(dW); b.part = w.tl_part; b.sums = &sums;
+    if (runs) {
+        b.X2 = A; b.gather = g->row_in; b.dY = static_cast<const float*>(dPre); b.ysel = g->row_dst;
+    } else {
+        b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.dY = static_cast<const float*>(w.G); b.ysel = ysel; b.dY_alt = static_cast<const float*>(y_alt); b.yscale = yscale;
+    }
     if (W0 && rgcn_loop_bwd(g, desc)) {
-        TypedLinearBwdArgs b{};
-        b.tiles = &g->pair_tiles_loop; b.X = X32; b.gather = g->idx[RGNN_IDX_PAIR_SRC]; b.W = W32; b.dY = static_cast<const float*>(w.G);
-        b.dXrow = static_cast<float*>(w.dXp); b.dW = static_cast<float*>(dW); b.part = w.tl_part; b.sums = &sums;
-        b.ysel = ysel; b.dY_alt = static_cast<const float*>(y_alt); b.yscale = yscale;
-        s.tiles = &g->all_tiles_loop;
+        b.tiles = runs ? &g->run_tiles_loop : &g->pair_tiles_loop;
+        s.tiles = runs ? &g->all_tiles_run_loop : &g->all_tiles_loop;
         RGNN_TRY(typed_linear_bwd_loop(K, D, b, s, st));
+    } else if (runs) {
+        if (h) {
+            TypedLinearBwdBf16Args c{};
+            c.tiles = &g->run_tiles_cu2; c.X = X; c.A2 = A; c.gather = g->row_in; c.W = W; c.w_bf16 = 1;
+            c.dY = dPre; c.ysel = g->row_dst; c.dXrow = w.dXp; c.dW = static_cast<float*>(dW); c.part = w.tl_part; c.label = "typed_linear_bwd"; c.sums = &sums;
+            RGNN_TRY(typed_linear_bwd_bf16(D, c, st));
+        } else {
+            b.tiles = run_chunks(g, D).f32_bwd;
+            RGNN_TRY(typed_linear_bwd(K, D, b, st));
+        }
+        if (W0) RGNN_TRY(typed_linear_bwd(K, D, s, st));
     } else {
         RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
                         w.dXp, h, static_cast<float*>(dW), w.tl_part, "typed_linear_bwd", st, false, ysel, y_alt, yscale, K, 1, &sums));
@@ -591,7 +660,11 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* extra = W0 ? w.dX0 : nullptr;
     if (acc && W0) RGNN_TRY(add_into((size_t)g->N * K, static_cast<const float*>(dX), w.dX0, st));
     else if (acc) extra = static_cast<const float*>(dX);
-    RGNN_TRY(node_grad_sum(g, K, w.dXp, nullptr, nullptr, extra, dX, st, h, 0));
+    if (runs)      // over u's edges: the row of the edge's run, times 1/c
+        RGNN_TRY(gather_sum(g->src_items, K, nullptr, g->src_row, 0, coef ? g->src_invc : nullptr, 1, 0, w.dXp, dX, w.partial, st, 3, "node_grad_sum",
+                            "node_grad_sum.combine", 1, h, 0, nullptr, extra));
+    else
+        RGNN_TRY(node_grad_sum(g, K, w.dXp, nullptr, nullptr, extra, dX, st, h, 0));
     return ga.flush(st);
 }
 

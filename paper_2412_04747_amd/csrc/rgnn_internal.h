@@ -144,6 +144,21 @@ struct rgnn_graph {
     bool rel_src_tied = false;             // every relation's sources are of one node type (rel_src_type is then valid)
     rgnn::ItemList relrun_items;           // runs by relation
     rgnn::ItemList relpair_items;          // pairs by relation (rows of the compact tensors are already in this order)
+    // Rows per (destination, relation) run instead of per (source, relation) pair (run_rows; schedule.h).  The rows are in (relation,
+    // several edges before one, destination) order.
+    bool run_rows = false;
+    int64_t num_multi_runs = 0, num_single_runs = 0;
+    int32_t* run_row = nullptr;            // [Q] row of a run
+    int32_t* row_in = nullptr;             // [Q] by row: source of the run's only edge, or the top bit | number of the run among those
+                                           // with several edges, in run order
+    int32_t* row_dst = nullptr;            // [Q] by row: destination
+    int32_t* multi_end = nullptr;          // [R] end of a relation's rows of runs with several edges
+    int32_t* src_row = nullptr;            // [E] by (source, relation, CSR position): row of the edge's run
+    float* src_invc = nullptr;             // [E] 1 / c_{v,r} of that edge
+    rgnn::TileList run_tiles, run_tiles_wide, run_tiles_cu2, run_tiles_cu1, run_tiles_loop, all_tiles_run_loop;   // as those of the pairs
+    rgnn::ItemList multi_run_items;        // CSR edges of the runs with several edges (row: their number)
+    rgnn::ItemList dstrun_items;           // runs by destination
+    rgnn::ItemList src_items;              // edges by source
     rgnn::LongList long_runs;              // runs (run_ptr) too long for one lane
     rgnn::LongList long_pairs;             // pairs (out_ptr) too long for one lane
     std::vector<void*> allocs;             // every device allocation, for destroy
@@ -178,6 +193,7 @@ struct TypedLinearArgs {
     int y_stride = 1;        // rows of Y are y_stride * d_out floats apart (1 or 2)
     int relu = 0;            // with accumulate: Y = max(Y + result, 0)
     const FoldArgs* fold = nullptr;   // folds weights in the same launch (gathered rows, no scatter, accumulate or vec)
+    const float* X2 = nullptr;        // gather[i] < 0: row i reads X2[gather[i] & 0x7FFFFFFF] (plain products of gathered rows)
     int sign_matters = 0;    // 1: a backward takes a branch on the sign of what becomes of Y (leaky ReLU; ReLU, also the caller's own)
 };
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st);
@@ -233,6 +249,7 @@ struct TypedLinearBwdArgs {
     const float* hcoef = nullptr;    // [rows][2][sel_heads]
     const float* wvec = nullptr;     // [segs][ND]
     int sel_heads = 0;
+    const float* X2 = nullptr;       // gather[i] < 0: row i of X is X2[gather[i] & 0x7FFFFFFF]; row i of dY is dY[ysel[i]] (no dY_alt)
     int dy_stride = 1;               // rows of dY are dy_stride * d_out floats apart (1 or 2)
     ShareSums* sums = nullptr;       // the slots are left to the caller's sums (part then has to last until they are launched)
 };
@@ -255,6 +272,10 @@ rgnn_status_t typed_linear_bf16(int d, const TypedLinearBf16Args& a, hipStream_t
 // (X[gather[i]] W[seg], X[gather[i]] W2[seg]) in rows 256 wide
 struct TypedLinearFwdBf16Args {
     const TileList* tiles; const void* X; const int32_t* gather; int scatter_out; const void* W; const void* W2; void* Y; const char* label;
+    // gather[i] < 0: row i is row gather[i] & 0x7FFFFFFF of A2, whose rows are two bf16 planes (256 + 256 bytes); within a segment these
+    // come first, up to row planes_end[seg] (one weight)
+    const void* A2 = nullptr;
+    const int32_t* planes_end = nullptr;
 };
 rgnn_status_t typed_linear_fwd_bf16(const TypedLinearFwdBf16Args& a, hipStream_t st);
 
@@ -281,6 +302,7 @@ struct TypedLinearBwdBf16Args {
     const int32_t* ysel = nullptr;
     const void* dY_alt = nullptr;
     const float* yscale = nullptr;
+    const void* A2 = nullptr;    // gather[i] < 0: row i of X is the first plane of row gather[i] & 0x7FFFFFFF of A2; row i of dY is dY[ysel[i]] (no dY_alt)
     ShareSums* sums = nullptr;   // as in TypedLinearBwdArgs
 };
 rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipStream_t st);

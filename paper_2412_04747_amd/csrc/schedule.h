@@ -45,6 +45,25 @@ inline bool sched_row_select(int layer, int dtype, int d, int heads, int R, int6
                                                             (6 * single_pairs >= edges || single_pairs * d >= 4000000))));
     return false;
 }
+// Rows per (destination, relation) run instead of per (source, relation) pair.  Where destinations are popular and sources are not, a graph
+// has fewer runs than pairs; summing a run's inputs before the product, and multiplying a run's gradient row once, then moves fewer
+// rows: 2 E + 7 Q - 2 Q1 over a training step (Q runs, Q1 of them with one edge, which are read where they are) against
+// 2 E + 7 P - 2 P1, and has fewer products.  The graph gets the lists for it where that is so (sched_run_rows).
+// RGCN, forward + backward, us, pairs / runs, at 7 Q - 2 Q1 from 0.54 to 0.72 of 7 P - 2 P1: 300k edges, 60 relations, width 32 81 / 81, 64
+// 145 / 126, 128 277 / 211, bf16 128 138 / 136; 3M edges 443 / 340, 930 / 649, 2283 / 1438, 911 / 753; at equal numbers 78 / 76, 140 /
+// 139, 273 / 268 and 129 / 132 (300k edges); at 1.7 times the rows 172 / 205 (width 128, 8 relations).  Below 131072 edges the sum, a
+// launch or two more, costs what the rest saves: 100k edges 56 / 56, 85 / 88, 131 / 126, 95 / 98.
+inline bool sched_run_rows(int64_t edges, int64_t pairs, int64_t single_pairs, int64_t runs, int64_t single_runs) {
+    return edges >= (1 << 17) && 20 * (7 * runs - 2 * single_runs) <= 19 * (7 * pairs - 2 * single_pairs);
+}
+// The calls that take them.  Every flag but the accumulation of gradients asks for an alternative of the rows per pair.
+inline bool sched_use_run_rows(bool lists, int layer, int64_t edges, int d, uint32_t flags) {
+    return lists && !(flags & ~(uint32_t)RGNN_FLAG_ACCUMULATE) && layer == RGNN_LAYER_RGCN && edges * d >= 8000000;
+}
+// RGCN forwards that keep nothing for a backward: the saving has to come from the forward alone.  Pairs / runs, us: 300k edges, 60
+// relations, width 32 34 / 46, 64 59 / 64, 128 129 / 109; 1M 75 / 73, 145 / 124, 340 / 266; bf16 1M 137 / 145, 3M 397 / 408, 16M and 500
+// relations 2551 / 2374.
+inline bool sched_run_rows_infer(bool rows_bf16, int64_t edges, int d) { return edges * d >= (rows_bf16 ? 1000000000 : 30000000); }
 // HGT: the key and message linears of the nodes are folded into the per-relation weights when every relation's
 // sources have one node type.
 inline bool sched_hgt_folded(bool rel_src_tied, uint32_t flags) {

@@ -46,7 +46,8 @@ struct Rank1 { const float* coef; int stride; const int32_t* seg; const float* v
 rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int32_t* rowidx, int row_by_k,
                          const float* coef, int cstride, int cabs, const void* src, void* out, float* partial,
                          hipStream_t st, int role, const char* label, const char* combine_label, int heads = 1,
-                         int src_bf16 = 0, int out_bf16 = 0, const Rank1* r1 = nullptr);
+                         int src_bf16 = 0, int out_bf16 = 0, const Rank1* r1 = nullptr,
+                         const float* extra = nullptr);     // role 3: added to the output rows (may be out)
 // RGAT's backward (heads 1, 2 or 4), one launch: for the pairs with several edges G[p] = sum_e att_e dOut[dst_e] (+ ds_src[p] ws[r] per
 // head, with ws) and ds_src[p] = sum_e dz_e per head (element p * ds_src_stride + h; not for the pairs that are cut: the caller sums
 // those); by relation U[h][r] = sum_q ds_dst[q][h] X[dst_q], whose cut relations stay as pieces in run_partial
@@ -62,7 +63,8 @@ rgnn_status_t rgat_bwd_walks(const rgnn_graph* g, const RgatBwdWalks& a, hipStre
 // and of output rows (out_copy elements apart).  full_exp: expf instead of __expf (bf16 rows: always).  The partial rows carry the factor
 // pow2_share(piece_len) (device_utils.h).
 rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, void* out, int out_bf16, const char* label,
-                               hipStream_t st, const Rank1* r1 = nullptr, int heads = 1, int copies = 1, size_t out_copy = 0);
+                               hipStream_t st, const Rank1* r1 = nullptr, int heads = 1, int copies = 1, size_t out_copy = 0,
+                               const float* extra = nullptr);
 rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
                               int out_bf16, float* ms, bool full_exp, int piece_len, const char* label, hipStream_t st);
 // H weighted sums of the same gathered rows in one walk (coef [entries][H]); out [H][out_rows][D]

@@ -337,6 +337,7 @@ struct GatherArgs {
     int sum2_stride;      // for the whole segments, added in entry order; the caller sums the cut segments itself.  With
     int s2off;            // r1.vec set, the walk also adds that sum times r1.vec[r1.seg[row_i]] to the row (r1.coef then
                           // serves only the cut segments, where their pieces are combined)
+    const float* extra;   // optional (EX kernels): out[row_i] += extra[row_i] (cut segments: where their pieces are combined); may be out
 };
 
 // the rank-1 term of a whole segment whose coefficient the walk has just summed
@@ -349,6 +350,13 @@ __device__ __forceinline__ void add_rank1_own(const Rank1& r1, float c, size_t r
 }
 
 template <int D, int V>
+__device__ __forceinline__ void add_row(const float* extra, size_t row, int cv, float (&acc)[V]) {
+    if (!extra) return;
+    float t[V];
+    load_cols(extra + row * D + cv * V, t);
+    fma_cols(acc, 1.f, t);
+}
+template <int D, int V>
 __device__ __forceinline__ void add_rank1(const Rank1& r1, int lanes_per_head, size_t row, int cv, float (&acc)[V]) {
     if (!r1.coef) return;
     const float c = r1.coef[row * r1.stride + cv / lanes_per_head];
@@ -358,12 +366,12 @@ __device__ __forceinline__ void add_rank1(const Rank1& r1, int lanes_per_head, s
 }
 
 // ROLE gives each use its own kernel name in profiler output (0 forward aggregation over destinations,
-// 1 backward aggregation over pairs, 2 destination-side weight gradient).  The forward aggregation
+// 1 backward aggregation over pairs, 2 destination-side weight gradient, 3 gradient rows of the runs over sources, plus a row).  The forward aggregation
 // gathers rows of the large per-pair tensor, most of them once: with fp32 rows those loads carry the
 // non-temporal hint (NT; it did not pay for the 2-byte rows, whose pairs are shared by more edges in the
 // workloads that use them); the other two gather rows of node tensors, which are reused and stay cached.
 // TI / TO: storage type of the gathered rows and of the output rows (float or bf16_t).
-template <int D, typename TI, typename TO, bool R1, bool NT, bool S2 = false>
+template <int D, typename TI, typename TO, bool R1, bool NT, bool S2 = false, bool EX = false>
 __device__ __forceinline__ void gather_general(const GatherArgs& a, int blk) {
     constexpr int V = RowT<TI>::V, LPR = D / V, IPB = 256 / LPR;
     int i = blk * IPB + threadIdx.x / LPR;
@@ -417,8 +425,9 @@ __device__ __forceinline__ void gather_general(const GatherArgs& a, int blk) {
     const int slot = a.it.slot[i];
     if (slot < 0) {
         if (R1) add_rank1<D>(a.r1, a.lanes_per_head, (size_t)a.it.row[i], cv, acc0);
+        if (EX) add_row<D>(a.extra, (size_t)a.it.row[i], cv, acc0);
         if (S2) add_rank1_own<D>(a.r1, s2, (size_t)a.it.row[i], cv, acc0);
-        store_cols(static_cast<TO*>(a.out) + (size_t)a.it.row[i] * D + cv * V, acc0);
+        store_row<D, TO>(a.out, (size_t)a.it.row[i], cv, acc0);
         if (S2 && cv % a.lanes_per_head == 0) a.sum2[(size_t)a.it.row[i] * a.sum2_stride + head] = s2;
     } else {
         store_cols(a.partial + (size_t)slot * D + cv * V, acc0);
@@ -429,7 +438,7 @@ __device__ __forceinline__ void gather_general(const GatherArgs& a, int blk) {
 // such a segment, so the general kernel would spend its time on the item -> indices -> rows -> store
 // chain; here a group of lanes takes two of them at a time, all loads of both independent (entries
 // past a segment's end repeat its last one with a zero coefficient).
-template <int D, typename TI, typename TO, bool R1, bool NT, bool S2 = false>
+template <int D, typename TI, typename TO, bool R1, bool NT, bool S2 = false, bool EX = false>
 __device__ __forceinline__ void gather_short(const GatherArgs& a, int blk, int first, int n) {
     constexpr int V = RowT<TI>::V, LPR = D / V, GPB = 256 / LPR;
     const int g = blk * GPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
@@ -475,8 +484,9 @@ __device__ __forceinline__ void gather_short(const GatherArgs& a, int blk, int f
         for (int u = 0; u < kShortLen; ++u) fma_cols(acc, c[q][u], v[q][u]);
         if (i0 + q < n) {
             if (R1) add_rank1<D>(a.r1, a.lanes_per_head, (size_t)orow[q], cv, acc);
+            if (EX) add_row<D>(a.extra, (size_t)orow[q], cv, acc);
             if (S2) add_rank1_own<D>(a.r1, s2[q], (size_t)orow[q], cv, acc);
-            store_cols(static_cast<TO*>(a.out) + (size_t)orow[q] * D + cv * V, acc);
+            store_row<D, TO>(a.out, (size_t)orow[q], cv, acc);
             if (S2 && cv % a.lanes_per_head == 0) a.sum2[(size_t)orow[q] * a.sum2_stride + head] = s2[q];
         }
     }
@@ -485,7 +495,7 @@ __device__ __forceinline__ void gather_short(const GatherArgs& a, int blk, int f
 // The whole segments with exactly one entry, items [first, first + n): out[row_i] = c * src[row].
 // A group of lanes handles four of them at a time, all loads of the four independent, which keeps
 // enough rows in flight where the general kernel would wait on one short dependent chain per item.
-template <int D, typename TI, typename TO, bool R1, bool NT>
+template <int D, typename TI, typename TO, bool R1, bool NT, bool EX = false>
 __device__ __forceinline__ void gather_single(const GatherArgs& a, int blk, int first, int n) {
     constexpr int V = RowT<TI>::V, LPR = D / V, GPB = 256 / LPR;
     const int g = blk * GPB + threadIdx.x / LPR, cv = threadIdx.x % LPR;
@@ -521,7 +531,8 @@ __device__ __forceinline__ void gather_single(const GatherArgs& a, int blk, int 
 #pragma unroll
             for (int q = 0; q < V; ++q) v[u][q] *= c[u];
             if (R1) add_rank1<D>(a.r1, a.lanes_per_head, (size_t)orow[u], cv, v[u]);
-            store_cols(static_cast<TO*>(a.out) + (size_t)orow[u] * D + cv * V, v[u]);
+            if (EX) add_row<D>(a.extra, (size_t)orow[u], cv, v[u]);
+            store_row<D, TO>(a.out, (size_t)orow[u], cv, v[u]);
         }
     }
 }
@@ -536,16 +547,16 @@ struct GatherRanges { int general_blocks, short_blocks, short_first, short_n, si
 template <int D, int ROLE, typename TI, typename TO, bool R1 = false>
 __global__ __launch_bounds__(256) void gather_sum_kernel(GatherArgs a, GatherRanges r) {
     const int blk = blockIdx.x;
-    if (blk < r.general_blocks) gather_general<D, TI, TO, R1, ROLE == 0>(a, blk);
-    else if (blk < r.general_blocks + r.short_blocks) gather_short<D, TI, TO, R1, ROLE == 0>(a, blk - r.general_blocks, r.short_first, r.short_n);
-    else gather_single<D, TI, TO, R1, ROLE == 0>(a, blk - r.general_blocks - r.short_blocks, r.single_first, r.single_n);
+    if (blk < r.general_blocks) gather_general<D, TI, TO, R1, ROLE == 0, false, ROLE == 3>(a, blk);
+    else if (blk < r.general_blocks + r.short_blocks) gather_short<D, TI, TO, R1, ROLE == 0, false, ROLE == 3>(a, blk - r.general_blocks, r.short_first, r.short_n);
+    else gather_single<D, TI, TO, R1, ROLE == 0, ROLE == 3>(a, blk - r.general_blocks - r.short_blocks, r.single_first, r.single_n);
 }
 template <int D, int ROLE, typename TI, typename TO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void gather_general_kernel(GatherArgs a) { gather_general<D, TI, TO, false, ROLE == 0>(a, blockIdx.x); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void gather_general_kernel(GatherArgs a) { gather_general<D, TI, TO, false, ROLE == 0, false, ROLE == 3>(a, blockIdx.x); }
 template <int D, int ROLE, typename TI, typename TO>
-__global__ __launch_bounds__(256) void gather_short_kernel(GatherArgs a, int first, int n) { gather_short<D, TI, TO, false, ROLE == 0>(a, blockIdx.x, first, n); }
+__global__ __launch_bounds__(256) void gather_short_kernel(GatherArgs a, int first, int n) { gather_short<D, TI, TO, false, ROLE == 0, false, ROLE == 3>(a, blockIdx.x, first, n); }
 template <int D, int ROLE, typename TI, typename TO>
-__global__ __launch_bounds__(256) void gather_single_kernel(GatherArgs a, int first, int n) { gather_single<D, TI, TO, false, ROLE == 0>(a, blockIdx.x, first, n); }
+__global__ __launch_bounds__(256) void gather_single_kernel(GatherArgs a, int first, int n) { gather_single<D, TI, TO, false, ROLE == 0, ROLE == 3>(a, blockIdx.x, first, n); }
 
 // NH weighted sums of the same rows in one walk: out[h][row_i] = sum_j coef[k][h] * src[row], k and row as
 // in gather_sum_kernel (fp32 rows).  out is [NH][out_rows][D], the partial rows [NH][num_partials][D].
@@ -618,7 +629,7 @@ template <int D, typename TO, int TH, int C4>
 __global__ __launch_bounds__(TH) void combine_partials_kernel(const int32_t* __restrict__ split_row,
                                                               const int32_t* __restrict__ split_ptr,
                                                               const float* __restrict__ partial, TO* __restrict__ out,
-                                                              size_t partial_copy, size_t out_copy, Rank1 r1, int lanes_per_head) {
+                                                              size_t partial_copy, size_t out_copy, Rank1 r1, int lanes_per_head, const float* extra) {
     constexpr int G = TH / C4;
     __shared__ float4 red[TH];
     partial += blockIdx.y * partial_copy;
@@ -654,7 +665,8 @@ __global__ __launch_bounds__(TH) void combine_partials_kernel(const int32_t* __r
         }
         float tv[4] = {t.x, t.y, t.z, t.w};
         add_rank1<D>(r1, lanes_per_head, (size_t)split_row[s], c4, tv);
-        store_cols(out + (size_t)split_row[s] * D + c4 * 4, tv);
+        add_row<D>(extra, (size_t)split_row[s], c4, tv);
+        store_row<D, TO>(out, (size_t)split_row[s], c4, tv);
     }
 }
 // Hub nodes and pairs: mostly two or three pieces per cut segment and thousands of segments, so small workgroups (1024
@@ -1356,7 +1368,7 @@ rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* part
 }
 
 rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, void* out, int out_bf16, const char* label,
-                               hipStream_t st, const Rank1* r1, int heads, int copies, size_t out_copy) {
+                               hipStream_t st, const Rank1* r1, int heads, int copies, size_t out_copy, const float* extra) {
     if (L.num_split == 0) return RGNN_OK;
     const Rank1 r1v = r1 ? *r1 : Rank1{nullptr, 0, nullptr, nullptr};
     KernelTimer kt(st, label);
@@ -1364,12 +1376,15 @@ rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, v
     do {                                                                                                               \
         if (few_long_segments(L))                                                                                      \
             hipLaunchKernelGGL((combine_partials_kernel<DD_, TO_, 1024, 8>), dim3(L.num_split, copies, DD_ / 32), dim3(1024), 0, st, L.split_row, \
-                               L.split_ptr, partial, static_cast<TO_*>(out), (size_t)L.num_partials * DD_, out_copy, r1v, (DD_ / 4) / heads); \
+                               L.split_ptr, partial, static_cast<TO_*>(out), (size_t)L.num_partials * DD_, out_copy, r1v, (DD_ / 4) / heads, extra); \
         else                                                                                                           \
             hipLaunchKernelGGL((combine_partials_kernel<DD_, TO_, 256, DD_ / 4>), dim3(L.num_split, copies), dim3(256), 0, st, L.split_row, \
-                               L.split_ptr, partial, static_cast<TO_*>(out), (size_t)L.num_partials * DD_, out_copy, r1v, (DD_ / 4) / heads); \
+                               L.split_ptr, partial, static_cast<TO_*>(out), (size_t)L.num_partials * DD_, out_copy, r1v, (DD_ / 4) / heads, extra); \
     } while (0)
-    if (D == 256) {
+    if (out_bf16 == 2) {
+        if (D != 128) RGNN_FAIL(RGNN_EUNSUPPORTED, "combine_partials: two bf16 planes at width 128 only");
+        RGNN_LAUNCH_COMBINE(128, bf16_planes_t);
+    } else if (D == 256) {
         if (out_bf16) RGNN_LAUNCH_COMBINE(256, bf16_t);
         else RGNN_LAUNCH_COMBINE(256, float);
     } else if (out_bf16) {
@@ -1385,7 +1400,7 @@ rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, v
 rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int32_t* rowidx, int row_by_k,
                          const float* coef, int cstride, int cabs, const void* src, void* out, float* partial,
                          hipStream_t st, int role, const char* label, const char* combine_label, int heads,
-                         int src_bf16, int out_bf16, const Rank1* r1) {
+                         int src_bf16, int out_bf16, const Rank1* r1, const float* extra) {
     if (L.num_items == 0) return RGNN_OK;
     const Rank1 r1v = r1 ? *r1 : Rank1{nullptr, 0, nullptr, nullptr};
     const int lpr = D / (src_bf16 ? 8 : 4);
@@ -1393,7 +1408,8 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
     const int ns = batched_count(L.num_single, current_schedule_flags());
     const int nsh = batched_count(L.num_short, current_schedule_flags());
     const int skip_first = nsh > 0 ? L.first_short : L.first_single;
-    GatherArgs a{dev_items(L), via, rowidx, row_by_k, coef, cstride, cabs, lpr / heads, src, out, partial, skip_first, nsh + ns, r1v, nullptr, 1, heads};
+    GatherArgs a{dev_items(L), via, rowidx, row_by_k, coef, cstride, cabs, lpr / heads, src, out, partial, skip_first, nsh + ns, r1v, nullptr, 1, heads, extra};
+    if (extra && role != 3) RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: rows are added to the sums over sources only");
     {
         KernelTimer kt(st, label);
         GatherRanges r{};
@@ -1406,7 +1422,8 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
     do {                                                                                                                   \
         if (role == 0) RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 0, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
         else if (role == 1) RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 1, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
-        else RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 2, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
+        else if (role == 2) RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 2, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
+        else RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 3, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
         RGNN_CHECK_LAUNCH();                                                                                               \
     } while (0)
         if (r1 && (src_bf16 || out_bf16 || role != 1)) RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: the rank-1 term is built for fp32 rows of the pair-major walk");
@@ -1415,6 +1432,12 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
                 RGNN_DISPATCH_D(D, hipLaunchKernelGGL((gather_sum_kernel<DD, 1, float, float, true>), grid, dim3(256), 0, st, a, r));
                 RGNN_CHECK_LAUNCH();
             }
+        } else if (out_bf16 == 2) {
+            if (D != 128 || !src_bf16 || role != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: sums in two bf16 planes are built for bf16 rows of width 128");
+            if (r.general_blocks > 0) hipLaunchKernelGGL((gather_general_kernel<128, 1, bf16_t, bf16_planes_t>), dim3(r.general_blocks), dim3(256), 0, st, a);
+            if (nsh > 0) hipLaunchKernelGGL((gather_short_kernel<128, 1, bf16_t, bf16_planes_t>), dim3(r.short_blocks), dim3(256), 0, st, a, L.first_short, nsh);
+            if (ns > 0) hipLaunchKernelGGL((gather_single_kernel<128, 1, bf16_t, bf16_planes_t>), dim3(single_blocks), dim3(256), 0, st, a, L.first_single, ns);
+            RGNN_CHECK_LAUNCH();
         } else if (!src_bf16) {
             if (grid.x > 0) RGNN_LAUNCH_GATHER(gather_sum_kernel, grid, a, r);
         } else {
@@ -1424,7 +1447,7 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
         }
 #undef RGNN_LAUNCH_GATHER
     }
-    return combine_partials(L, D, partial, out, out_bf16, combine_label, st, &r1v, heads);
+    return combine_partials(L, D, partial, out, out_bf16, combine_label, st, &r1v, heads, 1, 0, extra);
 }
 
 rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, const int32_t* via, const int32_t* rowidx,

@@ -79,6 +79,8 @@ __device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int
 //                                                                  s_out[row][h] over the h-th of s_heads column slices
 //   DYG      backward: dY rows are read through the list  RS       backward: rowscale / Avec / xvec in use
 //   OS       the rows of Y are OS * ND floats apart (2: the key or message half of HGT's pair rows)
+//   XSEL     input rows come from two tensors: list entry g >= 0 is row g of X, otherwise row g & 0x7FFFFFFF of X2 (the rows
+//            per run: a run's only source, or the sum of its sources)
 //
 // At width 128 the stage holds half of the columns at a time, so that eight wavefronts fit beside the 64 KB weight: two per
 // SIMD, one multiplying while the other stages; and the result goes to memory straight from the accumulators, a 128-byte line
@@ -95,10 +97,16 @@ struct FwdShape {
     static constexpr int XS = (!DIRECT && ND > KS ? ND : KS) + 4;   // row stride of the per-wave stage
     static constexpr size_t LDS = sizeof(float) * (KD * ND + NW * 32 * XS);
 };
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1>
+// row g of X, or with XSEL of the tensor that g's top bit says
+template <int D, bool XSEL>
+__device__ __forceinline__ const float* input_row(const float* __restrict__ X, const float* __restrict__ X2, int g) {
+    return (XSEL && g < 0 ? X2 : X) + (size_t)(XSEL ? g & 0x7FFFFFFF : g) * D;
+}
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1, bool XSEL = false>
 __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                          const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
-                                         float* __restrict__ s_out, int s_heads, int relu) {
+                                         float* __restrict__ s_out, int s_heads, int relu, const float* __restrict__ X2 = nullptr) {
+    static_assert(!XSEL || (GATHER && !SCATTER && !ACCUM && !VEC), "two input tensors: plain products of gathered rows");
     using S = FwdShape<KD, ND, VEC, ACCUM>;
     constexpr int NW = S::NW, XS = S::XS, KS = S::KS, PH = KD / KS;
     constexpr int CB = ND / 32;
@@ -143,7 +151,7 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
 #define RGNN_FETCH_ROWS()                                                           \
     _Pragma("unroll") for (int it = 0; it < NX; ++it) {                             \
         const int g_ = LANEIDX ? __shfl(gi[0], ri + it * RPI) : gi[LANEIDX ? 0 : it]; \
-        xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)g_ * KD + ci * 4);       \
+        xr[it] = *reinterpret_cast<const v4f*>(input_row<KD, XSEL>(X, X2, g_) + ci * 4); \
         if (SCATTER) gcur[SCATTER ? it : 0] = g_;                                   \
     }
         RGNN_FETCH_IDX(wave)
@@ -262,17 +270,17 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
     }
 }
 
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool FOLD = false>
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool FOLD = false, bool XSEL = false>
 __global__ __launch_bounds__((64 * FwdShape<KD, ND, VEC, ACCUM>::NW))
 void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                   const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
-                                  float* __restrict__ s_out, int s_heads, int relu, FoldArgs fold) {
+                                  float* __restrict__ s_out, int s_heads, int relu, FoldArgs fold, const float* __restrict__ X2) {
     // RGAT: the folded vectors that the kernel after this one reads (a launch of their own cost 5 us behind this one)
     if (FOLD && (int)blockIdx.x >= (int)gridDim.x - fold.blocks) {
         if (threadIdx.x < 256) fold_weight_block(fold, blockIdx.x - (gridDim.x - fold.blocks));
         return;
     }
-    fwd_wave<KD, ND, GATHER, SCATTER, ACCUM, VEC>(t, blockIdx.x, X, gather, W, Y, vec, s_out, s_heads, relu);
+    fwd_wave<KD, ND, GATHER, SCATTER, ACCUM, VEC, 1, XSEL>(t, blockIdx.x, X, gather, W, Y, vec, s_out, s_heads, relu, X2);
 }
 
 // Several products that do not depend on each other in one launch (HGT: a node linear, rows gathered and scattered, and the two
@@ -332,15 +340,20 @@ __global__ __launch_bounds__((64 * FwdShape<D, D, false, false>::NW)) void typed
 // pairs (74 % of the pairs of 1.2M edges) are then neither written by the pair-major walk nor read from where it put them,
 // and are read from dOut, a table small enough for the caches: 832k pairs, 32 -> 64 columns, walk 79 -> 30 us, this kernel
 // 87 -> 92 us; 2.15M pairs of width 64, walk 226 -> 90 us, this kernel 345 -> 373 us.
-struct RowSelect { const int32_t* sel; const float* alt; const float2* ds_scale; const float* scale; const float* hcoef; const float* wvec; };
+//
+// XSEL (rows per run): input rows from two tensors as in the forward, X or x2, and row i of dY is dY[sel[i]].
+struct RowSelect {
+    const int32_t* sel; const float* alt; const float2* ds_scale; const float* scale; const float* hcoef; const float* wvec; const float* x2;
+};
 // DS: the rows of dY are DS * ND floats apart (not with SEL).
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1>
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, bool XSEL = false>
 __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                          const float* __restrict__ W, const float* __restrict__ dY, float* __restrict__ dXrow,
                                          const float* __restrict__ rowscale, const float* __restrict__ vec,
                                          float* __restrict__ part, const RowSelect& ys) {
     static_assert(!SEL || (!DYG && DS == 1), "the row selector replaces the dY gather");
     static_assert(HS == 0 || (SEL && !RS && (HS == 2 || HS == 4)), "per-head row selector: two or four heads, no rowscale");
+    static_assert(!XSEL || (GATHER && !SCATTER && SEL && !RS && HS == 0), "two input tensors: gathered rows, dY through its own list");
     constexpr int NW = 8;
     constexpr int XS = KD + 4, YS = (ND > KD ? ND : KD) + 4, WS = ND + 1;
     constexpr int KB = KD / 32, NB = ND / 32, WB = KB * NB;
@@ -419,12 +432,14 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
 #pragma unroll
             for (int it = 0; it < NXR; ++it) {
                 const int gx = LANEIDX ? __shfl(gsn, rx + it * RPX) : gi[it];
-                xr[it] = *reinterpret_cast<const v4f*>(X + (size_t)gx * KD + cx * 4);
+                xr[it] = *reinterpret_cast<const v4f*>(input_row<KD, XSEL>(X, ys.x2, gx) + cx * 4);
                 gcur[it] = gx;
             }
 #pragma unroll
             for (int it = 0; it < NYR; ++it) {
-                if (SEL) {
+                if (XSEL) {
+                    yr[it] = *reinterpret_cast<const v4f*>(dY + (size_t)__shfl(ysn, ry + it * RPY) * ND + cy * 4);
+                } else if (SEL) {
                     const int sl = __shfl(ysn, ry + it * RPY);
                     const float* base = sl < 0 ? ys.alt : dY;
                     yr[it] = *reinterpret_cast<const v4f*>(base + (size_t)(sl & 0x7FFFFFFF) * ND + cy * 4);
@@ -443,7 +458,7 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
                 const float2 pr = ys.ds_scale[min(ra + u * 32 + (lane & 31), rbnd - 1)];
                 dsr = pr.x;
                 alr = ysn < 0 ? pr.y : 1.f;
-            } else if (SEL) {
+            } else if (SEL && !XSEL) {
                 // without scales the load goes to the selectors (any bits) and is not used: no conditional load
                 const float* from = ys.scale ? ys.scale : reinterpret_cast<const float*>(ys.sel);
                 const float sc = from[min(ra + u * 32 + (lane & 31), rbnd - 1)];
@@ -478,7 +493,7 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
                     const float a0 = __shfl(hcf[2], from), a1 = __shfl(hcf[3], from);
                     const float bq = hd & 1 ? b1 : b0, aq = hd & 1 ? a1 : a0;
                     v = v4f{v[0] * aq + bq * xv.x, v[1] * aq + bq * xv.y, v[2] * aq + bq * xv.z, v[3] * aq + bq * xv.w};
-                } else if (SEL) {
+                } else if (SEL && !XSEL) {
                     const float sc = __shfl(alr, ry + it * RPY);
                     v = v4f{v[0] * sc, v[1] * sc, v[2] * sc, v[3] * sc};
                 }
@@ -649,7 +664,7 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
     }
 }
 
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1>
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, bool XSEL = false>
 __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, const float* __restrict__ X,
                                                                     const int32_t* __restrict__ gather,
                                                                     const float* __restrict__ W,
@@ -658,7 +673,7 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, 
                                                                     const float* __restrict__ rowscale,
                                                                     const float* __restrict__ vec,
                                                                     float* __restrict__ part, RowSelect ys) {
-    bwd_wave<KD, ND, GATHER, DYG, SCATTER, RS, SEL, HS, DS>(t, blockIdx.x, X, gather, W, dY, dXrow, rowscale, vec, part, ys);
+    bwd_wave<KD, ND, GATHER, DYG, SCATTER, RS, SEL, HS, DS, XSEL>(t, blockIdx.x, X, gather, W, dY, dXrow, rowscale, vec, part, ys);
 }
 // The backward of the products above.  A workgroup has a compute unit to itself, and a chunk costs a load of the weight and a flush
 // of the gradient whatever its length, so the chunks of all jobs together are one per compute unit (sizes as above: 30 + 29 + 21.5 us
@@ -672,13 +687,13 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_jobs_kernel(BwdJobs jobs
     else bwd_wave<D, D, true, true, true, false>(j.t, chunk, j.X, j.gather, j.W, j.dY, j.dX, nullptr, nullptr, j.part, none);
 }
 
-// RGCN: the pairs' product (with the row selector or without) and the self-loop's, the first `chunks` workgroups and the others; chunks
+// RGCN: the pairs' product (with the row selector or without), or the runs' (XSEL), and the self-loop's, the first `chunks` workgroups and the others; chunks
 // as above (833k pairs and 120k nodes, 32 -> 64 columns: 100 and 23 us, together 110).
-template <int KD, int ND, bool SEL>
+template <int KD, int ND, bool SEL, bool XSEL>
 __global__ __launch_bounds__(512) void typed_linear_bwd_loop_kernel(BwdJob pair, RowSelect ys, BwdJob loop) {
     const RowSelect none{};
     if ((int)blockIdx.x < pair.chunks)
-        bwd_wave<KD, ND, true, false, false, false, SEL>(pair.t, blockIdx.x, pair.X, pair.gather, pair.W, pair.dY, pair.dX, nullptr, nullptr, pair.part, ys);
+        bwd_wave<KD, ND, true, false, false, false, SEL, 0, 1, XSEL>(pair.t, blockIdx.x, pair.X, pair.gather, pair.W, pair.dY, pair.dX, nullptr, nullptr, pair.part, ys);
     else
         bwd_wave<KD, ND, false, false, false, false>(loop.t, blockIdx.x - pair.chunks, loop.X, nullptr, loop.W, loop.dY, loop.dX, nullptr, nullptr, loop.part, none);
 }
@@ -688,16 +703,16 @@ static TileArgs tile_args(const TileList& t) {
     return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot};
 }
 
-template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool FOLD = false>
+template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool FOLD = false, bool XSEL = false>
 static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st) {
     using S = FwdShape<KD, ND, VEC, ACCUM>;
     constexpr size_t lds = S::LDS;
-    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, FOLD>;
+    auto kern = typed_linear_fwd_wave_kernel<KD, ND, GATHER, SCATTER, ACCUM, VEC, FOLD, XSEL>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     const FoldArgs fold = a.fold ? *a.fold : FoldArgs{};
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks + fold.blocks), dim3(64 * S::NW), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
-                       a.vec, a.s_out, a.s_heads, a.relu, fold);
+                       a.vec, a.s_out, a.s_heads, a.relu, fold, a.X2);
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -711,6 +726,10 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
     if (a.fold && (!g || sc || ac || v || a.fold->nd % 32)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: folds go with plain products of gathered rows");
     if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
     if (a.y_stride != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built in the launches of several products only");
+    if (a.X2) {
+        if (!g || sc || ac || v || a.fold) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: two input tensors go with plain products of gathered rows");
+        return launch_fwd_wave<KD, ND, true, false, false, false, false, true>(a, st);
+    }
     if (g && !sc && !ac && v) return launch_fwd_wave<KD, ND, true, false, false, true>(a, st);
     if (g && !sc && !ac && !v && a.fold) return launch_fwd_wave<KD, ND, true, false, false, false, true>(a, st);
     if (g && !sc && !ac && !v) return launch_fwd_wave<KD, ND, true, false, false, false>(a, st);
@@ -731,7 +750,7 @@ rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hi
     // activation may also be the caller's).  A value within
     // rounding of zero then decides a gradient row, and the rounding stays the one of the fp32 instructions (1.43M pairs:
     // 0.42 ms, split 0.28).
-    if (d_in == 128 && d_out == 128) return a.sign_matters ? launch_fwd<128, 128>(a, st) : typed_linear_split_fwd(a, st);
+    if (d_in == 128 && d_out == 128) return a.sign_matters || a.X2 ? launch_fwd<128, 128>(a, st) : typed_linear_split_fwd(a, st);
     if (d_in == 32 && d_out == 64) return launch_fwd<32, 64>(a, st);
     if (d_in == 64 && d_out == 32) return launch_fwd<64, 32>(a, st);
     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear: d_in = %d, d_out = %d not supported (need 32 / 64 / 128, different widths only among 32 and 64)", d_in, d_out);
@@ -741,16 +760,16 @@ size_t typed_linear_bwd_scratch_floats(int d_in, int d_out, const TileList& t, i
     return (size_t)std::max(t.num_slots, 1) * ((size_t)d_in * d_out + (size_t)std::max(vectors, 1) * d_in);
 }
 
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1>
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, bool XSEL = false>
 static rgnn_status_t launch_bwd_wave(const TypedLinearBwdArgs& a, hipStream_t st) {
     constexpr int WREG = 32 * (KD + 4) + 32 * ((ND > KD ? ND : KD) + 4) + 32;
     static_assert(WREG >= KD * ND + (HS ? HS : 1) * KD, "per-wavefront LDS region must hold a weight-gradient copy");
     const size_t lds = sizeof(float) * (KD * (ND + 1) + 8 * WREG);
-    auto kern = typed_linear_bwd_wave_kernel<KD, ND, GATHER, DYG, SCATTER, RS, SEL, HS, DS>;
+    auto kern = typed_linear_bwd_wave_kernel<KD, ND, GATHER, DYG, SCATTER, RS, SEL, HS, DS, XSEL>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(512), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W,
-                       a.dY, a.dXrow, a.rowscale, a.vec, a.part, RowSelect{a.ysel, a.dY_alt, a.ds_yscale, a.yscale, a.hcoef, a.wvec});
+                       a.dY, a.dXrow, a.rowscale, a.vec, a.part, RowSelect{a.ysel, a.dY_alt, a.ds_yscale, a.yscale, a.hcoef, a.wvec, a.X2});
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -766,7 +785,11 @@ static rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
         if constexpr (KD <= 64 && ND <= 64) {
             const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
             done = true;
-            if (a.dy_stride == 2) {
+            if (a.X2) {
+                if (!(g && a.ysel && !dg && !sc && !rs) || a.dY_alt || a.vec || a.yscale || a.ds_yscale || a.hcoef || a.dy_stride != 1)
+                    RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: two input tensors go with gathered X, a list of the dY rows and nothing else");
+                RGNN_TRY((launch_bwd_wave<KD, ND, true, false, false, false, true, 0, 1, true>(a, st)));
+            } else if (a.dy_stride == 2) {
                 if (!(g && !dg && !sc && !rs && !a.ysel && KD == ND))
                     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY rows two widths apart are built for gathered X, ungathered dY, no rowscale and no selector only");
                 if constexpr (KD == ND) RGNN_TRY((launch_bwd_wave<KD, ND, true, false, false, false, false, 0, 2>(a, st)));
@@ -806,8 +829,8 @@ static rgnn_status_t launch_bwd_loop(const TypedLinearBwdArgs& p, const TypedLin
     constexpr size_t lds = sizeof(float) * (KD * (ND + 1) + 8 * (32 * (KD + 4) + 32 * ((ND > KD ? ND : KD) + 4) + 32));
     const BwdJob pair{tile_args(*p.tiles), p.tiles->num_chunks, 1, p.X, p.gather, p.W, p.dY, p.dXrow, p.part};
     const BwdJob loop{tile_args(*l.tiles), l.tiles->num_chunks, 0, l.X, nullptr, l.W, l.dY, l.dXrow, l.part};
-    const RowSelect ys{p.ysel, p.dY_alt, nullptr, p.yscale, nullptr, nullptr};
-    auto kern = p.ysel ? typed_linear_bwd_loop_kernel<KD, ND, true> : typed_linear_bwd_loop_kernel<KD, ND, false>;
+    const RowSelect ys{p.ysel, p.dY_alt, nullptr, p.yscale, nullptr, nullptr, p.X2};
+    auto kern = p.X2 ? typed_linear_bwd_loop_kernel<KD, ND, true, true> : p.ysel ? typed_linear_bwd_loop_kernel<KD, ND, true, false> : typed_linear_bwd_loop_kernel<KD, ND, false, false>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, "typed_linear_loop_bwd");
     hipLaunchKernelGGL(kern, dim3(pair.chunks + loop.chunks), dim3(512), lds, st, pair, ys, loop);
@@ -816,7 +839,7 @@ static rgnn_status_t launch_bwd_loop(const TypedLinearBwdArgs& p, const TypedLin
 }
 rgnn_status_t typed_linear_bwd_loop(int d_in, int d_out, const TypedLinearBwdArgs& p, const TypedLinearBwdArgs& l, hipStream_t st) {
     const bool plain = !p.rowscale && !l.rowscale && !p.hcoef && !p.ds_yscale && p.gather && !l.gather && !p.dy_gathered && !p.scatter_dx && !l.ysel &&
-                       p.dy_stride == 1 && l.dy_stride == 1 && p.sums && l.sums && (!p.ysel || p.dY_alt);
+                       p.dy_stride == 1 && l.dy_stride == 1 && p.sums && l.sums && !l.X2 && (p.X2 ? p.ysel && !p.dY_alt && !p.yscale : !p.ysel || p.dY_alt);
     if (!plain) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward with self-loop: plain products with their sums only");
     for (const TypedLinearBwdArgs* a : {&p, &l}) RGNN_TRY(typed_linear_slot_reduce(*a->tiles, a->part, d_in * d_out, d_in, a->dW, nullptr, st, a->sums));
     if (p.tiles->num_tiles + l.tiles->num_tiles == 0) return RGNN_OK;

@@ -379,7 +379,10 @@ struct BwdArgs {
     const float* dY_alt;
     const float2* ds_yscale;
     const float* yscale;
+    const float* X2;         // XSEL: list entry g < 0 is row g & 0x7FFFFFFF of X2 (SEL is then a plain list of dY rows)
 };
+template <bool XSEL>
+__device__ __forceinline__ const float* input_row(const BwdArgs& a, int g) { return (XSEL && g < 0 ? a.X2 : a.X) + (size_t)(XSEL ? g & 0x7FFFFFFF : g) * D; }
 __device__ __forceinline__ const float* selected_row(const BwdArgs& a, int sl) { return (sl < 0 ? a.dY_alt : a.dY) + (size_t)(sl & 0x7FFFFFFF) * D; }
 template <bool RS>
 __device__ __forceinline__ float selected_scale(const BwdArgs& a, int row, int sl) {
@@ -396,7 +399,7 @@ __device__ __forceinline__ int of_row(int v, int k, int half) {
     const int a = __builtin_amdgcn_readlane(v, 2 * k), b = __builtin_amdgcn_readlane(v, 2 * k + 1);
     return half ? b : a;
 }
-template <bool GATHER, bool BOTH, bool RS, bool SEL>
+template <bool GATHER, bool BOTH, bool RS, bool SEL, bool XSEL>
 __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, float4* avb, RowOf* row_of, int* bad, int u0, int u1) {
     constexpr int DEPTH = 2;                               // units in flight per thread: 64 KB per compute unit
     const int tid = threadIdx.x & 255;
@@ -419,13 +422,13 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int row = n.row0 + min(ld.lr + 8 * k, n.rows - 1), g = GATHER ? of_row(gi[q], k, half) : row;
-            xr[p][k] = *reinterpret_cast<const float4*>(a.X + (size_t)g * D + ld.c4 * 4);
+            xr[p][k] = *reinterpret_cast<const float4*>(input_row<XSEL>(a, g) + ld.c4 * 4);
             const float* const y = SEL ? selected_row(a, of_row(yi[q], k, half)) : a.dY + (size_t)(BOTH ? g : row) * a.ldd;
             yr[p][k] = *reinterpret_cast<const float4*>(y + ld.c4 * 4);
         }
         const int row = n.row0 + min(jrow, n.rows - 1);
         rs[p] = RS ? (SEL ? a.ds_yscale[row].x : a.rowscale[row]) : 0.f;
-        sc[p] = SEL ? selected_scale<RS>(a, row, yi[q]) : 1.f;
+        sc[p] = SEL && !XSEL ? selected_scale<RS>(a, row, yi[q]) : 1.f;
     };
 #pragma unroll
     for (int p = 0; p < 2 * DEPTH; ++p) fetch_idx(p, u0 + p);
@@ -475,7 +478,7 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
                 }
                 ld.put(t, k, x, ok, seen);
                 float4 y = yr[p % DEPTH][k];
-                if (SEL) {
+                if (SEL && !XSEL) {
                     const float s = __int_as_float(of_row(__float_as_int(sc[p % DEPTH]), k, half));
                     y = make_float4(y.x * s, y.y * s, y.z * s, y.w * s);
                 }
@@ -539,7 +542,7 @@ __device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* ld
     }
 }
 
-template <bool GATHER, bool BOTH, bool RS, bool SEL>
+template <bool GATHER, bool BOTH, bool RS, bool SEL, bool XSEL>
 __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = (threadIdx.x >> 6) & 3, m = lane & 31, kh = lane >> 5;
     // Transposing reads: the 16-column groups g and g + 4 of the 128 form a 32 x 32 block (see the bf16 backward); this
@@ -623,7 +626,7 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
                     const int q = min(k + 2 * j + kh, n.rows - 1), r = n.row0 + q, g = GATHER ? __shfl(gm, q) : r;
                     const float* const yp = SEL ? selected_row(a, __shfl(ym, q)) : a.dY + (size_t)(BOTH ? g : r) * a.ldd;
                     const float s = SEL ? __shfl(sm, q) : 1.f;
-                    x[j] = a.X[(size_t)g * D + 16 * band + f];
+                    x[j] = input_row<XSEL>(a, g)[16 * band + f];
 #pragma unroll
                     for (int b = 0; b < 4; ++b) y[j][b] = yp[f + 16 * b] * s;
                 }
@@ -638,10 +641,10 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
     }
 }
 
-// GATHER: X rows through the list; BOTH: dY rows and dXrow rows as well; SEL: dY rows through the row selector
-template <bool GATHER, bool BOTH, bool RS, bool SEL = false>
+// GATHER: X rows through the list; BOTH: dY rows and dXrow rows as well; SEL: dY rows through the row selector; XSEL: X rows from two tensors
+template <bool GATHER, bool BOTH, bool RS, bool SEL = false, bool XSEL = false>
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) void typed_linear_split_bwd_kernel(BwdArgs a) {
-    static_assert(!(BOTH && (RS || SEL)) && (GATHER || !BOTH), "combinations the layers use");
+    static_assert(!(BOTH && (RS || SEL)) && (GATHER || !BOTH) && (!XSEL || (GATHER && SEL && !RS)), "combinations the layers use");
     extern __shared__ __align__(16) unsigned char lds[];   // [2] plane buffers, [2][8][32] float4 vector sums
     __shared__ int bad[4];
     __shared__ __align__(16) RowOf row_of[4];
@@ -650,8 +653,8 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     __syncthreads();
     if (u0 >= u1) return;
     if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH, RS, SEL>(a, lds, row_of, bad, u0, u1);
-    else if (threadIdx.x < 512) bwd_gradient<GATHER, BOTH, RS, SEL>(a, lds, bad, u0, u1);
-    else bwd_load<GATHER, BOTH, RS, SEL>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF), row_of, bad, u0, u1);
+    else if (threadIdx.x < 512) bwd_gradient<GATHER, BOTH, RS, SEL, XSEL>(a, lds, bad, u0, u1);
+    else bwd_load<GATHER, BOTH, RS, SEL, XSEL>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF), row_of, bad, u0, u1);
 }
 
 TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
@@ -667,15 +670,15 @@ rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
-template <bool GATHER, bool BOTH, bool RS, bool SEL = false>
+template <bool GATHER, bool BOTH, bool RS, bool SEL = false, bool XSEL = false>
 rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, const TileList& t, hipStream_t st) {
     const size_t lds = 2 * BUF + 2 * 256 * sizeof(float4);
-    auto kern = typed_linear_split_bwd_kernel<GATHER, BOTH, RS, SEL>;
+    auto kern = typed_linear_split_bwd_kernel<GATHER, BOTH, RS, SEL, XSEL>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(768), lds, st,
                        BwdArgs{tile_args(t), a.X, a.gather, a.W, a.dY, a.dy_stride * D, a.dXrow, a.rowscale, a.vec, a.part, a.ysel, a.dY_alt,
-                               a.ds_yscale, a.yscale});
+                               a.ds_yscale, a.yscale, a.X2});
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -685,7 +688,7 @@ rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, const TileList& t, hipStre
 rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
     const TileList& t = *a.tiles;
     if (t.num_tiles == 0) return RGNN_OK;
-    if (!a.gather || a.accumulate || a.vec || a.relu)
+    if (!a.gather || a.accumulate || a.vec || a.relu || a.X2)
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the split product is built for gathered rows, without accumulate / vec / activation");
     return a.scatter_out ? launch_fwd<true>(a, t, st) : launch_fwd<false>(a, t, st);
 }
@@ -693,6 +696,11 @@ rgnn_status_t typed_linear_split_fwd(const TypedLinearArgs& a, hipStream_t st) {
 rgnn_status_t typed_linear_split_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
     const TileList& t = *a.tiles;
     const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
+    if (a.X2) {
+        if (!g || dg || sc || rs || !a.ysel || a.dY_alt || a.vec || a.yscale || a.ds_yscale || a.hcoef || a.dy_stride != 1)
+            RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: two input tensors go with gathered X, a list of the dY rows and nothing else");
+        return t.num_tiles ? launch_bwd<true, false, false, true, true>(a, t, st) : RGNN_OK;
+    }
     if (a.ysel && (dg || !g || rs || a.dy_stride != 1 || a.hcoef || !a.dY_alt || (a.ds_yscale ? !a.vec || a.yscale : a.vec != nullptr)))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: the row selector needs gathered X, ungathered dY, and vec with the (rowscale, scale) pairs or neither; no heads at width 128");
     if (dg != sc) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY gathered and dXrow scattered must go together");
