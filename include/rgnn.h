@@ -276,6 +276,11 @@ rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc
  * head; ms [N, H, 2] fp32 = (max_e l_e, sum_e exp(l_e - max)) per head over the incoming
  * edges of each destination that has any, l_e = leakyrelu(z_e): the attention weight
  * of an edge is exp(l_e - m) / s and is recomputed by the backward call.
+ * On a large graph with fewer (destination, relation) runs than (source, relation) pairs, with one head and no desc.flags but
+ * RGNN_FLAG_ACCUMULATE, the layer takes the softmax within a run before the product and keeps rows per run instead of per pair
+ * (the kernel run_inputs in the timing report tells); `saved` then has another layout, which is the library's own, and the pair
+ * and row_select fields of rgnn_schedule describe the rows per pair that a flag brings back.  A forward with saved == NULL
+ * may keep the rows per pair where one with `saved` does not: the two then agree up to rounding.
  */
 rgnn_status_t rgnn_rgat_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W,
                             const void* w_s, const void* w_t, void* out, void* saved, void* workspace,

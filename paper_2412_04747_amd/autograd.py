@@ -31,6 +31,14 @@ def _bufs(graph, layer, desc, key):
     return graph.workspaces[k]
 
 
+def _room(graph, layer, desc, key, keep):
+    """(workspace, saved) of a forward call; keep: a backward may follow."""
+    ws, s = _bufs(graph, layer, desc, key)
+    if keep:
+        return ws, _buf(s) if s else None
+    return (_buf(ws.numel() + 256 + s) if s else ws), None
+
+
 def release(graph):
     """Drop the cached workspaces of a graph (Graph.close() does the same)."""
     graph.workspaces.clear()
@@ -46,13 +54,12 @@ def _f32(t):
 
 class _Rgat(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, graph, slope, heads, X, W, w_s, w_t):
+    def forward(ctx, graph, keep, slope, heads, X, W, w_s, w_t):
         X, W, w_s, w_t = _f32(X), _f32(W), _f32(w_s), _f32(w_t)
         d_in, d = W.shape[-2], W.shape[-1]
         desc = B.make_desc(B.RGNN_F32, d_in, d, heads, slope)
-        ws, s = _bufs(graph, B.RGNN_LAYER_RGAT, desc, (d_in, d, heads))
+        ws, saved = _room(graph, B.RGNN_LAYER_RGAT, desc, (d_in, d, heads), keep)
         out = torch.empty(graph.N, d, device=X.device)
-        saved = _buf(s)
         B.rgnn_rgat_fwd(graph.handle, desc, X, W, w_s, w_t, out, saved, ws, _stream())
         ctx.graph, ctx.desc, ctx.ws, ctx.saved_buf = graph, desc, ws, saved
         ctx.save_for_backward(X, W, w_s, w_t, out)
@@ -65,20 +72,19 @@ class _Rgat(torch.autograd.Function):
         dX, dW, dws, dwt = (torch.empty_like(t) for t in (X, W, w_s, w_t))
         B.rgnn_rgat_bwd(ctx.graph.handle, ctx.desc, X, W, w_s, w_t, out, ctx.saved_buf, dOut, dX, dW, dws, dwt, ctx.ws,
                         _stream())
-        return None, None, None, dX, dW, dws, dwt
+        return None, None, None, None, dX, dW, dws, dwt
 
 
 class _Rgcn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, graph, norm, act, X, W, W0):
+    def forward(ctx, graph, keep, norm, act, X, W, W0):
         X, W, W0 = _f32(X), _f32(W), _f32(W0)
         d_in, d = W.shape[-2], W.shape[-1]
         desc = B.make_desc(B.RGNN_F32, d_in, d, 1, 0.0,
                            B.RGNN_NORM_IN_DEGREE_PER_REL if norm == "in_degree_per_rel" else B.RGNN_NORM_NONE,
                            B.RGNN_ACT_RELU if act == "relu" else B.RGNN_ACT_NONE)
-        ws, s = _bufs(graph, B.RGNN_LAYER_RGCN, desc, (d_in, d, norm, act))
+        ws, saved = _room(graph, B.RGNN_LAYER_RGCN, desc, (d_in, d, norm, act), keep)
         out = torch.empty(graph.N, d, device=X.device)
-        saved = _buf(s) if s else None
         B.rgnn_rgcn_fwd(graph.handle, desc, X, W, W0, out, saved, ws, _stream())
         ctx.graph, ctx.desc, ctx.ws, ctx.saved_buf, ctx.has_w0 = graph, desc, ws, saved, W0 is not None
         ctx.save_for_backward(X, W, out, *([W0] if W0 is not None else []))
@@ -92,7 +98,7 @@ class _Rgcn(torch.autograd.Function):
         dX, dW = torch.empty_like(X), torch.empty_like(W)
         dW0 = torch.empty_like(W0) if W0 is not None else None
         B.rgnn_rgcn_bwd(ctx.graph.handle, ctx.desc, X, W, W0, out, ctx.saved_buf, dOut, dX, dW, dW0, ctx.ws, _stream())
-        return None, None, None, dX, dW, dW0
+        return None, None, None, None, dX, dW, dW0
 
 
 class _Hgt(torch.autograd.Function):
@@ -124,12 +130,12 @@ class _Hgt(torch.autograd.Function):
 def rgat(graph, X, W, w_s, w_t, slope=0.2, heads=1):
     """RGAT layer (listing of the single-headed RGAT layer in the thesis; with heads > 1 each head
     works on its slice of the d columns): out [N, d]."""
-    return _Rgat.apply(graph, float(slope), int(heads), X, W, w_s, w_t)
+    return _Rgat.apply(graph, torch.is_grad_enabled(), float(slope), int(heads), X, W, w_s, w_t)
 
 
 def rgcn(graph, X, W, W0=None, norm="in_degree_per_rel", act="none"):
     """RGCN layer, Eq. (rgcn): out [N, d]."""
-    return _Rgcn.apply(graph, norm, act, X, W, W0)
+    return _Rgcn.apply(graph, torch.is_grad_enabled(), norm, act, X, W, W0)
 
 
 def hgt(graph, X, Wk, Wq, Wv, Wo, Watt, Wmsg, mu=None):

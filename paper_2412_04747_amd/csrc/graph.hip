@@ -172,6 +172,18 @@ static rgnn_status_t download(std::vector<int32_t>& h, const int32_t* d, size_t 
 rgnn_status_t build_index_device(rgnn_graph* g, int format, const int32_t* a, const int32_t* b, const int32_t* relp,
                                  const int32_t* ntypep, const int32_t* rstp, const int32_t* rdtp, int mem);
 rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr);
+rgnn_status_t block_bounds(const rgnn_graph* g, int B, const int32_t* rel_ptr, const int32_t* node, std::vector<int32_t>& bound);
+
+static rgnn_status_t build_blocks(Uploader& U, ItemList& L, int64_t entries, const int32_t* rel_ptr, const int32_t* node) {
+    const rgnn_graph* g = U.g;
+    const int B = node_blocks(g->N, g->R, entries);
+    std::vector<int32_t> bound;
+    RGNN_TRY(block_bounds(g, B, rel_ptr, node, bound));
+    const BlockPlan p = plan_blocks(bound, g->R, B, block_cut(entries, g->num_cus));
+    L.num_items = (int32_t)p.beg.size(); L.num_partials = p.num_partials; L.num_split = (int32_t)p.split_row.size();
+    U.up({{&p.beg, &L.beg}, {&p.end, &L.end}, {&p.row, &L.row}, {&p.slot, &L.slot}, {&p.split_row, &L.split_row}, {&p.split_ptr, &L.split_ptr}});
+    return U.st;
+}
 
 static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const int32_t* b, const int32_t* relp,
                            const int32_t* ntypep, const int32_t* rstp, const int32_t* rdtp, int mem) {
@@ -241,6 +253,10 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
         build_tiles(U, relrun_ptr, kTileRows, {{&g->run_tiles_loop, loop_runs}, {&g->run_tiles, kMaxChunks}, {&g->run_tiles_wide, kWideChunksPerCU * cus},
                                                {&g->run_tiles_cu2, 2 * cus}, {&g->run_tiles_cu1, cus}});
         build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles_run_loop, std::max(cus - loop_runs, 1)}});
+    }
+    if (g->run_rows) {
+        RGNN_TRY(build_blocks(U, g->pair_blocks, g->P, g->idx[RGNN_IDX_PAIR_PTR], g->idx[RGNN_IDX_PAIR_SRC]));
+        RGNN_TRY(build_blocks(U, g->run_blocks, g->Q, g->idx[RGNN_IDX_RELRUN_PTR], g->relrun_dst));
     }
     for (ItemPlans::Request& r : plans.requests) upload_items(U, *r.list, r.plan.get());
     return U.st;

@@ -435,7 +435,8 @@ __global__ void k_several(long long Q, const int32_t* idx, const int32_t* run_pt
 // run i of the (relation, destination) order; incl: running counts of the runs with several edges in that order, num: in run order
 __global__ void k_run_rows(long long Q, const int32_t* relrun_idx, const int32_t* relrun_ptr, const int32_t* run_rel, const int32_t* run_ptr,
                            const int32_t* run_dst, const int32_t* in_src, const int32_t* incl, const int32_t* num, int32_t* run_row,
-                           int32_t* row_in, int32_t* row_dst, int32_t* multi_end) {
+                           int32_t* run_row_tag, int32_t* multi_run, int32_t* row_in, int32_t* row_dst, int32_t* row_run,
+                           int32_t* multi_end) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= Q) return;
     const int32_t q = relrun_idx[i], r = run_rel[q], b = relrun_ptr[r], e = relrun_ptr[r + 1], beg = run_ptr[q];
@@ -443,6 +444,9 @@ __global__ void k_run_rows(long long Q, const int32_t* relrun_idx, const int32_t
     const bool multi = run_ptr[q + 1] - beg > 1;
     const int32_t row = multi ? b + mine - 1 : b + several + ((int32_t)i - b - mine);
     run_row[q] = row;
+    row_run[row] = q;
+    run_row_tag[q] = multi ? (int32_t)((uint32_t)row | 0x80000000u) : row;
+    if (multi) multi_run[num[q] - 1] = q;
     row_dst[row] = run_dst[q];
     row_in[row] = multi ? (int32_t)((uint32_t)(num[q] - 1) | 0x80000000u) : in_src[beg];
     if (i == b) multi_end[r] = b + several;
@@ -462,15 +466,41 @@ __global__ void k_src_ptr(long long N, long long P, long long E, const int32_t* 
     if (u <= N) src_ptr[u] = srcpair_ptr[u] < P ? start[srcpair_idx[srcpair_ptr[u]]] : (int32_t)E;
 }
 __global__ void k_src_edges(long long E, const int32_t* out_epos, const int32_t* out_ptr, const int32_t* in_pair, const int32_t* in_run,
-                            const int32_t* run_row, const int32_t* start, const float* in_invc, int32_t* src_row, float* src_invc) {
+                            const int32_t* in_rel, const int32_t* in_cnt, const int32_t* run_row, const int32_t* start, const float* in_invc, int32_t* src_row,
+                            float* src_invc, int32_t* src_run, int32_t* src_rel, int32_t* in_spos) {
     const long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= E) return;
     const int32_t c = out_epos[j], p = in_pair[c], at = start[p] + ((int32_t)j - out_ptr[p]);
     src_row[at] = run_row[in_run[c]];
     src_invc[at] = in_invc[c];
+    src_run[at] = in_cnt[c] > 1 ? in_run[c] : (int32_t)((uint32_t)in_run[c] | 0x80000000u);
+    src_rel[at] = in_rel[c];
+    in_spos[c] = at;
 }
 
 }  // namespace
+
+// First entry of relation r = i / (B + 1) whose node is in block i % (B + 1) or later.  N * B < 2^63: both are int32.
+__global__ static void k_block_bound(long long n, int B, long long N, const int32_t* rel_ptr, const int32_t* node, int32_t* bound) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t r = (int32_t)(i / (B + 1)), b = (int32_t)(i % (B + 1));
+    const long long v = (N * b + B - 1) / B;               // blocks as equal as can be
+    int32_t lo = rel_ptr[r], hi = rel_ptr[r + 1];
+    while (lo < hi) {
+        const int32_t mid = lo + (hi - lo) / 2;
+        if (node[mid] < v) lo = mid + 1; else hi = mid;
+    }
+    bound[i] = lo;
+}
+rgnn_status_t block_bounds(const rgnn_graph* g, int B, const int32_t* rel_ptr, const int32_t* node, std::vector<int32_t>& bound) {
+    bound.resize((size_t)g->R * (B + 1));
+    Tmp t;
+    RGNN_TRY(t.alloc(bound.size() * sizeof(int32_t)));
+    LAUNCH(k_block_bound, bound.size(), (long long)bound.size(), B, (long long)g->N, rel_ptr, node, t.as<int32_t>());
+    RGNN_HIP(hipMemcpy(bound.data(), t.p, bound.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    return RGNN_OK;
+}
 
 // Fills g->run_row .. g->src_invc; src_ptr ([N + 1], edges by source) goes to the host.  E > 0.  Synchronous.
 rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr) {
@@ -486,19 +516,25 @@ rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr) {
     RGNN_TRY(keep<int32_t>(g, (size_t)g->R, &g->multi_end));
     RGNN_TRY(keep<int32_t>(g, (size_t)E, &g->src_row));
     RGNN_TRY(keep<float>(g, (size_t)E, &g->src_invc));
+    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->run_row_tag));
+    RGNN_TRY(keep<int32_t>(g, (size_t)g->num_multi_runs, &g->multi_run));
+    for (int32_t** p : {&g->src_run, &g->src_rel, &g->in_spos}) RGNN_TRY(keep<int32_t>(g, (size_t)E, p));
+    RGNN_TRY(keep<int32_t>(g, (size_t)P, &g->pair_spos));
+    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_run));
     RGNN_HIP(hipMemset(g->multi_end, 0, (size_t)g->R * sizeof(int32_t)));
     LAUNCH(k_several, (size_t)Q, Q, (const int32_t*)nullptr, g->idx[RGNN_IDX_RUN_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), b.as<int32_t>(), (size_t)Q));
     LAUNCH(k_several, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RUN_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), c.as<int32_t>(), (size_t)Q));
     LAUNCH(k_run_rows, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RELRUN_PTR], g->idx[RGNN_IDX_RUN_REL], g->idx[RGNN_IDX_RUN_PTR],
-           g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_IN_SRC], c.as<int32_t>(), b.as<int32_t>(), g->run_row, g->row_in, g->row_dst, g->multi_end);
+           g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_IN_SRC], c.as<int32_t>(), b.as<int32_t>(), g->run_row, g->run_row_tag,
+           g->multi_run, g->row_in, g->row_dst, g->row_run, g->multi_end);
     LAUNCH(k_pair_len, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], g->idx[RGNN_IDX_OUT_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), b.as<int32_t>(), (size_t)P));
-    LAUNCH(k_pair_start, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], a.as<int32_t>(), b.as<int32_t>(), c.as<int32_t>());
-    LAUNCH(k_src_ptr, (size_t)N + 1, N, P, E, g->idx[RGNN_IDX_SRCPAIR_PTR], g->idx[RGNN_IDX_SRCPAIR_IDX], c.as<int32_t>(), d.as<int32_t>());
+    LAUNCH(k_pair_start, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], a.as<int32_t>(), b.as<int32_t>(), g->pair_spos);
+    LAUNCH(k_src_ptr, (size_t)N + 1, N, P, E, g->idx[RGNN_IDX_SRCPAIR_PTR], g->idx[RGNN_IDX_SRCPAIR_IDX], g->pair_spos, d.as<int32_t>());
     LAUNCH(k_src_edges, (size_t)E, E, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_PTR], g->idx[RGNN_IDX_IN_PAIR], g->idx[RGNN_IDX_IN_RUN],
-           g->run_row, c.as<int32_t>(), g->in_invc, g->src_row, g->src_invc);
+           g->idx[RGNN_IDX_IN_REL], g->idx[RGNN_IDX_IN_CNT], g->run_row, g->pair_spos, g->in_invc, g->src_row, g->src_invc, g->src_run, g->src_rel, g->in_spos);
     src_ptr.resize((size_t)N + 1);
     RGNN_HIP(hipMemcpy(src_ptr.data(), d.p, src_ptr.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     return RGNN_OK;

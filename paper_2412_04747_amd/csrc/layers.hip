@@ -167,6 +167,52 @@ struct RgatBwdWs {
     float* tl_part; float* partial; float* run_partial;
     float* acc_dW; float* acc_dws; float* acc_dwt;      // RGNN_FLAG_ACCUMULATE: the parameter gradients of this call
 };
+// Rows per run (one head): Y[Q] product rows, A and lq as rgat_run_inputs leaves them (with the pieces of its cut runs), wsp = W w_s.
+// All of it lies in `saved`, so that the forward's scratch is no larger than that of the rows per pair.
+struct RgatRunSaved { float* Y; float* s_dst; float* ms; float* A; float* lq; float* wsp; float* wtp; float* partial; float* part_ms; };
+struct RgatRunBwdWs {
+    float* dH; float* weight; float* rowdot; float* stat; float* dz; float* ds_dst; float* ds_src; float* A; float* U; float* tl_part; float* partial; float* a_partial;
+    float* u_partial; float* acc_dW; float* acc_dws; float* acc_dwt;
+};
+inline bool rgat_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
+    return sched_rgat_run_rows(g->run_rows, d->heads, g->R, g->E, d->d_out, d->flags);
+}
+size_t carve_rgat_run_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgatRunSaved* s) {
+    Carver c(base);
+    const size_t Q = g->Q, M = g->num_multi_runs, rk = (size_t)g->R * d->d_in, parts = g->multi_run_items.num_partials;
+    s->Y = c.take<float>(Q * d->d_out);
+    s->s_dst = c.take<float>(Q);
+    s->ms = c.take<float>(2 * (size_t)g->N);
+    s->A = c.take<float>(M * d->d_in);
+    s->lq = c.take<float>(2 * Q);
+    s->wsp = c.take<float>(rk);
+    s->wtp = c.take<float>(rk);
+    s->partial = c.take<float>(parts * d->d_in);
+    s->part_ms = c.take<float>(2 * parts);
+    return c.off;
+}
+size_t carve_rgat_run_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgatRunBwdWs* w) {
+    Carver c(base);
+    const size_t Q = g->Q, rk = (size_t)g->R * d->d_in, rd = (size_t)g->R * d->d_out;
+    w->dH = c.take<float>(Q * d->d_in);
+    w->weight = c.take<float>(Q);
+    w->rowdot = c.take<float>(Q);
+    w->stat = c.take<float>(4 * Q);
+    w->dz = c.take<float>((size_t)g->E);
+    w->ds_dst = c.take<float>(Q);
+    w->ds_src = c.take<float>((size_t)g->P);
+    w->A = c.take<float>(rk);
+    w->U = c.take<float>(rk);
+    w->tl_part = c.take<float>(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, *run_chunks(g, d->d_out).f32_bwd));
+    w->partial = c.take<float>((size_t)g->src_items.num_partials * d->d_in);
+    w->a_partial = c.take<float>((size_t)g->pair_blocks.num_partials * d->d_in);
+    w->u_partial = c.take<float>((size_t)g->run_blocks.num_partials * d->d_in);
+    const bool acc = grads_accumulate(d);
+    w->acc_dW = acc ? c.take<float>(rk * d->d_out) : nullptr;
+    w->acc_dws = acc ? c.take<float>(rd) : nullptr;
+    w->acc_dwt = acc ? c.take<float>(rd) : nullptr;
+    return c.off;
+}
 // RGAT with one head, and up to width 64 with two or four: the gradient rows of single-edge pairs are not written per
 // pair; the typed-linear backward reads att_e * dOut[dst_e] through its row selector.
 inline bool rgat_row_select(const rgnn_layer_desc_t* d) { return sched_row_select(RGNN_LAYER_RGAT, d->dtype, d->d_out, d->heads, 0, 0, 0, d->flags); }
@@ -226,7 +272,7 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // ---- RGCN buffers -----------------------------------------------------------------------
 // Rows per run: A[m] = the mean (sum) of the input rows of the m-th run with several edges, fp32, or with bf16 rows in two planes of bf16; Hs holds a message row per run.
 struct RgcnFwdWs { void* Hs; float* partial; float* A; };
-inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_use_run_rows(g->run_rows, RGNN_LAYER_RGCN, g->E, d->d_out, d->flags); }
+inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, d->flags); }
 size_t carve_rgcn_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, float** A) {
     Carver c(base);
     if (rgcn_run_rows(g, d)) *A = c.take<float>((size_t)g->num_multi_runs * d->d_in);
@@ -440,6 +486,14 @@ rgnn_status_t tl_bwd(bool rows16, const Chunkings& tiles, int d, const void* X,
     b.ysel = ysel; b.dY_alt = static_cast<const float*>(y_alt); b.yscale = yscale; b.sums = sums;
     return typed_linear_bwd(d_in, d, b, st);
 }
+// A forward that keeps nothing (what fits the static scratch with rows per pair only takes those, with a workspace of the caller's too).
+bool rgat_run_rows_infer(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
+    if (!rgat_run_rows(g, d) || !sched_rgat_run_rows_infer(g->R, g->E, d->d_out)) return false;
+    RgatFwdWs fw; RgatSaved ps; RgatRunSaved rs;
+    const size_t f = align_up(carve_rgat_fwd(g, d, nullptr, &fw) + stage_bytes(g, RGNN_LAYER_RGAT, d, false));
+    const size_t most = RGNN_STATIC_SCRATCH_BYTES;
+    return f + carve_rgat_run_saved(g, d, nullptr, &rs) <= most || f + carve_rgat_saved(g, d, nullptr, &ps) > most;
+}
 }  // namespace
 
 extern "C" rgnn_status_t rgnn_workspace_bytes(const rgnn_graph_t* g, int32_t layer, const rgnn_layer_desc_t* desc,
@@ -451,8 +505,15 @@ extern "C" rgnn_status_t rgnn_workspace_bytes(const rgnn_graph_t* g, int32_t lay
     if (layer == RGNN_LAYER_RGAT) {
         RgatFwdWs fw; RgatBwdWs bw; RgatSaved sv;
         f = carve_rgat_fwd(g, desc, nullptr, &fw);
-        b = carve_rgat_bwd(g, desc, nullptr, &bw);
-        s = carve_rgat_saved(g, desc, nullptr, &sv);
+        if (rgat_run_rows(g, desc)) {
+            RgatRunBwdWs rb; RgatRunSaved rs;
+            b = carve_rgat_run_bwd(g, desc, nullptr, &rb);
+            s = carve_rgat_run_saved(g, desc, nullptr, &rs);
+            if (!rgat_run_rows_infer(g, desc)) s = std::max(s, carve_rgat_saved(g, desc, nullptr, &sv));
+        } else {
+            b = carve_rgat_bwd(g, desc, nullptr, &bw);
+            s = carve_rgat_saved(g, desc, nullptr, &sv);
+        }
     } else if (layer == RGNN_LAYER_RGCN) {
         RgcnFwdWs fw; RgcnBwdWs bw;
         f = carve_rgcn_fwd(g, desc, nullptr, &fw);
@@ -701,8 +762,8 @@ rgnn_status_t static_scratch(void** p) {
 }
 }  // namespace rgnn
 
-static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W,
-                                   const void* w_s, const void* w_t, void* out, void* saved, void* workspace, void* stream);
+static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W, const void* w_s,
+                                   const void* w_t, void* out, void* saved, void* workspace, void* stream);
 
 extern "C" rgnn_status_t rgnn_rgat_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X,
                                        const void* W, const void* w_s, const void* w_t, void* out, void* saved,
@@ -713,9 +774,12 @@ extern "C" rgnn_status_t rgnn_rgat_fwd(const rgnn_graph_t* g, const rgnn_layer_d
 extern "C" rgnn_status_t rgnn_rgat_fwd_static(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X,
                                               const void* W, const void* w_s, const void* w_t, void* out, void* saved,
                                               void* stream) {
-    size_t need = 0, sv = 0;
-    RGNN_TRY(rgnn_workspace_bytes(g, RGNN_LAYER_RGAT, desc, &need, nullptr, &sv));
-    if (!saved) need = align_up(need) + sv;      // inference: the would-be saved tensors are scratch too
+    size_t need = 0;
+    RGNN_TRY(rgnn_workspace_bytes(g, RGNN_LAYER_RGAT, desc, &need, nullptr, nullptr));
+    if (!saved) {                                // inference: the would-be saved tensors are scratch too
+        RgatSaved ps; RgatRunSaved rs;
+        need = align_up(need) + (rgat_run_rows_infer(g, desc) ? carve_rgat_run_saved(g, desc, nullptr, &rs) : carve_rgat_saved(g, desc, nullptr, &ps));
+    }
     if (need > (size_t)RGNN_STATIC_SCRATCH_BYTES)
         RGNN_FAIL(RGNN_EWORKSPACE, "rgnn_rgat_fwd_static: this call needs %zu bytes of scratch, the static buffer holds %zu",
                   need, (size_t)RGNN_STATIC_SCRATCH_BYTES);
@@ -724,8 +788,8 @@ extern "C" rgnn_status_t rgnn_rgat_fwd_static(const rgnn_graph_t* g, const rgnn_
     return rgat_fwd_impl(g, desc, X, W, w_s, w_t, out, saved, ws, stream);
 }
 
-static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W,
-                                   const void* w_s, const void* w_t, void* out, void* saved, void* workspace, void* stream) {
+static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W, const void* w_s,
+                                   const void* w_t, void* out, void* saved, void* workspace, void* stream) {
     RGNN_TRY(check_desc(g, desc, RGNN_LAYER_RGAT));
     ScheduleFlagsScope sched_scope(desc->flags);
     if (missing(g, X) || !W || !w_s || !w_t || missing(g, out)) RGNN_FAIL(RGNN_EINVAL, "a required tensor pointer is NULL");
@@ -734,6 +798,7 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     const int D = desc->d_out, K = desc->d_in;
     RgatFwdWs w; RgatSaved sv;
     const size_t carved = carve_rgat_fwd(g, desc, workspace, &w);
+    const bool runs = saved ? rgat_run_rows(g, desc) : rgat_run_rows_infer(g, desc);
     saved = saved_or_scratch(g, RGNN_LAYER_RGAT, desc, saved, workspace, carved);
     Bf16Stage stg(workspace, carved, desc->dtype == RGNN_BF16, st);
     X = stg.in(X, (size_t)g->N * K);
@@ -741,8 +806,23 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     w_s = stg.in(w_s, (size_t)g->R * D);
     w_t = stg.in(w_t, (size_t)g->R * D);
     RGNN_TRY(stg.status);
-    carve_rgat_saved(g, desc, saved, &sv);
     const float *Xf = static_cast<const float*>(X), *Wf = static_cast<const float*>(W);
+    if (runs) {
+        RgatRunSaved rs;
+        carve_rgat_run_saved(g, desc, saved, &rs);
+        const float *ws = static_cast<const float*>(w_s), *wt = static_cast<const float*>(w_t);
+        // 1. wsp = W w_s, wtp = W w_t, and the destination halves of the logits
+        RGNN_TRY(fold_weight(fold_args(g->R, K, D, 1, Wf, ws, rs.wsp, wt, rs.wtp), st));
+        RGNN_TRY(rgat_run_logit(g, K, Xf, rs.wtp, rs.s_dst, st));
+        // 2. the inputs of the runs with several edges, weighted within the run;  3. Y = A W, a run with one edge reading its source's row
+        RGNN_TRY(rgat_run_inputs(g, K, Xf, rs.wsp, rs.s_dst, desc->slope, rs.A, rs.lq, rs.partial, rs.part_ms, st));
+        TypedLinearArgs a{};
+        a.tiles = run_chunks(g, D).f32; a.X = Xf; a.X2 = rs.A; a.gather = g->row_in; a.W = Wf; a.Y = rs.Y; a.sign_matters = 1;
+        RGNN_TRY(typed_linear_fwd(K, D, a, st));
+        // 4. per destination over its runs: softmax and weighted sum
+        return rgat_run_aggregate(g, D, rs.Y, ws, rs.s_dst, desc->slope, rs.lq, static_cast<float*>(out), rs.ms, w.partial, w.part_ms, st);
+    }
+    carve_rgat_saved(g, desc, saved, &sv);
     const bool fused = rgat_fused(desc);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[r]
     //    (the comparison schedules also take the source half of the logit per pair, s_src[p] = Hs[p] . w_s[r])
@@ -780,6 +860,44 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
                               sv.ms, w.partial, w.part_ms, st);
 }
 
+// Rows per run; X .. dOut in fp32.
+static rgnn_status_t rgat_run_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const float* X, const float* W, const float* w_s,
+                                  const float* w_t, const void* saved, const float* dOut, float* dX, void* dW, void* dw_s, void* dw_t,
+                                  const RgatRunBwdWs& w, hipStream_t st) {
+    const int D = desc->d_out, K = desc->d_in;
+    RgatRunSaved sv;
+    carve_rgat_run_saved(g, desc, const_cast<void*>(saved), &sv);
+    GradAcc ga;
+    dW = ga.route(w.acc_dW, dW, (size_t)g->R * K * D);
+    dw_s = ga.route(w.acc_dws, dw_s, (size_t)g->R * D);
+    dw_t = ga.route(w.acc_dwt, dw_t, (size_t)g->R * D);
+    ShareSums sums;
+    auto pieces = [&](const ItemList& L, const float* partial, float* to) {
+        return SumArgs{partial, L.split_row, L.split_ptr, to, (size_t)L.num_partials * K, (size_t)g->R * K, L.num_split, K, 1};
+    };
+    RGNN_TRY(rgat_run_weights(g, sv.ms, sv.lq, w.weight, st));
+    // 1. dH[q] = dOut[dst_q] W[r]^T;  dW[r] = sum over r's runs of (weight A[q])^T dOut[dst_q];  rowdot = dH[q] . weight A[q]
+    TypedLinearBwdArgs b{};
+    b.tiles = run_chunks(g, D).f32_bwd; b.X = X; b.X2 = sv.A; b.gather = g->row_in; b.W = W; b.dY = dOut; b.ysel = g->row_dst; b.yscale = w.weight;
+    b.rowdot = w.rowdot; b.num = g->row_run;
+    b.dXrow = w.dH; b.dW = static_cast<float*>(dW); b.part = w.tl_part; b.sums = &sums;
+    RGNN_TRY(typed_linear_bwd(K, D, b, st));
+    // 2. what the edges of a run need
+    RGNN_TRY(rgat_run_stat(g, desc->slope, w.rowdot, w.weight, sv.ms, sv.lq, sv.s_dst, w.stat, w.ds_dst, st));
+    // 3. per source over its edges: dz, and dX without the destination halves
+    RGNN_TRY(rgat_source_walk(g, K, X, w.dH, sv.wsp, w.stat, desc->slope, w.dz, dX, grads_accumulate(desc), w.partial, st));
+    // 4. sums of dz over the runs with several edges;  A[r] = sum over r's pairs of ds_src X[src], U[r] = sum over r's runs of ds_dst X[dst]
+    RGNN_TRY(segment_scalar_sum((int)g->Q, g->idx[RGNN_IDX_RUN_PTR], g->long_runs, g->in_spos, w.dz, 1, 0, w.ds_dst, st, "ds_dst_sum", 2));
+    RGNN_TRY(rgat_block_sums(g, K, X, w.dz, w.ds_src, w.ds_dst, w.A, w.a_partial, w.U, w.u_partial, st));
+    sums.pieces = pieces(g->pair_blocks, w.a_partial, w.A);
+    sums.pieces2 = pieces(g->run_blocks, w.u_partial, w.U);
+    RGNN_TRY(sums.launch(st));
+    // 5. dX[v] += sum over v's runs of ds_dst[q] (W[r] w_t[r]);  dw_s = A W, dw_t = U W, dW += A^T (x) w_s + U^T (x) w_t
+    const RgatFinish fin{g->R, K, D, 1, W, w_s, w_t, w.A, w.U, static_cast<float*>(dW), static_cast<float*>(dw_s), static_cast<float*>(dw_t), 0};
+    RGNN_TRY(rgat_run_term(g, K, w.ds_dst, sv.wtp, dX, fin, st));
+    return ga.flush(st);
+}
+
 extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X,
                                        const void* W, const void* w_s, const void* w_t, const void* out,
                                        const void* saved, const void* dOut, void* dX, void* dW, void* dw_s,
@@ -791,14 +909,18 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     if (!workspace || !saved) RGNN_FAIL(RGNN_EWORKSPACE, "workspace or saved is NULL");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int D = desc->d_out, K = desc->d_in;
-    RgatBwdWs w; RgatSaved sv;
-    Bf16Stage stg(workspace, carve_rgat_bwd(g, desc, workspace, &w), desc->dtype == RGNN_BF16, st);
+    RgatBwdWs w; RgatSaved sv; RgatRunBwdWs rw;
+    const bool runs = rgat_run_rows(g, desc);
+    Bf16Stage stg(workspace, runs ? carve_rgat_run_bwd(g, desc, workspace, &rw) : carve_rgat_bwd(g, desc, workspace, &w), desc->dtype == RGNN_BF16, st);
     X = stg.in(X, (size_t)g->N * K);
     W = stg.in(W, (size_t)g->R * K * D);
     w_s = stg.in(w_s, (size_t)g->R * D);
     w_t = stg.in(w_t, (size_t)g->R * D);
     dOut = stg.in(dOut, (size_t)g->N * D);
     RGNN_TRY(stg.status);
+    if (runs)
+        return rgat_run_bwd(g, desc, static_cast<const float*>(X), static_cast<const float*>(W), static_cast<const float*>(w_s), static_cast<const float*>(w_t),
+                            saved, static_cast<const float*>(dOut), static_cast<float*>(dX), dW, dw_s, dw_t, rw, st);
     carve_rgat_saved(g, desc, const_cast<void*>(saved), &sv);
     const float* Xf = static_cast<const float*>(X);
     const float* Wf = static_cast<const float*>(W);

@@ -36,6 +36,7 @@ struct FusedArgs {
     const int32_t* in_rel;    // [E]
     const int32_t* in_run;    // [E]
     const float* Hs;          // [P][D]
+    float2* lq;               // rows per run: (max, sum of exp) of a run's logits
     const float* w_s;         // [R][D]
     const float* s_dst;       // [Q][H]
     float slope;
@@ -60,6 +61,13 @@ struct FusedArgs {
 
 __device__ __forceinline__ float leaky(float z, float slope) { return z > 0.f ? z : slope * z; }
 
+// What a forward walk goes over:
+//   kPairs      the edges of a destination; row in_pair[e] of Hs
+//   kRunInputs  the edges of a run; row in_pair[e] (the source) of Hs (X), which stays cached; (m, s) go to lq[the run]
+//   kRuns       the runs of a destination; row in_pair[q] of Hs, the top bit set for a run with several edges, whose logit and weight are
+//               lq[q]; the others' are kept there
+enum Walk { kPairs, kRunInputs, kRuns };
+
 // row of w_s for relation r: columns 4c..4c+3
 template <int D, bool LDSW>
 __device__ __forceinline__ float4 ws_row(const FusedArgs& a, const float* ws_lds, int r, int c) {
@@ -71,10 +79,23 @@ __device__ __forceinline__ float4 load_row_nt(const float* p) {
     return make_float4(t[0], t[1], t[2], t[3]);
 }
 
+template <int MODE>
+__device__ __forceinline__ float4 walk_row(const float* p) { return MODE == kRunInputs ? *reinterpret_cast<const float4*>(p) : load_row_nt(p); }
+template <int MODE, int D>
+__device__ __forceinline__ const float* row_at(const float* rows, int i) { return rows + (size_t)(MODE == kRuns ? i & 0x7FFFFFFF : i) * D; }
+
 // ---------------------------------------------------------------- forward
 
+// kRuns: logit and weight of a run with several edges in place of its destination half
+__device__ __forceinline__ void take_run(const FusedArgs& a, int tagged, int q, float& sd, float& w) {
+    float2 l = a.lq[q];                        // (unconditional; what lies there for a run with one edge is not used)
+    asm volatile("" : "+v"(l.x), "+v"(l.y), "+v"(sd));      // ... and kept so: a branch here would part the lanes that hand values round
+    sd = tagged < 0 ? l.x : sd;
+    w = tagged < 0 ? l.y : 1.f;
+}
+
 // General items: any length, whole destinations or pieces of cut ones.
-template <int D, int LPH, bool LDSW>
+template <int D, int LPH, bool LDSW, int MODE>
 __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_lds, int i, int c) {
     constexpr int LPR = D / 4, H = LPR / LPH;
     const int head = c / LPH;
@@ -83,13 +104,16 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
     const size_t v = (size_t)a.it.row[i];
     float4 acc0 = make_float4(0.f, 0.f, 0.f, 0.f), acc1 = acc0;
     float m = -INFINITY, s = 0.f;
+    int run = 0;                                             // kRunInputs: the run
     if (b < e) {
         // indices of chunk 0 (entries past the end repeat the last edge; they get weight zero)
         int jj = min(b + c, e - 1);
         // one head: lane c also fetches the destination half of edge c's logit; several heads: the run id, and every
         // lane reads its own head's entry when the batch is formed
-        int cpr = a.in_pair[jj], crl = a.in_rel[jj], crn = a.in_run[jj];
-        float csd = H == 1 ? a.s_dst[crn] : 0.f;
+        int cpr = a.in_pair[jj], crl = a.in_rel[jj], crn = MODE == kRuns ? jj : a.in_run[jj];
+        if (MODE == kRunInputs) run = crn;
+        float csd = H == 1 ? a.s_dst[crn] : 0.f, cw = 1.f;     // kRuns: cw its weight, csd its logit where it has several edges
+        if (MODE == kRuns) take_run(a, cpr, jj, csd, cw);
         for (int jc = b; jc < e; jc += LPR) {
             const bool more = jc + LPR < e;
             int npr = cpr, nrl = crl, nrn = 0;
@@ -97,7 +121,7 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
                 jj = min(jc + LPR + c, e - 1);
                 npr = a.in_pair[jj];
                 nrl = a.in_rel[jj];
-                nrn = a.in_run[jj];
+                nrn = MODE == kRuns ? jj : a.in_run[jj];
             }
             const int cend = min(LPR, e - jc);
 #pragma unroll
@@ -105,10 +129,11 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
                 if (k >= cend) break;
                 float4 h[4];
                 float sd[4];
+                int pr[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int pr = group_lane<LPR>(cpr, k + u);
-                    h[u] = load_row_nt(a.Hs + (size_t)pr * D + c * 4);
+                    pr[u] = group_lane<LPR>(cpr, k + u);
+                    h[u] = walk_row<MODE>(row_at<MODE, D>(a.Hs, pr[u]) + c * 4);
                     if (H > 1) sd[u] = a.s_dst[(size_t)group_lane<LPR>(crn, k + u) * H + head];
                 }
                 __builtin_amdgcn_sched_barrier(0);      // the w_s rows are read when the message rows arrive, not held meanwhile
@@ -116,12 +141,27 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const float4 w = ws_row<D, LDSW>(a, ws_lds, group_lane<LPR>(crl, k + u), c);
-                    const float z = group_sum<LPH>(dot4(h[u], w)) + (H == 1 ? group_lane<LPR>(csd, k + u) : sd[u]);
-                    l[u] = k + u < cend ? leaky(z, a.slope) : -INFINITY;
+                    const float add = H == 1 ? group_lane<LPR>(csd, k + u) : sd[u];
+                    float z = group_sum<LPH>(dot4(h[u], w)) + add;
+                    z = leaky(z, a.slope);
+                    if (MODE == kRuns && pr[u] < 0) z = add;
+                    l[u] = k + u < cend ? z : -INFINITY;
+                }
+                if (MODE == kRuns) {
+                    float mine = 0.f;                         // lane u keeps the logit of run u where that is its only edge's
+                    int mpr = -1;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (c == u) { mine = l[u]; mpr = pr[u]; }
+                    if (c < 4 && k + c < cend && mpr >= 0) a.lq[jc + k + c] = make_float2(mine, 1.f);
                 }
                 const float mn = fmaxf(fmaxf(m, fmaxf(l[0], l[1])), fmaxf(l[2], l[3]));
                 const float sc = __expf(m - mn);              // 0 in the first batch (m = -inf), 1 while the maximum stands
-                const float p0 = __expf(l[0] - mn), p1 = __expf(l[1] - mn), p2 = __expf(l[2] - mn), p3 = __expf(l[3] - mn);
+                float p0 = __expf(l[0] - mn), p1 = __expf(l[1] - mn), p2 = __expf(l[2] - mn), p3 = __expf(l[3] - mn);
+                if (MODE == kRuns) {
+                    p0 *= group_lane<LPR>(cw, k); p1 *= group_lane<LPR>(cw, k + 1);
+                    p2 *= group_lane<LPR>(cw, k + 2); p3 *= group_lane<LPR>(cw, k + 3);
+                }
                 s = s * sc + ((p0 + p1) + (p2 + p3));
                 acc0.x *= sc; acc0.y *= sc; acc0.z *= sc; acc0.w *= sc;
                 acc1.x *= sc; acc1.y *= sc; acc1.z *= sc; acc1.w *= sc;
@@ -133,6 +173,7 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
             }
             if (more) {
                 if (H == 1) csd = a.s_dst[nrn];
+                if (MODE == kRuns) take_run(a, npr, nrn, csd, cw);
                 cpr = npr;
                 crl = nrl;
                 crn = nrn;
@@ -143,7 +184,9 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
     if (slot < 0) {
         const float inv = s > 0.f ? 1.f / s : 0.f;           // a destination without edges gets the zero row
         *reinterpret_cast<float4*>(a.out + v * D + c * 4) = make_float4(acc0.x * inv, acc0.y * inv, acc0.z * inv, acc0.w * inv);
-        if (c % LPH == 0) a.ms[v * H + head] = make_float2(b < e ? m : 0.f, b < e ? s : 1.f);
+        if (MODE == kRunInputs) {
+            if (c == 0) a.lq[run] = make_float2(m, s);
+        } else if (c % LPH == 0) a.ms[v * H + head] = make_float2(b < e ? m : 0.f, b < e ? s : 1.f);
     } else {
         *reinterpret_cast<float4*>(a.partial + (size_t)slot * D + c * 4) = acc0;
         if (c % LPH == 0) a.part_ms[(size_t)slot * H + head] = make_float2(m, s);
@@ -151,7 +194,7 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
 }
 
 // Whole destinations with 2..kShortLen edges: two per lane group, every load of both independent.
-template <int D, int LPH, bool LDSW>
+template <int D, int LPH, bool LDSW, int MODE>
 __device__ __forceinline__ void fwd_short(const FusedArgs& a, const float* ws_lds, int g2, int c) {
     constexpr int LPR = D / 4, H = LPR / LPH;
     const int head = c / LPH;
@@ -172,16 +215,18 @@ __device__ __forceinline__ void fwd_short(const FusedArgs& a, const float* ws_ld
             const int jj = min(b[q] + u, e[q] - 1);
             pr[q][u] = a.in_pair[jj];
             rl[q][u] = a.in_rel[jj];
-            rn[q][u] = a.in_run[jj];
+            rn[q][u] = MODE == kRuns ? jj : a.in_run[jj];
         }
     float4 h[2][kShortLen];
-    float sd[2][kShortLen];
+    float sd[2][kShortLen], rw[2][kShortLen];
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int u = 0; u < kShortLen; ++u) {
-            h[q][u] = load_row_nt(a.Hs + (size_t)pr[q][u] * D + c * 4);
+            h[q][u] = walk_row<MODE>(row_at<MODE, D>(a.Hs, pr[q][u]) + c * 4);
             sd[q][u] = a.s_dst[(size_t)rn[q][u] * H + head];
+            rw[q][u] = 1.f;
+            if (MODE == kRuns) take_run(a, pr[q][u], rn[q][u], sd[q][u], rw[q][u]);
         }
     __builtin_amdgcn_sched_barrier(0);      // the w_s rows are read when the message rows arrive, not held meanwhile
 #pragma unroll
@@ -190,28 +235,33 @@ __device__ __forceinline__ void fwd_short(const FusedArgs& a, const float* ws_ld
 #pragma unroll
         for (int u = 0; u < kShortLen; ++u) {
             const float4 w = ws_row<D, LDSW>(a, ws_lds, rl[q][u], c);
-            const float z = group_sum<LPH>(dot4(h[q][u], w)) + sd[q][u];
-            l[u] = b[q] + u < e[q] ? leaky(z, a.slope) : -INFINITY;
+            float z = leaky(group_sum<LPH>(dot4(h[q][u], w)) + sd[q][u], a.slope);
+            if (MODE == kRuns && pr[q][u] < 0) z = sd[q][u];
+            l[u] = b[q] + u < e[q] ? z : -INFINITY;
+            if (MODE == kRuns && c == u && i0 + q < a.short_n && b[q] + u < e[q] && pr[q][u] >= 0) a.lq[b[q] + u] = make_float2(z, 1.f);
             m = fmaxf(m, l[u]);
         }
         float s = 0.f;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int u = 0; u < kShortLen; ++u) {
-            const float p = __expf(l[u] - m);
+            float p = __expf(l[u] - m);
+            if (MODE == kRuns) p *= rw[q][u];
             s += p;
             fma4(acc, p, h[q][u]);
         }
         if (i0 + q < a.short_n) {
             const float inv = 1.f / s;
             *reinterpret_cast<float4*>(a.out + (size_t)orow[q] * D + c * 4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-            if (c % LPH == 0) a.ms[(size_t)orow[q] * H + head] = make_float2(m, s);
+            if (MODE == kRunInputs) {
+                if (c == 0) a.lq[rn[q][0]] = make_float2(m, s);
+            } else if (c % LPH == 0) a.ms[(size_t)orow[q] * H + head] = make_float2(m, s);
         }
     }
 }
 
 // Whole destinations with one edge (attention weight 1): four per lane group.
-template <int D, int LPH, bool LDSW>
+template <int D, int LPH, bool LDSW, int MODE>
 __device__ __forceinline__ void fwd_single(const FusedArgs& a, const float* ws_lds, int g4, int c) {
     constexpr int LPR = D / 4, H = LPR / LPH;
     const int head = c / LPH;
@@ -227,23 +277,27 @@ __device__ __forceinline__ void fwd_single(const FusedArgs& a, const float* ws_l
     for (int u = 0; u < 4; ++u) {
         pr[u] = a.in_pair[j[u]];
         rl[u] = a.in_rel[j[u]];
-        rn[u] = a.in_run[j[u]];
+        rn[u] = MODE == kRuns ? j[u] : a.in_run[j[u]];
     }
     float4 h[4];
-    float sd[4];
+    float sd[4], rw[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        h[u] = load_row_nt(a.Hs + (size_t)pr[u] * D + c * 4);
+        h[u] = walk_row<MODE>(row_at<MODE, D>(a.Hs, pr[u]) + c * 4);
         sd[u] = a.s_dst[(size_t)rn[u] * H + head];
+        rw[u] = 1.f;
+        if (MODE == kRuns) take_run(a, pr[u], rn[u], sd[u], rw[u]);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const float4 w = ws_row<D, LDSW>(a, ws_lds, rl[u], c);
-        const float z = group_sum<LPH>(dot4(h[u], w)) + sd[u];
+        float z = leaky(group_sum<LPH>(dot4(h[u], w)) + sd[u], a.slope);
+        if (MODE == kRuns && pr[u] < 0) z = sd[u];
         if (i0 + u < a.single_n) {
             *reinterpret_cast<float4*>(a.out + (size_t)orow[u] * D + c * 4) = h[u];
-            if (c % LPH == 0) a.ms[(size_t)orow[u] * H + head] = make_float2(leaky(z, a.slope), 1.f);
+            if (MODE == kRuns && c == 0 && pr[u] >= 0) a.lq[j[u]] = make_float2(z, 1.f);
+            if (c % LPH == 0) a.ms[(size_t)orow[u] * H + head] = make_float2(z, rw[u]);
         }
     }
 }
@@ -260,15 +314,16 @@ __device__ __forceinline__ const float* stage_ws(const FusedArgs& a) {
     return ws_lds;
 }
 
-template <int D, int LPH, bool LDSW>
+template <int D, int LPH, bool LDSW, int MODE>
 __global__ __launch_bounds__(kFusedThreads) void rgat_aggregate_fwd_kernel(FusedArgs a) {
     constexpr int LPR = D / 4, GPB = kFusedThreads / LPR;
     const float* ws_lds = stage_ws<D, LDSW>(a);
     const int grp = threadIdx.x / LPR, c = threadIdx.x % LPR;
     const int stride = gridDim.x * GPB, first = blockIdx.x * GPB + grp;
-    for (int i = first; i < a.general_n; i += stride) fwd_general<D, LPH, LDSW>(a, ws_lds, i >= a.skip_first ? i + a.skip_n : i, c);
-    for (int g2 = first; 2 * g2 < a.short_n; g2 += stride) fwd_short<D, LPH, LDSW>(a, ws_lds, g2, c);
-    for (int g4 = first; 4 * g4 < a.single_n; g4 += stride) fwd_single<D, LPH, LDSW>(a, ws_lds, g4, c);
+    for (int i = first; i < a.general_n; i += stride) fwd_general<D, LPH, LDSW, MODE>(a, ws_lds, i >= a.skip_first ? i + a.skip_n : i, c);
+    for (int g2 = first; 2 * g2 < a.short_n; g2 += stride) fwd_short<D, LPH, LDSW, MODE>(a, ws_lds, g2, c);
+    if (MODE != kRunInputs)                     // (those have several edges)
+        for (int g4 = first; 4 * g4 < a.single_n; g4 += stride) fwd_single<D, LPH, LDSW, MODE>(a, ws_lds, g4, c);
 }
 
 // ---------------------------------------------------------------- backward
@@ -412,27 +467,62 @@ rgnn_status_t launch_fused(K kernel, const rgnn_graph* g, size_t lds, size_t gro
         else RGNN_FAIL(RGNN_EUNSUPPORTED, "fused RGAT traversal: width %d with %d heads is not built", (int)(D_), (int)(H_)); \
     } while (0)
 
-rgnn_status_t rgat_aggregate_fwd(const rgnn_graph* g, int D, int H, const float* Hs, const float* w_s, const float* s_dst,
-                                 float slope, float* out, float* ms, float* partial, float* part_ms, hipStream_t st) {
-    const ItemList& L = g->dst_items;
-    if (L.num_items == 0) return RGNN_OK;
-    const int ns = batched_count(L.num_single, current_schedule_flags());
+// the walk over a list: fills a's item fields
+template <int MODE>
+static rgnn_status_t launch_walk(const rgnn_graph* g, const ItemList& L, int D, int H, FusedArgs a, const char* label, hipStream_t st) {
+    const int ns = MODE == kRunInputs ? 0 : batched_count(L.num_single, current_schedule_flags());
     const int nsh = batched_count(L.num_short, current_schedule_flags());
-    FusedArgs a{};
-    a.it = dev_items(L); a.in_pair = g->idx[RGNN_IDX_IN_PAIR]; a.in_rel = g->idx[RGNN_IDX_IN_REL]; a.in_run = g->idx[RGNN_IDX_IN_RUN];
-    a.Hs = Hs; a.w_s = w_s; a.s_dst = s_dst; a.slope = slope; a.R = g->R;
-    a.out = out; a.ms = reinterpret_cast<float2*>(ms); a.partial = partial; a.part_ms = reinterpret_cast<float2*>(part_ms);
+    a.it = dev_items(L); a.R = g->R;
     a.general_n = L.num_items - nsh - ns; a.skip_first = nsh > 0 ? L.first_short : L.first_single; a.skip_n = nsh + ns;
     a.short_first = L.first_short; a.short_n = nsh; a.single_first = L.first_single; a.single_n = ns;
     const size_t lds = (size_t)g->R * D * sizeof(float);
     const bool ldsw = sched_ws_in_lds(g->R, D);
     const size_t groups = std::max<size_t>({(size_t)a.general_n, (size_t)(nsh + 1) / 2, (size_t)(ns + 3) / 4});
-    {
-        KernelTimer kt(st, "aggregate_fwd");
-        if (ldsw) RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, true>, g, lds, groups, DD / 4, a, st)));
-        else RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, false>, g, 0, groups, DD / 4, a, st)));
+    KernelTimer kt(st, label);
+    if constexpr (MODE == kPairs) {
+        if (ldsw) RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, true, MODE>, g, lds, groups, DD / 4, a, st)));
+        else RGNN_DISPATCH_DH(D, H, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, LL, false, MODE>, g, 0, groups, DD / 4, a, st)));
+    } else {
+        if (ldsw) RGNN_DISPATCH_D(D, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, DD / 4, true, MODE>, g, lds, groups, DD / 4, a, st)));
+        else RGNN_DISPATCH_D(D, RGNN_TRY(launch_fused(rgat_aggregate_fwd_kernel<DD, DD / 4, false, MODE>, g, 0, groups, DD / 4, a, st)));
     }
+    return RGNN_OK;
+}
+
+rgnn_status_t rgat_aggregate_fwd(const rgnn_graph* g, int D, int H, const float* Hs, const float* w_s, const float* s_dst,
+                                 float slope, float* out, float* ms, float* partial, float* part_ms, hipStream_t st) {
+    const ItemList& L = g->dst_items;
+    if (L.num_items == 0) return RGNN_OK;
+    FusedArgs a{};
+    a.in_pair = g->idx[RGNN_IDX_IN_PAIR]; a.in_rel = g->idx[RGNN_IDX_IN_REL]; a.in_run = g->idx[RGNN_IDX_IN_RUN];
+    a.Hs = Hs; a.w_s = w_s; a.s_dst = s_dst; a.slope = slope;
+    a.out = out; a.ms = reinterpret_cast<float2*>(ms); a.partial = partial; a.part_ms = reinterpret_cast<float2*>(part_ms);
+    RGNN_TRY(launch_walk<kPairs>(g, L, D, H, a, "aggregate_fwd", st));
     return combine_softmax(L, D, H, partial, part_ms, out, 0, ms, false, 1, "aggregate_fwd.combine", st);
+}
+
+rgnn_status_t rgat_run_inputs(const rgnn_graph* g, int K, const float* X, const float* wsp, const float* s_dst, float slope, float* A, float* lq,
+                              float* partial, float* part_ms, hipStream_t st) {
+    const ItemList& L = g->multi_run_items;
+    if (L.num_items == 0) return RGNN_OK;
+    FusedArgs a{};
+    a.in_pair = g->idx[RGNN_IDX_IN_SRC]; a.in_rel = g->idx[RGNN_IDX_IN_REL]; a.in_run = g->idx[RGNN_IDX_IN_RUN];
+    a.Hs = X; a.w_s = wsp; a.s_dst = s_dst; a.slope = slope; a.lq = reinterpret_cast<float2*>(lq);
+    a.out = A; a.partial = partial; a.part_ms = reinterpret_cast<float2*>(part_ms);
+    RGNN_TRY(launch_walk<kRunInputs>(g, L, K, 1, a, "run_inputs", st));
+    return combine_softmax(L, K, 1, partial, part_ms, A, 0, lq, false, 1, "run_inputs.combine", st, g->multi_run);
+}
+
+rgnn_status_t rgat_run_aggregate(const rgnn_graph* g, int D, const float* Y, const float* w_s, const float* s_dst, float slope, float* lq, float* out,
+                                 float* ms, float* partial, float* part_ms, hipStream_t st) {
+    const ItemList& L = g->dstrun_items;
+    if (L.num_items == 0) return RGNN_OK;
+    FusedArgs a{};
+    a.in_pair = g->run_row_tag; a.in_rel = g->idx[RGNN_IDX_RUN_REL];
+    a.Hs = Y; a.w_s = w_s; a.s_dst = s_dst; a.slope = slope; a.lq = reinterpret_cast<float2*>(lq);
+    a.out = out; a.ms = reinterpret_cast<float2*>(ms); a.partial = partial; a.part_ms = reinterpret_cast<float2*>(part_ms);
+    RGNN_TRY(launch_walk<kRuns>(g, L, D, 1, a, "aggregate_fwd", st));
+    return combine_softmax(L, D, 1, partial, part_ms, out, 0, ms, false, 1, "aggregate_fwd.combine", st);
 }
 
 rgnn_status_t rgat_edge_dot_bwd(const rgnn_graph* g, int D, int H, const float* Hs, const float* w_s, const float* s_dst,

@@ -149,16 +149,23 @@ struct rgnn_graph {
     bool run_rows = false;
     int64_t num_multi_runs = 0, num_single_runs = 0;
     int32_t* run_row = nullptr;            // [Q] row of a run
+    int32_t* run_row_tag = nullptr;        // [Q] the same, with the top bit set when the run has several edges
+    int32_t* multi_run = nullptr;          // [num_multi_runs] run of each number
     int32_t* row_in = nullptr;             // [Q] by row: source of the run's only edge, or the top bit | number of the run among those
                                            // with several edges, in run order
     int32_t* row_dst = nullptr;            // [Q] by row: destination
     int32_t* multi_end = nullptr;          // [R] end of a relation's rows of runs with several edges
     int32_t* src_row = nullptr;            // [E] by (source, relation, CSR position): row of the edge's run
     float* src_invc = nullptr;             // [E] 1 / c_{v,r} of that edge
+    int32_t *src_run = nullptr, *src_rel = nullptr;       // [E] its run, with the top bit set when it is the run's only edge, and its relation
+    int32_t* in_spos = nullptr;            // [E] place in that order of a CSR edge
+    int32_t* pair_spos = nullptr;          // [P] and of a pair's first edge
+    int32_t* row_run = nullptr;            // [Q] run of a row
     rgnn::TileList run_tiles, run_tiles_wide, run_tiles_cu2, run_tiles_cu1, run_tiles_loop, all_tiles_run_loop;   // as those of the pairs
     rgnn::ItemList multi_run_items;        // CSR edges of the runs with several edges (row: their number)
     rgnn::ItemList dstrun_items;           // runs by destination
     rgnn::ItemList src_items;              // edges by source
+    rgnn::ItemList pair_blocks, run_blocks;               // pairs, and runs, by relation and block of nodes (plan_blocks)
     rgnn::LongList long_runs;              // runs (run_ptr) too long for one lane
     rgnn::LongList long_pairs;             // pairs (out_ptr) too long for one lane
     std::vector<void*> allocs;             // every device allocation, for destroy
@@ -206,7 +213,7 @@ struct SumArgs {
     __host__ __device__ int64_t blocks() const { return (int64_t)num_split * copies * (D / 16); }
 };
 // What backward typed linears leave to be summed: dW[s] (kn floats) and, when given, dW2[s] (kd floats) = sums of segment s's slots of
-// kn + kd floats each, for up to kMax lists, and optionally pieces as above.  One launch (traversal.hip) sums them all.
+// kn + kd floats each, for up to kMax lists, and optionally two sets of pieces as above.  One launch (traversal.hip) sums them all.
 struct ShareSums {
     static constexpr int kMax = 4;
     enum { kMany, kUneven, kFew };           // how a list's slots lie (traversal.hip)
@@ -217,7 +224,7 @@ struct ShareSums {
     };
     Job job[kMax];
     int n = 0;
-    SumArgs pieces{};
+    SumArgs pieces{}, pieces2{};
     rgnn_status_t add(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2);
     rgnn_status_t launch(hipStream_t st);      // and is empty again
 };
@@ -249,7 +256,10 @@ struct TypedLinearBwdArgs {
     const float* hcoef = nullptr;    // [rows][2][sel_heads]
     const float* wvec = nullptr;     // [segs][ND]
     int sel_heads = 0;
-    const float* X2 = nullptr;       // gather[i] < 0: row i of X is X2[gather[i] & 0x7FFFFFFF]; row i of dY is dY[ysel[i]] (no dY_alt)
+    const float* X2 = nullptr;       // gather[i] < 0: row i of X is X2[gather[i] & 0x7FFFFFFF]; row i of dY is dY[ysel[i]] (no dY_alt); with
+                                     // yscale the X row counts yscale[num[i]] times in dW, and rowdot[num[i]] = dXrow[i] . yscale[num[i]] X row
+    float* rowdot = nullptr;
+    const int32_t* num = nullptr;
     int dy_stride = 1;               // rows of dY are dy_stride * d_out floats apart (1 or 2)
     ShareSums* sums = nullptr;       // the slots are left to the caller's sums (part then has to last until they are launched)
 };

@@ -57,13 +57,24 @@ inline bool sched_run_rows(int64_t edges, int64_t pairs, int64_t single_pairs, i
     return edges >= (1 << 17) && 20 * (7 * runs - 2 * single_runs) <= 19 * (7 * pairs - 2 * single_pairs);
 }
 // The calls that take them.  Every flag but the accumulation of gradients asks for an alternative of the rows per pair.
-inline bool sched_use_run_rows(bool lists, int layer, int64_t edges, int d, uint32_t flags) {
-    return lists && !(flags & ~(uint32_t)RGNN_FLAG_ACCUMULATE) && layer == RGNN_LAYER_RGCN && edges * d >= 8000000;
-}
+inline bool sched_use_run_rows(bool lists, uint32_t flags) { return lists && !(flags & ~(uint32_t)RGNN_FLAG_ACCUMULATE); }
+inline bool sched_rgcn_run_rows(bool lists, int64_t edges, int d, uint32_t flags) { return sched_use_run_rows(lists, flags) && edges * d >= 8000000; }
 // RGCN forwards that keep nothing for a backward: the saving has to come from the forward alone.  Pairs / runs, us: 300k edges, 60
 // relations, width 32 34 / 46, 64 59 / 64, 128 129 / 109; 1M 75 / 73, 145 / 124, 340 / 266; bf16 1M 137 / 145, 3M 397 / 408, 16M and 500
 // relations 2551 / 2374.
 inline bool sched_run_rows_infer(bool rows_bf16, int64_t edges, int d) { return edges * d >= (rows_bf16 ? 1000000000 : 30000000); }
+// RGAT with one head.  The walks look the relations' folded vectors up, once per run or edge, so more relations move the line out, and at
+// width 32 the indices outweigh the rows.  Forward + backward, us, pairs / runs, at 7 Q - 2 Q1 from 0.54 to 0.72 of 7 P - 2 P1: 8 relations,
+// width 64 173 / 152 at 300k edges, 1108 / 798 at 3M, 128 178 / 162 at 140k, 463 / 338 at 550k; 60 relations, 64 300 / 260 at 550k, 1317 / 990 at 3M, 128
+// 213 / 217 at 140k, 352 / 306 at 300k, 2873 / 1930 at 3M, 32 175 / 182 at 550k, 307 / 292 at 1.2M; 400 relations, 64 396 / 440 at 550k, 683 / 683
+// at 1.2M, 1533 / 1380 at 3M, 128 451 / 485 at 300k, 1394 / 1220 at 1.2M, 32 788 / 838 at 3M.
+inline bool sched_rgat_run_rows(bool lists, int heads, int R, int64_t edges, int d, uint32_t flags) {
+    return heads == 1 && sched_use_run_rows(lists, flags) && edges * d >= 16000000 + (int64_t)R * (d < 64 ? 640000 : 160000);
+}
+// ... and for forwards that keep nothing for a backward, where the softmax within the runs is paid and the cheaper backward is not there.  Pairs / runs
+// as a ratio: width 64 1.04 and 1.02 (8 and 60 relations, 1.2M and 3M edges), 0.99 and 0.90 at 550k, 400 relations 0.90 at 3M; 128 1.11 and 1.08 at
+// 550k, 0.99 and 1.00 at 300k, 400 relations 1.00 at 1.2M and 1.06 at 3M; 32 0.93 at 3M.
+inline bool sched_rgat_run_rows_infer(int R, int64_t edges, int d) { return d >= 64 && edges * d >= 64000000 + (int64_t)R * 640000; }
 // HGT: the key and message linears of the nodes are folded into the per-relation weights when every relation's
 // sources have one node type.
 inline bool sched_hgt_folded(bool rel_src_tied, uint32_t flags) {

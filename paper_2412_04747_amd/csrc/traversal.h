@@ -39,6 +39,31 @@ rgnn_status_t rgat_aggregate_fwd(const rgnn_graph* g, int D, int H, const float*
 rgnn_status_t rgat_edge_dot_bwd(const rgnn_graph* g, int D, int H, const float* Hs, const float* w_s, const float* s_dst,
                                 const float* ms, const float* dOut, const float* out, float slope, float* adz, float* G,
                                 float* ds_src, float* dsy, hipStream_t st);
+// Rows per run, one head:
+//   the inputs of the m-th run with several edges, A[m] = sum of X[src_e] weighted by their softmax within the run, from the logits
+//   X[src_e] . wsp[r] + s_dst[q]; lq[q] = (max logit, sum of exp(logit - max)).  partial / part_ms: pieces of runs that are cut
+rgnn_status_t rgat_run_inputs(const rgnn_graph* g, int K, const float* X, const float* wsp, const float* s_dst, float slope, float* A, float* lq,
+                              float* partial, float* part_ms, hipStream_t st);
+//   out[v] = sum over v's runs of their rows Y, a run weighing sum exp(logit - max over v); a run with one edge has the logit
+//   Y . w_s[r] + s_dst[q], which becomes its lq[q] (may be null without such runs to be kept); ms[v] = (max, sum of exp)
+rgnn_status_t rgat_run_aggregate(const rgnn_graph* g, int D, const float* Y, const float* w_s, const float* s_dst, float slope, float* lq, float* out,
+                                 float* ms, float* partial, float* part_ms, hipStream_t st);
+//   the destination halves of the logits, s_dst[q] = X[dst_q] . wtp[r]
+rgnn_status_t rgat_run_logit(const rgnn_graph* g, int K, const float* X, const float* wtp, float* s_dst, hipStream_t st);
+//   backward (rgat_runs.hip): weight[q] = what A[q] (or the source's row) counts in out[dst_q];
+//   stat[q] = (s_dst[q] or the logit of the run's only edge, max of v, 1 / sum of v, dOut[v] . out[v] = sum over v's runs of rowdot), and
+//   ds_dst of the runs with one edge
+rgnn_status_t rgat_run_weights(const rgnn_graph* g, const float* ms, const float* lq, float* weight, hipStream_t st);
+rgnn_status_t rgat_run_stat(const rgnn_graph* g, float slope, const float* rowdot, const float* weight, const float* ms, const float* lq, const float* s_dst,
+                            float* stat, float* ds_dst, hipStream_t st);
+//   per source u, over its edges in the order of src_items: dz[i], and dX[u] = sum att_e dH[row of e's run] + dz_e wsp[r_e] (+ dX[u], acc),
+//   with dH = dOut W^T per run
+rgnn_status_t rgat_source_walk(const rgnn_graph* g, int K, const float* X, const float* dH, const float* wsp, const float* stat, float slope, float* dz,
+                               float* dX, bool acc, float* partial, hipStream_t st);
+//   A[r] = sum over r's pairs of ds_src X[src], ds_src the sum of the pair's dz (ds_src: scratch [P] for the long ones); U[r] = sum over r's
+//   runs of ds_dst X[dst]; what the partials hold is left to the caller's sums (pair_blocks, run_blocks)
+rgnn_status_t rgat_block_sums(const rgnn_graph* g, int K, const float* X, const float* dz, float* ds_src, const float* ds_dst, float* A, float* a_partial,
+                              float* U, float* u_partial, hipStream_t st);
 // workgroups of `threads` threads with `lds` bytes of dynamic LDS that stay resident per compute unit (cached per kernel)
 rgnn_status_t resident_blocks_per_cu(const void* kernel, int threads, size_t lds, int* out);
 // Optional rank-1 term of a gather-sum: out[i] += coef[i * stride + head] * vec[seg[i]] (fp32 vec rows of the output width)
@@ -66,7 +91,8 @@ rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, v
                                hipStream_t st, const Rank1* r1 = nullptr, int heads = 1, int copies = 1, size_t out_copy = 0,
                                const float* extra = nullptr);
 rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
-                              int out_bf16, float* ms, bool full_exp, int piece_len, const char* label, hipStream_t st);
+                              int out_bf16, float* ms, bool full_exp, int piece_len, const char* label, hipStream_t st,
+                              const int32_t* ms_row = nullptr);      // (max, sum) of segment v at ms_row[v] instead of v
 // H weighted sums of the same gathered rows in one walk (coef [entries][H]); out [H][out_rows][D]
 rgnn_status_t gather_heads_rows(const ItemList& L, int D, int H, int out_rows, const int32_t* via, const int32_t* rowidx,
                                 int row_by_k, const float* coef, const float* src, float* out, float* partial,
@@ -78,6 +104,8 @@ struct RgatFinish {
     float* dW; float* dw_s; float* dw_t;
     int blocks;          // set by the launcher
 };
+//   dX[v] += sum over v's runs of ds_dst[q] wtp[r], and the parameter gradients
+rgnn_status_t rgat_run_term(const rgnn_graph* g, int D, const float* ds_dst, const float* wtp, float* dX, RgatFinish fin, hipStream_t st);
 rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const float* ds_dst, const float* wtp,
                             const float* extra, void* dX, hipStream_t st, int in_bf16 = 0, int out_bf16 = 0, int heads = 1,
                             const void* dXp2 = nullptr, const RgatFinish* finish = nullptr);

@@ -687,7 +687,7 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
                                                               const int32_t* __restrict__ split_ptr,
                                                               const float* __restrict__ partial,
                                                               const float2* __restrict__ part_ms, TO* __restrict__ out,
-                                                              float2* __restrict__ ms, int piece_len) {
+                                                              float2* __restrict__ ms, const int32_t* __restrict__ ms_row, int piece_len) {
     constexpr int LPR = D / 4, G = 256 / LPR, LPH = LPR / H;
     auto ex = [](float x) { return FULL ? expf(x) : __expf(x); };
     __shared__ float4 red[256];
@@ -746,7 +746,7 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
 #pragma unroll
         for (int q = 0; q < 4; ++q) t[q] *= inv;
         store_cols(out + v * D + c * 4, t);
-        if (c % LPH == 0) ms[v * H + head] = make_float2(M, S);
+        if (c % LPH == 0) ms[(ms_row ? (size_t)ms_row[v] : v) * H + head] = make_float2(M, S);
     }
 }
 
@@ -937,7 +937,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void s
         }
         blk -= j.blocks;
     }
-    if (blk < s.pieces.blocks()) piece_sum_block(s.pieces, blk, red);
+    if (blk < s.pieces.blocks()) {
+        piece_sum_block(s.pieces, blk, red);
+        return;
+    }
+    blk -= (int)s.pieces.blocks();
+    if (blk < s.pieces2.blocks()) piece_sum_block(s.pieces2, blk, red);
 }
 
 rgnn_status_t ShareSums::add(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2) {
@@ -950,7 +955,7 @@ rgnn_status_t ShareSums::add(const TileList& tiles, const float* part, int kn, i
     return RGNN_OK;
 }
 rgnn_status_t ShareSums::launch(hipStream_t st) {
-    int64_t blocks = pieces.blocks();
+    int64_t blocks = pieces.blocks() + pieces2.blocks();
     for (int k = 0; k < n; ++k) blocks += job[k].blocks;
     if (blocks > INT32_MAX / 2) RGNN_FAIL(RGNN_EUNSUPPORTED, "weight-gradient sums: too many segments");
     if (blocks > 0) {
@@ -960,7 +965,7 @@ rgnn_status_t ShareSums::launch(hipStream_t st) {
         RGNN_CHECK_LAUNCH();
     }
     n = 0;
-    pieces = SumArgs{};
+    pieces = pieces2 = SumArgs{};
     return RGNN_OK;
 }
 rgnn_status_t typed_linear_slot_reduce(const TileList& tiles, const float* part, int kn, int kd, float* dW, float* dW2, hipStream_t st,
@@ -1212,6 +1217,69 @@ __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a, RgatF
 
 // ------------------------------------------------------------------ elementwise
 
+// Rows per run: dX[v] += sum over v's runs of ds_dst[q] wtp[run_rel[q]].  A group of D / 4 lanes per destination, relations and coefficients of
+// D / 4 runs at a time, a lane each; wtp in LDS where it fits (persistent workgroups).  The first `fin.blocks` workgroups finish the
+// layer's parameter gradients.  Bound by the rows of dX, read and written: 900k destinations of width 64, 4.4M runs 252 us with a load of the
+// folded vector per run, so 123.
+constexpr int kRunTermThreads = 512;
+template <int D, bool LDSW>
+__global__ __launch_bounds__(kRunTermThreads) void run_term_kernel(int N, int R, const int32_t* __restrict__ dst_run_ptr, const int32_t* __restrict__ run_rel,
+                                                                   const float* __restrict__ ds_dst, const float* __restrict__ wtp, float* __restrict__ dX,
+                                                                   RgatFinish fin) {
+    constexpr int LPR = D / 4, GPB = kRunTermThreads / LPR;
+    extern __shared__ __align__(16) float smem[];          // max(R * D, 512) floats
+    if ((int)blockIdx.x < fin.blocks) {
+        if (threadIdx.x >= 256) return;                    // (whole wavefronts, which the barriers inside no longer count)
+        param_finish_block(fin, blockIdx.x, smem);
+        return;
+    }
+    const float* w = wtp;
+    if (LDSW) {
+        for (int i = threadIdx.x; i < R * D / 4; i += kRunTermThreads) reinterpret_cast<float4*>(smem)[i] = reinterpret_cast<const float4*>(wtp)[i];
+        __syncthreads();
+        w = smem;
+    }
+    // the next destination's first runs and its row are asked for before this one's sums, and the ends of the runs of the one after it
+    const int c = threadIdx.x % LPR;
+    const int64_t step = (int64_t)(gridDim.x - fin.blocks) * GPB, last = N - 1;
+    int64_t v = (int64_t)(blockIdx.x - fin.blocks) * GPB + threadIdx.x / LPR;
+    if (v >= N) return;
+    int b = dst_run_ptr[v], e = dst_run_ptr[v + 1];
+    int64_t vn = min(v + step, last);
+    int bn = dst_run_ptr[vn], en = dst_run_ptr[vn + 1];
+    int j = max(min(b + c, e - 1), 0), rel = run_rel[j];
+    float ds = ds_dst[j];
+    float4 x = *reinterpret_cast<const float4*>(dX + v * D + c * 4);
+    for (; v < N; v += step) {
+        j = max(min(bn + c, en - 1), 0);
+        const int reln = run_rel[j];
+        const float dsn = ds_dst[j];
+        const float4 xn = *reinterpret_cast<const float4*>(dX + vn * D + c * 4);
+        const int64_t vnn = min(vn + step, last);
+        const int bnn = dst_run_ptr[vnn], enn = dst_run_ptr[vnn + 1];
+        float4 acc1 = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int jc = b; jc < e; jc += LPR) {
+            if (jc > b) {
+                j = min(jc + c, e - 1);
+                rel = run_rel[j];
+                ds = ds_dst[j];
+            }
+            const int n = min(LPR, e - jc);
+            const float d = c < n ? ds : 0.f;
+#pragma unroll
+            for (int k = 0; k < LPR; k += 2) {
+                if (k >= n) break;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    fma4(t ? acc1 : x, group_lane<LPR>(d, k + t), *reinterpret_cast<const float4*>(w + (size_t)group_lane<LPR>(rel, k + t) * D + c * 4));
+            }
+        }
+        fma4(x, 1.f, acc1);
+        if (b < e) *reinterpret_cast<float4*>(dX + v * D + c * 4) = x;
+        b = bn; e = en; bn = bnn; en = enn; rel = reln; ds = dsn; x = xn; vn = vnn;
+    }
+}
+
 __global__ void relu_kernel(size_t n, float* __restrict__ x) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) x[i] = x[i] > 0.f ? x[i] : 0.f;
@@ -1342,13 +1410,13 @@ rgnn_status_t edge_softmax(const rgnn_graph* g, const float* s_src, const float*
     } while (0)
 
 rgnn_status_t combine_softmax(const ItemList& L, int D, int H, const float* partial, const float* part_ms, void* out,
-                              int out_bf16, float* ms, bool full_exp, int piece_len, const char* label, hipStream_t st) {
+                              int out_bf16, float* ms, bool full_exp, int piece_len, const char* label, hipStream_t st, const int32_t* ms_row) {
     if (L.num_split == 0) return RGNN_OK;
     KernelTimer kt(st, label);
 #define RGNN_COMBINE(HH, TO_, FULL_)                                                                                  \
     RGNN_DISPATCH_D(D, hipLaunchKernelGGL((combine_softmax_kernel<DD, (DD / (HH) >= 16 ? (HH) : 1), TO_, FULL_>), dim3(L.num_split), dim3(256), 0, st, \
                                           L.split_row, L.split_ptr, partial, reinterpret_cast<const float2*>(part_ms), \
-                                          static_cast<TO_*>(out), reinterpret_cast<float2*>(ms), piece_len))
+                                          static_cast<TO_*>(out), reinterpret_cast<float2*>(ms), ms_row, piece_len))
 #define RGNN_COMBINE_H(HH)                                                                                            \
     do {                                                                                                              \
         if (out_bf16) RGNN_COMBINE(HH, bf16_t, true);                                                                 \
@@ -1555,6 +1623,28 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
         RGNN_DISPATCH_ROWS(D, in_bf16, out_bf16, hipLaunchKernelGGL((node_grad_sum_kernel<DD, TI, TO, 0, false>), grid, dim3(256), 0, st, a, fin));
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
+}
+
+template <int D, bool LDSW>
+static rgnn_status_t launch_run_term(const rgnn_graph* g, const float* ds_dst, const float* wtp, float* dX, const RgatFinish& fin, hipStream_t st) {
+    const size_t lds = std::max<size_t>(LDSW ? (size_t)g->R * D : 0, 512) * sizeof(float), groups = kRunTermThreads / (D / 4);
+    const void* fn = reinterpret_cast<const void*>(run_term_kernel<D, LDSW>);
+    RGNN_TRY(allow_dynamic_lds(fn, lds));
+    int per_cu = 1;
+    RGNN_TRY(resident_blocks_per_cu(fn, kRunTermThreads, lds, &per_cu));
+    const size_t blocks = std::min<size_t>(((size_t)g->N + groups - 1) / groups, (size_t)per_cu * g->num_cus);
+    hipLaunchKernelGGL((run_term_kernel<D, LDSW>), dim3((unsigned)blocks + fin.blocks), dim3(kRunTermThreads), lds, st, (int)g->N, g->R,
+                       g->idx[RGNN_IDX_DST_RUN_PTR], g->idx[RGNN_IDX_RUN_REL], ds_dst, wtp, dX, fin);
+    RGNN_CHECK_LAUNCH();
+    return RGNN_OK;
+}
+rgnn_status_t rgat_run_term(const rgnn_graph* g, int D, const float* ds_dst, const float* wtp, float* dX, RgatFinish fin, hipStream_t st) {
+    const int64_t blocks = (int64_t)fin.R * (fin.nd / 32 + (fin.kd * fin.nd + 1023) / 1024);
+    if (blocks > 1 << 22) RGNN_FAIL(RGNN_EUNSUPPORTED, "run term: the parameter gradients of %d relations are too many", fin.R);
+    fin.blocks = (int)blocks;
+    KernelTimer kt(st, "run_term");
+    if (sched_ws_in_lds(g->R, D)) RGNN_DISPATCH_D(D, return (launch_run_term<DD, true>(g, ds_dst, wtp, dX, fin, st)));
+    else RGNN_DISPATCH_D(D, return (launch_run_term<DD, false>(g, ds_dst, wtp, dX, fin, st)));
 }
 
 rgnn_status_t widen_bf16(size_t n, const uint16_t* src, float* dst, hipStream_t st) {

@@ -341,12 +341,14 @@ __global__ __launch_bounds__((64 * FwdShape<D, D, false, false>::NW)) void typed
 // and are read from dOut, a table small enough for the caches: 832k pairs, 32 -> 64 columns, walk 79 -> 30 us, this kernel
 // 87 -> 92 us; 2.15M pairs of width 64, walk 226 -> 90 us, this kernel 345 -> 373 us.
 //
-// XSEL (rows per run): input rows from two tensors as in the forward, X or x2, and row i of dY is dY[sel[i]].
+// XSEL (rows per run): input rows from two tensors as in the forward, X or x2, and row i of dY is dY[sel[i]].  2: the input row counts
+// scale[n] times, n = num[i] (RGAT: the weight of the run), and dot[n] = dXrow[i] . (scale[n] input row i).
 struct RowSelect {
     const int32_t* sel; const float* alt; const float2* ds_scale; const float* scale; const float* hcoef; const float* wvec; const float* x2;
+    float* dot; const int32_t* num;
 };
 // DS: the rows of dY are DS * ND floats apart (not with SEL).
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, bool XSEL = false>
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, int XSEL = 0>
 __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                          const float* __restrict__ W, const float* __restrict__ dY, float* __restrict__ dXrow,
                                          const float* __restrict__ rowscale, const float* __restrict__ vec,
@@ -404,6 +406,7 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
         v4f xr[NXR], yr[NYR];
         float dsr = 0.f;
         int gi[NXR], gcur[NXR];
+        int nmn = 0, nmc = 0; // XSEL 2: num of row (lane & 31) of the unit whose rows are fetched next, and of the one in yr
         int ysn = 0;          // SEL: selector of row (lane & 31) of the unit whose rows are fetched next
         float alr = 1.f;      // SEL: scale of row (lane & 31) of the unit whose rows are in yr
         // HS: (b[h0], b[h0 + 1], a[h0], a[h0 + 1]) of row (lane & 31) of the unit whose rows are in yr, a = 1 for a row
@@ -427,12 +430,13 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
                 }
             }
             if (SEL) ysn = ys.sel[min(ra + u * 32 + (lane & 31), rbnd - 1)];
+            if (XSEL == 2) nmn = ys.num[min(ra + u * 32 + (lane & 31), rbnd - 1)];
         };
         auto fetch = [&](int u) {
 #pragma unroll
             for (int it = 0; it < NXR; ++it) {
                 const int gx = LANEIDX ? __shfl(gsn, rx + it * RPX) : gi[it];
-                xr[it] = *reinterpret_cast<const v4f*>(input_row<KD, XSEL>(X, ys.x2, gx) + cx * 4);
+                xr[it] = *reinterpret_cast<const v4f*>(input_row<KD, (XSEL > 0)>(X, ys.x2, gx) + cx * 4);
                 gcur[it] = gx;
             }
 #pragma unroll
@@ -458,6 +462,9 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
                 const float2 pr = ys.ds_scale[min(ra + u * 32 + (lane & 31), rbnd - 1)];
                 dsr = pr.x;
                 alr = ysn < 0 ? pr.y : 1.f;
+            } else if (XSEL == 2) {
+                nmc = nmn;
+                alr = ys.scale[nmn];
             } else if (SEL && !XSEL) {
                 // without scales the load goes to the selectors (any bits) and is not used: no conditional load
                 const float* from = ys.scale ? ys.scale : reinterpret_cast<const float*>(ys.sel);
@@ -472,11 +479,16 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
         fetch_idx(wave + NW);
         for (int u = wave; u < nu; u += NW) {
             const int rows_left = rbnd - (ra + u * 32);      // rows of this unit that exist (may exceed 32)
+            const int num = nmc;
             int gout[NXR];
 #pragma unroll
             for (int it = 0; it < NXR; ++it) {
                 const bool ok = rx + it * RPX < rows_left;
                 v4f v = xr[it];
+                if (XSEL == 2) {
+                    const float sc = __shfl(alr, rx + it * RPX);
+                    v = v4f{v[0] * sc, v[1] * sc, v[2] * sc, v[3] * sc};
+                }
                 if (!ok) v = v4f{0.f, 0.f, 0.f, 0.f};
                 *reinterpret_cast<v4f*>(Xw + (rx + it * RPX) * XS + cx * 4) = v;
                 gout[it] = gcur[it];
@@ -615,6 +627,11 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
                     o.x += sc * xv.x; o.y += sc * xv.y; o.z += sc * xv.z; o.w += sc * xv.w;
                 }
                 const size_t d = SCATTER ? (size_t)gout[it] : (size_t)(ra + u * 32 + r);
+                if (XSEL == 2) {
+                    const float p = group_sum<LPRX>(dot4(*reinterpret_cast<const float4*>(Xw + r * XS + cx * 4), o));
+                    const int n = __shfl(num, r);
+                    if (cx == 0 && r < rows_left) ys.dot[n] = p;
+                }
                 if (r < rows_left) {
                     const v4f ov = {o.x, o.y, o.z, o.w};
                     __builtin_nontemporal_store(ov, reinterpret_cast<v4f*>(dXrow + d * KD + cx * 4));
@@ -664,7 +681,7 @@ __device__ __forceinline__ void bwd_wave(const TileArgs& t, int chunk, const flo
     }
 }
 
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, bool XSEL = false>
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, int XSEL = 0>
 __global__ __launch_bounds__(512) void typed_linear_bwd_wave_kernel(TileArgs t, const float* __restrict__ X,
                                                                     const int32_t* __restrict__ gather,
                                                                     const float* __restrict__ W,
@@ -689,7 +706,7 @@ __global__ __launch_bounds__(512) void typed_linear_bwd_jobs_kernel(BwdJobs jobs
 
 // RGCN: the pairs' product (with the row selector or without), or the runs' (XSEL), and the self-loop's, the first `chunks` workgroups and the others; chunks
 // as above (833k pairs and 120k nodes, 32 -> 64 columns: 100 and 23 us, together 110).
-template <int KD, int ND, bool SEL, bool XSEL>
+template <int KD, int ND, bool SEL, int XSEL>
 __global__ __launch_bounds__(512) void typed_linear_bwd_loop_kernel(BwdJob pair, RowSelect ys, BwdJob loop) {
     const RowSelect none{};
     if ((int)blockIdx.x < pair.chunks)
@@ -760,7 +777,7 @@ size_t typed_linear_bwd_scratch_floats(int d_in, int d_out, const TileList& t, i
     return (size_t)std::max(t.num_slots, 1) * ((size_t)d_in * d_out + (size_t)std::max(vectors, 1) * d_in);
 }
 
-template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, bool XSEL = false>
+template <int KD, int ND, bool GATHER, bool DYG, bool SCATTER, bool RS, bool SEL = false, int HS = 0, int DS = 1, int XSEL = 0>
 static rgnn_status_t launch_bwd_wave(const TypedLinearBwdArgs& a, hipStream_t st) {
     constexpr int WREG = 32 * (KD + 4) + 32 * ((ND > KD ? ND : KD) + 4) + 32;
     static_assert(WREG >= KD * ND + (HS ? HS : 1) * KD, "per-wavefront LDS region must hold a weight-gradient copy");
@@ -769,7 +786,7 @@ static rgnn_status_t launch_bwd_wave(const TypedLinearBwdArgs& a, hipStream_t st
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks), dim3(512), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W,
-                       a.dY, a.dXrow, a.rowscale, a.vec, a.part, RowSelect{a.ysel, a.dY_alt, a.ds_yscale, a.yscale, a.hcoef, a.wvec, a.X2});
+                       a.dY, a.dXrow, a.rowscale, a.vec, a.part, RowSelect{a.ysel, a.dY_alt, a.ds_yscale, a.yscale, a.hcoef, a.wvec, a.X2, a.rowdot, a.num});
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -786,9 +803,11 @@ static rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, hipStream_t st) {
             const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
             done = true;
             if (a.X2) {
-                if (!(g && a.ysel && !dg && !sc && !rs) || a.dY_alt || a.vec || a.yscale || a.ds_yscale || a.hcoef || a.dy_stride != 1)
-                    RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: two input tensors go with gathered X, a list of the dY rows and nothing else");
-                RGNN_TRY((launch_bwd_wave<KD, ND, true, false, false, false, true, 0, 1, true>(a, st)));
+                if (!(g && a.ysel && !dg && !sc && !rs) || a.dY_alt || a.vec || a.ds_yscale || a.hcoef || a.dy_stride != 1)
+                    RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: two input tensors go with gathered X, a list of the dY rows and scales at most");
+                if (a.yscale && !(a.rowdot && a.num)) RGNN_FAIL(RGNN_EINVAL, "typed linear backward: scales of input rows go with numbers and products");
+                if (a.yscale) RGNN_TRY((launch_bwd_wave<KD, ND, true, false, false, false, true, 0, 1, 2>(a, st)));
+                else RGNN_TRY((launch_bwd_wave<KD, ND, true, false, false, false, true, 0, 1, 1>(a, st)));
             } else if (a.dy_stride == 2) {
                 if (!(g && !dg && !sc && !rs && !a.ysel && KD == ND))
                     RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: dY rows two widths apart are built for gathered X, ungathered dY, no rowscale and no selector only");
@@ -829,8 +848,8 @@ static rgnn_status_t launch_bwd_loop(const TypedLinearBwdArgs& p, const TypedLin
     constexpr size_t lds = sizeof(float) * (KD * (ND + 1) + 8 * (32 * (KD + 4) + 32 * ((ND > KD ? ND : KD) + 4) + 32));
     const BwdJob pair{tile_args(*p.tiles), p.tiles->num_chunks, 1, p.X, p.gather, p.W, p.dY, p.dXrow, p.part};
     const BwdJob loop{tile_args(*l.tiles), l.tiles->num_chunks, 0, l.X, nullptr, l.W, l.dY, l.dXrow, l.part};
-    const RowSelect ys{p.ysel, p.dY_alt, nullptr, p.yscale, nullptr, nullptr, p.X2};
-    auto kern = p.X2 ? typed_linear_bwd_loop_kernel<KD, ND, true, true> : p.ysel ? typed_linear_bwd_loop_kernel<KD, ND, true, false> : typed_linear_bwd_loop_kernel<KD, ND, false, false>;
+    const RowSelect ys{p.ysel, p.dY_alt, nullptr, p.yscale, nullptr, nullptr, p.X2, nullptr, nullptr};
+    auto kern = p.X2 ? typed_linear_bwd_loop_kernel<KD, ND, true, 1> : p.ysel ? typed_linear_bwd_loop_kernel<KD, ND, true, 0> : typed_linear_bwd_loop_kernel<KD, ND, false, 0>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, "typed_linear_loop_bwd");
     hipLaunchKernelGGL(kern, dim3(pair.chunks + loop.chunks), dim3(512), lds, st, pair, ys, loop);

@@ -379,9 +379,11 @@ struct BwdArgs {
     const float* dY_alt;
     const float2* ds_yscale;
     const float* yscale;
-    const float* X2;         // XSEL: list entry g < 0 is row g & 0x7FFFFFFF of X2 (SEL is then a plain list of dY rows)
+    const float* X2;         // XSEL: list entry g < 0 is row g & 0x7FFFFFFF of X2 (SEL is then a plain list of dY rows); 2: X rows count yscale[n] times,
+    float* dot;              // n = num[i], and dot[n] = dXrow[i] . yscale[n] X row
+    const int32_t* num;
 };
-template <bool XSEL>
+template <int XSEL>
 __device__ __forceinline__ const float* input_row(const BwdArgs& a, int g) { return (XSEL && g < 0 ? a.X2 : a.X) + (size_t)(XSEL ? g & 0x7FFFFFFF : g) * D; }
 __device__ __forceinline__ const float* selected_row(const BwdArgs& a, int sl) { return (sl < 0 ? a.dY_alt : a.dY) + (size_t)(sl & 0x7FFFFFFF) * D; }
 template <bool RS>
@@ -393,14 +395,18 @@ __device__ __forceinline__ float selected_scale(const BwdArgs& a, int row, int s
 constexpr int SLOT = D * D + D;
 struct RowOf { int to[UNIT]; float s[UNIT]; };   // destinations and rowscales of a unit's rows on its way through the pipeline
 constexpr int BUF = 6 * PLANE;               // planes of a unit: X, then dY
+// XSEL 2: the unit's X rows in fp32 for the products with dXrow ([2][32][512 bytes] behind the planes), whose sums over each wavefront's 32
+// columns the loading wavefronts add (a ring like the flags)
+constexpr int XROWS = UNIT * 4 * D;
+struct DotOf { float band[4][UNIT]; int num[UNIT]; };
 
 // A value that lane half + 2 k keeps, for the 32 lanes of that half of the wavefront (no trip through LDS).
 __device__ __forceinline__ int of_row(int v, int k, int half) {
     const int a = __builtin_amdgcn_readlane(v, 2 * k), b = __builtin_amdgcn_readlane(v, 2 * k + 1);
     return half ? b : a;
 }
-template <bool GATHER, bool BOTH, bool RS, bool SEL, bool XSEL>
-__device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, float4* avb, RowOf* row_of, int* bad, int u0, int u1) {
+template <bool GATHER, bool BOTH, bool RS, bool SEL, int XSEL>
+__device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, float4* avb, RowOf* row_of, DotOf* dot_of, int* bad, int u0, int u1) {
     constexpr int DEPTH = 2;                               // units in flight per thread: 64 KB per compute unit
     const int tid = threadIdx.x & 255;
     const Loader ld(tid);
@@ -410,12 +416,14 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
     // (a register instead of four), and hands them to the 32 lanes of that row.
     const int lane = tid & 63, half = lane >> 5, jrow = 2 * (tid >> 6) + (lane & 1) + 8 * ((lane >> 1) & 3);
     int gi[2 * DEPTH], yi[2 * DEPTH];                      // indices run further ahead (see the forward)
+    int ni[XSEL == 2 ? 2 * DEPTH : 1];                     // XSEL 2: num
     float rs[DEPTH], sc[DEPTH];
     auto fetch_idx = [&](int p, int u) {
         const Unit n = units.get(min(u, u1 - 1));
         const int row = n.row0 + min(jrow, n.rows - 1);    // (an empty second half: the tile's last row)
         gi[p] = GATHER ? a.gather[row] : row;
         yi[p] = SEL ? a.ysel[row] : row;
+        if (XSEL == 2) ni[XSEL == 2 ? p : 0] = a.num[row];
     };
     auto fetch = [&](int p, int q, int u) {
         const Unit n = units.get(min(u, u1 - 1));
@@ -428,7 +436,7 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
         }
         const int row = n.row0 + min(jrow, n.rows - 1);
         rs[p] = RS ? (SEL ? a.ds_yscale[row].x : a.rowscale[row]) : 0.f;
-        sc[p] = SEL && !XSEL ? selected_scale<RS>(a, row, yi[q]) : 1.f;
+        sc[p] = XSEL == 2 ? a.yscale[ni[XSEL == 2 ? q : 0]] : SEL && !XSEL ? selected_scale<RS>(a, row, yi[q]) : 1.f;
     };
 #pragma unroll
     for (int p = 0; p < 2 * DEPTH; ++p) fetch_idx(p, u0 + p);
@@ -449,6 +457,11 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
             reinterpret_cast<float4*>(a.part + (size_t)pending * SLOT + D * D)[tid] = s;
         }
         pending = -1;
+        if (XSEL == 2 && u - 1 >= u0 && tid < UNIT) {          // the rows of the unit that was multiplied before this barrier
+            const Unit p = units.get(u - 1);
+            DotOf& q = dot_of[(u - 1) & 3];
+            if (tid < p.rows) a.dot[q.num[tid]] = (q.band[0][tid] + q.band[1][tid]) + (q.band[2][tid] + q.band[3][tid]);
+        }
         const Unit n = units.get(min(u + 1, u1 - 1));
         const int next_seg = u + 1 < u1 ? n.seg : -2;
         if (next_seg != seg && u + 1 <= u1) {
@@ -467,11 +480,17 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
             float4 au = make_float4(0.f, 0.f, 0.f, 0.f);     // the unit's share first: fewer roundings at the sum's magnitude
             if (RS && lane < 8) row_of[(u + 1) & 3].s[jrow] = rs[p % DEPTH];
             if (BOTH && lane < 8) row_of[(u + 1) & 3].to[jrow] = gi[p];
+            if (XSEL == 2 && lane < 8) dot_of[(u + 1) & 3].num[jrow] = ni[XSEL == 2 ? p : 0];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const bool ok = u + 1 < u1 && ld.lr + 8 * k < n.rows;
                 float4 x = xr[p % DEPTH][k];
                 if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (XSEL == 2) {
+                    const float s = __int_as_float(of_row(__float_as_int(sc[p % DEPTH]), k, half));
+                    x = make_float4(x.x * s, x.y * s, x.z * s, x.w * s);
+                    *reinterpret_cast<float4*>(lds + 2 * BUF + ((u + 1) & 1) * XROWS + (ld.lr + 8 * k) * 512 + ld.c4 * 16) = x;
+                }
                 if (RS) {
                     const float r = __int_as_float(of_row(__float_as_int(rs[p % DEPTH]), k, half));
                     fma4(au, ok ? r : 0.f, x);
@@ -502,8 +521,8 @@ __device__ __forceinline__ void bwd_load(const BwdArgs& a, unsigned char* lds, f
         if (u + p <= u1) step(p, u + p);
 }
 
-template <bool GATHER, bool BOTH, bool RS, bool SEL>
-__device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* lds, const RowOf* row_of, int* bad, int u0, int u1) {
+template <bool GATHER, bool BOTH, bool RS, bool SEL, int XSEL>
+__device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* lds, const RowOf* row_of, DotOf* dot_of, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = threadIdx.x >> 6, m = lane & 31, kh = lane >> 5;
     float vcol = 0.f;                                      // RS: this lane's column of vec[seg]
     Units units(a.t, u0 >> 1, u1 >> 1);
@@ -538,11 +557,23 @@ __device__ __forceinline__ void bwd_multiply(const BwdArgs& a, unsigned char* ld
             const int sl = a.ysel[r];
             return RowAt{selected_row(a, sl), selected_scale<RS>(a, r, sl)};
         });
+        if (XSEL == 2) {
+            int at = (4 * kh) * 512 + (band * 32 + m) * 4;
+            asm volatile("" : "+v"(at));
+            const unsigned char* const x = lds + 2 * BUF + (u & 1) * XROWS + at;
+            float mine = 0.f;                              // lane m keeps the sum of the m-th of its half's 16 rows
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float p = group_sum<32>(d[v] * *reinterpret_cast<const float*>(x + (8 * (v >> 2) + (v & 3)) * 512));
+                if (m == v) mine = p;
+            }
+            if (m < 16) dot_of[u & 3].band[band][8 * (m >> 2) + 4 * kh + (m & 3)] = mine;
+        }
         store_rows<BOTH, RS>(d, a.dX + (BOTH ? 0 : (size_t)n.row0 * D) + band * 32 + m, n.rows, kh, D, row_of[u & 3].to, row_of[u & 3].s, vcol);
     }
 }
 
-template <bool GATHER, bool BOTH, bool RS, bool SEL, bool XSEL>
+template <bool GATHER, bool BOTH, bool RS, bool SEL, int XSEL>
 __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* lds, int* bad, int u0, int u1) {
     const int lane = threadIdx.x & 63, band = (threadIdx.x >> 6) & 3, m = lane & 31, kh = lane >> 5;
     // Transposing reads: the 16-column groups g and g + 4 of the 128 form a 32 x 32 block (see the bf16 backward); this
@@ -617,7 +648,7 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
             const int f = (m & 15) + 64 * (m >> 4);
             const int rm = n.row0 + min(m, n.rows - 1);
             const int gm = GATHER ? a.gather[rm] : 0, ym = SEL ? a.ysel[rm] : 0;    // of row m of the unit
-            const float sm = SEL ? selected_scale<RS>(a, rm, ym) : 1.f;
+            const float sm = XSEL == 2 ? a.yscale[a.num[rm]] : SEL && !XSEL ? selected_scale<RS>(a, rm, ym) : 1.f;      // (XSEL: of the X row)
 #pragma unroll 1
             for (int k = 0; k < UNIT; k += 2 * J) {
                 float x[J], y[J][4];
@@ -626,9 +657,9 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
                     const int q = min(k + 2 * j + kh, n.rows - 1), r = n.row0 + q, g = GATHER ? __shfl(gm, q) : r;
                     const float* const yp = SEL ? selected_row(a, __shfl(ym, q)) : a.dY + (size_t)(BOTH ? g : r) * a.ldd;
                     const float s = SEL ? __shfl(sm, q) : 1.f;
-                    x[j] = input_row<XSEL>(a, g)[16 * band + f];
+                    x[j] = input_row<XSEL>(a, g)[16 * band + f] * (XSEL == 2 ? s : 1.f);
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) y[j][b] = yp[f + 16 * b] * s;
+                    for (int b = 0; b < 4; ++b) y[j][b] = yp[f + 16 * b] * (XSEL ? 1.f : s);
                 }
 #pragma unroll
                 for (int j = 0; j < J; ++j) {
@@ -642,19 +673,20 @@ __device__ __forceinline__ void bwd_gradient(const BwdArgs& a, unsigned char* ld
 }
 
 // GATHER: X rows through the list; BOTH: dY rows and dXrow rows as well; SEL: dY rows through the row selector; XSEL: X rows from two tensors
-template <bool GATHER, bool BOTH, bool RS, bool SEL = false, bool XSEL = false>
+template <bool GATHER, bool BOTH, bool RS, bool SEL = false, int XSEL = 0>
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) void typed_linear_split_bwd_kernel(BwdArgs a) {
     static_assert(!(BOTH && (RS || SEL)) && (GATHER || !BOTH) && (!XSEL || (GATHER && SEL && !RS)), "combinations the layers use");
     extern __shared__ __align__(16) unsigned char lds[];   // [2] plane buffers, [2][8][32] float4 vector sums
     __shared__ int bad[4];
     __shared__ __align__(16) RowOf row_of[4];
+    __shared__ DotOf dot_of[XSEL == 2 ? 4 : 1];
     const int u0 = 2 * a.t.chunk_tile[blockIdx.x], u1 = 2 * a.t.chunk_tile[blockIdx.x + 1];
     if (threadIdx.x < 4) bad[threadIdx.x] = 0;
     __syncthreads();
     if (u0 >= u1) return;
-    if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH, RS, SEL>(a, lds, row_of, bad, u0, u1);
+    if (threadIdx.x < 256) bwd_multiply<GATHER, BOTH, RS, SEL, XSEL>(a, lds, row_of, dot_of, bad, u0, u1);
     else if (threadIdx.x < 512) bwd_gradient<GATHER, BOTH, RS, SEL, XSEL>(a, lds, bad, u0, u1);
-    else bwd_load<GATHER, BOTH, RS, SEL, XSEL>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF), row_of, bad, u0, u1);
+    else bwd_load<GATHER, BOTH, RS, SEL, XSEL>(a, lds, reinterpret_cast<float4*>(lds + 2 * BUF), row_of, dot_of, bad, u0, u1);
 }
 
 TileArgs tile_args(const TileList& t) { return TileArgs{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot}; }
@@ -670,15 +702,15 @@ rgnn_status_t launch_fwd(const TypedLinearArgs& a, const TileList& t, hipStream_
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
-template <bool GATHER, bool BOTH, bool RS, bool SEL = false, bool XSEL = false>
+template <bool GATHER, bool BOTH, bool RS, bool SEL = false, int XSEL = 0>
 rgnn_status_t launch_bwd(const TypedLinearBwdArgs& a, const TileList& t, hipStream_t st) {
-    const size_t lds = 2 * BUF + 2 * 256 * sizeof(float4);
+    const size_t lds = 2 * BUF + (XSEL == 2 ? 2 * XROWS : 2 * 256 * (int)sizeof(float4));
     auto kern = typed_linear_split_bwd_kernel<GATHER, BOTH, RS, SEL, XSEL>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, a.label ? a.label : "typed_linear_bwd");
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(768), lds, st,
                        BwdArgs{tile_args(t), a.X, a.gather, a.W, a.dY, a.dy_stride * D, a.dXrow, a.rowscale, a.vec, a.part, a.ysel, a.dY_alt,
-                               a.ds_yscale, a.yscale, a.X2});
+                               a.ds_yscale, a.yscale, a.X2, a.rowdot, a.num});
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -697,9 +729,10 @@ rgnn_status_t typed_linear_split_bwd(const TypedLinearBwdArgs& a, hipStream_t st
     const TileList& t = *a.tiles;
     const bool g = a.gather != nullptr, dg = g && a.dy_gathered, sc = g && a.scatter_dx, rs = a.rowscale != nullptr;
     if (a.X2) {
-        if (!g || dg || sc || rs || !a.ysel || a.dY_alt || a.vec || a.yscale || a.ds_yscale || a.hcoef || a.dy_stride != 1)
-            RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: two input tensors go with gathered X, a list of the dY rows and nothing else");
-        return t.num_tiles ? launch_bwd<true, false, false, true, true>(a, t, st) : RGNN_OK;
+        if (!g || dg || sc || rs || !a.ysel || a.dY_alt || a.vec || a.ds_yscale || a.hcoef || a.dy_stride != 1)
+            RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: two input tensors go with gathered X, a list of the dY rows and scales at most");
+        if (t.num_tiles == 0) return RGNN_OK;
+        return a.yscale ? launch_bwd<true, false, false, true, 2>(a, t, st) : launch_bwd<true, false, false, true, 1>(a, t, st);
     }
     if (a.ysel && (dg || !g || rs || a.dy_stride != 1 || a.hcoef || !a.dY_alt || (a.ds_yscale ? !a.vec || a.yscale : a.vec != nullptr)))
         RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear backward: the row selector needs gathered X, ungathered dY, and vec with the (rowscale, scale) pairs or neither; no heads at width 128");

@@ -172,6 +172,53 @@ inline ItemPlan plan_items(const std::vector<int32_t>& ptr, int max_len, int min
     return L;
 }
 
+// Rows of nodes summed per relation, where a relation's entries are in node order: items of one (relation, block of nodes) each, cut at
+// `cut` entries, and dealt so that every eighth item in a row is of the same eighth of the blocks, a block's items one after the other.
+// Workgroups go to the eight chiplets in turn, so a block's rows are read into one chiplet's L2 once for all relations.  bound[r * (B + 1)
+// + b]: first entry of relation r in block b.  row: the relation (-1: nothing to do); a relation in one item has slot -1, one without
+// entries an item of none.
+constexpr int kNodeBlock = 8192;    // nodes of a block: 2 MB of rows of width 64
+constexpr int kChiplets = 8;
+struct BlockPlan {
+    int32_t num_partials = 0;
+    std::vector<int32_t> beg, end, row, slot, split_row, split_ptr;
+};
+// Blocks for N nodes: of kNodeBlock, or larger ones so that the (relation, block) cells hold some entries on average.
+inline int node_blocks(int64_t N, int32_t R, int64_t entries) {
+    return (int)std::max<int64_t>(std::min<int64_t>((N + kNodeBlock - 1) / kNodeBlock, entries / 64 / std::max(R, 1)), 1);
+}
+inline int block_cut(int64_t entries, int cus) { return (int)std::min<int64_t>(std::max<int64_t>(entries / (16 * cus), 256), 1024); }
+inline BlockPlan plan_blocks(const std::vector<int32_t>& bound, int32_t R, int B, int cut) {
+    BlockPlan L;
+    std::vector<int32_t> first((size_t)R), pieces((size_t)R);       // first slot, items of a relation
+    L.split_ptr.push_back(0);
+    for (int32_t r = 0; r < R; ++r) {
+        for (int b = 0; b < B; ++b) pieces[r] += (bound[(size_t)r * (B + 1) + b + 1] - bound[(size_t)r * (B + 1) + b] + cut - 1) / cut;
+        first[r] = pieces[r] > 1 ? L.num_partials : -1;
+        if (pieces[r] > 1) {
+            L.num_partials += pieces[r];
+            L.split_row.push_back(r);
+            L.split_ptr.push_back(L.num_partials);
+        }
+    }
+    struct Item { int32_t beg, end, row, slot; };
+    std::vector<Item> queue[kChiplets];
+    for (int b = 0; b < B; ++b)
+        for (int32_t r = 0; r < R; ++r)
+            for (int32_t a = bound[(size_t)r * (B + 1) + b], e = bound[(size_t)r * (B + 1) + b + 1]; a < e; a += cut)
+                queue[b % kChiplets].push_back({a, std::min(a + cut, e), r, first[r] < 0 ? -1 : first[r]++});
+    for (int32_t r = 0; r < R; ++r)
+        if (pieces[r] == 0) queue[r % kChiplets].push_back({0, 0, r, -1});
+    size_t n = 0;
+    for (const auto& q : queue) n = std::max(n, q.size());
+    for (size_t k = 0; k < n; ++k)
+        for (const auto& q : queue) {
+            const Item i = k < q.size() ? q[k] : Item{0, 0, -1, -1};
+            L.beg.push_back(i.beg); L.end.push_back(i.end); L.row.push_back(i.row); L.slot.push_back(i.slot);
+        }
+    return L;
+}
+
 // Longest item for a list of `total` entries: kItemMax on large lists; shorter on small ones, where
 // a few long serial walks would otherwise be the whole run time (never below kSerialMax, so that
 // every item a single lane walks stays short).

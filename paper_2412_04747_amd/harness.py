@@ -96,7 +96,7 @@ class RgatLayer:
                         self.dX, self.dW, self.dw_s, self.dw_t, self.ws, _stream())
 
     def saved_views(self):
-        """The parts of `saved`: Hs [P, d], s_dst [Q, heads], ms [N, heads, 2]."""
+        """The parts of `saved` where rows are kept per pair: Hs [P, d], s_dst [Q, heads], ms [N, heads, 2]."""
         P, Q, N, d, H = self.g.P, self.g.Q, self.g.N, self.d, self.H
         al = lambda n: (max(n, 1) * 4 + 255) // 256 * 256 // 4
         f32 = self.saved.view(torch.float32)

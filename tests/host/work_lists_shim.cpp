@@ -43,6 +43,19 @@ int wl_tiles_field(int which, int32_t* out, int cap) {
 void wl_tiles_scalars(int32_t* out3) {
     out3[0] = g_tiles.num_chunks; out3[1] = g_tiles.num_slots; out3[2] = g_tiles.num_segs;
 }
+int wl_plan_blocks(const int32_t* bound, int R, int B, int cut) {
+    const rgnn::BlockPlan p = rgnn::plan_blocks(std::vector<int32_t>(bound, bound + (size_t)R * (B + 1)), R, B, cut);
+    g_items = rgnn::ItemPlan{};
+    g_items.beg = p.beg; g_items.end = p.end; g_items.row = p.row; g_items.slot = p.slot;
+    g_items.split_row = p.split_row; g_items.split_ptr = p.split_ptr; g_items.num_partials = p.num_partials;
+    return (int)p.beg.size();
+}
+// rows per run: the graph's lists (RGCN and RGAT have them), then layer 0 RGCN / 1 RGAT / 2 RGAT forward that keeps nothing
+int wl_run_rows(long long E, long long P, long long P1, long long Q, long long Q1, int layer, int heads, int R, int d, int flags) {
+    const bool lists = rgnn::sched_run_rows(E, P, P1, Q, Q1);
+    if (layer == 0) return rgnn::sched_rgcn_run_rows(lists, E, d, (uint32_t)flags);
+    return rgnn::sched_rgat_run_rows(lists, heads, R, E, d, (uint32_t)flags) && (layer == 1 || rgnn::sched_rgat_run_rows_infer(R, E, d));
+}
 int wl_pair_share(long long P, long long N, int cus, int lists) { return rgnn::pair_share(P, N, cus, lists); }
 int wl_item_cut(long long total) { return rgnn::item_cut(total); }
 int wl_constant(int which) {

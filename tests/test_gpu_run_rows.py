@@ -14,7 +14,7 @@ def _graph(seed, E):
     """Destinations of 1 to thousands of edges, runs of one edge and of hundreds (cut into pieces), a hub source, and relations without
     an edge (11), with single-edge runs only (12), with runs of several edges only (13), with one run (14)."""
     rng = np.random.default_rng(seed)
-    N, R = 9001, 15
+    N, R = 9001 if E < 400000 else 40009, 15
     src = rng.integers(0, N, E)
     dst = (N * rng.random(E) ** 3).astype(np.int64)
     rel = rng.integers(0, 11, E)
@@ -88,4 +88,109 @@ def test_rgcn(k, d, dtype, norm, act, loop, flags, saved):
     torch.cuda.synchronize()
     for n, v in L.grads().items():
         assert torch.equal(v, first[n]), n
+    g.close()
+
+
+def _area(guards, n):
+    big, mid = _guarded(n)
+    guards.append(big)
+    return mid
+
+
+@pytest.mark.parametrize("k,d,dtype,flags,spread", [
+    (64, 64, "f32", 0, 1), (32, 64, "f32", 32, 1), (64, 32, "f32", 0, 1), (32, 32, "f32", 32, 1), (128, 128, "f32", 0, 1),
+    (128, 128, "f32", 32, 9), (64, 64, "bf16", 0, 1)])       # (135 relations of width 128: their folded vectors do not fit in LDS)
+def test_rgat(k, d, dtype, flags, spread):
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    E = {32: 810007, 64: 290011, 128: 300007}[d]
+    N, R, src, dst, rel, rng = _graph(57 + k + d, E)
+    R, rel = R * spread, rel * spread
+    print(f"run rows rgat {k}->{d} {dtype} flags={flags} R={R}", flush=True)
+    p = synth.rgat_params(rng, N, R, k, d)
+    if dtype == "bf16":
+        p = {n: synth.round_to_bf16(v) for n, v in p.items()}
+    g = Graph(N, R, src, dst, rel)
+    L = RgatLayer(g, d, dtype=dtype, flags=flags, d_in=k)
+    L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    f, b, s = B.rgnn_workspace_bytes(g.handle, B.RGNN_LAYER_RGAT, L.desc)
+    guards = []
+    L.saved, L.ws = _area(guards, s), _area(guards, f)
+    B.rgnn_profile_start()
+    L.fwd()
+    torch.cuda.synchronize()
+    assert "run_inputs" in B.rgnn_profile_stop()
+    a = (N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"])
+    check(L.out, O.rgat_fwd(*a), TOL_F32, "out")
+    out = L.out.clone()
+    L.ws = _area(guards, b)
+    base = 1.0 if flags else 0.0
+    for v in L.grads().values():
+        v.fill_(1.0)
+    L.bwd()
+    torch.cuda.synchronize()
+    wg = O.rgat_bwd(*a, p["dOut"])
+    for n, v in L.grads().items():
+        check(v - base, wg[n], TOL_F32, n)
+    for r in range(R):                                       # by relation: a small one would hide among the others
+        for n in ("dW", "dw_s", "dw_t"):
+            check(L.grads()[n][r] - base, wg[n][r], 4 * TOL_F32, f"{n}[{r}]")
+    for big in guards:
+        _intact(big, "a buffer")
+    first = {n: v.clone() for n, v in L.grads().items()}
+    # a forward that keeps nothing, in exactly the workspace reported for it (rows per pair at these sizes); the same bits again, and from the
+    # static scratch
+    guards2 = []
+    L.out.fill_(7.0)
+    B.rgnn_rgat_fwd(g.handle, L.desc, L.X, L.W, L.w_s, L.w_t, L.out, None, _area(guards2, (f + 255) // 256 * 256 + s))
+    torch.cuda.synchronize()
+    check(L.out, O.rgat_fwd(*a), TOL_F32, "out of a forward that keeps nothing")
+    L.saved.fill_(0xFF)
+    L.out.fill_(7.0)
+    B.rgnn_rgat_fwd_static(g.handle, L.desc, L.X, L.W, L.w_s, L.w_t, L.out, L.saved)
+    for v in L.grads().values():
+        v.fill_(1.0)
+    L.bwd()
+    torch.cuda.synchronize()
+    assert torch.equal(L.out, out)
+    for n, v in L.grads().items():
+        assert torch.equal(v, first[n]), n
+    for big in guards2:
+        _intact(big, "the workspace of an inference call")
+    g.close()
+
+
+@pytest.mark.parametrize("n,fits", [(121, True), (160, False)])
+def test_rgat_forward_that_keeps_nothing(n, fits):
+    """Runs of nine edges.  Rows per run, from a workspace and from the static scratch; where that holds the rows per pair only, those from both."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    rng = np.random.default_rng(5)
+    N, R, runs, d = 54000, 8, 1000 * n, 64
+    q = np.repeat(np.arange(runs), 9)
+    rel, dst, src = (q % R).astype(np.int32), (q // 3).astype(np.int32), np.empty(9 * runs, np.int32)
+    for r in range(R):
+        m = np.flatnonzero(rel == r)
+        src[m] = rng.permutation(len(m)) % 25000
+    g = Graph(N, R, src, dst, rel)
+    p = synth.rgat_params(rng, N, R, d, d)
+    L = RgatLayer(g, d)
+    L.load(p["X"], p["W"], p["w_s"], p["w_t"])
+    f, _, s = B.rgnn_workspace_bytes(g.handle, B.RGNN_LAYER_RGAT, L.desc)
+    guards, names, outs = [], [], []
+    ws = _area(guards, (f + 255) // 256 * 256 + s)
+    a = (L.X, L.W, L.w_s, L.w_t, L.out)
+    for call in (L.fwd, lambda: B.rgnn_rgat_fwd(g.handle, L.desc, *a, None, ws), lambda: B.rgnn_rgat_fwd_static(g.handle, L.desc, *a, None)):
+        L.out.fill_(7.0)
+        B.rgnn_profile_start()
+        call()
+        torch.cuda.synchronize()
+        names.append("run_inputs" in B.rgnn_profile_stop())
+        outs.append(L.out.clone())
+    check(outs[0], O.rgat_fwd(N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"]), TOL_F32, "out")
+    check(outs[1], O.rgat_fwd(N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"]), TOL_F32, "out")
+    assert names == [True, fits, fits] and torch.equal(outs[1], outs[2])
+    _intact(guards[0], "the workspace")
     g.close()

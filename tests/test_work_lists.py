@@ -302,3 +302,48 @@ def test_row_selector_of_rgcn_where_it_pays(wl, d, R, singles, want):
     assert pick(wl, c, k, flags=4)["row_select"] == 0
     if d == 128:
         assert pick(wl, c, k, dtype="bf16")["row_select"] == 1
+
+
+@pytest.mark.parametrize("R,B,cut,mean", [(1, 1, 256, 900), (7, 5, 256, 40), (40, 23, 64, 100), (300, 16, 1024, 3)])
+def test_blocks_cover_each_relation_once(wl, R, B, cut, mean):
+    """Every entry in one item of its relation and block, no item above the cut, the pieces of a relation in slots of its own, a relation
+    in one item (or without entries) written by an item without a slot, and the items of a block of one chiplet only."""
+    rng = np.random.default_rng(R + B)
+    cells = rng.poisson(mean, (R, B)) * (rng.random((R, B)) < 0.7)
+    cells[R // 2] = 0
+    ends = np.cumsum(cells.ravel()).reshape(R, B)
+    bound = np.concatenate([ends[:, :1] - cells[:, :1], ends], 1).astype(np.int32)
+    n = wl.wl_plan_blocks(bound.ctypes.data_as(C.c_void_p), R, B, cut)
+    beg, end, row, slot, split_row, split_ptr = (_field(wl.wl_items_field, i) for i in range(6))
+    assert n == len(beg) and n % 8 == 0 and np.all(end - beg <= cut)
+    seen, written, of_slot = np.zeros(ends[-1, -1], int), np.zeros(R, int), {}
+    for i in range(n):
+        if row[i] < 0:
+            continue
+        seen[beg[i]:end[i]] += 1
+        if beg[i] < end[i]:
+            b = np.searchsorted(ends[row[i]], beg[i], side="right")
+            assert bound[row[i], b] <= beg[i] and end[i] <= bound[row[i], b + 1] and i % 8 == b % 8
+        if slot[i] < 0:
+            written[row[i]] += 1
+        else:
+            assert slot[i] not in of_slot
+            of_slot[slot[i]] = row[i]
+    assert np.all(seen == 1)
+    for k, r in enumerate(split_row):
+        written[r] += 1
+        assert all(of_slot[s] == r for s in range(split_ptr[k], split_ptr[k + 1]))
+    assert np.all(written == 1) and len(of_slot) == split_ptr[-1]
+
+
+@pytest.mark.parametrize("E,d,R,rows,want", [
+    (131071, 128, 1, 0.6, "000"), (131072, 128, 1, 0.6, "110"), (131072, 128, 1, 0.96, "000"), (240000, 32, 8, 0.6, "000"), (250000, 32, 8, 0.6, "100"),
+    (269999, 64, 8, 0.6, "100"), (270000, 64, 8, 0.6, "110"), (1079999, 64, 8, 0.6, "110"), (1080000, 64, 8, 0.6, "111"), (8499999, 32, 400, 0.6, "100"),
+    (8500000, 32, 400, 0.6, "110"), (2499999, 128, 400, 0.6, "110"), (2500000, 128, 400, 0.6, "111"), (1 << 30, 64, 1 << 20, 0.6, "100")])
+def test_rows_per_run_where_they_pay(wl, E, d, R, rows, want):
+    """RGCN, RGAT, and RGAT forwards that keep nothing."""
+    pick_ = lambda layer, heads=1, flags=0: wl.wl_run_rows(C.c_longlong(E), C.c_longlong(E), C.c_longlong(E), C.c_longlong(int(rows * E)),
+                                                           C.c_longlong(int(rows * E)), layer, heads, R, d, flags)
+    assert "".join(str(pick_(layer)) for layer in range(3)) == want
+    assert "".join(str(pick_(layer, flags=32)) for layer in range(3)) == want                # the accumulation of gradients
+    assert not any(pick_(layer, flags=f) for layer in range(3) for f in (1, 2, 4, 8, 16)) and not pick_(1, heads=2)
