@@ -435,7 +435,7 @@ __global__ void k_several(long long Q, const int32_t* idx, const int32_t* run_pt
 // run i of the (relation, destination) order; incl: running counts of the runs with several edges in that order, num: in run order
 __global__ void k_run_rows(long long Q, const int32_t* relrun_idx, const int32_t* relrun_ptr, const int32_t* run_rel, const int32_t* run_ptr,
                            const int32_t* run_dst, const int32_t* in_src, const int32_t* incl, const int32_t* num, int32_t* run_row,
-                           int32_t* run_row_tag, int32_t* multi_run, int32_t* row_in, int32_t* row_dst, int32_t* row_run,
+                           int32_t* run_tag, int32_t* multi_run, int32_t* row_in, int32_t* row_dst, int32_t* row_run,
                            int32_t* multi_end) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= Q) return;
@@ -445,7 +445,7 @@ __global__ void k_run_rows(long long Q, const int32_t* relrun_idx, const int32_t
     const int32_t row = multi ? b + mine - 1 : b + several + ((int32_t)i - b - mine);
     run_row[q] = row;
     row_run[row] = q;
-    run_row_tag[q] = multi ? (int32_t)((uint32_t)row | 0x80000000u) : row;
+    run_tag[q] = multi ? (int32_t)((uint32_t)q | 0x80000000u) : q;
     if (multi) multi_run[num[q] - 1] = q;
     row_dst[row] = run_dst[q];
     row_in[row] = multi ? (int32_t)((uint32_t)(num[q] - 1) | 0x80000000u) : in_src[beg];
@@ -502,21 +502,21 @@ rgnn_status_t block_bounds(const rgnn_graph* g, int B, const int32_t* rel_ptr, c
     return RGNN_OK;
 }
 
-// Fills g->run_row .. g->src_invc; src_ptr ([N + 1], edges by source) goes to the host.  E > 0.  Synchronous.
+// Fills g->run_tag .. g->row_run; src_ptr ([N + 1], edges by source) goes to the host.  E > 0.  Synchronous.
 rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr) {
     const long long N = g->N, E = g->E, P = g->P, Q = g->Q;
-    Tmp a, b, c, d;
+    Tmp a, b, c, d, run_row;                               // run_row: row of a run
     RGNN_TRY(a.alloc((size_t)std::max(P, Q) * sizeof(int32_t)));
     RGNN_TRY(b.alloc((size_t)std::max(P, Q) * sizeof(int32_t)));
     RGNN_TRY(c.alloc((size_t)std::max(P, Q) * sizeof(int32_t)));
     RGNN_TRY(d.alloc(((size_t)N + 1) * sizeof(int32_t)));
-    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->run_row));
+    RGNN_TRY(run_row.alloc((size_t)Q * sizeof(int32_t)));
     RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_in));
     RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_dst));
     RGNN_TRY(keep<int32_t>(g, (size_t)g->R, &g->multi_end));
     RGNN_TRY(keep<int32_t>(g, (size_t)E, &g->src_row));
     RGNN_TRY(keep<float>(g, (size_t)E, &g->src_invc));
-    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->run_row_tag));
+    RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->run_tag));
     RGNN_TRY(keep<int32_t>(g, (size_t)g->num_multi_runs, &g->multi_run));
     for (int32_t** p : {&g->src_run, &g->src_rel, &g->in_spos}) RGNN_TRY(keep<int32_t>(g, (size_t)E, p));
     RGNN_TRY(keep<int32_t>(g, (size_t)P, &g->pair_spos));
@@ -527,14 +527,14 @@ rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr) {
     LAUNCH(k_several, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RUN_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), c.as<int32_t>(), (size_t)Q));
     LAUNCH(k_run_rows, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RELRUN_PTR], g->idx[RGNN_IDX_RUN_REL], g->idx[RGNN_IDX_RUN_PTR],
-           g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_IN_SRC], c.as<int32_t>(), b.as<int32_t>(), g->run_row, g->run_row_tag,
+           g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_IN_SRC], c.as<int32_t>(), b.as<int32_t>(), run_row.as<int32_t>(), g->run_tag,
            g->multi_run, g->row_in, g->row_dst, g->row_run, g->multi_end);
     LAUNCH(k_pair_len, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], g->idx[RGNN_IDX_OUT_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), b.as<int32_t>(), (size_t)P));
     LAUNCH(k_pair_start, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], a.as<int32_t>(), b.as<int32_t>(), g->pair_spos);
     LAUNCH(k_src_ptr, (size_t)N + 1, N, P, E, g->idx[RGNN_IDX_SRCPAIR_PTR], g->idx[RGNN_IDX_SRCPAIR_IDX], g->pair_spos, d.as<int32_t>());
     LAUNCH(k_src_edges, (size_t)E, E, g->idx[RGNN_IDX_OUT_EPOS], g->idx[RGNN_IDX_OUT_PTR], g->idx[RGNN_IDX_IN_PAIR], g->idx[RGNN_IDX_IN_RUN],
-           g->idx[RGNN_IDX_IN_REL], g->idx[RGNN_IDX_IN_CNT], g->run_row, g->pair_spos, g->in_invc, g->src_row, g->src_invc, g->src_run, g->src_rel, g->in_spos);
+           g->idx[RGNN_IDX_IN_REL], g->idx[RGNN_IDX_IN_CNT], run_row.as<int32_t>(), g->pair_spos, g->in_invc, g->src_row, g->src_invc, g->src_run, g->src_rel, g->in_spos);
     src_ptr.resize((size_t)N + 1);
     RGNN_HIP(hipMemcpy(src_ptr.data(), d.p, src_ptr.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     return RGNN_OK;

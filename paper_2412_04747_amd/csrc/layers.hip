@@ -596,14 +596,14 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
         RGNN_TRY(rgcn_run_inputs(g, desc, h ? X : static_cast<const void*>(X32), h, A, w.partial, st));
         if (h) {
             TypedLinearFwdBf16Args a{&g->run_tiles_cu2, X, g->row_in, 0, W, nullptr, w.Hs, "typed_linear_fwd"};
-            a.A2 = A; a.planes_end = g->multi_end;
+            a.A2 = A; a.planes_end = g->multi_end; a.to = g->row_run;
             RGNN_TRY(typed_linear_fwd_bf16(a, st));
         } else {
             TypedLinearArgs a{};
-            a.tiles = run_chunks(g, D).f32; a.X = X32; a.X2 = A; a.gather = g->row_in; a.W = W32; a.Y = static_cast<float*>(w.Hs); a.sign_matters = 1;
+            a.tiles = run_chunks(g, D).f32; a.X = X32; a.X2 = A; a.gather = g->row_in; a.to = g->row_run; a.W = W32; a.Y = static_cast<float*>(w.Hs); a.sign_matters = 1;
             RGNN_TRY(typed_linear_fwd(desc->d_in, D, a, st));
         }
-        RGNN_TRY(gather_sum(g->dstrun_items, D, nullptr, g->run_row, 0, nullptr, 1, 0, w.Hs, out, w.partial, st, 0, "aggregate_fwd", "aggregate_fwd.combine",
+        RGNN_TRY(gather_sum(g->dstrun_items, D, nullptr, nullptr, 0, nullptr, 1, 0, w.Hs, out, w.partial, st, 0, "aggregate_fwd", "aggregate_fwd.combine",
                             1, h, 0));
     } else {
         // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
@@ -817,7 +817,7 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
         // 2. the inputs of the runs with several edges, weighted within the run;  3. Y = A W, a run with one edge reading its source's row
         RGNN_TRY(rgat_run_inputs(g, K, Xf, rs.wsp, rs.s_dst, desc->slope, rs.A, rs.lq, rs.partial, rs.part_ms, st));
         TypedLinearArgs a{};
-        a.tiles = run_chunks(g, D).f32; a.X = Xf; a.X2 = rs.A; a.gather = g->row_in; a.W = Wf; a.Y = rs.Y; a.sign_matters = 1;
+        a.tiles = run_chunks(g, D).f32; a.X = Xf; a.X2 = rs.A; a.gather = g->row_in; a.to = g->row_run; a.W = Wf; a.Y = rs.Y; a.sign_matters = 1;
         RGNN_TRY(typed_linear_fwd(K, D, a, st));
         // 4. per destination over its runs: softmax and weighted sum
         return rgat_run_aggregate(g, D, rs.Y, ws, rs.s_dst, desc->slope, rs.lq, static_cast<float*>(out), rs.ms, w.partial, w.part_ms, st);

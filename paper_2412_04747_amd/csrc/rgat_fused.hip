@@ -518,7 +518,7 @@ rgnn_status_t rgat_run_aggregate(const rgnn_graph* g, int D, const float* Y, con
     const ItemList& L = g->dstrun_items;
     if (L.num_items == 0) return RGNN_OK;
     FusedArgs a{};
-    a.in_pair = g->run_row_tag; a.in_rel = g->idx[RGNN_IDX_RUN_REL];
+    a.in_pair = g->run_tag; a.in_rel = g->idx[RGNN_IDX_RUN_REL];
     a.Hs = Y; a.w_s = w_s; a.s_dst = s_dst; a.slope = slope; a.lq = reinterpret_cast<float2*>(lq);
     a.out = out; a.ms = reinterpret_cast<float2*>(ms); a.partial = partial; a.part_ms = reinterpret_cast<float2*>(part_ms);
     RGNN_TRY(launch_walk<kRuns>(g, L, D, 1, a, "aggregate_fwd", st));

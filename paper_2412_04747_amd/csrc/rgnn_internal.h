@@ -148,8 +148,7 @@ struct rgnn_graph {
     // several edges before one, destination) order.
     bool run_rows = false;
     int64_t num_multi_runs = 0, num_single_runs = 0;
-    int32_t* run_row = nullptr;            // [Q] row of a run
-    int32_t* run_row_tag = nullptr;        // [Q] the same, with the top bit set when the run has several edges
+    int32_t* run_tag = nullptr;            // [Q] the run, with the top bit set when it has several edges
     int32_t* multi_run = nullptr;          // [num_multi_runs] run of each number
     int32_t* row_in = nullptr;             // [Q] by row: source of the run's only edge, or the top bit | number of the run among those
                                            // with several edges, in run order
@@ -200,7 +199,8 @@ struct TypedLinearArgs {
     int y_stride = 1;        // rows of Y are y_stride * d_out floats apart (1 or 2)
     int relu = 0;            // with accumulate: Y = max(Y + result, 0)
     const FoldArgs* fold = nullptr;   // folds weights in the same launch (gathered rows, no scatter, accumulate or vec)
-    const float* X2 = nullptr;        // gather[i] < 0: row i reads X2[gather[i] & 0x7FFFFFFF] (plain products of gathered rows)
+    const float* X2 = nullptr;        // gather[i] < 0: row i reads X2[gather[i] & 0x7FFFFFFF] (plain products of gathered rows); row i of the
+    const int32_t* to = nullptr;      // result is then row to[i] of Y
     int sign_matters = 0;    // 1: a backward takes a branch on the sign of what becomes of Y (leaky ReLU; ReLU, also the caller's own)
 };
 rgnn_status_t typed_linear_fwd(int d_in, int d_out, const TypedLinearArgs& a, hipStream_t st);
@@ -286,6 +286,7 @@ struct TypedLinearFwdBf16Args {
     // come first, up to row planes_end[seg] (one weight)
     const void* A2 = nullptr;
     const int32_t* planes_end = nullptr;
+    const int32_t* to = nullptr;     // with A2: row i of the result is row to[i] of Y
 };
 rgnn_status_t typed_linear_fwd_bf16(const TypedLinearFwdBf16Args& a, hipStream_t st);
 

@@ -80,7 +80,7 @@ __device__ __forceinline__ int run_end(const int32_t* __restrict__ tile_seg, int
 //   DYG      backward: dY rows are read through the list  RS       backward: rowscale / Avec / xvec in use
 //   OS       the rows of Y are OS * ND floats apart (2: the key or message half of HGT's pair rows)
 //   XSEL     input rows come from two tensors: list entry g >= 0 is row g of X, otherwise row g & 0x7FFFFFFF of X2 (the rows
-//            per run: a run's only source, or the sum of its sources)
+//            per run: a run's only source, or the sum of its sources); forward: row i of the result goes to row to[i] of Y
 //
 // At width 128 the stage holds half of the columns at a time, so that eight wavefronts fit beside the 64 KB weight: two per
 // SIMD, one multiplying while the other stages; and the result goes to memory straight from the accumulators, a 128-byte line
@@ -97,6 +97,11 @@ struct FwdShape {
     static constexpr int XS = (!DIRECT && ND > KS ? ND : KS) + 4;   // row stride of the per-wave stage
     static constexpr size_t LDS = sizeof(float) * (KD * ND + NW * 32 * XS);
 };
+// what lane r keeps for the lower half of the wavefront, lane r + 4 for the upper one
+__device__ __forceinline__ int row_of_half(int v, int r, int kh) {
+    const int a = __builtin_amdgcn_readlane(v, r), b = __builtin_amdgcn_readlane(v, r + 4);
+    return kh ? b : a;
+}
 // row g of X, or with XSEL of the tensor that g's top bit says
 template <int D, bool XSEL>
 __device__ __forceinline__ const float* input_row(const float* __restrict__ X, const float* __restrict__ X2, int g) {
@@ -105,7 +110,8 @@ __device__ __forceinline__ const float* input_row(const float* __restrict__ X, c
 template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, int OS = 1, bool XSEL = false>
 __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                          const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
-                                         float* __restrict__ s_out, int s_heads, int relu, const float* __restrict__ X2 = nullptr) {
+                                         float* __restrict__ s_out, int s_heads, int relu, const float* __restrict__ X2 = nullptr,
+                                         const int32_t* __restrict__ to = nullptr) {
     static_assert(!XSEL || (GATHER && !SCATTER && !ACCUM && !VEC), "two input tensors: plain products of gathered rows");
     using S = FwdShape<KD, ND, VEC, ACCUM>;
     constexpr int NW = S::NW, XS = S::XS, KS = S::KS, PH = KD / KS;
@@ -140,7 +146,9 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
         constexpr bool LANEIDX = GATHER && KD == 128;
         v4f xr[NX];
         int gi[LANEIDX ? 1 : NX], gcur[SCATTER ? NX : 1];
+        int ti = 0, tcur = 0;                               // XSEL: to[] of row (lane & 31), like gi and gcur
 #define RGNN_FETCH_IDX(U)                                                           \
+    if (XSEL) ti = to[min(ra + (U) * 32 + m, rbnd - 1)];                            \
     if (LANEIDX) gi[0] = gather[min(ra + (U) * 32 + m, rbnd - 1)];                  \
     else {                                                                          \
         _Pragma("unroll") for (int it = 0; it < NX; ++it) {                         \
@@ -153,12 +161,14 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
         const int g_ = LANEIDX ? __shfl(gi[0], ri + it * RPI) : gi[LANEIDX ? 0 : it]; \
         xr[it] = *reinterpret_cast<const v4f*>(input_row<KD, XSEL>(X, X2, g_) + ci * 4); \
         if (SCATTER) gcur[SCATTER ? it : 0] = g_;                                   \
-    }
+    }                                                                               \
+    if (XSEL) tcur = ti;
         RGNN_FETCH_IDX(wave)
         RGNN_FETCH_ROWS()
         RGNN_FETCH_IDX(wave + NW)
         for (int u = wave; u < nu; u += NW) {
             int gout[SCATTER ? NX : 1];
+            const int tout = tcur;
             if (SCATTER) {
 #pragma unroll
                 for (int it = 0; it < NX; ++it) gout[SCATTER ? it : 0] = gcur[SCATTER ? it : 0];
@@ -218,6 +228,7 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
                     if (full || acc_row(v, kh) < left) {
+                        float* const yx = Y + (size_t)(XSEL ? row_of_half(tout, acc_row(v, 0), kh) : 0) * (OS * ND) + m;
 #pragma unroll
                         for (int b = 0; b < CB; ++b) {
                             float y = acc[b][v];
@@ -225,7 +236,7 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
                                 y += old1[DIRECT && ACCUM ? b * 16 + v : 0];
                                 if (relu) y = y > 0.f ? y : 0.f;
                             }
-                            __builtin_nontemporal_store(y, yu + acc_row(v, 0) * (OS * ND) + b * 32);
+                            __builtin_nontemporal_store(y, XSEL ? yx + b * 32 : yu + acc_row(v, 0) * (OS * ND) + b * 32);
                         }
                     }
             } else {
@@ -239,7 +250,7 @@ __device__ __forceinline__ void fwd_wave(const TileArgs& t, int chunk, const flo
                     const int r = ro + it * RPO, row = ra + u * 32 + r;
                     const bool ok = row < rbnd;
                     float4 y = *reinterpret_cast<const float4*>(Xw + r * XS + co * 4);
-                    const size_t d = SCATTER ? (size_t)gout[SCATTER ? it : 0] : (size_t)min(row, rbnd - 1);
+                    const size_t d = XSEL ? (size_t)__shfl(tout, r) : SCATTER ? (size_t)gout[SCATTER ? it : 0] : (size_t)min(row, rbnd - 1);
                     float4* yp = reinterpret_cast<float4*>(Y + d * (OS * ND) + co * 4);
                     if (ACCUM) {
                         const v4f o = old[ACCUM && !DIRECT ? it : 0];
@@ -274,13 +285,14 @@ template <int KD, int ND, bool GATHER, bool SCATTER, bool ACCUM, bool VEC, bool 
 __global__ __launch_bounds__((64 * FwdShape<KD, ND, VEC, ACCUM>::NW))
 void typed_linear_fwd_wave_kernel(TileArgs t, const float* __restrict__ X, const int32_t* __restrict__ gather,
                                   const float* __restrict__ W, float* __restrict__ Y, const float* __restrict__ vec,
-                                  float* __restrict__ s_out, int s_heads, int relu, FoldArgs fold, const float* __restrict__ X2) {
+                                  float* __restrict__ s_out, int s_heads, int relu, FoldArgs fold, const float* __restrict__ X2,
+                                  const int32_t* __restrict__ to) {
     // RGAT: the folded vectors that the kernel after this one reads (a launch of their own cost 5 us behind this one)
     if (FOLD && (int)blockIdx.x >= (int)gridDim.x - fold.blocks) {
         if (threadIdx.x < 256) fold_weight_block(fold, blockIdx.x - (gridDim.x - fold.blocks));
         return;
     }
-    fwd_wave<KD, ND, GATHER, SCATTER, ACCUM, VEC, 1, XSEL>(t, blockIdx.x, X, gather, W, Y, vec, s_out, s_heads, relu, X2);
+    fwd_wave<KD, ND, GATHER, SCATTER, ACCUM, VEC, 1, XSEL>(t, blockIdx.x, X, gather, W, Y, vec, s_out, s_heads, relu, X2, to);
 }
 
 // Several products that do not depend on each other in one launch (HGT: a node linear, rows gathered and scattered, and the two
@@ -729,7 +741,7 @@ static rgnn_status_t launch_fwd_wave(const TypedLinearArgs& a, hipStream_t st) {
     KernelTimer kt(st, a.label ? a.label : "typed_linear_fwd");
     const FoldArgs fold = a.fold ? *a.fold : FoldArgs{};
     hipLaunchKernelGGL(kern, dim3(a.tiles->num_chunks + fold.blocks), dim3(64 * S::NW), lds, st, tile_args(*a.tiles), a.X, a.gather, a.W, a.Y,
-                       a.vec, a.s_out, a.s_heads, a.relu, fold, a.X2);
+                       a.vec, a.s_out, a.s_heads, a.relu, fold, a.X2, a.to);
     RGNN_HIP(hipGetLastError());
     return RGNN_OK;
 }
@@ -744,7 +756,7 @@ static rgnn_status_t launch_fwd(const TypedLinearArgs& a, hipStream_t st) {
     if (a.relu && !ac) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: the activation is built into the accumulating variant only");
     if (a.y_stride != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: output rows two widths apart are built in the launches of several products only");
     if (a.X2) {
-        if (!g || sc || ac || v || a.fold) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: two input tensors go with plain products of gathered rows");
+        if (!g || sc || ac || v || a.fold || !a.to) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed linear forward: two input tensors go with plain products of gathered rows");
         return launch_fwd_wave<KD, ND, true, false, false, false, false, true>(a, st);
     }
     if (g && !sc && !ac && v) return launch_fwd_wave<KD, ND, true, false, false, true>(a, st);

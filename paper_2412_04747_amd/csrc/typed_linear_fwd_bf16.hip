@@ -31,6 +31,7 @@ struct FwdArgs {
     void* Y;
     const bf16_t* A2;        // XSEL
     const int32_t* planes_end;
+    const int32_t* to;
 };
 
 
@@ -39,6 +40,8 @@ constexpr int D = 128, TILE = 64 * 2 * D, WT = D * 2 * D;      // bytes of 64 ro
 //   NB  weights      SCATTER  row i of the result goes where row i of the input came from
 //   XSEL  rows per run: list entry g >= 0 is row g of X, otherwise row g & 0x7FFFFFFF of A2, two bf16 planes (a sum of bf16 rows rounded
 //         to one would add a rounding that the sum of the products does not have).  Within a segment the rows of A2 come first.
+//         Row i of the result goes to row to[i]: in the order of the walk that sums them (16M edges, 7M runs: this kernel 998 -> 1018 us, the
+//         walk 812 -> 742; the fp32 walks of the runs take the same either way).
 template <int NB, bool SCATTER, bool XSEL = false>
 __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
     static_assert((NB == 1 || !SCATTER) && (!XSEL || (NB == 1 && !SCATTER)), "combinations the layers use");
@@ -65,12 +68,16 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
     const int t0 = a.chunk_tile[blockIdx.x], t1 = a.chunk_tile[blockIdx.x + 1];
     if (t0 >= t1) return;
     rgnn_v4u xr[2], xl[2];
-    int gi[2], gcur[2];
+    int gi[2], gcur[2], to[2] = {0, 0}, tn[2] = {0, 0};     // XSEL: to[] of the rows in xr, and of those asked for next
     TileTable tt(a.tile_seg, a.tile_row0, a.tile_row1, t0, t1);
     auto fetch_idx = [&](int ti) {
         const int l = tt.lane_of(ti), row0 = tt.row0_at(l), row1 = tt.row1_at(l);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) gi[k] = a.gather[min(row0 + lr + 32 * k, row1 - 1)];
+        for (int k = 0; k < 2; ++k) {
+            const int row = min(row0 + lr + 32 * k, row1 - 1);
+            gi[k] = a.gather[row];
+            if (XSEL) tn[k] = a.to[row];
+        }
     };
     auto fetch = [&]() {
 #pragma unroll
@@ -80,6 +87,7 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
             xr[k] = *reinterpret_cast<const rgnn_v4u*>(x);
             if (XSEL) xl[k] = *reinterpret_cast<const rgnn_v4u*>(x + (gi[k] < 0 ? D : 0));   // (unconditional; a row of X again is not used)
             gcur[k] = gi[k];
+            to[k] = tn[k];
         }
     };
     fetch_idx(t0);
@@ -107,7 +115,7 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
             two[k] = XSEL && row0 + 32 * k < planes_end;
             const rgnn_v4u z = {0u, 0u, 0u, 0u};
             if (two[k]) *reinterpret_cast<rgnn_v4u*>(Lt + io + k * 32 * 256) = gcur[k] < 0 ? xl[k] : z;
-            gout[k] = gcur[k];
+            gout[k] = XSEL ? to[k] : gcur[k];
         }
         __syncthreads();   // the tile is complete, and the previous one's result rows have been read out
         fetch();           // unconditional, past the end the last tile again: see the backward
@@ -149,10 +157,10 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 const int r = lr + 32 * k;
-                const size_t to = SCATTER ? (size_t)gout[k] : (size_t)(row0 + r);
+                const size_t at = SCATTER || XSEL ? (size_t)gout[k] : (size_t)(row0 + r);
                 if (r < rows)
                     __builtin_nontemporal_store(*reinterpret_cast<const rgnn_v4u*>(St + nb * TILE + io + k * 32 * 256),
-                                                reinterpret_cast<rgnn_v4u*>(static_cast<bf16_t*>(a.Y) + (to * NB + nb) * D + lc * 8));
+                                                reinterpret_cast<rgnn_v4u*>(static_cast<bf16_t*>(a.Y) + (at * NB + nb) * D + lc * 8));
             }
     }
 }
@@ -167,11 +175,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 rgnn_status_t typed_linear_fwd_bf16(const TypedLinearFwdBf16Args& x, hipStream_t st) {
     const TileList& t = *x.tiles;
     if (t.num_tiles == 0) return RGNN_OK;
-    if (!x.gather || (x.W2 && x.scatter_out) || (x.A2 && (x.W2 || x.scatter_out || !x.planes_end))) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_fwd_bf16: gathered rows; two weights with result rows in order only");
+    if (!x.gather || (x.W2 && x.scatter_out) || (x.A2 && (x.W2 || x.scatter_out || !x.planes_end || !x.to))) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_fwd_bf16: gathered rows; two weights with result rows in order only");
     const int nb = x.W2 ? 2 : 1;
     const size_t lds = (size_t)nb * WT + (1 + nb + (x.A2 ? 1 : 0)) * TILE;
     const FwdArgs a{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, static_cast<const bf16_t*>(x.X), x.gather,
-                    {static_cast<const bf16_t*>(x.W), static_cast<const bf16_t*>(x.W2)}, x.Y, static_cast<const bf16_t*>(x.A2), x.planes_end};
+                    {static_cast<const bf16_t*>(x.W), static_cast<const bf16_t*>(x.W2)}, x.Y, static_cast<const bf16_t*>(x.A2), x.planes_end, x.to};
     auto kern = x.W2 ? typed_linear_fwd_bf16_two_kernel : x.A2 ? typed_linear_fwd_bf16_kernel<false, true> : x.scatter_out ? typed_linear_fwd_bf16_kernel<true, false> : typed_linear_fwd_bf16_kernel<false, false>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, x.label);
