@@ -203,6 +203,7 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     plans.ask(g->relrun_items, relrun_ptr, item_cut(g->E));
     plans.ask(g->pair_items_multi, out_ptr, item_cut(g->E), 2);
     plans.ask(g->relpair_items, pair_ptr, item_cut(g->P));
+    for (int64_t u = 0; u < g->N; ++u) g->max_node_pairs = std::max(g->max_node_pairs, srcpair_ptr[u + 1] - srcpair_ptr[u]);
     plans.ask(g->srcpair_items, srcpair_ptr, 1 << 30);
     for (int64_t v = 0; v < g->N; ++v) g->max_in_degree = std::max<int64_t>(g->max_in_degree, in_ptr[v + 1] - in_ptr[v]);
     // (only schedules of small graphs ask for it: a destination's runs are dealt to eight half wavefronts in turn)

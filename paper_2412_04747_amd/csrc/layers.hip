@@ -325,6 +325,10 @@ size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // of the nodes are folded into the per-relation weights (Wf = Wk[type] Watt[r], Wv[type] Wmsg[r]), so
 // K, V and their gradients do not exist and the per-pair rows come straight from X.
 inline bool hgt_folded(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_hgt_folded(g->rel_src_tied, d->flags); }
+// The sum over a node's pairs goes with the query's product of the node (rows in bf16).
+inline bool hgt_pairs_with_query(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
+    return hgt_folded(g, d) && rows_bf16(d) && sched_hgt_pairs_with_query(g->N, g->P, g->max_node_pairs);
+}
 // folded path, fp32 rows up to width 64: the backwards of the two pair linears and of the query linear in one launch.  Backward of the
 // layer with one launch / a launch each, width 64: 30 relations 100 / 123 us at 100k edges, 706 / 752 at 1.5M; 500 of equal frequency
 // 292 / 297 at 20k, 583 / 644 at 400k; 1500 871 / 892 at 100k, 2005 / 2022 at 1.5M.
@@ -387,7 +391,7 @@ size_t carve_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     w->dKM = c.rows(2 * pd, h); w->dQ = c.rows(nd, h);
     w->dKp = c.rows(pd, h); w->dVp = c.rows(h && fold ? 0 : pd, h);     // folded, bf16 rows: dKp holds the sum of both
     w->dK = c.rows(fold ? 0 : nd, h); w->dV = c.rows(fold ? 0 : nd, h);
-    w->dXk = c.take<float>(h || fold ? 0 : nd); w->dXq = c.take<float>(h && !fold ? 0 : nd); w->dXv = c.take<float>(h || fold ? 0 : nd);
+    w->dXk = c.take<float>(h || fold ? 0 : nd); w->dXq = c.take<float>((h && !fold) || hgt_pairs_with_query(g, d) ? 0 : nd); w->dXv = c.take<float>(h || fold ? 0 : nd);
     // shares of the weight gradients, which one launch adds: output, query (and unfolded value) linears; both pair linears
     const bool jobs = hgt_bwd_jobs(g, d);
     const size_t nodes = std::max(tl_bwd_scratch(h, node_chunks(g, d->d_out), d->d_in, d->d_out), jobs ? typed_linear_bwd_scratch_floats(D, D, g->node_tiles_hgt) : 0);
@@ -1170,6 +1174,14 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
             b.tiles = &g->pair_tiles_cu1; b.X = X; b.gather = psrc; b.W = sv.Wf_att; b.W2 = sv.Wf_msg; b.w_bf16 = 1; b.dY = w.dKM;
             b.dy_stride = 2; b.dXrow = w.dKp; b.dW = w.dWf_att; b.dW2 = w.dWf_msg; b.part = w.pair_part[0]; b.label = "pair_linear_bwd"; b.sums = &sums;
             RGNN_TRY(typed_linear_bwd_bf16(D, b, st));
+            if (hgt_pairs_with_query(g, desc)) {
+                // dX = dQ Wq^T + sums over each node's pairs, with dWq
+                TypedLinearBwdBf16Args q{};
+                q.tiles = node_chunks(g, D).cu2; q.X = X; q.gather = perm; q.both_gathered = 1; q.W = Wq16; q.w_bf16 = 1; q.dY = w.dQ;
+                q.dXrow = dX; q.dx_f32 = 1; q.accumulate = acc; q.dW = static_cast<float*>(dWq); q.part = w.node_part[1]; q.label = "node_linear_q_bwd";
+                q.sum_ptr = g->idx[RGNN_IDX_SRCPAIR_PTR]; q.sum_row = g->idx[RGNN_IDX_SRCPAIR_IDX]; q.sum_rows = w.dKp; q.sums = &sums;
+                RGNN_TRY(typed_linear_bwd_bf16(D, q, st));
+            }
         } else if (!hgt_bwd_jobs(g, desc)) {
             RGNN_TRY(tl_bwd(false, pair_chunks(g, D), D, Xr, psrc, 0, static_cast<const float*>(sv.Wf_att), nullptr, dKa, w.dKp, false, w.dWf_att,
                             w.pair_part[0], "pair_linear_att_bwd", st, false, nullptr, nullptr, nullptr, 0, 2, &sums));
@@ -1188,13 +1200,14 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
             b[2].dY = static_cast<const float*>(w.dQ); b[2].dXrow = w.dXq; b[2].dW = static_cast<float*>(dWq); b[2].part = w.node_part[1];
             for (TypedLinearBwdArgs& x : b) { x.X = static_cast<const float*>(Xr); x.sums = &sums; }
             RGNN_TRY(typed_linear_bwd_jobs(D, b, 3, "node_pair_linears_bwd", st));
-        } else {
+        } else if (!hgt_pairs_with_query(g, desc)) {
             RGNN_TRY(tl_bwd(h, node_chunks(g, D), D, Xr, perm, 1, Wq32, Wq16, w.dQ, w.dXq, false, static_cast<float*>(dWq),
                             w.node_part[1], "node_linear_q_bwd", st, false, nullptr, nullptr, nullptr, 0, 1, &sums));
         }
         RGNN_TRY(sums.launch(st));
         RGNN_TRY(hgt_fold_bwd(g->T, g->R, hw, w.dWf_att, w.dWf_msg, static_cast<float*>(dWk), static_cast<float*>(dWv),
                               static_cast<float*>(dWatt), static_cast<float*>(dWmsg), static_cast<float*>(dmu), st));
+        if (hgt_pairs_with_query(g, desc)) return ga.flush(st);
         if (acc) RGNN_TRY(add_into((size_t)g->N * D, static_cast<const float*>(dX), w.dXq, st));
         RGNN_TRY(node_grad_sum(g, D, w.dKp, nullptr, nullptr, w.dXq, dX, st, h, 0, 1, h ? nullptr : w.dVp));
         return ga.flush(st);

@@ -136,6 +136,7 @@ struct rgnn_graph {
     rgnn::ItemList pair_items;             // transposed edges by pair
     rgnn::ItemList pair_items_multi;       // the same, pairs with two or more edges only
     rgnn::ItemList srcpair_items;          // pairs by source node (never cut)
+    int32_t max_node_pairs = 0;            // most pairs of a source node
     int32_t* in_pair_tag = nullptr;        // [E] in_pair with the top bit set when the pair has a single edge
     float* pair_scale = nullptr;           // [P] 1 / c_{v,r} of the only edge of a single-edge pair, 1 for the other pairs
     int32_t* pair_ysel = nullptr;          // [P] pair id, or for a pair with one edge the top bit | that edge's destination
@@ -314,6 +315,10 @@ struct TypedLinearBwdBf16Args {
     const void* dY_alt = nullptr;
     const float* yscale = nullptr;
     const void* A2 = nullptr;    // gather[i] < 0: row i of X is the first plane of row gather[i] & 0x7FFFFFFF of A2; row i of dY is dY[ysel[i]] (no dY_alt)
+    // optional (bf16 weight, fp32 dXrow gathered on both sides): dXrow[n] += the rows sum_row[sum_ptr[n] .. sum_ptr[n + 1]) of sum_rows
+    const int32_t* sum_ptr = nullptr;
+    const int32_t* sum_row = nullptr;
+    const void* sum_rows = nullptr;
     ShareSums* sums = nullptr;   // as in TypedLinearBwdArgs
 };
 rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipStream_t st);

@@ -39,6 +39,9 @@ struct BwdArgs {
     const bf16_t* dY_alt;
     const float* yscale;
     const bf16_t* A2;        // XSEL
+    const int32_t* sum_ptr;  // PAIRS
+    const int32_t* sum_row;
+    const bf16_t* sum_rows;
     const void* W[2];
     void* dX;
     float* part;
@@ -58,12 +61,16 @@ __device__ __forceinline__ rgnn_v4u scale8(rgnn_v4u x, float s) {
 //   SEL    row i of dY is dY[ysel[i]], or dY_alt[ysel[i] & 0x7FFFFFFF] when the top bit of ysel[i] is set; with yscale it is
 //          multiplied by yscale[i] (and rounded to bf16 again) on its way into LDS
 //   DX32   dXrow is fp32, ACC: and added to           otherwise bf16
+//   PAIRS  with BOTH and DX32: dXrow row n also gets the sum of the rows sum_row[sum_ptr[n] .. sum_ptr[n + 1]) of sum_rows (HGT: the query's
+//          part of dX and the sum over the node's pairs).  A lane adds its 16 columns of its row, two rows at a time, the list two tiles ahead.
+//          As a walk of its own that read the query's part again: 2M nodes, 5.4M pairs 408 + 670 us, so 862.  (Whole rows added by the threads
+//          that load a tile, and handed over through LDS, need 25 registers more than two workgroups per compute unit leave: 968.)
 //   XSEL   rows per run (typed_linear_fwd_bf16.hip): X rows from X or A2, and row i of dY is dY[ysel[i]].  The first plane of A2 is enough
 //          here: a rounding of A[q] / c weighs what those of its c edges' dOut / c did in rows per pair (dW of 2M edges against 64 bits:
 //          6.9e-4 per pair, 4.9e-4 per run)
-template <int NB, int WPL, bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool XSEL = false>
+template <int NB, int WPL, bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool XSEL = false, bool PAIRS = false>
 __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
-    static_assert(!(SEL && BOTH) && (GATHER || !BOTH) && (DX32 || !ACC) && (NB == 1 || !SEL) && (!XSEL || (SEL && GATHER)), "combinations the layers use");
+    static_assert(!(SEL && BOTH) && (GATHER || !BOTH) && (DX32 || !ACC) && (NB == 1 || !SEL) && (!XSEL || (SEL && GATHER)) && (!PAIRS || (BOTH && DX32)), "combinations the layers use");
     constexpr int D = 128, TILE = 64 * 2 * D;             // bytes of a 64-row tile
     constexpr int SLOT = NB * D * D;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -129,6 +136,21 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
         }
     };
     if (t0 >= t1) return;
+    // PAIRS: list ends and first four entries of the lane's row rb * 32 + m of this tile, list ends one tile on, node two tiles on
+    int pb = 0, pe = 0, p0 = 0, p1 = 0, p2 = 0, p3 = 0, pbn = 0, pen = 0, node = 0;
+    auto node_of = [&](int ti) {
+        const int l = tt.lane_of(ti);
+        return a.gather[min(tt.row0_at(l) + rb * 32 + m, tt.row1_at(l) - 1)];
+    };
+    auto pair_at = [&](int p, int e) { return a.sum_row[max(min(p, e - 1), 0)]; };
+    if (PAIRS) {
+        node = node_of(t0);
+        pb = a.sum_ptr[node]; pe = a.sum_ptr[node + 1];
+        node = node_of(min(t0 + 1, t1 - 1));
+        pbn = a.sum_ptr[node]; pen = a.sum_ptr[node + 1];
+        node = node_of(min(t0 + 2, t1 - 1));
+        p0 = pair_at(pb, pe); p1 = pair_at(pb + 1, pe); p2 = pair_at(pb + 2, pe); p3 = pair_at(pb + 3, pe);
+    }
     fetch_idx(t0);
     fetch();
     fetch_idx(min(t0 + 1, t1 - 1));
@@ -195,6 +217,13 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
             if (DX32 && BOTH && lc == 0) gidx[lr + 32 * k] = gcur[k];
         }
         __syncthreads();   // the tile is complete
+        const int sb = pb, se = pe, s0 = p0, s1 = p1, s2 = p2, s3 = p3;
+        if (PAIRS) {
+            pb = pbn; pe = pen;
+            p0 = pair_at(pb, pe); p1 = pair_at(pb + 1, pe); p2 = pair_at(pb + 2, pe); p3 = pair_at(pb + 3, pe);
+            pbn = a.sum_ptr[node]; pen = a.sum_ptr[node + 1];
+            node = node_of(min(ti + 3, t1 - 1));
+        }
         // (unconditional, past the end the last tile again: were the loads skipped on some path, the waits for the rows would
         // have to drain the stores issued after them as well)
         fetch();
@@ -213,6 +242,30 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
                     d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Wl + (nb * WPL + pl) * WT + wrow + at), by, d, 0, 0, 0);
             }
         // d[v] = dXrow[row rb * 32 + m][feature ob * 32 + 8 (v / 4) + 4 kh + v % 4]
+        if (PAIRS) {
+            // two rows at a time, 16 columns of each to a lane
+            auto add2 = [&](int i0, int i1, bool two) {
+                uint2 x[2][4];
+                const bf16_t* const r0 = a.sum_rows + (size_t)i0 * D + ob * 32 + 4 * kh;
+                const bf16_t* const r1 = a.sum_rows + (size_t)i1 * D + ob * 32 + 4 * kh;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[0][q] = *reinterpret_cast<const uint2*>(r0 + 8 * q);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[1][q] = *reinterpret_cast<const uint2*>(r1 + 8 * q);
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+                    if (y == 0 || two) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            d[4 * q] += __uint_as_float(x[y][q].x << 16); d[4 * q + 1] += __uint_as_float(x[y][q].x & 0xFFFF0000u);
+                            d[4 * q + 2] += __uint_as_float(x[y][q].y << 16); d[4 * q + 3] += __uint_as_float(x[y][q].y & 0xFFFF0000u);
+                        }
+                    }
+            };
+            if (sb < se) add2(s0, s1, sb + 1 < se);
+            if (sb + 2 < se) add2(s2, s3, sb + 3 < se);
+            for (int p = sb + 4; p < se; p += 2) add2(a.sum_row[p], pair_at(p + 1, se), p + 1 < se);
+        }
         if (DX32) {
             if (rb * 32 + m < rows) {
                 const size_t r = BOTH ? (size_t)gidx[rb * 32 + m] : (size_t)(row0 + rb * 32 + m);
@@ -276,9 +329,9 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
 
 // One weight in bf16: 128 registers and 80 KB of LDS leave room for two workgroups per compute unit, so that one loads
 // while the other multiplies; two weights (or one split into two planes) take twice the room for W and run alone.
-template <bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool XSEL = false>
+template <bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool XSEL = false, bool PAIRS = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void typed_linear_bwd_bf16_kernel(BwdArgs a) {
-    bwd_tiles<1, 1, GATHER, BOTH, SEL, DX32, ACC, XSEL>(a);
+    bwd_tiles<1, 1, GATHER, BOTH, SEL, DX32, ACC, XSEL, PAIRS>(a);
 }
 template <int NB, int WPL, bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_bwd_bf16_big_kernel(BwdArgs a) {
@@ -293,7 +346,7 @@ rgnn_status_t launch(K kern, const TypedLinearBwdBf16Args& a, int nb, int wpl, h
     const TileList& t = *a.tiles;
     BwdArgs b{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot, static_cast<const bf16_t*>(a.X), a.gather,
               static_cast<const bf16_t*>(a.dY), a.dy_stride * 128, a.ysel, static_cast<const bf16_t*>(a.dY_alt), a.yscale, static_cast<const bf16_t*>(a.A2),
-              {a.W, a.W2}, a.dXrow, a.part};
+              a.sum_ptr, a.sum_row, static_cast<const bf16_t*>(a.sum_rows), {a.W, a.W2}, a.dXrow, a.part};
     KernelTimer kt(st, a.label);
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st, b);
     RGNN_HIP(hipGetLastError());
@@ -313,6 +366,8 @@ rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipS
         if (sel && (both || a.dx_f32 || a.dy_stride != 1 || a.W2 || !a.w_bf16))
             RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: the row selector is built for one bf16 weight, ungathered dY and bf16 result rows");
         if (a.accumulate && !(both && a.dx_f32)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: accumulation is built for fp32 rows gathered on both sides");
+        if (a.sum_rows && (!both || !a.dx_f32 || a.W2 || !a.w_bf16 || !a.sum_ptr || !a.sum_row))
+            RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: rows are added for one bf16 weight, fp32 rows gathered on both sides");
         if (a.W2) {
             if (both || a.dx_f32 || !a.w_bf16 || a.dy_stride != 2) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: two weights are built in bf16, for gradient rows side by side and bf16 result rows");
             RGNN_TRY(launch(typed_linear_bwd_bf16_big_kernel<2, 1, true, false, false, false, false>, a, 2, 1, st));
@@ -323,6 +378,9 @@ rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipS
             RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, false, true, false, false, true>, a, 1, 1, st));
         } else if (sel) {
             RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, false, true, false, false>, a, 1, 1, st));
+        } else if (a.sum_rows) {
+            if (a.accumulate) RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, true, false, true>, a, 1, 1, st));
+            else RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, false, false, true>, a, 1, 1, st));
         } else if (both && a.dx_f32 && a.accumulate) {
             RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, true>, a, 1, 1, st));
         } else if (both && a.dx_f32) {
