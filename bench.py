@@ -54,6 +54,53 @@ def counter_traffic(label, sha):
     return rows[label], f"{rel} (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command at lib_sha16 {sha}; not measured by this run)"
 
 
+def run_row_work(name, E, N, P, Q, Q1, R, d, bf16=False, layer="rgat", n_dst=None):
+    """algorithmic_work for the kernels of the plan that keeps rows per (destination, relation) run (RGCN, RGAT with one head); Q1 of
+    the Q runs have one edge and read their source's row where it is.  In bfloat16 at width 128 the sum of a run is kept as two
+    bf16 planes, of which the backward reads one."""
+    M, Em = Q - Q1, E - Q1            # runs with several edges, and their edges
+    half = bf16 and d == 128
+    r32 = d * 4
+    row = d * 2 if half else r32
+    mm = "hbm" if d == 128 else "mfma"
+    w2, wb = d * d * 4, d * d * (2 if half else 4)
+    rgat = layer == "rgat"
+    table = {
+        # per edge: source's row, source, relation and run (RGCN: coefficient); per run: the sum, s_dst and (max, sum)
+        "run_inputs": ("hbm", Em * (row + (12 if rgat else 8)) + M * ((row + 12) if rgat else (2 * row if half else row) + 8), 4.0 * Em * d),
+        # input row(s), result row, gather index and place of the result
+        "typed_linear_fwd": ("hbm" if half else "mfma", Q1 * row + M * (2 * row if half else row) + Q * (row + 8) + R * wb, 2.0 * Q * d * d),
+        # per run: its row; RGAT: tag, relation, s_dst, (max, sum) read or written; per node the result row and its item; RGAT: (max, sum)
+        "aggregate_fwd": ("hbm", Q * (row + (20 if rgat else 0)) + N * (r32 + (16 if rgat else 8)), 4.0 * Q * d),
+        # input row, gradient row, result row, both indices; RGAT: number, weight and product of the run
+        "typed_linear_bwd": (mm, Q * (3 * row + (20 if rgat else 8)) + R * (wb + w2), 4.0 * Q * d * d),
+        "typed_linear_loop_bwd": ("mfma", Q * (3 * row + 8) + R * 2 * w2 + N * 3 * r32 + 2 * w2, 4.0 * (Q + N) * d * d),
+        "run_weights": ("hbm", Q * 16 + N * 8, 4.0 * Q),
+        "run_stat": ("hbm", Q * 40 + Q1 * 4 + N * 12, 8.0 * Q),
+        # per edge: the run's gradient row, its 16 bytes, three indices, dz; per node its row in and out
+        "source_walk": ("hbm", E * (row + 32) + N * (2 * row + 16), 8.0 * E * d),
+        # the nodes' rows, once for the pairs and once for the runs (structural: a block of nodes is read once for all relations);
+        # per pair node and list ends, per edge dz, per run destination, index and ds_dst
+        "block_sums": ("hbm", 2 * N * row + P * 12 + E * 4 + Q * 12, 2.0 * (P + Q) * d),
+        "run_term": ("hbm", N * 2 * row + Q * 8, 2.0 * Q * d),
+        "run_logit": ("hbm", Q * 12 + (N if n_dst is None else n_dst) * row, 2.0 * Q * d),
+        # RGCN: per edge the run's gradient row, its index and coefficient
+        "node_grad_sum": ("hbm", E * (row + 8) + N * (r32 + 16), 2.0 * E * d),
+    }
+    return table.get(name)
+
+
+def run_row_steps(kern_ms, E, N, P, Q, Q1, d):
+    """step_rooflines for the rows per run: the traversals of the forward, of the backward by source, and the sums of its parameter
+    gradients and destination halves."""
+    work = lambda *names: sum(run_row_work(n, E, N, P, Q, Q1, 0, d)[1] for n in names)
+    return _steps(kern_ms, {
+        "S3_traversal_fwd": (work("run_inputs", "aggregate_fwd"), ("run_inputs", "run_inputs.combine", "aggregate_fwd", "aggregate_fwd.combine")),
+        "S4_traversal_bwd_src": (work("source_walk", "run_stat") + E * 8 + Q * 8, ("run_stat", "source_walk", "source_walk.combine", "ds_dst_sum")),
+        "S5_sums_bwd": (work("block_sums", "run_term"), ("block_sums", "run_term")),
+    })
+
+
 def step_rooflines(kern_ms, E, N, P, P1, Q, d):
     """Single-head RGAT: the traversal steps as wholes against the HBM peak: all kernels that implement a step, over
     the bytes the step itself needs per edge / node / pair (listed with each step below), whatever else the kernels move."""
@@ -71,6 +118,10 @@ def step_rooflines(kern_ms, E, N, P, P1, Q, d):
         "S5_traversal_bwd_pair": ((E - P1) * (row + 16) + (P - P1) * (row + 4) + Q * (row + 12),
                                   ("pair_run_walks", "aggregate_bwd_pair.combine", "ds_src_sum")),
     }
+    return _steps(kern_ms, steps)
+
+
+def _steps(kern_ms, steps):
     out = {}
     for k, (nbytes, names) in steps.items():
         ms = sum(kern_ms.get(n, 0.0) for n in names)
@@ -461,7 +512,20 @@ def main():
         print(f"[bench] max relative error vs oracle: {parity}", file=sys.stderr, flush=True)
 
     half = c["dtype"] == "bf16" and d == 128
-    work = lambda name: algorithmic_work(name, E, N, P, Q, R, T, d, H, P1, c["dtype"] == "bf16", c["layer"], sched, n_dst)
+    # rows per run instead of per pair: the library's pick on large graphs with fewer runs
+    runs = "run_inputs" in rep
+    Q1 = int((np.unique(c["dst"].astype(np.int64) * R + c["rel"], return_counts=True)[1] == 1).sum()) if runs else 0
+
+    def work(name):
+        if runs and not name.endswith((".reduce", ".combine", ".finish")):
+            w = run_row_work(name, E, N, P, Q, Q1, R, d, c["dtype"] == "bf16", c["layer"], n_dst)
+            if w:
+                return w
+        w = algorithmic_work(name, E, N, P, Q, R, T, d, H, P1, c["dtype"] == "bf16", c["layer"], sched, n_dst)
+        if name == "node_linear_q_bwd" and "node_grad_sum" not in rep and sched.get("hgt_folded") and half:
+            w = (w[0], w[1] + P * (d * 2 + 4) + N * 8, w[2] + 1.0 * P * d)      # with the sum over the node's pairs
+        return w
+
     kernels = []
     for name, (n, ms) in rep.items():
         avg_ms = ms / n
@@ -504,7 +568,9 @@ def main():
     roof["launches_timed"] = dom_n
     roof["algorithmic_bytes"] = w[1] if w else None
     kern_ms = {k["name"]: k["ms_per_step"] for k in kernels}
-    steps_roof = step_rooflines(kern_ms, E, N, P, P1, Q, d) if c["layer"] == "rgat" and H == 1 and not fwd_only else None
+    steps_roof = None
+    if c["layer"] == "rgat" and H == 1 and not fwd_only:
+        steps_roof = run_row_steps(kern_ms, E, N, P, Q, Q1, d) if runs else step_rooflines(kern_ms, E, N, P, P1, Q, d)
     if steps_roof:
         for k, v in steps_roof.items():
             print(f"[bench] {k:24s} {v['ms']:.3f} ms  {v['achieved']:.0f} GB/s = {v['frac']:.2f} of HBM peak", file=sys.stderr, flush=True)
@@ -524,6 +590,7 @@ def main():
         "roofline": roof,
         "roofline_steps": steps_roof,
         "schedule": sched,
+        "rows_per_run": runs,
         "lib_sha16": sha,
         "cpu_baseline": cpu,
         # the separate pass with events around every kernel, which the `kernels` table and `roofline_steps` come from
