@@ -1220,10 +1220,10 @@ __global__ __launch_bounds__(256) void node_grad_sum_kernel(NodeSumArgs a, RgatF
 // Rows per run: dX[v] += sum over v's runs of ds_dst[q] wtp[run_rel[q]].  A group of D / 4 lanes per destination, relations and coefficients of
 // D / 4 runs at a time, a lane each; wtp in LDS where it fits (persistent workgroups).  The first `fin.blocks` workgroups finish the
 // layer's parameter gradients.  Bound by the rows of dX, read and written: 900k destinations of width 64, 4.4M runs 252 us with a load of the
-// folded vector per run, so 123.
+// folded vector per run, 123 with it in LDS, 117 by length.
 constexpr int kRunTermThreads = 512;
 template <int D, bool LDSW>
-__global__ __launch_bounds__(kRunTermThreads) void run_term_kernel(int N, int R, const int32_t* __restrict__ dst_run_ptr, const int32_t* __restrict__ run_rel,
+__global__ __launch_bounds__(kRunTermThreads) void run_term_kernel(Items it, int R, const int32_t* __restrict__ dst_run_ptr, const int32_t* __restrict__ run_rel,
                                                                    const float* __restrict__ ds_dst, const float* __restrict__ wtp, float* __restrict__ dX,
                                                                    RgatFinish fin) {
     constexpr int LPR = D / 4, GPB = kRunTermThreads / LPR;
@@ -1239,24 +1239,24 @@ __global__ __launch_bounds__(kRunTermThreads) void run_term_kernel(int N, int R,
         __syncthreads();
         w = smem;
     }
-    // the next destination's first runs and its row are asked for before this one's sums, and the ends of the runs of the one after it
-    const int c = threadIdx.x % LPR;
-    const int64_t step = (int64_t)(gridDim.x - fin.blocks) * GPB, last = N - 1;
-    int64_t v = (int64_t)(blockIdx.x - fin.blocks) * GPB + threadIdx.x / LPR;
-    if (v >= N) return;
-    int b = dst_run_ptr[v], e = dst_run_ptr[v + 1];
-    int64_t vn = min(v + step, last);
-    int bn = dst_run_ptr[vn], en = dst_run_ptr[vn + 1];
+    // The next item's first runs and its row are asked for before this one's sums, and the ends of the one after it.  The items lie by
+    // length, so that those of a wavefront end together; the first piece of a cut destination takes the whole of it.
+    const int c = threadIdx.x % LPR, step = (gridDim.x - fin.blocks) * GPB, last = it.n - 1;
+    int i = (blockIdx.x - fin.blocks) * GPB + threadIdx.x / LPR;
+    if (i >= it.n) return;
+    int b = it.beg[i], e = it.end[i], v = it.row[i], cut = it.slot[i];
+    int k1 = min(i + step, last), bn = it.beg[k1], en = it.end[k1], vn = it.row[k1], cutn = it.slot[k1];
     int j = max(min(b + c, e - 1), 0), rel = run_rel[j];
     float ds = ds_dst[j];
-    float4 x = *reinterpret_cast<const float4*>(dX + v * D + c * 4);
-    for (; v < N; v += step) {
+    float4 x = *reinterpret_cast<const float4*>(dX + (size_t)v * D + c * 4);
+    for (; i < it.n; i += step) {
         j = max(min(bn + c, en - 1), 0);
         const int reln = run_rel[j];
         const float dsn = ds_dst[j];
-        const float4 xn = *reinterpret_cast<const float4*>(dX + vn * D + c * 4);
-        const int64_t vnn = min(vn + step, last);
-        const int bnn = dst_run_ptr[vnn], enn = dst_run_ptr[vnn + 1];
+        const float4 xn = *reinterpret_cast<const float4*>(dX + (size_t)vn * D + c * 4);
+        k1 = min(i + 2 * step, last);
+        const int bnn = it.beg[k1], enn = it.end[k1], vnn = it.row[k1], cutnn = it.slot[k1];
+        if (cut >= 0) e = b == dst_run_ptr[v] ? dst_run_ptr[v + 1] : b;
         float4 acc1 = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int jc = b; jc < e; jc += LPR) {
             if (jc > b) {
@@ -1275,8 +1275,8 @@ __global__ __launch_bounds__(kRunTermThreads) void run_term_kernel(int N, int R,
             }
         }
         fma4(x, 1.f, acc1);
-        if (b < e) *reinterpret_cast<float4*>(dX + v * D + c * 4) = x;
-        b = bn; e = en; bn = bnn; en = enn; rel = reln; ds = dsn; x = xn; vn = vnn;
+        if (b < e) *reinterpret_cast<float4*>(dX + (size_t)v * D + c * 4) = x;
+        b = bn; e = en; v = vn; cut = cutn; bn = bnn; en = enn; vn = vnn; cutn = cutnn; rel = reln; ds = dsn; x = xn;
     }
 }
 
@@ -1632,8 +1632,9 @@ static rgnn_status_t launch_run_term(const rgnn_graph* g, const float* ds_dst, c
     RGNN_TRY(allow_dynamic_lds(fn, lds));
     int per_cu = 1;
     RGNN_TRY(resident_blocks_per_cu(fn, kRunTermThreads, lds, &per_cu));
-    const size_t blocks = std::min<size_t>(((size_t)g->N + groups - 1) / groups, (size_t)per_cu * g->num_cus);
-    hipLaunchKernelGGL((run_term_kernel<D, LDSW>), dim3((unsigned)blocks + fin.blocks), dim3(kRunTermThreads), lds, st, (int)g->N, g->R,
+    const ItemList& L = g->dstrun_items;
+    const size_t blocks = std::min<size_t>(((size_t)L.num_items + groups - 1) / groups, (size_t)per_cu * g->num_cus);
+    hipLaunchKernelGGL((run_term_kernel<D, LDSW>), dim3((unsigned)blocks + fin.blocks), dim3(kRunTermThreads), lds, st, dev_items(L), g->R,
                        g->idx[RGNN_IDX_DST_RUN_PTR], g->idx[RGNN_IDX_RUN_REL], ds_dst, wtp, dX, fin);
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
