@@ -846,11 +846,7 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     RGNN_TRY(typed_linear_fwd(K, D, a, st));
     // 2. destination half, once per (dst, rel) run, reordered: s_dst[q] = X[dst] . (W[r] w_t[r])  (per head: the head's columns)
     if (!with_fold) RGNN_TRY(fold_weight(fold, st));
-    if (H > 1) {
-        RGNN_TRY(run_logit_heads(g, K, H, Xf, w.wtp, sv.s_dst, st));
-    } else {
-        RGNN_TRY(run_logit(g, K, Xf, w.wtp, sv.s_dst, st));
-    }
+    RGNN_TRY(run_logit(g, K, H, Xf, w.wtp, sv.s_dst, st));
     if (!fused) {
         // 3'. edge softmax in a pass of its own (one attention weight per edge, and (max, sum) per destination for the
         //     backward call), then the weighted sum: by the destination-segment walk, or edge by edge with atomic adds

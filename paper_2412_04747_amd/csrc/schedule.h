@@ -93,6 +93,12 @@ inline bool sched_hgt_pairs_with_query(int64_t nodes, int64_t pairs, int most) {
 inline bool sched_fused_softmax(uint32_t flags) {
     return !flag_set(flags, RGNN_FLAG_SEPARATE_SOFTMAX) && !flag_set(flags, RGNN_FLAG_EDGE_PARALLEL_AGGREGATION);
 }
+// RGAT, rows per pair: the destination halves of the logits with the folded vectors of all relations and heads in LDS, one workgroup of 1024
+// threads per compute unit or more, where the runs are many for what each of them then loads.  From memory / from LDS, us, width 64, four
+// heads: 100 relations 7.3 / 8.0 at 59k runs, 14.0 / 12.0 at 207k, 55 / 33 at 1.1M; 30 relations 7.2 / 6.3 at 51k; width 128 45 / 29 at 429k.
+inline bool sched_halves_in_lds(int R, int heads, int d, int64_t runs) {
+    return (size_t)R * heads * d * sizeof(float) <= 150 * 1024 && runs >= 1024 * (int64_t)R;
+}
 inline bool sched_ws_in_lds(int R, int d) { return (size_t)R * d * sizeof(float) <= kWsLdsMax; }
 
 // RGCN forward of a small graph in one launch (rgcn_small.hip), which reads a weight per (relation, destination) run, and one per

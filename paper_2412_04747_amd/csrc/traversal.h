@@ -20,7 +20,6 @@ rgnn_status_t fold_weight(const FoldArgs& f, hipStream_t st);
 // Folds go into another kernel's launch while their workgroups leave most of the 2^32 lanes of a grid to that kernel, whose workgroups
 // may have 512 threads (it saves a launch of some microseconds; with as many folds as this one the launch takes milliseconds).
 inline bool fold_rides(const FoldArgs& f) { return f.blocks <= 1 << 22; }
-rgnn_status_t run_logit(const rgnn_graph* g, int D, const float* X, const float* wtp, float* s_dst, hipStream_t st);
 rgnn_status_t segment_scalar_sum(int n, const int32_t* ptr, const LongList& lng, const int32_t* via, const float* val,
                                  int stride, int off, float* out, hipStream_t st, const char* label, int min_len = 0,
                                  int heads = 1, bool long_only = false, int ostride = 0,     // ostride 0: heads
@@ -133,9 +132,8 @@ rgnn_status_t hgt_attend_bwd(const rgnn_graph* g, int D, int H, const void* KM, 
 //   backward, pair-major: dKM[p] = (sum dl Q[dst], sum att dZ[dst]); partial rows are 2 D wide
 rgnn_status_t hgt_pair_bwd(const rgnn_graph* g, int D, int H, const void* Q, const void* dZ, const float* adl, void* dKM,
                            float* partial, hipStream_t st, int rows_bf16);
-// rgat_heads.hip: pieces of multi-head RGAT
-rgnn_status_t run_logit_heads(const rgnn_graph* g, int D, int H, const float* X, const float* wtp, float* s_dst,
-                              hipStream_t st);
+// rgat_heads.hip: s_dst[q][h] = X[dst_q] . wtp[r][h]
+rgnn_status_t run_logit(const rgnn_graph* g, int D, int H, const float* X, const float* wtp, float* s_dst, hipStream_t st);
 // out[v] = sum_e |att_e| Hs[pair_e] edge by edge with atomic adds (zeroes out first); fp32 rows
 rgnn_status_t aggregate_edge_parallel(const rgnn_graph* g, int D, const float* att, const float* Hs, float* out,
                                       hipStream_t st);

@@ -29,27 +29,6 @@ ScheduleFlagsScope::~ScheduleFlagsScope() { g_schedule_flags = prev; }
 
 __global__ __launch_bounds__(256) void fold_weight_kernel(FoldArgs f) { fold_weight_block(f, blockIdx.x); }
 
-// s_dst[q] = X[run_dst[q]] . wtp[run_rel[q]]; each lane group takes four consecutive runs so
-// that four row reads are in flight per lane.
-template <int D>
-__global__ void run_logit_kernel(int Q, const int32_t* __restrict__ run_dst, const int32_t* __restrict__ run_rel,
-                                 const float* __restrict__ X, const float* __restrict__ wtp, float* __restrict__ s_dst) {
-    constexpr int LPR = D / 4;
-    const int q0 = (blockIdx.x * (256 / LPR) + threadIdx.x / LPR) * 4, c4 = threadIdx.x % LPR;
-    float4 x[4], w[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int q = min(q0 + u, Q - 1);
-        x[u] = *reinterpret_cast<const float4*>(X + (size_t)run_dst[q] * D + c4 * 4);
-        w[u] = *reinterpret_cast<const float4*>(wtp + (size_t)run_rel[q] * D + c4 * 4);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const float s = group_sum<LPR>(dot4(x[u], w[u]));
-        if (q0 + u < Q && c4 == 0) s_dst[q0 + u] = s;
-    }
-}
-
 // out[i * ostride + h] = sum_{j in [ptr[i], ptr[i+1])} val[(via ? via[j] : j) * stride + off + h],  h < heads.
 // One launch: the first n_long * heads workgroups take one (long segment, head) each (segments of more
 // than kSerialMax entries, listed by the graph index; the hub runs are thousands of entries long), the
@@ -1331,15 +1310,6 @@ rgnn_status_t fold_weight(const FoldArgs& f, hipStream_t st) {
     if (f.H > 1 && f.w2) RGNN_FAIL(RGNN_EUNSUPPORTED, "fold_weight: two vectors per relation are built for one head");
     KernelTimer kt(st, "fold_weight");
     hipLaunchKernelGGL(fold_weight_kernel, dim3(f.blocks), dim3(256), 0, st, f);
-    RGNN_CHECK_LAUNCH();
-    return RGNN_OK;
-}
-
-rgnn_status_t run_logit(const rgnn_graph* g, int D, const float* X, const float* wtp, float* s_dst, hipStream_t st) {
-    if (g->Q == 0) return RGNN_OK;
-    KernelTimer kt(st, "run_logit");
-    RGNN_DISPATCH_D(D, hipLaunchKernelGGL(run_logit_kernel<DD>, dim3(blocks_for((size_t)((g->Q + 3) / 4) * (DD / 4), 256)), dim3(256), 0,
-                                     st, (int)g->Q, g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_RUN_REL], X, wtp, s_dst));
     RGNN_CHECK_LAUNCH();
     return RGNN_OK;
 }
