@@ -44,17 +44,18 @@ __device__ __forceinline__ float group_sum(float v) {
     if (W >= 64) v += __shfl_xor(v, 32);
     return v;
 }
-// Four sums over a group of W >= 8 lanes at once, each with the roundings of group_sum: lane c ends with sum entry_of(c) % 4, as the
+// Four sums over a group of W >= 4 lanes at once, each with the roundings of group_sum: lane c ends with sum entry_of(c) % 4 (W = 4: c % 4), as the
 // other quads' lanes of that sum do.  Eleven instructions for twenty.  entry_of(c): in every second quad the sums lie in reverse, where
 // the mirrors put them; with a list's entry k + entry_of(c) kept by lane c, the lane that has an entry's data also gets its sum.
 __host__ __device__ constexpr int entry_of(int c) { return (c & 4) ? c ^ 3 : c; }
 template <int W>
 __device__ __forceinline__ float group_sum4(const float (&p)[4], int c) {
-    const bool b0 = entry_of(c) & 1, b1 = entry_of(c) & 2;
+    const int t = W >= 8 ? entry_of(c) : c;
+    const bool b0 = t & 1, b1 = t & 2;
     const float u0 = (b0 ? p[1] : p[0]) + dpp_move<kDppQuadSwap1>(b0 ? p[0] : p[1]);
     const float u1 = (b0 ? p[3] : p[2]) + dpp_move<kDppQuadSwap1>(b0 ? p[2] : p[3]);
     float v = (b1 ? u1 : u0) + dpp_move<kDppQuadSwap2>(b1 ? u0 : u1);
-    v += dpp_move<kDppHalfMirror>(v);
+    if (W >= 8) v += dpp_move<kDppHalfMirror>(v);
     if (W >= 16) v += dpp_move<kDppMirror>(v);
     if (W >= 32) v += __shfl_xor(v, 16);
     return v;

@@ -352,6 +352,7 @@ __device__ __forceinline__ void bwd_item(const FusedArgs& a, const float* ws_lds
     const float4 ov = *reinterpret_cast<const float4*>(a.fout + v * D + c * 4);
     const float2 st = a.ms[v * H + head];
     const int own = H == 1 ? entry_of(c) : c;                // lane c's edge of a chunk
+    const int t = (LPH >= 8 ? entry_of(c) : c) & 3;          // several heads: the edge of four whose sums lane c gets
     int jj = min(b + own, e - 1);
     int cpr = a.in_pair[jj], crl = a.in_rel[jj], crn = a.in_run[jj];
     float csd = H == 1 ? a.s_dst[crn] : 0.f;
@@ -371,14 +372,14 @@ __device__ __forceinline__ void bwd_item(const FusedArgs& a, const float* ws_lds
         for (int k = 0; k < LPR; k += 4) {
             if (k >= cend) break;
             float4 h[4];
-            float sd[4];
             int pr[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 pr[u] = group_lane<LPR>(cpr, H == 1 ? entry_of(k + u) : k + u);
                 h[u] = load_row_nt(a.Hs + (size_t)(pr[u] & 0x7FFFFFFF) * D + c * 4);
-                if (H > 1) sd[u] = a.s_dst[(size_t)group_lane<LPR>(crn, k + u) * H + head];
             }
+            const int prt = H > 1 ? __shfl(cpr, k + t, LPR) : 0;
+            const float sdt = H > 1 ? a.s_dst[(size_t)__shfl(crn, k + t, LPR) * H + head] : 0.f;
             __builtin_amdgcn_sched_barrier(0);      // the w_s rows are read when the message rows arrive, not held meanwhile
             if constexpr (H == 1) {
                 // the four edges' sums at once, and what follows from an edge's in the lane that keeps the edge (quad k / 4)
@@ -407,30 +408,25 @@ __device__ __forceinline__ void bwd_item(const FusedArgs& a, const float* ws_lds
                 }
                 continue;
             }
-            float2 mine = make_float2(0.f, 0.f);      // (att, dz) of edge jc + k + (c % LPH): lanes 0..3 of a head store one each
+            // Several heads: a lane gets the sums of one edge and its head, and forms what follows (with eight lanes or more per head, two
+            // lanes or more do the same, and the first four store).
+            float pz[4], pg[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float4 w = ws_row<D, LDSW>(a, ws_lds, group_lane<LPR>(crl, k + u), c);
-                const float z = group_sum<LPH>(dot4(h[u], w)) + sd[u];
-                const float g = group_sum<LPH>(dot4(go, h[u]));
-                const float al = __expf(leaky(z, a.slope) - m) * inv;
-                const float dz = al * (g - gbar) * (z > 0.f ? 1.f : a.slope);
-                if (c % LPH == u) mine = make_float2(al, dz);
-                if (a.own_singles && k + u < cend && pr[u] < 0 && c % LPH == 0) {
-                    float* hc = reinterpret_cast<float*>(a.dsy) + (size_t)(pr[u] & 0x7FFFFFFF) * 2 * H;
+                pz[u] = dot4(h[u], ws_row<D, LDSW>(a, ws_lds, group_lane<LPR>(crl, k + u), c));
+                pg[u] = dot4(go, h[u]);
+            }
+            const float z = group_sum4<LPH>(pz, c) + sdt, g = group_sum4<LPH>(pg, c);
+            const float al = __expf(leaky(z, a.slope) - m) * inv;
+            const float dz = al * (g - gbar) * (z > 0.f ? 1.f : a.slope);
+            if (c % LPH < 4 && k + t < cend) {
+                float* o = a.adz + (size_t)(jc + k + t) * 2 * H + head;
+                o[0] = al;
+                o[H] = dz;
+                if (a.own_singles && prt < 0) {
+                    float* hc = reinterpret_cast<float*>(a.dsy) + (size_t)(prt & 0x7FFFFFFF) * 2 * H;
                     hc[head] = dz;
                     hc[H + head] = al;
-                }
-            }
-            {
-                // lane (head h, t) holds edge k + t of head h; the values change lanes so that lane t * H + h stores them:
-                // the H lanes of an edge then write neighbouring floats
-                const int t = c / H, h = c % H;
-                const float al = __shfl(mine.x, h * LPH + t, LPR), dz = __shfl(mine.y, h * LPH + t, LPR);
-                if (c < 4 * H && k + t < cend) {
-                    float* o = a.adz + (size_t)(jc + k + t) * 2 * H + h;
-                    o[0] = al;
-                    o[H] = dz;
                 }
             }
         }
