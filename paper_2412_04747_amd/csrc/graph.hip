@@ -103,14 +103,15 @@ struct Uploader {
 
 // Tile lists over one segmentation: the tiles are planned and uploaded once, every list gets its own chunks.
 struct Chunking { TileList* list; int max_chunks; };
-static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int tile_rows, std::initializer_list<Chunking> lists) {
+static void build_tiles(Uploader& U, const std::vector<int32_t>& seg_ptr, int tile_rows, std::initializer_list<Chunking> lists,
+                        const std::vector<int32_t>* weight = nullptr) {
     TilePlan p = plan_tiles(seg_ptr, tile_rows);
     std::vector<TilePlan> chunked(lists.size());
     int32_t *seg = nullptr, *row0 = nullptr, *row1 = nullptr;
     std::vector<Uploader::Array> all{{&p.tile_seg, &seg}, {&p.tile_row0, &row0}, {&p.tile_row1, &row1}};
     size_t i = 0;
     for (const Chunking& c : lists) {
-        chunk_tiles(p, c.max_chunks);
+        chunk_tiles(p, c.max_chunks, weight);
         TileList& t = *c.list;
         t.tile_rows = p.tile_rows; t.num_tiles = p.num_tiles; t.num_chunks = p.num_chunks; t.num_slots = p.num_slots;
         t.num_segs = p.num_segs; t.max_seg_slots = p.max_seg_slots; t.max_chunk_slots = p.max_chunk_slots;
@@ -246,6 +247,18 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
                                          {&g->pair_tiles_cu2, 2 * cus}, {&g->pair_tiles_cu1, cus}});
     build_tiles(U, ntype_ptr, kTileRows, {{&g->node_tiles_hgt, std::max(cus - 2 * hgt_pairs, 1)}, {&g->node_tiles, kMaxChunks}, {&g->node_tiles_wide, kWideChunksPerCU * cus},
                                           {&g->node_tiles_cu2, 2 * cus}, {&g->node_tiles_cu1, cus}});
+    if (g->rel_src_tied && sched_hgt_pairs_with_query(g->N, g->P, g->max_node_pairs)) {
+        std::vector<int32_t> perm, weight;
+        RGNN_TRY(download(perm, g->idx[RGNN_IDX_NTYPE_PERM], (size_t)g->N));
+        for (int t = 0; t < g->T; ++t)
+            for (int32_t a = ntype_ptr[t]; a < ntype_ptr[t + 1]; a += kTileRows) {
+                const int32_t e = std::min<int32_t>(a + kTileRows, ntype_ptr[t + 1]);
+                int32_t pairs = 0;
+                for (int32_t i = a; i < e; ++i) pairs += srcpair_ptr[perm[i] + 1] - srcpair_ptr[perm[i]];
+                weight.push_back(kSumRowWeight * (e - a) + kSumPairWeight * pairs);
+            }
+        build_tiles(U, ntype_ptr, kTileRows, {{&g->node_tiles_sum, 2 * cus}}, &weight);
+    }
     build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles, kMaxChunks}, {&g->all_tiles_cu1, cus}, {&g->all_tiles_loop, std::max(cus - loop_pairs, 1)}});
     build_long(U, g->long_runs, run_ptr);
     build_long(U, g->long_pairs, out_ptr);

@@ -395,8 +395,9 @@ size_t carve_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* ba
     // shares of the weight gradients, which one launch adds: output, query (and unfolded value) linears; both pair linears
     const bool jobs = hgt_bwd_jobs(g, d);
     const size_t nodes = std::max(tl_bwd_scratch(h, node_chunks(g, d->d_out), d->d_in, d->d_out), jobs ? typed_linear_bwd_scratch_floats(D, D, g->node_tiles_hgt) : 0);
+    const size_t query = std::max(nodes, hgt_pairs_with_query(g, d) ? (size_t)D * D * g->node_tiles_sum.num_slots : 0);
     const size_t pairs = std::max(tl_bwd_scratch(h, pair_chunks(g, d->d_out), d->d_in, d->d_out), jobs ? typed_linear_bwd_scratch_floats(D, D, g->pair_tiles_hgt) : 0);
-    w->node_part[0] = c.take<float>(nodes); w->node_part[1] = c.take<float>(nodes); w->node_part[2] = c.take<float>(fold ? 0 : nodes);
+    w->node_part[0] = c.take<float>(nodes); w->node_part[1] = c.take<float>(query); w->node_part[2] = c.take<float>(fold ? 0 : nodes);
     w->pair_part[0] = c.take<float>(pairs); w->pair_part[1] = c.take<float>(h && fold ? 0 : pairs);
     w->partial = c.take<float>(std::max(2 * (size_t)g->pair_items.num_partials, (size_t)g->dst_items.num_partials) * D);
     const bool acc = grads_accumulate(d);
@@ -1173,7 +1174,7 @@ extern "C" rgnn_status_t rgnn_hgt_bwd(const rgnn_graph_t* g, const rgnn_layer_de
             if (hgt_pairs_with_query(g, desc)) {
                 // dX = dQ Wq^T + sums over each node's pairs, with dWq
                 TypedLinearBwdBf16Args q{};
-                q.tiles = node_chunks(g, D).cu2; q.X = X; q.gather = perm; q.both_gathered = 1; q.W = Wq16; q.w_bf16 = 1; q.dY = w.dQ;
+                q.tiles = &g->node_tiles_sum; q.X = X; q.gather = perm; q.both_gathered = 1; q.W = Wq16; q.w_bf16 = 1; q.dY = w.dQ;
                 q.dXrow = dX; q.dx_f32 = 1; q.accumulate = acc; q.dW = static_cast<float*>(dWq); q.part = w.node_part[1]; q.label = "node_linear_q_bwd";
                 q.sum_ptr = g->idx[RGNN_IDX_SRCPAIR_PTR]; q.sum_row = g->idx[RGNN_IDX_SRCPAIR_IDX]; q.sum_rows = w.dKp; q.sums = &sums;
                 RGNN_TRY(typed_linear_bwd_bf16(D, q, st));

@@ -137,6 +137,7 @@ struct rgnn_graph {
     rgnn::ItemList pair_items_multi;       // the same, pairs with two or more edges only
     rgnn::ItemList srcpair_items;          // pairs by source node (never cut)
     int32_t max_node_pairs = 0;            // most pairs of a source node
+    rgnn::TileList node_tiles_sum;         // node tiles by type, in chunks of like numbers of rows and pairs (HGT: the pairs' sum with the query's product)
     int32_t* in_pair_tag = nullptr;        // [E] in_pair with the top bit set when the pair has a single edge
     float* pair_scale = nullptr;           // [P] 1 / c_{v,r} of the only edge of a single-edge pair, 1 for the other pairs
     int32_t* pair_ysel = nullptr;          // [P] pair id, or for a pair with one edge the top bit | that edge's destination

@@ -83,7 +83,7 @@ inline bool sched_hgt_folded(bool rel_src_tied, uint32_t flags) {
 // HGT, rows in bf16: the sum over a node's pairs in the query's product (typed_linear_bwd_bf16.hip, PAIRS) where nodes have few, and none
 // has many (32 rows wait for the one with most).  The walk's gathers are wider; what is saved is a row of fp32 per node, written and read.
 // Layer, forward + backward, us, walk / in the product: at 1.2 pairs per node 380 / 367 (120k nodes), 1241 / 1169 (500k); 1.5 167 / 165 (30k); 2.7
-// 318 / 320 (60k), 515 / 515 (120k), 10375 / 10135 (2M); 4.5 414 / 416 (60k), 719 / 722 (120k); 5 3004 / 2955 (500k), 5967 / 5929 (1M); 6.3
+// 318 / 320 (60k), 515 / 515 (120k), 10375 / 10100 (2M); 4.5 414 / 416 (60k), 719 / 722 (120k); 5 3004 / 2955 (500k), 5967 / 5929 (1M); 6.3
 // 2398 / 2394 (300k); 15 4345 / 4416 (300k); 31 2558 / 2627 (60k).
 inline bool sched_hgt_pairs_with_query(int64_t nodes, int64_t pairs, int most) {
     return pairs > 0 && most <= 32 && (pairs <= 2 * nodes || (pairs <= 5 * nodes && nodes >= 150000));

@@ -63,8 +63,10 @@ __device__ __forceinline__ rgnn_v4u scale8(rgnn_v4u x, float s) {
 //   DX32   dXrow is fp32, ACC: and added to           otherwise bf16
 //   PAIRS  with BOTH and DX32: dXrow row n also gets the sum of the rows sum_row[sum_ptr[n] .. sum_ptr[n + 1]) of sum_rows (HGT: the query's
 //          part of dX and the sum over the node's pairs).  A lane adds its 16 columns of its row, two rows at a time, the list two tiles ahead.
-//          As a walk of its own that read the query's part again: 2M nodes, 5.4M pairs 408 + 670 us, so 862.  (Whole rows added by the threads
-//          that load a tile, and handed over through LDS, need 25 registers more than two workgroups per compute unit leave: 968.)
+//          As a walk of its own that read the query's part again: 2M nodes, 5.4M pairs 408 + 670 us, so 829 in
+//          chunks that weigh alike (chunk_tiles), 862 in chunks of as many tiles; where node types differ in their pairs, 2M nodes, 4.5M pairs,
+//          406 + 617, 783 and 1079.  (Whole rows added by the threads
+//          that load a tile, and handed over through LDS, need 25 registers more than two workgroups per compute unit leave: 968 for the 862.)
 //   XSEL   rows per run (typed_linear_fwd_bf16.hip): X rows from X or A2, and row i of dY is dY[ysel[i]].  The first plane of A2 is enough
 //          here: a rounding of A[q] / c weighs what those of its c edges' dOut / c did in rows per pair (dW of 2M edges against 64 bits:
 //          6.9e-4 per pair, 4.9e-4 per run)

@@ -23,6 +23,9 @@ constexpr int kWideMin = 29;        // items with at least this many entries: a 
                                     // eight lane groups share it in batches of four entries, and each has to get some)
 constexpr int kSerialMax = 32;      // longest segment a single lane walks; longer ones get a wavefront
 
+// What a row and a pair of a node weigh in the chunks of the query's product with the pairs' sum: 405 us for 2M rows, 455 more for 5.4M pairs.
+constexpr int kSumRowWeight = 12, kSumPairWeight = 5;
+
 // Tiles of at most `tile_rows` rows that never straddle a segment, in row order, grouped into
 // chunks of consecutive tiles.  A chunk accumulates one weight gradient per segment it touches
 // and flushes each to a "slot"; slots are numbered in chunk order, so the slots of one segment
@@ -36,8 +39,9 @@ struct TilePlan {
     std::vector<int32_t> seg_slot_ptr;                     // [num_segs + 1]
 };
 
-// (Re)groups the tiles of a plan into chunks: fills the chunk and slot fields.
-inline void chunk_tiles(TilePlan& t, int max_chunks) {
+// (Re)groups the tiles of a plan into chunks: fills the chunk and slot fields.  weight: of the tiles, where they take unlike times; the chunks
+// then weigh alike, as far as whole tiles do, and every chunk has one.
+inline void chunk_tiles(TilePlan& t, int max_chunks, const std::vector<int32_t>* weight = nullptr) {
     const int nt = t.num_tiles, S = t.num_segs;
     // a chunk pays for one weight-tile load and one weight-gradient flush, so it should span several
     // tiles; but small inputs still need a few hundred chunks to occupy the compute units
@@ -48,9 +52,21 @@ inline void chunk_tiles(TilePlan& t, int max_chunks) {
     std::vector<int32_t> seg_slots(std::max(S, 0), 0);
     int slots = 0;
     t.max_chunk_slots = 0;
+    int64_t total = 0, done = 0;
+    if (weight)
+        for (int32_t w : *weight) total += w;
     for (int c = 0; c < nc; ++c) {
-        t.chunk_tile[c] = (int32_t)((int64_t)nt * c / nc);
-        t.chunk_tile[c + 1] = (int32_t)((int64_t)nt * (c + 1) / nc);
+        if (weight) {
+            int i = t.chunk_tile[c];
+            const int last = nt - (nc - c - 1);            // (leaves a tile for every chunk after this one)
+            do done += (*weight)[i++];
+            while (i < last && 2 * nc * done + (int64_t)nc * (*weight)[i] <= 2 * total * (c + 1));
+            while (c + 1 == nc && i < nt) ++i;
+            t.chunk_tile[c + 1] = i;
+        } else {
+            t.chunk_tile[c] = (int32_t)((int64_t)nt * c / nc);
+            t.chunk_tile[c + 1] = (int32_t)((int64_t)nt * (c + 1) / nc);
+        }
         t.chunk_slot[c] = slots;
         for (int i = t.chunk_tile[c]; i < t.chunk_tile[c + 1]; ++i)
             if (i == t.chunk_tile[c] || t.tile_seg[i] != t.tile_seg[i - 1]) {

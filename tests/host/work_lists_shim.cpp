@@ -34,6 +34,12 @@ int wl_plan_tiles(const int32_t* seg_ptr, int nseg, int tile_rows, int max_chunk
     g_tiles = rgnn::plan_tiles(std::vector<int32_t>(seg_ptr, seg_ptr + nseg + 1), tile_rows, max_chunks);
     return g_tiles.num_tiles;
 }
+int wl_weigh_chunks(const int32_t* seg_ptr, int nseg, int tile_rows, int max_chunks, const int32_t* weight) {
+    g_tiles = rgnn::plan_tiles(std::vector<int32_t>(seg_ptr, seg_ptr + nseg + 1), tile_rows);
+    const std::vector<int32_t> w(weight, weight + g_tiles.num_tiles);
+    rgnn::chunk_tiles(g_tiles, max_chunks, &w);
+    return g_tiles.num_chunks;
+}
 // which: 0 tile_seg, 1 tile_row0, 2 tile_row1, 3 chunk_tile, 4 chunk_slot, 5 seg_slot_ptr
 int wl_tiles_field(int which, int32_t* out, int cap) {
     const std::vector<int32_t>* f[] = {&g_tiles.tile_seg, &g_tiles.tile_row0, &g_tiles.tile_row1, &g_tiles.chunk_tile,

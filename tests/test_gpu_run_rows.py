@@ -5,6 +5,7 @@ import pytest
 from oracle import layers as O
 from paper_2412_04747_amd import synth
 from parity import check, TOL_F32, TOL_BF16
+from test_gpu_hipgraph import _capture_and_replay
 from test_gpu_workspace_bounds import _guarded, _intact
 
 pytestmark = pytest.mark.gpu
@@ -193,4 +194,24 @@ def test_rgat_forward_that_keeps_nothing(n, fits):
     check(outs[1], O.rgat_fwd(N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"]), TOL_F32, "out")
     assert names == [True, fits, fits] and torch.equal(outs[1], outs[2])
     _intact(guards[0], "the workspace")
+    g.close()
+
+
+@pytest.mark.parametrize("layer,dtype", [("rgat", "f32"), ("rgcn", "f32"), ("rgcn", "bf16")])
+def test_replays(layer, dtype):
+    """Forward + backward recorded into a HIP graph: every replay leaves the bits of the eager calls."""
+    from paper_2412_04747_amd.harness import Graph, RgatLayer, RgcnLayer
+    d = 128 if dtype == "bf16" else 64
+    N, R, src, dst, rel, rng = _graph(91, 290011)
+    print(f"run rows replays {layer} {dtype}", flush=True)
+    g = Graph(N, R, src, dst, rel)
+    if layer == "rgat":
+        p = synth.rgat_params(rng, N, R, d, d)
+        L = RgatLayer(g, d)
+        L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    else:
+        p = synth.rgcn_params(rng, N, R, d, d, self_loop=True)
+        L = RgcnLayer(g, d, "in_degree_per_rel", "relu", True, dtype=dtype)
+        L.load(p["X"], p["W"], p["W0"], p["dOut"])
+    _capture_and_replay(L, lambda: [L.out, *L.grads().values()])
     g.close()

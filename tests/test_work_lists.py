@@ -347,3 +347,20 @@ def test_rows_per_run_where_they_pay(wl, E, d, R, rows, want):
     assert "".join(str(pick_(layer)) for layer in range(3)) == want
     assert "".join(str(pick_(layer, flags=32)) for layer in range(3)) == want                # the accumulation of gradients
     assert not any(pick_(layer, flags=f) for layer in range(3) for f in (1, 2, 4, 8, 16)) and not pick_(1, heads=2)
+
+
+@pytest.mark.parametrize("S,rows,max_chunks", [(1, 64, 4), (3, 700, 512), (5, 40000, 512), (8, 300000, 512), (2, 20000, 1000)])
+def test_chunks_of_like_weight(wl, S, rows, max_chunks):
+    """Chunks cover the tiles in order, have a tile each and weigh no more than their share and a tile; the slots follow the chunks."""
+    rng = np.random.default_rng(S + rows)
+    seg_ptr = np.concatenate([[0], np.cumsum(rng.integers(0, 2 * rows // S + 1, S))]).astype(np.int32)
+    seg_ptr[-1] = max(seg_ptr[-1], seg_ptr[-2] + 1)
+    tiles = int(np.sum((np.diff(seg_ptr) + 63) // 64))
+    weight = np.ascontiguousarray(rng.choice([12, 700, 768, 800, 2000, 5000], tiles), np.int32)
+    n = wl.wl_weigh_chunks(seg_ptr.ctypes.data_as(C.c_void_p), S, 64, max_chunks, weight.ctypes.data_as(C.c_void_p))
+    seg, chunk_tile, chunk_slot, seg_slot_ptr = (_field(wl.wl_tiles_field, i) for i in (0, 3, 4, 5))
+    assert n == len(chunk_tile) - 1 and chunk_tile[0] == 0 and chunk_tile[-1] == tiles and np.all(np.diff(chunk_tile) >= 1)
+    sums = np.add.reduceat(weight.astype(np.int64), chunk_tile[:-1])
+    assert sums.max() <= weight.sum() / n + weight.max()
+    want = [len(set(seg[a:b])) for a, b in zip(chunk_tile[:-1], chunk_tile[1:])]
+    assert np.array_equal(np.concatenate([[0], np.cumsum(want)])[:-1], chunk_slot) and seg_slot_ptr[-1] == sum(want)
