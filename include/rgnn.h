@@ -298,8 +298,9 @@ rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc
  * The call allocates nothing.  X, W, w_s, w_t, out and `saved` are the caller's, as in rgnn_rgat_fwd; with
  * saved == NULL (inference) the tensors that would have been saved are placed in the static buffer as well.
  *   - The scratch a call needs is the forward size rgnn_workspace_bytes reports (plus, with saved == NULL, that
- *     size rounded up to 256 and the saved size); a call that needs more than RGNN_STATIC_SCRATCH_BYTES fails
- *     with RGNN_EWORKSPACE before anything is enqueued.
+ *     size rounded up to 256 and the saved size, or less where that is sized for rows per run and the call keeps
+ *     rows per pair); a call that needs more than RGNN_STATIC_SCRATCH_BYTES fails with RGNN_EWORKSPACE before
+ *     anything is enqueued.
  *   - Every call on a GPU uses that GPU's one buffer: calls that overlap in time on one GPU (two streams, two
  *     threads) race; serialise them.  The buffer keeps the previous call's contents; no kernel of the forward
  *     reads scratch it has not written in the same call, so nothing has to be cleared.

@@ -215,3 +215,27 @@ def test_replays(layer, dtype):
         L.load(p["X"], p["W"], p["W0"], p["dOut"])
     _capture_and_replay(L, lambda: [L.out, *L.grads().values()])
     g.close()
+
+
+@pytest.mark.parametrize("layer,d", [("rgat", 64), ("rgat", 128), ("rgcn", 64)])
+def test_autograd_without_gradients(layer, d):
+    """A forward of the autograd front end that no backward follows keeps nothing and gives the same result up to rounding."""
+    import torch
+    from paper_2412_04747_amd import autograd as A
+    N, R, src, dst, rel, rng = _graph(17, 290011)
+    print(f"run rows without gradients {layer} {d}", flush=True)
+    g = A.Graph(N, R, src, dst, rel)
+    torch.manual_seed(3)
+    conv = A.RgatConv(R, d) if layer == "rgat" else A.RgcnConv(R, d)
+    X = torch.randn(N, d, device="cuda", requires_grad=True)
+    out = conv(g, X)
+    with torch.no_grad():
+        again = conv(g, X)
+    assert out.requires_grad and not again.requires_grad
+    check(again, out.detach().cpu().numpy(), TOL_F32, "out")
+    out.sum().backward()                                     # (the forward that keeps nothing has left what this one needs alone)
+    first = X.grad.clone()
+    X.grad = None
+    conv(g, X).sum().backward()
+    assert torch.equal(X.grad, first)
+    g.close()
