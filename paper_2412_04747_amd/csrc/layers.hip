@@ -587,18 +587,24 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* W32 = !h ? stg.in(W, (size_t)g->R * desc->d_in * D) : nullptr;
     const float* W032 = stg.in(W0, (size_t)desc->d_in * D);
     RGNN_TRY(stg.status);
+    // What the backward reads is left in `saved` whichever plan the forward takes: the backward cannot tell.
+    const bool runs = rgcn_run_rows(g, desc) && (saved || sched_run_rows_infer(h, g->E, D));
+    const void* const Xr = h ? X : static_cast<const void*>(X32);
+    float* A = w.A;
+    if (runs && saved) {
+        (void)carve_rgcn_saved(g, desc, saved, &A);
+        RGNN_TRY(rgcn_run_inputs(g, desc, Xr, h, A, w.partial, st));
+    }
     // (one launch: rows of out are written while others of X are still read, so an out that shares memory with X goes to the
     // general plan, which has read X by then unless there is a self-loop)
     if (!overlap(X, (size_t)g->N * desc->d_in * sizeof(float), out, (size_t)g->N * D * sizeof(float)) &&
         sched_rgcn_small(desc->dtype, desc->d_in, D, W0 != nullptr, g->Q, g->N, g->dst_items.num_split > 0, g->longest_chain.runs,
                          g->longest_chain.edges, desc->flags))
         return rgcn_small_fwd(g, desc->d_in, D, X32, W32, W032, desc->norm == RGNN_NORM_IN_DEGREE_PER_REL, relu, static_cast<float*>(out), st);
-    if (rgcn_run_rows(g, desc) && (saved || sched_run_rows_infer(h, g->E, D))) {
+    if (runs) {
         // The sum over a run's edges comes before the product: a row of messages per run, not per pair, and a run with one edge reads its
         // source's row directly.
-        float* A = w.A;
-        if (saved) (void)carve_rgcn_saved(g, desc, saved, &A);
-        RGNN_TRY(rgcn_run_inputs(g, desc, h ? X : static_cast<const void*>(X32), h, A, w.partial, st));
+        if (!saved) RGNN_TRY(rgcn_run_inputs(g, desc, Xr, h, A, w.partial, st));
         if (h) {
             TypedLinearFwdBf16Args a{&g->run_tiles_cu2, X, g->row_in, 0, W, nullptr, w.Hs, "typed_linear_fwd"};
             a.A2 = A; a.planes_end = g->multi_end; a.to = g->row_run;

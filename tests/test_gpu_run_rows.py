@@ -92,6 +92,36 @@ def test_rgcn(k, d, dtype, norm, act, loop, flags, saved):
     g.close()
 
 
+@pytest.mark.parametrize("N,R,E,dsts,k,d,loop", [
+    (3000, 4, 200000, 2500, 64, 64, False), (2000, 8, 140000, 1000, 32, 64, True), (3000, 4, 260000, 1500, 32, 32, False),
+    (3000, 4, 260000, 1500, 64, 32, True), (6080, 8, 140000, 80, 64, 64, True)])
+def test_rgcn_of_few_destinations(N, R, E, dsts, k, d, loop):
+    """Rows per run whose forward is the one launch of a small graph: it leaves the sums that the backward reads as well."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    rng = np.random.default_rng(N + E + k)
+    print(f"run rows rgcn of few destinations N={N} R={R} E={E} {dsts} {k}->{d} loop={loop}", flush=True)
+    src, dst, rel = (rng.integers(0, n, E).astype(np.int32) for n in (N, dsts, R))
+    p = synth.rgcn_params(rng, N, R, k, d, self_loop=loop)
+    g = Graph(N, R, src, dst, rel)
+    L = RgcnLayer(g, d, self_loop=loop, d_in=k)
+    L.load(p["X"], p["W"], p["W0"], p["dOut"])
+    L.saved.fill_(0xFF)
+    B.rgnn_profile_start()
+    L.fwd()
+    L.bwd()
+    torch.cuda.synchronize()
+    rep = B.rgnn_profile_stop()
+    a = (N, src, dst, rel, p["X"], p["W"], p["W0"])
+    check(L.out, O.rgcn_fwd(*a), TOL_F32, "out")
+    want = O.rgcn_bwd(*a, p["dOut"])
+    for n, v in L.grads().items():
+        check(v, want[n], TOL_F32, n)
+    assert "rgcn_small_fwd" in rep and rep["run_inputs"][0] == 1 and "aggregate_bwd_pair" not in rep
+    g.close()
+
+
 def _area(guards, n):
     big, mid = _guarded(n)
     guards.append(big)
