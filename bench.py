@@ -54,27 +54,24 @@ def counter_traffic(label, sha):
     return rows[label], f"{rel} (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command at lib_sha16 {sha}; not measured by this run)"
 
 
-def run_row_work(name, E, N, P, Q, Q1, R, d, bf16=False, layer="rgat", n_dst=None):
-    """algorithmic_work for the kernels of the plan that keeps rows per (destination, relation) run (RGCN, RGAT with one head); Q1 of
-    the Q runs have one edge and read their source's row where it is.  In bfloat16 at width 128 the sum of a run is kept as two
-    bf16 planes, of which the backward reads one."""
+def run_row_work(name, E, N, P, Q, Q1, R, d, layer="rgat", n_dst=None):
+    """algorithmic_work for the kernels of the plan that keeps rows per (destination, relation) run (RGCN, RGAT with one head; fp32
+    rows); Q1 of the Q runs have one edge and read their source's row where it is."""
     M, Em = Q - Q1, E - Q1            # runs with several edges, and their edges
-    half = bf16 and d == 128
-    r32 = d * 4
-    row = d * 2 if half else r32
+    row = d * 4
     mm = "hbm" if d == 128 else "mfma"
-    w2, wb = d * d * 4, d * d * (2 if half else 4)
+    w2 = d * d * 4
     rgat = layer == "rgat"
     table = {
         # per edge: source's row, source, relation and run (RGCN: coefficient); per run: the sum, s_dst and (max, sum)
-        "run_inputs": ("hbm", Em * (row + (12 if rgat else 8)) + M * ((row + 12) if rgat else (2 * row if half else row) + 8), 4.0 * Em * d),
+        "run_inputs": ("hbm", Em * (row + (12 if rgat else 8)) + M * (row + (12 if rgat else 8)), 4.0 * Em * d),
         # input row(s), result row, gather index and place of the result
-        "typed_linear_fwd": ("hbm" if half else "mfma", Q1 * row + M * (2 * row if half else row) + Q * (row + 8) + R * wb, 2.0 * Q * d * d),
+        "typed_linear_fwd": ("mfma", Q * (2 * row + 8) + R * w2, 2.0 * Q * d * d),
         # per run: its row; RGAT: tag, relation, s_dst, (max, sum) read or written; per node the result row and its item; RGAT: (max, sum)
-        "aggregate_fwd": ("hbm", Q * (row + (20 if rgat else 0)) + N * (r32 + (16 if rgat else 8)), 4.0 * Q * d),
+        "aggregate_fwd": ("hbm", Q * (row + (20 if rgat else 0)) + N * (row + (16 if rgat else 8)), 4.0 * Q * d),
         # input row, gradient row, result row, both indices; RGAT: number, weight and product of the run
-        "typed_linear_bwd": (mm, Q * (3 * row + (20 if rgat else 8)) + R * (wb + w2), 4.0 * Q * d * d),
-        "typed_linear_loop_bwd": ("mfma", Q * (3 * row + 8) + R * 2 * w2 + N * 3 * r32 + 2 * w2, 4.0 * (Q + N) * d * d),
+        "typed_linear_bwd": (mm, Q * (3 * row + (20 if rgat else 8)) + R * 2 * w2, 4.0 * Q * d * d),
+        "typed_linear_loop_bwd": ("mfma", Q * (3 * row + 8) + R * 2 * w2 + N * 3 * row + 2 * w2, 4.0 * (Q + N) * d * d),
         "run_weights": ("hbm", Q * 16 + N * 8, 4.0 * Q),
         "run_stat": ("hbm", Q * 40 + Q1 * 4 + N * 12, 8.0 * Q),
         # per edge: the run's gradient row, its 16 bytes, three indices, dz; per node its row in and out
@@ -85,7 +82,7 @@ def run_row_work(name, E, N, P, Q, Q1, R, d, bf16=False, layer="rgat", n_dst=Non
         "run_term": ("hbm", N * 2 * row + Q * 8, 2.0 * Q * d),
         "run_logit": ("hbm", Q * 12 + (N if n_dst is None else n_dst) * row, 2.0 * Q * d),
         # RGCN: per edge the run's gradient row, its index and coefficient
-        "node_grad_sum": ("hbm", E * (row + 8) + N * (r32 + 16), 2.0 * E * d),
+        "node_grad_sum": ("hbm", E * (row + 8) + N * (row + 16), 2.0 * E * d),
     }
     return table.get(name)
 
@@ -518,7 +515,7 @@ def main():
 
     def work(name):
         if runs and not name.endswith((".reduce", ".combine", ".finish")):
-            w = run_row_work(name, E, N, P, Q, Q1, R, d, c["dtype"] == "bf16", c["layer"], n_dst)
+            w = run_row_work(name, E, N, P, Q, Q1, R, d, c["layer"], n_dst)
             if w:
                 return w
         w = algorithmic_work(name, E, N, P, Q, R, T, d, H, P1, c["dtype"] == "bf16", c["layer"], sched, n_dst)

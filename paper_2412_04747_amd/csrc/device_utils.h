@@ -180,26 +180,6 @@ __device__ __forceinline__ void store_cols(bf16_t* __restrict__ p, const float (
         *reinterpret_cast<uint2*>(p) = make_uint2(bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]));
     }
 }
-// Columns cv * V + 0..V-1 of row `row` of a tensor of D columns.  bf16_planes_t: a row is two bf16 rows, the values rounded and what the
-// rounding left (16 bits of the fp32 value between them), 4 D bytes.
-struct bf16_planes_t { bf16_t plane[2]; };
-template <int D, typename TO, int V>
-__device__ __forceinline__ void store_row(void* out, size_t row, int cv, const float (&v)[V]) {
-    if constexpr (sizeof(TO) == sizeof(bf16_planes_t) && !__is_same(TO, float)) {
-        bf16_t* p = static_cast<bf16_t*>(out) + row * 2 * D + cv * V;
-        float lo[V];
-#pragma unroll
-        for (int q = 0; q < V; q += 2) {
-            const unsigned h = bf16_pack2(v[q], v[q + 1]);
-            lo[q] = v[q] - __uint_as_float(h << 16);
-            lo[q + 1] = v[q + 1] - __uint_as_float(h & 0xFFFF0000u);
-        }
-        store_cols(p, v);
-        store_cols(p + D, lo);
-    } else {
-        store_cols(static_cast<TO*>(out) + row * D + cv * V, v);
-    }
-}
 template <int V>
 __device__ __forceinline__ void zero_cols(float (&v)[V]) {
 #pragma unroll

@@ -264,8 +264,7 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     build_long(U, g->long_pairs, out_ptr);
     if (g->run_rows) {
         const int loop_runs = pair_share(g->Q, g->N, cus, 1);
-        build_tiles(U, relrun_ptr, kTileRows, {{&g->run_tiles_loop, loop_runs}, {&g->run_tiles, kMaxChunks}, {&g->run_tiles_wide, kWideChunksPerCU * cus},
-                                               {&g->run_tiles_cu2, 2 * cus}, {&g->run_tiles_cu1, cus}});
+        build_tiles(U, relrun_ptr, kTileRows, {{&g->run_tiles_loop, loop_runs}, {&g->run_tiles_wide, kWideChunksPerCU * cus}, {&g->run_tiles_cu1, cus}});
         build_tiles(U, std::vector<int32_t>{0, (int32_t)g->N}, kTileRows, {{&g->all_tiles_run_loop, std::max(cus - loop_runs, 1)}});
     }
     if (g->run_rows) {

@@ -435,8 +435,7 @@ __global__ void k_several(long long Q, const int32_t* idx, const int32_t* run_pt
 // run i of the (relation, destination) order; incl: running counts of the runs with several edges in that order, num: in run order
 __global__ void k_run_rows(long long Q, const int32_t* relrun_idx, const int32_t* relrun_ptr, const int32_t* run_rel, const int32_t* run_ptr,
                            const int32_t* run_dst, const int32_t* in_src, const int32_t* incl, const int32_t* num, int32_t* run_row,
-                           int32_t* run_tag, int32_t* multi_run, int32_t* row_in, int32_t* row_dst, int32_t* row_run,
-                           int32_t* multi_end) {
+                           int32_t* run_tag, int32_t* multi_run, int32_t* row_in, int32_t* row_dst, int32_t* row_run) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= Q) return;
     const int32_t q = relrun_idx[i], r = run_rel[q], b = relrun_ptr[r], e = relrun_ptr[r + 1], beg = run_ptr[q];
@@ -449,7 +448,6 @@ __global__ void k_run_rows(long long Q, const int32_t* relrun_idx, const int32_t
     if (multi) multi_run[num[q] - 1] = q;
     row_dst[row] = run_dst[q];
     row_in[row] = multi ? (int32_t)((uint32_t)(num[q] - 1) | 0x80000000u) : in_src[beg];
-    if (i == b) multi_end[r] = b + several;
 }
 __global__ void k_pair_len(long long P, const int32_t* srcpair_idx, const int32_t* out_ptr, int32_t* len) {
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -513,7 +511,6 @@ rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr) {
     RGNN_TRY(run_row.alloc((size_t)Q * sizeof(int32_t)));
     RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_in));
     RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_dst));
-    RGNN_TRY(keep<int32_t>(g, (size_t)g->R, &g->multi_end));
     RGNN_TRY(keep<int32_t>(g, (size_t)E, &g->src_row));
     RGNN_TRY(keep<float>(g, (size_t)E, &g->src_invc));
     RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->run_tag));
@@ -521,14 +518,13 @@ rgnn_status_t build_run_rows(rgnn_graph* g, std::vector<int32_t>& src_ptr) {
     for (int32_t** p : {&g->src_run, &g->src_rel, &g->in_spos}) RGNN_TRY(keep<int32_t>(g, (size_t)E, p));
     RGNN_TRY(keep<int32_t>(g, (size_t)P, &g->pair_spos));
     RGNN_TRY(keep<int32_t>(g, (size_t)Q, &g->row_run));
-    RGNN_HIP(hipMemset(g->multi_end, 0, (size_t)g->R * sizeof(int32_t)));
     LAUNCH(k_several, (size_t)Q, Q, (const int32_t*)nullptr, g->idx[RGNN_IDX_RUN_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), b.as<int32_t>(), (size_t)Q));
     LAUNCH(k_several, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RUN_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), c.as<int32_t>(), (size_t)Q));
     LAUNCH(k_run_rows, (size_t)Q, Q, g->idx[RGNN_IDX_RELRUN_IDX], g->idx[RGNN_IDX_RELRUN_PTR], g->idx[RGNN_IDX_RUN_REL], g->idx[RGNN_IDX_RUN_PTR],
            g->idx[RGNN_IDX_RUN_DST], g->idx[RGNN_IDX_IN_SRC], c.as<int32_t>(), b.as<int32_t>(), run_row.as<int32_t>(), g->run_tag,
-           g->multi_run, g->row_in, g->row_dst, g->row_run, g->multi_end);
+           g->multi_run, g->row_in, g->row_dst, g->row_run);
     LAUNCH(k_pair_len, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], g->idx[RGNN_IDX_OUT_PTR], a.as<int32_t>());
     RGNN_TRY(inclusive_scan(a.as<int32_t>(), b.as<int32_t>(), (size_t)P));
     LAUNCH(k_pair_start, (size_t)P, P, g->idx[RGNN_IDX_SRCPAIR_IDX], a.as<int32_t>(), b.as<int32_t>(), g->pair_spos);

@@ -147,9 +147,9 @@ inline Chunkings pair_chunks(const rgnn_graph_t* g, int width) {
 inline Chunkings node_chunks(const rgnn_graph_t* g, int width) {
     return chunkings(g->node_tiles, g->node_tiles_wide, g->node_tiles_cu2, g->node_tiles_cu1, width);
 }
-// rows per run instead of per pair
+// rows per run instead of per pair (fp32 only: neither many nor cu2)
 inline Chunkings run_chunks(const rgnn_graph_t* g, int width) {
-    return chunkings(g->run_tiles, g->run_tiles_wide, g->run_tiles_cu2, g->run_tiles_cu1, width);
+    return chunkings(g->run_tiles_wide, g->run_tiles_wide, g->run_tiles_cu1, g->run_tiles_cu1, width);
 }
 inline const rgnn::TileList* all_chunks(const rgnn_graph_t* g, int width) { return width == 128 ? &g->all_tiles_cu1 : &g->all_tiles; }
 // floats of scratch a backward typed linear needs on a list
@@ -270,9 +270,9 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 }
 
 // ---- RGCN buffers -----------------------------------------------------------------------
-// Rows per run: A[m] = the mean (sum) of the input rows of the m-th run with several edges, fp32, or with bf16 rows in two planes of bf16; Hs holds a message row per run.
+// Rows per run: A[m] = the mean (sum) of the input rows of the m-th run with several edges; Hs holds a message row per run.
 struct RgcnFwdWs { void* Hs; float* partial; float* A; };
-inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, d->flags); }
+inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, d->flags); }
 size_t carve_rgcn_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, float** A) {
     Carver c(base);
     if (rgcn_run_rows(g, d)) *A = c.take<float>((size_t)g->num_multi_runs * d->d_in);
@@ -562,10 +562,9 @@ extern "C" rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, con
 // =========================================================================== RGCN
 
 // A[m] = sum over the edges of the m-th run with several edges of X[src_e] / c, or of X[src_e]
-static rgnn_status_t rgcn_run_inputs(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, bool x16, float* A, float* partial, hipStream_t st) {
+static rgnn_status_t rgcn_run_inputs(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const float* X, float* A, float* partial, hipStream_t st) {
     const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
-    return gather_sum(g->multi_run_items, desc->d_in, nullptr, g->idx[RGNN_IDX_IN_SRC], 0, coef, 1, 0, X, A, partial, st, 1, "run_inputs", "run_inputs.combine",
-                      1, x16, x16 ? 2 : 0);
+    return gather_sum(g->multi_run_items, desc->d_in, nullptr, g->idx[RGNN_IDX_IN_SRC], 0, coef, 1, 0, X, A, partial, st, 1, "run_inputs", "run_inputs.combine");
 }
 
 extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X,
@@ -588,12 +587,11 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     const float* W032 = stg.in(W0, (size_t)desc->d_in * D);
     RGNN_TRY(stg.status);
     // What the backward reads is left in `saved` whichever plan the forward takes: the backward cannot tell.
-    const bool runs = rgcn_run_rows(g, desc) && (saved || sched_run_rows_infer(h, g->E, D));
-    const void* const Xr = h ? X : static_cast<const void*>(X32);
+    const bool runs = rgcn_run_rows(g, desc) && (saved || sched_run_rows_infer(g->E, D));
     float* A = w.A;
     if (runs && saved) {
         (void)carve_rgcn_saved(g, desc, saved, &A);
-        RGNN_TRY(rgcn_run_inputs(g, desc, Xr, h, A, w.partial, st));
+        RGNN_TRY(rgcn_run_inputs(g, desc, X32, A, w.partial, st));
     }
     // (one launch: rows of out are written while others of X are still read, so an out that shares memory with X goes to the
     // general plan, which has read X by then unless there is a self-loop)
@@ -604,18 +602,11 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     if (runs) {
         // The sum over a run's edges comes before the product: a row of messages per run, not per pair, and a run with one edge reads its
         // source's row directly.
-        if (!saved) RGNN_TRY(rgcn_run_inputs(g, desc, Xr, h, A, w.partial, st));
-        if (h) {
-            TypedLinearFwdBf16Args a{&g->run_tiles_cu2, X, g->row_in, 0, W, nullptr, w.Hs, "typed_linear_fwd"};
-            a.A2 = A; a.planes_end = g->multi_end; a.to = g->row_run;
-            RGNN_TRY(typed_linear_fwd_bf16(a, st));
-        } else {
-            TypedLinearArgs a{};
-            a.tiles = run_chunks(g, D).f32; a.X = X32; a.X2 = A; a.gather = g->row_in; a.to = g->row_run; a.W = W32; a.Y = static_cast<float*>(w.Hs); a.sign_matters = 1;
-            RGNN_TRY(typed_linear_fwd(desc->d_in, D, a, st));
-        }
-        RGNN_TRY(gather_sum(g->dstrun_items, D, nullptr, nullptr, 0, nullptr, 1, 0, w.Hs, out, w.partial, st, 0, "aggregate_fwd", "aggregate_fwd.combine",
-                            1, h, 0));
+        if (!saved) RGNN_TRY(rgcn_run_inputs(g, desc, X32, A, w.partial, st));
+        TypedLinearArgs a{};
+        a.tiles = run_chunks(g, D).f32; a.X = X32; a.X2 = A; a.gather = g->row_in; a.to = g->row_run; a.W = W32; a.Y = static_cast<float*>(w.Hs); a.sign_matters = 1;
+        RGNN_TRY(typed_linear_fwd(desc->d_in, D, a, st));
+        RGNN_TRY(gather_sum(g->dstrun_items, D, nullptr, nullptr, 0, nullptr, 1, 0, w.Hs, out, w.partial, st, 0, "aggregate_fwd", "aggregate_fwd.combine"));
     } else {
         // 1. compact messages: Hs[p] = X[pair_src[p]] W[rel(p)]
         RGNN_TRY(tl_fwd(bf16, pair_chunks(g, D), D, X32, X16, g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.Hs, h, "typed_linear_fwd", st,
@@ -679,7 +670,7 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
         (void)carve_rgcn_saved(g, desc, const_cast<void*>(saved), &kept);
         A = kept;
     } else if (runs) {
-        RGNN_TRY(rgcn_run_inputs(g, desc, h ? X : static_cast<const void*>(X32), h, w.A, w.partial, st));
+        RGNN_TRY(rgcn_run_inputs(g, desc, X32, w.A, w.partial, st));
     }
     // 1. dHs[p] = sum_{e in out(p)} (1/c_e) dPre[dst_e]     (rows per run: the row of run q is dPre[dst_q])
     const float* coef = desc->norm == RGNN_NORM_IN_DEGREE_PER_REL ? g->in_invc : nullptr;
@@ -712,15 +703,8 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
         s.tiles = runs ? &g->all_tiles_run_loop : &g->all_tiles_loop;
         RGNN_TRY(typed_linear_bwd_loop(K, D, b, s, st));
     } else if (runs) {
-        if (h) {
-            TypedLinearBwdBf16Args c{};
-            c.tiles = &g->run_tiles_cu2; c.X = X; c.A2 = A; c.gather = g->row_in; c.W = W; c.w_bf16 = 1;
-            c.dY = dPre; c.ysel = g->row_dst; c.dXrow = w.dXp; c.dW = static_cast<float*>(dW); c.part = w.tl_part; c.label = "typed_linear_bwd"; c.sums = &sums;
-            RGNN_TRY(typed_linear_bwd_bf16(D, c, st));
-        } else {
-            b.tiles = run_chunks(g, D).f32_bwd;
-            RGNN_TRY(typed_linear_bwd(K, D, b, st));
-        }
+        b.tiles = run_chunks(g, D).f32_bwd;
+        RGNN_TRY(typed_linear_bwd(K, D, b, st));
         if (W0) RGNN_TRY(typed_linear_bwd(K, D, s, st));
     } else {
         RGNN_TRY(tl_bwd(h, pair_chunks(g, D), D, h ? X : static_cast<const void*>(X32), g->idx[RGNN_IDX_PAIR_SRC], 0, W32, W16, w.G,
@@ -734,7 +718,7 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     else if (acc) extra = static_cast<const float*>(dX);
     if (runs)      // over u's edges: the row of the edge's run, times 1/c
         RGNN_TRY(gather_sum(g->src_items, K, nullptr, g->src_row, 0, coef ? g->src_invc : nullptr, 1, 0, w.dXp, dX, w.partial, st, 3, "node_grad_sum",
-                            "node_grad_sum.combine", 1, h, 0, nullptr, extra));
+                            "node_grad_sum.combine", 1, 0, 0, nullptr, extra));
     else
         RGNN_TRY(node_grad_sum(g, K, w.dXp, nullptr, nullptr, extra, dX, st, h, 0));
     return ga.flush(st);

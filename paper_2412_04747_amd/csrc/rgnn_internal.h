@@ -155,14 +155,13 @@ struct rgnn_graph {
     int32_t* row_in = nullptr;             // [Q] by row: source of the run's only edge, or the top bit | number of the run among those
                                            // with several edges, in run order
     int32_t* row_dst = nullptr;            // [Q] by row: destination
-    int32_t* multi_end = nullptr;          // [R] end of a relation's rows of runs with several edges
     int32_t* src_row = nullptr;            // [E] by (source, relation, CSR position): row of the edge's run
     float* src_invc = nullptr;             // [E] 1 / c_{v,r} of that edge
     int32_t *src_run = nullptr, *src_rel = nullptr;       // [E] its run, with the top bit set when it is the run's only edge, and its relation
     int32_t* in_spos = nullptr;            // [E] place in that order of a CSR edge
     int32_t* pair_spos = nullptr;          // [P] and of a pair's first edge
     int32_t* row_run = nullptr;            // [Q] run of a row
-    rgnn::TileList run_tiles, run_tiles_wide, run_tiles_cu2, run_tiles_cu1, run_tiles_loop, all_tiles_run_loop;   // as those of the pairs
+    rgnn::TileList run_tiles_wide, run_tiles_cu1, run_tiles_loop, all_tiles_run_loop;   // as those of the pairs
     rgnn::ItemList multi_run_items;        // CSR edges of the runs with several edges (row: their number)
     rgnn::ItemList dstrun_items;           // runs by destination
     rgnn::ItemList src_items;              // edges by source
@@ -284,11 +283,6 @@ rgnn_status_t typed_linear_bf16(int d, const TypedLinearBf16Args& a, hipStream_t
 // (X[gather[i]] W[seg], X[gather[i]] W2[seg]) in rows 256 wide
 struct TypedLinearFwdBf16Args {
     const TileList* tiles; const void* X; const int32_t* gather; int scatter_out; const void* W; const void* W2; void* Y; const char* label;
-    // gather[i] < 0: row i is row gather[i] & 0x7FFFFFFF of A2, whose rows are two bf16 planes (256 + 256 bytes); within a segment these
-    // come first, up to row planes_end[seg] (one weight)
-    const void* A2 = nullptr;
-    const int32_t* planes_end = nullptr;
-    const int32_t* to = nullptr;     // with A2: row i of the result is row to[i] of Y
 };
 rgnn_status_t typed_linear_fwd_bf16(const TypedLinearFwdBf16Args& a, hipStream_t st);
 
@@ -315,7 +309,6 @@ struct TypedLinearBwdBf16Args {
     const int32_t* ysel = nullptr;
     const void* dY_alt = nullptr;
     const float* yscale = nullptr;
-    const void* A2 = nullptr;    // gather[i] < 0: row i of X is the first plane of row gather[i] & 0x7FFFFFFF of A2; row i of dY is dY[ysel[i]] (no dY_alt)
     // optional (bf16 weight, fp32 dXrow gathered on both sides): dXrow[n] += the rows sum_row[sum_ptr[n] .. sum_ptr[n + 1]) of sum_rows
     const int32_t* sum_ptr = nullptr;
     const int32_t* sum_row = nullptr;

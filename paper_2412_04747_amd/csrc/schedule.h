@@ -50,9 +50,11 @@ inline bool sched_row_select(int layer, int dtype, int d, int heads, int R, int6
 // rows: 2 E + 7 Q - 2 Q1 over a training step (Q runs, Q1 of them with one edge, which are read where they are) against
 // 2 E + 7 P - 2 P1, and has fewer products.  The graph gets the lists for it where that is so (sched_run_rows).
 // RGCN, forward + backward, us, pairs / runs, at 7 Q - 2 Q1 from 0.54 to 0.72 of 7 P - 2 P1: 300k edges, 60 relations, width 32 81 / 81, 64
-// 145 / 126, 128 277 / 211, bf16 128 138 / 136; 3M edges 443 / 340, 930 / 649, 2283 / 1438, 911 / 753; at equal numbers 78 / 76, 140 /
-// 139, 273 / 268 and 129 / 132 (300k edges); at 1.7 times the rows 172 / 205 (width 128, 8 relations).  Below 131072 edges the sum, a
-// launch or two more, costs what the rest saves: 100k edges 56 / 56, 85 / 88, 131 / 126, 95 / 98.
+// 145 / 126, 128 277 / 211; 3M edges 443 / 340, 930 / 649, 2283 / 1438; at equal numbers 78 / 76, 140 /
+// 139 and 273 / 268 (300k edges); at 1.7 times the rows 172 / 205 (width 128, 8 relations).  Below 131072 edges the sum, a
+// launch or two more, costs what the rest saves: 100k edges 56 / 56, 85 / 88, 131 / 126.
+// Not where rows are stored in bf16 (layers.hip): a row of a run is a partial sum of out, and the sum of a run's inputs a partial sum of dW;
+// both were rounded to bf16 once, which rows per pair do not do (error of out with 64 edges per run and non-negative features 1.7e-3 for 3.4e-4).
 inline bool sched_run_rows(int64_t edges, int64_t pairs, int64_t single_pairs, int64_t runs, int64_t single_runs) {
     return edges >= (1 << 17) && 20 * (7 * runs - 2 * single_runs) <= 19 * (7 * pairs - 2 * single_pairs);
 }
@@ -60,9 +62,8 @@ inline bool sched_run_rows(int64_t edges, int64_t pairs, int64_t single_pairs, i
 inline bool sched_use_run_rows(bool lists, uint32_t flags) { return lists && !(flags & ~(uint32_t)RGNN_FLAG_ACCUMULATE); }
 inline bool sched_rgcn_run_rows(bool lists, int64_t edges, int d, uint32_t flags) { return sched_use_run_rows(lists, flags) && edges * d >= 8000000; }
 // RGCN forwards that keep nothing for a backward: the saving has to come from the forward alone.  Pairs / runs, us: 300k edges, 60
-// relations, width 32 34 / 46, 64 59 / 64, 128 129 / 109; 1M 75 / 73, 145 / 124, 340 / 266; bf16 1M 137 / 145, 3M 397 / 408, 16M and 500
-// relations 2551 / 2374.
-inline bool sched_run_rows_infer(bool rows_bf16, int64_t edges, int d) { return edges * d >= (rows_bf16 ? 1000000000 : 30000000); }
+// relations, width 32 34 / 46, 64 59 / 64, 128 129 / 109; 1M 75 / 73, 145 / 124, 340 / 266.
+inline bool sched_run_rows_infer(int64_t edges, int d) { return edges * d >= 30000000; }
 // RGAT with one head.  The walks look the relations' folded vectors up, once per run or edge, so more relations move the line out, and at
 // width 32 the indices outweigh the rows.  Forward + backward, us, pairs / runs, at 7 Q - 2 Q1 from 0.54 to 0.72 of 7 P - 2 P1: 8 relations,
 // width 64 173 / 152 at 300k edges, 1108 / 798 at 3M, 128 178 / 162 at 140k, 463 / 338 at 550k; 60 relations, 64 300 / 260 at 550k, 1317 / 990 at 3M, 128

@@ -406,7 +406,7 @@ __device__ __forceinline__ void gather_general(const GatherArgs& a, int blk) {
         if (R1) add_rank1<D>(a.r1, a.lanes_per_head, (size_t)a.it.row[i], cv, acc0);
         if (EX) add_row<D>(a.extra, (size_t)a.it.row[i], cv, acc0);
         if (S2) add_rank1_own<D>(a.r1, s2, (size_t)a.it.row[i], cv, acc0);
-        store_row<D, TO>(a.out, (size_t)a.it.row[i], cv, acc0);
+        store_cols(static_cast<TO*>(a.out) + (size_t)a.it.row[i] * D + cv * V, acc0);
         if (S2 && cv % a.lanes_per_head == 0) a.sum2[(size_t)a.it.row[i] * a.sum2_stride + head] = s2;
     } else {
         store_cols(a.partial + (size_t)slot * D + cv * V, acc0);
@@ -465,7 +465,7 @@ __device__ __forceinline__ void gather_short(const GatherArgs& a, int blk, int f
             if (R1) add_rank1<D>(a.r1, a.lanes_per_head, (size_t)orow[q], cv, acc);
             if (EX) add_row<D>(a.extra, (size_t)orow[q], cv, acc);
             if (S2) add_rank1_own<D>(a.r1, s2[q], (size_t)orow[q], cv, acc);
-            store_row<D, TO>(a.out, (size_t)orow[q], cv, acc);
+            store_cols(static_cast<TO*>(a.out) + (size_t)orow[q] * D + cv * V, acc);
             if (S2 && cv % a.lanes_per_head == 0) a.sum2[(size_t)orow[q] * a.sum2_stride + head] = s2[q];
         }
     }
@@ -511,7 +511,7 @@ __device__ __forceinline__ void gather_single(const GatherArgs& a, int blk, int 
             for (int q = 0; q < V; ++q) v[u][q] *= c[u];
             if (R1) add_rank1<D>(a.r1, a.lanes_per_head, (size_t)orow[u], cv, v[u]);
             if (EX) add_row<D>(a.extra, (size_t)orow[u], cv, v[u]);
-            store_row<D, TO>(a.out, (size_t)orow[u], cv, v[u]);
+            store_cols(static_cast<TO*>(a.out) + (size_t)orow[u] * D + cv * V, v[u]);
         }
     }
 }
@@ -531,11 +531,11 @@ __global__ __launch_bounds__(256) void gather_sum_kernel(GatherArgs a, GatherRan
     else gather_single<D, TI, TO, R1, ROLE == 0, ROLE == 3>(a, blk - r.general_blocks - r.short_blocks, r.single_first, r.single_n);
 }
 template <int D, int ROLE, typename TI, typename TO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void gather_general_kernel(GatherArgs a) { gather_general<D, TI, TO, false, ROLE == 0, false, ROLE == 3>(a, blockIdx.x); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void gather_general_kernel(GatherArgs a) { gather_general<D, TI, TO, false, ROLE == 0>(a, blockIdx.x); }
 template <int D, int ROLE, typename TI, typename TO>
-__global__ __launch_bounds__(256) void gather_short_kernel(GatherArgs a, int first, int n) { gather_short<D, TI, TO, false, ROLE == 0, false, ROLE == 3>(a, blockIdx.x, first, n); }
+__global__ __launch_bounds__(256) void gather_short_kernel(GatherArgs a, int first, int n) { gather_short<D, TI, TO, false, ROLE == 0>(a, blockIdx.x, first, n); }
 template <int D, int ROLE, typename TI, typename TO>
-__global__ __launch_bounds__(256) void gather_single_kernel(GatherArgs a, int first, int n) { gather_single<D, TI, TO, false, ROLE == 0, ROLE == 3>(a, blockIdx.x, first, n); }
+__global__ __launch_bounds__(256) void gather_single_kernel(GatherArgs a, int first, int n) { gather_single<D, TI, TO, false, ROLE == 0>(a, blockIdx.x, first, n); }
 
 // NH weighted sums of the same rows in one walk: out[h][row_i] = sum_j coef[k][h] * src[row], k and row as
 // in gather_sum_kernel (fp32 rows).  out is [NH][out_rows][D], the partial rows [NH][num_partials][D].
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(TH) void combine_partials_kernel(const int32_t* __r
         float tv[4] = {t.x, t.y, t.z, t.w};
         add_rank1<D>(r1, lanes_per_head, (size_t)split_row[s], c4, tv);
         add_row<D>(extra, (size_t)split_row[s], c4, tv);
-        store_row<D, TO>(out, (size_t)split_row[s], c4, tv);
+        store_cols(out + (size_t)split_row[s] * D + c4 * 4, tv);
     }
 }
 // Hub nodes and pairs: mostly two or three pieces per cut segment and thousands of segments, so small workgroups (1024
@@ -1419,10 +1419,7 @@ rgnn_status_t combine_partials(const ItemList& L, int D, const float* partial, v
             hipLaunchKernelGGL((combine_partials_kernel<DD_, TO_, 256, DD_ / 4>), dim3(L.num_split, copies), dim3(256), 0, st, L.split_row, \
                                L.split_ptr, partial, static_cast<TO_*>(out), (size_t)L.num_partials * DD_, out_copy, r1v, (DD_ / 4) / heads, extra); \
     } while (0)
-    if (out_bf16 == 2) {
-        if (D != 128) RGNN_FAIL(RGNN_EUNSUPPORTED, "combine_partials: two bf16 planes at width 128 only");
-        RGNN_LAUNCH_COMBINE(128, bf16_planes_t);
-    } else if (D == 256) {
+    if (D == 256) {
         if (out_bf16) RGNN_LAUNCH_COMBINE(256, bf16_t);
         else RGNN_LAUNCH_COMBINE(256, float);
     } else if (out_bf16) {
@@ -1460,8 +1457,7 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
     do {                                                                                                                   \
         if (role == 0) RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 0, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
         else if (role == 1) RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 1, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
-        else if (role == 2) RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 2, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
-        else RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 3, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
+        else RGNN_DISPATCH_ROWS(D, src_bf16, out_bf16, hipLaunchKernelGGL((KERNEL<DD, 2, TI, TO>), GRID, dim3(256), 0, st, __VA_ARGS__)); \
         RGNN_CHECK_LAUNCH();                                                                                               \
     } while (0)
         if (r1 && (src_bf16 || out_bf16 || role != 1)) RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: the rank-1 term is built for fp32 rows of the pair-major walk");
@@ -1470,12 +1466,12 @@ rgnn_status_t gather_sum(const ItemList& L, int D, const int32_t* via, const int
                 RGNN_DISPATCH_D(D, hipLaunchKernelGGL((gather_sum_kernel<DD, 1, float, float, true>), grid, dim3(256), 0, st, a, r));
                 RGNN_CHECK_LAUNCH();
             }
-        } else if (out_bf16 == 2) {
-            if (D != 128 || !src_bf16 || role != 1) RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: sums in two bf16 planes are built for bf16 rows of width 128");
-            if (r.general_blocks > 0) hipLaunchKernelGGL((gather_general_kernel<128, 1, bf16_t, bf16_planes_t>), dim3(r.general_blocks), dim3(256), 0, st, a);
-            if (nsh > 0) hipLaunchKernelGGL((gather_short_kernel<128, 1, bf16_t, bf16_planes_t>), dim3(r.short_blocks), dim3(256), 0, st, a, L.first_short, nsh);
-            if (ns > 0) hipLaunchKernelGGL((gather_single_kernel<128, 1, bf16_t, bf16_planes_t>), dim3(single_blocks), dim3(256), 0, st, a, L.first_single, ns);
-            RGNN_CHECK_LAUNCH();
+        } else if (role == 3) {
+            if (src_bf16 || out_bf16) RGNN_FAIL(RGNN_EUNSUPPORTED, "gather_sum: the sums over sources are built for fp32 rows");
+            if (grid.x > 0) {
+                RGNN_DISPATCH_D(D, hipLaunchKernelGGL((gather_sum_kernel<DD, 3, float, float>), grid, dim3(256), 0, st, a, r));
+                RGNN_CHECK_LAUNCH();
+            }
         } else if (!src_bf16) {
             if (grid.x > 0) RGNN_LAUNCH_GATHER(gather_sum_kernel, grid, a, r);
         } else {

@@ -38,7 +38,6 @@ struct BwdArgs {
     const int32_t* ysel;
     const bf16_t* dY_alt;
     const float* yscale;
-    const bf16_t* A2;        // XSEL
     const int32_t* sum_ptr;  // PAIRS
     const int32_t* sum_row;
     const bf16_t* sum_rows;
@@ -67,12 +66,9 @@ __device__ __forceinline__ rgnn_v4u scale8(rgnn_v4u x, float s) {
 //          chunks that weigh alike (chunk_tiles), 862 in chunks of as many tiles; where node types differ in their pairs, 2M nodes, 4.5M pairs,
 //          406 + 617, 783 and 1079.  (Whole rows added by the threads
 //          that load a tile, and handed over through LDS, need 25 registers more than two workgroups per compute unit leave: 968 for the 862.)
-//   XSEL   rows per run (typed_linear_fwd_bf16.hip): X rows from X or A2, and row i of dY is dY[ysel[i]].  The first plane of A2 is enough
-//          here: a rounding of A[q] / c weighs what those of its c edges' dOut / c did in rows per pair (dW of 2M edges against 64 bits:
-//          6.9e-4 per pair, 4.9e-4 per run)
-template <int NB, int WPL, bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool XSEL = false, bool PAIRS = false>
+template <int NB, int WPL, bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool PAIRS = false>
 __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
-    static_assert(!(SEL && BOTH) && (GATHER || !BOTH) && (DX32 || !ACC) && (NB == 1 || !SEL) && (!XSEL || (SEL && GATHER)) && (!PAIRS || (BOTH && DX32)), "combinations the layers use");
+    static_assert(!(SEL && BOTH) && (GATHER || !BOTH) && (DX32 || !ACC) && (NB == 1 || !SEL) && (!PAIRS || (BOTH && DX32)), "combinations the layers use");
     constexpr int D = 128, TILE = 64 * 2 * D;             // bytes of a 64-row tile
     constexpr int SLOT = NB * D * D;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -120,17 +116,15 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
             const int row = min(row0 + lr + 32 * k, row1 - 1);
             gi[k] = GATHER ? a.gather[row] : row;
             gy[k] = SEL ? a.ysel[row] : BOTH ? gi[k] : row;
-            if (SEL && !XSEL && a.yscale) sc[k] = a.yscale[row];
+            if (SEL && a.yscale) sc[k] = a.yscale[row];
         }
     };
     auto fetch = [&]() {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const bf16_t* x = a.X + (size_t)gi[k] * D + lc * 8;
-            if (XSEL && gi[k] < 0) x = a.A2 + (size_t)(gi[k] & 0x7FFFFFFF) * (2 * D) + lc * 8;
-            xr[k] = *reinterpret_cast<const rgnn_v4u*>(x);
-            const bf16_t* y = SEL && !XSEL && gy[k] < 0 ? a.dY_alt : a.dY;
-            y += (size_t)(SEL && !XSEL ? gy[k] & 0x7FFFFFFF : gy[k]) * a.ldd + lc * 8;
+            xr[k] = *reinterpret_cast<const rgnn_v4u*>(a.X + (size_t)gi[k] * D + lc * 8);
+            const bf16_t* y = SEL && gy[k] < 0 ? a.dY_alt : a.dY;
+            y += (size_t)(SEL ? gy[k] & 0x7FFFFFFF : gy[k]) * a.ldd + lc * 8;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) yr[nb][k] = *reinterpret_cast<const rgnn_v4u*>(y + nb * D);
             gcur[k] = gi[k];
@@ -212,7 +206,7 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 rgnn_v4u y = yr[nb][k];
-                if (SEL && !XSEL && a.yscale) y = scale8(y, scc[k]);
+                if (SEL && a.yscale) y = scale8(y, scc[k]);
                 *reinterpret_cast<rgnn_v4u*>(Yt + nb * TILE + io + k * 32 * 256) = ok ? y : z;
             }
             gout[k] = gcur[k];
@@ -331,9 +325,9 @@ __device__ __forceinline__ void bwd_tiles(const BwdArgs& a) {
 
 // One weight in bf16: 128 registers and 80 KB of LDS leave room for two workgroups per compute unit, so that one loads
 // while the other multiplies; two weights (or one split into two planes) take twice the room for W and run alone.
-template <bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool XSEL = false, bool PAIRS = false>
+template <bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC, bool PAIRS = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void typed_linear_bwd_bf16_kernel(BwdArgs a) {
-    bwd_tiles<1, 1, GATHER, BOTH, SEL, DX32, ACC, XSEL, PAIRS>(a);
+    bwd_tiles<1, 1, GATHER, BOTH, SEL, DX32, ACC, PAIRS>(a);
 }
 template <int NB, int WPL, bool GATHER, bool BOTH, bool SEL, bool DX32, bool ACC>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_bwd_bf16_big_kernel(BwdArgs a) {
@@ -347,7 +341,7 @@ rgnn_status_t launch(K kern, const TypedLinearBwdBf16Args& a, int nb, int wpl, h
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     const TileList& t = *a.tiles;
     BwdArgs b{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, t.chunk_slot, static_cast<const bf16_t*>(a.X), a.gather,
-              static_cast<const bf16_t*>(a.dY), a.dy_stride * 128, a.ysel, static_cast<const bf16_t*>(a.dY_alt), a.yscale, static_cast<const bf16_t*>(a.A2),
+              static_cast<const bf16_t*>(a.dY), a.dy_stride * 128, a.ysel, static_cast<const bf16_t*>(a.dY_alt), a.yscale,
               a.sum_ptr, a.sum_row, static_cast<const bf16_t*>(a.sum_rows), {a.W, a.W2}, a.dXrow, a.part};
     KernelTimer kt(st, a.label);
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st, b);
@@ -363,9 +357,7 @@ rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipS
         const bool both = a.both_gathered != 0, sel = a.ysel != nullptr;
         if (both && !a.gather) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: rows gathered on both sides need a gather list");
         if (!a.gather) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: built for gathered X rows");
-        if (a.A2 ? !sel || a.dY_alt || a.yscale : sel && !a.dY_alt)
-            RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: the row selector needs a second dY tensor, or a second X tensor and neither that nor scales");
-        if (sel && (both || a.dx_f32 || a.dy_stride != 1 || a.W2 || !a.w_bf16))
+        if (sel && (both || !a.dY_alt || a.dx_f32 || a.dy_stride != 1 || a.W2 || !a.w_bf16))
             RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: the row selector is built for one bf16 weight, ungathered dY and bf16 result rows");
         if (a.accumulate && !(both && a.dx_f32)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: accumulation is built for fp32 rows gathered on both sides");
         if (a.sum_rows && (!both || !a.dx_f32 || a.W2 || !a.w_bf16 || !a.sum_ptr || !a.sum_row))
@@ -376,13 +368,11 @@ rgnn_status_t typed_linear_bwd_bf16(int d, const TypedLinearBwdBf16Args& a, hipS
         } else if (!a.w_bf16) {
             if (both || a.dx_f32) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_bwd_bf16: an fp32 weight is built for ungathered dY and bf16 result rows");
             RGNN_TRY(launch(typed_linear_bwd_bf16_big_kernel<1, 2, true, false, false, false, false>, a, 1, 2, st));
-        } else if (a.A2) {
-            RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, false, true, false, false, true>, a, 1, 1, st));
         } else if (sel) {
             RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, false, true, false, false>, a, 1, 1, st));
         } else if (a.sum_rows) {
-            if (a.accumulate) RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, true, false, true>, a, 1, 1, st));
-            else RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, false, false, true>, a, 1, 1, st));
+            if (a.accumulate) RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, true, true>, a, 1, 1, st));
+            else RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, false, true>, a, 1, 1, st));
         } else if (both && a.dx_f32 && a.accumulate) {
             RGNN_TRY(launch(typed_linear_bwd_bf16_kernel<true, true, false, true, true>, a, 1, 1, st));
         } else if (both && a.dx_f32) {

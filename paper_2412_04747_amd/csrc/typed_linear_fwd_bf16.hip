@@ -29,27 +29,19 @@ struct FwdArgs {
     const int32_t* gather;
     const bf16_t* W[2];
     void* Y;
-    const bf16_t* A2;        // XSEL
-    const int32_t* planes_end;
-    const int32_t* to;
 };
 
 
 constexpr int D = 128, TILE = 64 * 2 * D, WT = D * 2 * D;      // bytes of 64 rows and of a weight
 
 //   NB  weights      SCATTER  row i of the result goes where row i of the input came from
-//   XSEL  rows per run: list entry g >= 0 is row g of X, otherwise row g & 0x7FFFFFFF of A2, two bf16 planes (a sum of bf16 rows rounded
-//         to one would add a rounding that the sum of the products does not have).  Within a segment the rows of A2 come first.
-//         Row i of the result goes to row to[i]: in the order of the walk that sums them (16M edges, 7M runs: this kernel 998 -> 1018 us, the
-//         walk 812 -> 742; the fp32 walks of the runs take the same either way).
-template <int NB, bool SCATTER, bool XSEL = false>
+template <int NB, bool SCATTER>
 __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
-    static_assert((NB == 1 || !SCATTER) && (!XSEL || (NB == 1 && !SCATTER)), "combinations the layers use");
+    static_assert(NB == 1 || !SCATTER, "combinations the layers use");
     extern __shared__ __align__(16) unsigned char lds[];
     unsigned char* const Wl = lds;                        // [NB][128][256]
     unsigned char* const Xt = lds + NB * WT;              // [64][256]
     unsigned char* const St = Xt + TILE;                  // [NB][64][256]  the result rows on their way out
-    unsigned char* const Lt = St + NB * TILE;             // XSEL: [64][256] second planes of the rows of A2
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 31, kh = lane >> 5;
     // rows in and out: 16 lanes per 256 bytes, two rows per thread (in), four pieces (out)
@@ -67,38 +59,29 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
     const int xrow = (rb * 32 + m) * 256, xsw = (kh ^ swz(m)) << 4;
     const int t0 = a.chunk_tile[blockIdx.x], t1 = a.chunk_tile[blockIdx.x + 1];
     if (t0 >= t1) return;
-    rgnn_v4u xr[2], xl[2];
-    int gi[2], gcur[2], to[2] = {0, 0}, tn[2] = {0, 0};     // XSEL: to[] of the rows in xr, and of those asked for next
+    rgnn_v4u xr[2];
+    int gi[2], gcur[2];
     TileTable tt(a.tile_seg, a.tile_row0, a.tile_row1, t0, t1);
     auto fetch_idx = [&](int ti) {
         const int l = tt.lane_of(ti), row0 = tt.row0_at(l), row1 = tt.row1_at(l);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int row = min(row0 + lr + 32 * k, row1 - 1);
-            gi[k] = a.gather[row];
-            if (XSEL) tn[k] = a.to[row];
-        }
+        for (int k = 0; k < 2; ++k) gi[k] = a.gather[min(row0 + lr + 32 * k, row1 - 1)];
     };
     auto fetch = [&]() {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const bf16_t* x = a.X + (size_t)gi[k] * D + lc * 8;
-            if (XSEL && gi[k] < 0) x = a.A2 + (size_t)(gi[k] & 0x7FFFFFFF) * (2 * D) + lc * 8;
-            xr[k] = *reinterpret_cast<const rgnn_v4u*>(x);
-            if (XSEL) xl[k] = *reinterpret_cast<const rgnn_v4u*>(x + (gi[k] < 0 ? D : 0));   // (unconditional; a row of X again is not used)
+            xr[k] = *reinterpret_cast<const rgnn_v4u*>(a.X + (size_t)gi[k] * D + lc * 8);
             gcur[k] = gi[k];
-            to[k] = tn[k];
         }
     };
     fetch_idx(t0);
     fetch();
     fetch_idx(min(t0 + 1, t1 - 1));
-    int cur_seg = -1, planes_end = 0;      // XSEL: rows below planes_end are rows of A2
+    int cur_seg = -1;
     for (int ti = t0; ti < t1; ++ti) {
         const int tl = tt.lane_of(ti), seg = tt.seg_at(tl);
         if (seg != cur_seg) {              // (all operand reads of the previous tile lie before its second barrier)
             cur_seg = seg;
-            if (XSEL) planes_end = __builtin_amdgcn_readfirstlane(a.planes_end[seg]);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -108,14 +91,10 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
         }
         const int row0 = tt.row0_at(tl), rows = tt.row1_at(tl) - row0;
         int gout[2];
-        bool two[2];                       // XSEL: this half of the tile has second planes
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             *reinterpret_cast<rgnn_v4u*>(Xt + io + k * 32 * 256) = xr[k];   // past the end the last row again: not stored
-            two[k] = XSEL && row0 + 32 * k < planes_end;
-            const rgnn_v4u z = {0u, 0u, 0u, 0u};
-            if (two[k]) *reinterpret_cast<rgnn_v4u*>(Lt + io + k * 32 * 256) = gcur[k] < 0 ? xl[k] : z;
-            gout[k] = XSEL ? to[k] : gcur[k];
+            gout[k] = gcur[k];
         }
         __syncthreads();   // the tile is complete, and the previous one's result rows have been read out
         fetch();           // unconditional, past the end the last tile again: see the backward
@@ -134,14 +113,6 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
                 d[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr8(w + woff[0], w + woff[1]), bx, d[nb], 0, 0, 0);
             }
         }
-        if (XSEL && (rb ? two[1] : two[0])) {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const bf16x8 bx = *reinterpret_cast<const bf16x8*>(Lt + xrow + (xsw ^ (s << 5)));
-                const unsigned char* w = Wl + s * 4096;
-                d[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr8(w + woff[0], w + woff[1]), bx, d[0], 0, 0, 0);
-            }
-        }
         // d[v] = row rb * 32 + m, block row 8 (v / 4) + 4 kh + v % 4: features 16 fb + (0..15), then 64 further
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -157,17 +128,17 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 const int r = lr + 32 * k;
-                const size_t at = SCATTER || XSEL ? (size_t)gout[k] : (size_t)(row0 + r);
+                const size_t to = SCATTER ? (size_t)gout[k] : (size_t)(row0 + r);
                 if (r < rows)
                     __builtin_nontemporal_store(*reinterpret_cast<const rgnn_v4u*>(St + nb * TILE + io + k * 32 * 256),
-                                                reinterpret_cast<rgnn_v4u*>(static_cast<bf16_t*>(a.Y) + (at * NB + nb) * D + lc * 8));
+                                                reinterpret_cast<rgnn_v4u*>(static_cast<bf16_t*>(a.Y) + (to * NB + nb) * D + lc * 8));
             }
     }
 }
 
 // One weight: two workgroups per compute unit; two weights take the room of both.
-template <bool SCATTER, bool XSEL>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void typed_linear_fwd_bf16_kernel(FwdArgs a) { fwd_tiles<1, SCATTER, XSEL>(a); }
+template <bool SCATTER>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) void typed_linear_fwd_bf16_kernel(FwdArgs a) { fwd_tiles<1, SCATTER>(a); }
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void typed_linear_fwd_bf16_two_kernel(FwdArgs a) { fwd_tiles<2, false>(a); }
 
 }  // namespace
@@ -175,12 +146,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 rgnn_status_t typed_linear_fwd_bf16(const TypedLinearFwdBf16Args& x, hipStream_t st) {
     const TileList& t = *x.tiles;
     if (t.num_tiles == 0) return RGNN_OK;
-    if (!x.gather || (x.W2 && x.scatter_out) || (x.A2 && (x.W2 || x.scatter_out || !x.planes_end || !x.to))) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_fwd_bf16: gathered rows; two weights with result rows in order only");
+    if (!x.gather || (x.W2 && x.scatter_out)) RGNN_FAIL(RGNN_EUNSUPPORTED, "typed_linear_fwd_bf16: gathered rows; two weights with result rows in order only");
     const int nb = x.W2 ? 2 : 1;
-    const size_t lds = (size_t)nb * WT + (1 + nb + (x.A2 ? 1 : 0)) * TILE;
+    const size_t lds = (size_t)nb * WT + (1 + nb) * TILE;
     const FwdArgs a{t.tile_seg, t.tile_row0, t.tile_row1, t.chunk_tile, static_cast<const bf16_t*>(x.X), x.gather,
-                    {static_cast<const bf16_t*>(x.W), static_cast<const bf16_t*>(x.W2)}, x.Y, static_cast<const bf16_t*>(x.A2), x.planes_end, x.to};
-    auto kern = x.W2 ? typed_linear_fwd_bf16_two_kernel : x.A2 ? typed_linear_fwd_bf16_kernel<false, true> : x.scatter_out ? typed_linear_fwd_bf16_kernel<true, false> : typed_linear_fwd_bf16_kernel<false, false>;
+                    {static_cast<const bf16_t*>(x.W), static_cast<const bf16_t*>(x.W2)}, x.Y};
+    auto kern = x.W2 ? typed_linear_fwd_bf16_two_kernel : x.scatter_out ? typed_linear_fwd_bf16_kernel<true> : typed_linear_fwd_bf16_kernel<false>;
     RGNN_TRY(allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     KernelTimer kt(st, x.label);
     hipLaunchKernelGGL(kern, dim3(t.num_chunks), dim3(512), lds, st, a);

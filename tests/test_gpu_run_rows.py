@@ -4,7 +4,7 @@ import pytest
 
 from oracle import layers as O
 from paper_2412_04747_amd import synth
-from parity import check, TOL_F32, TOL_BF16
+from parity import check, TOL_F32
 from test_gpu_hipgraph import _capture_and_replay
 from test_gpu_workspace_bounds import _guarded, _intact
 
@@ -33,20 +33,18 @@ def _graph(seed, E):
     (32, 64, "f32", "in_degree_per_rel", "relu", True, 0), (64, 32, "f32", "none", "none", False, 32),
     (64, 64, "f32", "in_degree_per_rel", "none", True, 32), (32, 32, "f32", "none", "none", True, 0),
     (64, 64, "bf16", "in_degree_per_rel", "none", False, 0),
-    (128, 128, "f32", "in_degree_per_rel", "none", False, 0), (128, 128, "f32", "none", "relu", True, 32),
-    (128, 128, "bf16", "in_degree_per_rel", "none", False, 0), (128, 128, "bf16", "none", "relu", True, 32)])
+    (128, 128, "f32", "in_degree_per_rel", "none", False, 0), (128, 128, "f32", "none", "relu", True, 32)])
 def test_rgcn(k, d, dtype, norm, act, loop, flags, saved):
     import torch
     from paper_2412_04747_amd import binding as B
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
-    E = 260011 if d == 32 or (d == 128 and dtype == "f32") else 140003
+    E = 260011 if d in (32, 128) else 140003
     N, R, src, dst, rel, rng = _graph(31 + k + d, E)
     print(f"run rows rgcn {k}->{d} {dtype} {norm} {act} loop={loop} flags={flags} saved={saved}", flush=True)
     p = synth.rgcn_params(rng, N, R, k, d, self_loop=loop)
     tol = TOL_F32
     if dtype == "bf16":
         p = {n: v if v is None else synth.round_to_bf16(v) for n, v in p.items()}
-        tol = TOL_BF16 if d == 128 else TOL_F32
     g = Graph(N, R, src, dst, rel)
     L = RgcnLayer(g, d, norm, act, loop, dtype=dtype, flags=flags, d_in=k)
     L.load(p["X"], p["W"], p["W0"], p["dOut"])
@@ -63,7 +61,7 @@ def test_rgcn(k, d, dtype, norm, act, loop, flags, saved):
     L.fwd()
     torch.cuda.synchronize()
     # a forward that keeps nothing takes the rows per pair below 30M elements, and the backward then sums the runs' inputs itself
-    assert ("run_inputs" in B.rgnn_profile_stop()) == (saved or (dtype == "f32" and E * d >= 30000000))
+    assert ("run_inputs" in B.rgnn_profile_stop()) == (saved or E * d >= 30000000)
     want = O.rgcn_fwd(N, src, dst, rel, p["X"], p["W"], p["W0"], norm, act)
     check(L.out, want, tol, "out")
     if act != "none":                                        # (the mask from the same values on both sides)
@@ -119,6 +117,65 @@ def test_rgcn_of_few_destinations(N, R, E, dsts, k, d, loop):
     for n, v in L.grads().items():
         check(v, want[n], TOL_F32, n)
     assert "rgcn_small_fwd" in rep and rep["run_inputs"][0] == 1 and "aggregate_bwd_pair" not in rep
+    g.close()
+
+
+def _popular(d, dtype, positive):
+    """500 destinations with a run of 70 edges in each of four relations, every (source, relation) pair with one edge."""
+    rng = np.random.default_rng(8)
+    N, R = 40000, 4
+    rel, dst = (a.ravel().astype(np.int32) for a in np.indices((R, 500, 70))[:2])
+    src = np.concatenate([rng.permutation(N)[:35000] for _ in range(R)]).astype(np.int32)
+    p = synth.rgcn_params(rng, N, R, d, d, self_loop=False)
+    if positive:
+        p["X"] = np.abs(p["X"])
+    if dtype == "bf16":
+        p = {n: v if v is None else synth.round_to_bf16(v) for n, v in p.items()}
+    return N, R, src, dst, rel, p
+
+
+def test_rgcn_rows_in_bf16_stay_per_pair():
+    """Rows stored in bf16, of non-negative features: sums are fp32.  A message is rounded to bf16 by up to 2^-9 of it (1.1e-3 rms); 280 of them
+    add up to a row of out of about 0.4 times the sum of their magnitudes, so the roundings average to 2e-4 of it (a row of a run in bf16:
+    four roundings, 1e-3).  Without 1/c, the gradient row of a pair with one edge is dOut as given, and the products in dW are exact: fp32
+    sums of 35000 terms."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    N, R, src, dst, rel, p = _popular(128, "bf16", True)
+    g = Graph(N, R, src, dst, rel)
+    L = RgcnLayer(g, 128, "none", dtype="bf16")
+    L.load(p["X"], p["W"], None, p["dOut"])
+    L.fwd()
+    L.bwd()
+    torch.cuda.synchronize()
+    a = (N, src, dst, rel, p["X"], p["W"], None)
+    want = O.rgcn_bwd(*a, p["dOut"], "none")
+    for n, got, ref, tol in (("out", L.out, O.rgcn_fwd(*a, "none"), 5e-4), ("dW", L.dW, want["dW"], 1e-5)):
+        err = np.linalg.norm(got.cpu().numpy() - ref) / np.linalg.norm(ref)
+        print(f"rgcn bf16 rows per pair: {n} {err:.2e}", flush=True)
+        assert err <= tol, (n, err)
+    g.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 32), ("f32", 64), ("f32", 128)])
+def test_rgcn_of_an_infinite_feature(dtype, d):
+    """One infinite feature makes the rows of its destinations infinite, none of them NaN, and no other row."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgcnLayer
+    N, R, src, dst, rel, p = _popular(d, dtype, False)
+    if d == 32:
+        src, dst, rel = np.concatenate([src] * 2), np.concatenate([dst, dst + 500]), np.concatenate([rel] * 2)
+    u = int(src[17])
+    p["X"][u, 3] = np.inf
+    g = Graph(N, R, src, dst, rel)
+    L = RgcnLayer(g, d, dtype=dtype)
+    L.load(p["X"], p["W"])
+    L.fwd()
+    torch.cuda.synchronize()
+    hit = np.unique(dst[src == u])
+    row = torch.zeros(N, dtype=torch.bool, device="cuda")
+    row[torch.as_tensor(hit, device="cuda").long()] = True
+    assert torch.isinf(L.out[row]).all() and torch.isfinite(L.out[~row]).all()
     g.close()
 
 
@@ -227,11 +284,11 @@ def test_rgat_forward_that_keeps_nothing(n, fits):
     g.close()
 
 
-@pytest.mark.parametrize("layer,dtype", [("rgat", "f32"), ("rgcn", "f32"), ("rgcn", "bf16")])
+@pytest.mark.parametrize("layer,dtype", [("rgat", "f32"), ("rgcn", "f32")])
 def test_replays(layer, dtype):
     """Forward + backward recorded into a HIP graph: every replay leaves the bits of the eager calls."""
     from paper_2412_04747_amd.harness import Graph, RgatLayer, RgcnLayer
-    d = 128 if dtype == "bf16" else 64
+    d = 64
     N, R, src, dst, rel, rng = _graph(91, 290011)
     print(f"run rows replays {layer} {dtype}", flush=True)
     g = Graph(N, R, src, dst, rel)
