@@ -23,6 +23,8 @@
  *     `workspace` and `saved` are caller-provided device buffers of at least the
  *     sizes rgnn_workspace_bytes reports; `saved` must be kept unchanged between
  *     a forward call and its backward call, `workspace` is scratch.
+ *   - A backward call takes the descriptor of its forward; only desc.flags may differ (`saved` has one size and
+ *     one layout whatever they are), HGT's RGNN_FLAG_NO_WEIGHT_FOLDING excepted.
  *   - Inference: a forward call with saved == NULL keeps nothing for a backward
  *     call; its `workspace` must then hold fwd_workspace + saved bytes (the
  *     tensors that would have been saved become scratch).
@@ -248,8 +250,8 @@ rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, const rgnn_lay
  * On a large graph with fewer (destination, relation) runs than (source, relation) pairs, with rows in fp32 and no desc.flags but
  * RGNN_FLAG_ACCUMULATE, the layer sums the inputs of a run before the product and keeps rows per run instead of per pair (the
  * row_select and pair fields of rgnn_schedule then describe the rows per pair that a flag brings back; the kernel run_inputs in
- * the timing report tells).  `saved` then holds the sums for the backward call; with saved == NULL there, whether or not the
- * forward had one, the backward forms them again.
+ * the timing report tells).  On such a graph `saved` holds the sums for the backward call, whichever plan the forward takes, and so
+ * also with flags; with saved == NULL there, whether or not the forward had one, the backward forms them again.
  */
 rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W,
                             const void* W0, void* out, void* saved, void* workspace, void* stream);
@@ -278,8 +280,10 @@ rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc
  * of an edge is exp(l_e - m) / s and is recomputed by the backward call.
  * On a large graph with fewer (destination, relation) runs than (source, relation) pairs, with one head and no desc.flags but
  * RGNN_FLAG_ACCUMULATE, the layer takes the softmax within a run before the product and keeps rows per run instead of per pair
- * (the kernel run_inputs in the timing report tells); `saved` then has another layout, which is the library's own, and the pair
- * and row_select fields of rgnn_schedule describe the rows per pair that a flag brings back.  A forward with saved == NULL
+ * (the kernel run_inputs in the timing report tells); the pair and row_select fields of rgnn_schedule describe the rows per pair that
+ * a flag brings back.  On such a graph `saved` has another layout, which is the library's own, with flags too: a forward
+ * with one adds what the rows per run need (unless out shares memory with X: it then keeps the rows per run), and a backward with one
+ * forms its message rows again, in its workspace.  A forward with saved == NULL
  * may keep the rows per pair where one with `saved` does not: the two then agree up to rounding.
  */
 rgnn_status_t rgnn_rgat_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W,

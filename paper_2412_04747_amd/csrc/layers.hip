@@ -166,9 +166,13 @@ struct RgatBwdWs {
     float* wtp; float* wsp; float* adz; float* ds_dst; float* ds_src; float* G; float* dXp; float* A; float* U;
     float* tl_part; float* partial; float* run_partial;
     float* acc_dW; float* acc_dws; float* acc_dwt;      // RGNN_FLAG_ACCUMULATE: the parameter gradients of this call
+    float* Hs;                                          // where `saved` is laid out for rows per run: the message rows, formed again
 };
 // Rows per run (one head): Y[Q] product rows, A and lq as rgat_run_inputs leaves them (with the pieces of its cut runs), wsp = W w_s.
 // All of it lies in `saved`, so that the forward's scratch is no larger than that of the rows per pair.
+// What a graph and a descriptor without its flags say decides how a kept `saved` is laid out, so that a backward may carry other flags
+// than its forward: a forward that a flag gives rows per pair leaves there what the rows per run need as well, and such a
+// backward forms its message rows again.
 struct RgatRunSaved { float* Y; float* s_dst; float* ms; float* A; float* lq; float* wsp; float* wtp; float* partial; float* part_ms; };
 struct RgatRunBwdWs {
     float* dH; float* weight; float* rowdot; float* stat; float* dz; float* ds_dst; float* ds_src; float* A; float* U; float* tl_part; float* partial; float* a_partial;
@@ -177,13 +181,26 @@ struct RgatRunBwdWs {
 inline bool rgat_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
     return sched_rgat_run_rows(g->run_rows, d->heads, g->R, g->E, d->d_out, d->flags);
 }
-size_t carve_rgat_run_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgatRunSaved* s) {
+inline bool rgat_keeps_runs(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
+    return sched_rgat_run_rows(g->run_rows, d->heads, g->R, g->E, d->d_out, 0);
+}
+// kept: s_dst and ms lie where the rows per pair have them, with Y and A in the place of Hs as far as they fit
+size_t carve_rgat_run_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgatRunSaved* s, bool kept) {
     Carver c(base);
     const size_t Q = g->Q, M = g->num_multi_runs, rk = (size_t)g->R * d->d_in, parts = g->multi_run_items.num_partials;
-    s->Y = c.take<float>(Q * d->d_out);
+    const size_t room = kept ? (size_t)g->P * d->d_out : 0;
+    if (kept) c.take<float>(room);
     s->s_dst = c.take<float>(Q);
     s->ms = c.take<float>(2 * (size_t)g->N);
-    s->A = c.take<float>(M * d->d_in);
+    size_t used = 0;
+    auto rows = [&](size_t n) {
+        if (n > room - used) return c.take<float>(n);
+        float* const p = base ? static_cast<float*>(base) + used : nullptr;
+        used += n;
+        return p;
+    };
+    s->Y = rows(Q * d->d_out);
+    s->A = rows(M * d->d_in);
     s->lq = c.take<float>(2 * Q);
     s->wsp = c.take<float>(rk);
     s->wtp = c.take<float>(rk);
@@ -237,6 +254,7 @@ size_t carve_rgat_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
         w->att = c.take<float>((size_t)g->E);
         w->part_m = c.take<float>(parts);
         w->part_s = c.take<float>(parts);
+        w->part_ms = w->part_m;              // (rows per run: both together)
     } else {
         w->part_ms = c.take<float>(2 * parts * H);
     }
@@ -266,6 +284,7 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     w->acc_dW = acc ? c.take<float>((size_t)g->R * d->d_in * d->d_out) : nullptr;
     w->acc_dws = acc ? c.take<float>((size_t)g->R * d->d_out) : nullptr;
     w->acc_dwt = acc ? c.take<float>((size_t)g->R * d->d_out) : nullptr;
+    w->Hs = rgat_keeps_runs(g, d) ? c.take<float>((size_t)g->P * d->d_out) : nullptr;
     return c.off;
 }
 
@@ -273,9 +292,11 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // Rows per run: A[m] = the mean (sum) of the input rows of the m-th run with several edges; Hs holds a message row per run.
 struct RgcnFwdWs { void* Hs; float* partial; float* A; };
 inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, d->flags); }
+// (whatever the flags: the backward may carry others than its forward)
+inline bool rgcn_keeps_sums(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, 0); }
 size_t carve_rgcn_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, float** A) {
     Carver c(base);
-    if (rgcn_run_rows(g, d)) *A = c.take<float>((size_t)g->num_multi_runs * d->d_in);
+    if (rgcn_keeps_sums(g, d)) *A = c.take<float>((size_t)g->num_multi_runs * d->d_in);
     return c.off;
 }
 struct RgcnBwdWs { float* A; void* dPre; float* dPre32; void* G; void* dXp; float* dX0; float* tl_part; float* loop_part; float* partial; float* acc_dW; float* acc_dW0; };
@@ -286,7 +307,7 @@ size_t carve_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
     const bool runs = rgcn_run_rows(g, d);
     w->Hs = c.rows((size_t)(runs ? std::max(g->P, g->Q) : g->P) * d->d_out, rows_bf16(d));
     w->partial = c.take<float>(std::max({(size_t)g->dst_items.num_partials * d->d_out, runs ? (size_t)g->dstrun_items.num_partials * d->d_out : 0,
-                                         runs ? (size_t)g->multi_run_items.num_partials * d->d_in : 0}));
+                                         rgcn_keeps_sums(g, d) ? (size_t)g->multi_run_items.num_partials * d->d_in : 0}));
     w->A = runs ? c.take<float>((size_t)g->num_multi_runs * d->d_in) : nullptr;
     return c.off;
 }
@@ -497,7 +518,7 @@ bool rgat_run_rows_infer(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
     RgatFwdWs fw; RgatSaved ps; RgatRunSaved rs;
     const size_t f = align_up(carve_rgat_fwd(g, d, nullptr, &fw) + stage_bytes(g, RGNN_LAYER_RGAT, d, false));
     const size_t most = RGNN_STATIC_SCRATCH_BYTES;
-    return f + carve_rgat_run_saved(g, d, nullptr, &rs) <= most || f + carve_rgat_saved(g, d, nullptr, &ps) > most;
+    return f + carve_rgat_run_saved(g, d, nullptr, &rs, false) <= most || f + carve_rgat_saved(g, d, nullptr, &ps) > most;
 }
 }  // namespace
 
@@ -510,15 +531,11 @@ extern "C" rgnn_status_t rgnn_workspace_bytes(const rgnn_graph_t* g, int32_t lay
     if (layer == RGNN_LAYER_RGAT) {
         RgatFwdWs fw; RgatBwdWs bw; RgatSaved sv;
         f = carve_rgat_fwd(g, desc, nullptr, &fw);
-        if (rgat_run_rows(g, desc)) {
-            RgatRunBwdWs rb; RgatRunSaved rs;
-            b = carve_rgat_run_bwd(g, desc, nullptr, &rb);
-            s = carve_rgat_run_saved(g, desc, nullptr, &rs);
-            if (!rgat_run_rows_infer(g, desc)) s = std::max(s, carve_rgat_saved(g, desc, nullptr, &sv));
-        } else {
-            b = carve_rgat_bwd(g, desc, nullptr, &bw);
-            s = carve_rgat_saved(g, desc, nullptr, &sv);
-        }
+        RgatRunBwdWs rb; RgatRunSaved rs;
+        b = rgat_run_rows(g, desc) ? carve_rgat_run_bwd(g, desc, nullptr, &rb) : carve_rgat_bwd(g, desc, nullptr, &bw);
+        s = carve_rgat_saved(g, desc, nullptr, &sv);
+        if (rgat_keeps_runs(g, desc))
+            for (bool kept : {true, false}) s = std::max(s, carve_rgat_run_saved(g, desc, nullptr, &rs, kept));
     } else if (layer == RGNN_LAYER_RGCN) {
         RgcnFwdWs fw; RgcnBwdWs bw;
         f = carve_rgcn_fwd(g, desc, nullptr, &fw);
@@ -589,7 +606,7 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     // What the backward reads is left in `saved` whichever plan the forward takes: the backward cannot tell.
     const bool runs = rgcn_run_rows(g, desc) && (saved || sched_run_rows_infer(g->E, D));
     float* A = w.A;
-    if (runs && saved) {
+    if (saved && rgcn_keeps_sums(g, desc)) {
         (void)carve_rgcn_saved(g, desc, saved, &A);
         RGNN_TRY(rgcn_run_inputs(g, desc, X32, A, w.partial, st));
     }
@@ -773,7 +790,7 @@ extern "C" rgnn_status_t rgnn_rgat_fwd_static(const rgnn_graph_t* g, const rgnn_
     RGNN_TRY(rgnn_workspace_bytes(g, RGNN_LAYER_RGAT, desc, &need, nullptr, nullptr));
     if (!saved) {                                // inference: the would-be saved tensors are scratch too
         RgatSaved ps; RgatRunSaved rs;
-        need = align_up(need) + (rgat_run_rows_infer(g, desc) ? carve_rgat_run_saved(g, desc, nullptr, &rs) : carve_rgat_saved(g, desc, nullptr, &ps));
+        need = align_up(need) + (rgat_run_rows_infer(g, desc) ? carve_rgat_run_saved(g, desc, nullptr, &rs, false) : carve_rgat_saved(g, desc, nullptr, &ps));
     }
     if (need > (size_t)RGNN_STATIC_SCRATCH_BYTES)
         RGNN_FAIL(RGNN_EWORKSPACE, "rgnn_rgat_fwd_static: this call needs %zu bytes of scratch, the static buffer holds %zu",
@@ -783,6 +800,9 @@ extern "C" rgnn_status_t rgnn_rgat_fwd_static(const rgnn_graph_t* g, const rgnn_
     return rgat_fwd_impl(g, desc, X, W, w_s, w_t, out, saved, ws, stream);
 }
 
+static rgnn_status_t rgat_pair_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const float* Xf, const float* Wf, const float* w_s,
+                                   const float* w_t, void* out, void* saved, const RgatFwdWs& w, hipStream_t st);
+
 static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W, const void* w_s,
                                    const void* w_t, void* out, void* saved, void* workspace, void* stream) {
     RGNN_TRY(check_desc(g, desc, RGNN_LAYER_RGAT));
@@ -791,9 +811,9 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     if (!workspace) RGNN_FAIL(RGNN_EWORKSPACE, "workspace is NULL");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int D = desc->d_out, K = desc->d_in;
-    RgatFwdWs w; RgatSaved sv;
+    RgatFwdWs w; RgatRunSaved rs;
     const size_t carved = carve_rgat_fwd(g, desc, workspace, &w);
-    const bool runs = saved ? rgat_run_rows(g, desc) : rgat_run_rows_infer(g, desc);
+    const bool kept = saved && rgat_keeps_runs(g, desc);
     saved = saved_or_scratch(g, RGNN_LAYER_RGAT, desc, saved, workspace, carved);
     Bf16Stage stg(workspace, carved, desc->dtype == RGNN_BF16, st);
     X = stg.in(X, (size_t)g->N * K);
@@ -801,11 +821,12 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     w_s = stg.in(w_s, (size_t)g->R * D);
     w_t = stg.in(w_t, (size_t)g->R * D);
     RGNN_TRY(stg.status);
-    const float *Xf = static_cast<const float*>(X), *Wf = static_cast<const float*>(W);
+    const float *Xf = static_cast<const float*>(X), *Wf = static_cast<const float*>(W), *ws = static_cast<const float*>(w_s), *wt = static_cast<const float*>(w_t);
+    // (with an out that shares memory with X, what is kept cannot be formed behind the rows per pair: then no flag brings those back)
+    const bool runs = kept ? rgat_run_rows(g, desc) || overlap(Xf, (size_t)g->N * K * sizeof(float), out, (size_t)g->N * D * sizeof(float))
+                           : rgat_run_rows_infer(g, desc);
+    if (runs || kept) carve_rgat_run_saved(g, desc, saved, &rs, kept);
     if (runs) {
-        RgatRunSaved rs;
-        carve_rgat_run_saved(g, desc, saved, &rs);
-        const float *ws = static_cast<const float*>(w_s), *wt = static_cast<const float*>(w_t);
         // 1. wsp = W w_s, wtp = W w_t, and the destination halves of the logits
         RGNN_TRY(fold_weight(fold_args(g->R, K, D, 1, Wf, ws, rs.wsp, wt, rs.wtp), st));
         RGNN_TRY(rgat_run_logit(g, K, Xf, rs.wtp, rs.s_dst, st));
@@ -817,6 +838,19 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
         // 4. per destination over its runs: softmax and weighted sum
         return rgat_run_aggregate(g, D, rs.Y, ws, rs.s_dst, desc->slope, rs.lq, static_cast<float*>(out), rs.ms, w.partial, w.part_ms, st);
     }
+    RGNN_TRY(rgat_pair_fwd(g, desc, Xf, Wf, ws, wt, out, saved, w, st));
+    if (!kept) return RGNN_OK;
+    // what rows per run need beside s_dst and (m, s), in the place of Hs and behind
+    RGNN_TRY(fold_weight(fold_args(g->R, K, D, 1, Wf, ws, rs.wsp, wt, rs.wtp), st));
+    RGNN_TRY(rgat_run_inputs(g, K, Xf, rs.wsp, rs.s_dst, desc->slope, rs.A, rs.lq, rs.partial, rs.part_ms, st));
+    return rgat_single_logits(g, K, Xf, rs.wsp, rs.s_dst, desc->slope, rs.lq, st);
+}
+
+// Rows per pair; X .. w_t in fp32.
+static rgnn_status_t rgat_pair_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const float* Xf, const float* Wf, const float* w_s,
+                                   const float* w_t, void* out, void* saved, const RgatFwdWs& w, hipStream_t st) {
+    const int D = desc->d_out, K = desc->d_in;
+    RgatSaved sv;
     carve_rgat_saved(g, desc, saved, &sv);
     const bool fused = rgat_fused(desc);
     // 1. compact messages: Hs[p] = X[pair_src[p]] W[r]
@@ -824,9 +858,9 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
     TypedLinearArgs a{};
     a.sign_matters = 1;
     a.tiles = pair_chunks(g, D).f32; a.X = Xf; a.gather = g->idx[RGNN_IDX_PAIR_SRC]; a.W = Wf; a.Y = sv.Hs;
-    if (!fused) { a.vec = static_cast<const float*>(w_s); a.s_out = w.s_src; }
+    if (!fused) { a.vec = w_s; a.s_out = w.s_src; }
     const int H = desc->heads;
-    const FoldArgs fold = fold_args(g->R, K, D, H, Wf, static_cast<const float*>(w_t), w.wtp);      // step 2; in the same launch if there is one
+    const FoldArgs fold = fold_args(g->R, K, D, H, Wf, w_t, w.wtp);      // step 2; in the same launch if there is one
     // At width 128 the product's LDS leaves a compute unit one workgroup of folds at a time: with many relations they are faster in a
     // launch of their own, unless uneven chunks leave compute units idle.  Forward, us, shared / apart, equal frequencies: 200 relations
     // 76 / 76 at 100k edges, 800 111 / 104, 2000 192 / 152, 566 / 538 at 1M; Zipf 1.1: 400 55 / 49 at 10k, 97 / 102 at 100k, 2000 803 / 824 at 1M.
@@ -847,8 +881,7 @@ static rgnn_status_t rgat_fwd_impl(const rgnn_graph_t* g, const rgnn_layer_desc_
                           w.partial, st, 0, "aggregate_fwd", "aggregate_fwd.combine");
     }
     // 3. one walk per destination: logit from the gathered row, running-maximum softmax, weighted sum
-    return rgat_aggregate_fwd(g, D, H, sv.Hs, static_cast<const float*>(w_s), sv.s_dst, desc->slope, static_cast<float*>(out),
-                              sv.ms, w.partial, w.part_ms, st);
+    return rgat_aggregate_fwd(g, D, H, sv.Hs, w_s, sv.s_dst, desc->slope, static_cast<float*>(out), sv.ms, w.partial, w.part_ms, st);
 }
 
 // Rows per run; X .. dOut in fp32.
@@ -857,7 +890,7 @@ static rgnn_status_t rgat_run_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t
                                   const RgatRunBwdWs& w, hipStream_t st) {
     const int D = desc->d_out, K = desc->d_in;
     RgatRunSaved sv;
-    carve_rgat_run_saved(g, desc, const_cast<void*>(saved), &sv);
+    carve_rgat_run_saved(g, desc, const_cast<void*>(saved), &sv, true);
     GradAcc ga;
     dW = ga.route(w.acc_dW, dW, (size_t)g->R * K * D);
     dw_s = ga.route(w.acc_dws, dw_s, (size_t)g->R * D);
@@ -915,6 +948,11 @@ extern "C" rgnn_status_t rgnn_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     carve_rgat_saved(g, desc, const_cast<void*>(saved), &sv);
     const float* Xf = static_cast<const float*>(X);
     const float* Wf = static_cast<const float*>(W);
+    if (rgat_keeps_runs(g, desc)) {              // (a flag asked for rows per pair)
+        TypedLinearArgs a{};
+        a.tiles = pair_chunks(g, D).f32; a.X = Xf; a.gather = g->idx[RGNN_IDX_PAIR_SRC]; a.W = Wf; a.Y = sv.Hs = w.Hs; a.sign_matters = 1;
+        RGNN_TRY(typed_linear_fwd(K, D, a, st));
+    }
     const float* dO = static_cast<const float*>(dOut);
     const bool acc = grads_accumulate(desc);
     GradAcc ga;

@@ -64,6 +64,31 @@ __global__ __launch_bounds__(kWalkThreads) void rgat_run_logit_kernel(Items it, 
     }
 }
 
+// lq[q] = (leakyrelu(X[src] . wsp[r] + s_dst[q]), 1) of the runs with one edge; four runs at a time.
+template <int D>
+__global__ __launch_bounds__(256) void rgat_single_logits_kernel(int Q, const int32_t* __restrict__ run_ptr, const int32_t* __restrict__ run_rel,
+                                                                 const int32_t* __restrict__ in_src, const float* __restrict__ X,
+                                                                 const float* __restrict__ wsp, const float* __restrict__ s_dst, float slope,
+                                                                 float2* __restrict__ lq) {
+    constexpr int LPR = D / 4;
+    const int64_t q0 = ((int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR) * 4;
+    const int c = threadIdx.x % LPR;
+    if (q0 >= Q) return;
+    float p[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t q = min(q0 + u, (int64_t)Q - 1);
+        p[u] = dot4(*reinterpret_cast<const float4*>(X + (size_t)in_src[run_ptr[q]] * D + c * 4),
+                    *reinterpret_cast<const float4*>(wsp + (size_t)run_rel[q] * D + c * 4));
+    }
+    const float s = group_sum4<LPR>(p, c);
+    const int64_t q = q0 + c;                              // lane c < 4 has run c's
+    if (c < 4 && q < Q && run_ptr[q + 1] - run_ptr[q] == 1) {
+        const float z = s + s_dst[q];
+        lq[q] = make_float2(z > 0.f ? z : slope * z, 1.f);
+    }
+}
+
 // A run's weight in its destination, for the weight gradient.  A lane per run.
 __global__ __launch_bounds__(256) void rgat_run_weights_kernel(int Q, const int32_t* __restrict__ run_dst, const float2* __restrict__ ms,
                                                                const float2* __restrict__ lq, float* __restrict__ weight) {
@@ -337,6 +362,16 @@ rgnn_status_t rgat_run_logit(const rgnn_graph* g, int K, const float* X, const f
     KernelTimer kt(st, "run_logit");
     if (sched_ws_in_lds(g->R, K)) RGNN_DISPATCH_D(K, return (launch_run_logit<DD, true>(g, X, wtp, s_dst, st)));
     else RGNN_DISPATCH_D(K, return (launch_run_logit<DD, false>(g, X, wtp, s_dst, st)));
+}
+
+rgnn_status_t rgat_single_logits(const rgnn_graph* g, int K, const float* X, const float* wsp, const float* s_dst, float slope, float* lq, hipStream_t st) {
+    if (g->Q == 0) return RGNN_OK;
+    KernelTimer kt(st, "single_logits");
+    RGNN_DISPATCH_D(K, hipLaunchKernelGGL(rgat_single_logits_kernel<DD>, dim3(blocks_for(((size_t)g->Q + 3) / 4 * (DD / 4), 256)), dim3(256), 0, st, (int)g->Q,
+                                          g->idx[RGNN_IDX_RUN_PTR], g->idx[RGNN_IDX_RUN_REL], g->idx[RGNN_IDX_IN_SRC], X, wsp, s_dst, slope,
+                                          reinterpret_cast<float2*>(lq)));
+    RGNN_CHECK_LAUNCH();
+    return RGNN_OK;
 }
 
 rgnn_status_t rgat_run_weights(const rgnn_graph* g, const float* ms, const float* lq, float* weight, hipStream_t st) {

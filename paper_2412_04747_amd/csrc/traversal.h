@@ -39,6 +39,8 @@ rgnn_status_t rgat_edge_dot_bwd(const rgnn_graph* g, int D, int H, const float* 
                                 const float* ms, const float* dOut, const float* out, float slope, float* adz, float* G,
                                 float* ds_src, float* dsy, hipStream_t st);
 // Rows per run, one head:
+//   lq[q] = (logit, 1) of the runs with one edge, where the walk over the runs does not write it
+rgnn_status_t rgat_single_logits(const rgnn_graph* g, int K, const float* X, const float* wsp, const float* s_dst, float slope, float* lq, hipStream_t st);
 //   the inputs of the m-th run with several edges, A[m] = sum of X[src_e] weighted by their softmax within the run, from the logits
 //   X[src_e] . wsp[r] + s_dst[q]; lq[q] = (max logit, sum of exp(logit - max)).  partial / part_ms: pieces of runs that are cut
 rgnn_status_t rgat_run_inputs(const rgnn_graph* g, int K, const float* X, const float* wsp, const float* s_dst, float slope, float* A, float* lq,

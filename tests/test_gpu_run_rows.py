@@ -284,6 +284,60 @@ def test_rgat_forward_that_keeps_nothing(n, fits):
     g.close()
 
 
+FLAGS = [
+    ("rgat", 64, 64, 16, 0), ("rgat", 64, 64, 1, 0), ("rgat", 64, 64, 4, 0), ("rgat", 32, 64, 2, 32), ("rgat", 128, 128, 16, 32), ("rgat", 64, 64, 0, 4),
+    ("rgat", 128, 128, 0, 4), ("rgat", 64, 32, 0, 2), ("rgat", 64, 64, 16, 4), ("rgat", 64, 64, 4, 4 | 32), ("rgcn", 64, 64, 2, 0), ("rgcn", 32, 64, 4, 0),
+    ("rgcn", 64, 64, 0, 4)]
+
+
+@pytest.mark.parametrize("layer,k,d,forward,backward,in_place", [(*c, False) for c in FLAGS] + [(*c, True) for c in FLAGS if c[1] == c[2]])
+def test_flags_of_one_call(layer, k, d, forward, backward, in_place):
+    """A backward need not carry the flags of its forward, in one `saved` that is as large for both, also where the forward writes out over X."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer, RgcnLayer
+    N, R, src, dst, rel, rng = _graph(5 + k + d, {32: 810007, 64: 290011, 128: 300007}[min(k, d)])
+    print(f"run rows {layer} {k}->{d} flags {forward} then {backward} in_place={in_place}", flush=True)
+    g = Graph(N, R, src, dst, rel)
+    if layer == "rgat":
+        p = synth.rgat_params(rng, N, R, k, d)
+        a = (N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"])
+        want, wg = O.rgat_fwd(*a), O.rgat_bwd(*a, p["dOut"])
+        which, make, names = B.RGNN_LAYER_RGAT, RgatLayer, ("X", "W", "w_s", "w_t", "dOut")
+    else:
+        p = synth.rgcn_params(rng, N, R, k, d, self_loop=False)
+        a = (N, src, dst, rel, p["X"], p["W"], None)
+        want, wg = O.rgcn_fwd(*a), O.rgcn_bwd(*a, p["dOut"])
+        which, make, names = B.RGNN_LAYER_RGCN, RgcnLayer, ("X", "W", "W0", "dOut")
+    F, G = make(g, d, flags=forward, d_in=k), make(g, d, flags=backward, d_in=k)
+    (f, _, s), (_, b, s2) = (B.rgnn_workspace_bytes(g.handle, which, L.desc) for L in (F, G))
+    assert s == s2 > 0
+    guards = []
+    F.saved, F.ws, G.ws = _area(guards, s), _area(guards, f), _area(guards, b)
+    F.saved.fill_(0xFF)
+    for L in (F, G):
+        L.load(*[p[n] for n in names])
+    if in_place:
+        F.out = F.X
+    B.rgnn_profile_start()
+    F.fwd()
+    torch.cuda.synchronize()
+    rep = B.rgnn_profile_stop()
+    assert "run_inputs" in rep and ("single_logits" in rep) == (layer == "rgat" and forward & ~32 > 0 and not in_place)
+    check(F.out, want, TOL_F32, "out")
+    G.out, G.saved = F.out, F.saved
+    base = 1.0 if backward & 32 else 0.0
+    for v in G.grads().values():
+        v.fill_(1.0)
+    G.bwd()
+    torch.cuda.synchronize()
+    for n, v in G.grads().items():
+        check(v - base, wg[n], TOL_F32, n)
+    for big in guards:
+        _intact(big, "a buffer")
+    g.close()
+
+
 @pytest.mark.parametrize("layer,dtype", [("rgat", "f32"), ("rgcn", "f32")])
 def test_replays(layer, dtype):
     """Forward + backward recorded into a HIP graph: every replay leaves the bits of the eager calls."""
