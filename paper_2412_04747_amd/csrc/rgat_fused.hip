@@ -84,6 +84,11 @@ __device__ __forceinline__ float4 walk_row(const float* p) { return MODE == kRun
 template <int MODE, int D>
 __device__ __forceinline__ const float* row_at(const float* rows, int i) { return rows + (size_t)(MODE == kRuns ? i & 0x7FFFFFFF : i) * D; }
 
+// What a softmax subtracts.  A run whose logits are all minus infinity weighs nothing in its destination, as its edges would: it gets the
+// zero row and (-inf, 0).
+template <int MODE>
+__device__ __forceinline__ float run_base(float m) { return MODE == kRunInputs ? softmax_base(m) : m; }
+
 // ---------------------------------------------------------------- forward
 
 // kRuns: logit and weight of a run with several edges in place of its destination half
@@ -156,8 +161,9 @@ __device__ __forceinline__ void fwd_general(const FusedArgs& a, const float* ws_
                     if (c < 4 && k + c < cend && mpr >= 0) a.lq[jc + k + c] = make_float2(mine, 1.f);
                 }
                 const float mn = fmaxf(fmaxf(m, fmaxf(l[0], l[1])), fmaxf(l[2], l[3]));
-                const float sc = __expf(m - mn);              // 0 in the first batch (m = -inf), 1 while the maximum stands
-                float p0 = __expf(l[0] - mn), p1 = __expf(l[1] - mn), p2 = __expf(l[2] - mn), p3 = __expf(l[3] - mn);
+                const float base = run_base<MODE>(mn);
+                const float sc = __expf(m - base);            // 0 in the first batch (m = -inf), 1 while the maximum stands
+                float p0 = __expf(l[0] - base), p1 = __expf(l[1] - base), p2 = __expf(l[2] - base), p3 = __expf(l[3] - base);
                 if (MODE == kRuns) {
                     p0 *= group_lane<LPR>(cw, k); p1 *= group_lane<LPR>(cw, k + 1);
                     p2 *= group_lane<LPR>(cw, k + 2); p3 *= group_lane<LPR>(cw, k + 3);
@@ -245,13 +251,13 @@ __device__ __forceinline__ void fwd_short(const FusedArgs& a, const float* ws_ld
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int u = 0; u < kShortLen; ++u) {
-            float p = __expf(l[u] - m);
+            float p = __expf(l[u] - run_base<MODE>(m));
             if (MODE == kRuns) p *= rw[q][u];
             s += p;
             fma4(acc, p, h[q][u]);
         }
         if (i0 + q < a.short_n) {
-            const float inv = 1.f / s;
+            const float inv = MODE != kRunInputs || s > 0.f ? 1.f / s : 0.f;
             *reinterpret_cast<float4*>(a.out + (size_t)orow[q] * D + c * 4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
             if (MODE == kRunInputs) {
                 if (c == 0) a.lq[rn[q][0]] = make_float2(m, s);

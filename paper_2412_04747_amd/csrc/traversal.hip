@@ -720,7 +720,8 @@ __global__ __launch_bounds__(256) void combine_softmax_kernel(const int32_t* __r
             S += w * q.y;
             t[0] += w * r.x; t[1] += w * r.y; t[2] += w * r.z; t[3] += w * r.w;
         }
-        const float inv = 1.f / S * (1.f / share) * (1.f / pow2_share(piece_len));
+        // (ms_row: the runs of RGAT, of which one without weight gets the zero row)
+        const float inv = ms_row && S == 0.f ? 0.f : 1.f / S * (1.f / share) * (1.f / pow2_share(piece_len));
         const size_t v = (size_t)split_row[s];
 #pragma unroll
         for (int q = 0; q < 4; ++q) t[q] *= inv;

@@ -249,6 +249,39 @@ def test_rgat(k, d, dtype, flags, spread):
     g.close()
 
 
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_rgat_of_logits_of_minus_infinity(d):
+    """A relation whose destination halves overflow to minus infinity, in runs of every length: its edges weigh nothing, and nothing is NaN
+    (in 64 bits the halves are -1e39, and the weights 0)."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    N, R, src, dst, rel, rng = _graph(3 + d, {32: 810007, 64: 290011, 128: 300007}[d])
+    masked = 10
+    other = np.bincount(dst[rel != masked], minlength=N) > 0
+    rel[(rel == masked) & ~other[dst]] = 0                   # (every destination has another edge)
+    p = synth.rgat_params(rng, N, R, d, d)
+    p["X"][:, 0] = 10
+    p["W"][masked][:, 0] = np.eye(d)[0]
+    p["w_t"][masked] = 0
+    p["w_t"][masked][0] = -1e38
+    print(f"run rows rgat minus infinity d={d}: runs of {np.unique(np.unique(dst[rel == masked], return_counts=True)[1])[[0, 1, -1]]} edges", flush=True)
+    g = Graph(N, R, src, dst, rel)
+    L = RgatLayer(g, d)
+    L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    B.rgnn_profile_start()
+    L.fwd()
+    L.bwd()
+    torch.cuda.synchronize()
+    assert "run_inputs" in B.rgnn_profile_stop()
+    a = (N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"])
+    check(L.out, O.rgat_fwd(*a), TOL_F32, "out")
+    want = O.rgat_bwd(*a, p["dOut"])
+    for n, v in L.grads().items():
+        check(v, want[n], TOL_F32, n)
+    g.close()
+
+
 @pytest.mark.parametrize("n,fits", [(121, True), (160, False)])
 def test_rgat_forward_that_keeps_nothing(n, fits):
     """Runs of nine edges.  Rows per run, from a workspace and from the static scratch; where that holds the rows per pair only, those from both."""
