@@ -909,10 +909,16 @@ static rgnn_status_t rgat_run_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t
     // 2. what the edges of a run need
     RGNN_TRY(rgat_run_stat(g, desc->slope, w.rowdot, w.weight, sv.ms, sv.lq, sv.s_dst, w.stat, w.ds_dst, st));
     // 3. per source over its edges: dz, and dX without the destination halves
-    RGNN_TRY(rgat_source_walk(g, K, X, w.dH, sv.wsp, w.stat, desc->slope, w.dz, dX, grads_accumulate(desc), w.partial, st));
+    //    (with a dX that shares memory with X, which step 4 reads, dz alone, and the walk again behind that)
+    const bool in_place = overlap(X, (size_t)g->N * K * sizeof(float), dX, (size_t)g->N * K * sizeof(float));
+    auto walk = [&](float* to) {
+        return rgat_source_walk(g, K, X, w.dH, sv.wsp, w.stat, desc->slope, w.dz, to, grads_accumulate(desc), w.partial, st);
+    };
+    RGNN_TRY(walk(in_place ? nullptr : dX));
     // 4. sums of dz over the runs with several edges;  A[r] = sum over r's pairs of ds_src X[src], U[r] = sum over r's runs of ds_dst X[dst]
     RGNN_TRY(segment_scalar_sum((int)g->Q, g->idx[RGNN_IDX_RUN_PTR], g->long_runs, g->in_spos, w.dz, 1, 0, w.ds_dst, st, "ds_dst_sum", 2));
     RGNN_TRY(rgat_block_sums(g, K, X, w.dz, w.ds_src, w.ds_dst, w.A, w.a_partial, w.U, w.u_partial, st));
+    if (in_place) RGNN_TRY(walk(dX));
     sums.pieces = pieces(g->pair_blocks, w.a_partial, w.A);
     sums.pieces2 = pieces(g->run_blocks, w.u_partial, w.U);
     RGNN_TRY(sums.launch(st));

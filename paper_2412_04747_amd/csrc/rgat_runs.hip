@@ -243,7 +243,7 @@ struct SourceArgs {
     float slope;
     int R, acc;
     float* dz;                // [E] by source
-    float* dX;                // [N][D]
+    float* dX;                // [N][D], or NULL: dz alone
     float* partial;
 };
 
@@ -316,6 +316,7 @@ __device__ __forceinline__ void source_item(const SourceArgs& a, const float* ws
     }
     fma4(acc0, 1.f, acc1);
     if (slot < 0) {
+        if (!a.dX) return;
         float4* o = reinterpret_cast<float4*>(a.dX + u * D + c * 4);
         if (a.acc) fma4(acc0, 1.f, *o);
         *o = acc0;
@@ -430,6 +431,7 @@ rgnn_status_t rgat_source_walk(const rgnn_graph* g, int K, const float* X, const
         if (sched_ws_in_lds(g->R, K)) RGNN_DISPATCH_D(K, RGNN_TRY((launch_source_walk<DD, true>(g, a, st))));
         else RGNN_DISPATCH_D(K, RGNN_TRY((launch_source_walk<DD, false>(g, a, st))));
     }
+    if (!dX) return RGNN_OK;
     return combine_partials(L, K, partial, dX, 0, "source_walk.combine", st, nullptr, 1, 1, 0, acc ? dX : nullptr);
 }
 

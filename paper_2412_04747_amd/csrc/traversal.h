@@ -57,7 +57,8 @@ rgnn_status_t rgat_run_logit(const rgnn_graph* g, int K, const float* X, const f
 rgnn_status_t rgat_run_weights(const rgnn_graph* g, const float* ms, const float* lq, float* weight, hipStream_t st);
 rgnn_status_t rgat_run_stat(const rgnn_graph* g, float slope, const float* rowdot, const float* weight, const float* ms, const float* lq, const float* s_dst,
                             float* stat, float* ds_dst, hipStream_t st);
-//   per source u, over its edges in the order of src_items: dz[i], and dX[u] = sum att_e dH[row of e's run] + dz_e wsp[r_e] (+ dX[u], acc),
+//   per source u, over its edges in the order of src_items: dz[i], and dX[u] = sum att_e dH[row of e's run] + dz_e wsp[r_e] (+ dX[u], acc;
+//   dX NULL: dz alone),
 //   with dH = dOut W^T per run
 rgnn_status_t rgat_source_walk(const rgnn_graph* g, int K, const float* X, const float* dH, const float* wsp, const float* stat, float slope, float* dz,
                                float* dX, bool acc, float* partial, hipStream_t st);

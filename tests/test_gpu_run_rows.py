@@ -282,6 +282,40 @@ def test_rgat_of_logits_of_minus_infinity(d):
     g.close()
 
 
+@pytest.mark.parametrize("layer,d,flags", [("rgat", 64, 0), ("rgat", 64, 32), ("rgat", 128, 0), ("rgcn", 64, 0)])
+def test_input_gradient_over_the_input(layer, d, flags):
+    """dX written over X: the same bits as in a buffer of its own (with flags: added to what that holds)."""
+    import torch
+    from paper_2412_04747_amd.harness import Graph, RgatLayer, RgcnLayer
+    N, R, src, dst, rel, rng = _graph(71 + d, 300007)
+    print(f"run rows {layer} dX over X d={d} flags={flags}", flush=True)
+    g = Graph(N, R, src, dst, rel)
+    if layer == "rgat":
+        p = synth.rgat_params(rng, N, R, d, d)
+        L = RgatLayer(g, d, flags=flags)
+        L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    else:
+        p = synth.rgcn_params(rng, N, R, d, d, self_loop=True)
+        L = RgcnLayer(g, d, self_loop=True, flags=flags)
+        L.load(p["X"], p["W"], p["W0"], p["dOut"])
+    L.fwd()
+    for v in L.grads().values():
+        v.zero_()
+    L.dX.copy_(L.X)
+    L.bwd()
+    torch.cuda.synchronize()
+    want = {n: v.clone() for n, v in L.grads().items()}
+    L.dX = L.X
+    for n, v in L.grads().items():
+        if n != "dX":
+            v.zero_()
+    L.bwd()
+    torch.cuda.synchronize()
+    for n, v in L.grads().items():
+        assert torch.equal(v, want[n]), n
+    g.close()
+
+
 @pytest.mark.parametrize("n,fits", [(121, True), (160, False)])
 def test_rgat_forward_that_keeps_nothing(n, fits):
     """Runs of nine edges.  Rows per run, from a workspace and from the static scratch; where that holds the rows per pair only, those from both."""
