@@ -98,10 +98,10 @@ __global__ __launch_bounds__(256) void rgat_run_weights_kernel(int Q, const int3
     weight[q] = __expf(l.x - st.x) * l.y * (1.f / st.y);
 }
 
-// What the walk below needs of an edge's run, and ds_dst of the runs with one edge, whose dz follows from the same numbers.
-// gbar_v = dOut[v] . out[v] is taken as the sum over v's runs of rowdot = weight dH_q . A_q, which the typed linear left: so it has the
-// roundings of the walk's g_e, and an edge that is alone in its destination gets dz = 0 exactly, as with rows per pair (with dOut . out the
-// error of dw_s against 64 bits was 4.7e-7 at 1.5M edges; so 2.9e-7, with the rows per pair 3.0e-7).  Eight lanes per destination.
+// What the walk below needs of an edge's run: of a run with one edge its logit and dz, which is ds_dst as well, of the others s_dst and gbar.
+// gbar_v = dOut[v] . out[v] is taken as the sum over v's runs of rowdot = weight dH_q . A_q, which the typed linear left (with dOut . out the
+// error of dw_s against 64 bits was 4.7e-7 at 1.5M edges; so 2.9e-7, with the rows per pair 3.0e-7).  An edge that is alone in its destination
+// so gets dz = 0 exactly, as with rows per pair.  Eight lanes per destination.
 __global__ __launch_bounds__(256) void rgat_run_stat_kernel(int N, float slope, const int32_t* __restrict__ dst_run_ptr, const int32_t* __restrict__ run_ptr,
                                                             const float* __restrict__ rowdot, const float* __restrict__ weight,
                                                             const float2* __restrict__ ms, const float2* __restrict__ lq,
@@ -139,8 +139,9 @@ __global__ __launch_bounds__(256) void rgat_run_stat_kernel(int N, float slope, 
                 dot[u] = rowdot[q]; w[u] = weight[q]; l[u] = lq[q]; sd[u] = s_dst[q];
                 one[u] = run_ptr[q + 1] - run_ptr[q] == 1;
             }
-            stat[q] = make_float4(one[u] ? l[u].x : sd[u], st[u].x, inv, gbar[u]);
-            if (one[u]) ds_dst[q] = (dot[u] - w[u] * gbar[u]) * (l[u].x > 0.f ? 1.f : slope);
+            const float dz = (dot[u] - w[u] * gbar[u]) * (l[u].x > 0.f ? 1.f : slope);
+            stat[q] = make_float4(one[u] ? l[u].x : sd[u], st[u].x, inv, one[u] ? dz : gbar[u]);
+            if (one[u]) ds_dst[q] = dz;
         }
     }
 }
@@ -292,9 +293,9 @@ __device__ __forceinline__ void source_item(const SourceArgs& a, const float* ws
                 const float g = group_sum4<LPR>(pg, c);
                 // the lanes of quad k / 4 have their edges' sums, and form what follows from them
                 float l = z > 0.f ? z : a.slope * z;
-                l = crun < 0 ? cst.x : l;                  // the only edge of its run: the forward's logit
+                l = crun < 0 ? cst.x : l;                  // the only edge of its run: the forward's logit, and dz
                 const float al = __expf(l - cst.y) * cst.z;
-                const float dz = al * (g - cst.w) * (l > 0.f ? 1.f : a.slope);
+                const float dz = crun < 0 ? cst.w : al * (g - cst.w) * (l > 0.f ? 1.f : a.slope);
                 mine = c >> 2 == k >> 2 ? dz : mine;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {

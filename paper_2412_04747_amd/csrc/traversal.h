@@ -52,8 +52,8 @@ rgnn_status_t rgat_run_aggregate(const rgnn_graph* g, int D, const float* Y, con
 //   the destination halves of the logits, s_dst[q] = X[dst_q] . wtp[r]
 rgnn_status_t rgat_run_logit(const rgnn_graph* g, int K, const float* X, const float* wtp, float* s_dst, hipStream_t st);
 //   backward (rgat_runs.hip): weight[q] = what A[q] (or the source's row) counts in out[dst_q];
-//   stat[q] = (s_dst[q] or the logit of the run's only edge, max of v, 1 / sum of v, dOut[v] . out[v] = sum over v's runs of rowdot), and
-//   ds_dst of the runs with one edge
+//   stat[q] = (s_dst[q], max of v, 1 / sum of v, dOut[v] . out[v] = sum over v's runs of rowdot), of a run with one edge (logit, max, 1 / sum, dz),
+//   and ds_dst of those
 rgnn_status_t rgat_run_weights(const rgnn_graph* g, const float* ms, const float* lq, float* weight, hipStream_t st);
 rgnn_status_t rgat_run_stat(const rgnn_graph* g, float slope, const float* rowdot, const float* weight, const float* ms, const float* lq, const float* s_dst,
                             float* stat, float* ds_dst, hipStream_t st);

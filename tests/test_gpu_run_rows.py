@@ -282,6 +282,31 @@ def test_rgat_of_logits_of_minus_infinity(d):
     g.close()
 
 
+@pytest.mark.parametrize("d,flags", [(32, 0), (64, 0), (128, 0), (128, 4)])
+def test_rgat_edges_alone_in_their_destination(d, flags):
+    """Their attention weight is 1 whatever the logit, so its gradient is 0, exactly: as much as a relation of such edges only has in dw_s and
+    dw_t, and its destinations, which are nobody's sources, in dX.  (flags: rows per pair)"""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    N, R, src, dst, rel, rng = _graph(13 + d, {32: 850007, 64: 290011, 128: 300007}[d])
+    src = np.concatenate([src, rng.integers(0, N, 500)]).astype(np.int32)
+    dst, rel = (np.concatenate(x).astype(np.int32) for x in ((dst, N + np.arange(500)), (rel, np.full(500, R))))
+    p = synth.rgat_params(rng, N + 500, R + 1, d, d)
+    print(f"run rows rgat edges alone in their destination d={d} flags={flags}", flush=True)
+    g = Graph(N + 500, R + 1, src, dst, rel)
+    L = RgatLayer(g, d, flags=flags)
+    L.load(p["X"], p["W"], p["w_s"], p["w_t"], p["dOut"])
+    L.fwd()
+    B.rgnn_profile_start()
+    L.bwd()
+    torch.cuda.synchronize()
+    assert ("source_walk" in B.rgnn_profile_stop()) == (flags == 0)
+    assert not L.dw_s[R].any() and not L.dw_t[R].any() and not L.dX[N:].any()
+    assert L.dw_s[:11].abs().max(1).values.min() > 0 and L.dX[:N].any()
+    g.close()
+
+
 @pytest.mark.parametrize("layer,d,flags", [("rgat", 64, 0), ("rgat", 64, 32), ("rgat", 128, 0), ("rgcn", 64, 0)])
 def test_input_gradient_over_the_input(layer, d, flags):
     """dX written over X: the same bits as in a buffer of its own (with flags: added to what that holds)."""
