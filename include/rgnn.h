@@ -26,8 +26,9 @@
  *   - A backward call takes the descriptor of its forward; only desc.flags may differ (`saved` has one size and
  *     one layout whatever they are), HGT's RGNN_FLAG_NO_WEIGHT_FOLDING excepted.
  *   - Inference: a forward call with saved == NULL keeps nothing for a backward
- *     call; its `workspace` must then hold fwd_workspace + saved bytes (the
- *     tensors that would have been saved become scratch).
+ *     call; its `workspace` must then hold fwd_workspace (rounded up to 256) + saved
+ *     bytes (the tensors that would have been saved become scratch; RGCN's
+ *     fwd_workspace counts them).
  *   - Weights are stored [type][d_in][d_out] so that y = x W (row vector times
  *     matrix), as in Eq. (rgcn).
  *   - Gradients are overwritten, unless desc.flags carries RGNN_FLAG_ACCUMULATE (then every gradient output of

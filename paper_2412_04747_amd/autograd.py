@@ -19,7 +19,7 @@ from .harness import Graph, _buf, _stream
 
 
 def _bufs(graph, layer, desc, key):
-    """(workspace, saved size) for a layer configuration on a graph.  The workspace lives in
+    """(workspace, (forward size, saved size)) for a layer configuration on a graph.  The workspace lives in
     `graph.workspaces` (sized by rgnn_workspace_bytes for this very graph), so it can neither outlive
     the graph nor be handed to another one."""
     if graph.handle is None:
@@ -27,16 +27,18 @@ def _bufs(graph, layer, desc, key):
     k = (layer,) + key
     if k not in graph.workspaces:
         f, b, s = B.rgnn_workspace_bytes(graph.handle, layer, desc)
-        graph.workspaces[k] = (_buf(max(f, b)), s)
+        graph.workspaces[k] = (_buf(max(f, b)), (f, s))
     return graph.workspaces[k]
 
 
 def _room(graph, layer, desc, key, keep):
-    """(workspace, saved) of a forward call; keep: a backward may follow."""
-    ws, s = _bufs(graph, layer, desc, key)
+    """(workspace, saved) of a forward call; keep: a backward may follow.  A call that keeps nothing takes the graph's workspace where
+    it holds what `saved` would as well (RGCN's forward size covers that), otherwise one for its duration."""
+    ws, (f, s) = _bufs(graph, layer, desc, key)
     if keep:
         return ws, _buf(s) if s else None
-    return (_buf(ws.numel() + 256 + s) if s else ws), None
+    need = f if layer == B.RGNN_LAYER_RGCN else (f + 255) // 256 * 256 + s
+    return (ws if ws.numel() >= need else _buf(need)), None
 
 
 def release(graph):
@@ -107,7 +109,7 @@ class _Hgt(torch.autograd.Function):
         X, Wk, Wq, Wv, Wo, Watt, Wmsg, mu = (_f32(t) for t in (X, Wk, Wq, Wv, Wo, Watt, Wmsg, mu))
         d, H = Wk.shape[-1], Watt.shape[1]
         desc = B.make_desc(B.RGNN_F32, d, d, H)
-        ws, s = _bufs(graph, B.RGNN_LAYER_HGT, desc, (d, H))
+        ws, (_, s) = _bufs(graph, B.RGNN_LAYER_HGT, desc, (d, H))
         out = torch.empty(graph.N, d, device=X.device)
         saved = _buf(s)
         B.rgnn_hgt_fwd(graph.handle, desc, X, Wk, Wq, Wv, Wo, Watt, Wmsg, mu, out, saved, ws, _stream())
@@ -129,12 +131,13 @@ class _Hgt(torch.autograd.Function):
 
 def rgat(graph, X, W, w_s, w_t, slope=0.2, heads=1):
     """RGAT layer (listing of the single-headed RGAT layer in the thesis; with heads > 1 each head
-    works on its slice of the d columns): out [N, d]."""
+    works on its slice of the d columns): out [N, d].  On a large graph a call outside grad mode may take another plan
+    than one inside: the two agree up to rounding."""
     return _Rgat.apply(graph, torch.is_grad_enabled(), float(slope), int(heads), X, W, w_s, w_t)
 
 
 def rgcn(graph, X, W, W0=None, norm="in_degree_per_rel", act="none"):
-    """RGCN layer, Eq. (rgcn): out [N, d]."""
+    """RGCN layer, Eq. (rgcn): out [N, d].  Inside and outside grad mode as with `rgat`."""
     return _Rgcn.apply(graph, torch.is_grad_enabled(), norm, act, X, W, W0)
 
 

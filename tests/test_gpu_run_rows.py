@@ -450,6 +450,31 @@ def test_replays(layer, dtype):
     g.close()
 
 
+@pytest.mark.parametrize("layer,d", [("rgat", 64), ("rgat", 128), ("rgcn", 64), ("rgcn", 128)])
+def test_memory_of_a_forward_without_gradients(layer, d):
+    """Beside the graph's workspace: out, and what RGAT would have saved with its forward scratch; for RGCN nothing else."""
+    import torch
+    from paper_2412_04747_amd import autograd as A
+    from paper_2412_04747_amd import binding as B
+    N, R, src, dst, rel, _ = _graph(17, 300007)
+    g = A.Graph(N, R, src, dst, rel)
+    conv = A.RgatConv(R, d) if layer == "rgat" else A.RgcnConv(R, d)
+    X = torch.randn(N, d, device="cuda")
+    f, _, s = B.rgnn_workspace_bytes(g.handle, *((B.RGNN_LAYER_RGAT, B.make_desc(d_in=d, d_out=d)) if layer == "rgat" else
+                                                 (B.RGNN_LAYER_RGCN, B.make_desc(d_in=d, d_out=d, norm=B.RGNN_NORM_IN_DEGREE_PER_REL))))
+    with torch.no_grad():
+        conv(g, X)
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        conv(g, X)
+        more = torch.cuda.max_memory_allocated() - before
+    print(f"run rows memory {layer} {d}: {more} bytes, out {4 * N * d}, forward {f}, saved {s}", flush=True)
+    assert s > 0 and more <= 4 * N * d + (f + s if layer == "rgat" else 0) + (1 << 20)
+    g.close()
+
+
 @pytest.mark.parametrize("layer,d", [("rgat", 64), ("rgat", 128), ("rgcn", 64)])
 def test_autograd_without_gradients(layer, d):
     """A forward of the autograd front end that no backward follows keeps nothing and gives the same result up to rounding."""
