@@ -199,9 +199,11 @@ struct BlockPlan {
     int32_t num_partials = 0;
     std::vector<int32_t> beg, end, row, slot, split_row, split_ptr;
 };
-// Blocks for N nodes: of kNodeBlock, or larger ones so that the (relation, block) cells hold some entries on average.
+// Blocks for N nodes: as many for every chiplet, of kNodeBlock or smaller, or larger ones so that the (relation, block) cells hold some
+// entries on average.
 inline int node_blocks(int64_t N, int32_t R, int64_t entries) {
-    return (int)std::max<int64_t>(std::min<int64_t>((N + kNodeBlock - 1) / kNodeBlock, entries / 64 / std::max(R, 1)), 1);
+    const int64_t want = (N + kChiplets * kNodeBlock - 1) / (kChiplets * kNodeBlock), most = entries / 64 / std::max(R, 1) / kChiplets;
+    return (int)std::max<int64_t>(std::min(want, most), 1) * kChiplets;
 }
 inline int block_cut(int64_t entries, int cus) { return (int)std::min<int64_t>(std::max<int64_t>(entries / (16 * cus), 256), 1024); }
 inline BlockPlan plan_blocks(const std::vector<int32_t>& bound, int32_t R, int B, int cut) {

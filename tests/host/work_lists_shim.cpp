@@ -49,6 +49,7 @@ int wl_tiles_field(int which, int32_t* out, int cap) {
 void wl_tiles_scalars(int32_t* out3) {
     out3[0] = g_tiles.num_chunks; out3[1] = g_tiles.num_slots; out3[2] = g_tiles.num_segs;
 }
+int wl_node_blocks(long long N, int R, long long entries) { return rgnn::node_blocks(N, R, entries); }
 int wl_plan_blocks(const int32_t* bound, int R, int B, int cut) {
     const rgnn::BlockPlan p = rgnn::plan_blocks(std::vector<int32_t>(bound, bound + (size_t)R * (B + 1)), R, B, cut);
     g_items = rgnn::ItemPlan{};

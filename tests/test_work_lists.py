@@ -336,6 +336,22 @@ def test_blocks_cover_each_relation_once(wl, R, B, cut, mean):
     assert np.all(written == 1) and len(of_slot) == split_ptr[-1]
 
 
+@pytest.mark.parametrize("N,R", [(5, 3), (1500, 8), (8192, 8), (14500, 20), (25000, 400), (94000, 20), (200000, 60), (1 << 20, 200)])
+def test_blocks_give_every_chiplet_its_share(wl, N, R):
+    """Nodes as likely as each other: an eighth of the entries for every chiplet, however few the nodes, and a tenth of that more at most."""
+    rng = np.random.default_rng(N)
+    E = 300000
+    key = np.sort(rng.integers(0, R * N, E))
+    B = wl.wl_node_blocks(C.c_longlong(N), R, C.c_longlong(E))
+    first = -(-N * np.arange(B + 1) // B)                    # first node of each block
+    bound = np.searchsorted(key, np.arange(R)[:, None] * N + first[None]).astype(np.int32)
+    wl.wl_plan_blocks(bound.ctypes.data_as(C.c_void_p), R, B, 256)
+    beg, end = (_field(wl.wl_items_field, i) for i in range(2))
+    share = np.bincount(np.arange(len(beg)) % 8, weights=end - beg, minlength=8) / E
+    assert B % 8 == 0 and abs(share.sum() - 1) < 1e-9
+    assert share.max() <= 1.1 / 8 or N < 8, share
+
+
 @pytest.mark.parametrize("E,d,R,rows,want", [
     (131071, 128, 1, 0.6, "000"), (131072, 128, 1, 0.6, "110"), (131072, 128, 1, 0.96, "000"), (240000, 32, 8, 0.6, "000"), (250000, 32, 8, 0.6, "100"),
     (269999, 64, 8, 0.6, "100"), (270000, 64, 8, 0.6, "110"), (1079999, 64, 8, 0.6, "110"), (1080000, 64, 8, 0.6, "111"), (8499999, 32, 400, 0.6, "100"),
