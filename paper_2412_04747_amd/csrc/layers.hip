@@ -291,43 +291,51 @@ size_t carve_rgat_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* b
 // ---- RGCN buffers -----------------------------------------------------------------------
 // Rows per run: A[m] = the mean (sum) of the input rows of the m-th run with several edges; Hs holds a message row per run.
 struct RgcnFwdWs { void* Hs; float* partial; float* A; };
-inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, d->flags); }
-// (whatever the flags: the backward may carry others than its forward)
-inline bool rgcn_keeps_sums(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) { return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, 0); }
-size_t carve_rgcn_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, float** A) {
+// A forward that is one launch goes with rows per pair in the backward: for rows per run it would have to form the sums as well.  Forward +
+// backward, us, pairs / runs: 3000 nodes, 4 relations, 260k edges, 32 x 32 35 / 44, 64 x 64 47 / 65; 2000, 8, 140k, 64 x 64 41 / 53; 2000, 16, 300k,
+// 32 x 64 47 / 52 (but 80 destinations, 8 relations, 140k edges, 64 x 64 67 / 56).  loop: with a self-loop.
+inline bool rgcn_small(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop, uint32_t flags) {
+    return sched_rgcn_small(d->dtype, d->d_in, d->d_out, loop, g->Q, g->N, g->dst_items.num_split > 0, g->longest_chain.runs, g->longest_chain.edges, flags);
+}
+// Whether `saved` holds the sums; whatever the flags: the backward may carry others than its forward.
+inline bool rgcn_keeps_sums(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop) {
+    return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, 0) && !rgcn_small(g, d, loop, 0);
+}
+inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop) { return sched_use_run_rows(rgcn_keeps_sums(g, d, loop), d->flags); }
+size_t carve_rgcn_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop, void* base, float** A) {
     Carver c(base);
-    if (rgcn_keeps_sums(g, d)) *A = c.take<float>((size_t)g->num_multi_runs * d->d_in);
+    if (rgcn_keeps_sums(g, d, loop)) *A = c.take<float>((size_t)g->num_multi_runs * d->d_in);
     return c.off;
 }
 struct RgcnBwdWs { float* A; void* dPre; float* dPre32; void* G; void* dXp; float* dX0; float* tl_part; float* loop_part; float* partial; float* acc_dW; float* acc_dW0; };
 
-size_t carve_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgcnFwdWs* w) {
+size_t carve_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop, void* base, RgcnFwdWs* w) {
     Carver c(base);
     // (a call without `saved` may take either plan and has to keep A here)
-    const bool runs = rgcn_run_rows(g, d);
+    const bool runs = rgcn_run_rows(g, d, loop);
     w->Hs = c.rows((size_t)(runs ? std::max(g->P, g->Q) : g->P) * d->d_out, rows_bf16(d));
     w->partial = c.take<float>(std::max({(size_t)g->dst_items.num_partials * d->d_out, runs ? (size_t)g->dstrun_items.num_partials * d->d_out : 0,
-                                         rgcn_keeps_sums(g, d) ? (size_t)g->multi_run_items.num_partials * d->d_in : 0}));
+                                         rgcn_keeps_sums(g, d, loop) ? (size_t)g->multi_run_items.num_partials * d->d_in : 0}));
     w->A = runs ? c.take<float>((size_t)g->num_multi_runs * d->d_in) : nullptr;
     return c.off;
 }
 // RGCN with a self-loop, fp32 up to width 64: its backward runs with the pairs', where the pairs' chunks are one per compute unit
 // (see Chunkings; with many short relations they stay apart).
 inline bool rgcn_loop_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
-    if (rgcn_run_rows(g, d)) return d->d_in <= 64 && d->d_out <= 64 && run_chunks(g, d->d_out).f32_bwd == &g->run_tiles_cu1;
+    if (rgcn_run_rows(g, d, true)) return d->d_in <= 64 && d->d_out <= 64 && run_chunks(g, d->d_out).f32_bwd == &g->run_tiles_cu1;
     return d->d_in <= 64 && d->d_out <= 64 && pair_chunks(g, d->d_out).f32_bwd == &g->pair_tiles_cu1;
 }
-size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgcnBwdWs* w) {
+size_t carve_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop, void* base, RgcnBwdWs* w) {
     Carver c(base);
     const bool h = rows_bf16(d), relu = d->activation == RGNN_ACT_RELU;
     w->dPre = c.rows(relu ? (size_t)g->N * d->d_out : 0, h);
     w->dPre32 = c.take<float>(relu && h ? (size_t)g->N * d->d_out : 0);   // fp32 copy for the self-loop kernels
-    const bool runs = rgcn_run_rows(g, d);
+    const bool runs = rgcn_run_rows(g, d, loop);
     w->G = runs ? nullptr : c.rows((size_t)g->P * d->d_out, h);
     w->dXp = c.rows((size_t)(runs ? g->Q : g->P) * d->d_in, h);        // (a row per run or per pair)
     w->A = runs ? c.take<float>((size_t)g->num_multi_runs * d->d_in) : nullptr;
     w->dX0 = c.take<float>((size_t)g->N * d->d_in);
-    const bool with_loop = rgcn_loop_bwd(g, d);
+    const bool with_loop = loop && rgcn_loop_bwd(g, d);
     w->tl_part = c.take<float>(std::max(tl_bwd_scratch(h, runs ? run_chunks(g, d->d_out) : pair_chunks(g, d->d_out), d->d_in, d->d_out),
                                         with_loop ? typed_linear_bwd_scratch_floats(d->d_in, d->d_out, runs ? g->run_tiles_loop : g->pair_tiles_loop) : 0));
     w->loop_part = c.take<float>(std::max(typed_linear_bwd_scratch_floats(d->d_in, d->d_out, g->all_tiles_cu1),
@@ -538,10 +546,12 @@ extern "C" rgnn_status_t rgnn_workspace_bytes(const rgnn_graph_t* g, int32_t lay
             for (bool kept : {true, false}) s = std::max(s, carve_rgat_run_saved(g, desc, nullptr, &rs, kept));
     } else if (layer == RGNN_LAYER_RGCN) {
         RgcnFwdWs fw; RgcnBwdWs bw;
-        f = carve_rgcn_fwd(g, desc, nullptr, &fw);
-        b = carve_rgcn_bwd(g, desc, nullptr, &bw);
         float* A;
-        s = carve_rgcn_saved(g, desc, nullptr, &A);
+        for (bool loop : {false, true}) {
+            f = std::max(f, carve_rgcn_fwd(g, desc, loop, nullptr, &fw));
+            b = std::max(b, carve_rgcn_bwd(g, desc, loop, nullptr, &bw));
+            s = std::max(s, carve_rgcn_saved(g, desc, loop, nullptr, &A));
+        }
     } else {
         HgtFwdWs fw; HgtBwdWs bw; HgtSaved sv;
         f = carve_hgt_fwd(g, desc, nullptr, &fw);
@@ -597,24 +607,23 @@ extern "C" rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_d
     const bool bf16 = desc->dtype == RGNN_BF16, h = rows_bf16(desc), relu = desc->activation == RGNN_ACT_RELU;
     const void* X16 = bf16 ? X : nullptr;
     const void* W16 = bf16 ? W : nullptr;
-    Bf16Stage stg(workspace, carve_rgcn_fwd(g, desc, workspace, &w), bf16, st);
+    Bf16Stage stg(workspace, carve_rgcn_fwd(g, desc, W0 != nullptr, workspace, &w), bf16, st);
     // fp32 copies for the fp32 kernels: everything below width 128, only the self-loop operands at 128
     const float* X32 = (!h || W0) ? stg.in(X, (size_t)g->N * desc->d_in) : nullptr;
     const float* W32 = !h ? stg.in(W, (size_t)g->R * desc->d_in * D) : nullptr;
     const float* W032 = stg.in(W0, (size_t)desc->d_in * D);
     RGNN_TRY(stg.status);
-    // What the backward reads is left in `saved` whichever plan the forward takes: the backward cannot tell.
-    const bool runs = rgcn_run_rows(g, desc) && (saved || sched_run_rows_infer(g->E, D));
+    // What the backward reads is left in `saved` whatever the flags: the backward cannot tell.
+    const bool runs = rgcn_run_rows(g, desc, W0) && (saved || sched_run_rows_infer(g->E, D));
     float* A = w.A;
-    if (saved && rgcn_keeps_sums(g, desc)) {
-        (void)carve_rgcn_saved(g, desc, saved, &A);
+    if (saved && rgcn_keeps_sums(g, desc, W0)) {
+        (void)carve_rgcn_saved(g, desc, W0, saved, &A);
         RGNN_TRY(rgcn_run_inputs(g, desc, X32, A, w.partial, st));
     }
     // (one launch: rows of out are written while others of X are still read, so an out that shares memory with X goes to the
     // general plan, which has read X by then unless there is a self-loop)
     if (!overlap(X, (size_t)g->N * desc->d_in * sizeof(float), out, (size_t)g->N * D * sizeof(float)) &&
-        sched_rgcn_small(desc->dtype, desc->d_in, D, W0 != nullptr, g->Q, g->N, g->dst_items.num_split > 0, g->longest_chain.runs,
-                         g->longest_chain.edges, desc->flags))
+        rgcn_small(g, desc, W0, desc->flags))
         return rgcn_small_fwd(g, desc->d_in, D, X32, W32, W032, desc->norm == RGNN_NORM_IN_DEGREE_PER_REL, relu, static_cast<float*>(out), st);
     if (runs) {
         // The sum over a run's edges comes before the product: a row of messages per run, not per pair, and a run with one edge reads its
@@ -660,7 +669,7 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
     RgcnBwdWs w;
     const bool bf16 = desc->dtype == RGNN_BF16, h = rows_bf16(desc), relu = desc->activation == RGNN_ACT_RELU;
     const void* W16 = bf16 ? W : nullptr;
-    Bf16Stage stg(workspace, carve_rgcn_bwd(g, desc, workspace, &w), bf16, st);
+    Bf16Stage stg(workspace, carve_rgcn_bwd(g, desc, W0 != nullptr, workspace, &w), bf16, st);
     const float* X32 = (!h || W0) ? stg.in(X, (size_t)g->N * K) : nullptr;
     const float* W32 = !h ? stg.in(W, (size_t)g->R * K * D) : nullptr;
     const float* W032 = stg.in(W0, (size_t)K * D);
@@ -680,11 +689,11 @@ extern "C" rgnn_status_t rgnn_rgcn_bwd(const rgnn_graph_t* g, const rgnn_layer_d
         dPre = w.dPre;
         dPre32 = both ? w.dPre32 : h ? nullptr : static_cast<const float*>(w.dPre);
     }
-    const bool runs = rgcn_run_rows(g, desc);
+    const bool runs = rgcn_run_rows(g, desc, W0);
     const float* A = w.A;
     if (runs && saved) {
         float* kept = nullptr;
-        (void)carve_rgcn_saved(g, desc, const_cast<void*>(saved), &kept);
+        (void)carve_rgcn_saved(g, desc, W0, const_cast<void*>(saved), &kept);
         A = kept;
     } else if (runs) {
         RGNN_TRY(rgcn_run_inputs(g, desc, X32, w.A, w.partial, st));

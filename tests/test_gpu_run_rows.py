@@ -94,7 +94,7 @@ def test_rgcn(k, d, dtype, norm, act, loop, flags, saved):
     (3000, 4, 200000, 2500, 64, 64, False), (2000, 8, 140000, 1000, 32, 64, True), (3000, 4, 260000, 1500, 32, 32, False),
     (3000, 4, 260000, 1500, 64, 32, True), (6080, 8, 140000, 80, 64, 64, True)])
 def test_rgcn_of_few_destinations(N, R, E, dsts, k, d, loop):
-    """Rows per run whose forward is the one launch of a small graph: it leaves the sums that the backward reads as well."""
+    """Graphs with fewer runs than pairs whose forward is the one launch of a small graph: its backward needs nothing of `saved`."""
     import torch
     from paper_2412_04747_amd import binding as B
     from paper_2412_04747_amd.harness import Graph, RgcnLayer
@@ -116,7 +116,7 @@ def test_rgcn_of_few_destinations(N, R, E, dsts, k, d, loop):
     want = O.rgcn_bwd(*a, p["dOut"])
     for n, v in L.grads().items():
         check(v, want[n], TOL_F32, n)
-    assert "rgcn_small_fwd" in rep and rep["run_inputs"][0] == 1 and "aggregate_bwd_pair" not in rep
+    assert "rgcn_small_fwd" in rep and "run_inputs" not in rep and "aggregate_bwd_pair" in rep
     g.close()
 
 
