@@ -224,6 +224,7 @@ static rgnn_status_t build(rgnn_graph* g, int format, const int32_t* a, const in
     }
     for (int64_t q = 0; q < g->Q; ++q) g->num_single_runs += run_ptr[q + 1] - run_ptr[q] == 1;
     g->num_multi_runs = g->Q - g->num_single_runs;
+    g->rows_saved = 7 * (g->P - g->Q) - 2 * (g->num_single_pairs - g->num_single_runs);
     g->run_rows = sched_run_rows(g->E, g->P, g->num_single_pairs, g->Q, g->num_single_runs);
     if (g->run_rows) {
         number.resize((size_t)g->Q);

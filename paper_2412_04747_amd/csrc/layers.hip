@@ -178,11 +178,11 @@ struct RgatRunBwdWs {
     float* dH; float* weight; float* rowdot; float* stat; float* dz; float* ds_dst; float* ds_src; float* A; float* U; float* tl_part; float* partial; float* a_partial;
     float* u_partial; float* acc_dW; float* acc_dws; float* acc_dwt;
 };
-inline bool rgat_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
-    return sched_rgat_run_rows(g->run_rows, d->heads, g->R, g->E, d->d_out, d->flags);
-}
 inline bool rgat_keeps_runs(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
-    return sched_rgat_run_rows(g->run_rows, d->heads, g->R, g->E, d->d_out, 0);
+    return sched_rgat_run_rows(g->run_rows, d->heads, g->R, g->E, d->d_out, 0) && sched_run_widths(d->d_in, d->d_out, g->E, g->rows_saved);
+}
+inline bool rgat_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d) {
+    return sched_use_run_rows(rgat_keeps_runs(g, d), d->flags);
 }
 // kept: s_dst and ms lie where the rows per pair have them, with Y and A in the place of Hs as far as they fit
 size_t carve_rgat_run_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, void* base, RgatRunSaved* s, bool kept) {
@@ -299,7 +299,8 @@ inline bool rgcn_small(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool l
 }
 // Whether `saved` holds the sums; whatever the flags: the backward may carry others than its forward.
 inline bool rgcn_keeps_sums(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop) {
-    return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, 0) && !rgcn_small(g, d, loop, 0);
+    return !rows_bf16(d) && sched_rgcn_run_rows(g->run_rows, g->E, d->d_out, 0) && sched_run_widths(d->d_in, d->d_out, g->E, g->rows_saved) &&
+           !rgcn_small(g, d, loop, 0);
 }
 inline bool rgcn_run_rows(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop) { return sched_use_run_rows(rgcn_keeps_sums(g, d, loop), d->flags); }
 size_t carve_rgcn_saved(const rgnn_graph_t* g, const rgnn_layer_desc_t* d, bool loop, void* base, float** A) {

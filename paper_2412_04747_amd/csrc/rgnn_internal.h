@@ -150,6 +150,7 @@ struct rgnn_graph {
     // several edges before one, destination) order.
     bool run_rows = false;
     int64_t num_multi_runs = 0, num_single_runs = 0;
+    int64_t rows_saved = 0;                // by rows per run over a training step (schedule.h)
     int32_t* run_tag = nullptr;            // [Q] the run, with the top bit set when it has several edges
     int32_t* multi_run = nullptr;          // [num_multi_runs] run of each number
     int32_t* row_in = nullptr;             // [Q] by row: source of the run's only edge, or the top bit | number of the run among those

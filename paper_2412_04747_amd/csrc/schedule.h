@@ -58,6 +58,11 @@ inline bool sched_row_select(int layer, int dtype, int d, int heads, int R, int6
 inline bool sched_run_rows(int64_t edges, int64_t pairs, int64_t single_pairs, int64_t runs, int64_t single_runs) {
     return edges >= (1 << 17) && 20 * (7 * runs - 2 * single_runs) <= 19 * (7 * pairs - 2 * single_pairs);
 }
+// Rows per run walk the edges over rows of the input width, rows per pair over those of the output width, so with narrower outputs the rows
+// saved (of the formula above) have to make up for the edges' longer ones.  64 -> 32, forward + backward, pairs / runs by rows saved per edge:
+// RGCN 0.81 to 0.87 of the time at 0.03 to 0.2 from 1.25M edges on, 0.93 to 0.95 at 0.37 to 0.43, 0.98 to 1.03 at 0.48 to 0.74, 1.0 to 1.3
+// above; RGAT 0.89 to 1.01 up to 0.42, 0.96 to 1.04 at 0.5 to 0.75, 1.0 to 1.18 above.  (32 -> 64: 1.05 to 1.6 throughout.)
+inline bool sched_run_widths(int d_in, int d_out, int64_t edges, int64_t rows_saved) { return d_in <= d_out || 20 * rows_saved >= 9 * edges; }
 // The calls that take them.  Every flag but the accumulation of gradients asks for an alternative of the rows per pair.
 inline bool sched_use_run_rows(bool lists, uint32_t flags) { return lists && !(flags & ~(uint32_t)RGNN_FLAG_ACCUMULATE); }
 inline bool sched_rgcn_run_rows(bool lists, int64_t edges, int d, uint32_t flags) { return sched_use_run_rows(lists, flags) && edges * d >= 8000000; }

@@ -307,6 +307,41 @@ def test_rgat_edges_alone_in_their_destination(d, flags):
     g.close()
 
 
+@pytest.mark.parametrize("layer", ["rgat", "rgcn"])
+@pytest.mark.parametrize("k,d,N,runs", [(64, 32, 30000, False), (32, 64, 30000, True), (64, 32, 80000, True)])
+def test_widths_that_differ(layer, k, d, N, runs):
+    """Narrower outputs on a graph of 20 edges per node, where rows per run save a seventh of a row per edge, and of 7.5, where they save
+    two thirds; wider ones."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer, RgcnLayer
+    R, E = 4, 600000
+    rng = np.random.default_rng(k + N)
+    src, rel = rng.integers(0, N, E).astype(np.int32), rng.integers(0, R, E).astype(np.int32)
+    dst = (N * rng.random(E) ** 3).astype(np.int32)
+    print(f"run rows {layer} {k}->{d} N={N}", flush=True)
+    g = Graph(N, R, src, dst, rel)
+    single = [int((np.diff(g.export(n)) == 1).sum()) for n in ("out_ptr", "run_ptr")]
+    saved = (7 * (g.P - g.Q) - 2 * (single[0] - single[1])) / E
+    assert saved < 0.2 if N == 30000 else saved > 0.6
+    if layer == "rgat":
+        p = synth.rgat_params(rng, N, R, k, d)
+        L = RgatLayer(g, d, d_in=k)
+        L.load(p["X"], p["W"], p["w_s"], p["w_t"])
+        want = O.rgat_fwd(N, src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"])
+    else:
+        p = synth.rgcn_params(rng, N, R, k, d)
+        L = RgcnLayer(g, d, d_in=k)
+        L.load(p["X"], p["W"])
+        want = O.rgcn_fwd(N, src, dst, rel, p["X"], p["W"])
+    B.rgnn_profile_start()
+    L.fwd()
+    torch.cuda.synchronize()
+    assert ("run_inputs" in B.rgnn_profile_stop()) == runs
+    check(L.out, want, TOL_F32, "out")
+    g.close()
+
+
 @pytest.mark.parametrize("layer,d,flags", [("rgat", 64, 0), ("rgat", 64, 32), ("rgat", 128, 0), ("rgcn", 64, 0)])
 def test_input_gradient_over_the_input(layer, d, flags):
     """dX written over X: the same bits as in a buffer of its own (with flags: added to what that holds)."""
