@@ -69,13 +69,18 @@ inline bool sched_rgcn_run_rows(bool lists, int64_t edges, int d, uint32_t flags
 // RGCN forwards that keep nothing for a backward: the saving has to come from the forward alone.  Pairs / runs, us: 300k edges, 60
 // relations, width 32 34 / 46, 64 59 / 64, 128 129 / 109; 1M 75 / 73, 145 / 124, 340 / 266.
 inline bool sched_run_rows_infer(int64_t edges, int d) { return edges * d >= 30000000; }
+// Workgroups that finish the parameter gradients of RGAT (traversal.hip), and how many go with run_term's (512 threads each).
+inline int64_t finish_blocks(int R, int d_in, int d) { return (int64_t)R * (d / 32 + (d_in * d + 1023) / 1024); }
+constexpr int64_t kMaxFinishBlocks = 1 << 22;
 // RGAT with one head.  The walks look the relations' folded vectors up, once per run or edge, so more relations move the line out, and at
 // width 32 the indices outweigh the rows.  Forward + backward, us, pairs / runs, at 7 Q - 2 Q1 from 0.54 to 0.72 of 7 P - 2 P1: 8 relations,
 // width 64 173 / 152 at 300k edges, 1108 / 798 at 3M, 128 178 / 162 at 140k, 463 / 338 at 550k; 60 relations, 64 300 / 260 at 550k, 1317 / 990 at 3M, 128
 // 213 / 217 at 140k, 352 / 306 at 300k, 2873 / 1930 at 3M, 32 175 / 182 at 550k, 307 / 292 at 1.2M; 400 relations, 64 396 / 440 at 550k, 683 / 683
 // at 1.2M, 1533 / 1380 at 3M, 128 451 / 485 at 300k, 1394 / 1220 at 1.2M, 32 788 / 838 at 3M.
+// Not with so many relations that the workgroups which finish their gradients in run_term's launch would leave few of the 2^32 lanes of a grid.
 inline bool sched_rgat_run_rows(bool lists, int heads, int R, int64_t edges, int d, uint32_t flags) {
-    return heads == 1 && sched_use_run_rows(lists, flags) && edges * d >= 16000000 + (int64_t)R * (d < 64 ? 640000 : 160000);
+    return heads == 1 && sched_use_run_rows(lists, flags) && edges * d >= 16000000 + (int64_t)R * (d < 64 ? 640000 : 160000) &&
+           finish_blocks(R, d, d) <= kMaxFinishBlocks;
 }
 // ... and for forwards that keep nothing for a backward, where the softmax within the runs is paid and the cheaper backward is not there.  Pairs / runs
 // as a ratio: width 64 1.04 and 1.02 (8 and 60 relations, 1.2M and 3M edges), 0.99 and 0.90 at 550k, 400 relations 0.90 at 3M; 128 1.11 and 1.08 at

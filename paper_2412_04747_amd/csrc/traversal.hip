@@ -1562,7 +1562,7 @@ rgnn_status_t node_grad_sum(const rgnn_graph* g, int D, const void* dXp, const f
                             const float* extra, void* dX, hipStream_t st, int in_bf16, int out_bf16, int heads,
                             const void* dXp2, const RgatFinish* finish) {
     RgatFinish fin = finish ? *finish : RgatFinish{};
-    const int64_t fin_blocks = finish ? (int64_t)fin.R * (fin.nd / 32 + (fin.kd * fin.nd + 1023) / 1024) : 0;
+    const int64_t fin_blocks = finish ? finish_blocks(fin.R, fin.kd, fin.nd) : 0;
     if (fin_blocks > INT32_MAX / 2) RGNN_FAIL(RGNN_EUNSUPPORTED, "node_grad_sum: the parameter gradients of %d relations are too many", fin.R);
     fin.blocks = (int)fin_blocks;
     if (finish && !ds_dst) RGNN_FAIL(RGNN_EINVAL, "node_grad_sum: the parameter gradients go with the run term");
@@ -1607,8 +1607,8 @@ static rgnn_status_t launch_run_term(const rgnn_graph* g, const float* ds_dst, c
     return RGNN_OK;
 }
 rgnn_status_t rgat_run_term(const rgnn_graph* g, int D, const float* ds_dst, const float* wtp, float* dX, RgatFinish fin, hipStream_t st) {
-    const int64_t blocks = (int64_t)fin.R * (fin.nd / 32 + (fin.kd * fin.nd + 1023) / 1024);
-    if (blocks > 1 << 22) RGNN_FAIL(RGNN_EUNSUPPORTED, "run term: the parameter gradients of %d relations are too many", fin.R);
+    const int64_t blocks = finish_blocks(fin.R, fin.kd, fin.nd);
+    if (blocks > kMaxFinishBlocks) RGNN_FAIL(RGNN_EUNSUPPORTED, "run term: the parameter gradients of %d relations are too many", fin.R);
     fin.blocks = (int)blocks;
     KernelTimer kt(st, "run_term");
     if (sched_ws_in_lds(g->R, D)) RGNN_DISPATCH_D(D, return (launch_run_term<DD, true>(g, ds_dst, wtp, dX, fin, st)));

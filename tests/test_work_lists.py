@@ -355,7 +355,8 @@ def test_blocks_give_every_chiplet_its_share(wl, N, R):
 @pytest.mark.parametrize("E,d,R,rows,want", [
     (131071, 128, 1, 0.6, "000"), (131072, 128, 1, 0.6, "110"), (131072, 128, 1, 0.96, "000"), (240000, 32, 8, 0.6, "000"), (250000, 32, 8, 0.6, "100"),
     (269999, 64, 8, 0.6, "100"), (270000, 64, 8, 0.6, "110"), (1079999, 64, 8, 0.6, "110"), (1080000, 64, 8, 0.6, "111"), (8499999, 32, 400, 0.6, "100"),
-    (8500000, 32, 400, 0.6, "110"), (2499999, 128, 400, 0.6, "110"), (2500000, 128, 400, 0.6, "111"), (1 << 30, 64, 1 << 20, 0.6, "100")])
+    (8500000, 32, 400, 0.6, "110"), (2499999, 128, 400, 0.6, "110"), (2500000, 128, 400, 0.6, "111"), (1 << 30, 64, 1 << 20, 0.6, "100"),
+    (2000000000, 128, 209715, 0.6, "111"), (2000000000, 128, 209716, 0.6, "100"), (2000000000, 64, 700000, 0.6, "100")])
 def test_rows_per_run_where_they_pay(wl, E, d, R, rows, want):
     """RGCN, RGAT, and RGAT forwards that keep nothing."""
     pick_ = lambda layer, heads=1, flags=0: wl.wl_run_rows(C.c_longlong(E), C.c_longlong(E), C.c_longlong(E), C.c_longlong(int(rows * E)),
