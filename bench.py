@@ -509,8 +509,9 @@ def main():
         print(f"[bench] max relative error vs oracle: {parity}", file=sys.stderr, flush=True)
 
     half = c["dtype"] == "bf16" and d == 128
-    # rows per run instead of per pair: the library's pick on large graphs with fewer runs
-    runs = "run_inputs" in rep
+    # rows per run instead of per pair: the library's pick on large graphs with fewer runs (a call whose flags bring the rows per pair
+    # back leaves the runs' inputs in `saved` as well)
+    runs = "run_inputs" in rep and not {"single_logits", "aggregate_bwd_pair"} & set(rep)
     Q1 = int((np.unique(c["dst"].astype(np.int64) * R + c["rel"], return_counts=True)[1] == 1).sum()) if runs else 0
 
     def work(name):

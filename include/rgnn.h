@@ -249,9 +249,11 @@ rgnn_status_t rgnn_schedule(const rgnn_graph_t* g, int32_t layer, const rgnn_lay
  *   dW [R, d_in, d_out], dW0 [d_in, d_out] (ignored when W0 is NULL).  `out` is the
  *   forward result (read only when activation != NONE).
  * On a large graph with fewer (destination, relation) runs than (source, relation) pairs, with rows in fp32, a forward of more than
- * one launch and no desc.flags but RGNN_FLAG_ACCUMULATE, the layer sums the inputs of a run before the product and keeps rows per run instead of per pair (the
- * row_select and pair fields of rgnn_schedule then describe the rows per pair that a flag brings back; the kernel run_inputs in
- * the timing report tells).  On such a graph `saved` holds the sums for the backward call, also with flags; with saved == NULL there, whether or not the forward had one, the backward forms them again.
+ * one launch and no desc.flags but RGNN_FLAG_ACCUMULATE, the layer sums the inputs of a run before the product and keeps rows per run
+ * instead of per pair (the row_select and pair fields of rgnn_schedule then describe the rows per pair that a flag brings back; the
+ * kernel run_inputs in the timing report tells).  With RGNN_NORM_NONE such a sum has to be in the range of fp32, where rows per pair ask
+ * that of the messages and their sum.  On such a graph `saved` holds the sums for the backward call, also with flags; with saved == NULL
+ * there, whether or not the forward had one, the backward forms them again.
  */
 rgnn_status_t rgnn_rgcn_fwd(const rgnn_graph_t* g, const rgnn_layer_desc_t* desc, const void* X, const void* W,
                             const void* W0, void* out, void* saved, void* workspace, void* stream);

@@ -301,6 +301,7 @@ __device__ __forceinline__ void fwd_single(const FusedArgs& a, const float* ws_l
         float z = leaky(group_sum<LPH>(dot4(h[u], w)) + sd[u], a.slope);
         if (MODE == kRuns && pr[u] < 0) z = sd[u];
         if (i0 + u < a.single_n) {
+            if (MODE == kRuns && !(rw[u] > 0.f)) h[u] = make_float4(NAN, NAN, NAN, NAN);     // a softmax of minus infinities
             *reinterpret_cast<float4*>(a.out + (size_t)orow[u] * D + c * 4) = h[u];
             if (MODE == kRuns && c == 0 && pr[u] >= 0) a.lq[j[u]] = make_float2(z, 1.f);
             if (c % LPH == 0) a.ms[(size_t)orow[u] * H + head] = make_float2(z, rw[u]);

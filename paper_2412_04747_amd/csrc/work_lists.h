@@ -200,7 +200,8 @@ struct BlockPlan {
     std::vector<int32_t> beg, end, row, slot, split_row, split_ptr;
 };
 // Blocks for N nodes: as many for every chiplet, of kNodeBlock or smaller, or larger ones so that the (relation, block) cells hold some
-// entries on average.
+// entries on average.  (8192 nodes, 100 relations, 600k edges of width 64: in one block the sums by relation take 62 us, in eight 14; 200k nodes,
+// 60 relations, width 128: in 25 blocks 108, in 32 87.)
 inline int node_blocks(int64_t N, int32_t R, int64_t entries) {
     const int64_t want = (N + kChiplets * kNodeBlock - 1) / (kChiplets * kNodeBlock), most = entries / 64 / std::max(R, 1) / kChiplets;
     return (int)std::max<int64_t>(std::min(want, most), 1) * kChiplets;

@@ -376,6 +376,38 @@ def test_input_gradient_over_the_input(layer, d, flags):
     g.close()
 
 
+@pytest.mark.parametrize("others", [0, 5000])
+def test_rgat_of_nothing_but_minus_infinity(others):
+    """Destinations all of whose logits are minus infinity, in one run of several edges: NaN, as a softmax gives, whether they are batched with
+    thousands of others of one run or not.  The rest of the graph knows nothing of it."""
+    import torch
+    from paper_2412_04747_amd import binding as B
+    from paper_2412_04747_amd.harness import Graph, RgatLayer
+    d = 64
+    N, R, src, dst, rel, rng = _graph(23, 290011)
+    at = N + np.arange(50 + others)                          # destinations of one run of three edges, the first 50 of the relation R
+    src = np.concatenate([src, rng.integers(0, N, 3 * len(at))]).astype(np.int32)
+    dst, rel = np.concatenate([dst, np.repeat(at, 3)]).astype(np.int32), np.concatenate([rel, np.where(np.repeat(at, 3) < N + 50, R, 0)]).astype(np.int32)
+    p = synth.rgat_params(rng, N + len(at), R + 1, d, d)
+    p["X"][:, 0] = 10
+    p["W"][R][:, 0] = np.eye(d)[0]
+    p["w_t"][R] = 0
+    p["w_t"][R][0] = -1e38
+    print(f"run rows rgat nothing but minus infinity, {others} others", flush=True)
+    g = Graph(N + len(at), R + 1, src, dst, rel)
+    L = RgatLayer(g, d)
+    L.load(p["X"], p["W"], p["w_s"], p["w_t"])
+    B.rgnn_profile_start()
+    L.fwd()
+    torch.cuda.synchronize()
+    assert "run_inputs" in B.rgnn_profile_stop()
+    assert L.out[N:N + 50].isnan().all()
+    want = O.rgat_fwd(N + len(at), src, dst, rel, p["X"], p["W"], p["w_s"], p["w_t"])
+    rest = np.r_[0:N, N + 50:N + len(at)]
+    check(L.out[torch.as_tensor(rest, device="cuda")], want[rest], TOL_F32, "out")
+    g.close()
+
+
 @pytest.mark.parametrize("n,fits", [(121, True), (160, False)])
 def test_rgat_forward_that_keeps_nothing(n, fits):
     """Runs of nine edges.  Rows per run, from a workspace and from the static scratch; where that holds the rows per pair only, those from both."""
