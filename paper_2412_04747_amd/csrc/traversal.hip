@@ -390,6 +390,7 @@ __device__ __forceinline__ void gather_general(const GatherArgs& a, int blk) {
             else load_cols(src + (size_t)row[u] * D + cv * V, v[u]);
             cc[u] = c[u];
             if (S2) s2 += c2[S2 ? u : 0];
+            if (sizeof(TI) == 4 && j + u >= e) zero_cols(v[u]);      // (it may be infinite: no weight 0)
         }
         if (j + 4 < e) {
             RGNN_GATHER_FETCH_IDX(j + 4)
@@ -460,7 +461,10 @@ __device__ __forceinline__ void gather_short(const GatherArgs& a, int blk, int f
         float acc[V];
         zero_cols(acc);
 #pragma unroll
-        for (int u = 0; u < kShortLen; ++u) fma_cols(acc, c[q][u], v[q][u]);
+        for (int u = 0; u < kShortLen; ++u) {
+            if (sizeof(TI) == 4 && b[q] + u >= e[q]) zero_cols(v[q][u]);
+            fma_cols(acc, c[q][u], v[q][u]);
+        }
         if (i0 + q < n) {
             if (R1) add_rank1<D>(a.r1, a.lanes_per_head, (size_t)orow[q], cv, acc);
             if (EX) add_row<D>(a.extra, (size_t)orow[q], cv, acc);
